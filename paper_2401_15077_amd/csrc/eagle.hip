@@ -115,6 +115,7 @@ struct eagle_ctx {
   // fast path (passes of <= 32 rows)
   float *h2, *PT2, *ssq1, *ssq2; int *cnt_gemm, *cnt_attn; size_t pt2_floats;
   bf16_t *xf2_d, *xf2_dB, *xf2_2d, *xf2_att, *xf2_ffn;
+  RowFact* facts;                      // [Mmax] rows of the pass in flight (written by its first kernel)
   float *moe_w, *xn; int* expert_used; int* experts_touched;   // (profiling) experts used, summed over the layers of a verify    // routing weights [E][largest pass], used flags [E], fp32 normalised rows (general path)
   int ssq1_groups = 0, ssq2_groups = 0;
   unsigned long long* trace = nullptr; int trace_sel = -1, gemm_no = 0, attn_trace_sel = -1, attn_no = 0, expand_trace = 0;   // profiling builds only
@@ -388,6 +389,7 @@ static size_t layout(eagle_ctx* c) {
   c->xf2_2d = a.take<bf16_t>((size_t)c->NXP * 32 * 2 * d);
   c->xf2_att = a.take<bf16_t>((size_t)c->NXP * 32 * H * dh);
   c->xf2_ffn = a.take<bf16_t>((size_t)c->NXP * 32 * F);
+  c->facts = a.take<RowFact>(Mm);
   c->ssq1 = a.take<float>(256 * 32); c->ssq2 = a.take<float>(256 * 32);
   c->trace = a.take<unsigned long long>(1024 * 8);
   c->cnt_gemm = a.take<int>(1024); c->cnt_attn = a.take<int>((size_t)128 * H);
@@ -882,8 +884,8 @@ static int head_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, bo
   const eagle_config& g = c->cfg;
   const int M = pass.rows_per_seq * pass.n_seq, MT = (M + 31) / 32;
   int rc, S;
-  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP);
-  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP);
+  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts);
+  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts);
   LAUNCH_CHECK();
   if ((rc = (c->cur_class = KC_FC, gemm(c, c->fc, c->xf_2d, MT, &S)))) return rc;
   const float* bias = c->loaded_layer[EAGLE_W_FC_BIAS][0] ? c->fc_bias : nullptr;
@@ -1091,7 +1093,8 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
 static Gemm2 gemm2_base(eagle_ctx* c, const Pass& pass, int M) {
   Gemm2 g;
   memset(&g, 0, sizeof(g));
-  g.M = M; g.pass = pass; g.tree = c->tree_d; g.st = c->st; g.d = c->cfg.d_model;
+  (void)pass;
+  g.M = M; g.facts = c->facts; g.d = c->cfg.d_model; g.in_scale.ssq = c->ssq1;   // (no row scale: groups stays 0)
   g.rope_cos = c->rope_cos; g.rope_sin = c->rope_sin; g.H = c->cfg.n_heads; g.kv_f32 = c->kv_f32; g.Q = c->Q;
   return g;
 }
@@ -1165,21 +1168,20 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
   return (c->cur_class = KC_DOWN, gemm2(c, w.dn, c->xf2_ffn, g, &c->ssq2_groups));
 }
 
-static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out, int out_kind, int only_last_row) {
+static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out) {
   Gemm2 g = gemm2_base(c, pass, M);
-  g.epi = EPI_LOGITS; g.logits = out; g.out_kind = out_kind; g.V = c->cfg.vocab; g.only_last_row = only_last_row;
+  g.epi = EPI_LOGITS; g.logits = out; g.V = c->cfg.vocab;
   if (scaled) g.in_scale = scale_of(c, c->ssq2, c->ssq2_groups);
   return (c->cur_class = KC_LMHEAD, gemm2(c, c->lm_head, c->xf2_d, g, nullptr));
 }
 
-static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new, float* logits_out, int out_kind,
-                           bool want_logits = true, int only_last_row = 0) {
+static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new, float* logits_out, bool want_logits = true) {
   const eagle_config& cf = c->cfg;
   const int M = pass.rows_per_seq * pass.n_seq, d = cf.d_model;
   int rc;
   const int eg = std::max(1, std::min(64, d / 64));
-  if (c->f32) k2_embed<float, 3><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const float*)c->embed, cf.vocab, M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2);
-  else k2_embed<bf16_t, 2><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const bf16_t*)c->embed, cf.vocab, M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2);
+  if (c->f32) k2_embed<float, 3><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const float*)c->embed, cf.vocab, M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2, kv_for(c, 0), c->facts);
+  else k2_embed<bf16_t, 2><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const bf16_t*)c->embed, cf.vocab, M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2, kv_for(c, 0), c->facts);
   LAUNCH_CHECK();
   c->ssq2_groups = eg;
   for (int l = 0; l < cf.n_layers; ++l)
@@ -1189,15 +1191,15 @@ static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_ne
   k_store_rows<<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->featbuf, c->F, c->pend_f, c->chunk_f, d);
   LAUNCH_CHECK();
   if (!want_logits) return EAGLE_OK;
-  return lm_head2(c, pass, M, true, logits_out, out_kind, only_last_row);
+  return lm_head2(c, pass, M, true, logits_out);
 }
 
 static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new, bool store_rows = true, bool want_logits = true) {
   const eagle_config& cf = c->cfg;
   const int M = pass.rows_per_seq * pass.n_seq, d = cf.d_model;
   int rc;
-  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP);
-  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP);
+  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts);
+  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts);
   LAUNCH_CHECK();
   Gemm2 g = gemm2_base(c, pass, M);
   g.epi = EPI_RESID; g.h_in = nullptr; g.h_out = c->h2; g.bias = c->loaded_layer[EAGLE_W_FC_BIAS][0] ? c->fc_bias : nullptr;
@@ -1209,7 +1211,7 @@ static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new,
     k_store_rows<<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->h2, c->node_f, c->pend_f, c->chunk_f, d);
     LAUNCH_CHECK();
   }
-  return lm_head2(c, pass, M, false, c->draft_logits, 0, 0);
+  return lm_head2(c, pass, M, false, c->draft_logits);
 }
 
 // ---------------------------------------------------------------------------- sequence life cycle
@@ -1248,7 +1250,7 @@ extern "C" int eagle_prefill(eagle_ctx* c, int32_t seq, const int32_t* prompt, i
     c->last_chunk_rows = cn; c->last_chunk_start = start;
     Pass pt{PASS_PREFILL_T, cn, 1, seq, 0, start, cn};
     const bool fast = cn <= 32 && c->q4;     // 4-bit weights: the prompt walks through the fused kernels 32 rows at a time
-    if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, 1, last, 1)
+    if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, last)
                    : target_forward(c, pt, start + cn, cn, last, c->vanilla_logits, 1, 1))) return rc;
     if (last) {
       k_choose<<<1, 1024, 0, c->stream>>>(c->st, seq, c->vanilla_logits, g.vocab, g.temperature, g.seed, c->pbuf, 1, n, c->D);
@@ -1405,7 +1407,7 @@ static int do_verify(eagle_ctx* c) {
   if (c->M * c->n_active <= 32) {
     Pass pv{PASS_VERIFY, c->M, c->n_active, 0, 0, 0, 0};
     pass_ctx(c, pv);
-    rc = target_forward2(c, pv, max_ctx(c), c->M, c->L, 0);
+    rc = target_forward2(c, pv, max_ctx(c), c->M, c->L);
   } else {
     Pass pv{PASS_VERIFY, c->M, c->n_active, 0, 0, 0, 0};
     pass_ctx(c, pv);
@@ -1554,7 +1556,7 @@ extern "C" int eagle_vanilla_step(eagle_ctx* c, int32_t* tokens) {
   const int B = c->n_active;
   Pass pv{PASS_VANILLA, 1, B, 0, 0, 0, 0};
   pass_ctx(c, pv);
-  if ((rc = (B <= 32 ? target_forward2(c, pv, max_ctx(c), 1, c->vanilla_logits, 1)
+  if ((rc = (B <= 32 ? target_forward2(c, pv, max_ctx(c), 1, c->vanilla_logits)
                      : target_forward(c, pv, max_ctx(c) + 1, 1, true, c->vanilla_logits, 1, 0)))) return rc;
   k_choose<<<B, 1024, 0, c->stream>>>(c->st, 0, c->vanilla_logits, g.vocab, g.temperature, g.seed, c->pbuf, 0, 0, c->D);
   LAUNCH_CHECK();

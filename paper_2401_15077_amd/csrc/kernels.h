@@ -70,6 +70,18 @@ __device__ inline RowInfo row_info(const Pass& p, const TreeDev* t, const SeqSta
   return o;
 }
 
+// What every kernel of a pass needs to know about a row, written once by the pass's first kernel (token embedding / FC
+// input).  The kernels behind it fetch it with one independent 16-byte load per half instead of walking tree, state and page
+// table again: that walk is a chain of three to four dependent loads, 1 us or more each, in front of every weight stream.
+struct alignas(16) RowFact {
+  int pos;                       // RoPE position
+  int kv_row;                    // (page * kv_heads << page_shift) | slot in page: row of the paged cache for kv head 0; -1: none
+  int out_row;                   // row of the pass's logits buffer, -1: no logits for this row
+  int seq;
+  int base, rel;                 // attention: keys [0, base) are visible; the row's own index among the new keys
+  uint32_t mask_lo, mask_hi;     // tree passes: visible new keys
+};
+
 struct KVCache {
   void* k; void* v;              // this layer's pages: [phys_page][kv_head][slot_in_page][head_dim]
   const int* page_table;         // [max_batch][pages_per_seq] -> physical page
@@ -78,6 +90,23 @@ struct KVCache {
 __device__ inline size_t kv_offset(const KVCache& c, int seq, int pos, int kvh) {
   int phys = c.page_table[seq * c.pages_per_seq + (pos >> c.page_shift)];
   return (((size_t)phys * c.n_kv_heads + kvh) << c.page_shift | (size_t)(pos & ((1 << c.page_shift) - 1))) * c.head_dim;
+}
+
+// The logits buffer of a pass: per tree node in drafting and verification, per sequence in vanilla passes and for a prompt's
+// last row.
+__device__ inline RowFact row_fact(const Pass& p, const TreeDev* t, const RowInfo& ri, const KVCache& c) {
+  RowFact f;
+  f.pos = ri.pos; f.seq = ri.seq; f.base = ri.base; f.rel = ri.rel;
+  f.mask_lo = (uint32_t)ri.mask; f.mask_hi = (uint32_t)(ri.mask >> 32);
+  f.kv_row = -1; f.out_row = -1;
+  if (ri.valid) {
+    const int phys = c.page_table[ri.seq * c.pages_per_seq + (ri.slot >> c.page_shift)];
+    f.kv_row = (phys * c.n_kv_heads << c.page_shift) | (ri.slot & ((1 << c.page_shift) - 1));
+    if (p.kind == PASS_VANILLA) f.out_row = ri.seq;
+    else if (p.kind == PASS_PREFILL_T) f.out_row = ri.rel == p.chunk_n - 1 ? ri.seq : -1;
+    else if (p.kind != PASS_PREFILL_D && ri.node >= 0) f.out_row = ri.seq * t->M + ri.node;
+  }
+  return f;
 }
 
 __device__ inline float cache_load(const float* p) { return *p; }
@@ -564,9 +593,10 @@ template <typename EmbT>
 __global__ __launch_bounds__(256) void k_fc_input(Pass pass, const TreeDev* tree, SeqState st, const int* tree_tok,
                                                   const float* pend_f /*[seq][D+1][d]*/, const float* node_f /*[seq][M][d]*/,
                                                   const float* chunk_f /*[chunk][d]*/, const EmbT* __restrict__ embed,
-                                                  bf16_t* XF, int d, int vocab, int MT, int nplanes) {
+                                                  bf16_t* XF, int d, int vocab, int MT, int nplanes, KVCache kv, RowFact* facts) {
   int r = blockIdx.x;
   RowInfo ri = row_info(pass, tree, st, r);
+  if (blockIdx.y == 0 && threadIdx.x == 0) facts[r] = row_fact(pass, tree, ri, kv);
   const int KS = 2 * d / 16;
   const float* f = nullptr;
   int tok = 0;

@@ -37,8 +37,13 @@ __device__ inline uint32_t pt_quad_bytes(int s, int Npad, int n4 /*multiple of 4
   return (uint32_t)((((size_t)s * Npad + n4) * 32 + (size_t)m * 4) * 4);
 }
 
-struct RowScale {            // 1/rms of the rows that produced the GEMM input; ssq == nullptr -> 1
-  const float* ssq;          // [groups][32] partial sums of squares
+// The wave's number as a scalar: everything derived from it (K range, tile addresses, buffer offsets) then stays in scalar
+// registers.  Left to the compiler it is a per-lane value, and every buffer load whose offset depends on it becomes a loop
+// over the lanes' distinct offsets.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+struct RowScale {            // 1/rms of the rows that produced the GEMM input; groups == 0 -> 1
+  const float* ssq;          // [groups <= 256][32] partial sums of squares
   int groups;
   float inv_d, eps;
 };
@@ -68,25 +73,38 @@ __device__ inline float block_row_rstd(const float* ssq, int groups, float inv_d
   __syncthreads();
   return tmp[16];
 }
-// The same value for all 32 rows at once, computed by a 512-thread block: thread (m, class c) loads its class's groups
-// (at most 16, all in flight) early in the kernel (rstd_class_partial); the classes are combined through LDS when the
-// epilogue needs the result (block_rstd_finish).
-__device__ inline float rstd_class_partial(const RowScale& rs) {
-  if (!rs.ssq) return 0.f;
-  const int m = threadIdx.x & 31, c = threadIdx.x >> 5;
-  float v[16];
+// The same value for all 32 rows at once, computed by a 512-thread block: thread (m, class c) requests its class's groups (at
+// most 16) and its row's facts BEFORE the weight stream without using them, so that they arrive in front of the first weight
+// tile and no load of the stream waits for them; the classes are combined through LDS when the epilogue needs the result
+// (block_rstd_finish).  ssq always points at 256 * 32 floats.  (Read and summed in front of the stream, with the row's facts
+// found by walking tree and page table, these were 4 to 5 dependent memory round trips before the first weight load; without
+// them: QKV 26.9 -> 25.4, gate/up 38.1 -> 36.5, down 26.2 -> 25.4 us at 7B widths, 4-bit gate/up 30.0 -> 22.3 us.)
+struct EarlyLoads { float ssq[16]; int pos, kv_row, out_row; };
+__device__ __forceinline__ void early_issue(const RowScale& rs, const RowFact* facts, EarlyLoads& e) {
+  const float* p = rs.ssq + (threadIdx.x >> 5) * 32 + (threadIdx.x & 31);
+  const RowFact* f = facts + (threadIdx.x & 31);
+  e.pos = f->pos; e.kv_row = f->kv_row; e.out_row = f->out_row;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int g = c + 16 * i;
-    v[i] = g < rs.groups ? rs.ssq[g * 32 + m] : 0.f;
+  for (int i = 0; i < 16; ++i) e.ssq[i] = 0.f;
+  if (rs.groups > 0) {                                         // (uniform branches: unneeded groups are not fetched)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e.ssq[i] = p[(size_t)i * 512];
   }
+  if (rs.groups > 64) {
+#pragma unroll
+    for (int i = 4; i < 16; ++i) e.ssq[i] = p[(size_t)i * 512];
+  }
+}
+__device__ inline float early_ssq(const RowScale& rs, EarlyLoads& e) {
   float a = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) a += v[i];
+  for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(e.ssq[i]));   // the sum stays here: hoisted, it would wait in front of the stream
+#pragma unroll
+  for (int i = 0; i < 16; ++i) a += (int)(threadIdx.x >> 5) + 16 * i < rs.groups ? e.ssq[i] : 0.f;
   return a;
 }
 __device__ inline void block_rstd_finish(const RowScale& rs, float part, float* out, float* tmp) {
-  if (!rs.ssq) {
+  if (rs.groups == 0) {
     if (threadIdx.x < 32) out[threadIdx.x] = 1.0f;
     __syncthreads();
     return;
@@ -120,12 +138,13 @@ struct Gemm2 {
   float* PT; int* counters;
   int M, epi;
   RowScale in_scale;
+  const RowFact* facts;                   // [32] rows of the pass
   // EPI_QKV
-  Pass pass; const TreeDev* tree; SeqState st; KVCache kv; int kv_f32; float* Q; const float* rope_cos; const float* rope_sin; int H;
+  KVCache kv; int kv_f32; float* Q; const float* rope_cos; const float* rope_sin; int H;
   // EPI_RESID / EPI_SWIGLU
   const float* h_in; float* h_out; const float* bias; const float* gain_next; bf16_t* xf_out; int xf_KS; float* ssq_out; int d;
   // EPI_LOGITS
-  float* logits; int out_kind, V, only_last_row;
+  float* logits; int V;
   const bf16_t* SC; int NG;               // 4-bit weights: scales [NRB][NG][2][16] and groups along K (W then holds codes)
   const float* row_w;                     // MoE: per-row routing weight applied to this GEMM's result (nullptr = 1)
   const int* skip_flag;                   // MoE: the whole launch is a no-op when *skip_flag == 0 (no row uses the expert)
@@ -195,12 +214,14 @@ __device__ inline void pt_sum16(const float* __restrict__ PT, int S, int Npad, i
   pt_finish16(b, S, outAB, outCD);
 }
 
-// what a thread needs about "its" row in the epilogue, fetched before the streaming loop so that the loads are
-// long finished when the last work-group gets there
-struct RowPre { int valid, seq, pos, slot; long dst; float ssq_part; };
+// Kernel arguments that the start of a weight stream needs, fetched together: the arguments come from memory, and a wait
+// between two groups of them costs another round trip in front of the first weight tile.
+__device__ __forceinline__ void pin_args(const Gemm2& g) {
+  asm volatile("" ::"s"(g.W), "s"(g.XF), "s"(g.NRB), "s"(g.KS), "s"(g.M), "s"(g.facts), "s"(g.in_scale.ssq), "s"(g.in_scale.groups), "s"(g.skip_flag));
+}
 
 template <int NXP>
-__device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float* rstd_s, const RowPre& rp) {
+__device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float* rstd_s, const EarlyLoads& rp) {
   const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;
   const int dh = g.kv.head_dim, half = dh >> 1, KVH = g.kv.n_kv_heads, H = g.H;
   const bool live = m < g.M;
@@ -235,9 +256,9 @@ __device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float*
       if (hd < H) {
         float* q = g.Q + ((size_t)m * H + hd) * dh;
         q[d1] = a; q[d2] = b;
-      } else if (rp.valid) {
+      } else if (rp.kv_row >= 0) {
         const int kvh = (hd - H) % KVH;
-        const size_t off = kv_offset(g.kv, rp.seq, rp.slot, kvh);
+        const size_t off = ((size_t)rp.kv_row + ((size_t)kvh << g.kv.page_shift)) * dh;
         void* base = hd < H + KVH ? g.kv.k : g.kv.v;
         if (g.kv_f32) { ((float*)base)[off + d1] = a; ((float*)base)[off + d2] = b; }
         else { ((bf16_t*)base)[off + d1] = f32_to_bf16(a); ((bf16_t*)base)[off + d2] = f32_to_bf16(b); }
@@ -331,10 +352,10 @@ __device__ inline void epilogue_swiglu(const Gemm2& g, int n0, int n1, const flo
   }
 }
 
-__device__ inline void epilogue_logits(const Gemm2& g, int n0, int n1, const float* rstd_s, const RowPre& rp) {
+__device__ inline void epilogue_logits(const Gemm2& g, int n0, int n1, const float* rstd_s, const EarlyLoads& rp) {
   const int m = threadIdx.x & 31, b = threadIdx.x >> 5;        // token m, quad b (and b + 16) of each 128-row batch
   const float rs = m < g.M ? rstd_s[m] : 0.f;
-  const long dst = rp.dst;                                     // where token m's logits row starts, or -1
+  const long dst = m < g.M && rp.out_row >= 0 ? (long)rp.out_row * g.V : -1;   // where token m's logits row starts, or -1
   const int nend = min(n1, g.V);
   const bool vec = (g.V & 3) == 0;                             // rows of the output are 16-byte aligned
   for (int nb0 = n0; nb0 < n1; nb0 += 128) {
@@ -517,9 +538,12 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float sh_small[16 * 33];
   __shared__ int s_last;
+  pin_args(g);
+  EarlyLoads el;                                                // used by the epilogue, much later
+  early_issue(g.in_scale, g.facts, el);
   if (g.skip_flag && *g.skip_flag == 0) return;               // uniform over the whole grid
   u32x4* xs = (u32x4*)smem;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = wave_id();
   // the work split in 32-bit arithmetic: every product stays far below 2^31 (<= 1024 groups x a few thousand row blocks)
   const unsigned uS = g.S, ugroups = g.groups, uNRB = g.NRB, uKS = g.KS, ulanes = g.lanes, ukparts = g.kparts;
   const int s = blockIdx.x % uS, grp = blockIdx.x / uS;
@@ -546,27 +570,6 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   // the first weight tiles are requested before anything else (a wave with fewer row blocks keeps more k-steps in flight)
   u32x4 pre[DEPTH * RW * NWP];
   if constexpr (!Q4) k2_prologue_dispatch<NWP, NXP, RW, RW, DEPTH>(nr, kb, ke, wp, g.wps, pre);
-
-  // row facts and the 1/rms inputs the epilogue will want: requested now, used (by the last work-group) much later
-  RowPre rp;
-  rp.valid = 0; rp.seq = 0; rp.pos = 0; rp.slot = 0; rp.dst = -1;
-  rp.ssq_part = rstd_class_partial(g.in_scale);
-  if (g.epi == EPI_QKV) {
-    const int m = threadIdx.x & 31;
-    if (m < g.M) {
-      const RowInfo ri = row_info(g.pass, g.tree, g.st, m);
-      rp.valid = ri.valid; rp.seq = ri.seq; rp.pos = ri.pos; rp.slot = ri.slot;
-    }
-  } else if (g.epi == EPI_LOGITS) {
-    const int m = threadIdx.x & 31;
-    if (m < g.M) {
-      const RowInfo ri = row_info(g.pass, g.tree, g.st, m);
-      if (ri.valid) {
-        if (g.out_kind == 0) { if (ri.node >= 0) rp.dst = ((long)ri.seq * g.tree->M + ri.node) * g.V; }
-        else if (!(g.only_last_row && ri.rel != g.pass.chunk_n - 1 && g.pass.kind != PASS_VANILLA)) rp.dst = (long)ri.seq * g.V;
-      }
-    }
-  }
 
   // stage this work-group's K slice of X: per plane a contiguous run of kt tiles (8 loads in flight per thread)
   for (int p = 0; p < NXP; ++p) {
@@ -655,12 +658,12 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   const int n0 = rb0 * 32, n1 = min(rb1 * 32, g.N);
   if (n1 <= n0) return;
   __shared__ float rstd_s[32];
-  if (g.epi != EPI_RESID) block_rstd_finish(g.in_scale, rp.ssq_part, rstd_s, sh_small);
+  if (g.epi != EPI_RESID) block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);
   switch (g.epi) {
-    case EPI_QKV: epilogue_qkv<NXP>(g, n0, n1, rstd_s, rp); break;
+    case EPI_QKV: epilogue_qkv<NXP>(g, n0, n1, rstd_s, el); break;
     case EPI_RESID: epilogue_resid<NXP>(g, grp, n0, n1, sh_small); break;
     case EPI_SWIGLU: epilogue_swiglu<NXP>(g, n0, n1, rstd_s); break;
-    default: epilogue_logits(g, n0, n1, rstd_s, rp); break;
+    default: epilogue_logits(g, n0, n1, rstd_s, el); break;
   }
   TRACE_STAMP(tr, 4);
 }
@@ -692,9 +695,13 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, NXP * KS * 1024, 0x00020000);
   const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : 0x80000000u;   // dead rows: out of range
 #define FK_XLOAD(q, kk) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane, (uint32_t)(((q) * KS + (kk)) * 1024), 0))
+  // Non-temporal: a weight byte is used once per pass and a pass's weights exceed every cache, so keeping them out leaves the L2s
+  // to the activations (7B, LLaMA shapes, us before / after: gate/up 36.5 / 34.5, LM head 49.0 / 45.0, QKV 25.4 / 23.9; a bare
+  // read of 2 GB runs at 6.9 TB/s with the hint and 6.25 without).  The 4-bit and fp32 streams keep plain loads: their head fits
+  // the 256 MB memory-side cache, from which the drafting passes then re-read it (4-bit LM head 32.7 us plain, 35.6 with the hint).
   auto wload = [&](int j, int p, int kk) -> u32x4 {
-    if constexpr (WB) return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(hw->rs, hw->vo[j], hw->so[j] + (uint32_t)kk * 1024u, 0));
-    else return *(const u32x4*)((const bf16_t*)(wp[j] + (size_t)kk * 64) + p * wps);
+    if constexpr (WB) return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(hw->rs, hw->vo[j], hw->so[j] + (uint32_t)kk * 1024u, 2));
+    else return __builtin_nontemporal_load((const u32x4*)((const bf16_t*)(wp[j] + (size_t)kk * 64) + p * wps));
   };
 #pragma unroll
   for (int dd = 0; dd < DEPTH; ++dd) {
@@ -883,8 +890,12 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   __shared__ float sh_small[16 * 33];
   __shared__ float rstd_s[32];
   float* red = (float*)smem;                                    // [8][NRMAX][16][64]
+  pin_args(g);
+  EarlyLoads el;                                                // used by the epilogue, much later
+  constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
+  if constexpr (!LATE) early_issue(g.in_scale, g.facts, el);
   if (g.skip_flag && *g.skip_flag == 0) return;                 // MoE: no row selected this expert (uniform over the grid)
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = wave_id();
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
   const unsigned G = gridDim.x;
@@ -918,21 +929,6 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   for (int j = 0; j < NRMAX; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  // row facts and 1/rms inputs, requested before the stream
-  RowPre rp;
-  rp.valid = 0; rp.seq = 0; rp.pos = 0; rp.slot = 0; rp.dst = -1;
-  rp.ssq_part = rstd_class_partial(g.in_scale);
-  {
-    const int m = threadIdx.x & 31;
-    if (m < g.M) {
-      const RowInfo ri = row_info(g.pass, g.tree, g.st, m);
-      if (g.epi == EPI_QKV) { rp.valid = ri.valid; rp.seq = ri.seq; rp.pos = ri.pos; rp.slot = ri.slot; }
-      else if (g.epi == EPI_LOGITS && ri.valid) {
-        if (g.out_kind == 0) { if (ri.node >= 0) rp.dst = ((long)ri.seq * g.tree->M + ri.node) * g.V; }
-        else if (!(g.only_last_row && ri.rel != g.pass.chunk_n - 1 && g.pass.kind != PASS_VANILLA)) rp.dst = (long)ri.seq * g.V;
-      }
-    }
-  }
   if constexpr (Q4) {
     // K is split over the waves by groups of 128; pointers to the codes / scales of each row block
     const int gb = (unsigned)w * (unsigned)g.NG / 8u, ge = (unsigned)(w + 1) * (unsigned)g.NG / 8u;
@@ -945,6 +941,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
       sq[j] = (const u32x4*)g.SC + rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
     }
     fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
+    if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
   fk_stream_dispatch<NWP, NXP, NRMAX, HALF>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane, &hw);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
@@ -954,7 +951,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
     if (j < nr)
 #pragma unroll
       for (int r = 0; r < 16; ++r) red[(((size_t)w * NRMAX + j) * 16 + r) * 64 + lane] = acc[j][r];
-  block_rstd_finish(g.in_scale, rp.ssq_part, rstd_s, sh_small);   // (contains the barriers that publish `red`)
+  block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);   // (contains the barriers that publish `red`)
   __syncthreads();
   const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;     // 16 slots of 32 tokens
   const bool live = m < g.M;
@@ -984,16 +981,16 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
       int d1, d2;
       if (hd < H + KVH) {        // q or k head: the two rows are a rotate-half pair
         const int i = pr >> 1;
-        const float cs = g.rope_cos[(size_t)rp.pos * half + i], sn = g.rope_sin[(size_t)rp.pos * half + i];
+        const float cs = g.rope_cos[(size_t)el.pos * half + i], sn = g.rope_sin[(size_t)el.pos * half + i];
         const float a2 = a * cs - b * sn, b2 = b * cs + a * sn;
         a = a2; b = b2; d1 = i; d2 = i + half;
       } else { d1 = pr; d2 = pr + 1; }
       if (hd < H) {
         float* q = g.Q + ((size_t)m * H + hd) * dh;
         q[d1] = a; q[d2] = b;
-      } else if (rp.valid) {
+      } else if (el.kv_row >= 0) {
         const int kvh = (hd - H) % KVH;
-        const size_t off = kv_offset(g.kv, rp.seq, rp.slot, kvh);
+        const size_t off = ((size_t)el.kv_row + ((size_t)kvh << g.kv.page_shift)) * dh;
         void* base = hd < H + KVH ? g.kv.k : g.kv.v;
         if (g.kv_f32) { ((float*)base)[off + d1] = a; ((float*)base)[off + d2] = b; }
         else { ((bf16_t*)base)[off + d1] = f32_to_bf16(a); ((bf16_t*)base)[off + d2] = f32_to_bf16(b); }
@@ -1034,17 +1031,18 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   } else {                                                      // EPI_LOGITS
     const int nend = min(g.N, g.V);
     const bool vec = (g.V & 3) == 0;
+    const long dst = live && el.out_row >= 0 ? (long)el.out_row * g.V : -1;
     for (int it = slot; it < nr * 8; it += 16) {                // item = (row block j, quad of 4 rows)
       const int j = it >> 3, qd = it & 7;
       const int n = (rb0 + j) * 32 + 4 * qd;
-      if (rp.dst < 0 || n >= nend) continue;
+      if (dst < 0 || n >= nend) continue;
       float v[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) v[t] = fk_sum(red, NRMAX, j, 4 * qd + t, m) * rs;
-      if (vec && n + 4 <= nend) { f32x4 o; o.x = v[0]; o.y = v[1]; o.z = v[2]; o.w = v[3]; *(f32x4*)(g.logits + rp.dst + n) = o; }
+      if (vec && n + 4 <= nend) { f32x4 o; o.x = v[0]; o.y = v[1]; o.z = v[2]; o.w = v[3]; *(f32x4*)(g.logits + dst + n) = o; }
       else {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) if (n + t < nend) g.logits[rp.dst + n + t] = v[t];
+        for (int t = 0; t < 4; ++t) if (n + t < nend) g.logits[dst + n + t] = v[t];
       }
     }
   }
@@ -1067,8 +1065,12 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   __shared__ float rstd_s[32];
   __shared__ int s_last;
   float* red = (float*)smem;                                    // [8][NRMAX][16][64]
+  pin_args(g);
+  EarlyLoads el;                                                // used by the epilogue, much later
+  constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
+  if constexpr (!LATE) early_issue(g.in_scale, g.facts, el);
   if (g.skip_flag && *g.skip_flag == 0) return;                 // uniform over the whole grid
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = wave_id();
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
   const unsigned uS = g.S, ugroups = g.groups, uNRB = g.NRB, uKS = g.KS;
@@ -1085,20 +1087,6 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   for (int j = 0; j < NRMAX; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  RowPre rp;
-  rp.valid = 0; rp.seq = 0; rp.pos = 0; rp.slot = 0; rp.dst = -1;
-  rp.ssq_part = rstd_class_partial(g.in_scale);
-  {
-    const int m = threadIdx.x & 31;
-    if (m < g.M && (g.epi == EPI_QKV || g.epi == EPI_LOGITS)) {
-      const RowInfo ri = row_info(g.pass, g.tree, g.st, m);
-      if (g.epi == EPI_QKV) { rp.valid = ri.valid; rp.seq = ri.seq; rp.pos = ri.pos; rp.slot = ri.slot; }
-      else if (ri.valid) {
-        if (g.out_kind == 0) { if (ri.node >= 0) rp.dst = ((long)ri.seq * g.tree->M + ri.node) * g.V; }
-        else if (!(g.only_last_row && ri.rel != g.pass.chunk_n - 1 && g.pass.kind != PASS_VANILLA)) rp.dst = (long)ri.seq * g.V;
-      }
-    }
-  }
   if constexpr (Q4) {
     const unsigned uNG = g.NG;
     const int G0 = (unsigned)s * uNG / uS, G1 = (unsigned)(s + 1) * uNG / uS, gt = G1 - G0;
@@ -1112,6 +1100,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
       sq[j] = (const u32x4*)g.SC + rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
     }
     fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
+    if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
   fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
@@ -1148,12 +1137,12 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   const int n0 = rb0 * 32, n1 = min(rb1 * 32, g.N);
   if (n1 <= n0) return;
-  if (g.epi != EPI_RESID) block_rstd_finish(g.in_scale, rp.ssq_part, rstd_s, sh_small);
+  if (g.epi != EPI_RESID) block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);
   switch (g.epi) {
-    case EPI_QKV: epilogue_qkv<NXP>(g, n0, n1, rstd_s, rp); break;
+    case EPI_QKV: epilogue_qkv<NXP>(g, n0, n1, rstd_s, el); break;
     case EPI_RESID: epilogue_resid<NXP>(g, grp, n0, n1, sh_small); break;
     case EPI_SWIGLU: epilogue_swiglu<NXP>(g, n0, n1, rstd_s); break;
-    default: epilogue_logits(g, n0, n1, rstd_s, rp); break;
+    default: epilogue_logits(g, n0, n1, rstd_s, el); break;
   }
   TRACE_STAMP(tr, 4);
 }
@@ -1163,7 +1152,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
 template <typename EmbT, int NXP>
 __global__ __launch_bounds__(256) void k2_embed(Pass pass, const TreeDev* tree, SeqState st, const int* tree_tok,
                                                 const EmbT* __restrict__ embed, int vocab, int M, int d, float* h,
-                                                const float* gain, bf16_t* xf_out, float* ssq_out) {
+                                                const float* gain, bf16_t* xf_out, float* ssq_out, KVCache kv, RowFact* facts) {
   __shared__ float sh[8 * 32];
   const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;          // 8 slots
   const int grp = blockIdx.x, groups = gridDim.x;
@@ -1175,6 +1164,7 @@ __global__ __launch_bounds__(256) void k2_embed(Pass pass, const TreeDev* tree, 
     if (pass.kind == PASS_VERIFY) tok = tree_tok[ri.seq * tree->M + ri.node];
     else tok = st.tokens[(size_t)ri.seq * st.tok_stride + ri.pos];
     tok = min(max(tok, 0), vocab - 1);
+    if (blockIdx.x == 0 && slot == 0) facts[m] = row_fact(pass, tree, ri, kv);
   }
   float ss = 0.f;
   for (int c = c0 + slot; c < c1; c += 8) {
