@@ -188,10 +188,10 @@ enum {
                                   EAGLE_GEMM_TRACE=<index of the launch within the verify phase> (read by eagle_init);
                                   events: 0 entered, 1 activations staged, 2 weight stream done, 3 partial sums
                                   published, 4 epilogue done (the work-groups that ran one). */
-  EAGLE_BUF_PREFILL_FEATURES   /* fp32 [rows, d_model]: target features of the rows of the most recent prompt pass of
-                                  eagle_prefill (the whole prompt when it fits one pass: 512 rows for dense bf16
-                                  models, 128 otherwise; else its last pass) -- Sec. 3.1: what the head's prompt
-                                  pass consumes */
+  EAGLE_BUF_PREFILL_FEATURES   /* fp32 [rows, d_model]: target features of the last rows of the most recent prompt of
+                                  eagle_prefill: its last window of 512 rows for bf16 models (128 where a width is no
+                                  multiple of 64 and for fp32 models, 32 for 4-bit weights), the whole prompt when it
+                                  fits one -- Sec. 3.1: what the head's prompt pass consumes */
 };
 int eagle_get_buffer(eagle_ctx *ctx, int32_t which, int32_t seq, void *host_dst, size_t cap_bytes);
 /* K and V (fp32, [n_kv_heads*head_dim] each) of target layer `layer` (or EAGLE_HEAD_LAYER) at cache position pos. */

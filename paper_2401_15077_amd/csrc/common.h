@@ -13,6 +13,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define EAGLE_MAX_DEPTH 15
 #define EAGLE_MAX_CHILD 8
 #define EAGLE_PREFILL_CHUNK 128
+#define EAGLE_PREFILL_WINDOW 512
+#define EAGLE_PREFILL_MAX 2048
 
 // Per-work-group time stamps (100 MHz wall clock) exist only in a library built with -DEAGLE_TRACE (a profiling build);
 // in the product build the macros expand to nothing and no kernel carries a trace store.

@@ -57,7 +57,7 @@ struct LayerW {
   float *attn_norm = nullptr, *mlp_norm = nullptr;
   bool moe = false;
 };
-struct GemmPlan { int S, ks_per_split, chunk; };
+struct GemmPlan { int S, ks_per_split, chunk, rbw, mw; };   // rbw, mw: tile shape of the large-M GEMM (0: k_gemm)
 
 // Kernel classes of the per-launch timing (profiling mode 2): what the launch computes, not which template ran
 // (the template's name is recorded beside it).
@@ -80,7 +80,7 @@ struct Arena {
 struct eagle_ctx {
   eagle_config cfg;
   hipStream_t stream;
-  char* ws; size_t ws_bytes;
+  char* ws; size_t ws_bytes, zero_end;
   bool f32, kv_f32, q4 = false;      // q4: weight matrices stored in 4 bits (fast path only)
   bool q4_staged = true;
   // 4-bit weights: epilogue classes (1 << epi) that take the streamed split-K kernel.  Measured at d = 4096 (us, streamed
@@ -90,8 +90,12 @@ struct eagle_ctx {
   int NWP, NXP, elt, kv_elt;         // weight planes, activation planes, bytes per weight / per KV element
   TreeDev tree_h; TreeDev* tree_d;
   int M, D, Mmax, max_level_rows;
-  int last_chunk_rows = 0, last_chunk_start = 0;   // rows of the most recent prompt pass of the target (their features stay in chunk_f)
-  int pf_chunk = EAGLE_PREFILL_CHUNK;   // rows of one prompt pass: 512 where the large-M GEMM exists (bf16, dense), else 128
+  int last_rows = 0, last_off = 0;     // the last window of the most recent prompt (EAGLE_BUF_PREFILL_FEATURES): rows, first row in chunk_f
+  // most rows of one prompt pass: where the large-M GEMM exists (bf16, every K a multiple of 64) a pass is as long as keeps the
+  // activations a small part of the card's memory, since every pass streams all weights, needs K slices (and their partial
+  // sums) to fill the chip with its narrow matrices, and rounds its tiles up once per matrix
+  int pf_chunk = EAGLE_PREFILL_CHUNK, pf_window = EAGLE_PREFILL_CHUNK;
+  bool big_gemm = false;
   // weights
   void* embed; PackedW lm_head, fc; float *final_norm, *fc_bias;
   std::vector<LayerW> layers;        // [n_layers] target + [1] head
@@ -139,7 +143,7 @@ struct eagle_ctx {
 };
 
 static GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
-  GemmPlan p;
+  GemmPlan p{};
   int wg_n = (NRB + 3) / 4;
   int S = std::max(1, std::min(16, 512 / std::max(1, wg_n)));
   S = std::min(S, std::max(1, KS / 8));
@@ -151,21 +155,33 @@ static GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
 
 // Which passes of the general path take the large-M GEMM: every pass of more than 128 rows (only prompts, and only
 // where the kernel exists), and batched tree passes of 65..128 rows of the models it covers.
-static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c->pf_chunk == 512); }
+static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c->big_gemm); }
 
-// Work split of the large-M GEMM (k_gemm_pf): work-group tiles of 8 row blocks x 4 row tiles; K is split only when the
-// tiles alone would leave most CUs idle (narrow matrices: O, down), since every split writes and re-reads M x N floats.
-static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu) {
-  GemmPlan p;
-  const int wgs = ((NRB + 7) / 8) * ((MT + 3) / 4);
-  // one tile of rows (a batched tree pass): the weights are streamed once, so deeper splits pay for themselves
-  // (a very long K -- the product with the transposed LM head -- affords 8)
-  int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? 16 : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
-  S = std::max(1, std::min(S, KS / (MT <= 4 ? 16 : 32)));
-  p.ks_per_split = ((KS + S - 1) / S + 3) / 4 * 4;
-  p.S = (KS + p.ks_per_split - 1) / p.ks_per_split;
-  p.chunk = 4;
-  return p;
+// Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
+// in a model of two terms, in us.  What the busiest CU multiplies: rounds x (32 x 32 tiles of a work-group) x k-steps of a slice
+// x the shape's measured time per tile and k-step.  Groups of work-groups that share a weight tile go round the 8 XCDs, so a
+// round is full when the XCD with one group more than the others is (LM-head transpose, 10 row tiles, 3 slices of 27 x 3
+// tiles: 243 work-groups, but 33 on the 32 CUs of one XCD: 355 us against 197 for 240 of the next shape).  And what the partial
+// sums cost that all but the fused epilogue write and read back, at 4.5 TB/s.
+static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue) {
+  GemmPlan best{};
+  double best_us = -1;
+  static const struct { int rbw, mw; double ns; } shapes[5] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}};
+  const int xcds = 8, cu_x = std::max(1, n_cu / xcds);
+  for (auto& sh : shapes) {
+    const int wt = 2 * sh.rbw, rt = 2 * sh.mw, mq = (MT + rt - 1) / rt, nt = (NRB + wt - 1) / wt;
+    if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
+    for (int S = 1; S <= 16; ++S) {
+      if (S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
+      const int kps = ((KS + S - 1) / S + 3) / 4 * 4, s_real = (KS + kps - 1) / kps;
+      const int rounds = ((nt * s_real + xcds - 1) / xcds * mq + cu_x - 1) / cu_x;
+      double us = 1e-3 * sh.ns * rounds * wt * rt * kps + 4.0;
+      if (!(fused_epilogue && s_real == 1)) us += (double)s_real * MT * NRB * 8192.0 / 4.5e6;
+      if (fused_epilogue && s_real > 1) us += 10.0;             // the SwiGLU kernel behind it
+      if (best_us < 0 || us < best_us) { best_us = us; best.S = s_real; best.ks_per_split = kps; best.chunk = 4; best.rbw = sh.rbw; best.mw = sh.mw; }
+    }
+  }
+  return best;
 }
 
 // Work split of the split-K kernel with streamed activations: S slices x groups of at most 4 row blocks, chosen by a
@@ -356,28 +372,10 @@ static size_t layout(eagle_ctx* c) {
   const int Mm = c->Mmax, MTm = Mm / 32;
   c->h = a.take<float>((size_t)Mm * d);
   c->Q = a.take<float>((size_t)Mm * H * dh);
-  c->xf_d = a.take<bf16_t>((size_t)c->NXP * Mm * d);
+  c->xf_d = a.take<bf16_t>((size_t)c->NXP * std::max(Mm, 2 * c->hl_chunk) * d);
   c->xf_2d = a.take<bf16_t>((size_t)c->NXP * Mm * 2 * d);
   c->xf_att = a.take<bf16_t>((size_t)c->NXP * Mm * H * dh);
   c->xf_ffn = a.take<bf16_t>((size_t)c->NXP * Mm * F);
-  // split-K partials: the largest S*Npad over all GEMM shapes, times Mmax
-  size_t worst = 0;
-  auto consider = [&](const PackedW& w) {
-    for (int mt = 1; mt <= MTm; ++mt) {
-      GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
-      worst = std::max(worst, (size_t)p.S * w.Npad * (size_t)(mt * 32));
-    }
-  };
-  consider(c->lm_head); consider(c->fc);
-  if (g.head_loss_rows > 0) consider(c->lm_head_T);
-  for (auto& w : c->layers) {
-    consider(w.qkv); consider(w.o);
-    if (w.moe) { consider(w.e_gu[0]); consider(w.e_dn[0]); } else { consider(w.gu); consider(w.dn); }
-  }
-  c->pt_floats = worst;
-  c->PT = a.take<float>(worst);
-  c->part_o = a.take<float>((size_t)Mm * H * 16 * dh);
-  c->part_ml = a.take<float>((size_t)Mm * H * 16 * 2);
   // fast path buffers
   c->h2 = a.take<float>((size_t)32 * d);
   c->xf2_d = a.take<bf16_t>((size_t)c->NXP * 32 * d);
@@ -405,6 +403,38 @@ static size_t layout(eagle_ctx* c) {
   }
   c->pt2_floats = worst2;
   c->PT2 = a.take<float>(worst2);
+  // scratch that every pass writes before it reads (not cleared by eagle_init)
+  c->zero_end = a.off;
+  // split-K partials of the general path: the largest S * Npad * rows over the GEMM shapes and the passes that run them
+  size_t worst = 0;
+  struct Seen { int NRB, KS, mt_max; bool fused; };
+  std::vector<Seen> seen;                                       // (the layers repeat the same few shapes)
+  auto consider = [&](const PackedW& w, int mt_max, bool fused) {
+    for (const Seen& q : seen) if (q.NRB == w.NRB && q.KS == w.KS && q.mt_max == mt_max && q.fused == fused) return;
+    seen.push_back(Seen{w.NRB, w.KS, mt_max, fused});
+    for (int mt = 1; mt <= mt_max; ++mt) {
+      const GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu, fused) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
+      if (fused && use_pf(c, mt) && p.S == 1) continue;          // SwiGLU inside the GEMM: nothing goes through memory
+      worst = std::max(worst, (size_t)p.S * w.Npad * (size_t)(mt * 32));
+    }
+  };
+  if (g.head_loss_rows > 0) { consider(c->lm_head, 2 * c->hl_chunk / 32, false); consider(c->lm_head_T, c->hl_chunk / 32, false); }
+  consider(c->lm_head, 4, false);                               // tree and vanilla passes; a prompt needs its last row tile only
+  consider(c->fc, MTm, false);
+  for (auto& w : c->layers) {
+    consider(w.qkv, MTm, false); consider(w.o, MTm, false);
+    if (w.moe) { consider(w.e_gu[0], MTm, false); consider(w.e_dn[0], MTm, false); } else { consider(w.gu, MTm, true); consider(w.dn, MTm, false); }
+  }
+  c->pt_floats = worst;
+  c->PT = a.take<float>(worst);
+  // attention partials: rows x KV splits, which attn_splits bounds (a pass of many row blocks is not split)
+  size_t part_rows = 32 * 16;
+  for (int rb = 2; rb <= MTm + B; ++rb) {                       // (sequence, 32-row block) pairs of a pass
+    const int s = std::min(16, c->n_cu / (H * rb));
+    if (s > 1) part_rows = std::max(part_rows, (size_t)32 * rb * s);
+  }
+  c->part_o = a.take<float>(part_rows * H * dh);
+  c->part_ml = a.take<float>(part_rows * H * 2);
   return (a.off + 255) & ~(size_t)255;
 }
 
@@ -437,14 +467,18 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
   for (int dlev = 1; dlev <= c->D; ++dlev) c->max_level_rows = std::max(c->max_level_rows, c->tree_h.n_level_rows[dlev]);
   if (cfg->max_batch * c->M > 128) return fail(EAGLE_EINVAL, "max_batch * n_nodes = %d rows exceeds the 128-row limit of one pass", cfg->max_batch * c->M);
   // (the large-M GEMM walks K in stages of 4 k-steps: every K of the model must be a multiple of 64)
-  c->pf_chunk = (!c->f32 && cfg->d_ffn % 64 == 0 && (cfg->n_heads * cfg->head_dim) % 64 == 0) ? 512 : EAGLE_PREFILL_CHUNK;
+  c->big_gemm = !c->f32 && cfg->weight_bits != 4 && cfg->d_ffn % 64 == 0 && (cfg->n_heads * cfg->head_dim) % 64 == 0;
+  if (c->big_gemm) {
+    c->pf_window = EAGLE_PREFILL_WINDOW;
+    c->pf_chunk = std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + EAGLE_PREFILL_WINDOW - 1) / EAGLE_PREFILL_WINDOW * EAGLE_PREFILL_WINDOW);
+  }
   if (c->q4) {
     // 4-bit weights exist in the fused kernels of the fast path only: every pass has at most 32 rows, the prompt included
     if (c->f32 || cfg->n_experts > 0) return fail(EAGLE_EINVAL, "weight_bits = 4 needs a dense bf16 model");
     if (cfg->d_model % EAGLE_Q4_GROUP || cfg->d_ffn % EAGLE_Q4_GROUP || (cfg->n_heads * cfg->head_dim) % EAGLE_Q4_GROUP)
       return fail(EAGLE_EINVAL, "weight_bits = 4 needs d_model, d_ffn and n_heads * head_dim to be multiples of %d", EAGLE_Q4_GROUP);
     if (cfg->max_batch * c->M > 32 || cfg->max_batch * (c->D + 1) > 32) return fail(EAGLE_EINVAL, "weight_bits = 4: max_batch * n_nodes and max_batch * (depth + 1) must not exceed 32 rows");
-    c->pf_chunk = 32;
+    c->pf_chunk = c->pf_window = 32;
   }
   int rows = std::max(c->pf_chunk, cfg->max_batch * c->M);
   c->Mmax = (rows + 31) / 32 * 32;
@@ -452,7 +486,9 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
   if (cfg->head_loss_rows > 0) {
     if (c->f32 || c->q4) return fail(EAGLE_EINVAL, "head_loss_rows > 0 needs a bf16 model with its weights as given");
     if (cfg->vocab % 64) return fail(EAGLE_EINVAL, "head_loss_rows > 0 needs vocab to be a multiple of 64");
-    c->hl_chunk = c->Mmax / 2 / 32 * 32;          // label rows and prediction rows share one pass of the LM head
+    // label rows and prediction rows share one pass of the LM head
+    const int want = std::min(EAGLE_PREFILL_MAX, 2 * ((cfg->head_loss_rows + 31) / 32 * 32));
+    c->hl_chunk = std::max(c->Mmax, want) / 2 / 32 * 32;
     if (c->hl_chunk < 32) return fail(EAGLE_EINVAL, "internal: no room for a loss pass");
   }
   return EAGLE_OK;
@@ -500,7 +536,7 @@ extern "C" int eagle_init(const eagle_config* cfg, void* workspace_dev, size_t w
   c->h_ctx.assign(g.max_batch, 0); c->h_ntok.assign(g.max_batch, 0); c->active.assign(g.max_batch, 0); c->head_stale.assign(g.max_batch, 0);
   // zero everything that is not a weight (finite garbage-free caches and padding rows)
   char* z0 = (char*)c->kc;
-  size_t zbytes = (size_t)(c->ws + need - z0);
+  size_t zbytes = (size_t)(c->ws + ((c->zero_end + 3) & ~(size_t)3) - z0);
   k_fill_u32<<<2048, 256, 0, c->stream>>>((uint32_t*)z0, 0u, zbytes / 4);
   if (hipGetLastError() != hipSuccess) { delete c; return fail(EAGLE_EHIP, "fill launch failed"); }
   if (hipMemcpyAsync(c->tree_d, &c->tree_h, sizeof(TreeDev), hipMemcpyHostToDevice, c->stream) != hipSuccess) { delete c; return fail(EAGLE_EHIP, "tree upload failed"); }
@@ -687,32 +723,33 @@ static hipError_t launch_gemm_mt(eagle_ctx* c, const PackedW& w, const bf16_t* X
   }
 }
 
+// The work-group tile of the plan, with or without the SwiGLU epilogue.
+template <int RBW, int MW>
+static hipError_t launch_pf(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, const GemmPlan& p, bf16_t* swiglu_out, int M) {
+  const int MQ = (MT + 2 * MW - 1) / (2 * MW), G = ((w.NRB + 2 * RBW - 1) / (2 * RBW)) * p.S;
+  const dim3 grid((G + 7) / 8 * 8 * MQ), block(128 * MW);
+  const double bytes = (double)w.N * w.K * c->elt;
+  if (swiglu_out) return launch_k(c, c->cur_class, bytes, "k_gemm_pf<swiglu>", k_gemm_pf<RBW, MW, true>, grid, block, (size_t)0,
+                                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M);
+  return launch_k(c, c->cur_class, bytes, "k_gemm_pf", k_gemm_pf<RBW, MW, false>, grid, block, (size_t)0,
+                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, (bf16_t*)nullptr, M);
+}
+
 // PT <- X (XF layout, MT row tiles) times W^T.  Returns the split count through *S.
 // swiglu_out (gate/up matrices only): where the plan has a single K slice in the large-M kernel, the SwiGLU epilogue runs
 // inside the GEMM and its output goes to swiglu_out in GEMM-input layout; *S is then 0 (nothing left in PT).
 static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S, bf16_t* swiglu_out = nullptr, int M = 0) {
   const bool big = use_pf(c, MT);
-  GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
-  if ((size_t)p.S * w.Npad * MT * 32 > c->pt_floats) return fail(EAGLE_EINVAL, "internal: partial buffer too small");
-  if (MT < 1 || MT * 32 > c->Mmax || (big && c->f32)) return fail(EAGLE_EINVAL, "internal: MT out of range");
-  *S = p.S;
+  GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu, swiglu_out != nullptr) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
+  const bool fuse = big && swiglu_out && p.S == 1;
+  if (!fuse && (size_t)p.S * w.Npad * MT * 32 > c->pt_floats) return fail(EAGLE_EINVAL, "internal: partial buffer too small");
+  if (MT < 1 || MT * 32 > std::max(c->Mmax, 2 * c->hl_chunk) || (big && c->f32)) return fail(EAGLE_EINVAL, "internal: MT out of range");
+  *S = fuse ? 0 : p.S;
   hipError_t e;
   if (big) {
-    static bool attr_set = false;
-    if (!attr_set) {
-      HIPCHK(hipFuncSetAttribute((const void*)k_gemm_pf<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
-      HIPCHK(hipFuncSetAttribute((const void*)k_gemm_pf<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
-      attr_set = true;
-    }
-    const int MQ = (MT + 3) / 4, G = ((w.NRB + 7) / 8) * p.S;
-    const int grid = (G + 7) / 8 * 8 * MQ;
-    if (swiglu_out && p.S == 1) {
-      *S = 0;
-      e = launch_k(c, c->cur_class, (double)w.N * w.K * c->elt, "k_gemm_pf<swiglu>", k_gemm_pf<2, true>, dim3(grid), dim3(256), (size_t)64 * 1024,
-                   (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M);
-    } else
-    e = launch_k(c, c->cur_class, (double)w.N * w.K * c->elt, "k_gemm_pf", k_gemm_pf<2, false>, dim3(grid), dim3(256), (size_t)64 * 1024,
-                 (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, (bf16_t*)nullptr, 0);
+    bf16_t* out = fuse ? swiglu_out : nullptr;
+    if (p.mw == 4) e = p.rbw == 4 ? launch_pf<4, 4>(c, w, XF, MT, p, out, M) : p.rbw == 3 ? launch_pf<3, 4>(c, w, XF, MT, p, out, M) : launch_pf<2, 4>(c, w, XF, MT, p, out, M);
+    else e = p.rbw == 4 ? launch_pf<4, 2>(c, w, XF, MT, p, out, M) : launch_pf<3, 2>(c, w, XF, MT, p, out, M);
   } else e = c->f32 ? launch_gemm_mt<3, 3>(c, w, XF, c->PT, MT, p) : launch_gemm_mt<1, 2>(c, w, XF, c->PT, MT, p);
   if (e != hipSuccess) return fail(EAGLE_EHIP, "gemm launch failed: %s", hipGetErrorString(e));
   return EAGLE_OK;
@@ -1244,10 +1281,13 @@ extern "C" int eagle_prefill(eagle_ctx* c, int32_t seq, const int32_t* prompt, i
   int zero = 0;
   HIPCHK(hipMemcpyAsync(c->st.ctx_len + seq, &zero, 4, hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));   // `zero` and `prompt` are host memory of the caller
-  for (int start = 0; start < n; start += c->pf_chunk) {
-    const int cn = std::min(c->pf_chunk, n - start);
+  // passes of about equal length, whole windows each (so the last window lies in the last pass)
+  const int n_pass = (n + c->pf_chunk - 1) / c->pf_chunk;
+  const int pass_rows = ((n + n_pass - 1) / n_pass + c->pf_window - 1) / c->pf_window * c->pf_window;
+  for (int start = 0; start < n; start += pass_rows) {
+    const int cn = std::min(pass_rows, n - start);
     const bool last = start + cn == n;
-    c->last_chunk_rows = cn; c->last_chunk_start = start;
+    c->last_off = (cn - 1) / c->pf_window * c->pf_window; c->last_rows = cn - c->last_off;
     Pass pt{PASS_PREFILL_T, cn, 1, seq, 0, start, cn};
     const bool fast = cn <= 32 && c->q4;     // 4-bit weights: the prompt walks through the fused kernels 32 rows at a time
     if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, last)
@@ -1289,7 +1329,7 @@ extern "C" int eagle_head_loss(eagle_ctx* c, const float* f, const float* fhat, 
   for (int r0 = 0; r0 < rows; r0 += c->hl_chunk) {
     const int rc_ = std::min(c->hl_chunk, rows - r0), rpad = (rc_ + 31) / 32 * 32;
     const int MTf = 2 * rpad / 32, MTb = rpad / 32;
-    if (MTf * 32 > c->Mmax) return fail(EAGLE_EINVAL, "internal: loss pass of %d rows exceeds the pass limit", MTf * 32);
+    if (MTf * 32 > 2 * c->hl_chunk) return fail(EAGLE_EINVAL, "internal: loss pass of %d rows exceeds the pass limit", MTf * 32);
     // labels in rows [0, rc_), predictions in rows [rpad, rpad + rc_) of one LM-head pass
     k_rows_to_xf<<<dim3(rc_, 2), 256, 0, c->stream>>>(f + (size_t)r0 * d, 0, c->xf_d, MTf, c->NXP, d);
     LAUNCH_CHECK();
@@ -1708,7 +1748,7 @@ extern "C" int eagle_get_buffer(eagle_ctx* c, int32_t which, int32_t seq, void* 
       return EAGLE_OK;
     }
     case EAGLE_BUF_GEMM_TRACE: src = c->trace; bytes = (size_t)1024 * 8 * 8; break;
-    case EAGLE_BUF_PREFILL_FEATURES: src = c->chunk_f; bytes = (size_t)c->last_chunk_rows * g.d_model * 4; break;
+    case EAGLE_BUF_PREFILL_FEATURES: src = c->chunk_f + (size_t)c->last_off * g.d_model; bytes = (size_t)c->last_rows * g.d_model * 4; break;
     default: return fail(EAGLE_EINVAL, "unknown buffer id %d", which);
   }
   if (cap < bytes) return fail(EAGLE_EINVAL, "destination of %zu bytes is smaller than the %zu needed", cap, bytes);

@@ -384,124 +384,135 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ Wp, siz
   }
 }
 
-// ============================================================================ large-M GEMM (prompt passes of up to 512 rows)
-// Same operands and the same PT[s][m][n] result as k_gemm, for passes whose rows fill several 128-row tiles: here the
+// ============================================================================ large-M GEMM (prompt passes, batched tree passes, the loss)
+// Same operands and the same PT[s][m][n] result as k_gemm, for passes whose rows fill several 32-row tiles: here the
 // MFMA pipes, not the weight stream, are the bound (Sec. 3.1: the head consumes the whole prompt's features, so the
 // prompt runs through the target and the head once, as one large matrix product per weight matrix).
-//   work-group tile  256 weight rows (8 row blocks) x 128 activation rows (4 row tiles), 4 waves;
-//   wave w           row blocks 2w, 2w+1 x all 4 activation tiles: 8 accumulator tiles, 16 MFMAs per k-step
-//   activations      the tile's 2 planes x 4 row tiles pass through LDS in chunks of CH k-steps, double-buffered; the
-//                    next chunk travels global -> registers while the current one is multiplied (one barrier a chunk)
-//   weights          each wave streams its own two row blocks global -> registers one chunk ahead
+//   work-group tile  2 * RBW row blocks of weights x 2 * MW tiles of 32 activation rows; 2 x MW waves
+//   wave (wn, wm)    RBW row blocks x 2 activation tiles, both activation planes: 4 * RBW MFMAs per k-step
+//   LDS              a ring of four k-steps of BOTH operands (20 to 24 KiB each for MW = 4, 14 to 16 for MW = 2), filled by
+//                    direct global -> LDS loads (both operands lie in memory in fragment order: one load = one 1 KiB tile)
+// At the barrier of k-step k every wave holds that step's fragments in registers, so its slot is refilled with step k + 4 at
+// once, step k + 1 is read from LDS behind the barrier, and both travel while the 4 * RBW MFMAs run: neither memory nor LDS
+// latency is waited for, and no registers are spent on data in flight (four separate arrays, so that the compiler can
+// tell the slot being filled from the slot being read and adds no wait of its own).
+// (Rings of 6 and 8 k-steps measured the same or slower, a K order rotated per work-group the same.)
+// Which tile: the host (plan_pf) takes the shape whose work-groups fill the CUs of every XCD in the fewest, fullest rounds.
+// Bound: the matrix pipes at the clock the card holds under them (1.05 to 1.2 PFLOP/s with weights from HBM; the library's own
+// 8192-cubed bf16 product reaches 1.2).  Inside a 512-row prompt pass at 7B widths, us before (8 x 4 tile, activations through
+// registers) / now: QKV 125 / 97, O and down 67 / 62 on average, gate/up 217 / 172; LLaMA2-70B gate/up 861 / 785.
 // Work-groups that share a weight tile (the activation-row tiles of one weight-row tile) get ids 8 apart, i.e. the same
 // XCD under round-robin dispatch, next to each other in dispatch order: the tile comes from HBM once and from that
 // XCD's L2 afterwards.
+// Every K range is a multiple of 4 k-steps (host).
 __device__ inline void xf_store8(bf16_t* XF, int m, int k8, int MT, int KS, int nplanes, const float* x);   // defined with the row producers below
 // SWIGLU (only with S = 1, gate/up matrices): instead of PT the kernel writes silu(gate) * up as the next GEMM's input
 // (XF layout, `act`, rows beyond M as zeros).  A row block of the fused matrix holds 16 gate rows and the 16 up rows of
 // the same features, and accumulator registers r and r + 8 of a lane are such a pair; the two lanes of an activation
 // row swap four values so that each holds 8 consecutive features = its 16 bytes of the output tile.
-template <int NXP, bool SWIGLU = false>
-__global__ __launch_bounds__(256, 2) void k_gemm_pf(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ XF,
-                                                 float* __restrict__ PT, int NRB, int KS, int ks_per_split, int S, int Npad,
-                                                 int MT /*32-row tiles of the pass*/, bf16_t* act = nullptr, int M = 0) {
-  constexpr int CH = 4;                                         // k-steps per LDS stage
-  constexpr int XT = NXP * 4 * CH;                              // activation tiles (1 KiB) per stage
-  constexpr int XR = XT / CH;                                   // activation tiles per stage and k-step = loads per wave and stage
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  u32x4* xs = (u32x4*)smem;                                     // [2 stages][NXP*4 tiles][CH][64]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int MQ = (MT + 3) >> 2, NT = (NRB + 7) >> 3, G = NT * S;
+template <int RBW, int MW, bool SWIGLU = false>
+__global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ XF,
+                                                           float* __restrict__ PT, int NRB, int KS, int ks_per_split, int S, int Npad,
+                                                           int MT /*32-row tiles of the pass*/, bf16_t* act, int M) {
+  constexpr int NXP = 2, WT = 2 * RBW, RT = 2 * MW, NTILE = WT + NXP * RT, NW = 2 * MW, LPW = (NTILE + NW - 1) / NW;
+  constexpr int SLOT = NTILE * 64;
+  __shared__ u32x4 s0[SLOT];                                    // per k-step: WT weight tiles, then NXP planes of RT activation tiles
+  __shared__ u32x4 s1[SLOT];
+  __shared__ u32x4 s2[SLOT];
+  __shared__ u32x4 s3[SLOT];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wn = w & 1, wm = w >> 1;
   // id -> (group = (weight-row tile, split), activation-row tile)
+  const int MQ = (MT + RT - 1) / RT, NT = (NRB + WT - 1) / WT, G = NT * S;
   const int L = blockIdx.x, blk = L / (8 * MQ), rem = L % (8 * MQ), mq = rem >> 3, g = blk * 8 + (rem & 7);
   if (g >= G) return;
   const int nt = g / S, s = g % S;
-  const int rbA = min(nt * 8 + 2 * wave, NRB - 1), rbB = min(nt * 8 + 2 * wave + 1, NRB - 1);
-  const bool liveA = nt * 8 + 2 * wave < NRB, liveB = nt * 8 + 2 * wave + 1 < NRB;
   const int k_begin = s * ks_per_split, k_end = min(KS, k_begin + ks_per_split);
   if (k_end <= k_begin) return;
   const int klast = k_end - 1;
-  f32x16 acc[2][4];
+  const int rb0 = nt * WT + wn * RBW, mt0 = mq * RT + wm * 2;
+  // a wave whose activation tiles or row blocks all lie beyond the end moves data and keeps the barriers, but multiplies nothing
+  const bool busy = mt0 < MT && rb0 < NRB;
+  // the tiles this wave loads, the same number in every wave (the last tile is loaded more than once where they do not divide)
+  const bf16_t* src[LPW];
+  int dst[LPW];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int u = 0; u < LPW; ++u) {
+    const int i = min(w + u * NW, NTILE - 1);
+    if (i < WT) src[u] = Wp + (size_t)min(nt * WT + i, NRB - 1) * KS * 512;
+    else src[u] = XF + (size_t)((i - WT) / RT * MT + min(mq * RT + (i - WT) % RT, MT - 1)) * KS * 512;
+    dst[u] = i * 64;
+  }
+  // (k-steps beyond the end are clamped, so that the number of loads in flight is the same on every path)
+  auto dma = [&](u32x4* slot, int k) {
+    const size_t ko = (size_t)min(k, klast) * 512;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int u = 0; u < LPW; ++u)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[u] + ko + lane * 8), (__attribute__((address_space(3))) void*)(slot + dst[u]), 16, 0, 0);
+  };
+  f32x16 acc[RBW][2];
+#pragma unroll
+  for (int j = 0; j < RBW; ++j)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
-  const u32x4* wA = (const u32x4*)(Wp + (size_t)rbA * KS * 512) + lane;
-  const u32x4* wB = (const u32x4*)(Wp + (size_t)rbB * KS * 512) + lane;
-  u32x4 xr[XR], ar[CH][2];
-  // Activations: global -> registers at the start of a stage, registers -> LDS at its end (the loads have the whole
-  // stage to arrive).  Load u of wave w carries tile u (= plane * 4 + row tile) of k-step c0 + w, which is piece
-  // (u * CH + w) * 64 + lane of the stage.  Every k range is a multiple of CH (host).
-  auto load_x = [&](int c0) {
+  u32x4 fa[2][RBW], fb[2][NXP * 2];
+  auto frags = [&](const u32x4* slot, int b) {
 #pragma unroll
-    for (int u = 0; u < XR; ++u) {
-      const int plane = u >> 2, mt = min(mq * 4 + (u & 3), MT - 1);
-      xr[u] = *((const u32x4*)(XF + (((size_t)plane * MT + mt) * KS + min(c0 + wave, klast)) * 512) + lane);
-    }
+    for (int j = 0; j < RBW; ++j) fa[b][j] = slot[(wn * RBW + j) * 64 + lane];
+#pragma unroll
+    for (int q = 0; q < NXP; ++q)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) fb[b][q * 2 + t] = slot[(WT + q * RT + wm * 2 + t) * 64 + lane];
   };
-  auto store_x = [&](int stage) {
+  auto mul = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < XR; ++u) xs[(size_t)stage * XT * 64 + (size_t)(u * CH + wave) * 64 + lane] = xr[u];
+    for (int q = 0; q < NXP; ++q)
+#pragma unroll
+      for (int j = 0; j < RBW; ++j)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[b][j]), __builtin_bit_cast(bf16x8, fb[b][q * 2 + t]), acc[j][t], 0, 0, 0);
   };
-  auto load_a = [&](int c0) {
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const size_t ko = (size_t)min(c0 + u, klast) * 64;
-      ar[u][0] = wA[ko]; ar[u][1] = wB[ko];
-    }
-  };
-  load_x(k_begin);
-  load_a(k_begin);
-  store_x(0);
-  __syncthreads();
-  int stage = 0;
-  for (int c0 = k_begin; c0 < k_end; c0 += CH, stage ^= 1) {
-    // the next stage's activations, in flight while this stage is multiplied (issued unconditionally -- k-steps are
-    // clamped to the last one -- so that the number of loads in flight is the same on every path and the compiler's
-    // waits name exactly the load they need)
-    load_x(c0 + CH);
-    const u32x4* xb = xs + (size_t)stage * XT * 64 + lane;
-    u32x4 bq[2][NXP * 4];                                       // the k-step being multiplied and the one after it
-#pragma unroll
-    for (int i = 0; i < NXP * 4; ++i) bq[0][i] = xb[(size_t)(i * CH) * 64];
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      if (u + 1 < CH) {
-#pragma unroll
-        for (int i = 0; i < NXP * 4; ++i) bq[(u + 1) & 1][i] = xb[(size_t)(i * CH + u + 1) * 64];
-      }
-#pragma unroll
-      for (int i = 0; i < NXP * 4; ++i) {
-        const int t = i & 3;
-        acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar[u][0]), __builtin_bit_cast(bf16x8, bq[u & 1][i]), acc[0][t], 0, 0, 0);
-        acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ar[u][1]), __builtin_bit_cast(bf16x8, bq[u & 1][i]), acc[1][t], 0, 0, 0);
-      }
-      // use a slot, refill that slot: the weight tiles of the same k-step of the NEXT stage
-      const size_t ko = (size_t)min(c0 + CH + u, klast) * 64;
-      ar[u][0] = wA[ko]; ar[u][1] = wB[ko];
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    store_x(stage ^ 1);                                         // the other stage was last read before the previous barrier
-    // A bare s_barrier behind a wait for this wave's LDS writes only: __syncthreads() carries a work-group fence, for
-    // which the compiler drains EVERY outstanding load -- the weight refills issued a moment ago included -- once per
-    // stage, which halves the MFMA rate.  All LDS reads of this stage were consumed by the MFMAs above.
-    __builtin_amdgcn_s_waitcnt(0xC07F);                         // lgkmcnt(0); vmcnt and expcnt left alone
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+  dma(s0, k_begin); dma(s1, k_begin + 1); dma(s2, k_begin + 2); dma(s3, k_begin + 3);
+  // vmcnt(n), the other counters left alone; a bare barrier: __syncthreads() would drain every load in flight
+#define PF_WAITV(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+#define PF_BAR() do { asm volatile("" ::: "memory"); __builtin_amdgcn_s_barrier(); asm volatile("" ::: "memory"); } while (0)
+  PF_WAITV(3 * LPW);
+  PF_BAR();
+  frags(s0, 0);
+  // all fragments of step k are in registers and this wave's loads of step k + 1 have landed -> barrier -> so have everyone's
+#define PF_STEP(i, cur, nxt)                                                        \
+  {                                                                                 \
+    __builtin_amdgcn_s_waitcnt(0xC07F);                    /* lgkmcnt(0) */         \
+    PF_WAITV(2 * LPW);                                                              \
+    PF_BAR();                                                                       \
+    frags(nxt, ((i) & 1) ^ 1);                                                      \
+    dma(cur, k + (i) + 4);                                                          \
+    if (busy) mul((i) & 1);                                                         \
+    __builtin_amdgcn_sched_barrier(0);                                              \
   }
+  for (int k = k_begin; k < k_end; k += 4) {
+    PF_STEP(0, s0, s1)
+    PF_STEP(1, s1, s2)
+    PF_STEP(2, s2, s3)
+    PF_STEP(3, s3, s0)
+  }
+  PF_WAITV(0);                                                  // no load may be on its way into LDS when the work-group ends
+#undef PF_STEP
+#undef PF_WAITV
+#undef PF_BAR
+  if (!busy) return;
   // accumulator register r of lane l: weight row 8*(r/4) + 4*(l/32) + r%4, activation row l%32; PT[s][m][n], n fastest
   if constexpr (SWIGLU) {
     const int hh = lane >> 5;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (!(j ? liveB : liveA)) continue;
-      const int rb = j ? rbB : rbA;
+    for (int j = 0; j < RBW; ++j) {
+      const int rb = rb0 + j;
+      if (rb >= NRB) continue;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int mt = mq * 4 + t;
+      for (int t = 0; t < 2; ++t) {
+        const int mt = mt0 + t;
         if (mt >= MT) continue;
         const int m = mt * 32 + (lane & 31);
         float v[8];                                             // features 4hh + {0..3} and 8 + 4hh + {0..3} of the block
@@ -524,12 +535,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf(const bf16_t* __restrict__ W
   }
   const int Mpad = MT * 32;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (!(j ? liveB : liveA)) continue;
-    const int rb = j ? rbB : rbA;
+  for (int j = 0; j < RBW; ++j) {
+    const int rb = rb0 + j;
+    if (rb >= NRB) continue;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int mt = mq * 4 + t;
+    for (int t = 0; t < 2; ++t) {
+      const int mt = mt0 + t;
       if (mt >= MT) continue;
       float* out = PT + ((size_t)s * Mpad + mt * 32 + (lane & 31)) * Npad + (size_t)rb * 32 + 4 * (lane >> 5);
 #pragma unroll

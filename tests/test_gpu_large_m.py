@@ -1,0 +1,31 @@
+"""The large-M GEMM (k_gemm_pf) at the edges of its tiles: prompt passes whose rows end inside a 32-row tile, inside a work-group
+tile (4 or 8 row tiles), at a window of 512 rows, and beyond one pass of 2048; a loss pass of more than 1024 rows.  Against the
+CPU oracle in fp64."""
+import numpy as np
+import pytest
+
+import synth
+from lockstep import Stats, check_prefill, lockstep_step
+from test_gpu_head_loss import _check, _engine, _features, _lm_head
+from test_gpu_parity import TOL, make_pair
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows", [65, 97, 129, 257, 333, 512, 513, 600, 1100, 2049, 2200])
+def test_prompt_rows_at_tile_edges(rows):
+    s, eng, orc = make_pair("mini-gqa", "T8", seed=11, max_seq=2300)
+    print("prompt of", rows, flush=True)
+    check_prefill(eng, orc, synth.prompt(rows, rows, s.vocab), TOL["bf16"])
+    lockstep_step(eng, orc, Stats(), TOL["bf16"])               # the head's cache of every prompt row is what drafting reads
+    eng.close()
+
+
+def test_loss_of_two_large_passes():
+    shape = synth.SHAPES["mini-gqa"]
+    eng = _engine(shape, head_loss_rows=1100)
+    Wdev, W64 = _lm_head(shape, 3)
+    eng.load_named("lm_head", Wdev)
+    f, fhat = _features(1100, shape.d_model, 9, 0.7)
+    _check(eng, W64.astype(np.float64), f, fhat, 0.1, "mini-gqa")
+    eng.close()
