@@ -119,6 +119,8 @@ struct eagle_ctx {
   // fast path (passes of <= 32 rows)
   float *h2, *PT2, *ssq1, *ssq2; int *cnt_gemm, *cnt_attn; size_t pt2_floats;
   bf16_t *xf2_d, *xf2_dB, *xf2_2d, *xf2_att, *xf2_ffn;
+  // grouped experts (general path of the bf16 models): which rows go to which expert, the gathered rows and their MLP inputs
+  MoePlan* moe_plan; int *moe_slot, *moe_row; bf16_t *xf_moe;
   RowFact* facts;                      // [Mmax] rows of the pass in flight (written by its first kernel)
   float *moe_w, *xn; int* expert_used; int* experts_touched;   // (profiling) experts used, summed over the layers of a verify    // routing weights [E][largest pass], used flags [E], fp32 normalised rows (general path)
   int ssq1_groups = 0, ssq2_groups = 0;
@@ -179,6 +181,41 @@ static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue) 
       if (!(fused_epilogue && s_real == 1)) us += (double)s_real * MT * NRB * 8192.0 / 4.5e6;
       if (fused_epilogue && s_real > 1) us += 10.0;             // the SwiGLU kernel behind it
       if (best_us < 0 || us < best_us) { best_us = us; best.S = s_real; best.ks_per_split = kps; best.chunk = 4; best.rbw = sh.rbw; best.mw = sh.mw; }
+    }
+  }
+  return best;
+}
+
+// The same model for the grouped GEMMs of a mixture of experts: M rows x topk experts each, padded per expert to columns of
+// 2 * mw tiles.  Routing is uneven, so half a column more per expert and half a round more at the end are counted.  Both GEMMs of the MLP share the column width; gate/up keeps one K slice (SwiGLU in its epilogue).
+struct PlanMoe { GemmPlan gu, dn; int cols; };
+static int moe_tiles(int M, int topk, int E) { return (M * topk + 31) / 32 + std::min(E, M * topk); }
+static PlanMoe plan_moe(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int M, int topk, int E, int n_cu) {
+  PlanMoe best{};
+  double best_us = -1;
+  static const struct { int rbw, mw; double ns; } shapes[5] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}};
+  const int used = std::min(E, M * topk), te = (M * topk + 32 * used - 1) / (32 * used), cu_x = std::max(1, n_cu / 8);
+  for (int mw = 2; mw <= 4; mw += 2) {
+    const int rt = 2 * mw;
+    const double cols = used * std::max(1.0, (double)te / rt + 0.5);
+    GemmPlan q[2] = {};
+    double us[2] = {-1, -1};
+    for (auto& sh : shapes) {
+      if (sh.mw != mw) continue;
+      for (int m = 0; m < 2; ++m) {
+        const int wt = 2 * sh.rbw, KS = m ? dn_KS : gu_KS, NRB = m ? dn_NRB : gu_NRB, nt = (NRB + wt - 1) / wt;
+        for (int S = 1; S <= (m ? 16 : 1); ++S) {
+          if (S > 1 && KS / S < 16) break;
+          const int kps = ((KS + S - 1) / S + 3) / 4 * 4, s_real = (KS + kps - 1) / kps;
+          const double full = (nt * s_real + 7) / 8 * cols / cu_x, rounds = full <= 1.0 ? 1.0 : full + 0.5;
+          const double t = 1e-3 * sh.ns * rounds * wt * std::min(rt, te) * kps + 4.0 + (m ? (double)s_real * used * te * NRB * 8192.0 / 4.5e6 : 0.0);
+          if (us[m] < 0 || t < us[m]) { us[m] = t; q[m].S = s_real; q[m].ks_per_split = kps; q[m].chunk = 4; q[m].rbw = sh.rbw; q[m].mw = mw; }
+        }
+      }
+    }
+    if (best_us < 0 || us[0] + us[1] < best_us) {
+      best_us = us[0] + us[1]; best.gu = q[0]; best.dn = q[1];
+      best.cols = std::min(M * topk, E + M * topk / (32 * rt));  // most columns any routing gives
     }
   }
   return best;
@@ -375,7 +412,13 @@ static size_t layout(eagle_ctx* c) {
   c->xf_d = a.take<bf16_t>((size_t)c->NXP * std::max(Mm, 2 * c->hl_chunk) * d);
   c->xf_2d = a.take<bf16_t>((size_t)c->NXP * Mm * 2 * d);
   c->xf_att = a.take<bf16_t>((size_t)c->NXP * Mm * H * dh);
-  c->xf_ffn = a.take<bf16_t>((size_t)c->NXP * Mm * F);
+  const bool grouped = c->big_gemm && g.n_experts > 0;
+  const int slots = grouped ? 32 * moe_tiles(Mm, g.experts_per_tok, g.n_experts) : 0;
+  c->xf_ffn = a.take<bf16_t>((size_t)c->NXP * std::max(Mm, slots) * F);
+  c->moe_plan = a.take<MoePlan>(1);
+  c->moe_slot = a.take<int>(grouped ? (size_t)g.n_experts * Mm : 1);
+  c->moe_row = a.take<int>(std::max(1, slots));
+  c->xf_moe = a.take<bf16_t>(std::max((size_t)8, (size_t)c->NXP * slots * d));
   // fast path buffers
   c->h2 = a.take<float>((size_t)32 * d);
   c->xf2_d = a.take<bf16_t>((size_t)c->NXP * 32 * d);
@@ -421,9 +464,16 @@ static size_t layout(eagle_ctx* c) {
   if (g.head_loss_rows > 0) { consider(c->lm_head, 2 * c->hl_chunk / 32, false); consider(c->lm_head_T, c->hl_chunk / 32, false); }
   consider(c->lm_head, 4, false);                               // tree and vanilla passes; a prompt needs its last row tile only
   consider(c->fc, MTm, false);
+  bool moe_seen = false;
   for (auto& w : c->layers) {
     consider(w.qkv, MTm, false); consider(w.o, MTm, false);
-    if (w.moe) { consider(w.e_gu[0], MTm, false); consider(w.e_dn[0], MTm, false); } else { consider(w.gu, MTm, true); consider(w.dn, MTm, false); }
+    if (w.moe && grouped) {
+      for (int mt = 1; mt <= MTm && !moe_seen; ++mt) {           // (the layers are alike)
+        const PlanMoe p = plan_moe(w.e_gu[0].NRB, w.e_gu[0].KS, w.e_dn[0].NRB, w.e_dn[0].KS, 32 * mt, g.experts_per_tok, g.n_experts, c->n_cu);
+        worst = std::max(worst, (size_t)p.dn.S * w.e_dn[0].Npad * 32 * moe_tiles(32 * mt, g.experts_per_tok, g.n_experts));
+      }
+      moe_seen = true;
+    } else if (w.moe) { consider(w.e_gu[0], MTm, false); consider(w.e_dn[0], MTm, false); } else { consider(w.gu, MTm, true); consider(w.dn, MTm, false); }
   }
   c->pt_floats = worst;
   c->PT = a.take<float>(worst);
@@ -730,9 +780,24 @@ static hipError_t launch_pf(eagle_ctx* c, const PackedW& w, const bf16_t* XF, in
   const dim3 grid((G + 7) / 8 * 8 * MQ), block(128 * MW);
   const double bytes = (double)w.N * w.K * c->elt;
   if (swiglu_out) return launch_k(c, c->cur_class, bytes, "k_gemm_pf<swiglu>", k_gemm_pf<RBW, MW, true>, grid, block, (size_t)0,
-                                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M);
+                                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M, (const MoePlan*)nullptr, (size_t)0, 0);
   return launch_k(c, c->cur_class, bytes, "k_gemm_pf", k_gemm_pf<RBW, MW, false>, grid, block, (size_t)0,
-                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, (bf16_t*)nullptr, M);
+                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, (bf16_t*)nullptr, M, (const MoePlan*)nullptr, (size_t)0, 0);
+}
+
+template <int RBW, int MW, bool SWIGLU>
+static hipError_t launch_pf_moe(eagle_ctx* c, const std::vector<PackedW>& w, const bf16_t* XF, int MT, const GemmPlan& p, int cols, bf16_t* act) {
+  const int G = ((w[0].NRB + 2 * RBW - 1) / (2 * RBW)) * p.S;
+  const size_t stride = w.size() > 1 ? (size_t)(w[1].w - w[0].w) : 0;
+  return launch_k(c, c->cur_class, (double)w[0].N * w[0].K * c->elt * w.size(), "k_gemm_pf<experts>", k_gemm_pf<RBW, MW, SWIGLU, true>,
+                  dim3((G + 7) / 8 * 8 * cols), dim3(128 * MW), (size_t)0, (const bf16_t*)w[0].w, XF, c->PT, w[0].NRB, w[0].KS, p.ks_per_split, p.S,
+                  w[0].Npad, MT, act, 0, (const MoePlan*)c->moe_plan, stride, cols);
+}
+template <bool SWIGLU>
+static hipError_t launch_pf_moe(eagle_ctx* c, const std::vector<PackedW>& w, const bf16_t* XF, int MT, const GemmPlan& p, int cols, bf16_t* act) {
+  if (p.mw == 4) return p.rbw == 4 ? launch_pf_moe<4, 4, SWIGLU>(c, w, XF, MT, p, cols, act) : p.rbw == 3 ? launch_pf_moe<3, 4, SWIGLU>(c, w, XF, MT, p, cols, act)
+                                                                                                : launch_pf_moe<2, 4, SWIGLU>(c, w, XF, MT, p, cols, act);
+  return p.rbw == 4 ? launch_pf_moe<4, 2, SWIGLU>(c, w, XF, MT, p, cols, act) : launch_pf_moe<3, 2, SWIGLU>(c, w, XF, MT, p, cols, act);
 }
 
 // PT <- X (XF layout, MT row tiles) times W^T.  Returns the split count through *S.
@@ -848,14 +913,32 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
   if ((rc = (c->cur_class = KC_O, gemm(c, w.o, c->xf_att, MT, &S)))) return rc;
   if ((rc = resnorm(c, M, MT, c->h, c->PT, S, w.o.Npad, nullptr, w.mlp_norm, c->xf_d, w.moe ? c->xn : nullptr))) return rc;
   if (w.moe) {
-    // top-k routed experts: every expert runs over all rows of the pass (the cost is the weight stream, not the
-    // rows); a row's result is scaled by its routing weight, which is 0 for experts it did not select
     const int E = g.n_experts;
     k_fill_u32<<<1, 64, 0, c->stream>>>((uint32_t*)c->expert_used, 0u, (size_t)E);
     LAUNCH_CHECK();
     k_router<<<M, 256, 0, c->stream>>>(c->xn, nullptr, nullptr, 0, 0.f, 0.f, nullptr, w.router, E, g.experts_per_tok, g.d_model, M, c->moe_w, c->Mmax, c->expert_used);
     LAUNCH_CHECK();
     if (c->prof_mode) { k_count_used<<<1, 64, 0, c->stream>>>(c->expert_used, E, c->experts_touched); LAUNCH_CHECK(); }
+    if (c->big_gemm) {
+      // every row goes to its own experts only: the rows are gathered by expert, the MLP of all experts is two launches, and
+      // the results are added per row in expert order.  (Every expert over all rows, row weights of 0 included, is E / topk
+      // times the matrix work and 4 launches an expert: LLaMA-sized experts, 1000 rows, 8 experts: 5.2 ms a layer.)
+      const int k = g.experts_per_tok, tiles = moe_tiles(32 * MT, k, E);
+      const PlanMoe p = plan_moe(w.e_gu[0].NRB, w.e_gu[0].KS, w.e_dn[0].NRB, w.e_dn[0].KS, 32 * MT, k, E, c->n_cu);
+      if (p.cols > MOE_MAX_COLS || (size_t)p.dn.S * w.e_dn[0].Npad * 32 * tiles > c->pt_floats) return fail(EAGLE_EINVAL, "internal: expert plan out of range");
+      k_moe_plan<<<1, 1024, 0, c->stream>>>(c->moe_w, c->Mmax, E, M, 2 * p.gu.mw, c->moe_plan, c->moe_slot, c->moe_row);
+      LAUNCH_CHECK();
+      k_moe_gather<<<dim3(tiles, (g.d_model / 16 + 15) / 16), 256, 0, c->stream>>>(c->moe_plan, c->moe_row, c->xf_d, MT, c->xf_moe, tiles, g.d_model / 16, c->NXP);
+      LAUNCH_CHECK();
+      hipError_t e = (c->cur_class = KC_GATEUP, launch_pf_moe<true>(c, w.e_gu, c->xf_moe, tiles, p.gu, p.cols, c->xf_ffn));
+      if (e == hipSuccess) e = (c->cur_class = KC_DOWN, launch_pf_moe<false>(c, w.e_dn, c->xf_ffn, tiles, p.dn, p.cols, nullptr));
+      if (e != hipSuccess) return fail(EAGLE_EHIP, "expert gemm launch failed: %s", hipGetErrorString(e));
+      k_resnorm<<<M, 256, 0, c->stream>>>(c->h, c->PT, p.dn.S, w.e_dn[0].Npad, tiles * 32, nullptr, c->h, next_gain, g.rms_eps, c->xf_d, MT, c->NXP, xout,
+                                          g.d_model, nullptr, c->moe_w, c->moe_slot, c->Mmax, E);
+      LAUNCH_CHECK();
+      return EAGLE_OK;
+    }
+    // (fp32 models: every expert over all rows; a row's result is scaled by its routing weight, 0 for experts it did not select)
     for (int e = 0; e < E; ++e) {
       if ((rc = (c->cur_class = KC_GATEUP, gemm(c, w.e_gu[e], c->xf_d, MT, &S)))) return rc;
       dim3 grid((F / 16 + 3) / 4, MT);

@@ -410,10 +410,16 @@ __device__ inline void xf_store8(bf16_t* XF, int m, int k8, int MT, int KS, int 
 // (XF layout, `act`, rows beyond M as zeros).  A row block of the fused matrix holds 16 gate rows and the 16 up rows of
 // the same features, and accumulator registers r and r + 8 of a lane are such a pair; the two lanes of an activation
 // row swap four values so that each holds 8 consecutive features = its 16 bytes of the output tile.
-template <int RBW, int MW, bool SWIGLU = false>
+// GROUPED (mixture of experts): the activation tiles are the experts' rows gathered one expert after the other (k_moe_gather),
+// every work-group column of RT tiles belongs to one expert (k_moe_plan), whose matrix starts `expert_stride` elements behind
+// the previous one's; columns beyond the last expert's end leave at once.
+constexpr int MOE_MAX_COLS = 256;
+struct MoePlan { int n_cols, pad[3]; int expert[MOE_MAX_COLS], tile0[MOE_MAX_COLS], rows[MOE_MAX_COLS]; };   // per column: expert, first tile, rows
+template <int RBW, int MW, bool SWIGLU = false, bool GROUPED = false>
 __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ XF,
-                                                           float* __restrict__ PT, int NRB, int KS, int ks_per_split, int S, int Npad,
-                                                           int MT /*32-row tiles of the pass*/, bf16_t* act, int M) {
+                                                         float* __restrict__ PT, int NRB, int KS, int ks_per_split, int S, int Npad,
+                                                         int MT /*32-row tiles of the pass*/, bf16_t* act, int M,
+                                                         const MoePlan* moe = nullptr, size_t expert_stride = 0, int MQ_grid = 0) {
   constexpr int NXP = 2, WT = 2 * RBW, RT = 2 * MW, NTILE = WT + NXP * RT, NW = 2 * MW, LPW = (NTILE + NW - 1) / NW;
   constexpr int SLOT = NTILE * 64;
   __shared__ u32x4 s0[SLOT];                                    // per k-step: WT weight tiles, then NXP planes of RT activation tiles
@@ -422,16 +428,25 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
   __shared__ u32x4 s3[SLOT];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wn = w & 1, wm = w >> 1;
   // id -> (group = (weight-row tile, split), activation-row tile)
-  const int MQ = (MT + RT - 1) / RT, NT = (NRB + WT - 1) / WT, G = NT * S;
+  const int MQ = GROUPED ? MQ_grid : (MT + RT - 1) / RT, NT = (NRB + WT - 1) / WT, G = NT * S;
   const int L = blockIdx.x, blk = L / (8 * MQ), rem = L % (8 * MQ), mq = rem >> 3, g = blk * 8 + (rem & 7);
   if (g >= G) return;
+  // this column's tiles [tile0, tile_end) and rows [.., row_end)
+  int tile0 = mq * RT, tile_end = min(MT, tile0 + RT), row_end = M;
+  if constexpr (GROUPED) {
+    if (mq >= moe->n_cols) return;
+    tile0 = moe->tile0[mq];
+    row_end = tile0 * 32 + moe->rows[mq];
+    tile_end = (row_end + 31) >> 5;
+    Wp += (size_t)moe->expert[mq] * expert_stride;
+  }
   const int nt = g / S, s = g % S;
   const int k_begin = s * ks_per_split, k_end = min(KS, k_begin + ks_per_split);
   if (k_end <= k_begin) return;
   const int klast = k_end - 1;
-  const int rb0 = nt * WT + wn * RBW, mt0 = mq * RT + wm * 2;
+  const int rb0 = nt * WT + wn * RBW, mt0 = tile0 + wm * 2;
   // a wave whose activation tiles or row blocks all lie beyond the end moves data and keeps the barriers, but multiplies nothing
-  const bool busy = mt0 < MT && rb0 < NRB;
+  const bool busy = mt0 < tile_end && rb0 < NRB;
   // the tiles this wave loads, the same number in every wave (the last tile is loaded more than once where they do not divide)
   const bf16_t* src[LPW];
   int dst[LPW];
@@ -439,7 +454,7 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
   for (int u = 0; u < LPW; ++u) {
     const int i = min(w + u * NW, NTILE - 1);
     if (i < WT) src[u] = Wp + (size_t)min(nt * WT + i, NRB - 1) * KS * 512;
-    else src[u] = XF + (size_t)((i - WT) / RT * MT + min(mq * RT + (i - WT) % RT, MT - 1)) * KS * 512;
+    else src[u] = XF + (size_t)((i - WT) / RT * MT + min(tile0 + (i - WT) % RT, tile_end - 1)) * KS * 512;
     dst[u] = i * 64;
   }
   // (k-steps beyond the end are clamped, so that the number of loads in flight is the same on every path)
@@ -513,13 +528,13 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const int mt = mt0 + t;
-        if (mt >= MT) continue;
+        if (mt >= tile_end) continue;
         const int m = mt * 32 + (lane & 31);
         float v[8];                                             // features 4hh + {0..3} and 8 + 4hh + {0..3} of the block
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
           const float gs = acc[j][t][r], us = acc[j][t][r + 8];
-          v[r] = m < M ? gs / (1.0f + __expf(-gs)) * us : 0.f;
+          v[r] = m < row_end ? gs / (1.0f + __expf(-gs)) * us : 0.f;
         }
         float x[8];
 #pragma unroll
@@ -541,7 +556,7 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int mt = mt0 + t;
-      if (mt >= MT) continue;
+      if (mt >= tile_end) continue;
       float* out = PT + ((size_t)s * Mpad + mt * 32 + (lane & 31)) * Npad + (size_t)rb * 32 + 4 * (lane >> 5);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -645,10 +660,26 @@ __global__ __launch_bounds__(256) void k_fc_input(Pass pass, const TreeDev* tree
 // x goes out in XF layout (GEMM input) and, optionally, as fp32 rows (features).  One block per row.
 __global__ __launch_bounds__(256) void k_resnorm(const float* h_in, const float* __restrict__ PT, int S, int Npad, int Mpad,
                                                  const float* bias, float* h_out, const float* gain, float eps,
-                                                 bf16_t* XF, int MT, int nplanes, float* xout, int d, const float* row_w) {
+                                                 bf16_t* XF, int MT, int nplanes, float* xout, int d, const float* row_w,
+                                                 const float* moe_w = nullptr, const int* moe_slot = nullptr, int moe_stride = 0, int E = 0) {
   __shared__ float sh[16];
+  __shared__ float pick_w[4];                    // grouped experts: weight and gathered row of each expert of this row, ascending
+  __shared__ int pick_s[4], n_pick;
   int r = blockIdx.x;
   float ss = 0.f;
+  if (moe_slot) {
+    if (threadIdx.x < 64) {                      // one wave looks at (at most 64) experts
+      const int e = threadIdx.x;
+      const int slot = e < E ? moe_slot[(size_t)e * moe_stride + r] : -1;
+      const unsigned long long sel = __ballot(slot >= 0);
+      if (slot >= 0) {
+        const int at = __popcll(sel & ((1ull << e) - 1ull));
+        pick_s[at] = slot; pick_w[at] = moe_w[(size_t)e * moe_stride + r];
+      }
+      if (e == 0) n_pick = __popcll(sel);
+    }
+    __syncthreads();
+  }
   // each thread owns chunks of 8 consecutive k; the first four chunks (rows of up to 8192 columns) stay in registers
   // for the second phase, further ones are read back from h_out
   constexpr int KEEP = 4;
@@ -656,6 +687,37 @@ __global__ __launch_bounds__(256) void k_resnorm(const float* h_in, const float*
   const float rw = row_w ? row_w[r] : 1.0f;    // MoE: this expert's routing weight for the row (0 = not routed here)
   auto phase1 = [&](int k8, float* v) {
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (moe_slot) {
+      float x[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) x[t] = h_in[(size_t)r * d + k8 + t];
+      for (int j = 0; j < n_pick; ++j) {
+        float b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < S; s0 += 4) {
+          f32x4 lo[4], hi[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float* src = PT + ((size_t)min(s0 + u, S - 1) * Mpad + pick_s[j]) * Npad + k8;
+            lo[u] = *(const f32x4*)src; hi[u] = *(const f32x4*)(src + 4);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (s0 + u < S) {
+              b[0] += lo[u].x; b[1] += lo[u].y; b[2] += lo[u].z; b[3] += lo[u].w;
+              b[4] += hi[u].x; b[5] += hi[u].y; b[6] += hi[u].z; b[7] += hi[u].w;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] += pick_w[j] * b[t];
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        h_out[(size_t)r * d + k8 + t] = x[t];
+        ss += x[t] * x[t];
+        v[t] = x[t];
+      }
+      return;
+    }
     if (PT) {
       for (int s0 = 0; s0 < S; s0 += 8) {        // eight splits' worth of loads in flight, added in split order
         f32x4 lo[8], hi[8];
@@ -1395,7 +1457,7 @@ __global__ __launch_bounds__(256) void k_router(const float* xnorm, const float*
                                                 float eps, const float* gain, const float* __restrict__ router, int E, int topk,
                                                 int d, int M, float* moe_w, int row_stride, int* expert_used) {
   __shared__ float sh[16];
-  __shared__ float lg[64];
+  __shared__ float lg[64], lgw[4][64];           // 256 threads: four waves
   const int r = blockIdx.x;
   float rstd = 1.f;
   if (!xnorm) {                                  // same class order as every other consumer of these partial sums
@@ -1417,25 +1479,41 @@ __global__ __launch_bounds__(256) void k_router(const float* xnorm, const float*
     rstd = 1.0f / sqrtf(tot * inv_d + eps);
     __syncthreads();                             // sh is reused by block_sum below
   }
-  for (int e = 0; e < E; ++e) {
-    float a = 0.f;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) {
-      const float x = xnorm ? xnorm[(size_t)r * d + k] : h[(size_t)r * d + k] * rstd * gain[k];
-      a += x * router[(size_t)e * d + k];
+  // a thread walks its columns once for eight experts at a time (the row and eight router rows in flight together); the
+  // waves' sums meet in LDS once for all of them.  (One expert after the other, each with a block-wide sum of its own: 62 us a
+  // call at 8 experts and 4096 columns.)
+  for (int e0 = 0; e0 < E; e0 += 8) {
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int k = threadIdx.x * 4; k < d; k += blockDim.x * 4) {   // d is a multiple of 64
+      f32x4 x;
+      if (xnorm) x = *(const f32x4*)(xnorm + (size_t)r * d + k);
+      else { x = *(const f32x4*)(h + (size_t)r * d + k) * rstd; x *= *(const f32x4*)(gain + k); }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const f32x4 w = *(const f32x4*)(router + (size_t)min(e0 + j, E - 1) * d + k);
+        a[j] += x.x * w.x + x.y * w.y + x.z * w.z + x.w * w.w;
+      }
     }
-    a = block_sum(a, sh);
-    if (threadIdx.x == 0) lg[e] = a;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      for (int o = 32; o > 0; o >>= 1) a[j] += __shfl_xor(a[j], o, 64);
+      if ((threadIdx.x & 63) == 0 && e0 + j < E) lgw[threadIdx.x >> 6][e0 + j] = a[j];
+    }
   }
+  __syncthreads();
+  if (threadIdx.x < 64) lg[threadIdx.x] = (lgw[0][threadIdx.x] + lgw[1][threadIdx.x]) + (lgw[2][threadIdx.x] + lgw[3][threadIdx.x]);
   __syncthreads();
   if (threadIdx.x == 0) {
     int sel[4];
     float sv[4];
     for (int j = 0; j < topk; ++j) {
-      float bv = -INFINITY; int bi = 0x7fffffff;
+      float bv = -INFINITY; int bi = -1;           // (the first free expert where no logit compares: a row of NaN stays one)
       for (int e = 0; e < E; ++e) {
         bool taken = false;
         for (int q = 0; q < j; ++q) taken |= (sel[q] == e);
-        if (!taken) better(bv, bi, lg[e], e);
+        if (taken) continue;
+        if (bi < 0) { bv = lg[e]; bi = e; }
+        else better(bv, bi, lg[e], e);
       }
       sel[j] = bi; sv[j] = bv;
     }
@@ -1448,6 +1526,67 @@ __global__ __launch_bounds__(256) void k_router(const float* xnorm, const float*
     }
   }
 }
+
+// Groups the rows of a pass by expert for the grouped GEMMs: expert e's rows, ascending, take consecutive slots from the first
+// free tile on, whole columns of `rt` 32-row tiles each.  slot_of[e][row] = slot or -1, row_of[slot] = row or -1 (the rest of an
+// expert's last tile).  One work-group; a wave per expert, 64 rows at a time.
+__global__ __launch_bounds__(1024) void k_moe_plan(const float* __restrict__ moe_w, int row_stride, int E, int M, int rt, MoePlan* plan, int* slot_of, int* row_of) {
+  __shared__ int cnt[64], first[64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int e = w; e < E; e += 16) {
+    int n = 0;
+    for (int r0 = 0; r0 < M; r0 += 64) n += __popcll(__ballot(r0 + lane < M && moe_w[(size_t)e * row_stride + r0 + lane] != 0.f));
+    if (lane == 0) cnt[e] = n;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int tile = 0, cols = 0;
+    for (int e = 0; e < E; ++e) {
+      first[e] = tile * 32;
+      for (int r = 0; r < cnt[e]; r += 32 * rt, ++cols) {
+        plan->expert[cols] = e; plan->tile0[cols] = tile; plan->rows[cols] = min(cnt[e] - r, 32 * rt);
+        tile += min(rt, (cnt[e] - r + 31) / 32);
+      }
+    }
+    plan->n_cols = cols;
+  }
+  __syncthreads();
+  for (int e = w; e < E; e += 16) {
+    int at = first[e];
+    for (int r0 = 0; r0 < M; r0 += 64) {
+      const int r = r0 + lane;
+      const bool mine = r < M && moe_w[(size_t)e * row_stride + r] != 0.f;
+      const unsigned long long m = __ballot(mine);
+      const int slot = at + __popcll(m & ((1ull << lane) - 1ull));
+      if (r < M) slot_of[(size_t)e * row_stride + r] = mine ? slot : -1;
+      if (mine) row_of[slot] = r;
+      at += __popcll(m);
+    }
+    for (int q = at + lane; q < (at + 31) / 32 * 32; q += 64) row_of[q] = -1;
+  }
+}
+
+// The experts' rows as one GEMM input: tile t of the output (32 slots) holds rows row_of[32 t ..] of XF; slots without a row are
+// zero.  A wave copies four k-steps of a tile, both planes (16 bytes a lane and k-step).  Grid (tiles, k-steps / 16).
+__global__ __launch_bounds__(256) void k_moe_gather(const MoePlan* __restrict__ plan, const int* __restrict__ row_of, const bf16_t* __restrict__ XF, int MT,
+                                                    bf16_t* __restrict__ out, int MT_out, int KS, int nplanes) {
+  const int last = plan->n_cols - 1, t = blockIdx.x;
+  if (last < 0 || t >= plan->tile0[last] + (plan->rows[last] + 31) / 32) return;
+  const int lane = threadIdx.x & 63, ks0 = blockIdx.y * 16 + (threadIdx.x >> 6) * 4;
+  const int row = row_of[t * 32 + (lane & 31)];
+  for (int q = 0; q < nplanes; ++q) {
+    u32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      v[u] = u32x4{0u, 0u, 0u, 0u};
+      if (row >= 0 && ks0 + u < KS) v[u] = *(const u32x4*)(XF + xf_index(row, 16 * (ks0 + u) + 8 * (lane >> 5), q, MT, KS));
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (ks0 + u < KS) *(u32x4*)(out + (((size_t)q * MT_out + t) * KS + ks0 + u) * 512 + lane * 8) = v[u];
+  }
+}
+
 
 // ============================================================================ debug / test access
 template <typename CT>

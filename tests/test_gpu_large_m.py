@@ -1,5 +1,5 @@
 """The large-M GEMM (k_gemm_pf) at the edges of its tiles: prompt passes whose rows end inside a 32-row tile, inside a work-group
-tile (4 or 8 row tiles), at a window of 512 rows, and beyond one pass of 2048; a loss pass of more than 1024 rows.  Against the
+tile (4 or 8 row tiles), at a window of 512 rows, and beyond one pass of 2048; rows grouped by expert; a loss pass of more than 1024 rows.  Against the
 CPU oracle in fp64."""
 import numpy as np
 import pytest
@@ -18,6 +18,16 @@ def test_prompt_rows_at_tile_edges(rows):
     print("prompt of", rows, flush=True)
     check_prefill(eng, orc, synth.prompt(rows, rows, s.vocab), TOL["bf16"])
     lockstep_step(eng, orc, Stats(), TOL["bf16"])               # the head's cache of every prompt row is what drafting reads
+    eng.close()
+
+
+@pytest.mark.parametrize("rows", [1, 7, 33, 64, 131, 513, 1100])
+def test_expert_rows_grouped(rows):
+    """Experts with no row, a few rows, and several tiles of rows; the grouped MLP adds a row's experts in ascending order."""
+    s, eng, orc = make_pair("mini-moe", "T8", seed=12, max_seq=1200)
+    print("prompt of", rows, flush=True)
+    check_prefill(eng, orc, synth.prompt(rows + 5, rows, s.vocab), TOL["bf16"])
+    lockstep_step(eng, orc, Stats(), TOL["bf16"])
     eng.close()
 
 
