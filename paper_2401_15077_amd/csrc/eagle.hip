@@ -119,6 +119,7 @@ struct eagle_ctx {
   // fast path (passes of <= 32 rows)
   float *h2, *PT2, *ssq1, *ssq2; int *cnt_gemm, *cnt_attn; size_t pt2_floats;
   bf16_t *xf2_d, *xf2_dB, *xf2_2d, *xf2_att, *xf2_ffn;
+  float* group_sums;                   // 4-bit weights: -24 * sum of x per (group of 128 columns, row) of the GEMM input at hand
   // grouped experts (general path of the bf16 models): which rows go to which expert, the gathered rows and their MLP inputs
   MoePlan* moe_plan; int *moe_slot, *moe_row; bf16_t *xf_moe;
   RowFact* facts;                      // [Mmax] rows of the pass in flight (written by its first kernel)
@@ -156,8 +157,8 @@ static GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
 }
 
 // Which passes of the general path take the large-M GEMM: every pass of more than 128 rows (only prompts, and only
-// where the kernel exists), and batched tree passes of 65..128 rows of the models it covers.
-static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c->big_gemm); }
+// where the kernel exists), and batched tree passes of 65..128 rows of the models it covers; with 4-bit weights all.
+static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c->big_gemm) || c->q4; }
 
 // Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
 // in a model of two terms, in us.  What the busiest CU multiplies: rounds x (32 x 32 tiles of a work-group) x k-steps of a slice
@@ -165,17 +166,19 @@ static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c-
 // round is full when the XCD with one group more than the others is (LM-head transpose, 10 row tiles, 3 slices of 27 x 3
 // tiles: 243 work-groups, but 33 on the 32 CUs of one XCD: 355 us against 197 for 240 of the next shape).  And what the partial
 // sums cost that all but the fused epilogue write and read back, at 4.5 TB/s.
-static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue) {
+// 4-bit weights (k_gemm_pf_q4): two row blocks per wave, K slices of whole groups of 8 k-steps.
+static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4) {
   GemmPlan best{};
   double best_us = -1;
-  static const struct { int rbw, mw; double ns; } shapes[5] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}};
+  static const struct { int rbw, mw; double ns; } shapes[7] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}, {2, 4, 17.0}};
   const int xcds = 8, cu_x = std::max(1, n_cu / xcds);
-  for (auto& sh : shapes) {
+  for (int i = q4 ? 5 : 0; i < (q4 ? 7 : 5); ++i) {
+    const auto& sh = shapes[i];
     const int wt = 2 * sh.rbw, rt = 2 * sh.mw, mq = (MT + rt - 1) / rt, nt = (NRB + wt - 1) / wt;
     if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
     for (int S = 1; S <= 16; ++S) {
       if (S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
-      const int kps = ((KS + S - 1) / S + 3) / 4 * 4, s_real = (KS + kps - 1) / kps;
+      const int unit = q4 ? 8 : 4, kps = ((KS + S - 1) / S + unit - 1) / unit * unit, s_real = (KS + kps - 1) / kps;
       const int rounds = ((nt * s_real + xcds - 1) / xcds * mq + cu_x - 1) / cu_x;
       double us = 1e-3 * sh.ns * rounds * wt * rt * kps + 4.0;
       if (!(fused_epilogue && s_real == 1)) us += (double)s_real * MT * NRB * 8192.0 / 4.5e6;
@@ -415,6 +418,8 @@ static size_t layout(eagle_ctx* c) {
   const bool grouped = c->big_gemm && g.n_experts > 0;
   const int slots = grouped ? 32 * moe_tiles(Mm, g.experts_per_tok, g.n_experts) : 0;
   c->xf_ffn = a.take<bf16_t>((size_t)c->NXP * std::max(Mm, slots) * F);
+  // (the last column of row tiles may read up to 7 tiles beyond the end)
+  c->group_sums = a.take<float>(c->q4 ? (size_t)std::max(std::max(F, H * dh), 2 * d) / EAGLE_Q4_GROUP * Mm + 256 : 1);
   c->moe_plan = a.take<MoePlan>(1);
   c->moe_slot = a.take<int>(grouped ? (size_t)g.n_experts * Mm : 1);
   c->moe_row = a.take<int>(std::max(1, slots));
@@ -456,7 +461,7 @@ static size_t layout(eagle_ctx* c) {
     for (const Seen& q : seen) if (q.NRB == w.NRB && q.KS == w.KS && q.mt_max == mt_max && q.fused == fused) return;
     seen.push_back(Seen{w.NRB, w.KS, mt_max, fused});
     for (int mt = 1; mt <= mt_max; ++mt) {
-      const GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu, fused) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
+      const GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu, fused, c->q4) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
       if (fused && use_pf(c, mt) && p.S == 1) continue;          // SwiGLU inside the GEMM: nothing goes through memory
       worst = std::max(worst, (size_t)p.S * w.Npad * (size_t)(mt * 32));
     }
@@ -523,12 +528,14 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
     c->pf_chunk = std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + EAGLE_PREFILL_WINDOW - 1) / EAGLE_PREFILL_WINDOW * EAGLE_PREFILL_WINDOW);
   }
   if (c->q4) {
-    // 4-bit weights exist in the fused kernels of the fast path only: every pass has at most 32 rows, the prompt included
+    // 4-bit weights: tree and vanilla passes exist in the fused kernels of the fast path only (at most 32 rows); prompt passes of
+    // more rows take the large-M GEMM
     if (c->f32 || cfg->n_experts > 0) return fail(EAGLE_EINVAL, "weight_bits = 4 needs a dense bf16 model");
     if (cfg->d_model % EAGLE_Q4_GROUP || cfg->d_ffn % EAGLE_Q4_GROUP || (cfg->n_heads * cfg->head_dim) % EAGLE_Q4_GROUP)
       return fail(EAGLE_EINVAL, "weight_bits = 4 needs d_model, d_ffn and n_heads * head_dim to be multiples of %d", EAGLE_Q4_GROUP);
     if (cfg->max_batch * c->M > 32 || cfg->max_batch * (c->D + 1) > 32) return fail(EAGLE_EINVAL, "weight_bits = 4: max_batch * n_nodes and max_batch * (depth + 1) must not exceed 32 rows");
-    c->pf_chunk = c->pf_window = 32;
+    c->pf_window = 32;
+    c->pf_chunk = std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + 31) / 32 * 32);
   }
   int rows = std::max(c->pf_chunk, cfg->max_batch * c->M);
   c->Mmax = (rows + 31) / 32 * 32;
@@ -800,18 +807,31 @@ static hipError_t launch_pf_moe(eagle_ctx* c, const std::vector<PackedW>& w, con
   return p.rbw == 4 ? launch_pf_moe<4, 2, SWIGLU>(c, w, XF, MT, p, cols, act) : launch_pf_moe<3, 2, SWIGLU>(c, w, XF, MT, p, cols, act);
 }
 
+template <int MW>
+static hipError_t launch_pf_q4(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, const GemmPlan& p, bf16_t* swiglu_out, int M) {
+  const int MQ = (MT + 2 * MW - 1) / (2 * MW), G = ((w.NRB + 3) / 4) * p.S;
+  return launch_k(c, c->cur_class, w.bytes(c->elt), "k_gemm_pf<4-bit weights>", swiglu_out ? k_gemm_pf_q4<MW, true> : k_gemm_pf_q4<MW, false>,
+                  dim3((G + 7) / 8 * 8 * MQ), dim3(128 * MW), (size_t)0, (const u32x4*)w.w, (const bf16_t*)w.sc, XF, (const float*)c->group_sums, c->PT, w.NRB, w.KS,
+                  p.ks_per_split / 8, p.S, w.Npad, MT, swiglu_out, M);
+}
+
 // PT <- X (XF layout, MT row tiles) times W^T.  Returns the split count through *S.
 // swiglu_out (gate/up matrices only): where the plan has a single K slice in the large-M kernel, the SwiGLU epilogue runs
 // inside the GEMM and its output goes to swiglu_out in GEMM-input layout; *S is then 0 (nothing left in PT).
 static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S, bf16_t* swiglu_out = nullptr, int M = 0) {
   const bool big = use_pf(c, MT);
-  GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu, swiglu_out != nullptr) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
+  GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu, swiglu_out != nullptr, c->q4) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
   const bool fuse = big && swiglu_out && p.S == 1;
   if (!fuse && (size_t)p.S * w.Npad * MT * 32 > c->pt_floats) return fail(EAGLE_EINVAL, "internal: partial buffer too small");
   if (MT < 1 || MT * 32 > std::max(c->Mmax, 2 * c->hl_chunk) || (big && c->f32)) return fail(EAGLE_EINVAL, "internal: MT out of range");
   *S = fuse ? 0 : p.S;
   hipError_t e;
-  if (big) {
+  if (w.q4) {
+    bf16_t* out = fuse ? swiglu_out : nullptr;
+    k_group_sums<<<dim3(MT, (w.NG + 3) / 4), 256, 0, c->stream>>>(XF, c->group_sums, MT, w.KS, c->NXP);
+    LAUNCH_CHECK();
+    e = p.mw == 4 ? launch_pf_q4<4>(c, w, XF, MT, p, out, M) : launch_pf_q4<2>(c, w, XF, MT, p, out, M);
+  } else if (big) {
     bf16_t* out = fuse ? swiglu_out : nullptr;
     if (p.mw == 4) e = p.rbw == 4 ? launch_pf<4, 4>(c, w, XF, MT, p, out, M) : p.rbw == 3 ? launch_pf<3, 4>(c, w, XF, MT, p, out, M) : launch_pf<2, 4>(c, w, XF, MT, p, out, M);
     else e = p.rbw == 4 ? launch_pf<4, 2>(c, w, XF, MT, p, out, M) : launch_pf<3, 2>(c, w, XF, MT, p, out, M);
@@ -971,6 +991,8 @@ static int lm_head(eagle_ctx* c, const Pass& pass, int M, int MT, float* out, in
   return EAGLE_OK;
 }
 
+static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out, const bf16_t* XF = nullptr);
+
 // Target model over the rows of `pass`: embedding -> layers -> final norm (= features) -> LM head.
 static int target_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, bool want_logits, float* logits_out, int out_kind, int only_last_row) {
   const eagle_config& g = c->cfg;
@@ -993,6 +1015,11 @@ static int target_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, 
     if ((rc = resnorm(c, nr, 1, c->featbuf + (size_t)row0 * g.d_model, nullptr, 0, 0, nullptr, nullptr, c->xf_2d, nullptr))) return rc;
     Pass sub = pass;
     sub.rows_per_seq = nr; sub.chunk_start = pass.chunk_start + row0; sub.chunk_n = nr;
+    if (c->q4) {
+      k_row_facts<<<1, 64, 0, c->stream>>>(sub, c->tree_d, c->st, nr, kv_for(c, 0), c->facts);
+      LAUNCH_CHECK();
+      return lm_head2(c, sub, nr, false, logits_out, c->xf_2d);
+    }
     return lm_head(c, sub, nr, 1, logits_out, out_kind, only_last_row, c->xf_2d);
   }
   if (want_logits) return lm_head(c, pass, M, MT, logits_out, out_kind, only_last_row);
@@ -1288,11 +1315,11 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
   return (c->cur_class = KC_DOWN, gemm2(c, w.dn, c->xf2_ffn, g, &c->ssq2_groups));
 }
 
-static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out) {
+static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out, const bf16_t* XF) {
   Gemm2 g = gemm2_base(c, pass, M);
   g.epi = EPI_LOGITS; g.logits = out; g.V = c->cfg.vocab;
   if (scaled) g.in_scale = scale_of(c, c->ssq2, c->ssq2_groups);
-  return (c->cur_class = KC_LMHEAD, gemm2(c, c->lm_head, c->xf2_d, g, nullptr));
+  return (c->cur_class = KC_LMHEAD, gemm2(c, c->lm_head, XF ? XF : c->xf2_d, g, nullptr));
 }
 
 static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new, float* logits_out, bool want_logits = true) {
@@ -1372,7 +1399,7 @@ extern "C" int eagle_prefill(eagle_ctx* c, int32_t seq, const int32_t* prompt, i
     const bool last = start + cn == n;
     c->last_off = (cn - 1) / c->pf_window * c->pf_window; c->last_rows = cn - c->last_off;
     Pass pt{PASS_PREFILL_T, cn, 1, seq, 0, start, cn};
-    const bool fast = cn <= 32 && c->q4;     // 4-bit weights: the prompt walks through the fused kernels 32 rows at a time
+    const bool fast = cn <= 32 && c->q4;     // 4-bit weights: a short prompt takes the fused kernels
     if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, last)
                    : target_forward(c, pt, start + cn, cn, last, c->vanilla_logits, 1, 1))) return rc;
     if (last) {

@@ -231,12 +231,21 @@ __global__ __launch_bounds__(256) void k_pack_weight(const SrcT* __restrict__ sr
 // Weight-only, symmetric, groups of 128 input columns: s = bf16(max|w| / 7), code = clip(rint(w / s), -8, 7) + 8, value
 // s * (code - 8).  Layout: "super-tiles" of 32 rows x 64 k = 1 KiB, tile (rb, T) at ((rb*KT + T) * 64) 16-byte lane
 // chunks (KT = K / 64); lane l (row l%32, k-half l/32) holds four 32-bit words, word j = the 8 codes of k-step j of
-// the super-tile, k = 64T + 16j + 8(l/32) + e, with code e at bit 4*(e/2) + 16*(e%2): ((word >> 4p) & 0x000F000F) |
-// 0x43004300 is then the bf16 pair (128 + code 2p, 128 + code 2p+1), i.e. the MFMA A operand of the k-step comes out of
-// one shift and one and-or per pair (128 + c is exact in bf16; the offset 136 = 128 + 8 is taken off per group).
+// the super-tile, k = 64T + 16j + 8(l/32) + e, with code e at bit 4*(e/2) + 16*(e%2), the word then rotated left by 3:
+// ((word rotated right by 4p) & 0x00780078) | 0x41804180 is then the bf16 pair (16 + code 2p, 16 + code 2p+1), i.e. the MFMA A
+// operand of the k-step comes out of one shift and one and-or per pair (16 + c is exact in bf16; the offset 24 = 16 + 8 is
+// taken off per group: the smallest that leaves room for four bits, so that as little as possible cancels).
 // Scales: bf16 [rb][group][lane-half][16] in accumulator-register order: entry (hh, r) belongs to row
 // 8*(r/4) + 4*hh + r%4 of the block, so a lane reads the scales of its 16 accumulator rows as 32 contiguous bytes.
 #define EAGLE_Q4_GROUP 128
+__device__ __forceinline__ u32x4 q4_expand(uint32_t wd) {
+  u32x4 v;
+  v.x = (wd & 0x00780078u) | 0x41804180u;
+  v.y = ((wd >> 4) & 0x00780078u) | 0x41804180u;
+  v.z = ((wd >> 8) & 0x00780078u) | 0x41804180u;
+  v.w = (__builtin_amdgcn_alignbit(wd, wd, 12) & 0x00780078u) | 0x41804180u;   // (the last high code straddles the word's end)
+  return v;
+}
 template <typename SrcT>
 __global__ __launch_bounds__(256) void k_pack_weight_q4(const SrcT* __restrict__ src, uint32_t* __restrict__ dst, bf16_t* __restrict__ sc,
                                                         int N, int K, int row_offset, int mode, int dh) {
@@ -271,7 +280,7 @@ __global__ __launch_bounds__(256) void k_pack_weight_q4(const SrcT* __restrict__
           const float q = fminf(fmaxf(rintf(w[64 * st + 16 * j + 8 * kh + e] / safe), -8.f), 7.f);
           wd |= (uint32_t)((int)q + 8) << (4 * (e >> 1) + 16 * (e & 1));
         }
-        words[j] = wd;
+        words[j] = (wd << 3) | (wd >> 29);
       }
       u32x4 v; v.x = words[0]; v.y = words[1]; v.z = words[2]; v.w = words[3];
       *(u32x4*)(dst + (((size_t)rb * KT + T) * 64 + rho + 32 * kh) * 4) = v;
@@ -406,10 +415,64 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ Wp, siz
 // XCD's L2 afterwards.
 // Every K range is a multiple of 4 k-steps (host).
 __device__ inline void xf_store8(bf16_t* XF, int m, int k8, int MT, int KS, int nplanes, const float* x);   // defined with the row producers below
-// SWIGLU (only with S = 1, gate/up matrices): instead of PT the kernel writes silu(gate) * up as the next GEMM's input
-// (XF layout, `act`, rows beyond M as zeros).  A row block of the fused matrix holds 16 gate rows and the 16 up rows of
-// the same features, and accumulator registers r and r + 8 of a lane are such a pair; the two lanes of an activation
-// row swap four values so that each holds 8 consecutive features = its 16 bytes of the output tile.
+// What both large-M GEMMs do with a wave's accumulators (row blocks rb0.., tiles mt0, mt0 + 1 below tile_end, rows below row_end).
+// SWIGLU (only with S = 1, gate/up matrices): silu(gate) * up as the next GEMM's input (XF layout, `act`, rows beyond the end as
+// zeros).  A row block of the fused matrix holds 16 gate rows and the 16 up rows of the same features, and accumulator registers
+// r and r + 8 of a lane are such a pair; the two lanes of an activation row swap four values so that each holds 8 consecutive
+// features = its 16 bytes of the output tile.
+template <int RBW, bool SWIGLU>
+__device__ __forceinline__ void pf_store(f32x16 (&acc)[RBW][2], float* __restrict__ PT, int s, int NRB, int Npad, int MT, bf16_t* act, int rb0, int mt0, int tile_end, int row_end) {
+  constexpr int NXP = 2;
+  const int lane = threadIdx.x & 63;
+  // accumulator register r of lane l: weight row 8*(r/4) + 4*(l/32) + r%4, activation row l%32; PT[s][m][n], n fastest
+  if constexpr (SWIGLU) {
+    const int hh = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < RBW; ++j) {
+      const int rb = rb0 + j;
+      if (rb >= NRB) continue;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int mt = mt0 + t;
+        if (mt >= tile_end) continue;
+        const int m = mt * 32 + (lane & 31);
+        float v[8];                                             // features 4hh + {0..3} and 8 + 4hh + {0..3} of the block
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const float gs = acc[j][t][r], us = acc[j][t][r + 8];
+          v[r] = m < row_end ? gs / (1.0f + __expf(-gs)) * us : 0.f;
+        }
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float got = __shfl_xor(hh ? v[i] : v[4 + i], 32, 64);   // the partner's features 4..7 (for hh = 0) or 8..11 (for hh = 1)
+          x[i] = hh ? got : v[i];
+          x[4 + i] = hh ? v[4 + i] : got;
+        }
+        xf_store8(act, m, 16 * rb + 8 * hh, MT, NRB, NXP, x);
+      }
+    }
+    return;
+  }
+  const int Mpad = MT * 32;
+#pragma unroll
+  for (int j = 0; j < RBW; ++j) {
+    const int rb = rb0 + j;
+    if (rb >= NRB) continue;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int mt = mt0 + t;
+      if (mt >= tile_end) continue;
+      float* out = PT + ((size_t)s * Mpad + mt * 32 + (lane & 31)) * Npad + (size_t)rb * 32 + 4 * (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4 v; v.x = acc[j][t][4 * i]; v.y = acc[j][t][4 * i + 1]; v.z = acc[j][t][4 * i + 2]; v.w = acc[j][t][4 * i + 3];
+        *(f32x4*)(out + 8 * i) = v;
+      }
+    }
+  }
+}
+
 // GROUPED (mixture of experts): the activation tiles are the experts' rows gathered one expert after the other (k_moe_gather),
 // every work-group column of RT tiles belongs to one expert (k_moe_plan), whose matrix starts `expert_stride` elements behind
 // the previous one's; columns beyond the last expert's end leave at once.
@@ -518,56 +581,190 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
 #undef PF_WAITV
 #undef PF_BAR
   if (!busy) return;
-  // accumulator register r of lane l: weight row 8*(r/4) + 4*(l/32) + r%4, activation row l%32; PT[s][m][n], n fastest
-  if constexpr (SWIGLU) {
-    const int hh = lane >> 5;
+  pf_store<RBW, SWIGLU>(acc, PT, s, NRB, Npad, MT, act, rb0, mt0, tile_end, row_end);
+}
+
+// ---- the same over 4-bit weights (layout: k_pack_weight_q4) -----------------------------------------------------------------
+// A wave owns 2 row blocks x 2 activation tiles.  Per group of 8 k-steps the MFMAs sum (16 + code) x into `part` (the codes become
+// bf16 with one shift and one and-or per pair, beside the MFMAs), and the group is folded into the result in fp32:
+// acc += scale * (part - 24 * sum of x).  The activations pass through the four-slot ring of k_gemm_pf; the codes of four k-steps (one
+// 1 KiB tile per row block) through two slots; the group's scales and its sums of x (-24 times them: k_group_sums) through one
+// slot each, requested at the group's first step and read behind its last.  Loads in flight are counted: step i waits for all
+// but the loads of the two steps before it.  K ranges are whole groups (host).
+// Bound: the matrix pipes; 8 MFMAs a k-step and wave, 16 more registers of sums than k_gemm_pf's 8-MFMA shape allow no more.
+// (The prompt used to walk through the decoding kernels 32 rows at a time, every pass streaming all codes: 3.2 ms per 32 rows
+// at 7B widths.)
+template <int MW, bool SWIGLU>
+__global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf_q4(const u32x4* __restrict__ Wq, const bf16_t* __restrict__ SC, const bf16_t* __restrict__ XF,
+                                                            const float* __restrict__ SX, float* __restrict__ PT, int NRB, int KS, int groups_per_split,
+                                                            int S, int Npad, int MT, bf16_t* act, int M) {
+  constexpr int RBW = 2, NXP = 2, WT = 2 * RBW, RT = 2 * MW, NW = 2 * MW, XT = NXP * RT, LPW = XT / NW;
+  __shared__ u32x4 s0[XT * 64];
+  __shared__ u32x4 s1[XT * 64];
+  __shared__ u32x4 s2[XT * 64];
+  __shared__ u32x4 s3[XT * 64];
+  __shared__ u32x4 c0[WT * 64];                                 // codes of the group's first / second four k-steps
+  __shared__ u32x4 c1[WT * 64];
+  __shared__ u32x4 scl[64];                                     // the group's scales: [WT row blocks][2 lane halves][16] bf16
+  __shared__ u32x4 sxs[64];                                     // -24 * sum of x over the group: [RT * 32 rows] fp32
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wn = w & 1, wm = w >> 1, hh = lane >> 5;
+  const int MQ = (MT + RT - 1) / RT, NT = (NRB + WT - 1) / WT, G = NT * S, NG = KS / 8, KT = KS / 4;
+  const int L = blockIdx.x, blk = L / (8 * MQ), rem = L % (8 * MQ), mq = rem >> 3, g = blk * 8 + (rem & 7);
+  if (g >= G) return;
+  const int nt = g / S, s = g % S;
+  const int g_begin = s * groups_per_split, g_end = min(NG, g_begin + groups_per_split);
+  if (g_end <= g_begin) return;
+  const int klast = g_end * 8 - 1, Tlast = g_end * 2 - 1;
+  const int tile0 = mq * RT, tile_end = min(MT, tile0 + RT);
+  const int rb0 = nt * WT + wn * RBW, mt0 = tile0 + wm * 2;
+  const bool busy = mt0 < tile_end && rb0 < NRB;
+  const bf16_t* src[LPW];
+  int dst[LPW];
+#pragma unroll
+  for (int u = 0; u < LPW; ++u) {
+    const int i = w + u * NW;
+    src[u] = XF + (size_t)(i / RT * MT + min(tile0 + i % RT, tile_end - 1)) * KS * 512;
+    dst[u] = i * 64;
+  }
+#define PF_LDS(p, l) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p), (__attribute__((address_space(3))) void*)(l), 16, 0, 0)
+  auto dma = [&](u32x4* slot, int k) {
+    const size_t ko = (size_t)min(k, klast) * 512;
+#pragma unroll
+    for (int u = 0; u < LPW; ++u) PF_LDS(src[u] + ko + lane * 8, slot + dst[u]);
+  };
+  const u32x4* csrc = Wq + (size_t)min(nt * WT + w % WT, NRB - 1) * KT * 64 + lane;   // one code tile per wave (MW = 4: two waves load the same)
+  auto dma_codes = [&](u32x4* slot, int T) { PF_LDS(csrc + (size_t)min(T, Tlast) * 64, slot + (w % WT) * 64); };
+  // lane l brings 16 bytes of the scales of row block l / 4 (lanes beyond the tile repeat the last ones) and of the sums of x
+  const bf16_t* ssrc = SC + (size_t)min(nt * WT + min(lane >> 2, WT - 1), NRB - 1) * NG * 32 + (lane & 3) * 8;
+  const float* xsrc = SX + tile0 * 32 + (lane & (RT * 8 - 1)) * 4;
+  const int Mpad = MT * 32;
+  f32x16 acc[RBW][2], part[RBW][2];
+#pragma unroll
+  for (int j = 0; j < RBW; ++j)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
+  u32x4 fb[2][NXP * 2], cd[2][RBW];
+  auto frags = [&](const u32x4* slot, int b) {
+#pragma unroll
+    for (int q = 0; q < NXP; ++q)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) fb[b][q * 2 + t] = slot[(q * RT + wm * 2 + t) * 64 + lane];
+  };
+  auto codes = [&](const u32x4* slot, int b) {
+#pragma unroll
+    for (int j = 0; j < RBW; ++j) cd[b][j] = slot[(wn * RBW + j) * 64 + lane];
+  };
+  auto mul = [&](int i) {                                       // k-step i of the group
+    const int b = i & 1;
+    u32x4 av[RBW];
 #pragma unroll
     for (int j = 0; j < RBW; ++j) {
-      const int rb = rb0 + j;
-      if (rb >= NRB) continue;
+      const uint32_t wd = cd[(i >> 2) & 1][j][i & 3];
+      av[j] = q4_expand(wd);
+    }
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int mt = mt0 + t;
-        if (mt >= tile_end) continue;
-        const int m = mt * 32 + (lane & 31);
-        float v[8];                                             // features 4hh + {0..3} and 8 + 4hh + {0..3} of the block
+    for (int q = 0; q < NXP; ++q)
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const float gs = acc[j][t][r], us = acc[j][t][r + 8];
-          v[r] = m < row_end ? gs / (1.0f + __expf(-gs)) * us : 0.f;
+      for (int j = 0; j < RBW; ++j)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          f32x16 z;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) z[r] = 0.f;
+          part[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[j]), __builtin_bit_cast(bf16x8, fb[b][q * 2 + t]),
+                                                               i == 0 && q == 0 ? z : part[j][t], 0, 0, 0);
         }
-        float x[8];
+  };
+#define PF_WAITV(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+#define PF_BAR() do { asm volatile("" ::: "memory"); __builtin_amdgcn_s_barrier(); asm volatile("" ::: "memory"); } while (0)
+  dma_codes(c0, 2 * g_begin);
+  dma(s0, 8 * g_begin); dma(s1, 8 * g_begin + 1); dma(s2, 8 * g_begin + 2); dma(s3, 8 * g_begin + 3);
+  PF_WAITV(3 * LPW);
+  PF_BAR();
+  frags(s0, 0);
+  codes(c0, 0);
+  // extra loads: 3 in a group's step 0 (codes, scales, sums of x), 1 in its step 4 (codes)
+#define PF_STEP(i, cur, nxt)                                                                            \
+  {                                                                                                     \
+    __builtin_amdgcn_s_waitcnt(0xC07F);                    /* lgkmcnt(0) */                             \
+    PF_WAITV(2 * LPW + ((i) == 1 || (i) == 2 ? 3 : (i) == 5 || (i) == 6 ? 1 : 0));                      \
+    PF_BAR();                                                                                           \
+    if ((i) == 0) {                                                                                     \
+      PF_LDS(ssrc + (size_t)gi * 32, scl);                                                              \
+      PF_LDS(xsrc + (size_t)gi * Mpad, sxs);                                                            \
+      dma_codes(c1, 2 * gi + 1);                                                                        \
+    }                                                                                                   \
+    if ((i) == 4) dma_codes(c0, 2 * gi + 2);                                                            \
+    frags(nxt, ((i) & 1) ^ 1);                                                                          \
+    if ((i) == 3) codes(c1, 1);                                                                         \
+    if ((i) == 7) codes(c0, 0);                                                                         \
+    dma(cur, 8 * gi + (i) + 4);                                                                         \
+    if (busy) mul(i);                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+  }
+  for (int gi = g_begin; gi < g_end; ++gi) {
+    PF_STEP(0, s0, s1)
+    PF_STEP(1, s1, s2)
+    PF_STEP(2, s2, s3)
+    PF_STEP(3, s3, s0)
+    PF_STEP(4, s0, s1)
+    PF_STEP(5, s1, s2)
+    PF_STEP(6, s2, s3)
+    PF_STEP(7, s3, s0)
+    if (busy) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float got = __shfl_xor(hh ? v[i] : v[4 + i], 32, 64);   // the partner's features 4..7 (for hh = 0) or 8..11 (for hh = 1)
-          x[i] = hh ? got : v[i];
-          x[4 + i] = hh ? v[4 + i] : got;
+      for (int j = 0; j < RBW; ++j) {
+        const u32x4 sa = scl[(wn * RBW + j) * 4 + 2 * hh], sb = scl[(wn * RBW + j) * 4 + 2 * hh + 1];
+        const uint32_t sw[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const float sx = ((const float*)sxs)[(wm * 2 + t) * 32 + (lane & 31)];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float sv = __builtin_bit_cast(float, (r & 1) ? (sw[r >> 1] & 0xFFFF0000u) : (sw[r >> 1] << 16));
+            acc[j][t][r] += sv * (part[j][t][r] + sx);
+          }
         }
-        xf_store8(act, m, 16 * rb + 8 * hh, MT, NRB, NXP, x);
       }
     }
-    return;
   }
-  const int Mpad = MT * 32;
+  PF_WAITV(0);                                                  // no load may be on its way into LDS when the work-group ends
+#undef PF_STEP
+#undef PF_WAITV
+#undef PF_BAR
+#undef PF_LDS
+  if (!busy) return;
+  pf_store<RBW, SWIGLU>(acc, PT, s, NRB, Npad, MT, act, rb0, mt0, tile_end, M);
+}
+
+// SX[group][row] = -24 * sum of x over the group's 128 columns (x = the sum of its planes), for k_gemm_pf_q4.  A wave per (32-row tile, group).
+__global__ __launch_bounds__(256) void k_group_sums(const bf16_t* __restrict__ XF, float* __restrict__ SX, int MT, int KS, int nplanes) {
+  const int lane = threadIdx.x & 63, g = blockIdx.y * 4 + (threadIdx.x >> 6), t = blockIdx.x;
+  if (g * 8 >= KS) return;
+  u32x4 v[8][2];
 #pragma unroll
-  for (int j = 0; j < RBW; ++j) {
-    const int rb = rb0 + j;
-    if (rb >= NRB) continue;
+  for (int u = 0; u < 8; ++u)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int mt = mt0 + t;
-      if (mt >= tile_end) continue;
-      float* out = PT + ((size_t)s * Mpad + mt * 32 + (lane & 31)) * Npad + (size_t)rb * 32 + 4 * (lane >> 5);
+    for (int q = 0; q < 2; ++q) v[u][q] = *(const u32x4*)(XF + (((size_t)min(q, nplanes - 1) * MT + t) * KS + 8 * g + u) * 512 + lane * 8);
+  float a = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        f32x4 v; v.x = acc[j][t][4 * i]; v.y = acc[j][t][4 * i + 1]; v.z = acc[j][t][4 * i + 2]; v.w = acc[j][t][4 * i + 3];
-        *(f32x4*)(out + 8 * i) = v;
-      }
-    }
-  }
+  for (int u = 0; u < 8; ++u)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (q < nplanes) a += __builtin_bit_cast(float, v[u][q][j] << 16) + __builtin_bit_cast(float, v[u][q][j] & 0xFFFF0000u);
+  a += __shfl_xor(a, 32, 64);
+  if (lane < 32) SX[(size_t)g * MT * 32 + t * 32 + lane] = -24.0f * a;
 }
 
 // ============================================================================ row producers
+// Row facts of a pass of at most 64 rows whose first kernel does not write them.
+__global__ __launch_bounds__(64) void k_row_facts(Pass pass, const TreeDev* tree, SeqState st, int M, KVCache kv, RowFact* facts) {
+  if ((int)threadIdx.x < M) facts[threadIdx.x] = row_fact(pass, tree, row_info(pass, tree, st, threadIdx.x), kv);
+}
 // h[r][:] = embedding of row r's token (fp32).  EmbT = float or bf16_t.
 template <typename EmbT>
 __global__ __launch_bounds__(256) void k_embed(Pass pass, const TreeDev* tree, SeqState st, const int* tree_tok,

@@ -486,11 +486,7 @@ __device__ __forceinline__ void k2_stream_q4(const u32x4* __restrict__ xs, int k
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
           const uint32_t wd = ks == 0 ? a4[st][j].x : ks == 1 ? a4[st][j].y : ks == 2 ? a4[st][j].z : a4[st][j].w;
-          u32x4 av;
-          av.x = (wd & 0x000F000Fu) | 0x43004300u;
-          av.y = ((wd >> 4) & 0x000F000Fu) | 0x43004300u;
-          av.z = ((wd >> 8) & 0x000F000Fu) | 0x43004300u;
-          av.w = ((wd >> 12) & 0x000F000Fu) | 0x43004300u;
+          const u32x4 av = q4_expand(wd);
 #pragma unroll
           for (int q = 0; q < NXP; ++q)
             part[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bq[q]), part[j], 0, 0, 0);
@@ -509,7 +505,7 @@ __device__ __forceinline__ void k2_stream_q4(const u32x4* __restrict__ xs, int k
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float sv = __builtin_bit_cast(float, (r & 1) ? (sw[r >> 1] & 0xFFFF0000u) : (sw[r >> 1] << 16));
-        acc[j][r] += sv * (part[j][r] - 136.0f * sx[r]);
+        acc[j][r] += sv * (part[j][r] - 24.0f * sx[r]);
       }
     }
   }
@@ -762,9 +758,9 @@ __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int
 
 // ---- the same stream over 4-bit weights (see k_pack_weight_q4 for the layout) -------------------------------------------
 // A wave owns the groups [gb, ge) of 128 k.  Per group: two 16-byte loads per row block bring the codes of its 8 k-steps;
-// a k-step's A operand is 128 + code (exact in bf16) -- two ALU operations per pair of codes, which run beside the MFMAs
-// -- so the group's partial sums come out as sum_k x_k (128 + c_k); an MFMA against an all-ones tile gives sum_k x_k of
-// the same k-steps, and the group is folded into the result as  acc += s_row * (partial - 136 * sum_x)  in fp32.
+// a k-step's A operand is 16 + code (exact in bf16) -- two ALU operations per pair of codes, which run beside the MFMAs
+// -- so the group's partial sums come out as sum_k x_k (16 + c_k); an MFMA against an all-ones tile gives sum_k x_k of
+// the same k-steps, and the group is folded into the result as  acc += s_row * (partial - 24 * sum_x)  in fp32.
 // Activation fragments are streamed from L2 as in fk_stream, one group (8 k-steps) ahead; the next group's codes are
 // requested as soon as a super-tile's registers are free.
 template <int NXP, int NR>
@@ -805,12 +801,7 @@ __device__ __forceinline__ void fk_stream_q4(const bf16_t* __restrict__ XF, int 
         const int kk = 8 * g + 4 * st + ks;
         auto expand = [&](int j) {
           const uint32_t wd = ks == 0 ? a4[st][j].x : ks == 1 ? a4[st][j].y : ks == 2 ? a4[st][j].z : a4[st][j].w;
-          u32x4 av;
-          av.x = (wd & 0x000F000Fu) | 0x43004300u;
-          av.y = ((wd >> 4) & 0x000F000Fu) | 0x43004300u;
-          av.z = ((wd >> 8) & 0x000F000Fu) | 0x43004300u;
-          av.w = ((wd >> 12) & 0x000F000Fu) | 0x43004300u;
-          return av;
+          return q4_expand(wd);
         };
         if constexpr (NR <= 2) {
           // plane by plane, so that consecutive MFMAs write different accumulators (measured: QKV 20.4 -> 19.3 us, down
@@ -854,7 +845,7 @@ __device__ __forceinline__ void fk_stream_q4(const bf16_t* __restrict__ XF, int 
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float sv = __builtin_bit_cast(float, (r & 1) ? (sw[r >> 1] & 0xFFFF0000u) : (sw[r >> 1] << 16));
-        acc[j][r] += sv * (part[j][r] - 136.0f * sx[r]);
+        acc[j][r] += sv * (part[j][r] - 24.0f * sx[r]);
       }
     }
   }
