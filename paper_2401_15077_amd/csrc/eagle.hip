@@ -887,7 +887,8 @@ static KVCache kv_for(eagle_ctx* c, int li) {
 
 static int resnorm(eagle_ctx* c, int M, int MT, const float* h_in, const float* PT, int S, int Npad, const float* bias,
                    const float* gain, bf16_t* XF, float* xout, const float* row_w = nullptr) {
-  k_resnorm<<<M, 256, 0, c->stream>>>(h_in, PT, S, Npad, MT * 32, bias, c->h, gain, c->cfg.rms_eps, XF, MT, c->NXP, xout, c->cfg.d_model, row_w);
+  k_resnorm<false><<<M, RESNORM_THREADS, 0, c->stream>>>(h_in, PT, S, Npad, MT * 32, bias, c->h, gain, c->cfg.rms_eps, XF, MT, c->NXP, xout, c->cfg.d_model, row_w,
+                                                         nullptr, nullptr, 0, 0);
   LAUNCH_CHECK();
   return EAGLE_OK;
 }
@@ -902,9 +903,9 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
   KVCache kv = kv_for(c, li);
   if ((rc = (c->cur_class = KC_QKV, gemm(c, w.qkv, c->xf_d, MT, &S)))) return rc;
   {
-    dim3 grid(M, (H + 2 * KVH + 3) / 4);
-    if (c->kv_f32) k_qkv_rope_store<float><<<grid, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->PT, S, w.qkv.Npad, MT * 32, c->rope_cos, c->rope_sin, c->Q, kv, H);
-    else k_qkv_rope_store<bf16_t><<<grid, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->PT, S, w.qkv.Npad, MT * 32, c->rope_cos, c->rope_sin, c->Q, kv, H);
+    dim3 grid(M, (w.qkv.N / 4 + 255) / 256);
+    if (c->kv_f32) k_qkv_rope_store<float><<<grid, 256, 0, c->stream>>>(c->facts, c->PT, S, w.qkv.N, w.qkv.Npad, MT * 32, c->rope_cos, c->rope_sin, c->Q, kv, H);
+    else k_qkv_rope_store<bf16_t><<<grid, 256, 0, c->stream>>>(c->facts, c->PT, S, w.qkv.N, w.qkv.Npad, MT * 32, c->rope_cos, c->rope_sin, c->Q, kv, H);
     LAUNCH_CHECK();
   }
   {
@@ -953,7 +954,7 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
       hipError_t e = (c->cur_class = KC_GATEUP, launch_pf_moe<true>(c, w.e_gu, c->xf_moe, tiles, p.gu, p.cols, c->xf_ffn));
       if (e == hipSuccess) e = (c->cur_class = KC_DOWN, launch_pf_moe<false>(c, w.e_dn, c->xf_ffn, tiles, p.dn, p.cols, nullptr));
       if (e != hipSuccess) return fail(EAGLE_EHIP, "expert gemm launch failed: %s", hipGetErrorString(e));
-      k_resnorm<<<M, 256, 0, c->stream>>>(c->h, c->PT, p.dn.S, w.e_dn[0].Npad, tiles * 32, nullptr, c->h, next_gain, g.rms_eps, c->xf_d, MT, c->NXP, xout,
+      k_resnorm<true><<<M, RESNORM_THREADS, 0, c->stream>>>(c->h, c->PT, p.dn.S, w.e_dn[0].Npad, tiles * 32, nullptr, c->h, next_gain, g.rms_eps, c->xf_d, MT, c->NXP, xout,
                                           g.d_model, nullptr, c->moe_w, c->moe_slot, c->Mmax, E);
       LAUNCH_CHECK();
       return EAGLE_OK;
@@ -998,8 +999,8 @@ static int target_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, 
   const eagle_config& g = c->cfg;
   const int M = pass.rows_per_seq * pass.n_seq, MT = (M + 31) / 32;
   int rc;
-  if (c->f32) k_embed<float><<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const float*)c->embed, c->h, g.d_model, g.vocab);
-  else k_embed<bf16_t><<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const bf16_t*)c->embed, c->h, g.d_model, g.vocab);
+  if (c->f32) k_embed<float><<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const float*)c->embed, c->h, g.d_model, g.vocab, kv_for(c, 0), c->facts);
+  else k_embed<bf16_t><<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const bf16_t*)c->embed, c->h, g.d_model, g.vocab, kv_for(c, 0), c->facts);
   LAUNCH_CHECK();
   if ((rc = resnorm(c, M, MT, c->h, nullptr, 0, 0, nullptr, c->layers[0].attn_norm, c->xf_d, nullptr))) return rc;
   for (int l = 0; l < g.n_layers; ++l) {

@@ -768,9 +768,10 @@ __global__ __launch_bounds__(64) void k_row_facts(Pass pass, const TreeDev* tree
 // h[r][:] = embedding of row r's token (fp32).  EmbT = float or bf16_t.
 template <typename EmbT>
 __global__ __launch_bounds__(256) void k_embed(Pass pass, const TreeDev* tree, SeqState st, const int* tree_tok,
-                                               const EmbT* __restrict__ embed, float* __restrict__ h, int d, int vocab) {
+                                               const EmbT* __restrict__ embed, float* __restrict__ h, int d, int vocab, KVCache kv, RowFact* facts) {
   int r = blockIdx.x;
   RowInfo ri = row_info(pass, tree, st, r);
+  if (threadIdx.x == 0) facts[r] = row_fact(pass, tree, ri, kv);
   int tok = 0;
   if (ri.valid) {
     if (pass.kind == PASS_VERIFY) tok = tree_tok[ri.seq * tree->M + ri.node];
@@ -854,17 +855,23 @@ __global__ __launch_bounds__(256) void k_fc_input(Pass pass, const TreeDev* tree
 }
 
 // h_out[r] = h_in[r] + sum_s PT[s][:, r] + bias ;  x = gain ? rmsnorm(h_out[r]) * gain : h_out[r]
-// x goes out in XF layout (GEMM input) and, optionally, as fp32 rows (features).  One block per row.
-__global__ __launch_bounds__(256) void k_resnorm(const float* h_in, const float* __restrict__ PT, int S, int Npad, int Mpad,
-                                                 const float* bias, float* h_out, const float* gain, float eps,
-                                                 bf16_t* XF, int MT, int nplanes, float* xout, int d, const float* row_w,
-                                                 const float* moe_w = nullptr, const int* moe_slot = nullptr, int moe_stride = 0, int E = 0) {
+// x goes out in XF layout (GEMM input) and, optionally, as fp32 rows (features).  One block per row; a thread owns chunks of 8
+// consecutive columns, the first RESNORM_KEEP of which (rows of up to 8192 columns) stay in registers between the two phases.
+// Bound by memory latency for passes of some hundred rows: everything a chunk needs -- residual, up to eight splits, bias and the
+// next norm's gain -- is requested together as 16-byte loads before anything is stored (h_out may be h_in: with element-wise
+// loads and stores in turn, each load waited for the store before it: 16.1 us a call at 104 rows and d = 4096, now 8.8).
+// MOE: the pass's experts ran grouped (k_moe_plan); the row's result is sum over its experts, ascending, of weight * sum_s PT[s][slot].
+constexpr int RESNORM_THREADS = 512, RESNORM_KEEP = 2;
+template <bool MOE = false>
+__global__ __launch_bounds__(RESNORM_THREADS) void k_resnorm(const float* h_in, const float* __restrict__ PT, int S, int Npad, int Mpad,
+                                                             const float* __restrict__ bias, float* h_out, const float* __restrict__ gain, float eps,
+                                                             bf16_t* __restrict__ XF, int MT, int nplanes, float* __restrict__ xout, int d, const float* __restrict__ row_w,
+                                                             const float* __restrict__ moe_w, const int* __restrict__ moe_slot, int moe_stride, int E) {
   __shared__ float sh[16];
-  __shared__ float pick_w[4];                    // grouped experts: weight and gathered row of each expert of this row, ascending
+  __shared__ float pick_w[4];                    // MOE: weight and gathered row of each expert of this row, ascending
   __shared__ int pick_s[4], n_pick;
-  int r = blockIdx.x;
-  float ss = 0.f;
-  if (moe_slot) {
+  const int r = blockIdx.x;
+  if constexpr (MOE) {
     if (threadIdx.x < 64) {                      // one wave looks at (at most 64) experts
       const int e = threadIdx.x;
       const int slot = e < E ? moe_slot[(size_t)e * moe_stride + r] : -1;
@@ -877,138 +884,126 @@ __global__ __launch_bounds__(256) void k_resnorm(const float* h_in, const float*
     }
     __syncthreads();
   }
-  // each thread owns chunks of 8 consecutive k; the first four chunks (rows of up to 8192 columns) stay in registers
-  // for the second phase, further ones are read back from h_out
-  constexpr int KEEP = 4;
-  float keep[KEEP][8];
-  const float rw = row_w ? row_w[r] : 1.0f;    // MoE: this expert's routing weight for the row (0 = not routed here)
-  auto phase1 = [&](int k8, float* v) {
-    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (moe_slot) {
-      float x[8];
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f}, one = {1.f, 1.f, 1.f, 1.f};
+  struct Chunk { f32x4 lo, hi, glo, ghi; };      // the residual's new values and the gain
+  Chunk keep[RESNORM_KEEP];
+  float ss = 0.f;
+  const float rw = row_w ? row_w[r] : 1.0f;      // every expert over all rows: this expert's routing weight (0 = not routed here)
+  auto add_splits = [&](int row, int k8, f32x4& alo, f32x4& ahi) {   // added in split order, eight splits' worth of loads in flight
+    for (int s0 = 0; s0 < S; s0 += 8) {
+      f32x4 lo[8], hi[8];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = h_in[(size_t)r * d + k8 + t];
-      for (int j = 0; j < n_pick; ++j) {
-        float b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < S; s0 += 4) {
-          f32x4 lo[4], hi[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float* src = PT + ((size_t)min(s0 + u, S - 1) * Mpad + pick_s[j]) * Npad + k8;
-            lo[u] = *(const f32x4*)src; hi[u] = *(const f32x4*)(src + 4);
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (s0 + u < S) {
-              b[0] += lo[u].x; b[1] += lo[u].y; b[2] += lo[u].z; b[3] += lo[u].w;
-              b[4] += hi[u].x; b[5] += hi[u].y; b[6] += hi[u].z; b[7] += hi[u].w;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) x[t] += pick_w[j] * b[t];
+      for (int u = 0; u < 8; ++u) {
+        const float* src = PT + ((size_t)min(s0 + u, S - 1) * Mpad + row) * Npad + k8;
+        lo[u] = *(const f32x4*)src; hi[u] = *(const f32x4*)(src + 4);
       }
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        h_out[(size_t)r * d + k8 + t] = x[t];
-        ss += x[t] * x[t];
-        v[t] = x[t];
-      }
-      return;
-    }
-    if (PT) {
-      for (int s0 = 0; s0 < S; s0 += 8) {        // eight splits' worth of loads in flight, added in split order
-        f32x4 lo[8], hi[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const float* src = PT + ((size_t)min(s0 + u, S - 1) * Mpad + r) * Npad + k8;
-          lo[u] = *(const f32x4*)src; hi[u] = *(const f32x4*)(src + 4);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (s0 + u < S) {
-            a[0] += lo[u].x; a[1] += lo[u].y; a[2] += lo[u].z; a[3] += lo[u].w;
-            a[4] += hi[u].x; a[5] += hi[u].y; a[6] += hi[u].z; a[7] += hi[u].w;
-          }
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      int k = k8 + t;
-      float x = h_in ? h_in[(size_t)r * d + k] : 0.f;
-      if (PT) x += row_w ? rw * a[t] : a[t];
-      if (bias) x += bias[k];
-      h_out[(size_t)r * d + k] = x;
-      ss += x * x;
-      v[t] = x;
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < S) { alo += lo[u]; ahi += hi[u]; }
     }
   };
+  auto phase1 = [&](int k8, Chunk& c) {
+    const float* hp = h_in + (size_t)r * d + k8;
+    c.lo = h_in ? *(const f32x4*)hp : zero; c.hi = h_in ? *(const f32x4*)(hp + 4) : zero;
+    c.glo = gain ? *(const f32x4*)(gain + k8) : one; c.ghi = gain ? *(const f32x4*)(gain + k8 + 4) : one;
+    const f32x4 blo = bias ? *(const f32x4*)(bias + k8) : zero, bhi = bias ? *(const f32x4*)(bias + k8 + 4) : zero;
+    if constexpr (MOE) {
+      for (int j = 0; j < n_pick; ++j) {
+        f32x4 alo = zero, ahi = zero;
+        add_splits(pick_s[j], k8, alo, ahi);
+        c.lo += pick_w[j] * alo; c.hi += pick_w[j] * ahi;
+      }
+    } else if (PT) {
+      f32x4 alo = zero, ahi = zero;
+      add_splits(r, k8, alo, ahi);
+      if (row_w) { alo *= rw; ahi *= rw; }
+      c.lo += alo; c.hi += ahi;
+    }
+    if (bias) { c.lo += blo; c.hi += bhi; }
+    float* out = h_out + (size_t)r * d + k8;
+    *(f32x4*)out = c.lo; *(f32x4*)(out + 4) = c.hi;
 #pragma unroll
-  for (int it = 0; it < KEEP; ++it) {
-    const int k8 = (it * (int)blockDim.x + (int)threadIdx.x) * 8;
+    for (int t = 0; t < 4; ++t) ss += c.lo[t] * c.lo[t];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) ss += c.hi[t] * c.hi[t];
+  };
+#pragma unroll
+  for (int it = 0; it < RESNORM_KEEP; ++it) {
+    const int k8 = (it * RESNORM_THREADS + (int)threadIdx.x) * 8;
     if (k8 < d) phase1(k8, keep[it]);
   }
-  for (int k8 = (KEEP * blockDim.x + threadIdx.x) * 8; k8 < d; k8 += blockDim.x * 8) { float v[8]; phase1(k8, v); }
+  for (int k8 = (RESNORM_KEEP * RESNORM_THREADS + (int)threadIdx.x) * 8; k8 < d; k8 += RESNORM_THREADS * 8) { Chunk c; phase1(k8, c); }
+  if (!XF && !xout) return;
   ss = block_sum(ss, sh);
-  float rstd = gain ? 1.0f / sqrtf(ss / (float)d + eps) : 1.0f;
+  const float rstd = gain ? 1.0f / sqrtf(ss / (float)d + eps) : 1.0f;
   const int KS = d / 16;
-  auto phase2 = [&](int k8, const float* v) {
-    float x[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      x[t] = gain ? v[t] * rstd * gain[k8 + t] : v[t];
-      if (xout) xout[(size_t)r * d + k8 + t] = x[t];
-    }
+  auto phase2 = [&](int k8, const Chunk& c) {
+    f32x4 lo = c.lo, hi = c.hi;
+    if (gain) { lo = lo * rstd * c.glo; hi = hi * rstd * c.ghi; }
+    if (xout) { *(f32x4*)(xout + (size_t)r * d + k8) = lo; *(f32x4*)(xout + (size_t)r * d + k8 + 4) = hi; }
+    const float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     if (XF) xf_store8(XF, r, k8, MT, KS, nplanes, x);
   };
-  if (!XF && !xout) return;
 #pragma unroll
-  for (int it = 0; it < KEEP; ++it) {
-    const int k8 = (it * (int)blockDim.x + (int)threadIdx.x) * 8;
+  for (int it = 0; it < RESNORM_KEEP; ++it) {
+    const int k8 = (it * RESNORM_THREADS + (int)threadIdx.x) * 8;
     if (k8 < d) phase2(k8, keep[it]);
   }
-  for (int k8 = (KEEP * blockDim.x + threadIdx.x) * 8; k8 < d; k8 += blockDim.x * 8) {
-    float v[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) v[t] = h_out[(size_t)r * d + k8 + t];
-    phase2(k8, v);
+  for (int k8 = (RESNORM_KEEP * RESNORM_THREADS + (int)threadIdx.x) * 8; k8 < d; k8 += RESNORM_THREADS * 8) {
+    Chunk c;
+    const float* hp = h_out + (size_t)r * d + k8;
+    c.lo = *(const f32x4*)hp; c.hi = *(const f32x4*)(hp + 4);
+    c.glo = gain ? *(const f32x4*)(gain + k8) : one; c.ghi = gain ? *(const f32x4*)(gain + k8 + 4) : one;
+    phase2(k8, c);
   }
 }
 
 // q, k, v = rows of PT (the fused QKV projection); rotate-half RoPE on q and k with the row's position id;
 // q -> Q[r][head][dh] fp32, k and v -> this layer's paged cache at the row's slot.
+// A thread owns four consecutive rows of the fused matrix: two rotate-half pairs of a q or k head (packed with partners adjacent,
+// PACK_ROPE), or four columns of a v head; the splits are read 16 bytes at a time, four in flight.  Where the row goes comes
+// from the pass's row facts, one load.  (A wave per head with element-wise loads, page-table walk included: 8.1 us a call at 104
+// rows, now 6.3.)  Grid (rows, columns / 1024).
 template <typename CT>
-__global__ __launch_bounds__(256) void k_qkv_rope_store(Pass pass, const TreeDev* tree, SeqState st,
-                                                        const float* __restrict__ PT, int S, int Npad, int Mpad,
+__global__ __launch_bounds__(256) void k_qkv_rope_store(const RowFact* __restrict__ facts, const float* __restrict__ PT, int S, int N, int Npad, int Mpad,
                                                         const float* __restrict__ rope_cos, const float* __restrict__ rope_sin,
-                                                        float* Q, KVCache kv, int H) {
-  // a wave per (row, head); four heads per block
-  const int r = blockIdx.x, hd = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int dh = kv.head_dim, half = dh >> 1, KVH = kv.n_kv_heads;
-  if (hd >= H + 2 * KVH) return;
-  RowInfo ri = row_info(pass, tree, st, r);
-  for (int i = threadIdx.x & 63; i < half; i += 64) {
-    // q/k heads are packed with rotate-half partners adjacent (PACK_ROPE); v heads keep their order
-    int n1 = hd < H + KVH ? hd * dh + 2 * i : hd * dh + i;
-    int n2 = hd < H + KVH ? n1 + 1 : n1 + half;
-    float a = 0.f, b = 0.f;
-    for (int s = 0; s < S; ++s) {
-      a += PT[((size_t)s * Mpad + r) * Npad + n1];
-      b += PT[((size_t)s * Mpad + r) * Npad + n2];
-    }
-    if (hd < H + KVH) {   // q or k head: rotate
-      float c = rope_cos[(size_t)ri.pos * half + i], sn = rope_sin[(size_t)ri.pos * half + i];
-      float a2 = a * c - b * sn, b2 = b * c + a * sn;
-      a = a2; b = b2;
-    }
-    if (hd < H) {
-      Q[((size_t)r * H + hd) * dh + i] = a;
-      Q[((size_t)r * H + hd) * dh + i + half] = b;
-    } else if (ri.valid) {
-      int kvh = (hd - H) % KVH;
-      CT* base = (CT*)(hd < H + KVH ? kv.k : kv.v) + kv_offset(kv, ri.seq, ri.slot, kvh);
-      cache_store(base + i, a);
-      cache_store(base + i + half, b);
-    }
+                                                        float* __restrict__ Q, KVCache kv, int H) {
+  const int r = blockIdx.x, n = (blockIdx.y * 256 + threadIdx.x) * 4;
+  if (n >= N) return;                                           // N is a multiple of 32
+  const int pos = facts[r].pos, kv_row = facts[r].kv_row;
+  const int dh = kv.head_dim, half = dh >> 1, KVH = kv.n_kv_heads, hd = n / dh, pr = n % dh;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < S; s0 += 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *(const f32x4*)(PT + ((size_t)min(s0 + u, S - 1) * Mpad + r) * Npad + n);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < S) a += v[u];
+  }
+  if (hd >= H + KVH) {                                          // v head
+    if (kv_row < 0) return;
+    CT* base = (CT*)kv.v + ((size_t)kv_row + ((size_t)(hd - H - KVH) << kv.page_shift)) * dh + pr;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) cache_store(base + t, a[t]);
+    return;
+  }
+  const int i = pr >> 1;                                        // pairs i, i + 1
+  float x1[2], x2[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const float c = rope_cos[(size_t)pos * half + i + p], sn = rope_sin[(size_t)pos * half + i + p];
+    x1[p] = a[2 * p] * c - a[2 * p + 1] * sn;
+    x2[p] = a[2 * p + 1] * c + a[2 * p] * sn;
+  }
+  if (hd < H) {
+    float* q = Q + ((size_t)r * H + hd) * dh + i;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) { q[p] = x1[p]; q[half + p] = x2[p]; }
+  } else if (kv_row >= 0) {
+    CT* base = (CT*)kv.k + ((size_t)kv_row + ((size_t)(hd - H) << kv.page_shift)) * dh + i;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) { cache_store(base + p, x1[p]); cache_store(base + half + p, x2[p]); }
   }
 }
 
