@@ -922,8 +922,8 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
       HIPCHK(hipFuncSetAttribute((const void*)k2_attn<CT, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024)); \
       attr_done = true;                                                                                                 \
     }                                                                                                                   \
-    hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * DH * 32 + 4 * 2 * 32) * 4, \
-        pass, (const TreeDev*)c->tree_d, c->st, kv, (const float*)c->Q, c->part_o, c->part_ml, H, n_splits, n_new, scale, c->cnt_attn, c->xf_att, c->NXP, (unsigned long long*)nullptr, MT, rblocks); \
+    hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * 32 * (DH + 4) + 4 * 2 * 32) * 4, \
+        pass, (const RowFact*)c->facts, kv, (const float*)c->Q, c->part_o, c->part_ml, H, n_splits, n_new, scale, c->cnt_attn, c->xf_att, c->NXP, (unsigned long long*)nullptr, MT, rblocks); \
     if (e_ != hipSuccess) return fail(EAGLE_EHIP, "attention launch failed: %s", hipGetErrorString(e_));                \
   } while (0)
     if (c->kv_f32) { if (dh == 128) ATTNG(float, 128); else if (dh == 64) ATTNG(float, 64); else ATTNG(float, 32); }
@@ -1274,8 +1274,8 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
       HIPCHK(hipFuncSetAttribute((const void*)k2_attn<CT, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024)); \
       attr_done = true;                                                                                                 \
     }                                                                                                                   \
-    hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * DH * 32 + 4 * 2 * 32) * 4, \
-        pass, (const TreeDev*)c->tree_d, c->st, kv, (const float*)c->Q, c->part_o, c->part_ml, H, n_splits, n_new, scale, c->cnt_attn, c->xf2_att, c->NXP, atrace, 1, 1); \
+    hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * 32 * (DH + 4) + 4 * 2 * 32) * 4, \
+        pass, (const RowFact*)c->facts, kv, (const float*)c->Q, c->part_o, c->part_ml, H, n_splits, n_new, scale, c->cnt_attn, c->xf2_att, c->NXP, atrace, 1, 1); \
     if (e_ != hipSuccess) return fail(EAGLE_EHIP, "attention launch failed: %s", hipGetErrorString(e_));                \
   } while (0)
     if (c->kv_f32) { if (dh == 128) ATTN2(float, 128); else if (dh == 64) ATTN2(float, 64); else ATTN2(float, 32); }

@@ -1221,51 +1221,67 @@ __device__ inline void load8(const bf16_t* p, float* x) {
   x[6] = __builtin_bit_cast(float, r.w << 16); x[7] = __builtin_bit_cast(float, r.w & 0xFFFF0000u);
 }
 
-// Folds NS splits (e, e+1, ...) of one (row, head) into the running (max, denominator, CW outputs): every load of the
-// chunk is in flight before the first use.
-template <int DH, int CW, int NS>
-__device__ __forceinline__ void attn_merge_chunk(const float* part_o, const float* part_ml, size_t e0, int d0, float& mx, float& den, float* x) {
-  constexpr int NQ = CW / 4;
-  float msv[NS], lsv[NS];
-  f32x4 ov[NS][NQ];
+// Four consecutive values of row m, columns k.. (k a multiple of 4), as GEMM input (8 bytes per plane).
+__device__ inline void xf_store4(bf16_t* XF, int m, int k, int MT, int KS, int nplanes, f32x4 x) {
 #pragma unroll
-  for (int u = 0; u < NS; ++u) {
-    const size_t e = e0 + u;
-    msv[u] = coh_load(part_ml + e * 2);
-    lsv[u] = coh_load(part_ml + e * 2 + 1);
+  for (int q = 0; q < 3; ++q)
+    if (q < nplanes) {
+      uint32_t b[4];
 #pragma unroll
-    for (int qd = 0; qd < NQ; ++qd) ov[u][qd] = coh_load16(part_o, (uint32_t)((e * DH + d0 + 4 * qd) * 4));
-  }
-  float cmx = mx;
+      for (int t = 0; t < 4; ++t) {
+        const bf16_t h = f32_to_bf16(x[t]);
+        b[t] = h;
+        x[t] -= bf16_to_f32(h);
+      }
+      uint2 v; v.x = b[0] | (b[1] << 16); v.y = b[2] | (b[3] << 16);
+      *(uint2*)(XF + xf_index(m, k, q, MT, KS)) = v;
+    }
+}
+
+// Folds NS splits (e, e+1, ...) of one (row, head) into the running (max, denominator, outputs) of IT items (rows) at once:
+// every load of the chunk is in flight before the first use.
+template <int DH, int IT, int NS>
+__device__ __forceinline__ void attn_merge_chunk(const float* part_o, const float* part_ml, const size_t* e0, int d0, float* mx, float* den, f32x4* x) {
+  float msv[IT][NS], lsv[IT][NS];
+  f32x4 ov[IT][NS];
 #pragma unroll
-  for (int u = 0; u < NS; ++u) cmx = fmaxf(cmx, msv[u]);
-  const float resc = (mx == -INFINITY) ? 0.f : __expf(mx - cmx);   // nothing to rescale on the first chunk
-  den *= resc;
+  for (int i = 0; i < IT; ++i)
 #pragma unroll
-  for (int t = 0; t < CW; ++t) x[t] *= resc;
-  mx = cmx;
+    for (int u = 0; u < NS; ++u) {
+      const size_t e = e0[i] + u;
+      msv[i][u] = coh_load(part_ml + e * 2);
+      lsv[i][u] = coh_load(part_ml + e * 2 + 1);
+      ov[i][u] = coh_load16(part_o, (uint32_t)((e * DH + d0) * 4));
+    }
 #pragma unroll
-  for (int u = 0; u < NS; ++u) {
-    const float wv = (msv[u] != -INFINITY) ? __expf(msv[u] - mx) : 0.f;
-    den += wv * lsv[u];
+  for (int i = 0; i < IT; ++i) {
+    float cmx = mx[i];
 #pragma unroll
-    for (int qd = 0; qd < NQ; ++qd) {
-      x[4 * qd] += wv * ov[u][qd].x; x[4 * qd + 1] += wv * ov[u][qd].y;
-      x[4 * qd + 2] += wv * ov[u][qd].z; x[4 * qd + 3] += wv * ov[u][qd].w;
+    for (int u = 0; u < NS; ++u) cmx = fmaxf(cmx, msv[i][u]);
+    const float resc = (mx[i] == -INFINITY) ? 0.f : __expf(mx[i] - cmx);   // nothing to rescale on the first chunk
+    den[i] *= resc;
+    x[i] *= resc;
+    mx[i] = cmx;
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      const float wv = (msv[i][u] != -INFINITY) ? __expf(msv[i][u] - cmx) : 0.f;
+      den[i] += wv * lsv[i][u];
+      x[i] += wv * ov[i][u];
     }
   }
 }
 
 template <typename CT, int DH>
-__global__ __launch_bounds__(256) void k2_attn(Pass pass, const TreeDev* tree, SeqState st, KVCache kv,
+__global__ __launch_bounds__(256) void k2_attn(Pass pass, const RowFact* __restrict__ facts, KVCache kv,
                                                const float* __restrict__ Q, float* part_o, float* part_ml, int H,
                                                int n_splits, int n_new, float scale, int* counters, bf16_t* xf_out,
                                                int nplanes, unsigned long long* trace, int MT, int rblocks) {
   constexpr int KSN = DH / 16;              // k-steps of the QK product
   constexpr int DB = DH / 32;               // 32-wide blocks of the head dimension
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_a[];
-  float* o_s = (float*)smem_a;              // [4 waves][DH][32]
-  float* ml_s = o_s + 4 * DH * 32;          // [4 waves][2][32]
+  constexpr int OS = DH + 4;                // row stride of o_s: 16-byte accesses along d and across rows without bank conflicts
+  float* o_s = (float*)smem_a;              // [4 waves][32 rows][OS]
+  float* ml_s = o_s + 4 * 32 * OS;          // [4 waves][2][32]
   __shared__ int s_last;
   // blockIdx.z = (sequence of the pass, 32-row block of that sequence's rows); MT = 32-row tiles of the XF output
   const int split = blockIdx.x, hd = blockIdx.y, seq_l = blockIdx.z / rblocks, rblk = blockIdx.z % rblocks;
@@ -1277,15 +1293,12 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const TreeDev* tree, S
   const int kvh = hd / (H / kv.n_kv_heads);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int q = lane & 31, hh = lane >> 5;
-  const RowInfo r_first = row_info(pass, tree, st, r0);
-  const int seq = r_first.seq, base = r_first.base;
-  // this lane's query row
-  int rel = 0, causal = 1;
-  unsigned long long mask = 0ull;
-  if (q < R) {
-    const RowInfo ri = row_info(pass, tree, st, r0 + q);
-    rel = ri.rel; causal = ri.causal; mask = ri.mask;
-  }
+  // the rows' facts were written by the pass's first kernel; pending rows and prompts see their own rows causally
+  const bool causal = pass.kind >= PASS_PREFILL_T || pass.kind == PASS_DRAFT_PENDING;
+  const RowFact fq = facts[r0 + min(q, R - 1)];                 // this lane's query row
+  const int seq = __builtin_amdgcn_readfirstlane(fq.seq), base = __builtin_amdgcn_readfirstlane(fq.base);
+  const int rel = fq.rel;
+  const unsigned long long mask = (unsigned long long)fq.mask_hi << 32 | fq.mask_lo;
   // The scaled queries as bf16 hi + lo B-operand fragments live in LDS, built once by the four waves together (wave w
   // converts k-steps w, w+4, ...); they share the memory of o_s, which is not written before every wave has left the
   // key loop.  (One load and one conversion of the queries per work-group instead of one per wave.)
@@ -1308,7 +1321,7 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const TreeDev* tree, S
   __syncthreads();
   // causal passes (prompt chunks, pending rows): the rows of this 32-row block see no new token beyond its own last row,
   // so the blocks of keys after it are not visited at all (they would contribute exp(-inf) = 0: same bits, less work)
-  const int T = base + (r_first.causal ? min(n_new, 32 * rblk + R) : n_new);
+  const int T = base + (causal ? min(n_new, 32 * rblk + R) : n_new);
   // the split boundaries depend on `base` only, so a row sees the same partition whatever else is in the pass
   const int span = base + max(64, (n_new + 63) / 64 * 64);   // passes with at most 64 new rows share one partition
   const int tps = ((span + n_splits - 1) / n_splits + 63) / 64 * 64;
@@ -1416,56 +1429,50 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const TreeDev* tree, S
   }
   TRACE_STAMP(tr, 1);
   __syncthreads();                          // every wave is done with the query fragments that o_s overlays
-  // merge the 4 waves through LDS: o_s[w][d][q], d = 32b + 8(r/4) + 4hh + r%4
+  // merge the 4 waves through LDS; accumulator register r of block b holds d = 32b + 8(r/4) + 4hh + r%4 of row q
 #pragma unroll
   for (int b = 0; b < DB; ++b)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o_s[((size_t)w * DH + 32 * b + 8 * (r >> 2) + 4 * hh + (r & 3)) * 32 + q] = oacc[b][r];
+    for (int i = 0; i < 4; ++i) {
+      f32x4 v; v.x = oacc[b][4 * i]; v.y = oacc[b][4 * i + 1]; v.z = oacc[b][4 * i + 2]; v.w = oacc[b][4 * i + 3];
+      *(f32x4*)(o_s + ((size_t)w * 32 + q) * OS + 32 * b + 8 * i + 4 * hh) = v;
+    }
   if (hh == 0) { ml_s[(w * 2 + 0) * 32 + q] = m_run; ml_s[(w * 2 + 1) * 32 + q] = l_run; }
   __syncthreads();
-  // thread = (query q2, 8-wide chunks c = tid/32, tid/32 + 8, ... of the head dimension)
-  const int q2 = tid & 31;
-  float mm = -INFINITY;
-#pragma unroll
-  for (int ww = 0; ww < 4; ++ww) mm = fmaxf(mm, ml_s[(ww * 2) * 32 + q2]);
-  float wgt[4], L = 0.f;
-#pragma unroll
-  for (int ww = 0; ww < 4; ++ww) {
-    const float mw = ml_s[(ww * 2) * 32 + q2];
-    wgt[ww] = (mw == -INFINITY) ? 0.f : __expf(mw - mm);
-    L += wgt[ww] * ml_s[(ww * 2 + 1) * 32 + q2];
-  }
+  // thread = (four consecutive columns d0, rows tid / LD + RT * i): the lanes of a row write its partial output, and read the
+  // other splits' below, in contiguous runs.  (With a row per lane each 16-byte access of a wave touched 64 cache lines: 4.6 us
+  // from the arrival to the end of the kernel at 5 splits and 27 rows, now 2.9.)
+  constexpr int LD = DH / 4, RT = 256 / LD, NI = 32 / RT;       // lanes per row, rows at a time, items per thread
+  const int d0 = (tid % LD) * 4, q0 = tid / LD;
   const int KSX = H * DH / 16;
-  const float inv = L > 0.f ? 1.0f / L : 0.f;
-  for (int c = tid >> 5; c < DH / 8; c += 8) {
-    float o[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float a = 0.f;
-#pragma unroll
-      for (int ww = 0; ww < 4; ++ww) a += wgt[ww] * o_s[((size_t)ww * DH + 8 * c + i) * 32 + q2];
-      o[i] = a;
-    }
+  for (int i = 0; i < NI; ++i) {
+    const int q2 = q0 + RT * i;
     if (q2 >= R) continue;
-    if (n_splits == 1) {
+    float mm = -INFINITY;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) o[t] *= inv;
-      xf_store8(xf_out, r0 + q2, hd * DH + 8 * c, MT, KSX, nplanes, o);
+    for (int ww = 0; ww < 4; ++ww) mm = fmaxf(mm, ml_s[(ww * 2) * 32 + q2]);
+    float L = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ww = 0; ww < 4; ++ww) {
+      const float mw = ml_s[(ww * 2) * 32 + q2];
+      const float wgt = (mw == -INFINITY) ? 0.f : __expf(mw - mm);
+      L += wgt * ml_s[(ww * 2 + 1) * 32 + q2];
+      o += wgt * *(const f32x4*)(o_s + ((size_t)ww * 32 + q2) * OS + d0);
+    }
+    if (n_splits == 1) {
+      const float inv = L > 0.f ? 1.0f / L : 0.f;
+      o *= inv;
+      xf_store4(xf_out, r0 + q2, hd * DH + d0, MT, KSX, nplanes, o);
     } else {
-      const uint32_t po = (uint32_t)(((((size_t)(r0 + q2) * H + hd) * n_splits + split) * DH + 8 * c) * 4);
-      f32x4 v0, v1;
-      v0.x = o[0]; v0.y = o[1]; v0.z = o[2]; v0.w = o[3]; v1.x = o[4]; v1.y = o[5]; v1.z = o[6]; v1.w = o[7];
-      coh_store16(part_o, po, v0);
-      coh_store16(part_o, po + 16, v1);
+      const size_t e = ((size_t)(r0 + q2) * H + hd) * n_splits + split;
+      coh_store16(part_o, (uint32_t)((e * DH + d0) * 4), o);
+      if (d0 == 0) { coh_store(part_ml + e * 2, mm); coh_store(part_ml + e * 2 + 1, L); }
     }
   }
   TRACE_STAMP(tr, 2);
   if (n_splits == 1) return;
-  if (q2 < R && tid < 32) {
-    const size_t ofs = (((size_t)(r0 + q2) * H + hd) * n_splits + split) * 2;
-    coh_store(part_ml + ofs, mm);
-    coh_store(part_ml + ofs + 1, L);
-  }
   publish_wait();
   __syncthreads();
   if (tid == 0) {
@@ -1478,33 +1485,44 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const TreeDev* tree, S
   TRACE_STAMP(tr, 3);
   if (!s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  // merge the splits of (sequence, head): thread = (row, CW-wide column chunk), one item per thread in the usual
-  // shapes.  Every load of up to 8 splits -- (max, sum) pairs and partial outputs -- is in flight at once, so the
-  // merge costs one memory round trip; more splits continue with a running rescale, in split order.
-  constexpr int CW = DH >= 128 ? 16 : 8;
-  for (int it = tid; it < R * (DH / CW); it += 256) {
-    const int r = it / (DH / CW), d0 = (it % (DH / CW)) * CW;
-    const size_t rowhead = ((size_t)(r0 + r) * H + hd) * n_splits;
-    float mx = -INFINITY, den = 0.f, x[CW];
+  // merge the splits of (sequence, head), two rows of a thread at a time.  Every load of up to 8 splits -- (max, sum) pairs and
+  // partial outputs -- is in flight at once, so the merge costs one memory round trip per pair of rows; more splits continue
+  // with a running rescale, in split order.
+  constexpr int IT = 2;
 #pragma unroll
-    for (int t = 0; t < CW; ++t) x[t] = 0.f;
+  for (int i0 = 0; i0 < NI; i0 += IT) {
+    if (q0 + RT * i0 >= R) break;
+    size_t rowhead[IT];
+    float mx[IT], den[IT];
+    f32x4 x[IT];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      rowhead[i] = ((size_t)(r0 + min(q0 + RT * (i0 + i), R - 1)) * H + hd) * n_splits;
+      mx[i] = -INFINITY; den[i] = 0.f;
+      x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     for (int sp0 = 0; sp0 < n_splits; sp0 += 8) {
+      size_t e[IT];
+#pragma unroll
+      for (int i = 0; i < IT; ++i) e[i] = rowhead[i] + sp0;
       switch (min(n_splits - sp0, 8)) {                        // uniform: exactly the loads that are needed
-        case 1: attn_merge_chunk<DH, CW, 1>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        case 2: attn_merge_chunk<DH, CW, 2>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        case 3: attn_merge_chunk<DH, CW, 3>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        case 4: attn_merge_chunk<DH, CW, 4>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        case 5: attn_merge_chunk<DH, CW, 5>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        case 6: attn_merge_chunk<DH, CW, 6>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        case 7: attn_merge_chunk<DH, CW, 7>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
-        default: attn_merge_chunk<DH, CW, 8>(part_o, part_ml, rowhead + sp0, d0, mx, den, x); break;
+        case 1: attn_merge_chunk<DH, IT, 1>(part_o, part_ml, e, d0, mx, den, x); break;
+        case 2: attn_merge_chunk<DH, IT, 2>(part_o, part_ml, e, d0, mx, den, x); break;
+        case 3: attn_merge_chunk<DH, IT, 3>(part_o, part_ml, e, d0, mx, den, x); break;
+        case 4: attn_merge_chunk<DH, IT, 4>(part_o, part_ml, e, d0, mx, den, x); break;
+        case 5: attn_merge_chunk<DH, IT, 5>(part_o, part_ml, e, d0, mx, den, x); break;
+        case 6: attn_merge_chunk<DH, IT, 6>(part_o, part_ml, e, d0, mx, den, x); break;
+        case 7: attn_merge_chunk<DH, IT, 7>(part_o, part_ml, e, d0, mx, den, x); break;
+        default: attn_merge_chunk<DH, IT, 8>(part_o, part_ml, e, d0, mx, den, x); break;
       }
     }
-    const float inv = den > 0.f ? 1.0f / den : 0.f;
 #pragma unroll
-    for (int t = 0; t < CW; ++t) x[t] *= inv;
-#pragma unroll
-    for (int h8 = 0; h8 < CW / 8; ++h8) xf_store8(xf_out, r0 + r, hd * DH + d0 + 8 * h8, MT, KSX, nplanes, x + 8 * h8);
+    for (int i = 0; i < IT; ++i) {
+      const int q2 = q0 + RT * (i0 + i);
+      if (q2 >= R) continue;
+      const float inv = den[i] > 0.f ? 1.0f / den[i] : 0.f;
+      xf_store4(xf_out, r0 + q2, hd * DH + d0, MT, KSX, nplanes, x[i] * inv);
+    }
   }
   TRACE_STAMP(tr, 4);
 }
