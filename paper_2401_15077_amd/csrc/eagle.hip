@@ -96,6 +96,12 @@ struct eagle_ctx {
   // sums) to fill the chip with its narrow matrices, and rounds its tiles up once per matrix
   int pf_chunk = EAGLE_PREFILL_CHUNK, pf_window = EAGLE_PREFILL_CHUNK;
   bool big_gemm = false;
+  // A bf16 cache rounds K and V, which turns a difference of 1e-7 between two orders of an fp32 sum into one of 2^-9 in some of
+  // the entries (1e-4 relative on the logits of a 32-layer model).  Dense models with such a cache therefore keep ONE order of
+  // every sum, whatever tile shape serves it: K slices by plan_slices, prompt passes of 512 rows (32 with 4-bit weights, whose
+  // codes then expand around 128 in every pass).
+  bool fixed_sums = false;
+  int q4_rot = 3;                    // 4-bit codes: rotation of the packed words (3: they expand to 16 + code, 0: to 128 + code)
   // weights
   void* embed; PackedW lm_head, fc; float *final_norm, *fc_bias;
   std::vector<LayerW> layers;        // [n_layers] target + [1] head
@@ -167,7 +173,12 @@ static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c-
 // tiles: 243 work-groups, but 33 on the 32 CUs of one XCD: 355 us against 197 for 240 of the next shape).  And what the partial
 // sums cost that all but the fused epilogue write and read back, at 4.5 TB/s.
 // 4-bit weights (k_gemm_pf_q4): two row blocks per wave, K slices of whole groups of 8 k-steps.
-static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4) {
+static int plan_slices(int NRB, int KS, int MT, int n_cu) {     // K slices as a function of the shape alone (fixed_sums)
+  const int wgs = ((NRB + 7) / 8) * ((MT + 3) / 4);
+  int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? 16 : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
+  return std::max(1, std::min(S, KS / (MT <= 4 ? 16 : 32)));
+}
+static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4, bool fixed_sums) {
   GemmPlan best{};
   double best_us = -1;
   static const struct { int rbw, mw; double ns; } shapes[7] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}, {2, 4, 17.0}};
@@ -176,8 +187,9 @@ static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, 
     const auto& sh = shapes[i];
     const int wt = 2 * sh.rbw, rt = 2 * sh.mw, mq = (MT + rt - 1) / rt, nt = (NRB + wt - 1) / wt;
     if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
-    for (int S = 1; S <= 16; ++S) {
-      if (S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
+    const int S_fix = fixed_sums ? plan_slices(NRB, KS, MT, n_cu) : 0;
+    for (int S = fixed_sums ? S_fix : 1; S <= (fixed_sums ? S_fix : 16); ++S) {
+      if (!fixed_sums && S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
       const int unit = q4 ? 8 : 4, kps = ((KS + S - 1) / S + unit - 1) / unit * unit, s_real = (KS + kps - 1) / kps;
       const int rounds = ((nt * s_real + xcds - 1) / xcds * mq + cu_x - 1) / cu_x;
       double us = 1e-3 * sh.ns * rounds * wt * rt * kps + 4.0;
@@ -461,7 +473,7 @@ static size_t layout(eagle_ctx* c) {
     for (const Seen& q : seen) if (q.NRB == w.NRB && q.KS == w.KS && q.mt_max == mt_max && q.fused == fused) return;
     seen.push_back(Seen{w.NRB, w.KS, mt_max, fused});
     for (int mt = 1; mt <= mt_max; ++mt) {
-      const GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu, fused, c->q4) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
+      const GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu, fused, c->q4, c->fixed_sums) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
       if (fused && use_pf(c, mt) && p.S == 1) continue;          // SwiGLU inside the GEMM: nothing goes through memory
       worst = std::max(worst, (size_t)p.S * w.Npad * (size_t)(mt * 32));
     }
@@ -517,6 +529,7 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
   c->NWP = c->f32 ? 3 : 1; c->NXP = c->f32 ? 3 : 2; c->elt = c->f32 ? 4 : 2;
   c->kv_f32 = cfg->kv_dtype == EAGLE_F32; c->kv_elt = c->kv_f32 ? 4 : 2;
   c->q4 = cfg->weight_bits == 4;
+  c->fixed_sums = !c->kv_f32 && cfg->n_experts == 0;
   c->M = c->tree_h.M; c->D = c->tree_h.D;
   c->max_level_rows = 1;
   for (int dlev = 1; dlev <= c->D; ++dlev) c->max_level_rows = std::max(c->max_level_rows, c->tree_h.n_level_rows[dlev]);
@@ -525,7 +538,8 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
   c->big_gemm = !c->f32 && cfg->weight_bits != 4 && cfg->d_ffn % 64 == 0 && (cfg->n_heads * cfg->head_dim) % 64 == 0;
   if (c->big_gemm) {
     c->pf_window = EAGLE_PREFILL_WINDOW;
-    c->pf_chunk = std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + EAGLE_PREFILL_WINDOW - 1) / EAGLE_PREFILL_WINDOW * EAGLE_PREFILL_WINDOW);
+    c->pf_chunk = c->fixed_sums ? EAGLE_PREFILL_WINDOW
+                                : std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + EAGLE_PREFILL_WINDOW - 1) / EAGLE_PREFILL_WINDOW * EAGLE_PREFILL_WINDOW);
   }
   if (c->q4) {
     // 4-bit weights: tree and vanilla passes exist in the fused kernels of the fast path only (at most 32 rows); prompt passes of
@@ -535,7 +549,8 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
       return fail(EAGLE_EINVAL, "weight_bits = 4 needs d_model, d_ffn and n_heads * head_dim to be multiples of %d", EAGLE_Q4_GROUP);
     if (cfg->max_batch * c->M > 32 || cfg->max_batch * (c->D + 1) > 32) return fail(EAGLE_EINVAL, "weight_bits = 4: max_batch * n_nodes and max_batch * (depth + 1) must not exceed 32 rows");
     c->pf_window = 32;
-    c->pf_chunk = std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + 31) / 32 * 32);
+    c->pf_chunk = c->fixed_sums ? 32 : std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + 31) / 32 * 32);
+    c->q4_rot = c->fixed_sums ? 0 : 3;
   }
   int rows = std::max(c->pf_chunk, cfg->max_batch * c->M);
   c->Mmax = (rows + 31) / 32 * 32;
@@ -656,7 +671,7 @@ static int pack_into(eagle_ctx* c, const void* src, PackedW& w, int N, int K, in
   if ((mode == PACK_GATE || mode == PACK_UP) && N % 16) return fail(EAGLE_EINVAL, "d_ffn must be a multiple of 16");
   if (w.q4) {
     const size_t items = (size_t)(mode == PACK_PLAIN ? (N + 31) / 32 * 32 : N) * w.NG;
-    k_pack_weight_q4<bf16_t><<<(unsigned)((items + 255) / 256), 256, 0, c->stream>>>((const bf16_t*)src, (uint32_t*)w.w, w.sc, N, K, row_offset, mode, c->cfg.head_dim);
+    k_pack_weight_q4<bf16_t><<<(unsigned)((items + 255) / 256), 256, 0, c->stream>>>((const bf16_t*)src, (uint32_t*)w.w, w.sc, N, K, row_offset, mode, c->cfg.head_dim, c->q4_rot);
     LAUNCH_CHECK();
     return EAGLE_OK;
   }
@@ -820,7 +835,7 @@ static hipError_t launch_pf_q4(eagle_ctx* c, const PackedW& w, const bf16_t* XF,
 // inside the GEMM and its output goes to swiglu_out in GEMM-input layout; *S is then 0 (nothing left in PT).
 static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S, bf16_t* swiglu_out = nullptr, int M = 0) {
   const bool big = use_pf(c, MT);
-  GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu, swiglu_out != nullptr, c->q4) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
+  GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu, swiglu_out != nullptr, c->q4, c->fixed_sums) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
   const bool fuse = big && swiglu_out && p.S == 1;
   if (!fuse && (size_t)p.S * w.Npad * MT * 32 > c->pt_floats) return fail(EAGLE_EINVAL, "internal: partial buffer too small");
   if (MT < 1 || MT * 32 > std::max(c->Mmax, 2 * c->hl_chunk) || (big && c->f32)) return fail(EAGLE_EINVAL, "internal: MT out of range");
@@ -887,6 +902,11 @@ static KVCache kv_for(eagle_ctx* c, int li) {
 
 static int resnorm(eagle_ctx* c, int M, int MT, const float* h_in, const float* PT, int S, int Npad, const float* bias,
                    const float* gain, bf16_t* XF, float* xout, const float* row_w = nullptr) {
+  if (c->fixed_sums) {
+    k_resnorm_fixed<<<M, 256, 0, c->stream>>>(h_in, PT, S, Npad, MT * 32, bias, c->h, gain, c->cfg.rms_eps, XF, MT, c->NXP, xout, c->cfg.d_model, row_w);
+    LAUNCH_CHECK();
+    return EAGLE_OK;
+  }
   k_resnorm<false><<<M, RESNORM_THREADS, 0, c->stream>>>(h_in, PT, S, Npad, MT * 32, bias, c->h, gain, c->cfg.rms_eps, XF, MT, c->NXP, xout, c->cfg.d_model, row_w,
                                                          nullptr, nullptr, 0, 0);
   LAUNCH_CHECK();
@@ -1141,7 +1161,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   if (w.q4 && ((c->q4_xk_mask >> g.epi) & 1)) {
     const PlanXK px = plan_xk_q4(w.NRB, w.NG, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
     if (px.S > 0) {
-      g.S = px.S; g.groups = px.groups; g.SC = w.sc; g.NG = w.NG;
+      g.S = px.S; g.groups = px.groups; g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
       g.trace = nullptr;
       if (groups_out) *groups_out = px.groups;
       if (g.ssq_out && px.groups > 256) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
@@ -1156,7 +1176,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     // staged, a work-group fetches its K slice of them once.  (Measured at d = 4096: O 13.9 us against 15.0 whole-K, down
     // 25.5 against 29.8, FC 18.9 against 21.8; the wide matrices are faster whole-K: QKV 20.2 against 27.3 -- their
     // epilogues would run on 64 CUs only.)
-    g.SC = w.sc; g.NG = w.NG;
+    g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;
     switch (p.RW) {
       case 1: e = launch_k2<1, 2, 1, 1, true>(c, bytes, g, p.lds); break;
@@ -1171,7 +1191,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     const int grid = std::max(c->n_cu, (w.NRB + 2) / 3);
     const int nrmax = (w.NRB + grid - 1) / grid;
     if (g.epi == EPI_RESID && (grid > 256 || nrmax > 2)) return fail(EAGLE_EINVAL, "internal: residual epilogue on a matrix with %d row blocks", w.NRB);
-    g.SC = w.sc; g.NG = w.NG;
+    g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;
     if (groups_out) *groups_out = grid;
     e = nrmax <= 1 ? launch_fk_q4<1>(c, bytes, g, grid) : nrmax == 2 ? launch_fk_q4<2>(c, bytes, g, grid) : launch_fk_q4<3>(c, bytes, g, grid);

@@ -234,21 +234,24 @@ __global__ __launch_bounds__(256) void k_pack_weight(const SrcT* __restrict__ sr
 // the super-tile, k = 64T + 16j + 8(l/32) + e, with code e at bit 4*(e/2) + 16*(e%2), the word then rotated left by 3:
 // ((word rotated right by 4p) & 0x00780078) | 0x41804180 is then the bf16 pair (16 + code 2p, 16 + code 2p+1), i.e. the MFMA A
 // operand of the k-step comes out of one shift and one and-or per pair (16 + c is exact in bf16; the offset 24 = 16 + 8 is
-// taken off per group: the smallest that leaves room for four bits, so that as little as possible cancels).
+// taken off per group: the smallest that leaves room for four bits, so that as little as possible cancels).  Not rotated, the
+// same takes 0x000F000F and 0x43004300 to pairs of 128 + code (offset 136).
 // Scales: bf16 [rb][group][lane-half][16] in accumulator-register order: entry (hh, r) belongs to row
 // 8*(r/4) + 4*hh + r%4 of the block, so a lane reads the scales of its 16 accumulator rows as 32 contiguous bytes.
 #define EAGLE_Q4_GROUP 128
-__device__ __forceinline__ u32x4 q4_expand(uint32_t wd) {
+struct Q4Format { uint32_t keep, bias; float offset; };        // bits of the codes, what they are or-ed into, what that adds to a code's value
+__host__ __device__ __forceinline__ Q4Format q4_format(int rot) { return rot ? Q4Format{0x00780078u, 0x41804180u, 24.0f} : Q4Format{0x000F000Fu, 0x43004300u, 136.0f}; }
+__device__ __forceinline__ u32x4 q4_expand(uint32_t wd, const Q4Format& f) {
   u32x4 v;
-  v.x = (wd & 0x00780078u) | 0x41804180u;
-  v.y = ((wd >> 4) & 0x00780078u) | 0x41804180u;
-  v.z = ((wd >> 8) & 0x00780078u) | 0x41804180u;
-  v.w = (__builtin_amdgcn_alignbit(wd, wd, 12) & 0x00780078u) | 0x41804180u;   // (the last high code straddles the word's end)
+  v.x = (wd & f.keep) | f.bias;
+  v.y = ((wd >> 4) & f.keep) | f.bias;
+  v.z = ((wd >> 8) & f.keep) | f.bias;
+  v.w = (__builtin_amdgcn_alignbit(wd, wd, 12) & f.keep) | f.bias;   // (rotated, the last high code straddles the word's end)
   return v;
 }
 template <typename SrcT>
 __global__ __launch_bounds__(256) void k_pack_weight_q4(const SrcT* __restrict__ src, uint32_t* __restrict__ dst, bf16_t* __restrict__ sc,
-                                                        int N, int K, int row_offset, int mode, int dh) {
+                                                        int N, int K, int row_offset, int mode, int dh, int rot) {
   const int NG = K / EAGLE_Q4_GROUP, KT = K / 64;
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int nrows = mode == PACK_PLAIN ? (N + 31) / 32 * 32 : N;          // only the plain map pads its last block
@@ -280,7 +283,7 @@ __global__ __launch_bounds__(256) void k_pack_weight_q4(const SrcT* __restrict__
           const float q = fminf(fmaxf(rintf(w[64 * st + 16 * j + 8 * kh + e] / safe), -8.f), 7.f);
           wd |= (uint32_t)((int)q + 8) << (4 * (e >> 1) + 16 * (e & 1));
         }
-        words[j] = (wd << 3) | (wd >> 29);
+        words[j] = __builtin_amdgcn_alignbit(wd, wd, (32 - rot) & 31);   // rotated left
       }
       u32x4 v; v.x = words[0]; v.y = words[1]; v.z = words[2]; v.w = words[3];
       *(u32x4*)(dst + (((size_t)rb * KT + T) * 64 + rho + 32 * kh) * 4) = v;
@@ -662,7 +665,7 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf_q4(const u32x4* __restr
 #pragma unroll
     for (int j = 0; j < RBW; ++j) {
       const uint32_t wd = cd[(i >> 2) & 1][j][i & 3];
-      av[j] = q4_expand(wd);
+      av[j] = q4_expand(wd, q4_format(3));
     }
 #pragma unroll
     for (int q = 0; q < NXP; ++q)
@@ -955,6 +958,80 @@ __global__ __launch_bounds__(RESNORM_THREADS) void k_resnorm(const float* h_in, 
     c.lo = *(const f32x4*)hp; c.hi = *(const f32x4*)(hp + 4);
     c.glo = gain ? *(const f32x4*)(gain + k8) : one; c.ghi = gain ? *(const f32x4*)(gain + k8 + 4) : one;
     phase2(k8, c);
+  }
+}
+
+// The same for dense models with a bf16 cache, whose sums keep one order (a row's sum of squares rounds differently here than above
+// in one row of some hundred, and the cache then rounds some K and V the other way): element by element, 16.1 us at 104 rows.
+__global__ __launch_bounds__(256) void k_resnorm_fixed(const float* h_in, const float* __restrict__ PT, int S, int Npad, int Mpad,
+                                                 const float* bias, float* h_out, const float* gain, float eps,
+                                                 bf16_t* XF, int MT, int nplanes, float* xout, int d, const float* row_w) {
+  __shared__ float sh[16];
+  int r = blockIdx.x;
+  float ss = 0.f;
+  // each thread owns chunks of 8 consecutive k; the first four chunks (rows of up to 8192 columns) stay in registers
+  // for the second phase, further ones are read back from h_out
+  constexpr int KEEP = 4;
+  float keep[KEEP][8];
+  const float rw = row_w ? row_w[r] : 1.0f;    // MoE: this expert's routing weight for the row (0 = not routed here)
+  auto phase1 = [&](int k8, float* v) {
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (PT) {
+      for (int s0 = 0; s0 < S; s0 += 8) {        // eight splits' worth of loads in flight, added in split order
+        f32x4 lo[8], hi[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const float* src = PT + ((size_t)min(s0 + u, S - 1) * Mpad + r) * Npad + k8;
+          lo[u] = *(const f32x4*)src; hi[u] = *(const f32x4*)(src + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (s0 + u < S) {
+            a[0] += lo[u].x; a[1] += lo[u].y; a[2] += lo[u].z; a[3] += lo[u].w;
+            a[4] += hi[u].x; a[5] += hi[u].y; a[6] += hi[u].z; a[7] += hi[u].w;
+          }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      int k = k8 + t;
+      float x = h_in ? h_in[(size_t)r * d + k] : 0.f;
+      if (PT) x += row_w ? rw * a[t] : a[t];
+      if (bias) x += bias[k];
+      h_out[(size_t)r * d + k] = x;
+      ss += x * x;
+      v[t] = x;
+    }
+  };
+#pragma unroll
+  for (int it = 0; it < KEEP; ++it) {
+    const int k8 = (it * (int)blockDim.x + (int)threadIdx.x) * 8;
+    if (k8 < d) phase1(k8, keep[it]);
+  }
+  for (int k8 = (KEEP * blockDim.x + threadIdx.x) * 8; k8 < d; k8 += blockDim.x * 8) { float v[8]; phase1(k8, v); }
+  ss = block_sum(ss, sh);
+  float rstd = gain ? 1.0f / sqrtf(ss / (float)d + eps) : 1.0f;
+  const int KS = d / 16;
+  auto phase2 = [&](int k8, const float* v) {
+    float x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      x[t] = gain ? v[t] * rstd * gain[k8 + t] : v[t];
+      if (xout) xout[(size_t)r * d + k8 + t] = x[t];
+    }
+    if (XF) xf_store8(XF, r, k8, MT, KS, nplanes, x);
+  };
+  if (!XF && !xout) return;
+#pragma unroll
+  for (int it = 0; it < KEEP; ++it) {
+    const int k8 = (it * (int)blockDim.x + (int)threadIdx.x) * 8;
+    if (k8 < d) phase2(k8, keep[it]);
+  }
+  for (int k8 = (KEEP * blockDim.x + threadIdx.x) * 8; k8 < d; k8 += blockDim.x * 8) {
+    float v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = h_out[(size_t)r * d + k8 + t];
+    phase2(k8, v);
   }
 }
 

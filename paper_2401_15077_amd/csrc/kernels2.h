@@ -145,6 +145,7 @@ struct Gemm2 {
   const float* h_in; float* h_out; const float* bias; const float* gain_next; bf16_t* xf_out; int xf_KS; float* ssq_out; int d;
   // EPI_LOGITS
   float* logits; int V;
+  Q4Format q4;                            // 4-bit weights: how a code becomes a bf16 value
   const bf16_t* SC; int NG;               // 4-bit weights: scales [NRB][NG][2][16] and groups along K (W then holds codes)
   const float* row_w;                     // MoE: per-row routing weight applied to this GEMM's result (nullptr = 1)
   const int* skip_flag;                   // MoE: the whole launch is a no-op when *skip_flag == 0 (no row uses the expert)
@@ -453,7 +454,7 @@ __device__ __forceinline__ void k2_stream(const u32x4* __restrict__ xs, int kt, 
 // slice starts at group g0 of the matrix).  With a quarter of the weight bytes the activation fragments are what a CU
 // fetches most of, so here they are fetched ONCE per work-group (into LDS) and every wave reads them from there.
 template <int NXP, int NR>
-__device__ __forceinline__ void k2_stream_q4(const u32x4* __restrict__ xs, int kt, int g0, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ void k2_stream_q4(const Q4Format fmt, const u32x4* __restrict__ xs, int kt, int g0, int gb, int ge, const u32x4* const* wq,
                                              const u32x4* const* sq, f32x16* acc, int lane) {
   if (ge <= gb) return;
   const int glast = ge - 1;
@@ -486,7 +487,7 @@ __device__ __forceinline__ void k2_stream_q4(const u32x4* __restrict__ xs, int k
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
           const uint32_t wd = ks == 0 ? a4[st][j].x : ks == 1 ? a4[st][j].y : ks == 2 ? a4[st][j].z : a4[st][j].w;
-          const u32x4 av = q4_expand(wd);
+          const u32x4 av = q4_expand(wd, fmt);
 #pragma unroll
           for (int q = 0; q < NXP; ++q)
             part[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bq[q]), part[j], 0, 0, 0);
@@ -505,16 +506,16 @@ __device__ __forceinline__ void k2_stream_q4(const u32x4* __restrict__ xs, int k
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float sv = __builtin_bit_cast(float, (r & 1) ? (sw[r >> 1] & 0xFFFF0000u) : (sw[r >> 1] << 16));
-        acc[j][r] += sv * (part[j][r] - 24.0f * sx[r]);
+        acc[j][r] += sv * (part[j][r] - fmt.offset * sx[r]);
       }
     }
   }
 }
 template <int NXP, int RW, int NR>
-__device__ __forceinline__ void k2_stream_q4_dispatch(int nr, const u32x4* xs, int kt, int g0, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ void k2_stream_q4_dispatch(int nr, const Q4Format fmt, const u32x4* xs, int kt, int g0, int gb, int ge, const u32x4* const* wq,
                                                       const u32x4* const* sq, f32x16* acc, int lane) {
-  if (nr == NR) k2_stream_q4<NXP, NR>(xs, kt, g0, gb, ge, wq, sq, acc, lane);
-  else if constexpr (NR > 1) k2_stream_q4_dispatch<NXP, RW, NR - 1>(nr, xs, kt, g0, gb, ge, wq, sq, acc, lane);
+  if (nr == NR) k2_stream_q4<NXP, NR>(fmt, xs, kt, g0, gb, ge, wq, sq, acc, lane);
+  else if constexpr (NR > 1) k2_stream_q4_dispatch<NXP, RW, NR - 1>(nr, fmt, xs, kt, g0, gb, ge, wq, sq, acc, lane);
 }
 
 template <int NWP, int NXP, int RW, int NR, int DEPTH>
@@ -600,7 +601,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
       wq[j] = (const u32x4*)g.W + (size_t)rb * (size_t)(g.KS / 4) * 64 + lane;
       sq[j] = (const u32x4*)g.SC + (size_t)rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
     }
-    k2_stream_q4_dispatch<NXP, RW, RW>(nr, xs, kt, gs0, qgb, qge, wq, sq, acc, lane);
+    k2_stream_q4_dispatch<NXP, RW, RW>(nr, g.q4, xs, kt, gs0, qgb, qge, wq, sq, acc, lane);
   } else
   k2_stream_dispatch<NWP, NXP, RW, RW, DEPTH>(nr, xs, kt, kb, ke, wp, g.wps, acc, lane, pre);
   TRACE_STAMP(tr, 2);
@@ -758,13 +759,13 @@ __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int
 
 // ---- the same stream over 4-bit weights (see k_pack_weight_q4 for the layout) -------------------------------------------
 // A wave owns the groups [gb, ge) of 128 k.  Per group: two 16-byte loads per row block bring the codes of its 8 k-steps;
-// a k-step's A operand is 16 + code (exact in bf16) -- two ALU operations per pair of codes, which run beside the MFMAs
+// a k-step's A operand is 16 + code (128 + code in the unrotated format) (exact in bf16) -- two ALU operations per pair of codes, which run beside the MFMAs
 // -- so the group's partial sums come out as sum_k x_k (16 + c_k); an MFMA against an all-ones tile gives sum_k x_k of
 // the same k-steps, and the group is folded into the result as  acc += s_row * (partial - 24 * sum_x)  in fp32.
 // Activation fragments are streamed from L2 as in fk_stream, one group (8 k-steps) ahead; the next group's codes are
 // requested as soon as a super-tile's registers are free.
 template <int NXP, int NR>
-__device__ __forceinline__ void fk_stream_q4(const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, const u32x4* const* wq,
                                              const u32x4* const* sq /*scales of (block j, group 0), this lane's half*/, int NG,
                                              f32x16* acc, int lane) {
   if (ge <= gb) return;
@@ -801,7 +802,7 @@ __device__ __forceinline__ void fk_stream_q4(const bf16_t* __restrict__ XF, int 
         const int kk = 8 * g + 4 * st + ks;
         auto expand = [&](int j) {
           const uint32_t wd = ks == 0 ? a4[st][j].x : ks == 1 ? a4[st][j].y : ks == 2 ? a4[st][j].z : a4[st][j].w;
-          return q4_expand(wd);
+          return q4_expand(wd, fmt);
         };
         if constexpr (NR <= 2) {
           // plane by plane, so that consecutive MFMAs write different accumulators (measured: QKV 20.4 -> 19.3 us, down
@@ -845,17 +846,17 @@ __device__ __forceinline__ void fk_stream_q4(const bf16_t* __restrict__ XF, int 
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float sv = __builtin_bit_cast(float, (r & 1) ? (sw[r >> 1] & 0xFFFF0000u) : (sw[r >> 1] << 16));
-        acc[j][r] += sv * (part[j][r] - 24.0f * sx[r]);
+        acc[j][r] += sv * (part[j][r] - fmt.offset * sx[r]);
       }
     }
   }
 #undef Q4_XLOAD
 }
 template <int NXP, int NR>
-__device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const bf16_t* XF, int KS, int M, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt, const bf16_t* XF, int KS, int M, int gb, int ge, const u32x4* const* wq,
                                                       const u32x4* const* sq, int NG, f32x16* acc, int lane) {
-  if (nr == NR) fk_stream_q4<NXP, NR>(XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
-  else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
+  if (nr == NR) fk_stream_q4<NXP, NR>(fmt, XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
+  else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
 }
 
 // sum over the 8 waves of element (row n_local of row block j, token m) of the per-wave accumulators parked in LDS
@@ -931,7 +932,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
       wq[j] = (const u32x4*)g.W + rb * (size_t)(g.KS / 4) * 64 + lane;
       sq[j] = (const u32x4*)g.SC + rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
     }
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
+    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
     if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
   fk_stream_dispatch<NWP, NXP, NRMAX, HALF>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane, &hw);
@@ -1090,7 +1091,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
       wq[j] = (const u32x4*)g.W + rb * (size_t)(g.KS / 4) * 64 + lane;
       sq[j] = (const u32x4*)g.SC + rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
     }
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
+    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
     if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
   fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane);
