@@ -162,9 +162,11 @@ static GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
   return p;
 }
 
-// Which passes of the general path take the large-M GEMM: every pass of more than 128 rows (only prompts, and only
-// where the kernel exists), and batched tree passes of 65..128 rows of the models it covers; with 4-bit weights all.
-static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= 3 && c->big_gemm) || c->q4; }
+// Which passes of the general path take the large-M GEMM: every pass of more than 128 rows (only prompts, and only where the
+// kernel exists), and shorter ones of the models it covers: prompts and batched tree passes of 33..128 rows (33..64 rows, us a
+// matrix against k_gemm: 7B QKV 27 / 34, O 12.3 / 17.3, gate/up 40 / 59, down 24 / 33; LM head 58 / 71), 65..128 where the sums
+// keep their order; with 4-bit weights all.
+static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= (c->fixed_sums ? 3 : 2) && c->big_gemm) || c->q4; }
 
 // Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
 // in a model of two terms, in us.  What the busiest CU multiplies: rounds x (32 x 32 tiles of a work-group) x k-steps of a slice
@@ -181,12 +183,13 @@ static int plan_slices(int NRB, int KS, int MT, int n_cu) {     // K slices as a
 static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4, bool fixed_sums) {
   GemmPlan best{};
   double best_us = -1;
-  static const struct { int rbw, mw; double ns; } shapes[7] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}, {2, 4, 17.0}};
+  static const struct { int rbw, mw; double ns; } shapes[9] = {{4, 1, 20.0}, {3, 1, 22.0}, {4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}, {2, 4, 17.0}};
   const int xcds = 8, cu_x = std::max(1, n_cu / xcds);
-  for (int i = q4 ? 5 : 0; i < (q4 ? 7 : 5); ++i) {
+  for (int i = q4 ? 7 : 0; i < (q4 ? 9 : 7); ++i) {
     const auto& sh = shapes[i];
     const int wt = 2 * sh.rbw, rt = 2 * sh.mw, mq = (MT + rt - 1) / rt, nt = (NRB + wt - 1) / wt;
     if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
+    if (!q4 && (MT <= 2) != (sh.mw == 1)) continue;            // two tiles of rows: work-groups of two waves, bound by the weight stream
     const int S_fix = fixed_sums ? plan_slices(NRB, KS, MT, n_cu) : 0;
     for (int S = fixed_sums ? S_fix : 1; S <= (fixed_sums ? S_fix : 16); ++S) {
       if (!fixed_sums && S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
@@ -849,7 +852,8 @@ static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S
   } else if (big) {
     bf16_t* out = fuse ? swiglu_out : nullptr;
     if (p.mw == 4) e = p.rbw == 4 ? launch_pf<4, 4>(c, w, XF, MT, p, out, M) : p.rbw == 3 ? launch_pf<3, 4>(c, w, XF, MT, p, out, M) : launch_pf<2, 4>(c, w, XF, MT, p, out, M);
-    else e = p.rbw == 4 ? launch_pf<4, 2>(c, w, XF, MT, p, out, M) : launch_pf<3, 2>(c, w, XF, MT, p, out, M);
+    else if (p.mw == 2) e = p.rbw == 4 ? launch_pf<4, 2>(c, w, XF, MT, p, out, M) : launch_pf<3, 2>(c, w, XF, MT, p, out, M);
+    else e = p.rbw == 4 ? launch_pf<4, 1>(c, w, XF, MT, p, out, M) : launch_pf<3, 1>(c, w, XF, MT, p, out, M);
   } else e = c->f32 ? launch_gemm_mt<3, 3>(c, w, XF, c->PT, MT, p) : launch_gemm_mt<1, 2>(c, w, XF, c->PT, MT, p);
   if (e != hipSuccess) return fail(EAGLE_EHIP, "gemm launch failed: %s", hipGetErrorString(e));
   return EAGLE_OK;

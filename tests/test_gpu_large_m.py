@@ -16,7 +16,7 @@ from test_gpu_parity import TOL, make_pair
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows", [65, 97, 129, 257, 333, 512, 513, 600, 1100, 2049, 2200])
+@pytest.mark.parametrize("rows", [33, 64, 65, 97, 129, 257, 333, 512, 513, 600, 1100, 2049, 2200])
 def test_prompt_rows_at_tile_edges(rows):
     s, eng, orc = make_pair("mini-gqa", "T8", seed=11, max_seq=2300)
     print("prompt of", rows, flush=True)
