@@ -221,6 +221,23 @@ __device__ __forceinline__ void pin_args(const Gemm2& g) {
   asm volatile("" ::"s"(g.W), "s"(g.XF), "s"(g.NRB), "s"(g.KS), "s"(g.M), "s"(g.facts), "s"(g.in_scale.ssq), "s"(g.in_scale.groups), "s"(g.skip_flag));
 }
 
+// Four consecutive values of row m, columns k.. (k a multiple of 4), as GEMM input (8 bytes per plane).
+__device__ inline void xf_store4(bf16_t* XF, int m, int k, int MT, int KS, int nplanes, f32x4 x) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    if (q < nplanes) {
+      uint32_t b[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const bf16_t h = f32_to_bf16(x[t]);
+        b[t] = h;
+        x[t] -= bf16_to_f32(h);
+      }
+      uint2 v; v.x = b[0] | (b[1] << 16); v.y = b[2] | (b[3] << 16);
+      *(uint2*)(XF + xf_index(m, k, q, MT, KS)) = v;
+    }
+}
+
 template <int NXP>
 __device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float* rstd_s, const EarlyLoads& rp) {
   const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;
@@ -268,41 +285,53 @@ __device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float*
   }
 }
 
+// A wave owns chunks of 8 output rows (n), a lane four of them: lanes 0..31 the first four of tokens 0..31, lanes 32..63 the other
+// four; residual, bias, gain and the partials come as 16-byte loads, all in flight together.  (A lane per chunk and token, row by
+// row, used half of the threads and touched 64 lines with each of its 16 four-byte accesses.)  A token's squares are added
+// chunk by chunk in row order, chunks c, c + 16, ... in one chain: the lower lanes begin a chunk's part, the upper ones go on.
 template <int NXP>
 __device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, float* sh /*>= 16*32 floats*/) {
-  const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;
+  const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5, w = threadIdx.x >> 6;
   const bool live = m < g.M;
-  const int nchunks = (n1 - n0 + 7) >> 3;
-  float ss = 0.f;
-  for (int c = slot; c < nchunks; c += V2_THREADS / 32) {
-    const int n = n0 + 8 * c;
-    float x[8], pv[8], hv[8], bv[8], gv[8];
-    int rows[8];
-    const float rw = g.row_w ? g.row_w[m] : 1.0f;
+  const int nchunks = (n1 - n0) >> 3;                        // n0 and n1 are multiples of 32 (d_model is one of 64)
+  const float rw = g.row_w ? g.row_w[m] : 1.0f;
+  float ss[2] = {0.f, 0.f};                                  // chains w and w + 8
+  int turn = 0;
+  for (int c = w; c < nchunks; c += V2_THREADS / 64, turn ^= 1) {
+    const int n = n0 + 8 * c + 4 * hh;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 hv = g.h_in && live ? *(const f32x4*)(g.h_in + (size_t)m * g.d + n) : zero;
+    const f32x4 bv = g.bias ? *(const f32x4*)(g.bias + n) : zero;
+    const f32x4 gv = g.gain_next ? *(const f32x4*)(g.gain_next + n) : zero;
+    f32x4 v = zero;
+    for (int s0 = 0; s0 < g.S; s0 += 8) {                    // added in split order
+      f32x4 p[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {                            // everything that does not depend on the partials first
-      rows[t] = min(n + t, n1 - 1);
-      hv[t] = (g.h_in && live) ? g.h_in[(size_t)m * g.d + rows[t]] : 0.f;
-      bv[t] = g.bias ? g.bias[rows[t]] : 0.f;
-      gv[t] = g.gain_next ? g.gain_next[rows[t]] : 1.0f;
-    }
-    pt_sum8(g.PT, g.S, g.Npad, n, n + 4, m, pv);            // rows up to the padded end of the block exist (zero weights)
+      for (int u = 0; u < 8; ++u)
+        if (u < 4 || g.S > 4) p[u] = coh_load16(g.PT, pt_quad_bytes(min(s0 + u, g.S - 1), g.Npad, n, m));
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      float v = 0.f;
-      if (n + t < n1) {
-        v = g.row_w ? rw * pv[t] : pv[t];
-        if (g.bias) v += bv[t];
-        if (g.h_in && live) v += hv[t];
-        if (live) g.h_out[(size_t)m * g.d + n + t] = v;
-        ss += v * v;
-        x[t] = g.gain_next ? v * gv[t] : v;
-      } else x[t] = 0.f;
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < g.S) v += p[u];
     }
-    if (live) xf_store8(g.xf_out, m, n, 1, g.xf_KS, NXP, x);
+    if (g.row_w) v *= rw;
+    if (g.bias) v += bv;
+    if (g.h_in && live) v += hv;
+    if (live) *(f32x4*)(g.h_out + (size_t)m * g.d + n) = v;
+    float a = turn ? ss[1] : ss[0];
+    float up = a;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) up = fmaf(v[t], v[t], up);   // (upper lanes: not used)
+    a = __shfl(up, m, 64);                                   // what the lower lanes have reached
+#pragma unroll
+    for (int t = 0; t < 4; ++t) a = fmaf(v[t], v[t], a);     // (lower lanes: not used)
+    a = __shfl(a, m + 32, 64);
+    if (turn) ss[1] = a; else ss[0] = a;
+    f32x4 x = v;
+    if (g.gain_next) x = v * gv;
+    if (live) xf_store4(g.xf_out, m, n, 1, g.xf_KS, NXP, x);
   }
   __syncthreads();
-  sh[slot * 32 + m] = ss;
+  if (hh == 0) { sh[w * 32 + m] = ss[0]; sh[(w + 8) * 32 + m] = ss[1]; }
   __syncthreads();
   if (threadIdx.x < 32 && g.ssq_out) {
     float a = 0.f;
@@ -859,13 +888,25 @@ __device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt
   else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
 }
 
-// sum over the 8 waves of element (row n_local of row block j, token m) of the per-wave accumulators parked in LDS
-// as red[w][j][r][lane] (MFMA layout: r = 4*(n_local/8) + n_local%4, lane = m + 32*((n_local/4)%2)); k-part order
+// The waves' accumulators parked in LDS as red[w][j][i][lane], 16 bytes each = registers 4i..4i+3 (MFMA layout: rows 8i + 4*(lane/32)
+// + 0..3 of row block j, token lane%32).  Sum over the 8 waves, in order, of the four rows 4*qd.. of block j, token m.
+__device__ __forceinline__ void fk_park(float* red, int nrmax, int w, int j, int lane, const f32x16& acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f32x4 v; v.x = acc[4 * i]; v.y = acc[4 * i + 1]; v.z = acc[4 * i + 2]; v.w = acc[4 * i + 3];
+    *(f32x4*)(red + ((((size_t)w * nrmax + j) * 4 + i) * 64 + lane) * 4) = v;
+  }
+}
+__device__ __forceinline__ f32x4 fk_sum4(const float* red, int nrmax, int j, int qd, int m) {
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 8; ++w) a += *(const f32x4*)(red + ((((size_t)w * nrmax + j) * 4 + (qd >> 1)) * 64 + m + 32 * (qd & 1)) * 4);
+  return a;
+}
 __device__ inline float fk_sum(const float* red, int nrmax, int j, int n_local, int m) {
-  const int r = 4 * (n_local >> 3) + (n_local & 3), l = m + 32 * ((n_local >> 2) & 1);
   float a = 0.f;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) a += red[(((size_t)w * nrmax + j) * 16 + r) * 64 + l];
+  for (int w = 0; w < 8; ++w) a += red[((((size_t)w * nrmax + j) * 4 + (n_local >> 3)) * 64 + m + 32 * ((n_local >> 2) & 1)) * 4 + (n_local & 3)];
   return a;
 }
 
@@ -940,35 +981,37 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   // park every wave's sums in LDS
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
-    if (j < nr)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) red[(((size_t)w * NRMAX + j) * 16 + r) * 64 + lane] = acc[j][r];
+    if (j < nr) fk_park(red, NRMAX, w, j, lane, acc[j]);
   block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);   // (contains the barriers that publish `red`)
   __syncthreads();
   const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;     // 16 slots of 32 tokens
   const bool live = m < g.M;
   const float rs = live ? rstd_s[m] : 0.f;
   if (g.epi == EPI_SWIGLU) {
-    // item = (row block j, half c2): 8 outputs f = rb*16 + 8*c2 .. +7 from gate rows 8*c2.. and up rows 16 + 8*c2..
-    for (int it = slot; it < nr * 2; it += 16) {
-      const int j = it >> 1, c2 = it & 1;
-      float x[8];
+    // item = (row block j, quarter qt): outputs f = rb*16 + 4*qt .. +3 from gate rows 4*qt.. and up rows 16 + 4*qt..
+    for (int it = slot; it < nr * 4; it += 16) {
+      const int j = it >> 2, qt = it & 3;
+      const f32x4 gq = fk_sum4(red, NRMAX, j, qt, m), uq = fk_sum4(red, NRMAX, j, 4 + qt, m);
+      f32x4 x;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float gg = fk_sum(red, NRMAX, j, 8 * c2 + t, m) * rs, uu = fk_sum(red, NRMAX, j, 16 + 8 * c2 + t, m) * rs;
+      for (int t = 0; t < 4; ++t) {
+        const float gg = gq[t] * rs, uu = uq[t] * rs;
         x[t] = gg / (1.0f + __expf(-gg)) * uu;
       }
-      if (live) xf_store8(g.xf_out, m, (rb0 + j) * 16 + 8 * c2, 1, g.xf_KS, NXP, x);
+      if (live) xf_store4(g.xf_out, m, (rb0 + j) * 16 + 4 * qt, 1, g.xf_KS, NXP, x);
     }
   } else if (g.epi == EPI_QKV) {
     const int dh = g.kv.head_dim, half = dh >> 1, KVH = g.kv.n_kv_heads, H = g.H;
-    // item = (row block j, rotate-half pair pp of 16): rows 2pp, 2pp + 1 of the block
-    for (int it = slot; it < nr * 16; it += 16) {
-      const int j = it >> 4, pp = it & 15;
-      const int n = (rb0 + j) * 32 + 2 * pp;
+    // item = (row block j, quad qd of 8): rows 4qd.. of the block, two rotate-half pairs
+    for (int it = slot; it < nr * 8; it += 16) {
+      const int j = it >> 3, qd = it & 7;
+      if (HALF && (4 * qd < (j == 0 ? row_lo : 0) || 4 * qd >= (j == nr - 1 ? row_hi : 32))) continue;   // the neighbour's rows
+      const f32x4 sum = fk_sum4(red, NRMAX, j, qd, m);
+#pragma unroll
+     for (int p = 0; p < 2; ++p) {
+      const int n = (rb0 + j) * 32 + 4 * qd + 2 * p;
       if (n >= g.N || !live) continue;
-      if (HALF && (2 * pp < (j == 0 ? row_lo : 0) || 2 * pp >= (j == nr - 1 ? row_hi : 32))) continue;   // the neighbour's rows
-      float a = fk_sum(red, NRMAX, j, 2 * pp, m) * rs, b = fk_sum(red, NRMAX, j, 2 * pp + 1, m) * rs;
+      float a = sum[2 * p] * rs, b = sum[2 * p + 1] * rs;
       const int hd = n / dh, pr = n % dh;
       int d1, d2;
       if (hd < H + KVH) {        // q or k head: the two rows are a rotate-half pair
@@ -987,6 +1030,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
         if (g.kv_f32) { ((float*)base)[off + d1] = a; ((float*)base)[off + d2] = b; }
         else { ((bf16_t*)base)[off + d1] = f32_to_bf16(a); ((bf16_t*)base)[off + d2] = f32_to_bf16(b); }
       }
+     }
     }
   } else if (g.epi == EPI_RESID) {
     // h_out = h_in + (routing weight *) W x + bias on this work-group's rows [n_lo, n_hi); per-token partial sums of
@@ -1028,10 +1072,8 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
       const int j = it >> 3, qd = it & 7;
       const int n = (rb0 + j) * 32 + 4 * qd;
       if (dst < 0 || n >= nend) continue;
-      float v[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = fk_sum(red, NRMAX, j, 4 * qd + t, m) * rs;
-      if (vec && n + 4 <= nend) { f32x4 o; o.x = v[0]; o.y = v[1]; o.z = v[2]; o.w = v[3]; *(f32x4*)(g.logits + dst + n) = o; }
+      const f32x4 v = fk_sum4(red, NRMAX, j, qd, m) * rs;
+      if (vec && n + 4 <= nend) *(f32x4*)(g.logits + dst + n) = v;
       else {
 #pragma unroll
         for (int t = 0; t < 4; ++t) if (n + t < nend) g.logits[dst + n + t] = v[t];
@@ -1098,22 +1140,14 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
-    if (j < nr)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) red[(((size_t)w * NRMAX + j) * 16 + r) * 64 + lane] = acc[j][r];
+    if (j < nr) fk_park(red, NRMAX, w, j, lane, acc[j]);
   __syncthreads();
   // the waves share the sum and the publication: item = (row block j, register quad i) -> rows 8i + 4(lane/32) + 0..3
   for (int it = w; it < nr * 4; it += 8) {
     const int j = it >> 2, i = it & 3;
-    float v[4];
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      float a = 0.f;
-#pragma unroll
-      for (int ww = 0; ww < 8; ++ww) a += red[(((size_t)ww * NRMAX + j) * 16 + 4 * i + t) * 64 + lane];
-      v[t] = a;
-    }
-    f32x4 o; o.x = v[0]; o.y = v[1]; o.z = v[2]; o.w = v[3];
+    for (int ww = 0; ww < 8; ++ww) o += *(const f32x4*)(red + ((((size_t)ww * NRMAX + j) * 4 + i) * 64 + lane) * 4);
     coh_store16(g.PT, pt_quad_bytes(s, g.Npad, (rb0 + j) * 32 + 8 * i + 4 * (lane >> 5), lane & 31), o);
   }
   TRACE_STAMP(tr, 3);
@@ -1220,23 +1254,6 @@ __device__ inline void load8(const bf16_t* p, float* x) {
   x[2] = __builtin_bit_cast(float, r.y << 16); x[3] = __builtin_bit_cast(float, r.y & 0xFFFF0000u);
   x[4] = __builtin_bit_cast(float, r.z << 16); x[5] = __builtin_bit_cast(float, r.z & 0xFFFF0000u);
   x[6] = __builtin_bit_cast(float, r.w << 16); x[7] = __builtin_bit_cast(float, r.w & 0xFFFF0000u);
-}
-
-// Four consecutive values of row m, columns k.. (k a multiple of 4), as GEMM input (8 bytes per plane).
-__device__ inline void xf_store4(bf16_t* XF, int m, int k, int MT, int KS, int nplanes, f32x4 x) {
-#pragma unroll
-  for (int q = 0; q < 3; ++q)
-    if (q < nplanes) {
-      uint32_t b[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bf16_t h = f32_to_bf16(x[t]);
-        b[t] = h;
-        x[t] -= bf16_to_f32(h);
-      }
-      uint2 v; v.x = b[0] | (b[1] << 16); v.y = b[2] | (b[3] << 16);
-      *(uint2*)(XF + xf_index(m, k, q, MT, KS)) = v;
-    }
 }
 
 // Folds NS splits (e, e+1, ...) of one (row, head) into the running (max, denominator, outputs) of IT items (rows) at once:
