@@ -60,13 +60,13 @@ typedef struct {
                                          symmetric, per output row and group of 128 input columns: scale = bf16(max|w| / 7),
                                          code = clip(rint(w / scale), -8, 7), value scale * code.  Needs a dense bf16
                                          model whose widths are multiples of 128, and at most 32 rows per pass
-                                         (max_batch * n_nodes <= 32); the prompt then runs 32 rows at a time. */
+                                         (max_batch * n_nodes <= 32); prompts may be longer. */
   int32_t head_loss_rows;             /* 0: off.  > 0: the workspace also holds what eagle_head_loss needs -- a second
                                          copy of the LM head re-tiled for the product with its transpose, and one
                                          pass's gradient of the logits -- (about 2 * vocab * d_model + 4 * vocab * pass
                                          rows bytes); needs a bf16 model with weight_bits 0 / 16 and vocab % 64 == 0.
-                                         The value itself only switches the feature on: any row count is processed in
-                                         passes. */
+                                         The value sizes those passes (up to 1024 rows): give the usual row count.  Any
+                                         row count is processed, in as many passes as it takes. */
 } eagle_config;
 
 /* Which tensor eagle_load_weight() is given.  Matrices are row-major [out_features, in_features] in the
@@ -224,8 +224,8 @@ int eagle_get_kernel_stats(eagle_ctx *ctx, int32_t phase, eagle_kernel_stat *out
  * f (the target's feature of the next position: the label) and fhat (the head's prediction) are DEVICE pointers to
  * fp32 [rows, d_model], row-major, only read; the LM head is the one loaded into the context (frozen: it gets no
  * gradient).  grad_fhat: DEVICE pointer, fp32 [rows, d_model], written (may be null: loss only).  loss_out: HOST
- * pointer to 3 floats: L, L_reg, L_cls.  Any rows >= 1; the rows are processed in passes of at most half the
- * context's largest pass each (256 rows for a dense bf16 model).  Leaves the decoding state of the context untouched
+ * pointer to 3 floats: L, L_reg, L_cls.  Any rows >= 1; the rows are processed in passes of head_loss_rows rows,
+ * at most 1024, and at least half of the context's largest pass.  Leaves the decoding state of the context untouched
  * (it uses only buffers that live within one pass).  Needs cfg.head_loss_rows > 0 and the LM head loaded
  * (EAGLE_ESTATE otherwise).  Synchronises the stream (the loss is returned by value). */
 int eagle_head_loss(eagle_ctx *ctx, const float *f_dev, const float *fhat_dev, int32_t rows, float w_cls,

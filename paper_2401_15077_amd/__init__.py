@@ -267,7 +267,7 @@ class Eagle:
         chunk = 512 if (s.dtype == "bf16" and s.d_ffn % 64 == 0 and (s.n_heads * s.head_dim) % 64 == 0) else 128
         if self.weight_bits == 4:
             chunk = 32
-        self.last_prefill_rows = (len(p) - 1) % chunk + 1          # rows of the prompt's last pass
+        self.last_prefill_rows = (len(p) - 1) % chunk + 1          # rows of the prompt's last window
         self.n_active = max(self.n_active, seq + 1)
         return int(first.value)
 

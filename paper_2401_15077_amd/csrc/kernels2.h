@@ -1458,8 +1458,7 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const RowFact* __restr
   if (hh == 0) { ml_s[(w * 2 + 0) * 32 + q] = m_run; ml_s[(w * 2 + 1) * 32 + q] = l_run; }
   __syncthreads();
   // thread = (four consecutive columns d0, rows tid / LD + RT * i): the lanes of a row write its partial output, and read the
-  // other splits' below, in contiguous runs.  (With a row per lane each 16-byte access of a wave touched 64 cache lines: 4.6 us
-  // from the arrival to the end of the kernel at 5 splits and 27 rows, now 2.9.)
+  // other splits' below, in contiguous runs.  (With a row per lane each 16-byte access of a wave touched 64 cache lines.)
   constexpr int LD = DH / 4, RT = 256 / LD, NI = 32 / RT;       // lanes per row, rows at a time, items per thread
   const int d0 = (tid % LD) * 4, q0 = tid / LD;
   const int KSX = H * DH / 16;
