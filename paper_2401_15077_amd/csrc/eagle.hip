@@ -3,6 +3,7 @@
 #include "../../include/eagle.h"
 #include "kernels.h"
 #include "kernels2.h"
+#include "plans.h"
 #include <hip/hip_ext.h>
 
 #include <cmath>
@@ -57,7 +58,6 @@ struct LayerW {
   float *attn_norm = nullptr, *mlp_norm = nullptr;
   bool moe = false;
 };
-struct GemmPlan { int S, ks_per_split, chunk, rbw, mw; };   // rbw, mw: tile shape of the large-M GEMM (0: k_gemm)
 
 // Kernel classes of the per-launch timing (profiling mode 2): what the launch computes, not which template ran
 // (the template's name is recorded beside it).
@@ -151,145 +151,7 @@ struct eagle_ctx {
   eagle_profile prof;
 };
 
-static GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
-  GemmPlan p{};
-  int wg_n = (NRB + 3) / 4;
-  int S = std::max(1, std::min(16, 512 / std::max(1, wg_n)));
-  S = std::min(S, std::max(1, KS / 8));
-  p.ks_per_split = (KS + S - 1) / S;
-  p.S = (KS + p.ks_per_split - 1) / p.ks_per_split;
-  p.chunk = std::max(1, 64 / (NXP * MT));
-  return p;
-}
-
-// Which passes of the general path take the large-M GEMM: every pass of more than 128 rows (only prompts, and only where the
-// kernel exists), and shorter ones of the models it covers: prompts and batched tree passes of 33..128 rows (33..64 rows, us a
-// matrix against k_gemm: 7B QKV 27 / 34, O 12.3 / 17.3, gate/up 40 / 59, down 24 / 33; LM head 58 / 71), 65..128 where the sums
-// keep their order; with 4-bit weights all.
-static bool use_pf(const eagle_ctx* c, int MT) { return MT > 4 || (MT >= (c->fixed_sums ? 3 : 2) && c->big_gemm) || c->q4; }
-
-// Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
-// in a model of two terms, in us.  What the busiest CU multiplies: rounds x (32 x 32 tiles of a work-group) x k-steps of a slice
-// x the shape's measured time per tile and k-step.  Groups of work-groups that share a weight tile go round the 8 XCDs, so a
-// round is full when the XCD with one group more than the others is (LM-head transpose, 10 row tiles, 3 slices of 27 x 3
-// tiles: 243 work-groups, but 33 on the 32 CUs of one XCD: 355 us against 197 for 240 of the next shape).  And what the partial
-// sums cost that all but the fused epilogue write and read back, at 4.5 TB/s.
-// 4-bit weights (k_gemm_pf_q4): two row blocks per wave, K slices of whole groups of 8 k-steps.
-static int plan_slices(int NRB, int KS, int MT, int n_cu) {     // K slices as a function of the shape alone (fixed_sums)
-  const int wgs = ((NRB + 7) / 8) * ((MT + 3) / 4);
-  int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? 16 : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
-  return std::max(1, std::min(S, KS / (MT <= 4 ? 16 : 32)));
-}
-static GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4, bool fixed_sums) {
-  GemmPlan best{};
-  double best_us = -1;
-  static const struct { int rbw, mw; double ns; } shapes[9] = {{4, 1, 20.0}, {3, 1, 22.0}, {4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}, {2, 4, 17.0}};
-  const int xcds = 8, cu_x = std::max(1, n_cu / xcds);
-  for (int i = q4 ? 7 : 0; i < (q4 ? 9 : 7); ++i) {
-    const auto& sh = shapes[i];
-    const int wt = 2 * sh.rbw, rt = 2 * sh.mw, mq = (MT + rt - 1) / rt, nt = (NRB + wt - 1) / wt;
-    if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
-    if (!q4 && (MT <= 2) != (sh.mw == 1)) continue;            // two tiles of rows: work-groups of two waves, bound by the weight stream
-    const int S_fix = fixed_sums ? plan_slices(NRB, KS, MT, n_cu) : 0;
-    for (int S = fixed_sums ? S_fix : 1; S <= (fixed_sums ? S_fix : 16); ++S) {
-      if (!fixed_sums && S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
-      const int unit = q4 ? 8 : 4, kps = ((KS + S - 1) / S + unit - 1) / unit * unit, s_real = (KS + kps - 1) / kps;
-      const int rounds = ((nt * s_real + xcds - 1) / xcds * mq + cu_x - 1) / cu_x;
-      double us = 1e-3 * sh.ns * rounds * wt * rt * kps + 4.0;
-      if (!(fused_epilogue && s_real == 1)) us += (double)s_real * MT * NRB * 8192.0 / 4.5e6;
-      if (fused_epilogue && s_real > 1) us += 10.0;             // the SwiGLU kernel behind it
-      if (best_us < 0 || us < best_us) { best_us = us; best.S = s_real; best.ks_per_split = kps; best.chunk = 4; best.rbw = sh.rbw; best.mw = sh.mw; }
-    }
-  }
-  return best;
-}
-
-// The same model for the grouped GEMMs of a mixture of experts: M rows x topk experts each, padded per expert to columns of
-// 2 * mw tiles.  Routing is uneven, so half a column more per expert and half a round more at the end are counted.  Both GEMMs of the MLP share the column width; gate/up keeps one K slice (SwiGLU in its epilogue).
-struct PlanMoe { GemmPlan gu, dn; int cols; };
-static int moe_tiles(int M, int topk, int E) { return (M * topk + 31) / 32 + std::min(E, M * topk); }
-static PlanMoe plan_moe(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int M, int topk, int E, int n_cu) {
-  PlanMoe best{};
-  double best_us = -1;
-  static const struct { int rbw, mw; double ns; } shapes[5] = {{4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}};
-  const int used = std::min(E, M * topk), te = (M * topk + 32 * used - 1) / (32 * used), cu_x = std::max(1, n_cu / 8);
-  for (int mw = 2; mw <= 4; mw += 2) {
-    const int rt = 2 * mw;
-    const double cols = used * std::max(1.0, (double)te / rt + 0.5);
-    GemmPlan q[2] = {};
-    double us[2] = {-1, -1};
-    for (auto& sh : shapes) {
-      if (sh.mw != mw) continue;
-      for (int m = 0; m < 2; ++m) {
-        const int wt = 2 * sh.rbw, KS = m ? dn_KS : gu_KS, NRB = m ? dn_NRB : gu_NRB, nt = (NRB + wt - 1) / wt;
-        for (int S = 1; S <= (m ? 16 : 1); ++S) {
-          if (S > 1 && KS / S < 16) break;
-          const int kps = ((KS + S - 1) / S + 3) / 4 * 4, s_real = (KS + kps - 1) / kps;
-          const double full = (nt * s_real + 7) / 8 * cols / cu_x, rounds = full <= 1.0 ? 1.0 : full + 0.5;
-          const double t = 1e-3 * sh.ns * rounds * wt * std::min(rt, te) * kps + 4.0 + (m ? (double)s_real * used * te * NRB * 8192.0 / 4.5e6 : 0.0);
-          if (us[m] < 0 || t < us[m]) { us[m] = t; q[m].S = s_real; q[m].ks_per_split = kps; q[m].chunk = 4; q[m].rbw = sh.rbw; q[m].mw = mw; }
-        }
-      }
-    }
-    if (best_us < 0 || us[0] + us[1] < best_us) {
-      best_us = us[0] + us[1]; best.gu = q[0]; best.dn = q[1];
-      best.cols = std::min(M * topk, E + M * topk / (32 * rt));  // most columns any routing gives
-    }
-  }
-  return best;
-}
-
-// Work split of the split-K kernel with streamed activations: S slices x groups of at most 4 row blocks, chosen by a
-// fetch model in KiB per work-group (weights + the live part of the X slice + twice the partials the last work-group
-// of a row group reads back, which sit on the critical path of one CU).  Depends on the matrix shape only.
-struct PlanXK { int S, groups, nrmax; long cost; };
-static PlanXK plan_xk(int NRB, int KS, int NXP, int n_cu, size_t pt_floats_per_slice, size_t pt_floats) {
-  PlanXK best; best.S = 0; best.groups = 0; best.nrmax = 0; best.cost = -1;
-  for (int S = 1; S <= 16; ++S) {
-    const int groups = std::min(NRB, n_cu / S);
-    if (groups < 1) break;
-    const int nrm = (NRB + groups - 1) / groups, kt = (KS + S - 1) / S;
-    if (nrm > 4 || kt < 16 || (size_t)S * pt_floats_per_slice > pt_floats) continue;
-    const long cost = (long)nrm * kt + (long)NXP * kt * 4 / 5 + 2L * S * nrm * 4;
-    if (best.cost < 0 || cost < best.cost) { best.S = S; best.groups = groups; best.nrmax = nrm; best.cost = cost; }
-  }
-  return best;
-}
-
-// Work split of the LDS-staged split-K kernel: S K-slices x `groups` row groups = one work-group each; inside a
-// work-group `lanes` x `kparts` waves (product 8): a wave owns every lanes-th row block of the group over one k-part.
-struct Plan2 { int S, groups, lanes, kparts, RW, kt_max; size_t lds; };
-static Plan2 plan2(int NRB, int KS, int NXP, int NWP, int n_cu, bool q4 = false) {
-  Plan2 p;
-  const int x_cap_kb = 128;                                   // LDS given to the X slice / the wave reduction
-  int S = 1;
-  // fewest K slices whose X slice fits (fewer partials to exchange); 4-bit weights: slices are whole groups of 8 k-steps
-  auto slice_ks = [&](int S_) { return q4 ? 8 * ((KS / 8 + S_ - 1) / S_) : (KS + S_ - 1) / S_; };
-  while (NXP * slice_ks(S) > x_cap_kb) ++S;
-  int groups = std::max(1, std::min(NRB, n_cu / S));
-  // few row blocks: split K further (slices of at least 4 k-steps) until the grid fills the chip
-  while (!q4 && groups * S * 2 <= n_cu && (KS + 2 * S - 1) / (2 * S) >= 4) S *= 2;
-  // many row blocks (wide matrices with a long K): more work-groups than CUs rather than more than 3 row blocks per wave
-  const int r_cap = 24;
-  if ((NRB + groups - 1) / groups > r_cap) groups = (NRB + r_cap - 1) / r_cap;
-  const int R = (NRB + groups - 1) / groups, kt = slice_ks(S);
-  long best = -1; int bl = 8, bk = 1;
-  const int cand[4][2] = {{8, 1}, {4, 2}, {2, 4}, {1, 8}};
-  for (auto& cd : cand) {
-    int rw = (R + cd[0] - 1) / cd[0];
-    if (rw > 3) continue;
-    if ((size_t)cd[0] * (cd[1] - 1) * rw * 4 > (size_t)x_cap_kb) continue;
-    long cost = (long)rw * ((kt + cd[1] - 1) / cd[1]);
-    if (best < 0 || cost < best) { best = cost; bl = cd[0]; bk = cd[1]; }
-  }
-  p.S = S; p.groups = groups; p.lanes = bl; p.kparts = bk;
-  int rw = (R + bl - 1) / bl;
-  p.RW = rw <= 1 ? 1 : rw <= 2 ? 2 : 3;
-  p.kt_max = kt;
-  size_t xs = (size_t)NXP * kt * 1024, red = (size_t)bl * (bk - 1) * p.RW * 4096;
-  p.lds = std::max(xs, red);
-  return p;
-}
+static bool use_pf(const eagle_ctx* c, int MT) { return plan_is_large_m(MT, c->big_gemm, c->fixed_sums, c->q4); }
 
 static int build_tree(const eagle_config* cfg, TreeDev* t) {
   int M = cfg->n_nodes;

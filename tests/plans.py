@@ -1,0 +1,73 @@
+"""The library's work-split planners (csrc/plans.h, host arithmetic only) compiled into a small shared object and called from
+Python, so that tests can say which tile shape and how many K slices a matrix product gets."""
+import ctypes
+import os
+import subprocess
+from collections import namedtuple
+
+import paper_2401_15077_amd as pkg
+
+Plan = namedtuple("Plan", "S kps rbw mw")
+
+_SHIM = r"""
+#include "plans.h"
+static void put(const GemmPlan& p, int* o) { o[0] = p.S; o[1] = p.ks_per_split; o[2] = p.rbw; o[3] = p.mw; }
+extern "C" {
+int shim_large_m(int MT, int big, int fixed, int q4) { return plan_is_large_m(MT, big != 0, fixed != 0, q4 != 0); }
+void shim_pf(int NRB, int KS, int MT, int n_cu, int fused, int q4, int fixed, int* o) { put(plan_pf(NRB, KS, MT, n_cu, fused != 0, q4 != 0, fixed != 0), o); }
+void shim_moe(const int* a, int* o) {
+  const PlanMoe p = plan_moe(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7]);
+  put(p.gu, o); put(p.dn, o + 4); o[8] = p.cols;
+}
+int shim_moe_tiles(int M, int topk, int E) { return moe_tiles(M, topk, E); }
+}
+"""
+
+
+class Plans:
+    def __init__(self, folder):
+        src, lib = os.path.join(folder, "shim.cpp"), os.path.join(folder, "shim.so")
+        with open(src, "w") as f:
+            f.write(_SHIM)
+        inc = os.path.join(os.path.dirname(pkg.__file__), "csrc")
+        subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", inc, src, "-o", lib])
+        self.lib = ctypes.CDLL(lib)
+
+    def large_m(self, MT, big=True, fixed=False, q4=False):
+        return bool(self.lib.shim_large_m(MT, big, fixed, q4))
+
+    def pf(self, NRB, KS, MT, fused=False, q4=False, fixed=False, n_cu=256):
+        o = (ctypes.c_int * 4)()
+        self.lib.shim_pf(NRB, KS, MT, n_cu, fused, q4, fixed, o)
+        return Plan(*o)
+
+    def moe(self, d, F, M, topk, E, n_cu=256):
+        """-> (gate/up plan, down plan, columns) for M rows of a mixture of E experts with widths d and F"""
+        a = (ctypes.c_int * 8)(2 * F // 32, d // 16, d // 32, F // 16, M, topk, E, n_cu)
+        o = (ctypes.c_int * 9)()
+        self.lib.shim_moe(a, o)
+        return Plan(*o[:4]), Plan(*o[4:8]), o[8]
+
+    def moe_tiles(self, M, topk, E):
+        return self.lib.shim_moe_tiles(M, topk, E)
+
+    def prompt(self, s, rows, kv="fp32", bits=16):
+        """matrix -> plan of one prompt pass of `rows` rows of a model shape (None: not the large-M GEMM)"""
+        MT, fixed = (rows + 31) // 32, kv == "bf16" and s.n_experts == 0
+        if not self.large_m(MT, bits == 16, fixed, bits == 4):
+            return {}
+        d, a, q4 = s.d_model, s.n_heads * s.head_dim, bits == 4
+        kw = dict(q4=q4, fixed=fixed)
+        out = {"qkv": self.pf((a + 2 * s.n_kv_heads * s.head_dim) // 32, d // 16, MT, **kw), "o": self.pf(d // 32, a // 16, MT, **kw),
+               "fc": self.pf(d // 32, 2 * d // 16, MT, **kw)}
+        if s.n_experts:
+            out["gate_up"], out["down"], _ = self.moe(d, s.d_ffn, 32 * MT, s.experts_per_tok, s.n_experts)
+        else:
+            out["gate_up"] = self.pf(2 * s.d_ffn // 32, d // 16, MT, fused=True, **kw)
+            out["down"] = self.pf(d // 32, s.d_ffn // 16, MT, **kw)
+        return out
+
+    def loss(self, s, rows):
+        """The two products of one loss pass of `rows` label rows: LM head over labels and predictions, and its transpose."""
+        mt = (rows + 31) // 32
+        return {"lm_head": self.pf((s.vocab + 31) // 32, s.d_model // 16, 2 * mt), "lm_head_T": self.pf(s.d_model // 32, s.vocab // 16, mt)}

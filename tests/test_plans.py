@@ -1,0 +1,66 @@
+"""The work splits of the matrix products (csrc/plans.h): every split covers K in whole units, every tile shape is one that the
+library launches, grouped experts stay within the columns and tiles that the workspace holds."""
+import random
+
+import pytest
+
+from plans import Plans
+
+SHAPES_16 = {(4, 1), (3, 1), (4, 2), (3, 2), (4, 4), (3, 4), (2, 4)}     # what gemm() launches
+SHAPES_4 = {(2, 2)}
+SHAPES_MOE = {(4, 2), (3, 2), (4, 4), (3, 4), (2, 4)}
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    return Plans(str(tmp_path_factory.mktemp("plans")))
+
+
+def _sizes(rng, unit):
+    """row blocks, k-steps (a multiple of `unit`), row tiles: spread over their logarithm"""
+    return int(2 ** rng.uniform(1, 11)), unit * max(1, int(2 ** rng.uniform(0, 9))), int(2 ** rng.uniform(0, 6.01))
+
+
+def test_splits_cover_k_in_whole_units_and_use_launched_tiles(plans):
+    rng, seen = random.Random(1), {False: set(), True: set()}
+    for _ in range(20000):
+        q4, fixed = rng.random() < 0.3, rng.random() < 0.3
+        NRB, KS, MT = _sizes(rng, 8 if q4 else 4)
+        MT = MT if q4 else max(2, MT)
+        p = plans.pf(NRB, KS, MT, fused=rng.random() < 0.5, q4=q4, fixed=fixed and not q4, n_cu=rng.choice([256, 256, 256, 64, 32]))
+        assert 1 <= p.S <= 16 and p.kps % (8 if q4 else 4) == 0 and (p.S - 1) * p.kps < KS <= p.S * p.kps, (NRB, KS, MT, p)
+        assert q4 or (p.mw == 1) == (MT <= 2), (NRB, KS, MT, p)
+        seen[q4].add((p.rbw, p.mw))
+    assert seen[False] == SHAPES_16 and seen[True] == SHAPES_4      # no shape is launched that no size takes
+
+
+def test_fixed_sums_take_their_slices_whatever_tile_serves_them(plans):
+    """Dense models with a bf16 cache: the K slices do not depend on whether the epilogue is fused."""
+    rng = random.Random(2)
+    for _ in range(3000):
+        NRB, KS, MT = _sizes(rng, 4)
+        a, b = (plans.pf(NRB, KS, max(2, MT), fused=f, fixed=True) for f in (False, True))
+        assert (a.S, a.kps) == (b.S, b.kps)
+
+
+def test_expert_columns_and_tiles_hold_any_routing(plans):
+    rng, seen = random.Random(3), set()
+    for _ in range(4000):
+        E = rng.choice([2, 4, 8, 16, 64])
+        k = rng.randint(1, min(4, E))
+        M = 32 * int(2 ** rng.uniform(0, 6.01))
+        d, F = 64 * int(2 ** rng.uniform(0, 7)), 64 * int(2 ** rng.uniform(0, 8))
+        gu, dn, cols = plans.moe(d, F, M, k, E)
+        assert gu.S == 1 and gu.mw == dn.mw and cols <= 256
+        seen |= {(gu.rbw, gu.mw), (dn.rbw, dn.mw)}
+        # rows per expert: even, one expert with all rows, random subsets
+        rows = rng.randint(max(1, M - 31), M)
+        counts = [0] * E
+        bias = [rng.random() ** rng.choice([0, 1, 6]) for _ in range(E)]
+        for _ in range(rows):
+            for e in sorted(range(E), key=lambda e: rng.random() * bias[e])[-k:]:
+                counts[e] += 1
+        rt = 2 * gu.mw
+        assert sum((c + 32 * rt - 1) // (32 * rt) for c in counts) <= cols
+        assert sum((c + 31) // 32 for c in counts) <= plans.moe_tiles(M, k, E)
+    assert seen == SHAPES_MOE
