@@ -64,3 +64,13 @@ def test_expert_columns_and_tiles_hold_any_routing(plans):
         assert sum((c + 32 * rt - 1) // (32 * rt) for c in counts) <= cols
         assert sum((c + 31) // 32 for c in counts) <= plans.moe_tiles(M, k, E)
     assert seen == SHAPES_MOE
+
+
+def test_expert_columns_are_not_wider_than_an_experts_rows(plans):
+    """Columns of eight row tiles only where an expert has more than four on average: waves without a live tile multiply nothing."""
+    for E, k in ((4, 2), (8, 2), (16, 1), (64, 4)):
+        for M in range(32, 2049, 32):
+            tiles = -(-M * k // (32 * min(E, M * k)))
+            for d, F in ((256, 320), (4096, 14336), (2048, 1408)):
+                gu, dn, _ = plans.moe(d, F, M, k, E)
+                assert gu.mw == 2 or tiles > 4, (E, k, M, d, F, gu)
