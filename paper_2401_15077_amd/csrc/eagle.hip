@@ -295,8 +295,8 @@ static size_t layout(eagle_ctx* c) {
   const bool grouped = c->big_gemm && g.n_experts > 0;
   const int slots = grouped ? 32 * moe_tiles(Mm, g.experts_per_tok, g.n_experts) : 0;
   c->xf_ffn = a.take<bf16_t>((size_t)c->NXP * std::max(Mm, slots) * F);
-  // (the last column of row tiles may read up to 7 tiles beyond the end)
-  c->group_sums = a.take<float>(c->q4 ? (size_t)std::max(std::max(F, H * dh), 2 * d) / EAGLE_Q4_GROUP * Mm + 256 : 1);
+  // (k_gemm_pf_q4: the last column of row tiles may read up to 3 tiles beyond the end)
+  c->group_sums = a.take<float>(c->q4 ? (size_t)std::max(std::max(F, H * dh), 2 * d) / EAGLE_Q4_GROUP * Mm + 96 : 1);
   c->moe_plan = a.take<MoePlan>(1);
   c->moe_slot = a.take<int>(grouped ? (size_t)g.n_experts * Mm : 1);
   c->moe_row = a.take<int>(std::max(1, slots));
@@ -688,11 +688,10 @@ static hipError_t launch_pf_moe(eagle_ctx* c, const std::vector<PackedW>& w, con
   return p.rbw == 4 ? launch_pf_moe<4, 2, SWIGLU>(c, w, XF, MT, p, cols, act) : launch_pf_moe<3, 2, SWIGLU>(c, w, XF, MT, p, cols, act);
 }
 
-template <int MW>
 static hipError_t launch_pf_q4(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, const GemmPlan& p, bf16_t* swiglu_out, int M) {
-  const int MQ = (MT + 2 * MW - 1) / (2 * MW), G = ((w.NRB + 3) / 4) * p.S;
-  return launch_k(c, c->cur_class, w.bytes(c->elt), "k_gemm_pf<4-bit weights>", swiglu_out ? k_gemm_pf_q4<MW, true> : k_gemm_pf_q4<MW, false>,
-                  dim3((G + 7) / 8 * 8 * MQ), dim3(128 * MW), (size_t)0, (const u32x4*)w.w, (const bf16_t*)w.sc, XF, (const float*)c->group_sums, c->PT, w.NRB, w.KS,
+  const int MQ = (MT + 3) / 4, G = ((w.NRB + 3) / 4) * p.S;
+  return launch_k(c, c->cur_class, w.bytes(c->elt), "k_gemm_pf<4-bit weights>", swiglu_out ? k_gemm_pf_q4<true> : k_gemm_pf_q4<false>,
+                  dim3((G + 7) / 8 * 8 * MQ), dim3(256), (size_t)0, (const u32x4*)w.w, (const bf16_t*)w.sc, XF, (const float*)c->group_sums, c->PT, w.NRB, w.KS,
                   p.ks_per_split / 8, p.S, w.Npad, MT, swiglu_out, M);
 }
 
@@ -711,7 +710,7 @@ static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S
     bf16_t* out = fuse ? swiglu_out : nullptr;
     k_group_sums<<<dim3(MT, (w.NG + 3) / 4), 256, 0, c->stream>>>(XF, c->group_sums, MT, w.KS, c->NXP);
     LAUNCH_CHECK();
-    e = p.mw == 4 ? launch_pf_q4<4>(c, w, XF, MT, p, out, M) : launch_pf_q4<2>(c, w, XF, MT, p, out, M);
+    e = launch_pf_q4(c, w, XF, MT, p, out, M);
   } else if (big) {
     bf16_t* out = fuse ? swiglu_out : nullptr;
     if (p.mw == 4) e = p.rbw == 4 ? launch_pf<4, 4>(c, w, XF, MT, p, out, M) : p.rbw == 3 ? launch_pf<3, 4>(c, w, XF, MT, p, out, M) : launch_pf<2, 4>(c, w, XF, MT, p, out, M);
@@ -770,7 +769,7 @@ static KVCache kv_for(eagle_ctx* c, int li) {
 static int resnorm(eagle_ctx* c, int M, int MT, const float* h_in, const float* PT, int S, int Npad, const float* bias,
                    const float* gain, bf16_t* XF, float* xout, const float* row_w = nullptr) {
   if (c->fixed_sums) {
-    k_resnorm_fixed<<<M, 256, 0, c->stream>>>(h_in, PT, S, Npad, MT * 32, bias, c->h, gain, c->cfg.rms_eps, XF, MT, c->NXP, xout, c->cfg.d_model, row_w);
+    k_resnorm_fixed<<<M, 256, 0, c->stream>>>(h_in, PT, S, Npad, MT * 32, bias, c->h, gain, c->cfg.rms_eps, XF, MT, c->NXP, xout, c->cfg.d_model);
     LAUNCH_CHECK();
     return EAGLE_OK;
   }
@@ -785,7 +784,7 @@ static int resnorm(eagle_ctx* c, int M, int MT, const float* h_in, const float* 
 static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, int t_max, int n_new, const float* next_gain, float* xout) {
   const eagle_config& g = c->cfg;
   LayerW& w = c->layers[li];
-  const int H = g.n_heads, KVH = g.n_kv_heads, dh = g.head_dim, F = g.d_ffn;
+  const int H = g.n_heads, dh = g.head_dim, F = g.d_ffn;
   int S = 1, rc;
   KVCache kv = kv_for(c, li);
   if ((rc = (c->cur_class = KC_QKV, gemm(c, w.qkv, c->xf_d, MT, &S)))) return rc;
@@ -879,7 +878,7 @@ static int lm_head(eagle_ctx* c, const Pass& pass, int M, int MT, float* out, in
   return EAGLE_OK;
 }
 
-static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out, const bf16_t* XF = nullptr);
+static int lm_head2(eagle_ctx* c, int M, bool scaled, float* out, const bf16_t* XF = nullptr);
 
 // Target model over the rows of `pass`: embedding -> layers -> final norm (= features) -> LM head.
 static int target_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, bool want_logits, float* logits_out, int out_kind, int only_last_row) {
@@ -906,7 +905,7 @@ static int target_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, 
     if (c->q4) {
       k_row_facts<<<1, 64, 0, c->stream>>>(sub, c->tree_d, c->st, nr, kv_for(c, 0), c->facts);
       LAUNCH_CHECK();
-      return lm_head2(c, sub, nr, false, logits_out, c->xf_2d);
+      return lm_head2(c, nr, false, logits_out, c->xf_2d);
     }
     return lm_head(c, sub, nr, 1, logits_out, out_kind, only_last_row, c->xf_2d);
   }
@@ -1125,10 +1124,9 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   return EAGLE_OK;
 }
 
-static Gemm2 gemm2_base(eagle_ctx* c, const Pass& pass, int M) {
+static Gemm2 gemm2_base(eagle_ctx* c, int M) {
   Gemm2 g;
   memset(&g, 0, sizeof(g));
-  (void)pass;
   g.M = M; g.facts = c->facts; g.d = c->cfg.d_model; g.in_scale.ssq = c->ssq1;   // (no row scale: groups stays 0)
   g.rope_cos = c->rope_cos; g.rope_sin = c->rope_sin; g.H = c->cfg.n_heads; g.kv_f32 = c->kv_f32; g.Q = c->Q;
   return g;
@@ -1145,7 +1143,7 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
   LayerW& w = c->layers[li];
   const int H = cf.n_heads, dh = cf.head_dim, d = cf.d_model, F = cf.d_ffn;
   int rc;
-  Gemm2 g = gemm2_base(c, pass, M);
+  Gemm2 g = gemm2_base(c, M);
   g.epi = EPI_QKV; g.in_scale = scale_of(c, c->ssq2, c->ssq2_groups); g.kv = kv_for(c, li);
   if ((rc = (c->cur_class = KC_QKV, gemm2(c, w.qkv, c->xf2_d, g, nullptr)))) return rc;
   {
@@ -1170,7 +1168,7 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
 #undef ATTN2
     LAUNCH_CHECK();
   }
-  g = gemm2_base(c, pass, M);
+  g = gemm2_base(c, M);
   g.epi = EPI_RESID; g.h_in = c->h2; g.h_out = c->h2; g.gain_next = w.mlp_norm; g.xf_out = c->xf2_d; g.xf_KS = d / 16; g.ssq_out = c->ssq1;
   if ((rc = (c->cur_class = KC_O, gemm2(c, w.o, c->xf2_att, g, &c->ssq1_groups)))) return rc;
   if (w.moe) {
@@ -1183,11 +1181,11 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
     LAUNCH_CHECK();
     if (c->prof_mode) { k_count_used<<<1, 64, 0, c->stream>>>(c->expert_used, E, c->experts_touched); LAUNCH_CHECK(); }
     for (int e = 0; e < E; ++e) {
-      g = gemm2_base(c, pass, M);
+      g = gemm2_base(c, M);
       g.epi = EPI_SWIGLU; g.in_scale = scale_of(c, c->ssq1, c->ssq1_groups); g.xf_out = c->xf2_ffn; g.xf_KS = F / 16;
       g.skip_flag = c->expert_used + e;
       if ((rc = (c->cur_class = KC_GATEUP, gemm2(c, w.e_gu[e], c->xf2_d, g, nullptr)))) return rc;
-      g = gemm2_base(c, pass, M);
+      g = gemm2_base(c, M);
       g.epi = EPI_RESID; g.h_in = c->h2; g.h_out = c->h2; g.gain_next = next_gain; g.xf_out = c->xf2_dB; g.xf_KS = d / 16; g.ssq_out = c->ssq2;
       g.row_w = c->moe_w + (size_t)e * c->Mmax; g.skip_flag = c->expert_used + e;
       if ((rc = (c->cur_class = KC_DOWN, gemm2(c, w.e_dn[e], c->xf2_ffn, g, &c->ssq2_groups)))) return rc;
@@ -1195,16 +1193,16 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
     std::swap(c->xf2_d, c->xf2_dB);     // the experts all read the old xf2_d; the new one was built beside it
     return EAGLE_OK;
   }
-  g = gemm2_base(c, pass, M);
+  g = gemm2_base(c, M);
   g.epi = EPI_SWIGLU; g.in_scale = scale_of(c, c->ssq1, c->ssq1_groups); g.xf_out = c->xf2_ffn; g.xf_KS = F / 16;
   if ((rc = (c->cur_class = KC_GATEUP, gemm2(c, w.gu, c->xf2_d, g, nullptr)))) return rc;
-  g = gemm2_base(c, pass, M);
+  g = gemm2_base(c, M);
   g.epi = EPI_RESID; g.h_in = c->h2; g.h_out = c->h2; g.gain_next = next_gain; g.xf_out = c->xf2_d; g.xf_KS = d / 16; g.ssq_out = c->ssq2;
   return (c->cur_class = KC_DOWN, gemm2(c, w.dn, c->xf2_ffn, g, &c->ssq2_groups));
 }
 
-static int lm_head2(eagle_ctx* c, const Pass& pass, int M, bool scaled, float* out, const bf16_t* XF) {
-  Gemm2 g = gemm2_base(c, pass, M);
+static int lm_head2(eagle_ctx* c, int M, bool scaled, float* out, const bf16_t* XF) {
+  Gemm2 g = gemm2_base(c, M);
   g.epi = EPI_LOGITS; g.logits = out; g.V = c->cfg.vocab;
   if (scaled) g.in_scale = scale_of(c, c->ssq2, c->ssq2_groups);
   return (c->cur_class = KC_LMHEAD, gemm2(c, c->lm_head, XF ? XF : c->xf2_d, g, nullptr));
@@ -1226,7 +1224,7 @@ static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_ne
   k_store_rows<<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->featbuf, c->F, c->pend_f, c->chunk_f, d);
   LAUNCH_CHECK();
   if (!want_logits) return EAGLE_OK;
-  return lm_head2(c, pass, M, true, logits_out);
+  return lm_head2(c, M, true, logits_out);
 }
 
 static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new, bool store_rows = true, bool want_logits = true) {
@@ -1236,7 +1234,7 @@ static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new,
   if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts);
   else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts);
   LAUNCH_CHECK();
-  Gemm2 g = gemm2_base(c, pass, M);
+  Gemm2 g = gemm2_base(c, M);
   g.epi = EPI_RESID; g.h_in = nullptr; g.h_out = c->h2; g.bias = c->loaded_layer[EAGLE_W_FC_BIAS][0] ? c->fc_bias : nullptr;
   g.gain_next = c->layers[cf.n_layers].attn_norm; g.xf_out = c->xf2_d; g.xf_KS = d / 16; g.ssq_out = c->ssq2;
   if ((rc = (c->cur_class = KC_FC, gemm2(c, c->fc, c->xf2_2d, g, &c->ssq2_groups)))) return rc;
@@ -1246,7 +1244,7 @@ static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new,
     k_store_rows<<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->h2, c->node_f, c->pend_f, c->chunk_f, d);
     LAUNCH_CHECK();
   }
-  return lm_head2(c, pass, M, false, c->draft_logits);
+  return lm_head2(c, M, false, c->draft_logits);
 }
 
 // ---------------------------------------------------------------------------- sequence life cycle

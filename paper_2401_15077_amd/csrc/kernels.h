@@ -597,11 +597,11 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
 // Bound: the matrix pipes; 8 MFMAs a k-step and wave, 16 more registers of sums than k_gemm_pf's 8-MFMA shape allow no more.
 // (The prompt used to walk through the decoding kernels 32 rows at a time, every pass streaming all codes: 3.2 ms per 32 rows
 // at 7B widths.)
-template <int MW, bool SWIGLU>
-__global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf_q4(const u32x4* __restrict__ Wq, const bf16_t* __restrict__ SC, const bf16_t* __restrict__ XF,
+template <bool SWIGLU>
+__global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__ Wq, const bf16_t* __restrict__ SC, const bf16_t* __restrict__ XF,
                                                             const float* __restrict__ SX, float* __restrict__ PT, int NRB, int KS, int groups_per_split,
                                                             int S, int Npad, int MT, bf16_t* act, int M) {
-  constexpr int RBW = 2, NXP = 2, WT = 2 * RBW, RT = 2 * MW, NW = 2 * MW, XT = NXP * RT, LPW = XT / NW;
+  constexpr int RBW = 2, NXP = 2, WT = 2 * RBW, RT = 4, NW = 4, XT = NXP * RT, LPW = XT / NW;
   __shared__ u32x4 s0[XT * 64];
   __shared__ u32x4 s1[XT * 64];
   __shared__ u32x4 s2[XT * 64];
@@ -635,8 +635,8 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf_q4(const u32x4* __restr
 #pragma unroll
     for (int u = 0; u < LPW; ++u) PF_LDS(src[u] + ko + lane * 8, slot + dst[u]);
   };
-  const u32x4* csrc = Wq + (size_t)min(nt * WT + w % WT, NRB - 1) * KT * 64 + lane;   // one code tile per wave (MW = 4: two waves load the same)
-  auto dma_codes = [&](u32x4* slot, int T) { PF_LDS(csrc + (size_t)min(T, Tlast) * 64, slot + (w % WT) * 64); };
+  const u32x4* csrc = Wq + (size_t)min(nt * WT + w, NRB - 1) * KT * 64 + lane;   // one code tile per wave
+  auto dma_codes = [&](u32x4* slot, int T) { PF_LDS(csrc + (size_t)min(T, Tlast) * 64, slot + w * 64); };
   // lane l brings 16 bytes of the scales of row block l / 4 (lanes beyond the tile repeat the last ones) and of the sums of x
   const bf16_t* ssrc = SC + (size_t)min(nt * WT + min(lane >> 2, WT - 1), NRB - 1) * NG * 32 + (lane & 3) * 8;
   const float* xsrc = SX + tile0 * 32 + (lane & (RT * 8 - 1)) * 4;
@@ -965,7 +965,7 @@ __global__ __launch_bounds__(RESNORM_THREADS) void k_resnorm(const float* h_in, 
 // in one row of some hundred, and the cache then rounds some K and V the other way): element by element, 16.1 us at 104 rows.
 __global__ __launch_bounds__(256) void k_resnorm_fixed(const float* h_in, const float* __restrict__ PT, int S, int Npad, int Mpad,
                                                  const float* bias, float* h_out, const float* gain, float eps,
-                                                 bf16_t* XF, int MT, int nplanes, float* xout, int d, const float* row_w) {
+                                                 bf16_t* XF, int MT, int nplanes, float* xout, int d) {
   __shared__ float sh[16];
   int r = blockIdx.x;
   float ss = 0.f;
@@ -973,7 +973,6 @@ __global__ __launch_bounds__(256) void k_resnorm_fixed(const float* h_in, const 
   // for the second phase, further ones are read back from h_out
   constexpr int KEEP = 4;
   float keep[KEEP][8];
-  const float rw = row_w ? row_w[r] : 1.0f;    // MoE: this expert's routing weight for the row (0 = not routed here)
   auto phase1 = [&](int k8, float* v) {
     float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (PT) {
@@ -996,7 +995,7 @@ __global__ __launch_bounds__(256) void k_resnorm_fixed(const float* h_in, const 
     for (int t = 0; t < 8; ++t) {
       int k = k8 + t;
       float x = h_in ? h_in[(size_t)r * d + k] : 0.f;
-      if (PT) x += row_w ? rw * a[t] : a[t];
+      if (PT) x += a[t];
       if (bias) x += bias[k];
       h_out[(size_t)r * d + k] = x;
       ss += x * x;
@@ -1855,7 +1854,6 @@ __global__ __launch_bounds__(256) void k_moe_gather(const MoePlan* __restrict__ 
       if (ks0 + u < KS) *(u32x4*)(out + (((size_t)q * MT_out + t) * KS + ks0 + u) * 512 + lane * 8) = v[u];
   }
 }
-
 
 // ============================================================================ debug / test access
 template <typename CT>

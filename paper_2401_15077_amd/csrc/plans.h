@@ -29,7 +29,7 @@ static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool 
 // round is full when the XCD with one group more than the others is (LM-head transpose, 10 row tiles, 3 slices of 27 x 3
 // tiles: 243 work-groups, but 33 on the 32 CUs of one XCD: 355 us against 197 for 240 of the next shape).  And what the partial
 // sums cost that all but the fused epilogue write and read back, at 4.5 TB/s.
-// 4-bit weights (k_gemm_pf_q4): two row blocks per wave, K slices of whole groups of 8 k-steps.
+// 4-bit weights (k_gemm_pf_q4): one shape, two row blocks per wave and two wave columns; K slices of whole groups of 8 k-steps.
 static inline int plan_slices(int NRB, int KS, int MT, int n_cu) {     // K slices as a function of the shape alone (fixed_sums)
   const int wgs = ((NRB + 7) / 8) * ((MT + 3) / 4);
   int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? 16 : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
@@ -38,9 +38,9 @@ static inline int plan_slices(int NRB, int KS, int MT, int n_cu) {     // K slic
 static inline GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4, bool fixed_sums) {
   GemmPlan best{};
   double best_us = -1;
-  static const struct { int rbw, mw; double ns; } shapes[9] = {{4, 1, 20.0}, {3, 1, 22.0}, {4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}, {2, 4, 17.0}};
+  static const struct { int rbw, mw; double ns; } shapes[8] = {{4, 1, 20.0}, {3, 1, 22.0}, {4, 2, 13.3}, {3, 2, 15.0}, {4, 4, 12.0}, {3, 4, 13.3}, {2, 4, 15.0}, {2, 2, 17.0}};
   const int xcds = 8, cu_x = std::max(1, n_cu / xcds);
-  for (int i = q4 ? 7 : 0; i < (q4 ? 9 : 7); ++i) {
+  for (int i = q4 ? 7 : 0; i < (q4 ? 8 : 7); ++i) {
     const auto& sh = shapes[i];
     const int wt = 2 * sh.rbw, rt = 2 * sh.mw, mq = (MT + rt - 1) / rt, nt = (NRB + wt - 1) / wt;
     if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
