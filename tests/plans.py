@@ -52,19 +52,18 @@ class Plans:
         return self.lib.shim_moe_tiles(M, topk, E)
 
     def prompt(self, s, rows, kv="fp32", bits=16):
-        """matrix -> plan of one prompt pass of `rows` rows of a model shape (None: not the large-M GEMM)"""
+        """matrix -> plan of one prompt pass of `rows` rows of a bf16 model (matrices that do not take the large-M GEMM are left out)"""
         MT, fixed = (rows + 31) // 32, kv == "bf16" and s.n_experts == 0
-        if not self.large_m(MT, bits == 16, fixed, bits == 4):
-            return {}
-        d, a, q4 = s.d_model, s.n_heads * s.head_dim, bits == 4
+        d, a, q4, out = s.d_model, s.n_heads * s.head_dim, bits == 4, {}
         kw = dict(q4=q4, fixed=fixed)
-        out = {"qkv": self.pf((a + 2 * s.n_kv_heads * s.head_dim) // 32, d // 16, MT, **kw), "o": self.pf(d // 32, a // 16, MT, **kw),
-               "fc": self.pf(d // 32, 2 * d // 16, MT, **kw)}
-        if s.n_experts:
+        if self.large_m(MT, bits == 16, fixed, q4):
+            out["qkv"] = self.pf((a + 2 * s.n_kv_heads * s.head_dim) // 32, d // 16, MT, **kw)
+            out["o"], out["fc"] = self.pf(d // 32, a // 16, MT, **kw), self.pf(d // 32, 2 * d // 16, MT, **kw)
+            if not s.n_experts:
+                out["gate_up"] = self.pf(2 * s.d_ffn // 32, d // 16, MT, fused=True, **kw)
+                out["down"] = self.pf(d // 32, s.d_ffn // 16, MT, **kw)
+        if s.n_experts:                         # experts are grouped whatever the rows
             out["gate_up"], out["down"], _ = self.moe(d, s.d_ffn, 32 * MT, s.experts_per_tok, s.n_experts)
-        else:
-            out["gate_up"] = self.pf(2 * s.d_ffn // 32, d // 16, MT, fused=True, **kw)
-            out["down"] = self.pf(d // 32, s.d_ffn // 16, MT, **kw)
         return out
 
     def loss(self, s, rows):

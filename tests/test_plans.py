@@ -4,7 +4,9 @@ import random
 
 import pytest
 
+import synth
 from plans import Plans
+from test_gpu_large_m import DENSE, EXPERTS, LOSS_ROWS
 
 SHAPES_16 = {(4, 1), (3, 1), (4, 2), (3, 2), (4, 4), (3, 4), (2, 4)}     # what gemm() launches
 SHAPES_4 = {(2, 2)}
@@ -74,3 +76,24 @@ def test_expert_columns_are_not_wider_than_an_experts_rows(plans):
             for d, F in ((256, 320), (4096, 14336), (2048, 1408)):
                 gu, dn, _ = plans.moe(d, F, M, k, E)
                 assert gu.mw == 2 or tiles > 4, (E, k, M, d, F, gu)
+
+
+def test_oracle_cases_reach_every_tile(plans):
+    """What the oracle tests of test_gpu_large_m.py run: every tile shape of the 16-bit kernels, with and without split K, the tiles of
+    8 row tiles (mw 4) with all waves at work, a last column that is partly filled, and SwiGLU in the epilogue."""
+    dense = [(m, p, rows) for s, lens in DENSE.values() for rows in lens for m, p in plans.prompt(s, rows).items()]
+    tiles = {(p.rbw, p.mw) for _, p, _ in dense}
+    assert tiles == SHAPES_16
+    wide = [(m, p, rows) for m, p, rows in dense if (p.rbw, p.mw) == (4, 4)]
+    assert any(p.S > 1 for _, p, _ in wide) and any(m == "gate_up" and p.S == 1 for m, p, _ in wide)
+    assert any((rows + 31) // 32 > 8 and ((rows + 31) // 32) % 8 not in (0, 7) for _, _, rows in wide)
+    # at LLaMA2-7B widths a prompt of some thousand rows takes the widest tile for every matrix
+    s, lens = DENSE["7b-widths"]
+    assert {(p.rbw, p.mw) for p in plans.prompt(s, lens[-1]).values()} == {(4, 4)}
+    experts = [p for s, lens, _ in EXPERTS.values() for rows in lens for m, p in plans.prompt(s, rows).items() if m in ("gate_up", "down")]
+    assert {(p.rbw, p.mw) for p in experts} >= {(4, 2), (4, 4), (3, 4), (2, 4)} and any(p.S > 1 and p.mw == 4 for p in experts)
+    loss = [plans.loss(synth.SHAPES["llama2-7b"], rows) for rows in LOSS_ROWS]
+    assert any(l["lm_head"].mw == 4 and l["lm_head"].S == 1 for l in loss) and any(l["lm_head_T"].mw == 4 and l["lm_head_T"].S > 1 for l in loss)
+    # the small models of that file: tiles of two and four row tiles only
+    small = [plans.prompt(synth.SHAPES["mini-gqa"], rows) for rows in range(33, 2049, 32)]
+    assert {(p.rbw, p.mw) for l in small for p in l.values()} == {(3, 1), (3, 2)}
