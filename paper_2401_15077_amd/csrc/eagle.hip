@@ -101,7 +101,7 @@ struct eagle_ctx {
   // every sum, whatever tile shape serves it: K slices by plan_slices, prompt passes of 512 rows (32 with 4-bit weights, whose
   // codes then expand around 128 in every pass).
   bool fixed_sums = false;
-  int q4_rot = 3;                    // 4-bit codes: rotation of the packed words (3: they expand to 16 + code, 0: to 128 + code)
+  int q4_rot = Q4_ROT_LARGE_M;       // 4-bit codes: rotation of the packed words (3: they expand to 16 + code, 0: to 128 + code)
   // weights
   void* embed; PackedW lm_head, fc; float *final_norm, *fc_bias;
   std::vector<LayerW> layers;        // [n_layers] target + [1] head
@@ -416,7 +416,7 @@ static int prepare(const eagle_config* cfg, eagle_ctx* c) {
     if (cfg->max_batch * c->M > 32 || cfg->max_batch * (c->D + 1) > 32) return fail(EAGLE_EINVAL, "weight_bits = 4: max_batch * n_nodes and max_batch * (depth + 1) must not exceed 32 rows");
     c->pf_window = 32;
     c->pf_chunk = c->fixed_sums ? 32 : std::min(EAGLE_PREFILL_MAX, (cfg->max_seq + 31) / 32 * 32);
-    c->q4_rot = c->fixed_sums ? 0 : 3;
+    c->q4_rot = c->fixed_sums ? 0 : Q4_ROT_LARGE_M;
   }
   int rows = std::max(c->pf_chunk, cfg->max_batch * c->M);
   c->Mmax = (rows + 31) / 32 * 32;
@@ -707,6 +707,7 @@ static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S
   *S = fuse ? 0 : p.S;
   hipError_t e;
   if (w.q4) {
+    if (c->q4_rot != Q4_ROT_LARGE_M) return fail(EAGLE_EINVAL, "internal: the large-M GEMM does not read 4-bit codes in this packing");
     bf16_t* out = fuse ? swiglu_out : nullptr;
     k_group_sums<<<dim3(MT, (w.NG + 3) / 4), 256, 0, c->stream>>>(XF, c->group_sums, MT, w.KS, c->NXP);
     LAUNCH_CHECK();

@@ -240,7 +240,8 @@ __global__ __launch_bounds__(256) void k_pack_weight(const SrcT* __restrict__ sr
 // 8*(r/4) + 4*hh + r%4 of the block, so a lane reads the scales of its 16 accumulator rows as 32 contiguous bytes.
 #define EAGLE_Q4_GROUP 128
 struct Q4Format { uint32_t keep, bias; float offset; };        // bits of the codes, what they are or-ed into, what that adds to a code's value
-__host__ __device__ __forceinline__ Q4Format q4_format(int rot) { return rot ? Q4Format{0x00780078u, 0x41804180u, 24.0f} : Q4Format{0x000F000Fu, 0x43004300u, 136.0f}; }
+constexpr int Q4_ROT_LARGE_M = 3;                               // the packing that k_gemm_pf_q4 and k_group_sums are built for
+__host__ __device__ constexpr Q4Format q4_format(int rot) { return rot ? Q4Format{0x00780078u, 0x41804180u, 24.0f} : Q4Format{0x000F000Fu, 0x43004300u, 136.0f}; }
 __device__ __forceinline__ u32x4 q4_expand(uint32_t wd, const Q4Format& f) {
   u32x4 v;
   v.x = (wd & f.keep) | f.bias;
@@ -665,7 +666,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__
 #pragma unroll
     for (int j = 0; j < RBW; ++j) {
       const uint32_t wd = cd[(i >> 2) & 1][j][i & 3];
-      av[j] = q4_expand(wd, q4_format(3));
+      av[j] = q4_expand(wd, q4_format(Q4_ROT_LARGE_M));
     }
 #pragma unroll
     for (int q = 0; q < NXP; ++q)
@@ -760,7 +761,7 @@ __global__ __launch_bounds__(256) void k_group_sums(const bf16_t* __restrict__ X
       for (int j = 0; j < 4; ++j)
         if (q < nplanes) a += __builtin_bit_cast(float, v[u][q][j] << 16) + __builtin_bit_cast(float, v[u][q][j] & 0xFFFF0000u);
   a += __shfl_xor(a, 32, 64);
-  if (lane < 32) SX[(size_t)g * MT * 32 + t * 32 + lane] = -24.0f * a;
+  if (lane < 32) SX[(size_t)g * MT * 32 + t * 32 + lane] = -q4_format(Q4_ROT_LARGE_M).offset * a;
 }
 
 // ============================================================================ row producers
