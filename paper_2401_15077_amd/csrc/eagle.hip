@@ -81,11 +81,11 @@ struct eagle_ctx {
   eagle_config cfg;
   hipStream_t stream;
   char* ws; size_t ws_bytes, zero_end;
-  bool f32, kv_f32, q4 = false;      // q4: weight matrices stored in 4 bits (fast path only)
+  bool f32, kv_f32, q4 = false;      // q4: weight matrices stored in 4 bits
   bool q4_staged = true;
-  // 4-bit weights: epilogue classes (1 << epi) that take the streamed split-K kernel.  Measured at d = 4096 (us, streamed
-  // split-K against the alternative): O 13.8 / 15.3 and down 20.8 / 26.7 and FC 16.3 / 20.0 (LDS-staged split-K, whose
-  // 128 KB slice limit forces 11 slices at K = 11008); QKV 26.3 / 21.7 (whole-K): the residual epilogue only.
+  // 4-bit weights: epilogue classes (1 << epi) that take the streamed split-K kernel.  Measured at d = 4096, 26 rows (us, streamed
+  // split-K / LDS-staged split-K, whose 128 KB slice limit forces 11 slices at K = 11008 / whole-K): O 10.5 / 12.0 / 14.6, down
+  // 16.4 / 24.5 / 29.0, FC (4 rows) 12.9 / 17.3 / 18.5; QKV 20.6 streamed, 18.5 whole-K: the residual epilogue only.
   int q4_xk_mask = 1 << EPI_RESID;
   int NWP, NXP, elt, kv_elt;         // weight planes, activation planes, bytes per weight / per KV element
   TreeDev tree_h; TreeDev* tree_d;
@@ -96,10 +96,13 @@ struct eagle_ctx {
   // sums) to fill the chip with its narrow matrices, and rounds its tiles up once per matrix
   int pf_chunk = EAGLE_PREFILL_CHUNK, pf_window = EAGLE_PREFILL_CHUNK;
   bool big_gemm = false;
-  // A bf16 cache rounds K and V, which turns a difference of 1e-7 between two orders of an fp32 sum into one of 2^-9 in some of
-  // the entries (1e-4 relative on the logits of a 32-layer model).  Dense models with such a cache therefore keep ONE order of
-  // every sum, whatever tile shape serves it: K slices by plan_slices, prompt passes of 512 rows (32 with 4-bit weights, whose
-  // codes then expand around 128 in every pass).
+  // Dense models with a bf16 cache keep the order of sums that a pass of so many rows has always had.  The cache rounds K and V,
+  // which turns a difference of 1e-7 between two orders of an fp32 sum into one of 2^-9 in about one entry of a thousand (1e-4
+  // relative on the logits of a 32-layer model): neither order is the more accurate one, but results would move visibly from
+  // release to release.  Kept: K slices by plan_slices, prompt passes of 512 rows (32 with 4-bit weights, whose codes then expand
+  // around 128 in every pass), the norm's sums of k_resnorm_fixed, k_gemm up to 64 rows.  (How many rows a pass has decides the
+  // order here as everywhere on the general path.)  Mixtures of experts are not held to it: grouping the rows by expert has
+  // reordered their sums already, and a router near-tie moves their logits as much as the rounding of the cache does.
   bool fixed_sums = false;
   int q4_rot = Q4_ROT_LARGE_M;       // 4-bit codes: rotation of the packed words (3: they expand to 16 + code, 0: to 128 + code)
   // weights
@@ -1040,9 +1043,9 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   if (w.q4 && c->q4_staged && (g.epi == EPI_RESID || (w.NRB + 2) / 3 > c->n_cu)) {   // (or too many row blocks for one round of whole-K work-groups: the LM head)
     // 4-bit weights, the LM head (and narrow matrices the streamed split-K plan cannot take): split-K with the activation
     // slice staged in LDS.  With a quarter of the weight bytes the activation fragments are most of what a CU fetches;
-    // staged, a work-group fetches its K slice of them once.  (Measured at d = 4096: O 13.9 us against 15.0 whole-K, down
-    // 25.5 against 29.8, FC 18.9 against 21.8; the wide matrices are faster whole-K: QKV 20.2 against 27.3 -- their
-    // epilogues would run on 64 CUs only.)
+    // staged, a work-group fetches its K slice of them once.  (Measured at d = 4096: O 12.0 us against 14.6 whole-K, down
+    // 24.5 against 29.0, LM head 37.7 against 39.7; the wide matrices are faster whole-K: QKV 20.2 against 27.3, measured
+    // before, since their epilogues would run on 64 CUs only.)
     g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;
     switch (p.RW) {

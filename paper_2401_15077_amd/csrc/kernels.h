@@ -411,9 +411,11 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ Wp, siz
 // tell the slot being filled from the slot being read and adds no wait of its own).
 // (Rings of 6 and 8 k-steps measured the same or slower, a K order rotated per work-group the same.)
 // Which tile: the host (plan_pf) takes the shape whose work-groups fill the CUs of every XCD in the fewest, fullest rounds.
-// Bound: the matrix pipes at the clock the card holds under them (1.05 to 1.2 PFLOP/s with weights from HBM; the library's own
-// 8192-cubed bf16 product reaches 1.2).  Inside a 512-row prompt pass at 7B widths, us before (8 x 4 tile, activations through
-// registers) / now: QKV 125 / 97, O and down 67 / 62 on average, gate/up 217 / 172; LLaMA2-70B gate/up 861 / 785.
+// Bound: the matrix pipes at the clock the card holds under them; the library's own 8192-cubed bf16 product reaches 1.2 PFLOP/s on
+// this card.  Issued work of both planes: 512 rows at 7B widths 1.0 PFLOP/s (QKV 101, O and down 64 on average, gate/up 182 us; the
+// kernel before, tiles of 8 x 4 with the activations through registers, 125, 67 and 217), 1024 rows at 13B widths 1.18 (gate/up 493
+// us), 2011 rows at 70B widths 1.28 (gate/up 2957 us).  With N(0, 0.02) weights the clock is higher: 91, 58 and 159 us at 7B.  Pipes
+// busy: 61 to 67 % at 512 rows, 71 to 73 % from 1024 on.
 // Work-groups that share a weight tile (the activation-row tiles of one weight-row tile) get ids 8 apart, i.e. the same
 // XCD under round-robin dispatch, next to each other in dispatch order: the tile comes from HBM once and from that
 // XCD's L2 afterwards.
@@ -964,8 +966,9 @@ __global__ __launch_bounds__(RESNORM_THREADS) void k_resnorm(const float* h_in, 
   }
 }
 
-// The same for dense models with a bf16 cache, whose sums keep one order (a row's sum of squares rounds differently here than above
-// in one row of some hundred, and the cache then rounds some K and V the other way): element by element, 16.1 us at 104 rows.
+// The same for dense models with a bf16 cache, which keep the sums of 256 threads a row (with 512 a row's sum of squares rounds
+// differently in one row of some hundred, and the cache then rounds some K and V the other way): element by element, 16.1 us at 104
+// rows.
 __global__ __launch_bounds__(256) void k_resnorm_fixed(const float* h_in, const float* __restrict__ PT, int S, int Npad, int Mpad,
                                                  const float* bias, float* h_out, const float* gain, float eps,
                                                  bf16_t* XF, int MT, int nplanes, float* xout, int d) {

@@ -20,7 +20,7 @@ static inline GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
 // Which passes of the general path take the large-M GEMM: every pass of more than 128 rows (only prompts, and only where the
 // kernel exists), and shorter ones of the models it covers: prompts and batched tree passes of 33..128 rows (33..64 rows, us a
 // matrix against k_gemm: 7B QKV 27 / 34, O 12.3 / 17.3, gate/up 40 / 59, down 24 / 33; LM head 58 / 71), 65..128 where the sums
-// keep their order; with 4-bit weights all.
+// keep their order (fixed_sums); with 4-bit weights all.
 static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool q4) { return MT > 4 || (MT >= (fixed_sums ? 3 : 2) && big_gemm) || q4; }
 
 // Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
@@ -30,7 +30,7 @@ static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool 
 // tiles: 243 work-groups, but 33 on the 32 CUs of one XCD: 355 us against 197 for 240 of the next shape).  And what the partial
 // sums cost that all but the fused epilogue write and read back, at 4.5 TB/s.
 // 4-bit weights (k_gemm_pf_q4): one shape, two row blocks per wave and two wave columns; K slices of whole groups of 8 k-steps.
-static inline int plan_slices(int NRB, int KS, int MT, int n_cu) {     // K slices as a function of the shape alone (fixed_sums)
+static inline int plan_slices(int NRB, int KS, int MT, int n_cu) {     // fixed_sums: K slices of a matrix and a number of row tiles, whatever tile serves them
   const int wgs = ((NRB + 7) / 8) * ((MT + 3) / 4);
   int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? 16 : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
   return std::max(1, std::min(S, KS / (MT <= 4 ? 16 : 32)));

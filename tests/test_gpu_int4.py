@@ -45,8 +45,8 @@ def run_int4(shape_name, n_layers, tree, seed, prompt_len, steps, dtype):
 
 
 def test_int4_small_gqa_model_lockstep():
-    """d 256, 8 query heads on 2 KV heads, FFN 384, vocab 512: two groups of 128 along every K, a 70-token prompt (three
-    32-row prompt passes through the fused kernels), fp64 oracle."""
+    """d 256, 8 query heads on 2 KV heads, FFN 384, vocab 512: two or three groups of 128 along every K, a 70-token prompt
+    (one pass of the large-M GEMM over 4-bit weights), fp64 oracle."""
     run_int4("mini-gqa", 2, "T10", 51, 70, 8, np.float64)
 
 

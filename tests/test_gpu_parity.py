@@ -281,7 +281,7 @@ def test_tiny_bf16_kv_cache():
 
 
 def test_llama7b_twin_prompt512():
-    """The benchmark's context length (512-token prompt: 4 prefill chunks, 8 KV pages, 5 KV splits in attention) at
+    """The benchmark's context length (512-token prompt: one prompt pass, 8 KV pages, 5 KV splits in attention) at
     LLaMA2-7B widths with 2 target layers."""
     st, toks, future = run_twin("llama2-7b", "T26", seed=7, n_layers=2, prompt_len=512, n_new=16, alpha=0.7773, max_seq=640)
     assert toks[:512 + 16] == future[:512 + 16]
