@@ -341,7 +341,7 @@ static size_t layout(eagle_ctx* c) {
     if (c->pt_floats) return;
     for (const Seen& q : seen) if (q.NRB == w.NRB && q.KS == w.KS && q.mt_max == mt_max && q.fused == fused) return;
     seen.push_back(Seen{w.NRB, w.KS, mt_max, fused});
-    for (int mt = 1; mt <= mt_max; ++mt) {
+    for (int mt = mt_max; mt >= 1 && (size_t)PLAN_MAX_SLICES * w.Npad * (size_t)(mt * 32) > worst; --mt) {   // (shorter passes cannot need more)
       const GemmPlan p = use_pf(c, mt) ? plan_pf(w.NRB, w.KS, mt, c->n_cu, fused, c->q4, c->fixed_sums) : plan_gemm(w.NRB, w.KS, c->NXP, mt);
       if (fused && use_pf(c, mt) && p.S == 1) continue;          // SwiGLU inside the GEMM: nothing goes through memory
       worst = std::max(worst, (size_t)p.S * w.Npad * (size_t)(mt * 32));
@@ -354,7 +354,8 @@ static size_t layout(eagle_ctx* c) {
   for (auto& w : c->layers) {
     consider(w.qkv, MTm, false); consider(w.o, MTm, false);
     if (w.moe && grouped) {
-      for (int mt = 1; mt <= MTm && !moe_seen && !c->pt_floats; ++mt) {           // (the layers are alike)
+      for (int mt = MTm; mt >= 1 && !moe_seen && !c->pt_floats; --mt) {           // (the layers are alike)
+        if ((size_t)PLAN_MAX_SLICES * w.e_dn[0].Npad * 32 * moe_tiles(32 * mt, g.experts_per_tok, g.n_experts) <= worst) break;
         const PlanMoe p = plan_moe(w.e_gu[0].NRB, w.e_gu[0].KS, w.e_dn[0].NRB, w.e_dn[0].KS, 32 * mt, g.experts_per_tok, g.n_experts, c->n_cu);
         worst = std::max(worst, (size_t)p.dn.S * w.e_dn[0].Npad * 32 * moe_tiles(32 * mt, g.experts_per_tok, g.n_experts));
       }

@@ -4,12 +4,13 @@
 #include <algorithm>
 #include <cstddef>
 
+constexpr int PLAN_MAX_SLICES = 16;   // most K slices any plan of the general path takes
 struct GemmPlan { int S, ks_per_split, chunk, rbw, mw; };   // rbw, mw: tile shape of the large-M GEMM (0: k_gemm)
 
 static inline GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
   GemmPlan p{};
   int wg_n = (NRB + 3) / 4;
-  int S = std::max(1, std::min(16, 512 / std::max(1, wg_n)));
+  int S = std::max(1, std::min(PLAN_MAX_SLICES, 512 / std::max(1, wg_n)));
   S = std::min(S, std::max(1, KS / 8));
   p.ks_per_split = (KS + S - 1) / S;
   p.S = (KS + p.ks_per_split - 1) / p.ks_per_split;
@@ -32,7 +33,7 @@ static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool 
 // 4-bit weights (k_gemm_pf_q4): one shape, two row blocks per wave and two wave columns; K slices of whole groups of 8 k-steps.
 static inline int plan_slices(int NRB, int KS, int MT, int n_cu) {     // fixed_sums: K slices of a matrix and a number of row tiles, whatever tile serves them
   const int wgs = ((NRB + 7) / 8) * ((MT + 3) / 4);
-  int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? 16 : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
+  int S = wgs * 2 > n_cu ? 1 : std::min(MT <= 4 ? PLAN_MAX_SLICES : KS >= 1024 ? 8 : 4, n_cu / std::max(1, wgs));
   return std::max(1, std::min(S, KS / (MT <= 4 ? 16 : 32)));
 }
 static inline GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epilogue, bool q4, bool fixed_sums) {
@@ -46,12 +47,15 @@ static inline GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epi
     if (MT <= 4 && sh.mw > 2) continue;                        // half of the work-group would idle
     if (!q4 && (MT <= 2) != (sh.mw == 1)) continue;            // two tiles of rows: work-groups of two waves, bound by the weight stream
     const int S_fix = fixed_sums ? plan_slices(NRB, KS, MT, n_cu) : 0;
-    for (int S = fixed_sums ? S_fix : 1; S <= (fixed_sums ? S_fix : 16); ++S) {
-      if (!fixed_sums && S > 1 && (KS / S < 16 || S * (double)MT * NRB * 8192.0 / 4.5e6 > best_us)) break;
+    // no split can beat all CUs at work all the time: shapes and slices whose price is above the best one already are not looked at
+    const double least = 1e-3 * sh.ns * NRB * MT * KS / (xcds * cu_x), slice_us = MT * NRB * 8192.0 / 4.5e6;
+    if (!fixed_sums && best_us >= 0 && least > best_us) continue;
+    for (int S = fixed_sums ? S_fix : 1; S <= (fixed_sums ? S_fix : PLAN_MAX_SLICES); ++S) {
+      if (!fixed_sums && S > 1 && (KS / S < 16 || least + S * slice_us > best_us)) break;
       const int unit = q4 ? 8 : 4, kps = ((KS + S - 1) / S + unit - 1) / unit * unit, s_real = (KS + kps - 1) / kps;
       const int rounds = ((nt * s_real + xcds - 1) / xcds * mq + cu_x - 1) / cu_x;
       double us = 1e-3 * sh.ns * rounds * wt * rt * kps + 4.0;
-      if (!(fused_epilogue && s_real == 1)) us += (double)s_real * MT * NRB * 8192.0 / 4.5e6;
+      if (!(fused_epilogue && s_real == 1)) us += s_real * slice_us;
       if (fused_epilogue && s_real > 1) us += 10.0;             // the SwiGLU kernel behind it
       if (best_us < 0 || us < best_us) { best_us = us; best.S = s_real; best.ks_per_split = kps; best.chunk = 4; best.rbw = sh.rbw; best.mw = sh.mw; }
     }
@@ -83,7 +87,7 @@ static inline PlanMoe plan_moe(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int
       if (sh.mw != mw) continue;
       for (int m = 0; m < 2; ++m) {
         const int wt = 2 * sh.rbw, KS = m ? dn_KS : gu_KS, NRB = m ? dn_NRB : gu_NRB, nt = (NRB + wt - 1) / wt;
-        for (int S = 1; S <= (m ? 16 : 1); ++S) {
+        for (int S = 1; S <= (m ? PLAN_MAX_SLICES : 1); ++S) {
           if (S > 1 && KS / S < 16) break;
           const int kps = ((KS + S - 1) / S + 3) / 4 * 4, s_real = (KS + kps - 1) / kps;
           const double full = (nt * s_real + 7) / 8 * cols / cu_x, rounds = full <= 1.0 ? 1.0 : full + 0.5;
