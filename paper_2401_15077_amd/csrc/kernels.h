@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ Wp, siz
 // prompt runs through the target and the head once, as one large matrix product per weight matrix).
 //   work-group tile  2 * RBW row blocks of weights x 2 * MW tiles of 32 activation rows; 2 x MW waves
 //   wave (wn, wm)    RBW row blocks x 2 activation tiles, both activation planes: 4 * RBW MFMAs per k-step
-//   LDS              a ring of four k-steps of BOTH operands (20 to 24 KiB each for MW = 4, 14 to 16 for MW = 2), filled by
+//   LDS              a ring of four k-steps of BOTH operands (20 to 24 KiB each for MW = 4, 14 to 16 for MW = 2, 10 to 12 for MW = 1), filled by
 //                    direct global -> LDS loads (both operands lie in memory in fragment order: one load = one 1 KiB tile)
 // At the barrier of k-step k every wave holds that step's fragments in registers, so its slot is refilled with step k + 4 at
 // once, step k + 1 is read from LDS behind the barrier, and both travel while the 4 * RBW MFMAs run: neither memory nor LDS

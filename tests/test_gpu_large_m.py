@@ -72,7 +72,10 @@ def _wide(base, d, ffn, **kw):
 DENSE = {"7b-widths": (synth.SHAPES["llama2-7b"].twin(1), (50, 333, 1060)), "d1536": (_wide("mini-gqa", 1536, 4096), (1490,))}
 EXPERTS = {"mixtral-widths": (synth.SHAPES["mixtral-8x7b"].twin(1), (300, 700), 31),
            "d256-e8": (replace(synth.SHAPES["mini-moe"], name="mini-moe-e8", n_experts=8, d_ffn=640), (1900,), 37),
-           "d768-e4": (_wide("mini-moe", 768, 2048), (1500,), 33)}
+           "d768-e4": (_wide("mini-moe", 768, 2048), (1500,), 33),
+           # the most experts and choices a model may have (most of the columns hold a few rows), and one choice of an odd number
+           "d256-e64-top4": (replace(synth.SHAPES["mini-moe"], name="mini-moe-e64", n_layers=1, n_experts=64, experts_per_tok=4), (3, 40, 150), 44),
+           "d256-e3-top1": (replace(synth.SHAPES["mini-moe"], name="mini-moe-e3", n_experts=3, experts_per_tok=1), (1, 200, 900), 40)}
 LOSS_ROWS = (300, 500, 1000)
 
 
@@ -141,6 +144,31 @@ def test_loss_rows_at_7b_widths():
     eng.close()
 
 
+@pytest.mark.parametrize("kv", ["fp32", "bf16"])
+@pytest.mark.parametrize("batch,tree", [(2, "T26"), (4, "T26"), (2, "B63"), (40, "root")])
+def test_batched_verify(batch, tree, kv):
+    """52, 104, 126 and 40 verify rows of several sequences through the large-M GEMM, LM head over all rows included; then a vanilla step."""
+    s = synth.SHAPES["mini-gqa"]
+    par, rk = synth.TREES[tree]
+    W = synth.make_weights(s, 15, synth.oracle_fmt(s))
+    eng = pkg.Eagle(s, par, rk, max_batch=batch, max_seq=256, kv_dtype=kv)
+    eng.load_weights(synth.iter_weights(s, 15, synth.device_fmt(s)))
+    orcs = [Oracle(s, W, par, rk, max_seq=256, dtype=np.float64, kv_store="bf16" if kv == "bf16" else None, seq_id=b) for b in range(batch)]
+    for b, orc in enumerate(orcs):
+        check_prefill(eng, orc, synth.prompt(15 + b, 30 + (17 * b) % 70, s.vocab), TOL["bf16"], seq=b)
+    sts = [Stats() for _ in orcs]
+    for _ in range(3):
+        lockstep_step_batch(eng, orcs, sts, TOL["bf16"])
+    eng.vanilla_step()                                          # the target alone: the root's row of the next verify pass
+    err = 0.0
+    for b, orc in enumerate(orcs):
+        orc.draft_tree()
+        err = max(err, float(np.abs(eng.get_buffer(pkg.BUF_VANILLA_LOGITS, b) - orc.verify()[1][0]).max()))
+    print(f"max|dL| {max(st.max_logit_err for st in sts):.2e} vanilla {err:.2e}", flush=True)
+    assert err <= TOL["bf16"]
+    eng.close()
+
+
 # ----------------------------------------------------------------------------- a bf16 cache
 # The oracle rounds K and V as the library does; an entry within rounding of a tie may go the other way on the two sides (one
 # bf16 ulp of that entry), which the tolerance of the bf16 models covers at these widths (the fp32 model's test of the bf16 cache
@@ -154,24 +182,6 @@ def test_prompt_rows_bf16_cache(rows):
     st = Stats()
     for _ in range(3):
         lockstep_step(eng, orc, st, TOL["bf16"])
-    eng.close()
-
-
-@pytest.mark.parametrize("batch,tree", [(2, "T26"), (4, "T26"), (2, "B63")])
-def test_batched_verify_bf16_cache(batch, tree):
-    """52, 104 and 126 verify rows of several sequences, bf16 weights, bf16 cache."""
-    s = synth.SHAPES["mini-gqa"]
-    par, rk = synth.TREES[tree]
-    W = synth.make_weights(s, 15, synth.oracle_fmt(s))
-    eng = pkg.Eagle(s, par, rk, max_batch=batch, max_seq=256, kv_dtype="bf16")
-    eng.load_weights(synth.iter_weights(s, 15, synth.device_fmt(s)))
-    orcs = [Oracle(s, W, par, rk, max_seq=256, dtype=np.float64, kv_store="bf16", seq_id=b) for b in range(batch)]
-    for b, orc in enumerate(orcs):
-        check_prefill(eng, orc, synth.prompt(15 + b, 30 + 17 * b, s.vocab), TOL["bf16"], seq=b)
-    sts = [Stats() for _ in orcs]
-    for _ in range(3):
-        lockstep_step_batch(eng, orcs, sts, TOL["bf16"])
-    print(f"max|dL| {max(st.max_logit_err for st in sts):.2e}", flush=True)
     eng.close()
 
 
