@@ -771,6 +771,15 @@ static KVCache kv_for(eagle_ctx* c, int li) {
   return kv;
 }
 
+static AttnArgs attn_args(eagle_ctx* c, const Pass& pass, const KVCache& kv, int n_splits, int n_new, bf16_t* xf_out, int MT, int rblocks, unsigned long long* trace) {
+  AttnArgs a;
+  a.rows_per_seq = pass.rows_per_seq; a.causal = pass.kind >= PASS_PREFILL_T || pass.kind == PASS_DRAFT_PENDING;
+  a.facts = c->facts; a.kv = kv; a.Q = c->Q; a.part_o = c->part_o; a.part_ml = c->part_ml;
+  a.H = c->cfg.n_heads; a.n_splits = n_splits; a.n_new = n_new; a.scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
+  a.counters = c->cnt_attn; a.xf_out = xf_out; a.nplanes = c->NXP; a.MT = MT; a.rblocks = rblocks; a.trace = trace;
+  return a;
+}
+
 static int resnorm(eagle_ctx* c, int M, int MT, const float* h_in, const float* PT, int S, int Npad, const float* bias,
                    const float* gain, bf16_t* XF, float* xout, const float* row_w = nullptr) {
   if (c->fixed_sums) {
@@ -805,7 +814,6 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
     int n_splits = attn_splits(c, t_max, H * pass.n_seq * rblocks);
     if (pass.n_seq * rblocks > 128) return fail(EAGLE_EINVAL, "internal: too many (sequence, row block) pairs in one pass");
     dim3 grid(n_splits, H, pass.n_seq * rblocks);
-    float scale = 1.0f / std::sqrt((float)dh);
 #define ATTNG(CT, DH)                                                                                                   \
   do {                                                                                                                  \
     static bool attr_done = false;                                                                                      \
@@ -814,7 +822,7 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
       attr_done = true;                                                                                                 \
     }                                                                                                                   \
     hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * 32 * (DH + 4) + 4 * 2 * 32) * 4, \
-        pass, (const RowFact*)c->facts, kv, (const float*)c->Q, c->part_o, c->part_ml, H, n_splits, n_new, scale, c->cnt_attn, c->xf_att, c->NXP, (unsigned long long*)nullptr, MT, rblocks); \
+        attn_args(c, pass, kv, n_splits, n_new, c->xf_att, MT, rblocks, nullptr)); \
     if (e_ != hipSuccess) return fail(EAGLE_EHIP, "attention launch failed: %s", hipGetErrorString(e_));                \
   } while (0)
     if (c->kv_f32) { if (dh == 128) ATTNG(float, 128); else if (dh == 64) ATTNG(float, 64); else ATTNG(float, 32); }
@@ -1155,7 +1163,6 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
     int n_splits = attn_splits(c, ctx_max + 64, H * pass.n_seq);
     unsigned long long* atrace = (c->attn_no++ == c->attn_trace_sel && n_splits * H <= 1024) ? c->trace : nullptr;
     dim3 grid(n_splits, H, pass.n_seq);
-    float scale = 1.0f / std::sqrt((float)dh);
     KVCache kv = kv_for(c, li);
 #define ATTN2(CT, DH)                                                                                                   \
   do {                                                                                                                  \
@@ -1165,7 +1172,7 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
       attr_done = true;                                                                                                 \
     }                                                                                                                   \
     hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * 32 * (DH + 4) + 4 * 2 * 32) * 4, \
-        pass, (const RowFact*)c->facts, kv, (const float*)c->Q, c->part_o, c->part_ml, H, n_splits, n_new, scale, c->cnt_attn, c->xf2_att, c->NXP, atrace, 1, 1); \
+        attn_args(c, pass, kv, n_splits, n_new, c->xf2_att, 1, 1, atrace)); \
     if (e_ != hipSuccess) return fail(EAGLE_EHIP, "attention launch failed: %s", hipGetErrorString(e_));                \
   } while (0)
     if (c->kv_f32) { if (dh == 128) ATTN2(float, 128); else if (dh == 64) ATTN2(float, 64); else ATTN2(float, 32); }

@@ -1289,54 +1289,50 @@ __device__ __forceinline__ void attn_merge_chunk(const float* part_o, const floa
   }
 }
 
+struct AttnArgs {
+  int rows_per_seq, causal;                // rows of a sequence in the pass; pending rows and prompts see their own rows causally
+  const RowFact* facts; KVCache kv; const float* Q; float* part_o; float* part_ml;
+  int H, n_splits, n_new; float scale; int* counters; bf16_t* xf_out; int nplanes, MT, rblocks;   // MT = 32-row tiles of the XF output
+  unsigned long long* trace;               // profiling builds only
+};
+
+// Work-group = (KV split, query head, (sequence of the pass, 32-row block of that sequence's rows)).
 template <typename CT, int DH>
-__global__ __launch_bounds__(256) void k2_attn(Pass pass, const RowFact* __restrict__ facts, KVCache kv,
-                                               const float* __restrict__ Q, float* part_o, float* part_ml, int H,
-                                               int n_splits, int n_new, float scale, int* counters, bf16_t* xf_out,
-                                               int nplanes, unsigned long long* trace, int MT, int rblocks) {
+__global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   constexpr int KSN = DH / 16;              // k-steps of the QK product
   constexpr int DB = DH / 32;               // 32-wide blocks of the head dimension
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_a[];
   constexpr int OS = DH + 4;                // row stride of o_s: 16-byte accesses along d and across rows without bank conflicts
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_a[];
   float* o_s = (float*)smem_a;              // [4 waves][32 rows][OS]
   float* ml_s = o_s + 4 * 32 * OS;          // [4 waves][2][32]
   __shared__ int s_last;
-  // blockIdx.z = (sequence of the pass, 32-row block of that sequence's rows); MT = 32-row tiles of the XF output
-  const int split = blockIdx.x, hd = blockIdx.y, seq_l = blockIdx.z / rblocks, rblk = blockIdx.z % rblocks;
+  const int split = blockIdx.x, hd = blockIdx.y, z = blockIdx.z;
+  const int H = A.H, n_splits = A.n_splits, n_new = A.n_new, MT = A.MT, nplanes = A.nplanes;
+  const KVCache& kv = A.kv;
+  const float* Q = A.Q;
+  float *part_o = A.part_o, *part_ml = A.part_ml;
+  bf16_t* xf_out = A.xf_out;
+  const int seq_l = z / A.rblocks, rblk = z % A.rblocks;
   // optional time stamps: 0 entered, 1 keys/values consumed, 2 waves merged + partials written, 3 arrived, 4 splits merged
-  unsigned long long* tr = TRACE_PTR((trace && threadIdx.x == 0 && seq_l == 0) ? trace + ((size_t)hd * gridDim.x + split) * 8 : nullptr);
+  unsigned long long* tr = TRACE_PTR((A.trace && threadIdx.x == 0 && seq_l == 0) ? A.trace + ((size_t)hd * n_splits + split) * 8 : nullptr);
   TRACE_STAMP(tr, 0);
-  const int r0 = seq_l * pass.rows_per_seq + 32 * rblk;
-  const int R = min(32, pass.rows_per_seq - 32 * rblk);
+  const int r0 = seq_l * A.rows_per_seq + 32 * rblk;
+  const int R = min(32, A.rows_per_seq - 32 * rblk);
   const int kvh = hd / (H / kv.n_kv_heads);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
   const int q = lane & 31, hh = lane >> 5;
-  // the rows' facts were written by the pass's first kernel; pending rows and prompts see their own rows causally
-  const bool causal = pass.kind >= PASS_PREFILL_T || pass.kind == PASS_DRAFT_PENDING;
-  const RowFact fq = facts[r0 + min(q, R - 1)];                 // this lane's query row
+  // the queries are requested before anything else: their address needs no load (wave w takes k-steps w, w + 4, ...)
+  constexpr int QI = (KSN + 3) / 4;
+  float qx[QI][8];
+#pragma unroll
+  for (int i = 0; i < QI; ++i)
+    if (w + 4 * i < KSN) load8(Q + ((size_t)(r0 + min(q, R - 1)) * H + hd) * DH + 16 * (w + 4 * i) + 8 * hh, qx[i]);
+  // (the rows' facts were written by the pass's first kernel)
+  const bool causal = A.causal;
+  const RowFact fq = A.facts[r0 + min(q, R - 1)];                 // this lane's query row
   const int seq = __builtin_amdgcn_readfirstlane(fq.seq), base = __builtin_amdgcn_readfirstlane(fq.base);
   const int rel = fq.rel;
   const unsigned long long mask = (unsigned long long)fq.mask_hi << 32 | fq.mask_lo;
-  // The scaled queries as bf16 hi + lo B-operand fragments live in LDS, built once by the four waves together (wave w
-  // converts k-steps w, w+4, ...); they share the memory of o_s, which is not written before every wave has left the
-  // key loop.  (One load and one conversion of the queries per work-group instead of one per wave.)
-  bf16x8* q_s = (bf16x8*)smem_a;                               // [2 planes][KSN][64 lanes]
-  for (int ks = w; ks < KSN; ks += 4) {
-    float x[8];
-    if (q < R) {
-      load8(Q + ((size_t)(r0 + q) * H + hd) * DH + 16 * ks + 8 * hh, x);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] *= scale;
-    } else {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = 0.f;
-    }
-    bf16x8 h8, l8;
-    split8(x, h8, l8);
-    q_s[(0 * KSN + ks) * 64 + lane] = h8;
-    q_s[(1 * KSN + ks) * 64 + lane] = l8;
-  }
-  __syncthreads();
   // causal passes (prompt chunks, pending rows): the rows of this 32-row block see no new token beyond its own last row,
   // so the blocks of keys after it are not visited at all (they would contribute exp(-inf) = 0: same bits, less work)
   const int T = base + (causal ? min(n_new, 32 * rblk + R) : n_new);
@@ -1344,32 +1340,68 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const RowFact* __restr
   const int span = base + max(64, (n_new + 63) / 64 * 64);   // passes with at most 64 new rows share one partition
   const int tps = ((span + n_splits - 1) / n_splits + 63) / 64 * 64;
   const int t_begin = split * tps, t_end = min(T, t_begin + tps);
+  // Wave w takes every 4th 32-token block.  A block starts on a multiple of 32 and therefore lies inside one 64-token
+  // (or larger) page.  The keys of the NEXT block are requested as soon as the scores of the current one are done
+  // (the registers are free then), after the current block's values, so that they travel while the softmax and the
+  // P V product run: a wave that walks several blocks pays about one memory round trip per block.
+  // A block's address is the same for the whole wave and stays in scalar registers; a lane adds a 32-bit offset.  (With an address
+  // per lane the 64 value loads of a block took their offsets from vector registers; that, a branch per score for the mask and
+  // the queries requested behind the facts: 15.2 us a launch at 7B, 550 keys, 26 rows, 13.9 without.)
+  float kx[KSN][8];
+  size_t blk = 0;
+  auto block_of = [&](int tok) -> size_t {
+    const int phys = __builtin_amdgcn_readfirstlane(kv.page_table[seq * kv.pages_per_seq + (tok >> kv.page_shift)]);
+    return (((size_t)phys * kv.n_kv_heads + kvh) << kv.page_shift | (size_t)(tok & ((1 << kv.page_shift) - 1))) * DH;
+  };
+  const uint32_t k_lane = (uint32_t)((lane & 31) * DH + 8 * hh), v_lane = (uint32_t)(4 * hh * DH + (lane & 31));
+  auto load_keys = [&](size_t at) {
+    const CT* kp = (const CT*)kv.k + at;
+#pragma unroll
+    for (int ks = 0; ks < KSN; ++ks) load8(kp + 16 * ks + k_lane, kx[ks]);
+  };
+  // slot t of lane-half hh in k-step j of the P V product is the token that accumulator register 8j+t of the same lane-half holds
+  float vx[2][DB][8];
+  auto load_values = [&](size_t at) {
+    const CT* vp = (const CT*)kv.v + at;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int tl = 16 * j + 8 * (t >> 2) + (t & 3);       // + 4 * hh
+          vx[j][b][t] = cache_load(vp + tl * DH + 32 * b + v_lane);
+        }
+  };
+  // The scaled queries as bf16 hi + lo B-operand fragments live in LDS, built once by the four waves together (wave w
+  // converts k-steps w, w+4, ...); they share the memory of o_s, which is not written before every wave has left the
+  // key loop.  (One load and one conversion of the queries per work-group instead of one per wave.)
+  bf16x8* q_s = (bf16x8*)smem_a;                               // [2 planes][KSN][64 lanes]
+#pragma unroll
+  for (int i = 0; i < QI; ++i) {
+    const int ks = w + 4 * i;
+    if (ks >= KSN) continue;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) qx[i][t] = q < R ? qx[i][t] * A.scale : 0.f;
+    bf16x8 h8, l8;
+    split8(qx[i], h8, l8);
+    q_s[(0 * KSN + ks) * 64 + lane] = h8;
+    q_s[(1 * KSN + ks) * 64 + lane] = l8;
+  }
+  __syncthreads();
+  {
+    const int tok0 = t_begin + 32 * w;
+    if (tok0 < t_end) { blk = block_of(tok0); load_keys(blk); }
+  }
   float m_run = -INFINITY, l_run = 0.f;
   f32x16 oacc[DB];
 #pragma unroll
   for (int b = 0; b < DB; ++b)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[b][r] = 0.f;
-
-  // Wave w takes every 4th 32-token block.  A block starts on a multiple of 32 and therefore lies inside one 64-token
-  // (or larger) page.  The keys of the NEXT block are requested as soon as the scores of the current one are done
-  // (the registers are free then), after the current block's values, so that they travel while the softmax and the
-  // P V product run: a wave that walks several blocks pays about one memory round trip per block.
-  float kx[KSN][8];
-  size_t blk = 0;
-  {
-    const int tok0 = t_begin + 32 * w;
-    if (tok0 < t_end) {
-      blk = kv_offset(kv, seq, tok0, kvh);
-      const CT* kp = (const CT*)kv.k + blk + (size_t)(lane & 31) * DH + 8 * hh;
-#pragma unroll
-      for (int ks = 0; ks < KSN; ++ks) load8(kp + 16 * ks, kx[ks]);
-    }
-  }
   for (int tok0 = t_begin + 32 * w; tok0 < t_end; tok0 += 128) {
-    const CT* vp = (const CT*)kv.v + blk;
     const bool more = tok0 + 128 < t_end;
-    const size_t blk_next = more ? kv_offset(kv, seq, tok0 + 128, kvh) : 0;   // look-up in flight during the scores
+    const size_t blk_next = more ? block_of(tok0 + 128) : 0;   // look-up in flight during the scores
     f32x16 sacc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
@@ -1382,36 +1414,23 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const RowFact* __restr
       sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, ql, sacc, 0, 0, 0);
       sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh, sacc, 0, 0, 0);
     }
-    // V gathers go out before the softmax arithmetic: slot t of lane-half hh in k-step j is the token that
-    // accumulator register 8j+t of the same lane-half holds
-    float vx[2][DB][8];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int tl = 16 * j + 8 * (t >> 2) + 4 * hh + (t & 3);
-          vx[j][b][t] = cache_load(vp + (size_t)tl * DH + 32 * b + (lane & 31));
-        }
-    if (more) {
-      const CT* kp = (const CT*)kv.k + blk_next + (size_t)(lane & 31) * DH + 8 * hh;
-#pragma unroll
-      for (int ks = 0; ks < KSN; ++ks) load8(kp + 16 * ks, kx[ks]);
-    }
+    load_values(blk);                                          // (out before the softmax arithmetic)
+    if (more) load_keys(blk_next);
     blk = blk_next;
-    // mask, running max and sum for this lane's query
+    // mask, running max and sum for this lane's query.  Bit i of vis: token tok0 + i is visible to the row.
+    uint32_t vis = 0xFFFFFFFFu;
+    if (tok0 + 32 > base || tok0 + 32 > t_end) {               // (uniform: most blocks hold cached tokens only)
+      const int sh = tok0 - base;
+      auto ones = [](int n) -> uint32_t { return n >= 32 ? 0xFFFFFFFFu : n <= 0 ? 0u : (1u << n) - 1u; };
+      if (causal) vis = ones(rel + 1 - sh);
+      else vis = ones(-sh) | (sh >= 64 || sh <= -32 ? 0u : sh >= 0 ? (uint32_t)(mask >> sh) : (uint32_t)(mask << -sh));
+      vis &= ones(t_end - tok0);
+    }
+    vis = q < R ? vis >> (4 * hh) : 0u;
     float bmax = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int t = tok0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-      bool vis = t < base;
-      if (!vis) {
-        const int j = t - base;
-        vis = causal ? (j <= rel) : (j < 64 && ((mask >> j) & 1ull));
-      }
-      vis = vis && t < t_end && q < R;
-      sacc[r] = vis ? sacc[r] : -INFINITY;
+      sacc[r] = (vis >> (8 * (r >> 2) + (r & 3))) & 1u ? sacc[r] : -INFINITY;
       bmax = fmaxf(bmax, sacc[r]);
     }
     bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
@@ -1493,7 +1512,7 @@ __global__ __launch_bounds__(256) void k2_attn(Pass pass, const RowFact* __restr
   publish_wait();
   __syncthreads();
   if (tid == 0) {
-    int* cnt = counters + blockIdx.z * H + hd;
+    int* cnt = A.counters + z * H + hd;
     int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = (old == n_splits - 1);
     if (s_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
