@@ -812,6 +812,8 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
     // the MFMA attention kernel of the fast path, one work-group per (KV split, head, sequence x 32-row block)
     int rblocks = (pass.rows_per_seq + 31) / 32;
     int n_splits = attn_splits(c, t_max, H * pass.n_seq * rblocks);
+    // (dense models with a bf16 cache keep k2_attn's order of sums, see fixed_sums)
+    const bool prompt = !c->fixed_sums && pass.kind >= PASS_PREFILL_T && pass.n_seq == 1 && n_splits == 1 && plan_is_prompt_attn(M, H, c->n_cu);
     if (pass.n_seq * rblocks > 128) return fail(EAGLE_EINVAL, "internal: too many (sequence, row block) pairs in one pass");
     dim3 grid(n_splits, H, pass.n_seq * rblocks);
 #define ATTNG(CT, DH)                                                                                                   \
@@ -819,10 +821,13 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
     static bool attr_done = false;                                                                                      \
     if (!attr_done) {                                                                                                   \
       HIPCHK(hipFuncSetAttribute((const void*)k2_attn<CT, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024)); \
+      HIPCHK(hipFuncSetAttribute((const void*)k2_attn_prompt<CT, DH>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024)); \
       attr_done = true;                                                                                                 \
     }                                                                                                                   \
-    hipError_t e_ = launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * 32 * (DH + 4) + 4 * 2 * 32) * 4, \
-        attn_args(c, pass, kv, n_splits, n_new, c->xf_att, MT, rblocks, nullptr)); \
+    const AttnArgs aa = attn_args(c, pass, kv, n_splits, n_new, c->xf_att, MT, rblocks, nullptr);                       \
+    hipError_t e_ = prompt                                                                                              \
+        ? launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn_prompt", k2_attn_prompt<CT, DH>, dim3(H, (M + 127) / 128), dim3(ATTN_PROMPT_THREADS), std::max((size_t)DH / 16 * 8 * 2048, (size_t)4 * (DH / 2 + 2) * 256), aa) \
+        : launch_k(c, KC_ATTN, attn_bytes(c, pass, n_new), "k2_attn", k2_attn<CT, DH>, grid, dim3(256), (size_t)(4 * 32 * (DH + 4) + 4 * 2 * 32) * 4, aa); \
     if (e_ != hipSuccess) return fail(EAGLE_EHIP, "attention launch failed: %s", hipGetErrorString(e_));                \
   } while (0)
     if (c->kv_f32) { if (dh == 128) ATTNG(float, 128); else if (dh == 64) ATTNG(float, 64); else ATTNG(float, 32); }

@@ -1562,3 +1562,182 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   }
   TRACE_STAMP(tr, 4);
 }
+
+// ============================================================================ causal attention of a prompt pass
+// The arithmetic of k2_attn (scores and outputs transposed, hi * hi + hi * lo + lo * hi on bf16 pieces of the fp32 values), for one
+// sequence of many rows: a work-group owns 128 rows of a head, a wave 32 of them, and the keys and values of 32 tokens at a time
+// are fetched, split into bf16 pieces and laid out as MFMA operands ONCE for the four waves, in LDS.  (k2_attn walks the tokens with
+// all four waves on the same 32 rows: every work-group fetches and splits all keys and values for 32 rows, which is what bounds it
+// there -- 41 GB/s a CU from the L2 and 64 four-byte loads a lane and block.)  Two tile buffers: the next tile is requested before
+// the products of this one and written behind them, one barrier a tile.  Work-groups of the last rows, which see the most tokens,
+// come first in the grid.
+#define ATTN_PROMPT_THREADS 512
+template <typename CT, int DH>
+__global__ __launch_bounds__(ATTN_PROMPT_THREADS, 2) void k2_attn_prompt(AttnArgs A) {
+  constexpr int KSN = DH / 16, DB = DH / 32, VP = 2 * DB;        // k-steps of the scores; (16 tokens, 32 dims) pieces of the values
+  constexpr int TILE = (KSN + VP) * 2 * 64;                      // 16-byte units of a tile: keys [plane][k-step][lane], values [plane][piece][lane]
+  constexpr int KI = (KSN + 3) / 4, VI = (VP + 3) / 4;           // a wave's share of a tile
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_a[];
+  const int H = A.H, rows = A.rows_per_seq;
+  const KVCache& kv = A.kv;
+  // consecutive work-groups go round the 8 XCDs: an XCD gets neighbouring heads, which share keys and values in grouped-query models
+  const int hd = H % 8 == 0 ? (int)(blockIdx.x % 8) * (H / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x;
+  const int blk = (int)gridDim.y - 1 - (int)blockIdx.y;
+  const int kvh = hd / (H / kv.n_kv_heads);
+  const int lane = threadIdx.x & 63, w = wave_id() & 3, kg = wave_id() >> 2, q = lane & 31, hh = lane >> 5;   // 32 rows w of the tiles kg, kg + 2, ...
+  bf16x8* tiles = (bf16x8*)smem_a + kg * 2 * TILE;               // [2][TILE] of the half
+  const int r0 = 128 * blk + 32 * w, row = min(r0 + q, rows - 1);
+  const bool live = r0 + q < rows;
+  bf16x8 qf[2][KSN];                                             // the wave's scaled queries, hi and lo
+#pragma unroll
+  for (int ks = 0; ks < KSN; ++ks) {
+    float x[8];
+    load8(A.Q + ((size_t)row * H + hd) * DH + 16 * ks + 8 * hh, x);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] *= A.scale;
+    split8(x, qf[0][ks], qf[1][ks]);
+  }
+  const RowFact fq = A.facts[row];
+  const int seq = __builtin_amdgcn_readfirstlane(fq.seq), base = __builtin_amdgcn_readfirstlane(fq.base), rel = fq.rel;
+  const int see = base + min(rows, 128 * blk + 128), see_w = base + min(rows, r0 + 32);   // tokens the work-group's / the wave's rows see
+  const int nt = (see + 31) / 32;
+  // page-table entries of 64 pages in the lanes of a register: no load stands in front of a tile's
+  int pages = 0, page0 = -64;
+  auto block_of = [&](int tok) -> size_t {
+    const int pg = tok >> kv.page_shift;
+    if (pg >= page0 + 64) { page0 = pg; pages = kv.page_table[seq * kv.pages_per_seq + min(pg + lane, kv.pages_per_seq - 1)]; }
+    const int phys = __builtin_amdgcn_readlane(pages, pg - page0);
+    return (((size_t)phys * kv.n_kv_heads + kvh) << kv.page_shift | (size_t)(tok & ((1 << kv.page_shift) - 1))) * DH;
+  };
+  float kx[KI][8], vx[VI][8];
+  const uint32_t k_lane = (uint32_t)((lane & 31) * DH + 8 * hh), v_lane = (uint32_t)(4 * hh * DH + (lane & 31));
+  auto fetch = [&](int tok) {
+    const size_t at = block_of(tok);
+    const CT *kp = (const CT*)kv.k + at, *vp = (const CT*)kv.v + at;
+#pragma unroll
+    for (int i = 0; i < KI; ++i)
+      if (w + 4 * i < KSN) load8(kp + 16 * (w + 4 * i) + k_lane, kx[i]);
+#pragma unroll
+    for (int i = 0; i < VI; ++i) {
+      const int pc = w + 4 * i, j = pc / DB, b = pc % DB;        // order of the tokens in a piece: see k2_attn
+      if (pc < VP)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) vx[i][t] = cache_load(vp + (16 * j + 8 * (t >> 2) + (t & 3)) * DH + 32 * b + v_lane);
+    }
+  };
+  auto put = [&](bf16x8* tile) {
+#pragma unroll
+    for (int i = 0; i < KI; ++i)
+      if (w + 4 * i < KSN) {
+        bf16x8 h8, l8;
+        split8(kx[i], h8, l8);
+        tile[(w + 4 * i) * 64 + lane] = h8;
+        tile[(KSN + w + 4 * i) * 64 + lane] = l8;
+      }
+#pragma unroll
+    for (int i = 0; i < VI; ++i)
+      if (w + 4 * i < VP) {
+        bf16x8 h8, l8;
+        split8(vx[i], h8, l8);
+        tile[(2 * KSN + w + 4 * i) * 64 + lane] = h8;
+        tile[(2 * KSN + VP + w + 4 * i) * 64 + lane] = l8;
+      }
+  };
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int b = 0; b < DB; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[b][r] = 0.f;
+  if (kg < nt) { fetch(32 * kg); put(tiles); }
+  __syncthreads();
+  for (int i = 0; 2 * i < nt; ++i) {
+    const int tok0 = 32 * (2 * i + kg);
+    const bool more = tok0 + 64 < 32 * nt;
+    const bf16x8* tile = tiles + (i & 1) * TILE;
+    if (more) fetch(tok0 + 64);
+    if (tok0 < see_w) {                                          // (uniform over the wave; the tiles behind hold only tokens its rows do not see)
+      f32x16 sacc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KSN; ++ks) {
+        const bf16x8 kh = tile[ks * 64 + lane], kl = tile[(KSN + ks) * 64 + lane];
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qf[0][ks], sacc, 0, 0, 0);
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qf[1][ks], sacc, 0, 0, 0);
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qf[0][ks], sacc, 0, 0, 0);
+      }
+      if (tok0 + 32 > base + r0) {                               // the tile holds tokens that some row does not see
+        const int n = live ? base + rel + 1 - tok0 : 0;          // token tok0 + i is visible iff i < n
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[r] = 8 * (r >> 2) + 4 * hh + (r & 3) < n ? sacc[r] : -INFINITY;
+      }
+      float bmax = sacc[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) bmax = fmaxf(bmax, sacc[r]);
+      bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+      const float m_new = fmaxf(m_run, bmax);
+      if (__any(m_new > m_run)) {                                // (otherwise the factor is 1 in every lane)
+        const float alpha = m_run == -INFINITY ? 0.f : __expf(m_run - m_new);
+        l_run *= alpha;
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[b][r] *= alpha;
+        m_run = m_new;
+      }
+      const float m_sub = m_new == -INFINITY ? 0.f : m_new;      // (no visible token yet: every score is -inf, every weight 0)
+      float psum = 0.f, pv[2][8];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float e = __expf(sacc[r] - m_sub);
+        pv[r >> 3][r & 7] = e;
+        psum += e;
+      }
+      psum += __shfl_xor(psum, 32, 64);
+      l_run += psum;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        bf16x8 ph, pl;
+        split8(pv[j], ph, pl);
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+          const bf16x8 vh = tile[(2 * KSN + j * DB + b) * 64 + lane], vl = tile[(2 * KSN + VP + j * DB + b) * 64 + lane];
+          oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, ph, oacc[b], 0, 0, 0);
+          oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, pl, oacc[b], 0, 0, 0);
+          oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl, ph, oacc[b], 0, 0, 0);
+        }
+      }
+    }
+    if (more) put(tiles + ((i + 1) & 1) * TILE);
+    __syncthreads();
+  }
+  // the second half's state goes through LDS to the first half's waves of the same rows
+  float* st = (float*)smem_a + (size_t)w * (16 * DB + 2) * 64 + lane;
+  if (kg == 1) {
+    st[0] = m_run; st[64] = l_run;
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st[(2 + 16 * b + r) * 64] = oacc[b][r];
+  }
+  __syncthreads();
+  if (kg == 1 || !live) return;
+  {
+    const float m1 = st[0], m_new = fmaxf(m_run, m1);            // (a live row's first half holds token 0: m_new is finite or NaN)
+    const float w0 = __expf(m_run - m_new), w1 = m1 == -INFINITY ? 0.f : __expf(m1 - m_new);
+    l_run = l_run * w0 + st[64] * w1;
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[b][r] = oacc[b][r] * w0 + st[(2 + 16 * b + r) * 64] * w1;
+  }
+  const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
+#pragma unroll
+  for (int b = 0; b < DB; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 o; o.x = oacc[b][4 * i]; o.y = oacc[b][4 * i + 1]; o.z = oacc[b][4 * i + 2]; o.w = oacc[b][4 * i + 3];
+      xf_store4(A.xf_out, r0 + q, hd * DH + 32 * b + 8 * i + 4 * hh, A.MT, H * DH / 16, A.nplanes, o * inv);
+    }
+}

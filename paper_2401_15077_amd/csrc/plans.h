@@ -24,6 +24,13 @@ static inline GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
 // keep their order (fixed_sums); with 4-bit weights all.
 static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool q4) { return MT > 4 || (MT >= (fixed_sums ? 3 : 2) && big_gemm) || q4; }
 
+// Which prompt passes take the attention kernel of 128 rows a work-group (k2_attn_prompt) instead of the one of 32 (k2_attn): those
+// whose small work-groups would go through the chip at least twice.  (Where they all fit at once, the run of tiles of one work-group
+// is what counts, and with few rows most of a 128-row block is padding.)  us a launch, 32 / 128 rows: 32 heads, 256 rows 16 / 22, 384
+// rows 29 / 31, 512 rows 40 / 38, 1024 rows 108 / 67; 40 heads, 300 rows 27 / 26, 1024 rows 140 / 69; 64 heads (8 of keys), 300
+// rows 40 / 27, 2011 rows 690 / 290.
+static inline bool plan_is_prompt_attn(int rows, int heads, int n_cu) { return rows >= 256 && heads * ((rows + 31) / 32) >= 2 * n_cu; }
+
 // Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
 // in a model of two terms, in us.  What the busiest CU multiplies: rounds x (32 x 32 tiles of a work-group) x k-steps of a slice
 // x the shape's measured time per tile and k-step.  Groups of work-groups that share a weight tile go round the 8 XCDs, so a

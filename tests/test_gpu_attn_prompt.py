@@ -1,0 +1,41 @@
+"""Causal attention of long prompts (k2_attn_prompt: 128 rows a work-group, two tiles of 32 tokens a round) against the CPU oracle:
+rows that end inside a wave's 32, at and behind a work-group's 128, in an odd number of tiles; every head dimension; grouped heads and
+a number of heads that is no multiple of 8; a second pass over a long cache (more than 64 pages); the bf16 cache of a mixture of experts."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import paper_2401_15077_amd as pkg
+import synth
+from lockstep import Stats, check_prefill, lockstep_step
+from oracle.eagle_oracle import Oracle
+
+pytestmark = pytest.mark.gpu
+
+# Two bf16 pieces hold 16 bits of a factor: 2^-17 relative per factor and some hundred terms of mixed sign stay below 2^-13 of the
+# largest logit, which is at most 4 in these models.  bf16 cache: the rounding of K and V can turn, 2^-9 of about one entry in a thousand.
+BOUND = {"fp32": 4 * 2.0 ** -13, "bf16": 1e-3}
+
+
+def _shape(base, heads, kv_heads, dh, **kw):
+    return replace(synth.SHAPES[base], name=f"{base}-h{heads}x{dh}", n_layers=1, n_heads=heads, n_kv_heads=kv_heads, head_dim=dh, **kw)
+
+
+@pytest.mark.parametrize("base,heads,kv_heads,dh,rows,kv,page", [
+    ("mini-gqa", 64, 8, 32, 256, "fp32", 64), ("mini-gqa", 64, 64, 32, 257, "fp32", 64), ("mini-gqa", 64, 8, 32, 383, "fp32", 32),
+    ("mini-gqa", 52, 4, 64, 385, "fp32", 64), ("mini-gqa", 52, 52, 64, 511, "fp32", 64), ("mini-gqa", 40, 8, 128, 448, "fp32", 128),
+    ("mini-gqa", 32, 4, 128, 513, "fp32", 64), ("mini-gqa", 12, 4, 32, 2700, "fp32", 32), ("mini-moe", 64, 8, 64, 300, "bf16", 64),
+    ("mini-moe", 64, 8, 128, 290, "fp32", 64)])
+def test_prompt_attention(base, heads, kv_heads, dh, rows, kv, page):
+    s = _shape(base, heads, kv_heads, dh)
+    par, rk = synth.TREES["T8"]
+    print(s.name, "prompt of", rows, kv, "pages of", page, flush=True)
+    eng = pkg.Eagle(s, par, rk, max_seq=rows + 64, kv_dtype=kv, page_tokens=page)
+    eng.load_weights(synth.iter_weights(s, 71, synth.device_fmt(s)))
+    orc = Oracle(s, synth.make_weights(s, 71, synth.oracle_fmt(s)), par, rk, max_seq=rows + 64, dtype=np.float32, kv_store="bf16" if kv == "bf16" else None)
+    err = check_prefill(eng, orc, synth.prompt(rows, rows, s.vocab), BOUND[kv])
+    st = Stats()
+    lockstep_step(eng, orc, st, 2e-2)                            # the head's cache of every prompt row is what drafting reads
+    print(f"max|dL| prompt {err:.2e} verify {st.max_logit_err:.2e}", flush=True)
+    eng.close()
