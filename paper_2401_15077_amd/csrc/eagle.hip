@@ -742,9 +742,11 @@ static int collect_gemm_events(eagle_ctx* c) {
 
 // KV splits of the attention kernel for `tokens` keys and `units` (head, sequence, row block) triples: one 32-token
 // block per wave (128 tokens per work-group) while that keeps the grid within one work-group per CU -- the kernel's
-// registers allow no more, and a second round of work-groups costs more than a wave walking a few blocks in turn.
+// registers allow no more, and a second round of work-groups costs more than a wave walking a few blocks in turn.  Up to 192
+// tokens stay in one work-group: a second block in two of its waves costs less than the exchange between two work-groups (a
+// tiny model's launch 8.9 -> 5.1 us; 7B with 139 tokens: a request of 8 layers 22.6 -> 22.3 ms).
 static int attn_splits(const eagle_ctx* c, int tokens, int units) {
-  const int by_tokens = (tokens + 127) / 128, by_cus = std::max(1, c->n_cu / std::max(1, units));
+  const int by_tokens = !c->fixed_sums && tokens <= 192 ? 1 : (tokens + 127) / 128, by_cus = std::max(1, c->n_cu / std::max(1, units));
   return std::max(1, std::min(16, std::min(by_tokens, by_cus)));
 }
 
@@ -961,24 +963,23 @@ static hipError_t launch_k2(eagle_ctx* c, double bytes, const Gemm2& g, size_t l
   return launch_k(c, c->cur_class, bytes, Q4 ? "k2_gemm<4-bit weights>" : "k2_gemm", k2_gemm<NWP, NXP, RW, DEPTH, Q4>, dim3(g.groups * g.S), dim3(V2_THREADS), lds, g);
 }
 
-template <int NRMAX, bool HALF = false>
+template <int NRMAX, bool HALF = false, int NWP = 1, int NXP = 2>
 static hipError_t launch_fk(eagle_ctx* c, double bytes, const Gemm2& g, int grid) {
   static bool attr_set = false;
-  // the waves' sums, and behind them the residual epilogue's staging rows
-  const size_t lds = (size_t)8 * NRMAX * 4096 + (g.epi == EPI_RESID ? (size_t)NRMAX * 32 * 33 * 4 : 0);
+  const size_t lds = (size_t)8 * NRMAX * 4096;
   if (lds > 144 * 1024) return hipErrorInvalidValue;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<1, 2, NRMAX, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<NWP, NXP, NRMAX, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  return launch_k(c, c->cur_class, bytes, HALF ? "k2_gemm_fk<half blocks>" : "k2_gemm_fk", k2_gemm_fk<1, 2, NRMAX, HALF>, dim3(grid), dim3(V2_THREADS), lds, g);
+  return launch_k(c, c->cur_class, bytes, HALF ? "k2_gemm_fk<half blocks>" : "k2_gemm_fk", k2_gemm_fk<NWP, NXP, NRMAX, HALF>, dim3(grid), dim3(V2_THREADS), lds, g);
 }
 
 template <int NRMAX>
 static hipError_t launch_fk_q4(eagle_ctx* c, double bytes, const Gemm2& g, int grid) {
   static bool attr_set = false;
-  const size_t lds = (size_t)8 * NRMAX * 4096 + (g.epi == EPI_RESID ? (size_t)NRMAX * 32 * 33 * 4 : 0);
+  const size_t lds = (size_t)8 * NRMAX * 4096;
   if (lds > 144 * 1024) return hipErrorInvalidValue;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<1, 2, NRMAX, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
@@ -1089,31 +1090,26 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   // CU, and a work-group that owns one row block over all of K fetches twice as many activation bytes as weight
   // bytes -- measured there: down 109.7 us whole-K against 85.8 us split-K, O 37.5 against 34.8)
   const bool fullk = !c->f32 && w.NRB >= c->n_cu && g.epi != EPI_RESID;
-  // ... and narrower ones with at least one HALF row block per CU (O, down, FC at d = 4096 / 5120): still whole-K, a
-  // work-group owns one or two halves
-  // (measured at d = 4096: 35.6 us against 26.0 for down, 16.0 against 14.2 for O -- every tile load of a work-group
-  // that owns a single half carries half the bytes, so half as much is in flight, and the whole activation vector is
-  // fetched by every work-group instead of a K slice of it; the split is therefore not used)
-  const bool halfk = false && !c->f32 && !fullk && 2 * w.NRB >= c->n_cu && c->n_cu <= 256 && fits_rsrc &&
-                     (g.epi == EPI_RESID || g.epi == EPI_QKV);
+  // (dense models with a bf16 cache keep their K slices, see fixed_sums)
+  const bool small = !c->fixed_sums && plan_is_whole_k(w.NRB, w.KS, c->NWP + c->NXP, c->n_cu);
   // other matrices of the bf16 configuration: split-K, with the activations either staged in LDS (plan2) or streamed
   // (plan_xk), whichever the fetch model prices lower
   PlanXK px; px.S = 0;
-  if (!fullk && !halfk && !c->f32) {
+  if (!fullk && !c->f32) {
     px = plan_xk(w.NRB, w.KS, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
     const int kt_s = (w.KS + p.S - 1) / p.S;
     const long staged = (long)R * kt_s + (long)c->NXP * kt_s + 2L * p.S * R * 4 + 40;
     if (px.S > 0 && px.cost >= staged) px.S = 0;
   }
-  if (px.S > 0) {
+  if (small) {
+    if (groups_out) *groups_out = w.NRB;
+    g.trace = nullptr;
+    e = c->f32 ? launch_fk<1, false, 3, 3>(c, bytes, g, w.NRB) : launch_fk<1>(c, bytes, g, w.NRB);
+  } else if (px.S > 0) {
     g.S = px.S; g.groups = px.groups;
     if (groups_out) *groups_out = px.groups;
     g.trace = (g.trace && px.groups * px.S <= 1024) ? g.trace : nullptr;
     e = px.nrmax <= 2 ? launch_xk<2>(c, bytes, g) : px.nrmax == 3 ? launch_xk<3>(c, bytes, g) : launch_xk<4>(c, bytes, g);
-  } else if (halfk) {
-    g.trace = (g.trace && c->n_cu <= 1024) ? g.trace : nullptr;
-    if (groups_out) *groups_out = c->n_cu;
-    e = launch_fk<2, true>(c, bytes, g, c->n_cu);
   } else if (fullk) {
     const int grid = fk_grid;
     if (groups_out) *groups_out = grid;
@@ -1236,9 +1232,7 @@ static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_ne
   c->ssq2_groups = eg;
   for (int l = 0; l < cf.n_layers; ++l)
     if ((rc = layer2(c, pass, M, l, ctx_max, n_new, l + 1 < cf.n_layers ? c->layers[l + 1].attn_norm : c->final_norm))) return rc;
-  k2_features<<<M, 256, 0, c->stream>>>(c->h2, scale_of(c, c->ssq2, c->ssq2_groups), c->final_norm, M, d, c->featbuf);
-  LAUNCH_CHECK();
-  k_store_rows<<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->featbuf, c->F, c->pend_f, c->chunk_f, d);
+  k2_features<<<M, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->h2, scale_of(c, c->ssq2, c->ssq2_groups), c->final_norm, d, c->F, c->pend_f, c->chunk_f);
   LAUNCH_CHECK();
   if (!want_logits) return EAGLE_OK;
   return lm_head2(c, M, true, logits_out);

@@ -1151,21 +1151,23 @@ __global__ __launch_bounds__(256) void k_logits(Pass pass, const TreeDev* tree, 
   out[dst + v] = a;
 }
 
-// copy rows (features): dst[dst_row(r)] = src[r]
-__global__ __launch_bounds__(256) void k_store_rows(Pass pass, const TreeDev* tree, SeqState st, const float* src,
-                                                    float* node_dst /*[seq][M][d]*/, float* pend_dst /*[seq][D+1][d]*/,
-                                                    float* chunk_dst /*[chunk][d]*/, int d) {
-  int r = blockIdx.x;
+// Where row r of a pass keeps its feature (nullptr: nowhere): tree nodes [seq][M][d], pending rows [seq][D+1][d], prompt rows [chunk][d].
+__device__ inline float* feature_row(const Pass& pass, const TreeDev* tree, const SeqState& st, int r, float* node_dst, float* pend_dst, float* chunk_dst, int d) {
   RowInfo ri = row_info(pass, tree, st, r);
-  if (!ri.valid) return;
-  float* dst = nullptr;
-  if (pass.kind == PASS_VERIFY || pass.kind == PASS_DRAFT_LEVEL) dst = node_dst + ((size_t)ri.seq * tree->M + ri.node) * d;
-  else if (pass.kind == PASS_DRAFT_PENDING) { if (ri.node == 0) dst = node_dst + ((size_t)ri.seq * tree->M) * d; }
-  else if (pass.kind == PASS_PREFILL_T) {
-    dst = chunk_dst + (size_t)ri.rel * d;
-  } else if (pass.kind == PASS_VANILLA) dst = pend_dst + (size_t)ri.seq * (tree->D + 1) * d;
+  if (!ri.valid) return nullptr;
+  if (pass.kind == PASS_VERIFY || pass.kind == PASS_DRAFT_LEVEL) return node_dst + ((size_t)ri.seq * tree->M + ri.node) * d;
+  if (pass.kind == PASS_DRAFT_PENDING) return ri.node == 0 ? node_dst + ((size_t)ri.seq * tree->M) * d : nullptr;
+  if (pass.kind == PASS_PREFILL_T) return chunk_dst + (size_t)ri.rel * d;
+  if (pass.kind == PASS_VANILLA) return pend_dst + (size_t)ri.seq * (tree->D + 1) * d;
+  return nullptr;
+}
+// copy rows (features): feature_row(r) = src[r]
+__global__ __launch_bounds__(256) void k_store_rows(Pass pass, const TreeDev* tree, SeqState st, const float* __restrict__ src,
+                                                    float* __restrict__ node_dst, float* __restrict__ pend_dst, float* __restrict__ chunk_dst, int d) {
+  const int r = blockIdx.x;
+  float* dst = feature_row(pass, tree, st, r, node_dst, pend_dst, chunk_dst, d);
   if (!dst) return;
-  for (int k = threadIdx.x; k < d; k += blockDim.x) dst[k] = src[(size_t)r * d + k];
+  for (int k = 4 * threadIdx.x; k < d; k += 1024) *(f32x4*)(dst + k) = *(const f32x4*)(src + (size_t)r * d + k);
 }
 
 // ============================================================================ training loss of the head (Sec. 3.2)

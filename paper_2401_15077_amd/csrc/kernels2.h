@@ -781,7 +781,7 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
 template <int NWP, int NXP, int NR, bool WB = false>
 __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, int M, int kb, int ke, const u32x4* const* wp,
                                                    size_t wps, f32x16* acc, int lane, const FkHalf* hw = nullptr) {
-  constexpr int DEPTH = NWP == 1 ? (NR == 1 ? 8 : NR == 2 ? 6 : NR == 3 ? 5 : 4) : 2;   // ~24 KiB in flight per wave; deeper measured the same
+  constexpr int DEPTH = NWP == 1 ? (NR == 1 ? 8 : NR == 2 ? 6 : NR == 3 ? 5 : 4) : NR == 1 ? 4 : 2;   // ~24 KiB in flight per wave; deeper measured the same
   if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH, WB>(XF, KS, M, kb, ke, wp, wps, acc, lane, hw);
   else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1, WB>(nr, XF, KS, M, kb, ke, wp, wps, acc, lane, hw);
 }
@@ -903,19 +903,11 @@ __device__ __forceinline__ f32x4 fk_sum4(const float* red, int nrmax, int j, int
   for (int w = 0; w < 8; ++w) a += *(const f32x4*)(red + ((((size_t)w * nrmax + j) * 4 + (qd >> 1)) * 64 + m + 32 * (qd & 1)) * 4);
   return a;
 }
-__device__ inline float fk_sum(const float* red, int nrmax, int j, int n_local, int m) {
-  float a = 0.f;
-#pragma unroll
-  for (int w = 0; w < 8; ++w) a += red[((((size_t)w * nrmax + j) * 4 + (n_local >> 3)) * 64 + m + 32 * ((n_local >> 2) & 1)) * 4 + (n_local & 3)];
-  return a;
-}
-
 // HALF: the unit of the work split is half a row block (16 weight rows) instead of a whole one, for matrices whose
 // row blocks do not divide evenly over the CUs (QKV at d = 4096: 384 blocks over 256 CUs = 1 or 2 each, but 3 halves
-// each) and for matrices with fewer row blocks than CUs (O, down, FC at d = 4096: 128 blocks = one half per CU, which
-// keeps them whole-K: no partial sums are exchanged).  A work-group then owns a run of halves; of a block it shares
-// with a neighbour it loads and finishes only its own 16 rows (the other lanes of the tile load nothing and multiply
-// zeros).  Rotate-half pairs are adjacent rows, so a half holds whole pairs.  Epilogues: QKV and the residual one.
+// each).  A work-group then owns a run of halves; of a block it shares with a neighbour it loads and finishes only its own
+// 16 rows (the other lanes of the tile load nothing and multiply zeros).  Rotate-half pairs are adjacent rows, so a half
+// holds whole pairs.  Epilogue: QKV.
 template <int NWP, int NXP, int NRMAX, bool HALF = false, bool Q4 = false>
 __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   static_assert(!Q4 || (!HALF && NWP == 1), "4-bit weights: whole row blocks, one plane");
@@ -978,6 +970,19 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   } else
   fk_stream_dispatch<NWP, NXP, NRMAX, HALF>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane, &hw);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
+  // residual epilogue: what the first item of a thread adds and multiplies, requested before the sums
+  f32x4 rh = {0.f, 0.f, 0.f, 0.f}, rbias = rh, rgain = rh;
+  auto load_resid = [&](int n) {
+    const int mm = threadIdx.x & 31;
+    if (g.h_in && mm < g.M) rh = *(const f32x4*)(g.h_in + (size_t)mm * g.d + n);
+    if (g.bias) rbias = *(const f32x4*)(g.bias + n);
+    if (g.gain_next) rgain = *(const f32x4*)(g.gain_next + n);
+  };
+  constexpr bool RESID = !HALF && NRMAX <= 2;                   // (host: at most two row blocks where this epilogue is used)
+  if (RESID && g.epi == EPI_RESID) {
+    const int n = (rb0 + (threadIdx.x >> 8)) * 32 + 4 * ((threadIdx.x >> 5) & 7);
+    if ((int)threadIdx.x >> 8 < nr && n < g.N) load_resid(n);
+  }
   // park every wave's sums in LDS
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
@@ -1032,24 +1037,24 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
       }
      }
     }
-  } else if (g.epi == EPI_RESID) {
-    // h_out = h_in + (routing weight *) W x + bias on this work-group's rows [n_lo, n_hi); per-token partial sums of
-    // squares for the consumer's RMSNorm; x * gain of the next norm in fragment layout.  One output per thread and
-    // round, parked in LDS behind `red`, then repacked in runs of 8 rows.
-    float* xo = red + (size_t)8 * NRMAX * 16 * 64;              // [rows <= 32*NRMAX][33]
-    const int n_lo = HALF ? rb0 * 32 + row_lo : rb0 * 32;
-    const int n_hi = min(HALF ? (rb1 - 1) * 32 + row_hi : rb1 * 32, g.N);
+  } else if (RESID && g.epi == EPI_RESID) {
+    // h_out = h_in + (routing weight *) W x + bias; per-token partial sums of squares for the consumer's RMSNorm; x * gain of the
+    // next norm as GEMM input.  item = (row block j, quad of 4 rows), the residual, bias and gain of the first on their way already
     const float rw = g.row_w ? g.row_w[m] : 1.0f;
     float ss = 0.f;
-    for (int nl = slot; nl < n_hi - n_lo; nl += 16) {
-      const int n = n_lo + nl;
-      float v = fk_sum(red, NRMAX, (n >> 5) - rb0, n & 31, m);
+    for (int it = slot; it < nr * 8; it += 16) {
+      const int j = it >> 3, qd = it & 7;
+      const int n = (rb0 + j) * 32 + 4 * qd;
+      if (n >= g.N) continue;                                   // (N is a multiple of 64)
+      if (it != slot) load_resid(n);
+      f32x4 v = fk_sum4(red, NRMAX, j, qd, m);
       if (g.row_w) v *= rw;
-      if (g.bias) v += g.bias[n];
-      if (g.h_in && live) v += g.h_in[(size_t)m * g.d + n];
-      if (live) g.h_out[(size_t)m * g.d + n] = v;
-      ss += v * v;
-      xo[nl * 33 + m] = g.gain_next ? v * g.gain_next[n] : v;
+      if (g.bias) v += rbias;
+      if (g.h_in && live) v += rh;
+      if (live) *(f32x4*)(g.h_out + (size_t)m * g.d + n) = v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) ss = fmaf(v[t], v[t], ss);
+      if (live) xf_store4(g.xf_out, m, n, 1, g.xf_KS, NXP, g.gain_next ? v * rgain : v);
     }
     sh_small[slot * 32 + m] = ss;
     __syncthreads();
@@ -1057,12 +1062,6 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
       float a = 0.f;
       for (int i = 0; i < 16; ++i) a += sh_small[i * 32 + threadIdx.x];
       g.ssq_out[blockIdx.x * 32 + threadIdx.x] = a;
-    }
-    for (int c = slot; c < (n_hi - n_lo + 7) >> 3; c += 16) {
-      float x[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) x[t] = 8 * c + t < n_hi - n_lo ? xo[(8 * c + t) * 33 + m] : 0.f;
-      if (live) xf_store8(g.xf_out, m, n_lo + 8 * c, 1, g.xf_KS, NXP, x);
     }
   } else {                                                      // EPI_LOGITS
     const int nend = min(g.N, g.V);
@@ -1216,13 +1215,16 @@ __global__ __launch_bounds__(256) void k2_embed(Pass pass, const TreeDev* tree, 
   }
 }
 
-// features[m][k] = h[m][k] * rstd[m] * gain[k]   (the target's final RMSNorm, Sec. 2: f is what the LM head reads)
-__global__ __launch_bounds__(256) void k2_features(const float* h, RowScale rs, const float* gain, int M, int d, float* out) {
+// The target's final RMSNorm (Sec. 2: f is what the LM head reads): h[m][k] * rstd[m] * gain[k], straight to where the pass keeps its
+// rows' features (see k_store_rows).
+__global__ __launch_bounds__(256) void k2_features(Pass pass, const TreeDev* tree, SeqState st, const float* __restrict__ h, RowScale rs, const float* __restrict__ gain,
+                                                   int d, float* __restrict__ node_dst, float* __restrict__ pend_dst, float* __restrict__ chunk_dst) {
   __shared__ float tmp[17];
   const int m = blockIdx.x;
-  if (m >= M) return;
+  float* dst = feature_row(pass, tree, st, m, node_dst, pend_dst, chunk_dst, d);
   const float r = block_row_rstd(rs.ssq, rs.groups, rs.inv_d, rs.eps, m, tmp);
-  for (int k = threadIdx.x; k < d; k += blockDim.x) out[(size_t)m * d + k] = h[(size_t)m * d + k] * r * gain[k];
+  if (!dst) return;
+  for (int k = 4 * threadIdx.x; k < d; k += 1024) *(f32x4*)(dst + k) = *(const f32x4*)(h + (size_t)m * d + k) * r * *(const f32x4*)(gain + k);
 }
 
 // ============================================================================ tree-masked paged attention, <= 32 rows per sequence

@@ -111,6 +111,12 @@ static inline PlanMoe plan_moe(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int
   return best;
 }
 
+// Small matrices of the fast path: a work-group per row block over all of K (k2_gemm_fk) instead of K slices whose partial sums cross
+// work-groups.  K x planes is what a work-group then fetches, in KiB per 16 columns: 400 of them take about what the exchange does
+// (store, acknowledge, count, read back: 5 us).  Whole requests, ms, sliced / whole: fp32, d 256 (96 KiB) 8.8 / 7.6; bf16, d 1024 (192)
+// 9.7 / 8.9; d 2048 (384) 12.5 / 12.0; matrices of 528 KiB 8.8 / 9.3.
+static inline bool plan_is_whole_k(int NRB, int KS, int planes, int n_cu) { return NRB <= n_cu && (long)KS * planes <= 400; }
+
 // Work split of the split-K kernel with streamed activations: S slices x groups of at most 4 row blocks, chosen by a
 // fetch model in KiB per work-group (weights + the live part of the X slice + twice the partials the last work-group
 // of a row group reads back, which sit on the critical path of one CU).  Depends on the matrix shape only.

@@ -19,6 +19,7 @@ void shim_moe(const int* a, int* o) {
   const PlanMoe p = plan_moe(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7]);
   put(p.gu, o); put(p.dn, o + 4); o[8] = p.cols;
 }
+int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
 int shim_moe_tiles(int M, int topk, int E) { return moe_tiles(M, topk, E); }
 }
 """
@@ -47,6 +48,9 @@ class Plans:
         o = (ctypes.c_int * 9)()
         self.lib.shim_moe(a, o)
         return Plan(*o[:4]), Plan(*o[4:8]), o[8]
+
+    def whole_k(self, NRB, KS, planes, n_cu=256):
+        return bool(self.lib.shim_whole_k(NRB, KS, planes, n_cu))
 
     def moe_tiles(self, M, topk, E):
         return self.lib.shim_moe_tiles(M, topk, E)
