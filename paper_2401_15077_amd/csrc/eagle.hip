@@ -507,6 +507,9 @@ extern "C" int eagle_init(const eagle_config* cfg, void* workspace_dev, size_t w
     if (hipMemcpyAsync(c->page_table, pt.data(), pt.size() * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess) { delete c; return fail(EAGLE_EHIP, "page table upload failed"); }
   }
+  if (g.temperature > 0.f && g.vocab <= 32768 &&
+      (hipFuncSetAttribute((const void*)k_accept<ACCEPT_SAMPLED>, hipFuncAttributeMaxDynamicSharedMemorySize, CDF_LDS) != hipSuccess ||
+       hipFuncSetAttribute((const void*)k_choose<false>, hipFuncAttributeMaxDynamicSharedMemorySize, CDF_LDS) != hipSuccess)) { delete c; return fail(EAGLE_EHIP, "shared memory of the sampling kernels"); }
   c->hint.future = c->hint_future; c->hint.stride = c->st.tok_stride; c->hint.n = c->hint_n;
   c->hint.alpha = c->hint_alpha; c->hint.bias = c->hint_bias; c->hint.seed = c->hint_seed;
   for (int i = 0; i < 4; ++i)
@@ -1258,6 +1261,15 @@ static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new,
   return lm_head2(c, M, false, c->draft_logits);
 }
 
+// The next token of n sequences from seq0 on, from their rows of vanilla_logits.
+static int choose(eagle_ctx* c, int n, int seq0, int is_prefill, int prefill_n) {
+  const eagle_config& g = c->cfg;
+  if (g.vocab > 32768) k_choose<true><<<n, 1024, 0, c->stream>>>(c->st, seq0, c->vanilla_logits, g.vocab, g.temperature, g.seed, c->pbuf, is_prefill, prefill_n, c->D);
+  else k_choose<false><<<n, 1024, g.temperature > 0.f ? CDF_LDS : 0, c->stream>>>(c->st, seq0, c->vanilla_logits, g.vocab, g.temperature, g.seed, c->pbuf, is_prefill, prefill_n, c->D);
+  LAUNCH_CHECK();
+  return EAGLE_OK;
+}
+
 // ---------------------------------------------------------------------------- sequence life cycle
 extern "C" int eagle_reset(eagle_ctx* c) {
   if (!c) return fail(EAGLE_EINVAL, "null context");
@@ -1300,8 +1312,7 @@ extern "C" int eagle_prefill(eagle_ctx* c, int32_t seq, const int32_t* prompt, i
     if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, last)
                    : target_forward(c, pt, start + cn, cn, last, c->vanilla_logits, 1, 1))) return rc;
     if (last) {
-      k_choose<<<1, 1024, 0, c->stream>>>(c->st, seq, c->vanilla_logits, g.vocab, g.temperature, g.seed, c->pbuf, 1, n, c->D);
-      LAUNCH_CHECK();
+      if ((rc = choose(c, 1, seq, 1, n))) return rc;
       HIPCHK(hipMemcpyAsync(c->pend_f + (size_t)seq * (c->D + 1) * g.d_model, c->chunk_f + (size_t)(cn - 1) * g.d_model,
                             (size_t)g.d_model * 4, hipMemcpyDeviceToDevice, c->stream));
     }
@@ -1413,6 +1424,13 @@ static int max_ctx(eagle_ctx* c) {
   return m;
 }
 
+static LevelNodes level_nodes(const eagle_ctx* c, int level) {
+  LevelNodes l;
+  memset(&l, 0, sizeof(l));                                      // (-1: the root)
+  if (level >= 0) for (int i = 0; i < c->tree_h.n_level_rows[level]; ++i) l.node[i] = (uint8_t)c->tree_h.level_rows[level][i];
+  return l;
+}
+
 static int do_draft(eagle_ctx* c) {
   int rc = step_ready(c);
   if (rc) return rc;
@@ -1426,8 +1444,8 @@ static int do_draft(eagle_ctx* c) {
   if ((rc = (fast1 ? head_forward2(c, p1, ctx, D1, false) : head_forward(c, p1, ctx + D1, D1, true)))) return rc;
   dim3 g0(1, B);
   const float* src1 = fast1 ? c->h2 : nullptr;   // fast path: k_expand stores the root's head feature itself
-  if (g.vocab > 32768) k_expand<true><<<g0, 1024, 0, c->stream>>>(-1, B, c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, src1, c->node_f, g.d_model, D1);
-  else k_expand<false><<<g0, 1024, 0, c->stream>>>(-1, B, c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, c->expand_trace ? c->trace : nullptr, src1, c->node_f, g.d_model, D1);
+  if (g.vocab > 32768) k_expand<true><<<g0, 1024, 0, c->stream>>>(-1, level_nodes(c, -1), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, src1, c->node_f, g.d_model, D1);
+  else k_expand<false><<<g0, 1024, 0, c->stream>>>(-1, level_nodes(c, -1), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, c->expand_trace ? c->trace : nullptr, src1, c->node_f, g.d_model, D1);
   LAUNCH_CHECK();
   for (int lev = 1; lev < c->D; ++lev) {
     int nr = c->tree_h.n_level_rows[lev];
@@ -1438,8 +1456,8 @@ static int do_draft(eagle_ctx* c) {
     if ((rc = (fastl ? head_forward2(c, pl, ctx, c->M, false) : head_forward(c, pl, ctx + c->M, c->M, true)))) return rc;
     dim3 gl(nr, B);
     const float* srcl = fastl ? c->h2 : nullptr;
-    if (g.vocab > 32768) k_expand<true><<<gl, 1024, 0, c->stream>>>(lev, B, c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, srcl, c->node_f, g.d_model, nr);
-    else k_expand<false><<<gl, 1024, 0, c->stream>>>(lev, B, c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, srcl, c->node_f, g.d_model, nr);
+    if (g.vocab > 32768) k_expand<true><<<gl, 1024, 0, c->stream>>>(lev, level_nodes(c, lev), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, srcl, c->node_f, g.d_model, nr);
+    else k_expand<false><<<gl, 1024, 0, c->stream>>>(lev, level_nodes(c, lev), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, srcl, c->node_f, g.d_model, nr);
     LAUNCH_CHECK();
   }
   c->phase = 1;
@@ -1474,7 +1492,11 @@ static int do_accept(eagle_ctx* c, float* pbuf, float* qbuf, int* row_amax) {
   const eagle_config& g = c->cfg;
   const int B = c->n_active;
   if (g.temperature <= 0.f) { k_row_argmax<<<B * c->M, 1024, 0, c->stream>>>(c->L, g.vocab, row_amax); LAUNCH_CHECK(); }
-  k_accept<<<B, 1024, 0, c->stream>>>(c->tree_d, c->st, c->L, c->draft_logits, c->tree_tok, g.vocab, g.temperature, g.seed, pbuf, qbuf, c->path, c->tok_out, c->len_out, row_amax);
+#define ACCEPT(KIND, LDS) k_accept<KIND><<<B, 1024, LDS, c->stream>>>(c->tree_d, c->st, c->L, c->draft_logits, c->tree_tok, g.vocab, g.temperature, g.seed, pbuf, qbuf, c->path, c->tok_out, c->len_out, row_amax)
+  if (g.temperature <= 0.f) ACCEPT(ACCEPT_GREEDY, 0);
+  else if (g.vocab > 32768) ACCEPT(ACCEPT_SAMPLED_BIGV, 0);
+  else ACCEPT(ACCEPT_SAMPLED, CDF_LDS);
+#undef ACCEPT
   LAUNCH_CHECK();
   return do_compact(c);
 }
@@ -1605,8 +1627,7 @@ extern "C" int eagle_vanilla_step(eagle_ctx* c, int32_t* tokens) {
   pass_ctx(c, pv);
   if ((rc = (B <= 32 ? target_forward2(c, pv, max_ctx(c), 1, c->vanilla_logits)
                      : target_forward(c, pv, max_ctx(c) + 1, 1, true, c->vanilla_logits, 1, 0)))) return rc;
-  k_choose<<<B, 1024, 0, c->stream>>>(c->st, 0, c->vanilla_logits, g.vocab, g.temperature, g.seed, c->pbuf, 0, 0, c->D);
-  LAUNCH_CHECK();
+  if ((rc = choose(c, B, 0, 0, 0))) return rc;
   std::vector<int> tk(B);
   for (int s = 0; s < B; ++s)
     HIPCHK(hipMemcpyAsync(&tk[s], c->st.tokens + (size_t)s * c->st.tok_stride + c->h_ntok[s], 4, hipMemcpyDeviceToHost, c->stream));
@@ -1698,8 +1719,8 @@ extern "C" int eagle_expand_level(eagle_ctx* c, int32_t level) {
   const int nr = level < 0 ? 1 : c->tree_h.n_level_rows[level];
   if (nr == 0) return EAGLE_OK;
   dim3 grid(nr, c->n_active);
-  if (g.vocab > 32768) k_expand<true><<<grid, 1024, 0, c->stream>>>(level, c->n_active, c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, nullptr, c->node_f, g.d_model, nr);
-  else k_expand<false><<<grid, 1024, 0, c->stream>>>(level, c->n_active, c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, nullptr, c->node_f, g.d_model, nr);
+  if (g.vocab > 32768) k_expand<true><<<grid, 1024, 0, c->stream>>>(level, level_nodes(c, level), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, nullptr, c->node_f, g.d_model, nr);
+  else k_expand<false><<<grid, 1024, 0, c->stream>>>(level, level_nodes(c, level), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, nullptr, c->node_f, g.d_model, nr);
   LAUNCH_CHECK();
   return EAGLE_OK;
 }

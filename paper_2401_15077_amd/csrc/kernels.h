@@ -148,28 +148,36 @@ __device__ inline float block_max(float v, float* sh) {
 __device__ inline void better(float& v, int& i, float v2, int i2) {
   if (v2 > v || (v2 == v && i2 < i)) { v = v2; i = i2; }
 }
-__device__ inline void block_argmax(float& v, int& i, float* shv, int* shi) {
-  for (int o = 32; o > 0; o >>= 1) {
-    float v2 = __shfl_xor(v, o, 64);
-    int i2 = __shfl_xor(i, o, 64);
-    better(v, i, v2, i2);
-  }
-  int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+// The pair as one number: larger value first, then lower index; -0 and +0 are equal, a NaN counts as -inf.  0 is below every pair.
+__device__ inline unsigned long long arg_key(float v, int i) {
+  uint32_t b = __builtin_bit_cast(uint32_t, v == v ? v + 0.0f : -INFINITY);
+  b ^= (uint32_t)((int)b >> 31) | 0x80000000u;
+  return (unsigned long long)b << 32 | (uint32_t)~i;
+}
+__device__ inline int arg_index(unsigned long long key) { return (int)~(uint32_t)key; }
+template <int CTRL, int ROWS>
+__device__ inline unsigned long long key_max_dpp(unsigned long long k) {   // lanes without a source lane take 0
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)k, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(k >> 32), CTRL, ROWS, 0xf, false);
+  const unsigned long long o = (unsigned long long)hi << 32 | lo;
+  return o > k ? o : k;
+}
+__device__ inline unsigned long long key_of_lane(unsigned long long k, int lane) {
+  return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, lane);
+}
+// Largest key of the block (at most 16 waves); sh: 16 entries.  Lane moves inside the vector unit (row shifts, row broadcasts) instead of
+// exchanges through the LDS unit (child selection at 1024 entries, two to four rounds: 12.3 -> 8.6 us a launch).
+__device__ inline unsigned long long block_max_key(unsigned long long k, unsigned long long* sh) {
+  k = key_max_dpp<0x111, 0xf>(k); k = key_max_dpp<0x112, 0xf>(k); k = key_max_dpp<0x114, 0xf>(k); k = key_max_dpp<0x118, 0xf>(k);   // row_shr 1, 2, 4, 8
+  k = key_max_dpp<0x142, 0xa>(k); k = key_max_dpp<0x143, 0xc>(k);                                                                  // row_bcast 15, 31
+  k = key_of_lane(k, 63);
+  const int nw = (blockDim.x + 63) >> 6, l = threadIdx.x & 15;
+  __syncthreads();                                               // (sh may still be read from the call before)
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = k;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) { shv[w] = v; shi[w] = i; }
-  __syncthreads();
-  // second level: lanes 0..15 of every wave take one per-wave result each and reduce them with four exchanges (the
-  // (value, index) order is total, so the exchange pattern does not matter); lane 0 broadcasts
-  const int l = threadIdx.x & 63;
-  v = l < nw ? shv[l] : -INFINITY;
-  i = l < nw ? shi[l] : 0x7fffffff;
-  for (int o = 8; o > 0; o >>= 1) {
-    float v2 = __shfl_xor(v, o, 64);
-    int i2 = __shfl_xor(i, o, 64);
-    better(v, i, v2, i2);
-  }
-  v = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
-  i = __builtin_amdgcn_readfirstlane(i);
+  k = l < nw ? sh[l] : 0;
+  k = key_max_dpp<0x111, 0xf>(k); k = key_max_dpp<0x112, 0xf>(k); k = key_max_dpp<0x114, 0xf>(k); k = key_max_dpp<0x118, 0xf>(k);
+  return key_of_lane(k, 15);
 }
 
 // ============================================================================ weight packing
@@ -1325,44 +1333,50 @@ struct HintDev {
 
 // Children of one tree node = the top-k entries of its (knob-adjusted, Gumbel-perturbed when non-greedy) head
 // logits, rank r = (r+1)-th largest, equal scores -> lower token id (App. A.1).  Block = (parent row, seq).
+struct LevelNodes { uint8_t node[EAGLE_MAX_NODES]; };            // a level's parent nodes, by row of its pass (kernel argument: no load in front)
 template <bool BIGV>   // BIGV: more than 32768 vocabulary entries (the scores of a row do not fit the block's registers)
-__global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, int n_seq, const TreeDev* tree, SeqState st,
+__global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelNodes nodes, const TreeDev* tree, SeqState st,
                                                  float* draft_logits /*[seq][M][V]*/, int* tree_tok, int* on_path, HintDev hint,
                                                  int V, float temperature, unsigned long long rng_seed, unsigned long long* trace,
                                                  const float* __restrict__ feat_src /*[pass rows][d] or null*/, float* node_f /*[seq][M][d]*/,
                                                  int d, int src_rows_per_seq) {
-  __shared__ float shv[16];
-  __shared__ int shi[16];
+  __shared__ unsigned long long shk[16];
   const int seq = blockIdx.y;
   unsigned long long* tr = TRACE_PTR((trace && threadIdx.x == 0 && blockIdx.x == 0 && seq == 0) ? trace : nullptr);
   TRACE_STAMP(tr, 0);
-  const int v = level < 0 ? 0 : tree->level_rows[level][blockIdx.x];
+  const int v = nodes.node[blockIdx.x];
   const int M = tree->M;
   // The node's own head feature (the row of the pass that produced these logits) goes to node_f here when the caller
   // asks for it: one block per row of the pass exists anyway, which saves a separate copy kernel per pass.
   // Row of the pass: a level pass lists the level's parent nodes in order; in a pending pass the root is the
   // sequence's last pending row.
-  if (feat_src) {
-    const int row = seq * src_rows_per_seq + (level < 0 ? max(st.n_pend[seq] - 1, 0) : (int)blockIdx.x);
-    const float* src = feat_src + (size_t)row * d;
-    float* dst = node_f + ((size_t)seq * M + v) * d;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) dst[k] = src[k];
-  }
   float* lg = draft_logits + ((size_t)seq * M + v) * V;
   // Loads are grouped by what they depend on, so that the kernel pays two memory round trips, not one per fact:
   // (1) everything addressed by (seq, v) alone, including the first 32 logits of every thread ...
   constexpr int XPT = 32;                                      // logits per thread and chunk (1024 threads: 32768)
   float x[XPT];
 #pragma unroll
-  for (int u = 0; u < XPT; ++u) x[u] = lg[min(u * 1024 + (int)threadIdx.x, V - 1)];
+  for (int u = 0; u < XPT; ++u) {
+    x[u] = -INFINITY;
+    if (u * 1024 < V) x[u] = lg[min(u * 1024 + (int)threadIdx.x, V - 1)];
+  }
   const int n = st.n_tok[seq];
+  const int feat_row = feat_src ? seq * src_rows_per_seq + (level < 0 ? max(st.n_pend[seq] - 1, 0) : (int)blockIdx.x) : 0;
   const int hn = hint.n[seq];
   const unsigned long long hseed = hint.seed[seq];
   const float halpha = hint.alpha[seq], hbias = hint.bias[seq];
   const int depth_v = tree->depth[v], nk = tree->nchild[v];
   const int on_v = v == 0 ? 0 : on_path[seq * M + v];
   const unsigned long long step_no = (unsigned long long)st.step_no[seq];
-  // (2) ... then what needs the sequence length: the root token, the target's future tokens at two positions
+  // (2) ... then what needs the sequence length: the feature row, stored at the end, the root token, the target's future tokens at two positions
+  f32x4 feat[2];                                               // columns 4 * tid .. of 8192; wider rows: below
+  const float* feat_in = feat_src ? feat_src + (size_t)feat_row * d : nullptr;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    feat[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int k = 4096 * i + 4 * (int)threadIdx.x;
+    if (feat_src && k < d) feat[i] = *(const f32x4*)(feat_in + k);
+  }
   const int stride = hint.stride;
   const int pos_child = n + depth_v;
   const int root_tok = st.tokens[(size_t)seq * st.tok_stride + max(n - 1, 0)];
@@ -1395,6 +1409,7 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, int n_
     // lower token id); only the thread that owned it removes it and looks for its next best.
 #pragma unroll
     for (int u = 0; u < XPT; ++u) {
+      if (u * 1024 >= V) continue;                             // (uniform: a small vocabulary uses the first few)
       const int j = u * 1024 + (int)threadIdx.x;
       float sc = x[u];
       if (j == hinted) { sc += adj; lg[j] = sc; }            // later phases read the adjusted logits
@@ -1404,26 +1419,27 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, int n_
       }
       x[u] = j < V ? sc : -INFINITY;
     }
-    float lv = -INFINITY; int li = 0x7fffffff;
+    // a thread's best entry that is not taken yet: bit u of `taken`
+    uint32_t taken = 0;
+    auto best = [&]() {
+      float lv = -INFINITY; int lu = -1;
 #pragma unroll
-    for (int u = 0; u < XPT; ++u) better(lv, li, x[u], u * 1024 + (int)threadIdx.x);
-    TRACE_STAMP_AFTER(tr, 2, lv);
-    for (int r = 0; r < nk; ++r) {
-      float bv = lv; int bi = li;
-      block_argmax(bv, bi, shv, shi);
-      if (bi == li) {                                           // mine: take it out, find my next best
-        lv = -INFINITY; li = 0x7fffffff;
-#pragma unroll
-        for (int u = 0; u < XPT; ++u) {
-          const int j = u * 1024 + (int)threadIdx.x;
-          if (j == bi) x[u] = -INFINITY;
-          better(lv, li, x[u], j);
-        }
-        if (lv == -INFINITY) li = 0x7fffffff;
+      for (int u = 0; u < XPT; ++u) {
+        if (u * 1024 >= V) continue;
+        const bool win = !(taken >> u & 1) && (x[u] > lv || lu < 0);
+        lv = win ? x[u] : lv; lu = win ? u : lu;
       }
+      const int j = lu * 1024 + (int)threadIdx.x;
+      return lu >= 0 && j < V ? arg_key(lv, j) : 0ull;
+    };
+    unsigned long long mine = best();
+    TRACE_STAMP_AFTER(tr, 2, x[0]);
+    for (int r = 0; r < nk; ++r) {
+      const unsigned long long top = block_max_key(mine, shk);
+      const int bi = arg_index(top);
+      if (top == mine) { taken |= 1u << (bi >> 10); mine = best(); }   // mine: take it out, find my next best
 #pragma unroll
       for (int q = 0; q < EAGLE_MAX_CHILD; ++q) if (q == r) picked[q] = bi;
-      __syncthreads();                                          // shv / shi are reused by the next round
     }
   } else {
     // Larger vocabularies: one pass with a per-thread sorted top-nk list, then rounds over the lists' heads.
@@ -1456,8 +1472,7 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, int n_
       }
     }
     for (int r = 0; r < nk; ++r) {
-      float bv = tv[0]; int bi = ti[0];
-      block_argmax(bv, bi, shv, shi);
+      const int bi = arg_index(block_max_key(arg_key(tv[0], ti[0]), shk));
       if (bi == ti[0]) {
 #pragma unroll
         for (int q = 0; q + 1 < EAGLE_MAX_CHILD; ++q) { tv[q] = tv[q + 1]; ti[q] = ti[q + 1]; }
@@ -1465,7 +1480,6 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, int n_
       }
 #pragma unroll
       for (int q = 0; q < EAGLE_MAX_CHILD; ++q) if (q == r) picked[q] = bi;
-      __syncthreads();
     }
   }
   if (threadIdx.x == 0) {
@@ -1475,6 +1489,15 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, int n_
         tree_tok[seq * M + childs[q]] = picked[q];
         on_path[seq * M + childs[q]] = (hinted >= 0 && picked[q] == hinted);
       }
+  }
+  if (feat_src) {
+    float* dst = node_f + ((size_t)seq * M + v) * d;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = 4096 * i + 4 * (int)threadIdx.x;
+      if (k < d) *(f32x4*)(dst + k) = feat[i];
+    }
+    for (int k = 8192 + (int)threadIdx.x; k < d; k += 1024) dst[k] = feat_in[k];
   }
   TRACE_STAMP(tr, 3);
 }
@@ -1528,29 +1551,135 @@ __device__ inline int block_inverse_cdf(const float* p, int V, float u, double* 
   return *res;
 }
 
+// The same two for at most 32768 entries, which a block of 1024 threads holds in registers: thread t owns entries t, t + 1024, ...
+// (the order in which block_softmax adds them).  Through memory every pass over a row was 128 KB of one CU's fetches (32000 entries,
+// two sequences, T26: acceptance 293 -> 122 us a launch, a sampled token of a vanilla step 60 -> 20).
+constexpr int VPT = 32;
+__device__ inline void reg_softmax(const float* __restrict__ x, float (&p)[VPT], int V, float invT, float* sh) {
+  const int tid = threadIdx.x;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    p[u] = -INFINITY;
+    if (tid < V - u * 1024) p[u] = (x + u * 1024)[tid];          // (a scalar base: per-thread addresses would be kept, and spilled)
+  }
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    p[u] = tid < V - u * 1024 ? p[u] * invT : -INFINITY;
+    mx = fmaxf(mx, p[u]);
+  }
+  mx = block_max(mx, sh);
+  float sm = 0.f;
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const float e = tid < V - u * 1024 ? expf(p[u] - mx) : 0.f;
+    p[u] = e;
+    sm += e;
+    if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);           // (interleaved over all entries the temporaries spill)
+  }
+  sm = block_sum(sm, sh);
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    p[u] /= sm;
+    if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+}
+// As block_inverse_cdf; ps: 33 * 1024 floats of LDS, in which the entries are laid out in order (a gap after every 32: the threads
+// then read their runs without bank conflicts).  The prefix over the threads' sums is a scan per wave and then over the waves.
+__device__ inline int reg_inverse_cdf(const float (&p)[VPT], int V, float u, float* ps, double* sh_d /*>= 1025 + 16*/, int* res) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));                                  // (its LDS addresses are not worth registers before this point)
+  const int lane = tid & 63, w = tid >> 6;
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    const int j = i * 1024 + tid;
+    if (j < V) ps[j + (j >> 5)] = p[i];
+  }
+  if (tid == 0) *res = V - 1;
+  __syncthreads();
+  const int per = (V + 1023) / 1024, j0 = tid * per, j1 = min(V, j0 + per);
+  double s = 0.0;
+  for (int j = j0; j < j1; ++j) s += (double)ps[j + (j >> 5)];
+  double inc = s;
+  for (int o = 1; o < 64; o <<= 1) {
+    const double v = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += v;
+  }
+  double* wave_tot = sh_d + 1025;
+  if (lane == 63) wave_tot[w] = inc;
+  const double before = __shfl_up(inc, 1, 64);
+  __syncthreads();
+  double base = 0.0;
+  for (int i = 0; i < w; ++i) base += wave_tot[i];
+  sh_d[tid] = lane == 0 ? base : base + before;
+  if (tid == 1023) sh_d[1024] = base + inc;
+  __syncthreads();
+  const double target = (double)u * sh_d[1024];
+  double c = sh_d[tid];
+  const double nxt = sh_d[tid + 1];
+  if (j0 < j1 && c <= target && (target < nxt || tid == 1023 || j1 == V)) {
+    int found = -1, last_pos = -1;
+    for (int j = j0; j < j1; ++j) {
+      const float pj = ps[j + (j >> 5)];
+      if (pj > 0.f) last_pos = j;
+      c += (double)pj;
+      if (c > target) { found = j; break; }
+    }
+    if (found < 0) found = last_pos;            // rounding left the running sum just short of the target
+    if (found >= 0) atomicMin(res, found);
+  }
+  __syncthreads();
+  return *res;
+}
+constexpr size_t CDF_LDS = (size_t)33 * 1024 * 4;              // dynamic LDS of the sampling kernels for at most 32768 entries
+
 // Pick the next token of every sequence from logits[seq][V] (prefill's first token, vanilla decoding):
 // argmax when greedy, else one inverse-CDF draw from softmax(logits / T).  Also advances the sequence state.
+// Index of the largest of V values (lowest among equals) for a block of 1024 threads, 16 loads of a thread in flight.
+__device__ inline int row_argmax(const float* __restrict__ lg, int V, unsigned long long* shk) {
+  const int tid = threadIdx.x;
+  float bv = -INFINITY; int bi = 0x7fffffff;
+  for (int j0 = 0; j0 < V; j0 += 16 * 1024) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      v[u] = -INFINITY;
+      if (tid < V - j0 - u * 1024) v[u] = (lg + j0 + u * 1024)[tid];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (tid < V - j0 - u * 1024) better(bv, bi, v[u], j0 + u * 1024 + tid);
+  }
+  return arg_index(block_max_key(arg_key(bv, bi), shk));
+}
+
+template <bool BIGV>   // BIGV: more than 32768 vocabulary entries
 __global__ __launch_bounds__(1024) void k_choose(SeqState st, int seq0, const float* logits, int V, float temperature,
                                                  unsigned long long rng_seed, float* pbuf /*[seq][V]*/, int is_prefill,
                                                  int prefill_n, int max_pend) {
   __shared__ float shv[16];
-  __shared__ int shi[16];
-  __shared__ double sh_f[1025];
+  __shared__ unsigned long long shk[16];
+  __shared__ double sh_f[1025 + 16];
   __shared__ int res;
+  extern __shared__ __attribute__((aligned(16))) float ps[];
   const int seq = seq0 + blockIdx.x;
   const float* lg = logits + (size_t)seq * V;
   int tok;
   if (temperature <= 0.f) {
-    float bv = -INFINITY; int bi = 0x7fffffff;
-    for (int j = threadIdx.x; j < V; j += blockDim.x) better(bv, bi, lg[j], j);
-    block_argmax(bv, bi, shv, shi);
-    tok = bi;
+    tok = row_argmax(lg, V, shk);
   } else {
-    float* p = pbuf + (size_t)seq * V;
-    block_softmax(lg, p, V, 1.0f / temperature, shv);
     int step = is_prefill ? 0 : st.step_no[seq];
     float u = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_FINAL, (unsigned long long)step), (uint32_t)seq, 0, 0) * 5.9604644775390625e-8f;
-    tok = block_inverse_cdf(p, V, u, sh_f, &res);
+    if constexpr (BIGV) {
+      float* p = pbuf + (size_t)seq * V;
+      block_softmax(lg, p, V, 1.0f / temperature, shv);
+      tok = block_inverse_cdf(p, V, u, sh_f, &res);
+    } else {
+      float p[VPT];
+      reg_softmax(lg, p, V, 1.0f / temperature, shv);
+      tok = reg_inverse_cdf(p, V, u, ps, sh_f, &res);
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1574,24 +1703,23 @@ __global__ __launch_bounds__(1024) void k_choose(SeqState st, int seq0, const fl
 // arg-max token of every row of logits (lowest id among equals), one block per row: the greedy walk below visits up
 // to depth + 1 nodes one after the other, and scanning their rows there would run on a single CU
 __global__ __launch_bounds__(1024) void k_row_argmax(const float* __restrict__ L, int V, int* __restrict__ amax) {
-  __shared__ float shv[16];
-  __shared__ int shi[16];
-  const float* lg = L + (size_t)blockIdx.x * V;
-  float bv = -INFINITY; int bi = 0x7fffffff;
-  for (int j = threadIdx.x; j < V; j += blockDim.x) better(bv, bi, lg[j], j);
-  block_argmax(bv, bi, shv, shi);
+  __shared__ unsigned long long shk[16];
+  const int bi = row_argmax(L + (size_t)blockIdx.x * V, V, shk);
   if (threadIdx.x == 0) amax[blockIdx.x] = bi;
 }
 
+enum { ACCEPT_GREEDY, ACCEPT_SAMPLED, ACCEPT_SAMPLED_BIGV };   // BIGV: more than 32768 vocabulary entries
+template <int KIND>
 __global__ __launch_bounds__(1024) void k_accept(const TreeDev* tree, SeqState st, const float* L /*[seq][M][V]*/,
                                                  const float* draft_logits, const int* tree_tok, int V, float temperature,
                                                  unsigned long long rng_seed, float* pbuf, float* qbuf,
                                                  int* path_out /*[seq][D+1]*/, int* tok_out, int* len_out,
                                                  const int* __restrict__ amax /*[seq][M], greedy only*/) {
   __shared__ float shv[16];
-  __shared__ int shi[16];
-  __shared__ double sh_f[1025];
+  __shared__ double sh_f[1025 + 16];
   __shared__ int res, s_next;
+  __shared__ float s_pt, s_qt;
+  extern __shared__ __attribute__((aligned(16))) float ps[];
   const int seq = blockIdx.x, M = tree->M, D1 = tree->D + 1;
   int cur = 0, len = 1, bonus = 0;
   if (threadIdx.x == 0) path_out[seq * D1] = 0;
@@ -1599,7 +1727,7 @@ __global__ __launch_bounds__(1024) void k_accept(const TreeDev* tree, SeqState s
   while (true) {
     const float* lg = L + ((size_t)seq * M + cur) * V;
     const int nk = tree->nchild[cur];
-    if (temperature <= 0.f) {
+    if constexpr (KIND == ACCEPT_GREEDY) {
       const int bi = amax[seq * M + cur];
       if (threadIdx.x == 0) {
         s_next = -1;
@@ -1610,6 +1738,52 @@ __global__ __launch_bounds__(1024) void k_accept(const TreeDev* tree, SeqState s
       }
       __syncthreads();
       if (s_next < 0) { bonus = bi; break; }
+    } else if constexpr (KIND == ACCEPT_SAMPLED) {
+      // target and proposal of the node in registers (see reg_softmax); the same sums as below
+      const int tid = threadIdx.x;
+      const float invT = 1.0f / temperature;
+      float p[VPT], q[VPT];
+      reg_softmax(lg, p, V, invT, shv);
+      if (nk > 0) reg_softmax(draft_logits + ((size_t)seq * M + cur) * V, q, V, invT, shv);
+      if (tid == 0) s_next = -1;
+      for (int r = 0; r < nk; ++r) {
+        const int c = tree->child[cur][r];
+        const int t = __builtin_amdgcn_readfirstlane(tree_tok[seq * M + c]);
+        const float rr = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_ACCEPT, (unsigned long long)step), (uint32_t)seq, (uint32_t)c, 0) * 5.9604644775390625e-8f;
+        float sm = 0.f, qs = 0.f;
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+          if (u * 1024 >= V) continue;
+          if (tid == t - u * 1024) { s_pt = p[u]; s_qt = q[u]; }
+          sm += fmaxf(p[u] - q[u], 0.f);
+        }
+        __syncthreads();
+        if (rr * s_qt < s_pt) { if (tid == 0) s_next = c; break; }
+        // residual target, proposal without t
+        sm = block_sum(sm, shv);
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+          if (u * 1024 >= V) continue;
+          if (sm > 1e-20f) p[u] = fmaxf(p[u] - q[u], 0.f) / sm;
+          if (tid == t - u * 1024) q[u] = 0.f;
+          qs += q[u];
+          if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        qs = block_sum(qs, shv);
+        if (qs > 0.f)
+#pragma unroll
+          for (int u = 0; u < VPT; ++u) {
+            q[u] /= qs;
+            if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+        __syncthreads();                                        // (s_pt, s_qt and shv are written again)
+      }
+      __syncthreads();
+      if (s_next < 0) {
+        const float u = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_FINAL, (unsigned long long)step), (uint32_t)seq, (uint32_t)cur, 0) * 5.9604644775390625e-8f;
+        bonus = reg_inverse_cdf(p, V, u, ps, sh_f, &res);
+        break;
+      }
     } else {
       float* p = pbuf + (size_t)seq * V;
       float* q = qbuf + (size_t)seq * V;

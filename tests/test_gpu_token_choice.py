@@ -1,0 +1,92 @@
+"""Child selection and acceptance at the edges of their vocabulary ranges (a thread of the kernels owns every 1024th entry, at most 32 of
+them in registers): the fp32 oracle's own logits, and integer logits full of ties."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import paper_2401_15077_amd as pkg
+import synth
+from lockstep import check_prefill
+from oracle.eagle_oracle import Oracle
+from test_gpu_parity import TOL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("vocab", [64, 1000, 1024, 1025, 4099, 31999, 32767, 32768, 32769])
+@pytest.mark.parametrize("temperature", [0.0, 1.0])
+def test_selection_and_acceptance_on_oracle_logits(vocab, temperature):
+    s = replace(synth.SHAPES["tiny"], name=f"tiny-v{vocab}", n_layers=1, vocab=vocab)
+    par, rk = synth.TREES["T26"]
+    print(s.name, "temperature", temperature, flush=True)
+    eng = pkg.Eagle(s, par, rk, max_seq=128, temperature=temperature, seed=99)
+    eng.load_weights(synth.iter_weights(s, 41, synth.device_fmt(s)))
+    orc = Oracle(s, synth.make_weights(s, 41, synth.oracle_fmt(s)), par, rk, max_seq=128, temperature=temperature, seed=99, dtype=np.float32)
+    check_prefill(eng, orc, synth.prompt(41, 20, vocab), TOL["fp32"], margin_thr=1e-4)
+    for step in range(4):
+        eng.draft_tree()
+        orc.draft_tree()
+        raw = np.zeros((len(par), vocab), np.float32)
+        for v, lg in orc.node_logits.items():
+            raw[v] = lg
+        eng.set_buffer(pkg.BUF_DRAFT_LOGITS, raw)
+        for level in [-1] + list(range(1, orc.tree.D)):
+            eng.expand_level(level)
+        assert list(eng.get_buffer(pkg.BUF_TREE_TOKENS)) == orc.tok, f"step {step}: tree tokens differ"
+        eng.verify()
+        _, L = orc.verify()
+        eng.set_buffer(pkg.BUF_LOGITS, L.astype(np.float32))
+        out, ln, path = eng.accept()
+        r = orc.accept()
+        n = int(ln[0])
+        same = [int(v) for v in path[0][:n]] == r["path"] and [int(t) for t in out[0][:n]] == r["emitted"]
+        # the same numbers in the same precision: only sums of probabilities are taken in another order (1e-6 relative)
+        assert same or r["margin"] < 1e-5, f"step {step}: {path[0][:n]} {out[0][:n]} against {r['path']} {r['emitted']} (margin {r['margin']})"
+        if not same:
+            break
+        orc.commit(r["path"], r["bonus"])
+    eng.close()
+
+
+@pytest.mark.parametrize("vocab", [64, 1025, 32768, 33000])
+def test_ties_go_to_the_lowest_token(vocab):
+    s = replace(synth.SHAPES["tiny"], name=f"tiny-v{vocab}", n_layers=1, vocab=vocab)
+    par, rk = synth.TREES["T26"]
+    M = len(par)
+    eng = pkg.Eagle(s, par, rk, max_seq=128)
+    eng.load_weights(synth.iter_weights(s, 43, synth.device_fmt(s)))
+    rng = np.random.default_rng(vocab)
+    levels = rng.integers(-3, 3, (2 * M, vocab)).astype(np.float32)
+    levels[::3] = -np.inf                                        # rows with a handful of finite entries, zeros of both signs among them
+    for row in levels[::3]:
+        row[rng.choice(vocab, 9, replace=False)] = np.array([0.0, -0.0, 0.0, -0.0, -1.0, -1.0, 2.0, -np.inf, -5.0], np.float32)
+    children = [[v for v in range(1, M) if par[v] == p] for p in range(M)]
+    for start in range(2):
+        eng.reset()
+        eng.prefill(0, synth.prompt(43 + start, 12, vocab))
+        eng.draft_tree()
+        draft, target = np.roll(levels[:M], start, 0), np.roll(levels[M:], start, 0)
+        eng.set_buffer(pkg.BUF_DRAFT_LOGITS, draft)
+        for level in [-1] + list(range(1, eng.D)):
+            eng.expand_level(level)
+        tok = eng.get_buffer(pkg.BUF_TREE_TOKENS)
+        for p in range(M):
+            want = np.argsort(-draft[p], kind="stable")[:len(children[p])]
+            got = [int(tok[v]) for v in sorted(children[p], key=lambda v: rk[v])]
+            assert got == list(want), (p, got, list(want))
+        eng.verify()
+        eng.set_buffer(pkg.BUF_LOGITS, target)
+        out, ln, path = eng.accept()
+        cur, walk, emitted = 0, [0], []
+        while True:
+            best = int(np.argmax(target[cur]))
+            nxt = [v for v in children[cur] if int(tok[v]) == best]
+            emitted.append(best)
+            if not nxt:
+                break
+            cur = nxt[0]
+            walk.append(cur)
+        n = int(ln[0])
+        assert [int(v) for v in path[0][:n]] == walk and [int(t) for t in out[0][:n]] == emitted
+    eng.close()
