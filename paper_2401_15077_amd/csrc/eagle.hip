@@ -1088,7 +1088,6 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   }
   // wide matrices of the bf16 configuration: whole-K work-groups with the epilogue in place (no partials) ...
   const int fk_grid = std::max(c->n_cu, (w.NRB + 3) / 4);
-  const bool fits_rsrc = (size_t)w.NRB * w.KS * 1024 < ((size_t)1 << 31);
   // (not for the residual epilogue, although the kernel has it: O and down at d = 8192 have exactly one row block per
   // CU, and a work-group that owns one row block over all of K fetches twice as many activation bytes as weight
   // bytes -- measured there: down 109.7 us whole-K against 85.8 us split-K, O 37.5 against 34.8)
@@ -1121,7 +1120,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     // QKV: split by half row blocks where that lowers the largest share (3 halves instead of 2 blocks at d = 4096);
     // a run of u halves touches at most u/2 + 1 blocks
     const int umax = (2 * w.NRB + grid - 1) / grid;
-    const bool half = g.epi == EPI_QKV && umax < 2 * nrmax && umax / 2 + 1 <= 2 && fits_rsrc;
+    const bool half = g.epi == EPI_QKV && umax < 2 * nrmax && umax / 2 + 1 <= 2;
     if (half) e = launch_fk<2, true>(c, bytes, g, grid);
     else e = nrmax <= 2 ? launch_fk<2>(c, bytes, g, grid) : nrmax == 3 ? launch_fk<3>(c, bytes, g, grid) : launch_fk<4>(c, bytes, g, grid);
   } else if (c->f32) {

@@ -42,6 +42,7 @@ __device__ inline uint32_t pt_quad_bytes(int s, int Npad, int n4 /*multiple of 4
 // over the lanes' distinct offsets.
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
 
+constexpr uint32_t OUT_OF_RANGE = 0x80000000u;   // byte offset beyond every buffer resource: a load returns zeros without a memory access
 struct RowScale {            // 1/rms of the rows that produced the GEMM input; groups == 0 -> 1
   const float* ssq;          // [groups <= 256][32] partial sums of squares
   int groups;
@@ -705,85 +706,88 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
 // The activation fragments come through buffer loads: a lane whose row (lane % 32) is not a live row of the pass gets
 // an offset beyond the buffer, which the hardware answers with zeros WITHOUT touching memory -- a pass of M rows moves
 // M/32 of the fragment bytes (26/32 in a 26-node verify, 1/8 and less in the head's passes).
-// Row-masked weight loads (half-block work split): the tiles of row block j come through a buffer resource over the
-// whole matrix; vo[j] is the lane's byte offset inside a tile, or an out-of-range offset for lanes whose weight row
-// is not this work-group's (zeros, no memory access); so[j] the byte offset of the block's first tile.
-struct FkHalf { __amdgpu_buffer_rsrc_t rs; uint32_t vo[4]; uint32_t so[4]; };
+// The weights come through buffer loads as well: a resource per plane over the work-group's row blocks, tile (j, k) at (j * KS + k) KiB,
+// vo[j] the lane's byte offset inside a tile of block j -- out of range for lanes whose weight row is not this work-group's (half
+// blocks).
+template <int NWP>
+struct FkWeights { __amdgpu_buffer_rsrc_t rs[NWP]; uint32_t vo[4]; };
+template <int NWP>
+__device__ __forceinline__ FkWeights<NWP> fk_weights(const bf16_t* W, size_t wps, int rb0, int nr, int KS, int lane, int row_lo = 0, int row_hi = 32) {
+  FkWeights<NWP> f;
+#pragma unroll
+  for (int p = 0; p < NWP; ++p) f.rs[p] = __builtin_amdgcn_make_buffer_rsrc((void*)(W + p * wps + (size_t)rb0 * KS * 512), 0, nr * KS * 1024, 0x00020000);
+  const int row = lane & 31;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) f.vo[j] = j < nr && row >= (j == 0 ? row_lo : 0) && row < (j == nr - 1 ? row_hi : 32) ? (uint32_t)lane * 16u : OUT_OF_RANGE;
+  return f;
+}
 
-template <int NWP, int NXP, int NR, int DEPTH, bool WB = false>
-__device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS, int M, int kb, int ke, const u32x4* const* wp,
-                                          size_t wps, f32x16* acc, int lane, const FkHalf* hw = nullptr) {
-  static_assert(!WB || NWP == 1, "row-masked weight loads exist for one weight plane only");
+template <int NWP, int NXP, int NR, int DEPTH>
+__device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS, int M, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
   constexpr int PMAX = NWP > NXP ? NWP : NXP;
   if (ke <= kb) return;
-  const int klast = ke - 1;
   u32x4 ta[DEPTH][NR][NWP], tb[DEPTH][NXP];
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, NXP * KS * 1024, 0x00020000);
-  const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : 0x80000000u;   // dead rows: out of range
-#define FK_XLOAD(q, kk) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane, (uint32_t)(((q) * KS + (kk)) * 1024), 0))
-  // Non-temporal: a weight byte is used once per pass and a pass's weights exceed every cache, so keeping them out leaves the L2s
+  const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : OUT_OF_RANGE;  // dead rows
+  // Weights non-temporal: a weight byte is used once per pass and a pass's weights exceed every cache, so keeping them out leaves the L2s
   // to the activations (7B, LLaMA shapes, us before / after: gate/up 36.5 / 34.5, LM head 49.0 / 45.0, QKV 25.4 / 23.9; a bare
   // read of 2 GB runs at 6.9 TB/s with the hint and 6.25 without).  The 4-bit and fp32 streams keep plain loads: their head fits
   // the 256 MB memory-side cache, from which the drafting passes then re-read it (4-bit LM head 32.7 us plain, 35.6 with the hint).
-  auto wload = [&](int j, int p, int kk) -> u32x4 {
-    if constexpr (WB) return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(hw->rs, hw->vo[j], hw->so[j] + (uint32_t)kk * 1024u, 2));
-    else return __builtin_nontemporal_load((const u32x4*)((const bf16_t*)(wp[j] + (size_t)kk * 64) + p * wps));
-  };
-#pragma unroll
-  for (int dd = 0; dd < DEPTH; ++dd) {
-    const int kk = min(kb + dd, klast);
+  auto load = [&](int dd, int k) {
 #pragma unroll
     for (int j = 0; j < NR; ++j)
 #pragma unroll
-      for (int p = 0; p < NWP; ++p) ta[dd][j][p] = wload(j, p, kk);
+      for (int p = 0; p < NWP; ++p)
+        ta[dd][j][p] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(fw.rs[p], fw.vo[j], (uint32_t)(j * KS + k) * 1024u, NWP == 1 ? 2 : 0));
 #pragma unroll
-    for (int q = 0; q < NXP; ++q) tb[dd][q] = FK_XLOAD(q, kk);
-  }
+    for (int q = 0; q < NXP; ++q)
+      tb[dd][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane, (uint32_t)(q * KS + k) * 1024u, 0));
+  };
+  auto mul = [&](int dd) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int p = 0; p < NWP; ++p)
+#pragma unroll
+        for (int q = 0; q < NXP; ++q)
+          if (p + q < PMAX)
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ta[dd][j][p]), __builtin_bit_cast(bf16x8, tb[dd][q]), acc[j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int dd = 0; dd < DEPTH; ++dd) load(dd, min(kb + dd, ke - 1));
   int k = kb;
-  for (; k + DEPTH < ke; k += DEPTH) {
+  // A round that has all of the next one to request; then the rounds that do not.  (With the k-steps behind the end clamped to the
+  // last one, a wave's 32 came as 35 or 36 at K = 4096 and O's 8 as 12, on the L2 -> CU path that binds these kernels; requested out
+  // of range they move nothing and still cost more than a branch.  26 rows at 7B, us clamped / out of range / branch: QKV 25.3 /
+  // 25.9 / 24.7, gate/up 35.4 / 36.0 / 34.7, O 13.6 / 13.3 / 12.5, down 24.0 / 23.5 / 23.5.  Four row blocks, whose depth divides
+  // the usual K: LM head 44.8 / 45.9 / 45.5, so they keep one loop.)
+  constexpr bool EXACT = NR < 4;
+  for (; k + (EXACT ? 2 * DEPTH - 1 : DEPTH) < ke; k += DEPTH) {
 #pragma unroll
     for (int dd = 0; dd < DEPTH; ++dd) {
-#pragma unroll
-      for (int j = 0; j < NR; ++j)
-#pragma unroll
-        for (int p = 0; p < NWP; ++p)
-#pragma unroll
-          for (int q = 0; q < NXP; ++q)
-            if (p + q < PMAX)
-              acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ta[dd][j][p]),
-                                                                __builtin_bit_cast(bf16x8, tb[dd][q]), acc[j], 0, 0, 0);
-      const int kn = min(k + dd + DEPTH, klast);
-#pragma unroll
-      for (int j = 0; j < NR; ++j)
-#pragma unroll
-        for (int p = 0; p < NWP; ++p) ta[dd][j][p] = wload(j, p, kn);
-#pragma unroll
-      for (int q = 0; q < NXP; ++q) tb[dd][q] = FK_XLOAD(q, kn);
+      mul(dd);
+      load(dd, EXACT ? k + dd + DEPTH : min(k + dd + DEPTH, ke - 1));
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  if (EXACT && k + DEPTH < ke) {
 #pragma unroll
-  for (int dd = 0; dd < DEPTH; ++dd) {
-    if (k + dd < ke) {
-#pragma unroll
-      for (int j = 0; j < NR; ++j)
-#pragma unroll
-        for (int p = 0; p < NWP; ++p)
-#pragma unroll
-          for (int q = 0; q < NXP; ++q)
-            if (p + q < PMAX)
-              acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ta[dd][j][p]),
-                                                                __builtin_bit_cast(bf16x8, tb[dd][q]), acc[j], 0, 0, 0);
+    for (int dd = 0; dd < DEPTH; ++dd) {
+      mul(dd);
+      if (k + dd + DEPTH < ke) load(dd, k + dd + DEPTH);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    k += DEPTH;
   }
+#pragma unroll
+  for (int dd = 0; dd < DEPTH; ++dd)
+    if (k + dd < ke) mul(dd);
 }
-#undef FK_XLOAD
-template <int NWP, int NXP, int NR, bool WB = false>
-__device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, int M, int kb, int ke, const u32x4* const* wp,
-                                                   size_t wps, f32x16* acc, int lane, const FkHalf* hw = nullptr) {
+template <int NWP, int NXP, int NR>
+__device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, int M, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
   constexpr int DEPTH = NWP == 1 ? (NR == 1 ? 8 : NR == 2 ? 6 : NR == 3 ? 5 : 4) : NR == 1 ? 4 : 2;   // ~24 KiB in flight per wave; deeper measured the same
-  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH, WB>(XF, KS, M, kb, ke, wp, wps, acc, lane, hw);
-  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1, WB>(nr, XF, KS, M, kb, ke, wp, wps, acc, lane, hw);
+  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, M, kb, ke, fw, acc, lane);
+  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, M, kb, ke, fw, acc, lane);
 }
 
 // ---- the same stream over 4-bit weights (see k_pack_weight_q4 for the layout) -------------------------------------------
@@ -794,25 +798,31 @@ __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int
 // Activation fragments are streamed from L2 as in fk_stream, one group (8 k-steps) ahead; the next group's codes are
 // requested as soon as a super-tile's registers are free.
 template <int NXP, int NR>
-__device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs /*codes from block 0 on*/,
                                              const u32x4* const* sq /*scales of (block j, group 0), this lane's half*/, int NG,
                                              f32x16* acc, int lane) {
   if (ge <= gb) return;
-  const int glast = ge - 1;
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, NXP * KS * 1024, 0x00020000);
-  const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : 0x80000000u;   // dead rows: out of range -> zeros
-#define Q4_XLOAD(q, kk) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane, (uint32_t)(((q) * KS + (kk)) * 1024), 0))
+  const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : OUT_OF_RANGE;   // dead rows: zeros
+#define Q4_XLOAD(q, kk, past) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane | (past), (uint32_t)(((q) * KS + (kk)) * 1024), 0))
+#define Q4_WLOAD(j, T, past) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrs, (uint32_t)lane * 16u | (past), (uint32_t)((j) * (KS / 4) + (T)) * 1024u, 0))
   u32x4 a4[2][NR], tb[8][NXP];                                 // codes of a group; activation fragments one group ahead
   const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
 #pragma unroll
   for (int st = 0; st < 2; ++st)
 #pragma unroll
-    for (int j = 0; j < NR; ++j) a4[st][j] = wq[j][(size_t)(2 * gb + st) * 64];
+    for (int j = 0; j < NR; ++j) a4[st][j] = Q4_WLOAD(j, 2 * gb + st, 0u);
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int q = 0; q < NXP; ++q) tb[i][q] = Q4_XLOAD(q, 8 * gb + i);
-  for (int g = gb; g < ge; ++g) {
+    for (int q = 0; q < NXP; ++q) tb[i][q] = Q4_XLOAD(q, 8 * gb + i, 0u);
+  // The last group, a copy of the loop's body, requests nothing: clamped to itself it fetched its activations and codes twice, one
+  // group in four at K = 4096 and the only one in O's slices.  (Three row blocks, for which a second body spills, request out of range.)
+  constexpr bool COPY = NR < 3;
+#pragma unroll
+  for (int last = COPY ? 0 : 1; last < 2; ++last)
+  for (int g = COPY && last ? ge - 1 : gb; g < (last ? ge : ge - 1); ++g) {
+    const uint32_t past = COPY || g + 1 < ge ? 0u : OUT_OF_RANGE;
     f32x16 part[NR], sx;
 #pragma unroll
     for (int r = 0; r < 16; ++r) sx[r] = 0.f;
@@ -823,7 +833,7 @@ __device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* _
     u32x4 sraw[NR][2];                                          // this group's scales: needed after its 8 k-steps
 #pragma unroll
     for (int j = 0; j < NR; ++j) { sraw[j][0] = sq[j][(size_t)g * 4]; sraw[j][1] = sq[j][(size_t)g * 4 + 1]; }
-    const int gn = min(g + 1, glast);
+    const int gn = g + 1;
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
 #pragma unroll
@@ -862,11 +872,11 @@ __device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* _
         // use a slot, refill that slot: the same k-step of the next group
         (void)kk;
 #pragma unroll
-        for (int q = 0; q < NXP; ++q) tb[4 * st + ks][q] = Q4_XLOAD(q, 8 * gn + 4 * st + ks);
+        for (int q = 0; q < NXP; ++q) if (!(COPY && last)) tb[4 * st + ks][q] = Q4_XLOAD(q, 8 * gn + 4 * st + ks, past);
       }
       // the super-tile's code registers are free: request the next group's
 #pragma unroll
-      for (int j = 0; j < NR; ++j) a4[st][j] = wq[j][(size_t)(2 * gn + st) * 64];
+      for (int j = 0; j < NR; ++j) if (!(COPY && last)) a4[st][j] = Q4_WLOAD(j, 2 * gn + st, past);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -880,12 +890,17 @@ __device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* _
     }
   }
 #undef Q4_XLOAD
+#undef Q4_WLOAD
 }
 template <int NXP, int NR>
-__device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt, const bf16_t* XF, int KS, int M, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt, const bf16_t* XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs,
                                                       const u32x4* const* sq, int NG, f32x16* acc, int lane) {
-  if (nr == NR) fk_stream_q4<NXP, NR>(fmt, XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
-  else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wq, sq, NG, acc, lane);
+  if (nr == NR) fk_stream_q4<NXP, NR>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane);
+  else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane);
+}
+// The codes of nr row blocks from rb0 on: KS / 4 tiles of 1 KiB a block.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t q4_codes(const bf16_t* W, int rb0, int nr, int KS) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)W + (size_t)rb0 * KS * 256), 0, nr * KS * 256, 0x00020000);
 }
 
 // The waves' accumulators parked in LDS as red[w][j][i][lane], 16 bytes each = registers 4i..4i+3 (MFMA layout: rows 8i + 4*(lane/32)
@@ -935,20 +950,6 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   }
   const int nr = rb1 - rb0;                                     // <= NRMAX (host)
   const int kb = (unsigned)w * (unsigned)g.KS / 8u, ke = (unsigned)(w + 1) * (unsigned)g.KS / 8u;
-  const u32x4* wp[NRMAX];
-#pragma unroll
-  for (int j = 0; j < NRMAX; ++j) wp[j] = (const u32x4*)(g.W + (size_t)min(rb0 + j, g.NRB - 1) * g.KS * 512) + lane;
-  FkHalf hw;
-  if constexpr (HALF) {
-    hw.rs = __builtin_amdgcn_make_buffer_rsrc((void*)g.W, 0, (int)((unsigned)g.NRB * (unsigned)g.KS * 1024u), 0x00020000);
-    const int row = lane & 31;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bool mine = j < nr && row >= (j == 0 ? row_lo : 0) && row < (j == nr - 1 ? row_hi : 32);
-      hw.vo[j] = mine ? (uint32_t)lane * 16u : 0x80000000u;
-      hw.so[j] = (uint32_t)min(rb0 + j, g.NRB - 1) * (uint32_t)g.KS * 1024u;
-    }
-  }
   f32x16 acc[NRMAX];
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
@@ -957,18 +958,13 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   if constexpr (Q4) {
     // K is split over the waves by groups of 128; pointers to the codes / scales of each row block
     const int gb = (unsigned)w * (unsigned)g.NG / 8u, ge = (unsigned)(w + 1) * (unsigned)g.NG / 8u;
-    const u32x4* wq[NRMAX];
     const u32x4* sq[NRMAX];
 #pragma unroll
-    for (int j = 0; j < NRMAX; ++j) {
-      const size_t rb = (size_t)min(rb0 + j, g.NRB - 1);
-      wq[j] = (const u32x4*)g.W + rb * (size_t)(g.KS / 4) * 64 + lane;
-      sq[j] = (const u32x4*)g.SC + rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
-    }
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
+    for (int j = 0; j < NRMAX; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(rb0 + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
+    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, rb0, nr, g.KS), sq, g.NG, acc, lane);
     if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
-  fk_stream_dispatch<NWP, NXP, NRMAX, HALF>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane, &hw);
+  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane, row_lo, row_hi), acc, lane);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
   // residual epilogue: what the first item of a thread adds and multiplies, requested before the sums
   f32x4 rh = {0.f, 0.f, 0.f, 0.f}, rbias = rh, rgain = rh;
@@ -1112,9 +1108,6 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   const int nr = rb1 - rb0;                                     // <= NRMAX (host)
   const int ks0 = (unsigned)s * uKS / uS, ks1 = (unsigned)(s + 1) * uKS / uS, kt = ks1 - ks0;
   const int kb = ks0 + (unsigned)w * (unsigned)kt / 8u, ke = ks0 + (unsigned)(w + 1) * (unsigned)kt / 8u;
-  const u32x4* wp[NRMAX];
-#pragma unroll
-  for (int j = 0; j < NRMAX; ++j) wp[j] = (const u32x4*)(g.W + (size_t)min(rb0 + j, g.NRB - 1) * g.KS * 512) + lane;
   f32x16 acc[NRMAX];
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
@@ -1124,18 +1117,13 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
     const unsigned uNG = g.NG;
     const int G0 = (unsigned)s * uNG / uS, G1 = (unsigned)(s + 1) * uNG / uS, gt = G1 - G0;
     const int gb = G0 + (unsigned)w * (unsigned)gt / 8u, ge = G0 + (unsigned)(w + 1) * (unsigned)gt / 8u;
-    const u32x4* wq[NRMAX];
     const u32x4* sq[NRMAX];
 #pragma unroll
-    for (int j = 0; j < NRMAX; ++j) {
-      const size_t rb = (size_t)min(rb0 + j, g.NRB - 1);
-      wq[j] = (const u32x4*)g.W + rb * (size_t)(g.KS / 4) * 64 + lane;
-      sq[j] = (const u32x4*)g.SC + rb * (size_t)g.NG * 4 + 2 * (lane >> 5);
-    }
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, wq, sq, g.NG, acc, lane);
+    for (int j = 0; j < NRMAX; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(rb0 + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
+    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, rb0, nr, g.KS), sq, g.NG, acc, lane);
     if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
-  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, wp, g.wps, acc, lane);
+  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane), acc, lane);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
