@@ -825,6 +825,16 @@ __device__ inline void xf_store8(bf16_t* XF, int m, int k8, int MT, int KS, int 
   }
 }
 
+// Row of a work-group in kernels that make one row of a GEMM input each.  A 128-byte line of that input holds 16 bytes of eight
+// rows (xf_index), and work-groups go to the eight XCDs in turn: with row = work-group number every line was written in eight pieces
+// by eight L2s.  Here eight neighbouring rows are the work-groups of one XCD, whose L2 puts the line together; the rows behind the
+// last whole block of 64 are taken as they come, so passes of a few rows still spread over the XCDs.  k_rows_to_xf, 1024 rows of 4096:
+// 20.3 -> 10.9 us; k_resnorm, 1024 rows of 5120: 33 -> 27, 2011 rows of 8192: 84 -> 66.
+__device__ inline int xcd_row() {
+  const int b = blockIdx.x;
+  return b < ((int)gridDim.x & ~63) ? (b & ~63) | (b & 7) << 3 | (b >> 3 & 7) : b;
+}
+
 // Input of the head's FC layer: concat(feature, embedding of the token one step ahead)  (Sec. 3.1).
 //   pending pass : feature = target feature kept at the last commit, token = committed token at pos+1
 //   level pass   : feature = the head's output at the node's parent, token = the node's drafted token
@@ -834,7 +844,7 @@ __global__ __launch_bounds__(256) void k_fc_input(Pass pass, const TreeDev* tree
                                                   const float* pend_f /*[seq][D+1][d]*/, const float* node_f /*[seq][M][d]*/,
                                                   const float* chunk_f /*[chunk][d]*/, const EmbT* __restrict__ embed,
                                                   bf16_t* XF, int d, int vocab, int MT, int nplanes, KVCache kv, RowFact* facts) {
-  int r = blockIdx.x;
+  const int r = xcd_row();
   RowInfo ri = row_info(pass, tree, st, r);
   if (blockIdx.y == 0 && threadIdx.x == 0) facts[r] = row_fact(pass, tree, ri, kv);
   const int KS = 2 * d / 16;
@@ -886,7 +896,7 @@ __global__ __launch_bounds__(RESNORM_THREADS) void k_resnorm(const float* h_in, 
   __shared__ float sh[16];
   __shared__ float pick_w[4];                    // MOE: weight and gathered row of each expert of this row, ascending
   __shared__ int pick_s[4], n_pick;
-  const int r = blockIdx.x;
+  const int r = xcd_row();
   if constexpr (MOE) {
     if (threadIdx.x < 64) {                      // one wave looks at (at most 64) experts
       const int e = threadIdx.x;
@@ -981,7 +991,7 @@ __global__ __launch_bounds__(256) void k_resnorm_fixed(const float* h_in, const 
                                                  const float* bias, float* h_out, const float* gain, float eps,
                                                  bf16_t* XF, int MT, int nplanes, float* xout, int d) {
   __shared__ float sh[16];
-  int r = blockIdx.x;
+  const int r = xcd_row();
   float ss = 0.f;
   // each thread owns chunks of 8 consecutive k; the first four chunks (rows of up to 8192 columns) stay in registers
   // for the second phase, further ones are read back from h_out
@@ -1181,7 +1191,7 @@ __global__ __launch_bounds__(256) void k_store_rows(Pass pass, const TreeDev* tr
 // ============================================================================ training loss of the head (Sec. 3.2)
 // Rows of fp32 features -> rows [row0, row0 + rows) of a GEMM input of MT 32-row tiles (XF layout).  Grid (rows, parts).
 __global__ __launch_bounds__(256) void k_rows_to_xf(const float* __restrict__ src, int row0, bf16_t* XF, int MT, int nplanes, int d) {
-  const int r = blockIdx.x;
+  const int r = xcd_row();
   for (int k8 = (blockIdx.y * blockDim.x + threadIdx.x) * 8; k8 < d; k8 += gridDim.y * blockDim.x * 8) {
     float x[8];
     const f32x4 a = *(const f32x4*)(src + (size_t)r * d + k8), b = *(const f32x4*)(src + (size_t)r * d + k8 + 4);
@@ -1198,88 +1208,121 @@ __global__ __launch_bounds__(256) void k_rows_to_xf(const float* __restrict__ sr
 // row_loss[r] = (sum of the row's smooth-L1 terms, the row's cross entropy); means are taken by the caller.
 // NCH > 0: a thread keeps its NCH chunks of 8 logits of both rows in registers (V <= 8192 * NCH), so the logits are
 // read once; NCH = 0: any V, three passes over the logits.
+// Bound by what one work-group has in flight (one of 1024 threads fits a CU): the features, and the first partial of every chunk, are
+// requested together before anything is added, the reductions of a phase share two barriers, and rows go to XCDs as xcd_row says.
+// 1024 rows of 32000: 193 us with two loads in flight a thread, now 127 (393 MB read and written, 3.1 TB/s); 300 rows: 93, now 64.
 template <int NCH>
 __global__ __launch_bounds__(1024) void k_head_loss_row(const float* __restrict__ Z, int S, int Mpad, int Npad, int zh_row0, int V,
                                                         const float* __restrict__ f, const float* __restrict__ fhat, int d,
                                                         float cls_scale, float reg_scale, bf16_t* DZ, int MT, int nplanes,
                                                         float* grad /*[rows][d] or null*/, float* row_loss /*[rows][2]*/) {
-  __shared__ float sh[16];
-  const int r = blockIdx.x;
-  auto load8 = [&](int row, int v8, float* x) {
-    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < S; ++s) {
-      const float* src = Z + ((size_t)s * Mpad + row) * Npad + v8;
-      const f32x4 a1 = *(const f32x4*)src, b1 = *(const f32x4*)(src + 4);
-      a += a1; b += b1;
+  __shared__ float sh[4 * 16];
+  const int r = xcd_row(), tid = threadIdx.x;
+  f += (size_t)r * d; fhat += (size_t)r * d;
+  if (grad) grad += (size_t)r * d;
+  const float* zrow = Z + (size_t)r * Npad;
+  const float* hrow = Z + (size_t)(zh_row0 + r) * Npad;
+  struct Eight { f32x4 lo, hi; };
+  auto at = [](const Eight& e, int t) { return t < 4 ? e.lo[t] : e.hi[t - 4]; };
+  auto first8 = [&](const float* row, int v8) { return Eight{*(const f32x4*)(row + v8), *(const f32x4*)(row + v8 + 4)}; };
+  auto more8 = [&](const float* row, int v8, Eight& e) {            // the other partials, in split order
+    for (int s = 1; s < S; ++s) {
+      const float* src = row + (size_t)s * Mpad * Npad + v8;
+      e.lo += *(const f32x4*)src; e.hi += *(const f32x4*)(src + 4);
     }
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
   };
+  auto load8 = [&](const float* row, int v8) { Eight e = first8(row, v8); more8(row, v8, e); return e; };
+  // one reduction over the block for up to four values: waves' results in sh[value][wave], combined in wave order
+  auto to_sh = [&](int i, float v) { if ((tid & 63) == 0) sh[i * 16 + (tid >> 6)] = v; };
+  auto sum16 = [&](int i) { float t = 0.f; for (int w = 0; w < 16; ++w) t += sh[i * 16 + w]; return t; };
+  auto max16 = [&](int i) { float t = sh[i * 16]; for (int w = 1; w < 16; ++w) t = fmaxf(t, sh[i * 16 + w]); return t; };
+
+  const int k0 = min(4 * tid, d - 4);                               // this thread's first four features
+  typedef f32x4 __attribute__((aligned(4))) caller4;                // the caller's rows may start at any float
+  const f32x4 f0 = *(const caller4*)(f + k0), p0 = *(const caller4*)(fhat + k0);
   constexpr int NR = NCH > 0 ? NCH : 1;
-  float zr[NR][8], hr[NR][8];
+  Eight zr[NR], hr[NR];
   float mz = -INFINITY, mh = -INFINITY;
+  auto max8 = [&](const Eight& z, const Eight& h) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) { mz = fmaxf(mz, at(z, t)); mh = fmaxf(mh, at(h, t)); }
+  };
+  if constexpr (NCH > 0) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {                                 // (behind the row's end: its last chunk again, not used)
+      const int v8 = min((c * 1024 + tid) * 8, V - 8);
+      zr[c] = first8(zrow, v8); hr[c] = first8(hrow, v8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  float reg = 0.f;
+  auto reg4 = [&](int k, f32x4 a, f32x4 b) {
+    f32x4 g;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float x = b[t] - a[t], ax = fabsf(x);
+      reg += ax < 1.0f ? 0.5f * x * x : ax - 0.5f;
+      g[t] = fminf(fmaxf(x, -1.0f), 1.0f) * reg_scale;
+    }
+    if (grad) *(caller4*)(grad + k) = g;
+  };
+  if (4 * tid < d) reg4(4 * tid, f0, p0);
+  for (int k = 4 * (tid + 1024); k < d; k += 4096) reg4(k, *(const caller4*)(f + k), *(const caller4*)(fhat + k));
   if constexpr (NCH > 0) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int v8 = (c * 1024 + (int)threadIdx.x) * 8;
-      if (v8 < V) {
-        load8(r, v8, zr[c]); load8(zh_row0 + r, v8, hr[c]);
-#pragma unroll
-        for (int t = 0; t < 8; ++t) { mz = fmaxf(mz, zr[c][t]); mh = fmaxf(mh, hr[c][t]); }
-      }
+      const int v8 = (c * 1024 + tid) * 8;
+      if (v8 < V) { more8(zrow, v8, zr[c]); more8(hrow, v8, hr[c]); max8(zr[c], hr[c]); }
     }
   } else {
-    for (int v8 = threadIdx.x * 8; v8 < V; v8 += blockDim.x * 8) {
-      load8(r, v8, zr[0]); load8(zh_row0 + r, v8, hr[0]);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) { mz = fmaxf(mz, zr[0][t]); mh = fmaxf(mh, hr[0][t]); }
-    }
+    for (int v8 = tid * 8; v8 < V; v8 += 8192) max8(load8(zrow, v8), load8(hrow, v8));
   }
-  mz = block_max(mz, sh);
-  mh = block_max(mh, sh);
+  to_sh(0, wave_max(mz)); to_sh(1, wave_max(mh));
+  __syncthreads();
+  mz = max16(0); mh = max16(1);
+  __syncthreads();
   float sz = 0.f, shh = 0.f, dot = 0.f;
-  auto sums8 = [&](const float* z, const float* zh) {
+  auto sums8 = [&](Eight& z, Eight& zh) {                           // the logits become exp(z - max) for the gradient
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      const float e = __expf(z[t] - mz);
-      sz += e; shh += __expf(zh[t] - mh); dot += e * (zh[t] - mh);
+      const float h = at(zh, t) - mh, e = __expf(at(z, t) - mz), eh = __expf(h);
+      sz += e; shh += eh; dot += e * h;
+      if (t < 4) { z.lo[t] = e; zh.lo[t] = eh; } else { z.hi[t - 4] = e; zh.hi[t - 4] = eh; }
     }
   };
   if constexpr (NCH > 0) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-      if ((c * 1024 + (int)threadIdx.x) * 8 < V) sums8(zr[c], hr[c]);
+      if ((c * 1024 + tid) * 8 < V) sums8(zr[c], hr[c]);
   } else {
-    for (int v8 = threadIdx.x * 8; v8 < V; v8 += blockDim.x * 8) { load8(r, v8, zr[0]); load8(zh_row0 + r, v8, hr[0]); sums8(zr[0], hr[0]); }
+    for (int v8 = tid * 8; v8 < V; v8 += 8192) { zr[0] = load8(zrow, v8); hr[0] = load8(hrow, v8); sums8(zr[0], hr[0]); }
   }
-  sz = block_sum(sz, sh);
-  shh = block_sum(shh, sh);
-  dot = block_sum(dot, sh);
-  const float cls = logf(shh) - dot / sz;                          // lse(zh) - sum_v p_v zh_v, both taken relative to mh
+  to_sh(0, wave_sum(sz)); to_sh(1, wave_sum(shh)); to_sh(2, wave_sum(dot)); to_sh(3, wave_sum(reg));
+  __syncthreads();
+  sz = sum16(0); shh = sum16(1); dot = sum16(2);
   const float isz = 1.0f / sz, ish = 1.0f / shh;
-  auto store8 = [&](int v8, const float* z, const float* zh) {
+  auto store8 = [&](int v8, const Eight& e, const Eight& eh) {
     float x[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) x[t] = (__expf(zh[t] - mh) * ish - __expf(z[t] - mz) * isz) * cls_scale;
+    for (int t = 0; t < 8; ++t) x[t] = (at(eh, t) * ish - at(e, t) * isz) * cls_scale;
     xf_store8(DZ, r, v8, MT, V / 16, nplanes, x);
   };
   if constexpr (NCH > 0) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int v8 = (c * 1024 + (int)threadIdx.x) * 8;
+      const int v8 = (c * 1024 + tid) * 8;
       if (v8 < V) store8(v8, zr[c], hr[c]);
     }
   } else {
-    for (int v8 = threadIdx.x * 8; v8 < V; v8 += blockDim.x * 8) { load8(r, v8, zr[0]); load8(zh_row0 + r, v8, hr[0]); store8(v8, zr[0], hr[0]); }
+    for (int v8 = tid * 8; v8 < V; v8 += 8192) {
+      Eight e = load8(zrow, v8), eh = load8(hrow, v8);
+      e.lo -= mz; e.hi -= mz; eh.lo -= mh; eh.hi -= mh;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) { e.lo[t] = __expf(e.lo[t]); e.hi[t] = __expf(e.hi[t]); eh.lo[t] = __expf(eh.lo[t]); eh.hi[t] = __expf(eh.hi[t]); }
+      store8(v8, e, eh);
+    }
   }
-  float reg = 0.f;
-  for (int k = threadIdx.x; k < d; k += blockDim.x) {
-    const float x = fhat[(size_t)r * d + k] - f[(size_t)r * d + k];
-    const float ax = fabsf(x);
-    reg += ax < 1.0f ? 0.5f * x * x : ax - 0.5f;
-    if (grad) grad[(size_t)r * d + k] = fminf(fmaxf(x, -1.0f), 1.0f) * reg_scale;
-  }
-  reg = block_sum(reg, sh);
-  if (threadIdx.x == 0) { row_loss[2 * r] = reg; row_loss[2 * r + 1] = cls; }
+  if (tid == 0) { row_loss[2 * r] = sum16(3); row_loss[2 * r + 1] = logf(shh) - dot / sz; }   // lse(zh) - sum_v p_v zh_v, both relative to mh
 }
 
 // grad[r][k] += sum over the S split-K partials of (dZ W)[r][k]   (the classification part of the gradient)
