@@ -30,11 +30,24 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- bf16
 __host__ __device__ inline bf16_t f32_to_bf16(float f) {   // round to nearest even
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_bit_cast(bf16_t, (__bf16)f);            // one v_cvt_pk_bf16_f32: the same result for every finite number and infinity
+#endif
   uint32_t u = __builtin_bit_cast(uint32_t, f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (bf16_t)(u >> 16);
 }
 __host__ __device__ inline float bf16_to_f32(bf16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
+
+// bf16(a) in the low, bf16(b) in the high half; a and b become what the rounding left.  One conversion for two values.
+__device__ inline uint32_t split_pair(float& a, float& b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 h = {(__bf16)a, (__bf16)b};
+  const uint32_t u = __builtin_bit_cast(uint32_t, h);
+  a -= __builtin_bit_cast(float, u << 16);
+  b -= __builtin_bit_cast(float, u & 0xffff0000u);
+  return u;
+}
 
 // x == p0 + p1 (+ p2) with every piece a bf16: the planes the MFMA GEMM multiplies.
 __device__ inline void split_bf16(float x, bf16_t* p, int nplanes) {

@@ -811,15 +811,9 @@ __device__ inline void xf_store8(bf16_t* XF, int m, int k8, int MT, int KS, int 
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     if (q < nplanes) {
-      uint32_t b[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const bf16_t h = f32_to_bf16(r[t]);
-        b[t] = h;
-        r[t] -= bf16_to_f32(h);
-      }
       u32x4 v;
-      v.x = b[0] | (b[1] << 16); v.y = b[2] | (b[3] << 16); v.z = b[4] | (b[5] << 16); v.w = b[6] | (b[7] << 16);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = split_pair(r[2 * t], r[2 * t + 1]);
       *(u32x4*)(XF + xf_index(m, k8, q, MT, KS)) = v;
     }
   }

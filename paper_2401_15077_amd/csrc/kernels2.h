@@ -224,17 +224,11 @@ __device__ __forceinline__ void pin_args(const Gemm2& g) {
 
 // Four consecutive values of row m, columns k.. (k a multiple of 4), as GEMM input (8 bytes per plane).
 __device__ inline void xf_store4(bf16_t* XF, int m, int k, int MT, int KS, int nplanes, f32x4 x) {
+  float r[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
   for (int q = 0; q < 3; ++q)
     if (q < nplanes) {
-      uint32_t b[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bf16_t h = f32_to_bf16(x[t]);
-        b[t] = h;
-        x[t] -= bf16_to_f32(h);
-      }
-      uint2 v; v.x = b[0] | (b[1] << 16); v.y = b[2] | (b[3] << 16);
+      uint2 v; v.x = split_pair(r[0], r[1]); v.y = split_pair(r[2], r[3]);
       *(uint2*)(XF + xf_index(m, k, q, MT, KS)) = v;
     }
 }
