@@ -11,6 +11,7 @@
 //     of squares; the consumer multiplies its outputs by 1/rms, which commutes with the matrix product.
 #pragma once
 #include "kernels.h"
+#include "plans.h"
 
 #define V2_THREADS 512
 
@@ -42,7 +43,7 @@ __device__ inline uint32_t pt_quad_bytes(int s, int Npad, int n4 /*multiple of 4
 // over the lanes' distinct offsets.
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
 
-constexpr uint32_t OUT_OF_RANGE = 0x80000000u;   // byte offset beyond every buffer resource: a load returns zeros without a memory access
+constexpr uint32_t OUT_OF_RANGE = 0x80000000u;   // lane offset beyond every buffer resource: a load returns zeros without a memory access (its scalar offset inside the resource)
 struct RowScale {            // 1/rms of the rows that produced the GEMM input; groups == 0 -> 1
   const float* ssq;          // [groups <= 256][32] partial sums of squares
   int groups;
@@ -796,7 +797,7 @@ __device__ __forceinline__ void fk_stream_q4(const Q4Format fmt, const bf16_t* _
                                              const u32x4* const* sq /*scales of (block j, group 0), this lane's half*/, int NG,
                                              f32x16* acc, int lane) {
   if (ge <= gb) return;
-  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, NXP * KS * 1024, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, q4_x_span(NXP, KS) * 1024, 0x00020000);
   const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : OUT_OF_RANGE;   // dead rows: zeros
 #define Q4_XLOAD(q, kk, past) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane | (past), (uint32_t)(((q) * KS + (kk)) * 1024), 0))
 #define Q4_WLOAD(j, T, past) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrs, (uint32_t)lane * 16u | (past), (uint32_t)((j) * (KS / 4) + (T)) * 1024u, 0))
@@ -892,9 +893,9 @@ __device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt
   if (nr == NR) fk_stream_q4<NXP, NR>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane);
   else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane);
 }
-// The codes of nr row blocks from rb0 on: KS / 4 tiles of 1 KiB a block.
+// The codes of nr row blocks from rb0 on.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t q4_codes(const bf16_t* W, int rb0, int nr, int KS) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)W + (size_t)rb0 * KS * 256), 0, nr * KS * 256, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)W + (size_t)rb0 * KS * 256), 0, q4_w_span(nr, KS) * 1024, 0x00020000);
 }
 
 // The waves' accumulators parked in LDS as red[w][j][i][lane], 16 bytes each = registers 4i..4i+3 (MFMA layout: rows 8i + 4*(lane/32)

@@ -1,10 +1,19 @@
-// Work splits of the matrix products: which tile shape, how many K slices, how many work-groups.  Host arithmetic on sizes only
-// (no device code, no context), so that it can be built and tested without a GPU.
+// Work splits of the matrix products: which tile shape, how many K slices, how many work-groups.  Arithmetic on sizes only (no device
+// code, no context), so that it can be built and tested without a GPU; the kernels call the constexpr functions too.
 #pragma once
 #include <algorithm>
 #include <cstddef>
 
 constexpr int PLAN_MAX_SLICES = 16;   // most K slices any plan of the general path takes
+
+// 1-KiB tiles that the buffer resources of the 4-bit stream (fk_stream_q4) span: those that exist -- activations [plane][k-step], codes
+// [row block][4 k-steps] -- and one group of 8 k-steps behind them.  With three row blocks the last group of a wave requests the one
+// behind it, with every lane's offset out of range so that nothing is read; the check compares that offset with the span minus the
+// scalar offset, so the scalar offset has to lie inside the span.  (Held at the last group instead, it costs the kernel 4 spilled
+// registers.)
+constexpr int q4_x_span(int planes, int KS) { return planes * KS + 8; }
+constexpr int q4_w_span(int row_blocks, int KS) { return row_blocks * (KS / 4) + 2; }
+
 struct GemmPlan { int S, ks_per_split, chunk, rbw, mw; };   // rbw, mw: tile shape of the large-M GEMM (0: k_gemm)
 
 static inline GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {

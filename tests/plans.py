@@ -20,6 +20,8 @@ void shim_moe(const int* a, int* o) {
   put(p.gu, o); put(p.dn, o + 4); o[8] = p.cols;
 }
 int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
+int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
+int shim_q4_w_span(int nr, int KS) { return q4_w_span(nr, KS); }
 int shim_moe_tiles(int M, int topk, int E) { return moe_tiles(M, topk, E); }
 }
 """
@@ -51,6 +53,9 @@ class Plans:
 
     def whole_k(self, NRB, KS, planes, n_cu=256):
         return bool(self.lib.shim_whole_k(NRB, KS, planes, n_cu))
+
+    def q4_spans(self, planes, row_blocks, KS):
+        return self.lib.shim_q4_x_span(planes, KS), self.lib.shim_q4_w_span(row_blocks, KS)
 
     def moe_tiles(self, M, topk, E):
         return self.lib.shim_moe_tiles(M, topk, E)

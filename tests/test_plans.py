@@ -97,3 +97,25 @@ def test_oracle_cases_reach_every_tile(plans):
     # the small models of that file: tiles of two and four row tiles only
     small = [plans.prompt(synth.SHAPES["mini-gqa"], rows) for rows in range(33, 2049, 32)]
     assert {(p.rbw, p.mw) for l in small for p in l.values()} == {(3, 1), (3, 2)}
+
+
+@pytest.mark.parametrize("slices", [1, 3, 8])
+def test_4bit_streams_keep_their_scalar_offsets_inside_the_buffers(plans, slices):
+    """What the 4-bit stream with three row blocks (fk_stream_q4) requests while a wave works on group g of its run [gb, ge): the tiles
+    of group g + 1, in the last round with the lanes out of range.  Tiles of both buffers, 8 k-steps a group: scalar offsets stay inside
+    the resources, requests whose lanes are in range inside the tiles that exist."""
+    planes, blocks = 2, 3
+    for NG in (1, 2, 3, 7, 8, 9, 32, 86, 112):
+        KS = 8 * NG
+        x_span, w_span = plans.q4_spans(planes, blocks, KS)
+        groups = []
+        for s in range(slices):
+            G0, G1 = s * NG // slices, (s + 1) * NG // slices
+            for w in range(8):
+                gb, ge = G0 + w * (G1 - G0) // 8, G0 + (w + 1) * (G1 - G0) // 8
+                for g in range(gb, ge):
+                    x, c = (planes - 1) * KS + 8 * (g + 1) + 7, (blocks - 1) * (KS // 4) + 2 * (g + 1) + 1
+                    assert x < x_span and c < w_span, (NG, g)
+                    assert g + 1 == ge or (x < planes * KS and c < blocks * (KS // 4)), (NG, g)
+                    groups.append(g)
+        assert groups == list(range(NG))
