@@ -316,7 +316,7 @@ static size_t layout(eagle_ctx* c) {
   c->xf2_att = a.take<bf16_t>((size_t)c->NXP * 32 * H * dh);
   c->xf2_ffn = a.take<bf16_t>((size_t)c->NXP * 32 * F);
   c->facts = a.take<RowFact>(Mm);
-  c->ssq1 = a.take<float>(256 * 32); c->ssq2 = a.take<float>(256 * 32);
+  c->ssq1 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32); c->ssq2 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32);
   c->trace = a.take<unsigned long long>(1024 * 8);
   c->cnt_gemm = a.take<int>(1024); c->cnt_attn = a.take<int>((size_t)128 * H);
   size_t worst2 = 0;
@@ -1042,7 +1042,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   g.XF = XF; g.S = p.S; g.groups = p.groups; g.lanes = p.lanes; g.kparts = p.kparts;
   g.PT = c->PT2; g.counters = c->cnt_gemm;
   g.trace = (c->gemm_no++ == c->trace_sel && p.groups * p.S <= 1024) ? c->trace : nullptr;
-  if (g.ssq_out && p.groups > 256) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
+  if (g.ssq_out && p.groups > PLAN_MAX_NORM_GROUPS) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
   if (groups_out) *groups_out = p.groups;
   const double bytes = w.bytes(c->elt);
   hipError_t e;
@@ -1052,7 +1052,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
       g.S = px.S; g.groups = px.groups; g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
       g.trace = nullptr;
       if (groups_out) *groups_out = px.groups;
-      if (g.ssq_out && px.groups > 256) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
+      if (g.ssq_out && px.groups > PLAN_MAX_NORM_GROUPS) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
       e = px.nrmax <= 1 ? launch_xk_q4<1>(c, bytes, g) : px.nrmax == 2 ? launch_xk_q4<2>(c, bytes, g) : launch_xk_q4<3>(c, bytes, g);
       if (e != hipSuccess) return fail(EAGLE_EHIP, "4-bit gemm launch failed: %s", hipGetErrorString(e));
       return EAGLE_OK;

@@ -5,6 +5,7 @@
 #include <cstddef>
 
 constexpr int PLAN_MAX_SLICES = 16;   // most K slices any plan of the general path takes
+constexpr int PLAN_MAX_NORM_GROUPS = 256;   // most work-groups whose partial sums of squares a norm adds up
 
 // 1-KiB tiles that the buffer resources of the 4-bit stream (fk_stream_q4) span: those that exist -- activations [plane][k-step], codes
 // [row block][4 k-steps] -- and one group of 8 k-steps behind them.  With three row blocks the last group of a wave requests the one
@@ -123,8 +124,9 @@ static inline PlanMoe plan_moe(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int
 // Small matrices of the fast path: a work-group per row block over all of K (k2_gemm_fk) instead of K slices whose partial sums cross
 // work-groups.  K x planes is what a work-group then fetches, in KiB per 16 columns: 400 of them take about what the exchange does
 // (store, acknowledge, count, read back: 5 us).  Whole requests, ms, sliced / whole: fp32, d 256 (96 KiB) 8.8 / 7.6; bf16, d 1024 (192)
-// 9.7 / 8.9; d 2048 (384) 12.5 / 12.0; matrices of 528 KiB 8.8 / 9.3.
-static inline bool plan_is_whole_k(int NRB, int KS, int planes, int n_cu) { return NRB <= n_cu && (long)KS * planes <= 400; }
+// 9.7 / 8.9; d 2048 (384) 12.5 / 12.0; matrices of 528 KiB 8.8 / 9.3.  A matrix that feeds a norm leaves partial sums of squares per
+// work-group, of which there may be PLAN_MAX_NORM_GROUPS, however many CUs the device has.
+static inline bool plan_is_whole_k(int NRB, int KS, int planes, int n_cu) { return NRB <= std::min(n_cu, PLAN_MAX_NORM_GROUPS) && (long)KS * planes <= 400; }
 
 // Work split of the split-K kernel with streamed activations: S slices x groups of at most 4 row blocks, chosen by a
 // fetch model in KiB per work-group (weights + the live part of the X slice + twice the partials the last work-group

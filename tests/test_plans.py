@@ -119,3 +119,9 @@ def test_4bit_streams_keep_their_scalar_offsets_inside_the_buffers(plans, slices
                     assert g + 1 == ge or (x < planes * KS and c < blocks * (KS // 4)), (NG, g)
                     groups.append(g)
         assert groups == list(range(NG))
+
+
+@pytest.mark.parametrize("n_cu", [64, 256, 304])
+def test_whole_k_matrices_leave_no_more_partial_sums_of_squares_than_their_buffers_hold(plans, n_cu):
+    for NRB in (1, 63, 64, 65, 255, 256, 257, 304, 305):
+        assert plans.whole_k(NRB, 64, 3, n_cu) == (NRB <= min(n_cu, 256)), NRB
