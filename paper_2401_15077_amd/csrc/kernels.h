@@ -1454,7 +1454,7 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelN
         float un = ((float)rng_u24(pre, (uint32_t)seq, (uint32_t)v, (uint32_t)min(j, V - 1)) + 0.5f) * 5.9604644775390625e-8f;
         sc = sc / temperature - logf(-logf(un));
       }
-      x[u] = j < V ? sc : -INFINITY;
+      x[u] = j < V && sc == sc ? sc : -INFINITY;             // (a NaN is no better than -inf, see arg_key)
     }
     // a thread's best entry that is not taken yet: bit u of `taken`
     uint32_t taken = 0;

@@ -90,3 +90,42 @@ def test_ties_go_to_the_lowest_token(vocab):
         n = int(ln[0])
         assert [int(v) for v in path[0][:n]] == walk and [int(t) for t in out[0][:n]] == emitted
     eng.close()
+
+
+@pytest.mark.parametrize("vocab", [64, 1025, 32768, 33000])
+@pytest.mark.parametrize("temperature", [0.0, 1.0])
+def test_nan_logits_hide_no_other_token(vocab, temperature):
+    """Children of rows with NaN among the head's logits are those of the same rows with -inf in their places: NaN in every thread's first
+    entry, in the best one's neighbours, in nearly all."""
+    s = replace(synth.SHAPES["tiny"], name=f"tiny-v{vocab}", n_layers=1, vocab=vocab)
+    par, rk = synth.TREES["T26"]
+    M = len(par)
+    print(s.name, "temperature", temperature, flush=True)
+    eng = pkg.Eagle(s, par, rk, max_seq=128, temperature=temperature, seed=7)
+    eng.load_weights(synth.iter_weights(s, 45, synth.device_fmt(s)))
+    eng.prefill(0, synth.prompt(45, 12, vocab))
+    eng.draft_tree()
+    rng = np.random.default_rng(vocab)
+    clean = rng.standard_normal((M, vocab)).astype(np.float32)
+    dirty = rng.random((M, vocab)) < 0.3
+    dirty[0::3, :min(1024, vocab - 16)] = True
+    dirty[1::3] = True
+    for row in dirty[1::3]:
+        row[rng.choice(vocab, 16, replace=False)] = False
+    children = [[v for v in range(1, M) if par[v] == p] for p in range(M)]
+    assert (vocab - dirty.sum(1)).min() >= max(len(c) for c in children)
+
+    def chosen(masked_with):
+        eng.set_buffer(pkg.BUF_DRAFT_LOGITS, np.where(dirty, np.float32(masked_with), clean))
+        for level in [-1] + list(range(1, eng.D)):
+            eng.expand_level(level)
+        return eng.get_buffer(pkg.BUF_TREE_TOKENS).copy()
+
+    tok = chosen(np.nan)
+    np.testing.assert_array_equal(tok, chosen(-np.inf))
+    for p in range(M):
+        got = [int(tok[v]) for v in sorted(children[p], key=lambda v: rk[v])]
+        assert len(set(got)) == len(got) and not any(dirty[p][t] for t in got), (p, got)
+        if temperature == 0.0:
+            assert got == list(np.argsort(np.where(dirty[p], np.inf, -clean[p]), kind="stable")[:len(got)]), (p, got)
+    eng.close()
