@@ -1499,7 +1499,7 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelN
           float un = ((float)rng_u24(pre, (uint32_t)seq, (uint32_t)v, (uint32_t)j) + 0.5f) * 5.9604644775390625e-8f;
           sc = sc / temperature - logf(-logf(un));
         }
-        float cv = sc; int ci = j;
+        float cv = sc == sc ? sc : -INFINITY; int ci = j;      // (a NaN is no better than -inf, but it has a token)
 #pragma unroll
         for (int q = 0; q < EAGLE_MAX_CHILD; ++q) {
           const bool win = cv > tv[q] || (cv == tv[q] && ci < ti[q]);
@@ -1523,7 +1523,8 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelN
 #pragma unroll
     for (int q = 0; q < EAGLE_MAX_CHILD; ++q)
       if (q < nk) {
-        tree_tok[seq * M + childs[q]] = picked[q];
+        // (fewer tokens in the vocabulary than children: nothing is left to pick, and acceptance indexes its vectors with the token)
+        tree_tok[seq * M + childs[q]] = min(max(picked[q], 0), V - 1);
         on_path[seq * M + childs[q]] = (hinted >= 0 && picked[q] == hinted);
       }
   }

@@ -129,3 +129,33 @@ def test_nan_logits_hide_no_other_token(vocab, temperature):
         if temperature == 0.0:
             assert got == list(np.argsort(np.where(dirty[p], np.inf, -clean[p]), kind="stable")[:len(got)]), (p, got)
     eng.close()
+
+
+@pytest.mark.parametrize("vocab", [2, 3, 32768, 33000])
+@pytest.mark.parametrize("temperature", [0.0, 1.0])
+def test_children_name_tokens_of_the_vocabulary(vocab, temperature):
+    """Rows of NaN alone, rows with fewer numbers than children, vocabularies with fewer tokens than children."""
+    s = replace(synth.SHAPES["tiny"], name=f"tiny-v{vocab}", n_layers=1, vocab=vocab)
+    par, rk = synth.TREES["T26"]
+    M = len(par)
+    print(s.name, "temperature", temperature, flush=True)
+    eng = pkg.Eagle(s, par, rk, max_seq=128, temperature=temperature, seed=7)
+    eng.load_weights(synth.iter_weights(s, 46, synth.device_fmt(s)))
+    eng.prefill(0, [1, 0, 1])
+    eng.draft_tree()
+    draft = np.full((M, vocab), np.nan, np.float32)
+    draft[1::2, vocab // 2] = 1.0
+    eng.set_buffer(pkg.BUF_DRAFT_LOGITS, draft)
+    for level in [-1] + list(range(1, eng.D)):
+        eng.expand_level(level)
+    tok = eng.get_buffer(pkg.BUF_TREE_TOKENS)
+    assert tok.min() >= 0 and tok.max() < vocab, tok
+    for p in range(M):
+        got = [int(tok[v]) for v in sorted((v for v in range(1, M) if par[v] == p), key=lambda v: rk[v])]
+        if vocab > 4:                                            # the row's number first, then the lowest tokens
+            assert got == ([vocab // 2, 0, 1, 2] if p % 2 else [0, 1, 2, 3])[:len(got)], (p, got)
+    eng.verify()
+    out, ln, path = eng.accept()
+    n = int(ln[0])
+    assert 1 <= n <= eng.D + 1 and path[0][0] == 0 and all(0 <= int(t) < vocab for t in out[0][:n])
+    eng.close()
