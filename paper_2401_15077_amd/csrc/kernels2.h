@@ -1709,8 +1709,8 @@ __global__ __launch_bounds__(ATTN_PROMPT_THREADS, 2) void k2_attn_prompt(AttnArg
   __syncthreads();
   if (kg == 1 || !live) return;
   {
-    const float m1 = st[0], m_new = fmaxf(m_run, m1);            // (a live row's first half holds token 0: m_new is finite or NaN)
-    const float w0 = __expf(m_run - m_new), w1 = m1 == -INFINITY ? 0.f : __expf(m1 - m_new);
+    const float m1 = st[0], m_new = fmaxf(m_run, m1);            // (-inf: a half that holds no visible token, or a row whose scores are all -inf)
+    const float w0 = m_run == -INFINITY ? 0.f : __expf(m_run - m_new), w1 = m1 == -INFINITY ? 0.f : __expf(m1 - m_new);
     l_run = l_run * w0 + st[64] * w1;
 #pragma unroll
     for (int b = 0; b < DB; ++b)

@@ -39,3 +39,27 @@ def test_prompt_attention(base, heads, kv_heads, dh, rows, kv, page):
     lockstep_step(eng, orc, st, 2e-2)                            # the head's cache of every prompt row is what drafting reads
     print(f"max|dL| prompt {err:.2e} verify {st.max_logit_err:.2e}", flush=True)
     eng.close()
+
+
+@pytest.mark.parametrize("rows", [64, 256, 300])
+def test_rows_whose_scores_are_all_minus_infinity_attend_to_nothing(rows):
+    """Queries and keys so large that every score of a row overflows to -inf (one token repeated, queries opposite to the keys, in the
+    columns that the rotary embedding turns least: 1.8e-4 a position): such rows take nothing from the values, with either attention
+    kernel (64 rows: 32 rows a work-group), as if the output projection were zero."""
+    s = _shape("mini-gqa", 64, 8, 32)
+    par, rk = synth.TREES["T8"]
+    token, low = 5, s.head_dim // 2 - 1
+    w = synth.make_weights(s, 72, synth.oracle_fmt(s))
+    u = w["embed"][token] / np.linalg.norm(w["embed"][token])
+    extreme = {}
+    for name, sign in (("layers.0.wq", 1e19), ("layers.0.wk", -1e19)):
+        m = np.zeros_like(w[name])
+        m[low::s.head_dim] = sign * u
+        extreme[name] = synth._bf16_round_bits(m)
+    eng = pkg.Eagle(s, par, rk, max_seq=rows + 64)
+    eng.load_weights((n, extreme.get(n, a)) for n, a in synth.iter_weights(s, 72, synth.device_fmt(s)))
+    w["layers.0.wo"] = np.zeros_like(w["layers.0.wo"])
+    orc = Oracle(s, w, par, rk, max_seq=rows + 64, dtype=np.float32)
+    err = check_prefill(eng, orc, np.full(rows, token, np.int32), BOUND["fp32"])
+    assert np.isfinite(err)
+    eng.close()
