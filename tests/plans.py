@@ -20,6 +20,7 @@ void shim_moe(const int* a, int* o) {
   put(p.gu, o); put(p.dn, o + 4); o[8] = p.cols;
 }
 int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
+int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
 int shim_q4_w_span(int nr, int KS) { return q4_w_span(nr, KS); }
 int shim_moe_tiles(int M, int topk, int E) { return moe_tiles(M, topk, E); }
@@ -53,6 +54,14 @@ class Plans:
 
     def whole_k(self, NRB, KS, planes, n_cu=256):
         return bool(self.lib.shim_whole_k(NRB, KS, planes, n_cu))
+
+    def prompt_attn(self, heads, rows, max_seq, n_cu=256):
+        """-> for every pass of a prompt of a bf16 model with an fp32 cache (eagle_prefill: whole windows of 512 rows, at most 2048, passes of
+        about equal length): its first row, its rows and whether it takes the attention kernel of 128 rows a work-group"""
+        chunk = min(2048, -(-max_seq // 512) * 512)
+        n = -(-rows // chunk)
+        each = -(-(-(-rows // n)) // 512) * 512
+        return [(at, min(each, rows - at), bool(self.lib.shim_prompt_attn(min(each, rows - at), heads, n_cu))) for at in range(0, rows, each)]
 
     def q4_spans(self, planes, row_blocks, KS):
         return self.lib.shim_q4_x_span(planes, KS), self.lib.shim_q4_w_span(row_blocks, KS)
