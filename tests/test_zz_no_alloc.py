@@ -46,18 +46,25 @@ def run_and_compare(a, b, steps):
 
 
 def test_accept_static_matches_accept_on_two_calls_in_a_row_the_second_smaller():
-    # first: two sequences, temperature 1 (both probability vectors of Alg. 1 live in the static array), vocab 32000
-    a, b = pair("tiny-v32k", "T15", 2, 1.0, 3)
+    # first: two sequences, temperature 1, more than 32768 entries (both probability vectors of Alg. 1 live in the static array)
+    a, b = pair("tiny-v40k", "T15", 2, 1.0, 6)
+    n0 = run_and_compare(a, b, 4)
+    a.close(); b.close()
+    # second, smaller: one sequence of the same vocabulary, then smaller vocabularies, which keep their vectors in registers
+    a, b = pair("tiny-v40k", "T15", 1, 1.0, 7)
     n1 = run_and_compare(a, b, 4)
     a.close(); b.close()
-    # second, smaller: one sequence, vocab 1024, temperature 1 -- then greedy (the arg-max array overlays the same bytes)
-    a, b = pair("tiny", "T15", 1, 1.0, 4)
+    a, b = pair("tiny-v32k", "T15", 2, 1.0, 3)
     n2 = run_and_compare(a, b, 4)
     a.close(); b.close()
+    a, b = pair("tiny", "T15", 1, 1.0, 4)
+    n3 = run_and_compare(a, b, 4)
+    a.close(); b.close()
+    # greedy: the arg-max array overlays the same bytes
     a, b = pair("tiny", "T26", 1, 0.0, 5)
     run_and_compare(a, b, 3)
     a.close(); b.close()
-    assert n1 > 8 and n2 > 4                                     # paths longer than one token were committed
+    assert n0 > 8 and n1 > 4 and n2 > 8 and n3 > 4               # paths longer than one token were committed
 
 
 def test_accept_static_rejects_sizes_beyond_the_static_array():
