@@ -1088,9 +1088,9 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   }
   // wide matrices of the bf16 configuration: whole-K work-groups with the epilogue in place (no partials) ...
   const int fk_grid = std::max(c->n_cu, (w.NRB + 3) / 4);
-  // (not for the residual epilogue, although the kernel has it: O and down at d = 8192 have exactly one row block per
-  // CU, and a work-group that owns one row block over all of K fetches twice as many activation bytes as weight
-  // bytes -- measured there: down 109.7 us whole-K against 85.8 us split-K, O 37.5 against 34.8)
+  // (not for the residual epilogue: O and down at d = 8192 have exactly one row block per CU, and a work-group that owns
+  // one row block over all of K fetches twice as many activation bytes as weight bytes -- measured there: down 109.7 us
+  // whole-K against 85.8 us split-K, O 37.5 against 34.8; short K is another matter, see `small`)
   const bool fullk = !c->f32 && w.NRB >= c->n_cu && g.epi != EPI_RESID;
   // (dense models with a bf16 cache keep their K slices, see fixed_sums)
   const bool small = !c->fixed_sums && plan_is_whole_k(w.NRB, w.KS, c->NWP + c->NXP, c->n_cu);

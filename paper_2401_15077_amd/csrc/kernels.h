@@ -1383,10 +1383,6 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelN
   TRACE_STAMP(tr, 0);
   const int v = nodes.node[blockIdx.x];
   const int M = tree->M;
-  // The node's own head feature (the row of the pass that produced these logits) goes to node_f here when the caller
-  // asks for it: one block per row of the pass exists anyway, which saves a separate copy kernel per pass.
-  // Row of the pass: a level pass lists the level's parent nodes in order; in a pending pass the root is the
-  // sequence's last pending row.
   float* lg = draft_logits + ((size_t)seq * M + v) * V;
   // Loads are grouped by what they depend on, so that the kernel pays two memory round trips, not one per fact:
   // (1) everything addressed by (seq, v) alone, including the first 32 logits of every thread ...
@@ -1398,6 +1394,9 @@ __global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelN
     if (u * 1024 < V) x[u] = lg[min(u * 1024 + (int)threadIdx.x, V - 1)];
   }
   const int n = st.n_tok[seq];
+  // The node's own head feature (the row of the pass that produced these logits) goes to node_f when the caller asks for it: one
+  // block per row of the pass exists anyway, which saves a separate copy kernel per pass.  Row of the pass: a level pass lists the
+  // level's parent nodes in order; in a pending pass the root is the sequence's last pending row.
   const int feat_row = feat_src ? seq * src_rows_per_seq + (level < 0 ? max(st.n_pend[seq] - 1, 0) : (int)blockIdx.x) : 0;
   const int hn = hint.n[seq];
   const unsigned long long hseed = hint.seed[seq];
@@ -1672,8 +1671,6 @@ __device__ inline int reg_inverse_cdf(const float (&p)[VPT], int V, float u, flo
 }
 constexpr size_t CDF_LDS = (size_t)33 * 1024 * 4;              // dynamic LDS of the sampling kernels for at most 32768 entries
 
-// Pick the next token of every sequence from logits[seq][V] (prefill's first token, vanilla decoding):
-// argmax when greedy, else one inverse-CDF draw from softmax(logits / T).  Also advances the sequence state.
 // Index of the largest of V values (lowest among equals) for a block of 1024 threads, 16 loads of a thread in flight.
 __device__ inline int row_argmax(const float* __restrict__ lg, int V, unsigned long long* shk) {
   const int tid = threadIdx.x;
@@ -1692,6 +1689,8 @@ __device__ inline int row_argmax(const float* __restrict__ lg, int V, unsigned l
   return arg_index(block_max_key(arg_key(bv, bi), shk));
 }
 
+// Pick the next token of every sequence from logits[seq][V] (prefill's first token, vanilla decoding):
+// argmax when greedy, else one inverse-CDF draw from softmax(logits / T).  Also advances the sequence state.
 template <bool BIGV>   // BIGV: more than 32768 vocabulary entries
 __global__ __launch_bounds__(1024) void k_choose(SeqState st, int seq0, const float* logits, int V, float temperature,
                                                  unsigned long long rng_seed, float* pbuf /*[seq][V]*/, int is_prefill,

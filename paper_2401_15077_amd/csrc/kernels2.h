@@ -690,14 +690,14 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   TRACE_STAMP(tr, 4);
 }
 
-// ---- full-K variant for wide matrices (QKV, gate/up, LM head) ----------------------------------------------------------
+// ---- full-K variant for wide matrices (QKV, gate/up, LM head) and small ones ----------------------------------------------------------
 // A work-group owns up to 4 whole row blocks over ALL of K: no partial sums leave the chip, no arrival counter, no
 // last work-group.  The eight waves split K eight ways; a wave streams, per k-step, the weight tiles of the group's
 // row blocks from HBM AND the activation fragments of that k-step straight from L2 (every work-group reads the whole
 // X, 512 KB at d = 4096, which the 32 work-groups of an XCD share through its L2) -- no LDS staging, no barrier until
 // the end.  The waves' sums meet in LDS (k-part order) and the epilogue runs on them in place.  Costs more bytes per
 // CU than the split-K kernel and saves its publish / arrive / read-back round trips; pays off for matrices with at
-// least as many row blocks as there are CUs.
+// least as many row blocks as there are CUs, and for those whose K is short (plan_is_whole_k; one row block a work-group).
 // The activation fragments come through buffer loads: a lane whose row (lane % 32) is not a live row of the pass gets
 // an offset beyond the buffer, which the hardware answers with zeros WITHOUT touching memory -- a pass of M rows moves
 // M/32 of the fragment bytes (26/32 in a 26-node verify, 1/8 and less in the head's passes).
@@ -755,7 +755,8 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
   // last one, a wave's 32 came as 35 or 36 at K = 4096 and O's 8 as 12, on the L2 -> CU path that binds these kernels; requested out
   // of range they move nothing and still cost more than a branch.  26 rows at 7B, us clamped / out of range / branch: QKV 25.3 /
   // 25.9 / 24.7, gate/up 35.4 / 36.0 / 34.7, O 13.6 / 13.3 / 12.5, down 24.0 / 23.5 / 23.5.  Four row blocks, whose depth divides
-  // the usual K: LM head 44.8 / 45.9 / 45.5, so they keep one loop.)
+  // the usual K: LM head 44.8 / 45.9 / 45.5, so they keep one loop.  A wave with fewer k-steps than DEPTH -- K below 1024 in bf16 and
+  // 512 in fp32 -- still fills its ring with the last one above.)
   constexpr bool EXACT = NR < 4;
   for (; k + (EXACT ? 2 * DEPTH - 1 : DEPTH) < ke; k += DEPTH) {
 #pragma unroll
