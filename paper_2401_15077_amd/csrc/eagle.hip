@@ -702,15 +702,15 @@ static hipError_t launch_pf_q4(eagle_ctx* c, const PackedW& w, const bf16_t* XF,
                   p.ks_per_split / 8, p.S, w.Npad, MT, swiglu_out, M);
 }
 
-// PT <- X (XF layout, MT row tiles) times W^T.  Returns the split count through *S.
+// PT <- X (XF layout, M rows in MT row tiles) times W^T.  Returns the split count through *S.
 // swiglu_out (gate/up matrices only): where the plan has a single K slice in the large-M kernel, the SwiGLU epilogue runs
 // inside the GEMM and its output goes to swiglu_out in GEMM-input layout; *S is then 0 (nothing left in PT).
-static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int* S, bf16_t* swiglu_out = nullptr, int M = 0) {
+static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int M, int* S, bf16_t* swiglu_out = nullptr) {
   const bool big = use_pf(c, MT);
   GemmPlan p = big ? plan_pf(w.NRB, w.KS, MT, c->n_cu, swiglu_out != nullptr, c->q4, c->fixed_sums) : plan_gemm(w.NRB, w.KS, c->NXP, MT);
   const bool fuse = big && swiglu_out && p.S == 1;
   if (!fuse && (size_t)p.S * w.Npad * MT * 32 > c->pt_floats) return fail(EAGLE_EINVAL, "internal: partial buffer too small");
-  if (MT < 1 || MT * 32 > std::max(c->Mmax, 2 * c->hl_chunk) || (big && c->f32)) return fail(EAGLE_EINVAL, "internal: MT out of range");
+  if (MT < 1 || MT * 32 > std::max(c->Mmax, 2 * c->hl_chunk) || M <= 32 * (MT - 1) || M > 32 * MT || (big && c->f32)) return fail(EAGLE_EINVAL, "internal: rows out of range");
   *S = fuse ? 0 : p.S;
   hipError_t e;
   if (w.q4) {
@@ -806,7 +806,7 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
   const int H = g.n_heads, dh = g.head_dim, F = g.d_ffn;
   int S = 1, rc;
   KVCache kv = kv_for(c, li);
-  if ((rc = (c->cur_class = KC_QKV, gemm(c, w.qkv, c->xf_d, MT, &S)))) return rc;
+  if ((rc = (c->cur_class = KC_QKV, gemm(c, w.qkv, c->xf_d, MT, M, &S)))) return rc;
   {
     dim3 grid(M, (w.qkv.N / 4 + 255) / 256);
     if (c->kv_f32) k_qkv_rope_store<float><<<grid, 256, 0, c->stream>>>(c->facts, c->PT, S, w.qkv.N, w.qkv.Npad, MT * 32, c->rope_cos, c->rope_sin, c->Q, kv, H);
@@ -840,7 +840,7 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
 #undef ATTNG
     LAUNCH_CHECK();
   }
-  if ((rc = (c->cur_class = KC_O, gemm(c, w.o, c->xf_att, MT, &S)))) return rc;
+  if ((rc = (c->cur_class = KC_O, gemm(c, w.o, c->xf_att, MT, M, &S)))) return rc;
   if ((rc = resnorm(c, M, MT, c->h, c->PT, S, w.o.Npad, nullptr, w.mlp_norm, c->xf_d, w.moe ? c->xn : nullptr))) return rc;
   if (w.moe) {
     const int E = g.n_experts;
@@ -870,31 +870,31 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
     }
     // (fp32 models: every expert over all rows; a row's result is scaled by its routing weight, 0 for experts it did not select)
     for (int e = 0; e < E; ++e) {
-      if ((rc = (c->cur_class = KC_GATEUP, gemm(c, w.e_gu[e], c->xf_d, MT, &S)))) return rc;
+      if ((rc = (c->cur_class = KC_GATEUP, gemm(c, w.e_gu[e], c->xf_d, MT, M, &S)))) return rc;
       dim3 grid((F / 16 + 3) / 4, MT);
       k_swiglu<<<grid, 256, 0, c->stream>>>(c->PT, S, w.e_gu[e].Npad, MT * 32, F, M, c->xf_ffn, MT, c->NXP);
       LAUNCH_CHECK();
-      if ((rc = (c->cur_class = KC_DOWN, gemm(c, w.e_dn[e], c->xf_ffn, MT, &S)))) return rc;
+      if ((rc = (c->cur_class = KC_DOWN, gemm(c, w.e_dn[e], c->xf_ffn, MT, M, &S)))) return rc;
       const bool last = e + 1 == E;     // only the last expert's pass produces the normalised output
       if ((rc = resnorm(c, M, MT, c->h, c->PT, S, w.e_dn[e].Npad, nullptr, last ? next_gain : nullptr, last ? c->xf_d : nullptr,
                         last ? xout : nullptr, c->moe_w + (size_t)e * c->Mmax))) return rc;
     }
     return EAGLE_OK;
   }
-  if ((rc = (c->cur_class = KC_GATEUP, gemm(c, w.gu, c->xf_d, MT, &S, c->xf_ffn, M)))) return rc;
+  if ((rc = (c->cur_class = KC_GATEUP, gemm(c, w.gu, c->xf_d, MT, M, &S, c->xf_ffn)))) return rc;
   if (S > 0) {
     dim3 grid((F / 16 + 3) / 4, MT);
     k_swiglu<<<grid, 256, 0, c->stream>>>(c->PT, S, w.gu.Npad, MT * 32, F, M, c->xf_ffn, MT, c->NXP);
     LAUNCH_CHECK();
   }
-  if ((rc = (c->cur_class = KC_DOWN, gemm(c, w.dn, c->xf_ffn, MT, &S)))) return rc;
+  if ((rc = (c->cur_class = KC_DOWN, gemm(c, w.dn, c->xf_ffn, MT, M, &S)))) return rc;
   return resnorm(c, M, MT, c->h, c->PT, S, w.dn.Npad, nullptr, next_gain, c->xf_d, xout);
 }
 
 static int lm_head(eagle_ctx* c, const Pass& pass, int M, int MT, float* out, int out_kind, int only_last_row,
                    const bf16_t* XF = nullptr) {
   int S, rc;
-  if ((rc = (c->cur_class = KC_LMHEAD, gemm(c, c->lm_head, XF ? XF : c->xf_d, MT, &S)))) return rc;
+  if ((rc = (c->cur_class = KC_LMHEAD, gemm(c, c->lm_head, XF ? XF : c->xf_d, MT, M, &S)))) return rc;
   dim3 grid((c->cfg.vocab + 255) / 256, M);
   k_logits<<<grid, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->PT, S, c->lm_head.Npad, MT * 32, out, out_kind, c->cfg.vocab, only_last_row);
   LAUNCH_CHECK();
@@ -944,7 +944,7 @@ static int head_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, bo
   if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts);
   else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts);
   LAUNCH_CHECK();
-  if ((rc = (c->cur_class = KC_FC, gemm(c, c->fc, c->xf_2d, MT, &S)))) return rc;
+  if ((rc = (c->cur_class = KC_FC, gemm(c, c->fc, c->xf_2d, MT, M, &S)))) return rc;
   const float* bias = c->loaded_layer[EAGLE_W_FC_BIAS][0] ? c->fc_bias : nullptr;
   if ((rc = resnorm(c, M, MT, nullptr, c->PT, S, c->fc.Npad, bias, c->layers[g.n_layers].attn_norm, c->xf_d, nullptr))) return rc;
   if ((rc = layer_forward(c, pass, M, MT, g.n_layers, t_max, n_new, nullptr, c->featbuf))) return rc;
@@ -1353,7 +1353,7 @@ extern "C" int eagle_head_loss(eagle_ctx* c, const float* f, const float* fhat, 
     k_rows_to_xf<<<dim3(rc_, 2), 256, 0, c->stream>>>(fhat + (size_t)r0 * d, rpad, c->xf_d, MTf, c->NXP, d);
     LAUNCH_CHECK();
     int S, rc;
-    if ((rc = (c->cur_class = KC_LMHEAD, gemm(c, c->lm_head, c->xf_d, MTf, &S)))) return rc;
+    if ((rc = (c->cur_class = KC_LMHEAD, gemm(c, c->lm_head, c->xf_d, MTf, MTf * 32, &S)))) return rc;
     auto loss_row = V <= 4 * 8192 ? k_head_loss_row<4> : k_head_loss_row<0>;   // larger vocabularies would spill: they stream
     loss_row<<<rc_, 1024, 0, c->stream>>>(c->PT, S, MTf * 32, c->lm_head.Npad, rpad, V, f + (size_t)r0 * d, fhat + (size_t)r0 * d, d,
                                           cls_scale, reg_scale, c->hl_dz, MTb, c->NXP, grad ? grad + (size_t)r0 * d : nullptr, c->hl_row_loss);
@@ -1361,7 +1361,7 @@ extern "C" int eagle_head_loss(eagle_ctx* c, const float* f, const float* fhat, 
     k_head_loss_accumulate<<<1, 64, 0, c->stream>>>(c->hl_row_loss, rc_, c->hl_acc);
     LAUNCH_CHECK();
     if (grad) {
-      if ((rc = (c->cur_class = KC_LMHEAD, gemm(c, c->lm_head_T, c->hl_dz, MTb, &S)))) return rc;
+      if ((rc = (c->cur_class = KC_LMHEAD, gemm(c, c->lm_head_T, c->hl_dz, MTb, rc_, &S)))) return rc;
       k_head_loss_grad_finish<<<dim3((d + 255) / 256, rc_), 256, 0, c->stream>>>(c->PT, S, MTb * 32, c->lm_head_T.Npad, grad + (size_t)r0 * d, d);
       LAUNCH_CHECK();
     }

@@ -501,6 +501,11 @@ __device__ __forceinline__ void pf_store(f32x16 (&acc)[RBW][2], float* __restric
   }
 }
 
+struct BufferRsrc { __amdgpu_buffer_rsrc_t rs; };
+// 16 bytes a lane straight into LDS (at `l` + 16 * lane).
+__device__ __forceinline__ void buffer_to_lds16(__amdgpu_buffer_rsrc_t rs, void* l, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)l, 16, lane_off, off, 0, 0);
+}
 // GROUPED (mixture of experts): the activation tiles are the experts' rows gathered one expert after the other (k_moe_gather),
 // every work-group column of RT tiles belongs to one expert (k_moe_plan), whose matrix starts `expert_stride` elements behind
 // the previous one's; columns beyond the last expert's end leave at once.
@@ -538,22 +543,28 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
   const int rb0 = nt * WT + wn * RBW, mt0 = tile0 + wm * 2;
   // a wave whose activation tiles or row blocks all lie beyond the end moves data and keeps the barriers, but multiplies nothing
   const bool busy = mt0 < tile_end && rb0 < NRB;
-  // the tiles this wave loads, the same number in every wave (the last tile is loaded more than once where they do not divide)
-  const bf16_t* src[LPW];
+  // The tiles this wave loads, the same number in every wave (the last tile is loaded more than once where they do not divide).  Buffer
+  // loads: a tile's base in a resource, the k-step in the scalar offset, no address arithmetic in the vector unit, and lanes of rows or
+  // blocks beyond the end out of range, which move nothing and leave zeros (zeros also cost the matrix pipes less power).  us a launch,
+  // before / after: grouped experts of a 1000-row prompt at Mixtral widths 1053 / 914 and 561 / 478; 183 to 300 rows at 7B widths 148 /
+  // 131, 83 / 71, 82 / 63; 104 rows, O and down 24.0 / 23.5; full tiles (1024 rows at 13B widths) 193 / 190 and 485 / 476.
+  BufferRsrc src[LPW];
+  uint32_t vo[LPW];
   int dst[LPW];
 #pragma unroll
   for (int u = 0; u < LPW; ++u) {
-    const int i = min(w + u * NW, NTILE - 1);
-    if (i < WT) src[u] = Wp + (size_t)min(nt * WT + i, NRB - 1) * KS * 512;
-    else src[u] = XF + (size_t)((i - WT) / RT * MT + min(tile0 + (i - WT) % RT, tile_end - 1)) * KS * 512;
+    const int i = min(w + u * NW, NTILE - 1), t = tile0 + (i - WT) % RT;
+    const bf16_t* p = i < WT ? Wp + (size_t)min(nt * WT + i, NRB - 1) * KS * 512 : XF + (size_t)((i - WT) / RT * MT + min(t, tile_end - 1)) * KS * 512;
+    src[u].rs = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, KS * 1024, 0x00020000);
+    vo[u] = (i < WT ? nt * WT + i < NRB : t * 32 + (lane & 31) < row_end) ? lane * 16u : 0x80000000u;
     dst[u] = i * 64;
   }
   // (k-steps beyond the end are clamped, so that the number of loads in flight is the same on every path)
   auto dma = [&](u32x4* slot, int k) {
-    const size_t ko = (size_t)min(k, klast) * 512;
+    const uint32_t ko = (uint32_t)min(k, klast) * 1024u;
 #pragma unroll
     for (int u = 0; u < LPW; ++u)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[u] + ko + lane * 8), (__attribute__((address_space(3))) void*)(slot + dst[u]), 16, 0, 0);
+      buffer_to_lds16(src[u].rs, slot + dst[u], vo[u], ko);
   };
   f32x16 acc[RBW][2];
 #pragma unroll
@@ -649,28 +660,31 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__
   const int tile0 = mq * RT, tile_end = min(MT, tile0 + RT);
   const int rb0 = nt * WT + wn * RBW, mt0 = tile0 + wm * 2;
   const bool busy = mt0 < tile_end && rb0 < NRB;
-  const bf16_t* src[LPW];
+  BufferRsrc src[LPW];                                          // (as in k_gemm_pf: rows beyond the end out of range)
+  uint32_t vo[LPW];
   int dst[LPW];
 #pragma unroll
   for (int u = 0; u < LPW; ++u) {
-    const int i = w + u * NW;
-    src[u] = XF + (size_t)(i / RT * MT + min(tile0 + i % RT, tile_end - 1)) * KS * 512;
+    const int i = w + u * NW, t = tile0 + i % RT;
+    src[u].rs = __builtin_amdgcn_make_buffer_rsrc((void*)(XF + (size_t)(i / RT * MT + min(t, tile_end - 1)) * KS * 512), 0, KS * 1024, 0x00020000);
+    vo[u] = t * 32 + (lane & 31) < M ? lane * 16u : 0x80000000u;
     dst[u] = i * 64;
   }
-#define PF_LDS(p, l) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p), (__attribute__((address_space(3))) void*)(l), 16, 0, 0)
   auto dma = [&](u32x4* slot, int k) {
-    const size_t ko = (size_t)min(k, klast) * 512;
+    const uint32_t ko = (uint32_t)min(k, klast) * 1024u;
 #pragma unroll
-    for (int u = 0; u < LPW; ++u) PF_LDS(src[u] + ko + lane * 8, slot + dst[u]);
+    for (int u = 0; u < LPW; ++u) buffer_to_lds16(src[u].rs, slot + dst[u], vo[u], ko);
   };
   // One code tile per wave: w % WT is w.  (Written as w the same loop comes out one instruction earlier, and a 500-token request at 7B
   // widths measured 0.7 to 0.9 % slower in two builds' comparisons, against 0.2 to 0.3 % between identical kernels; so it stays.)
-  const u32x4* csrc = Wq + (size_t)min(nt * WT + w % WT, NRB - 1) * KT * 64 + lane;
-  auto dma_codes = [&](u32x4* slot, int T) { PF_LDS(csrc + (size_t)min(T, Tlast) * 64, slot + (w % WT) * 64); };
+  BufferRsrc csrc, ssrc, xsrc;
+  csrc.rs = __builtin_amdgcn_make_buffer_rsrc((void*)(Wq + (size_t)min(nt * WT + w % WT, NRB - 1) * KT * 64), 0, KT * 1024, 0x00020000);
+  auto dma_codes = [&](u32x4* slot, int T) { buffer_to_lds16(csrc.rs, slot + (w % WT) * 64, lane * 16u, (uint32_t)min(T, Tlast) * 1024u); };
   // lane l brings 16 bytes of the scales of row block l / 4 (lanes beyond the tile repeat the last ones) and of the sums of x
-  const bf16_t* ssrc = SC + (size_t)min(nt * WT + min(lane >> 2, WT - 1), NRB - 1) * NG * 32 + (lane & 3) * 8;
-  const float* xsrc = SX + tile0 * 32 + (lane & (RT * 8 - 1)) * 4;
-  const int Mpad = MT * 32;
+  ssrc.rs = __builtin_amdgcn_make_buffer_rsrc((void*)(SC + (size_t)nt * WT * NG * 32), 0, min(WT, NRB - nt * WT) * NG * 64, 0x00020000);
+  const uint32_t s_lane = (uint32_t)(min(min(lane >> 2, WT - 1), NRB - 1 - nt * WT) * NG * 32 + (lane & 3) * 8) * 2u;
+  xsrc.rs = __builtin_amdgcn_make_buffer_rsrc((void*)SX, 0, NG * MT * 128, 0x00020000);
+  const uint32_t x_lane = (uint32_t)(tile0 * 32 + (lane & (RT * 8 - 1)) * 4) * 4u;
   f32x16 acc[RBW][2], part[RBW][2];
 #pragma unroll
   for (int j = 0; j < RBW; ++j)
@@ -725,8 +739,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__
     PF_WAITV(2 * LPW + ((i) == 1 || (i) == 2 ? 3 : (i) == 5 || (i) == 6 ? 1 : 0));                      \
     PF_BAR();                                                                                           \
     if ((i) == 0) {                                                                                     \
-      PF_LDS(ssrc + (size_t)gi * 32, scl);                                                              \
-      PF_LDS(xsrc + (size_t)gi * Mpad, sxs);                                                            \
+      buffer_to_lds16(ssrc.rs, scl, s_lane, (uint32_t)gi * 64u);                                        \
+      buffer_to_lds16(xsrc.rs, sxs, x_lane, (uint32_t)(gi * MT) * 128u);                                \
       dma_codes(c1, 2 * gi + 1);                                                                        \
     }                                                                                                   \
     if ((i) == 4) dma_codes(c0, 2 * gi + 2);                                                            \
@@ -768,7 +782,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__
 #undef PF_STEP
 #undef PF_WAITV
 #undef PF_BAR
-#undef PF_LDS
   if (!busy) return;
   static_assert(XT * 1024 >= 32 * PF_STAGE_LD * 4 && NW == 4, "a slot holds a staged tile");
   pf_store<RBW, SWIGLU>(acc, PT, s, NRB, Npad, MT, act, rb0, mt0, tile_end, M, (float*)(w & 2 ? (w & 1 ? s3 : s2) : (w & 1 ? s1 : s0)));
