@@ -729,6 +729,27 @@ static int gemm(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int M,
   return EAGLE_OK;
 }
 
+template <int NRMAX, int MT>
+static hipError_t launch_wk(eagle_ctx* c, double bytes, const GemmWK& g) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_wk<NRMAX, MT>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  return launch_k(c, c->cur_class, bytes, "k_gemm_wk", k_gemm_wk<NRMAX, MT>, dim3(c->n_cu), dim3(256), (size_t)128 * 1024, g);
+}
+// act <- SwiGLU of X (M rows in MT row tiles) times the gate/up matrix, all of K in a work-group (plan_is_wk).
+static int gemm_wk(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, int M, bf16_t* act) {
+  const GemmWK g{w.w, XF, w.NRB, w.KS, M, act};
+  const double bytes = w.bytes(c->elt);
+  const int nrmax = (w.NRB + c->n_cu - 1) / c->n_cu;
+  if (nrmax < 3 || nrmax > 4 || (nrmax == 4 && MT != 2) || w.KS % 4 || M <= 32 * (MT - 1) || M > 32 * MT) return fail(EAGLE_EINVAL, "internal: no whole-K plan for %d row blocks and %d rows", w.NRB, M);
+  hipError_t e = nrmax == 4 ? launch_wk<4, 2>(c, bytes, g) : MT == 2 ? launch_wk<3, 2>(c, bytes, g) : MT == 3 ? launch_wk<3, 3>(c, bytes, g) : launch_wk<3, 4>(c, bytes, g);
+  if (e != hipSuccess) return fail(EAGLE_EHIP, "gemm launch failed: %s", hipGetErrorString(e));
+  return EAGLE_OK;
+}
+
 // Reads the event pairs of the launches timed since the last call (the stream must have been synchronised).
 static int collect_gemm_events(eagle_ctx* c) {
   for (size_t i = 0; i < c->timed.size(); ++i) {
@@ -881,7 +902,11 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
     }
     return EAGLE_OK;
   }
-  if ((rc = (c->cur_class = KC_GATEUP, gemm(c, w.gu, c->xf_d, MT, M, &S, c->xf_ffn)))) return rc;
+  c->cur_class = KC_GATEUP;
+  if (plan_is_wk(w.gu.NRB, MT, c->n_cu, c->big_gemm, c->fixed_sums, c->q4)) {
+    if ((rc = gemm_wk(c, w.gu, c->xf_d, MT, M, c->xf_ffn))) return rc;
+    S = 0;
+  } else if ((rc = gemm(c, w.gu, c->xf_d, MT, M, &S, c->xf_ffn))) return rc;
   if (S > 0) {
     dim3 grid((F / 16 + 3) / 4, MT);
     k_swiglu<<<grid, 256, 0, c->stream>>>(c->PT, S, w.gu.Npad, MT * 32, F, M, c->xf_ffn, MT, c->NXP);

@@ -1074,6 +1074,140 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   TRACE_STAMP(tr, 4);
 }
 
+// ---- whole-K gate/up of passes of 33 to 128 rows --------------------------------------------------------------------------------
+// The structure of k2_gemm_fk with MT 32-row tiles of activations: a work-group owns up to NRMAX row blocks over all of K, its four
+// waves (one a SIMD: the sums of NRMAX x MT tiles take up to 192 registers) split K, weights HBM -> VGPR -> MFMA, activation fragments
+// straight from L2, sums through LDS, SwiGLU on them.  No partial sums in memory and no SwiGLU launch behind it.
+// A CU fetches weights from HBM and activations from L2 through one queue of about 38 KB in request order, so that a short L2 access
+// waits behind the long HBM access in front of it: 48 B/ns a CU with the two interleaved by the tile, 66 in segments of 32 KB and
+// 64 KB.  Hence the order here: the weights of four k-steps in one burst, all waves at once (the barrier), then activations only.
+// 104 rows at 7B widths, us: k_gemm_pf with two K slices and k_swiglu 51.4 + 8.4; this 56.3 with weights and activations requested
+// step by step, 54.0 in bursts; 55 rows 44.1 + 6.1 / 42.3 / 40.5.  Bound: the same queue (0.7 + 1.4 MB a CU) beside 25 to 30 us of MFMA.
+// QKV (1.5 row blocks a CU) measured no better this way than k_gemm_pf and k_qkv_rope_store.
+struct GemmWK { const bf16_t *W, *XF; int NRB, KS, M; bf16_t* act /*[plane][tile][NRB k-steps]*/; };
+template <int NR, int MT, int NRMAX>
+__device__ __forceinline__ void wk_stream(const GemmWK& g, int kb, int ke, const FkWeights<1>& fw, f32x16 (&acc)[NRMAX][MT], int lane) {
+  constexpr int XD = 4;                                         // k-steps of activations in flight
+  const int KS = g.KS;
+  u32x4 ta[2][4][NR], tb[XD][2][MT];
+  const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)g.XF, 0, 2 * MT * KS * 1024, 0x00020000);
+  const uint32_t xlane = (uint32_t)lane * 16u, xlast = 32 * (MT - 1) + (lane & 31) < g.M ? xlane : OUT_OF_RANGE;   // dead rows of the last tile
+  auto load_w = [&](int b, int k) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NR; ++j) ta[b][i][j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(fw.rs[0], fw.vo[j], (uint32_t)(j * KS + min(k + i, ke - 1)) * 1024u, 2));
+  };
+  auto load_x = [&](int s, int k) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) tb[s][q][t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, t == MT - 1 ? xlast : xlane, (uint32_t)((q * MT + t) * KS + k) * 1024u, 0));
+  };
+  auto mul = [&](int b, int i, int s) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int j = 0; j < NR; ++j)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+          acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ta[b][i][j]), __builtin_bit_cast(bf16x8, tb[s][q][t]), acc[j][t], 0, 0, 0);
+  };
+  load_w(0, kb);
+#pragma unroll
+  for (int i = 0; i < XD; ++i) load_x(i, min(kb + i, ke - 1));
+  int k = kb;
+  for (; k + 8 + XD <= ke; k += 8) {                            // (as often in every wave: the four K ranges are equally long)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      load_w(b ^ 1, k + 4 * b + 4);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        mul(b, i, (4 * b + i) % XD);
+        load_x((4 * b + i) % XD, k + 4 * b + i + XD);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  for (; k < ke; k += 8) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (k + 4 * b + 4 < ke) load_w(b ^ 1, k + 4 * b + 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (k + 4 * b + i < ke) mul(b, i, (4 * b + i) % XD);
+        if (k + 4 * b + i + XD < ke) load_x((4 * b + i) % XD, k + 4 * b + i + XD);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+}
+template <int NRMAX, int MT>
+__global__ __launch_bounds__(256, 1) void k_gemm_wk(GemmWK g) {
+  constexpr int UNITS = NRMAX * MT, ROUNDS = (UNITS + 3) / 4;
+  extern __shared__ __attribute__((aligned(16))) float wk_red[];    // [2][4 units][4 waves][4][64 lanes][4]
+  const int lane = threadIdx.x & 63, w = wave_id(), hh = lane >> 5;
+  const unsigned G = gridDim.x;
+  const int rb0 = (unsigned)blockIdx.x * (unsigned)g.NRB / G, rb1 = (unsigned)(blockIdx.x + 1) * (unsigned)g.NRB / G, nr = rb1 - rb0;   // NRMAX - 1 or NRMAX (host)
+  const int kq = g.KS / 4, kb = w * kq, ke = kb + kq;           // KS: a multiple of 4 (host)
+  f32x16 acc[NRMAX][MT];
+#pragma unroll
+  for (int j = 0; j < NRMAX; ++j)
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
+  const FkWeights<1> fw = fk_weights<1>(g.W, 0, rb0, nr, g.KS, lane);
+  if (nr == NRMAX) wk_stream<NRMAX, MT>(g, kb, ke, fw, acc, lane);
+  else wk_stream<NRMAX - 1, MT>(g, kb, ke, fw, acc, lane);
+  // Four units (row block, row tile) at a time: every wave parks its sums of them, wave v adds unit v's in wave order and finishes it.
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    float* buf = wk_red + (r & 1) * 16384;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int u = 4 * r + v;
+      if (u >= UNITS) continue;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = acc[u / MT][u % MT][4 * i + e];
+        *(f32x4*)(buf + ((size_t)((v * 4 + w) * 4 + i) * 64 + lane) * 4) = x;
+      }
+    }
+    __syncthreads();                                            // (the other half of wk_red is free: its readers came through here)
+    const int u = 4 * r + w, j = u / MT, t = u % MT, rb = rb0 + j;
+    if (u >= UNITS || j >= nr) continue;
+    const float* mine = buf + w * 4096;
+    float x[16];                                                // register 4i + e: weight row 8i + 4hh + e of the block, token lane % 32 of the tile
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 a = *(const f32x4*)(mine + ((size_t)i * 64 + lane) * 4);
+#pragma unroll
+      for (int ww = 1; ww < 4; ++ww) a += *(const f32x4*)(mine + ((size_t)(ww * 4 + i) * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[4 * i + e] = a[e];
+    }
+    // registers e and e + 8 are gate and up of one feature; the two lanes of a row swap four values so that each holds 8 in a row
+    const int m = 32 * t + (lane & 31);
+    float v[8], y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = m < g.M ? x[e] / (1.0f + __expf(-x[e])) * x[e + 8] : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float got = __shfl_xor(hh ? v[e] : v[4 + e], 32, 64);
+      y[e] = hh ? got : v[e];
+      y[4 + e] = hh ? v[4 + e] : got;
+    }
+    xf_store8(g.act, m, 16 * rb + 8 * hh, MT, g.NRB, 2, y);
+  }
+}
+
 // ---- split-K with streamed activations (narrow matrices with a long K: O, down) ------------------------------------------
 // The split-K kernel above keeps its X slice in LDS, so a long K forces many slices (11 at K = 11008) and the last
 // work-group of a row group reads that many partials on one CU.  Here the slice is streamed from L2 like in the

@@ -34,6 +34,15 @@ static inline GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
 // keep their order (fixed_sums); with 4-bit weights all.
 static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool q4) { return MT > 4 || (MT >= (fixed_sums ? 3 : 2) && big_gemm) || q4; }
 
+// Which gate/up products of 33 to 128 rows run over all of K in a work-group (k_gemm_wk; plan_pf otherwise): dense bf16 models whose
+// sums are not fixed, with three row blocks on the busiest CU, or four and at most 64 rows.  (With fewer the activations that every
+// work-group fetches outweigh what the K slices cost; with four and more rows the CUs that have three idle for a quarter of the time.
+// Requests with four / three / two sequences and the 26-node tree, ms, K slices / whole K: 7B widths, 8 layers (2.7 row blocks a CU)
+// 36.3 / 35.1, 33.4 / 31.9, 29.8 / 28.3; 13B widths, 6 layers (3.4) four 40.1 / 41.7, two 33.1 / 31.9.)
+static inline bool plan_is_wk(int NRB, int MT, int n_cu, bool big_gemm, bool fixed_sums, bool q4) {
+  return big_gemm && !fixed_sums && !q4 && MT >= 2 && MT <= 4 && NRB > 2 * n_cu && NRB <= (MT == 2 ? 4 : 3) * n_cu;
+}
+
 // Which prompt passes take the attention kernel of 128 rows a work-group (k2_attn_prompt) instead of the one of 32 (k2_attn): those
 // whose small work-groups would go through the chip at least twice.  (Where they all fit at once, the run of tiles of one work-group
 // is what counts, and with few rows most of a 128-row block is padding.)  us a launch, 32 / 128 rows: 32 heads, 256 rows 16 / 22, 384
