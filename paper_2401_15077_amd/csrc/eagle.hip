@@ -126,7 +126,7 @@ struct eagle_ctx {
   bf16_t *xf_d, *xf_2d, *xf_att, *xf_ffn;
   size_t pt_floats;
   // fast path (passes of <= 32 rows)
-  float *h2, *PT2, *ssq1, *ssq2; int *cnt_gemm, *cnt_attn; size_t pt2_floats;
+  float *h2, *PT2, *ssq1, *ssq2; int *cnt_gemm, *cnt_attn; size_t pt2_floats, pt2_all;   // of one launch's plan, of the buffer
   bf16_t *xf2_d, *xf2_dB, *xf2_2d, *xf2_att, *xf2_ffn;
   float* group_sums;                   // 4-bit weights: -24 * sum of x per (group of 128 columns, row) of the GEMM input at hand
   // grouped experts (general path of the bf16 models): which rows go to which expert, the gathered rows and their MLP inputs
@@ -220,6 +220,23 @@ static void take_packed(Arena& a, PackedW& w, int N, int K, int NWP, bool q4 = f
 }
 
 // Lays the context's buffers out in the workspace (or just measures when c->ws == nullptr).
+// Streamed split-K plan of a matrix on the fast path; S = 0 where the fetch model prices the LDS-staged kernel (plan2) lower.
+static PlanXK xk_plan(const eagle_ctx* c, const PackedW& w) {
+  const Plan2 p = plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4);
+  PlanXK px = plan_xk(w.NRB, w.KS, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
+  const int R = (w.NRB + p.groups - 1) / p.groups, kt_s = (w.KS + p.S - 1) / p.S;
+  const long staged = (long)R * kt_s + (long)c->NXP * kt_s + 2L * p.S * R * 4 + 40;
+  if (px.S > 0 && px.cost >= staged) px.S = 0;
+  return px;
+}
+// Mixture of experts on the fast path: all experts' gate/up in one launch and all their downs in another, where those are the whole-K and
+// the streamed split-K kernel (wide matrices).  Two launches an expert are sixteen a layer with eight experts, each with its own first
+// tiles, drain and (down) exchange, and most of them for nothing in the head's passes of a few rows: @@.
+static bool moe_in_two(const eagle_ctx* c, const PackedW& gu, const PackedW& dn) {
+  return c->cfg.n_experts > 1 && c->big_gemm && gu.NRB >= c->n_cu && !plan_is_whole_k(gu.NRB, gu.KS, c->NWP + c->NXP, c->n_cu) &&
+         !plan_is_whole_k(dn.NRB, dn.KS, c->NWP + c->NXP, c->n_cu) && xk_plan(c, dn).S > 0;
+}
+
 static size_t layout(eagle_ctx* c) {
   const eagle_config& g = c->cfg;
   Arena a(c->ws);
@@ -314,7 +331,7 @@ static size_t layout(eagle_ctx* c) {
   c->xn = a.take<float>(g.n_experts > 0 ? (size_t)Mm * d : 8);
   c->xf2_2d = a.take<bf16_t>((size_t)c->NXP * 32 * 2 * d);
   c->xf2_att = a.take<bf16_t>((size_t)c->NXP * 32 * H * dh);
-  c->xf2_ffn = a.take<bf16_t>((size_t)c->NXP * 32 * F);
+  c->xf2_ffn = a.take<bf16_t>((size_t)c->NXP * 32 * F * (grouped ? std::max(1, g.n_experts) : 1));
   c->facts = a.take<RowFact>(Mm);
   c->ssq1 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32); c->ssq2 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32);
   c->trace = a.take<unsigned long long>(1024 * 8);
@@ -330,6 +347,10 @@ static size_t layout(eagle_ctx* c) {
     if (w.moe) { consider2(w.e_gu[0]); consider2(w.e_dn[0]); } else { consider2(w.gu); consider2(w.dn); }
   }
   c->pt2_floats = worst2;
+  // (all experts of a layer in one launch: the slices of each)
+  for (auto& w : c->layers)
+    if (w.moe && moe_in_two(c, w.e_gu[0], w.e_dn[0])) { worst2 = std::max(worst2, (size_t)g.n_experts * xk_plan(c, w.e_dn[0]).S * w.e_dn[0].Npad * 32); break; }
+  c->pt2_all = worst2;
   c->PT2 = a.take<float>(worst2);
   // scratch that every pass writes before it reads (not cleared by eagle_init)
   c->zero_end = a.off;
@@ -991,17 +1012,17 @@ static hipError_t launch_k2(eagle_ctx* c, double bytes, const Gemm2& g, size_t l
   return launch_k(c, c->cur_class, bytes, Q4 ? "k2_gemm<4-bit weights>" : "k2_gemm", k2_gemm<NWP, NXP, RW, DEPTH, Q4>, dim3(g.groups * g.S), dim3(V2_THREADS), lds, g);
 }
 
-template <int NRMAX, bool HALF = false, int NWP = 1, int NXP = 2>
-static hipError_t launch_fk(eagle_ctx* c, double bytes, const Gemm2& g, int grid) {
+template <int NRMAX, bool HALF = false, int NWP = 1, int NXP = 2, bool EXPERTS = false>
+static hipError_t launch_fk(eagle_ctx* c, double bytes, const Gemm2& g, int grid, int experts = 1) {
   static bool attr_set = false;
   const size_t lds = (size_t)8 * NRMAX * 4096;
   if (lds > 144 * 1024) return hipErrorInvalidValue;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<NWP, NXP, NRMAX, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<NWP, NXP, NRMAX, HALF, false, EXPERTS>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  return launch_k(c, c->cur_class, bytes, HALF ? "k2_gemm_fk<half blocks>" : "k2_gemm_fk", k2_gemm_fk<NWP, NXP, NRMAX, HALF>, dim3(grid), dim3(V2_THREADS), lds, g);
+  return launch_k(c, c->cur_class, bytes, HALF ? "k2_gemm_fk<half blocks>" : "k2_gemm_fk", k2_gemm_fk<NWP, NXP, NRMAX, HALF, false, EXPERTS>, dim3(grid, experts), dim3(V2_THREADS), lds, g);
 }
 
 template <int NRMAX>
@@ -1017,16 +1038,16 @@ static hipError_t launch_fk_q4(eagle_ctx* c, double bytes, const Gemm2& g, int g
   return launch_k(c, c->cur_class, bytes, "k2_gemm_fk<4-bit weights>", k2_gemm_fk<1, 2, NRMAX, false, true>, dim3(grid), dim3(V2_THREADS), lds, g);
 }
 
-template <int NRMAX>
-static hipError_t launch_xk(eagle_ctx* c, double bytes, const Gemm2& g) {
+template <int NRMAX, bool EXPERTS = false>
+static hipError_t launch_xk(eagle_ctx* c, double bytes, const Gemm2& g, int experts = 1) {
   static bool attr_set = false;
   const size_t lds = (size_t)8 * NRMAX * 4096;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_xk<1, 2, NRMAX>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_xk<1, 2, NRMAX, false, EXPERTS>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  return launch_k(c, c->cur_class, bytes, "k2_gemm_xk", k2_gemm_xk<1, 2, NRMAX>, dim3(g.groups * g.S), dim3(V2_THREADS), lds, g);
+  return launch_k(c, c->cur_class, bytes, "k2_gemm_xk", k2_gemm_xk<1, 2, NRMAX, false, EXPERTS>, dim3(g.groups * g.S, experts), dim3(V2_THREADS), lds, g);
 }
 
 template <int NRMAX>
@@ -1057,7 +1078,7 @@ static PlanXK plan_xk_q4(int NRB, int NG, int NXP, int n_cu, size_t pt_floats_pe
 }
 
 // Runs one fused GEMM: g carries the epilogue description; the matrix, the input and the work split are filled here.
-static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int* groups_out) {
+static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int* groups_out, int experts = 1) {
   Plan2 p = plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4);
   const int R = (w.NRB + p.groups - 1) / p.groups;
   if ((R + p.lanes - 1) / p.lanes > p.RW) return fail(EAGLE_EINVAL, "internal: %d row blocks per wave exceed the kernel's %d", (R + p.lanes - 1) / p.lanes, p.RW);
@@ -1069,7 +1090,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   g.trace = (c->gemm_no++ == c->trace_sel && p.groups * p.S <= 1024) ? c->trace : nullptr;
   if (g.ssq_out && p.groups > PLAN_MAX_NORM_GROUPS) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
   if (groups_out) *groups_out = p.groups;
-  const double bytes = w.bytes(c->elt);
+  const double bytes = w.bytes(c->elt) * experts;
   hipError_t e;
   if (w.q4 && ((c->q4_xk_mask >> g.epi) & 1)) {
     const PlanXK px = plan_xk_q4(w.NRB, w.NG, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
@@ -1122,12 +1143,9 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   // other matrices of the bf16 configuration: split-K, with the activations either staged in LDS (plan2) or streamed
   // (plan_xk), whichever the fetch model prices lower
   PlanXK px; px.S = 0;
-  if (!fullk && !c->f32) {
-    px = plan_xk(w.NRB, w.KS, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
-    const int kt_s = (w.KS + p.S - 1) / p.S;
-    const long staged = (long)R * kt_s + (long)c->NXP * kt_s + 2L * p.S * R * 4 + 40;
-    if (px.S > 0 && px.cost >= staged) px.S = 0;
-  }
+  if (!fullk && !c->f32) px = xk_plan(c, w);
+  if (experts > 1 && (small || !(g.epi == EPI_RESID ? px.S > 0 : fullk && g.epi == EPI_SWIGLU))) return fail(EAGLE_EINVAL, "internal: this plan takes one expert a launch");
+  if (experts > 1) g.trace = nullptr;
   if (small) {
     if (groups_out) *groups_out = w.NRB;
     g.trace = nullptr;
@@ -1136,7 +1154,9 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     g.S = px.S; g.groups = px.groups;
     if (groups_out) *groups_out = px.groups;
     g.trace = (g.trace && px.groups * px.S <= 1024) ? g.trace : nullptr;
-    e = px.nrmax <= 2 ? launch_xk<2>(c, bytes, g) : px.nrmax == 3 ? launch_xk<3>(c, bytes, g) : launch_xk<4>(c, bytes, g);
+    if ((size_t)experts * px.S * w.Npad * 32 > c->pt2_all) return fail(EAGLE_EINVAL, "internal: fast-path partial buffer too small");
+    if (experts > 1) e = px.nrmax <= 2 ? launch_xk<2, true>(c, bytes, g, experts) : px.nrmax == 3 ? launch_xk<3, true>(c, bytes, g, experts) : launch_xk<4, true>(c, bytes, g, experts);
+    else e = px.nrmax <= 2 ? launch_xk<2>(c, bytes, g) : px.nrmax == 3 ? launch_xk<3>(c, bytes, g) : launch_xk<4>(c, bytes, g);
   } else if (fullk) {
     const int grid = fk_grid;
     if (groups_out) *groups_out = grid;
@@ -1147,6 +1167,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     const int umax = (2 * w.NRB + grid - 1) / grid;
     const bool half = g.epi == EPI_QKV && umax < 2 * nrmax && umax / 2 + 1 <= 2;
     if (half) e = launch_fk<2, true>(c, bytes, g, grid);
+    else if (experts > 1) e = nrmax <= 2 ? launch_fk<2, false, 1, 2, true>(c, bytes, g, grid, experts) : nrmax == 3 ? launch_fk<3, false, 1, 2, true>(c, bytes, g, grid, experts) : launch_fk<4, false, 1, 2, true>(c, bytes, g, grid, experts);
     else e = nrmax <= 2 ? launch_fk<2>(c, bytes, g, grid) : nrmax == 3 ? launch_fk<3>(c, bytes, g, grid) : launch_fk<4>(c, bytes, g, grid);
   } else if (c->f32) {
     switch (p.RW) {
@@ -1220,15 +1241,20 @@ static int layer2(eagle_ctx* c, const Pass& pass, int M, int li, int ctx_max, in
                                        cf.experts_per_tok, d, M, c->moe_w, c->Mmax, c->expert_used);
     LAUNCH_CHECK();
     if (c->prof_mode) { k_count_used<<<1, 64, 0, c->stream>>>(c->expert_used, E, c->experts_touched); LAUNCH_CHECK(); }
-    for (int e = 0; e < E; ++e) {
+    // All experts in two launches where both matrices are large (moe_in_two); else two launches an expert.
+    const bool two = moe_in_two(c, w.e_gu[0], w.e_dn[0]);
+    const size_t act = (size_t)c->NXP * 32 * F;
+    for (int e = 0; e < (two ? 1 : E); ++e) {
       g = gemm2_base(c, M);
       g.epi = EPI_SWIGLU; g.in_scale = scale_of(c, c->ssq1, c->ssq1_groups); g.xf_out = c->xf2_ffn; g.xf_KS = F / 16;
       g.skip_flag = c->expert_used + e;
-      if ((rc = (c->cur_class = KC_GATEUP, gemm2(c, w.e_gu[e], c->xf2_d, g, nullptr)))) return rc;
+      if (two) { g.w_stride = (size_t)(w.e_gu[1].w - w.e_gu[0].w); g.out_stride = act; }
+      if ((rc = (c->cur_class = KC_GATEUP, gemm2(c, w.e_gu[e], c->xf2_d, g, nullptr, two ? E : 1)))) return rc;
       g = gemm2_base(c, M);
       g.epi = EPI_RESID; g.h_in = c->h2; g.h_out = c->h2; g.gain_next = next_gain; g.xf_out = c->xf2_dB; g.xf_KS = d / 16; g.ssq_out = c->ssq2;
       g.row_w = c->moe_w + (size_t)e * c->Mmax; g.skip_flag = c->expert_used + e;
-      if ((rc = (c->cur_class = KC_DOWN, gemm2(c, w.e_dn[e], c->xf2_ffn, g, &c->ssq2_groups)))) return rc;
+      if (two) { g.w_stride = (size_t)(w.e_dn[1].w - w.e_dn[0].w); g.x_stride = act; g.row_w_stride = c->Mmax; }
+      if ((rc = (c->cur_class = KC_DOWN, gemm2(c, w.e_dn[e], c->xf2_ffn, g, &c->ssq2_groups, two ? E : 1)))) return rc;
     }
     std::swap(c->xf2_d, c->xf2_dB);     // the experts all read the old xf2_d; the new one was built beside it
     return EAGLE_OK;

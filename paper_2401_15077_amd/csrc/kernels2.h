@@ -150,7 +150,9 @@ struct Gemm2 {
   Q4Format q4;                            // 4-bit weights: how a code becomes a bf16 value
   const bf16_t* SC; int NG;               // 4-bit weights: scales [NRB][NG][2][16] and groups along K (W then holds codes)
   const float* row_w;                     // MoE: per-row routing weight applied to this GEMM's result (nullptr = 1)
-  const int* skip_flag;                   // MoE: the whole launch is a no-op when *skip_flag == 0 (no row uses the expert)
+  const int* skip_flag;                   // MoE: an expert's work is a no-op when its flag is 0 (no row uses it); [gridDim.y] with EXPERTS
+  // EXPERTS (all experts of a layer in one launch, gridDim.y of them): elements between their matrices, inputs and outputs, and between their routing weights
+  size_t w_stride, x_stride, out_stride; int row_w_stride;
   unsigned long long* trace;              // profiling builds (-DEAGLE_TRACE) only: [work-group][8] time stamps of this launch
 };
 
@@ -285,12 +287,14 @@ __device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float*
 // four; residual, bias, gain and the partials come as 16-byte loads, all in flight together.  (A lane per chunk and token, row by
 // row, used half of the threads and touched 64 lines with each of its 16 four-byte accesses.)  A token's squares are added
 // chunk by chunk in row order, chunks c, c + 16, ... in one chain: the lower lanes begin a chunk's part, the upper ones go on.
-template <int NXP>
-__device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, float* sh /*>= 16*32 floats*/) {
+// EXPERTS: the partials of every expert in `used` (g.S slices each), added per row in expert order with the routing weights, as one
+// launch per expert behind the other would.
+template <int NXP, bool EXPERTS = false>
+__device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, float* sh /*>= 16*32 floats*/, unsigned long long used = 1) {
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5, w = threadIdx.x >> 6;
   const bool live = m < g.M;
   const int nchunks = (n1 - n0) >> 3;                        // n0 and n1 are multiples of 32 (d_model is one of 64)
-  const float rw = g.row_w ? g.row_w[m] : 1.0f;
+  const float rw = !EXPERTS && g.row_w ? g.row_w[m] : 1.0f;
   float ss[2] = {0.f, 0.f};                                  // chains w and w + 8
   int turn = 0;
   for (int c = w; c < nchunks; c += V2_THREADS / 64, turn ^= 1) {
@@ -300,18 +304,46 @@ __device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, f
     const f32x4 bv = g.bias ? *(const f32x4*)(g.bias + n) : zero;
     const f32x4 gv = g.gain_next ? *(const f32x4*)(g.gain_next + n) : zero;
     f32x4 v = zero;
-    for (int s0 = 0; s0 < g.S; s0 += 8) {                    // added in split order
-      f32x4 p[8];
+    if constexpr (EXPERTS) {
+      v = hv;
+      for (unsigned long long left = used; left; ) {           // four experts' first four slices in flight at once
+        int ex[4], cnt = 0;
+        f32x4 p[4][4];
+        float re[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (u < 4 || g.S > 4) p[u] = coh_load16(g.PT, pt_quad_bytes(min(s0 + u, g.S - 1), g.Npad, n, m));
+        for (int b = 0; b < 4; ++b) {
+          ex[b] = __ffsll((long long)(left ? left : used)) - 1;
+          cnt += left != 0;
+          left &= left - 1;
+          re[b] = g.row_w[(size_t)ex[b] * g.row_w_stride + m];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (s0 + u < g.S) v += p[u];
+          for (int u = 0; u < 4; ++u) p[b][u] = coh_load16(g.PT, pt_quad_bytes(ex[b] * g.S + min(u, g.S - 1), g.Npad, n, m));
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          if (b >= cnt) continue;
+          f32x4 sum = zero;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) if (u < g.S) sum += p[b][u];
+          for (int u = 4; u < g.S; ++u) sum += coh_load16(g.PT, pt_quad_bytes(ex[b] * g.S + u, g.Npad, n, m));
+          sum *= re[b];
+          v = sum + v;
+        }
+      }
+    } else {
+      for (int s0 = 0; s0 < g.S; s0 += 8) {                  // added in split order
+        f32x4 p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (u < 4 || g.S > 4) p[u] = coh_load16(g.PT, pt_quad_bytes(min(s0 + u, g.S - 1), g.Npad, n, m));
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (s0 + u < g.S) v += p[u];
+      }
+      if (g.row_w) v *= rw;
+      if (g.bias) v += bv;
+      if (g.h_in && live) v += hv;
     }
-    if (g.row_w) v *= rw;
-    if (g.bias) v += bv;
-    if (g.h_in && live) v += hv;
     if (live) *(f32x4*)(g.h_out + (size_t)m * g.d + n) = v;
     float a = turn ? ss[1] : ss[0];
     float up = a;
@@ -919,7 +951,7 @@ __device__ __forceinline__ f32x4 fk_sum4(const float* red, int nrmax, int j, int
 // each).  A work-group then owns a run of halves; of a block it shares with a neighbour it loads and finishes only its own
 // 16 rows (the other lanes of the tile load nothing and multiply zeros).  Rotate-half pairs are adjacent rows, so a half
 // holds whole pairs.  Epilogue: QKV.
-template <int NWP, int NXP, int NRMAX, bool HALF = false, bool Q4 = false>
+template <int NWP, int NXP, int NRMAX, bool HALF = false, bool Q4 = false, bool EXPERTS = false>
 __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   static_assert(!Q4 || (!HALF && NWP == 1), "4-bit weights: whole row blocks, one plane");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -930,7 +962,8 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   EarlyLoads el;                                                // used by the epilogue, much later
   constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
   if constexpr (!LATE) early_issue(g.in_scale, g.facts, el);
-  if (g.skip_flag && *g.skip_flag == 0) return;                 // MoE: no row selected this expert (uniform over the grid)
+  if (g.skip_flag && g.skip_flag[EXPERTS ? blockIdx.y : 0] == 0) return;   // MoE: no row selected this expert (uniform over its work-groups)
+  if constexpr (EXPERTS) { g.W += blockIdx.y * g.w_stride; g.xf_out += blockIdx.y * g.out_stride; }
   const int lane = threadIdx.x & 63, w = wave_id();
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
@@ -1216,7 +1249,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_wk(GemmWK g) {
 // S x (row blocks) x 4 KiB per row group, and nothing waits for an LDS fill before the weight stream starts.
 // Partials, arrival counter and epilogues are those of k2_gemm.
 // Q4: 4-bit codes (k_pack_weight_q4); the slices are then whole groups of 128 columns (host: at least 8 groups a slice).
-template <int NWP, int NXP, int NRMAX, bool Q4 = false>
+template <int NWP, int NXP, int NRMAX, bool Q4 = false, bool EXPERTS = false>
 __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   static_assert(!Q4 || NWP == 1, "4-bit weights: one plane");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1228,7 +1261,12 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   EarlyLoads el;                                                // used by the epilogue, much later
   constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
   if constexpr (!LATE) early_issue(g.in_scale, g.facts, el);
-  if (g.skip_flag && *g.skip_flag == 0) return;                 // uniform over the whole grid
+  if (g.skip_flag && g.skip_flag[EXPERTS ? blockIdx.y : 0] == 0) return;   // uniform over the expert's work-groups
+  unsigned long long used = 1;                                  // the experts of this launch that some row selected
+  if constexpr (EXPERTS) {
+    used = __ballot((threadIdx.x & 63) < gridDim.y && g.skip_flag[min(threadIdx.x & 63, gridDim.y - 1)] != 0);
+    g.W += blockIdx.y * g.w_stride; g.XF += blockIdx.y * g.x_stride;
+  }
   const int lane = threadIdx.x & 63, w = wave_id();
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
@@ -1265,14 +1303,14 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ww = 0; ww < 8; ++ww) o += *(const f32x4*)(red + ((((size_t)ww * NRMAX + j) * 4 + i) * 64 + lane) * 4);
-    coh_store16(g.PT, pt_quad_bytes(s, g.Npad, (rb0 + j) * 32 + 8 * i + 4 * (lane >> 5), lane & 31), o);
+    coh_store16(g.PT, pt_quad_bytes(EXPERTS ? (int)(blockIdx.y * uS) + s : s, g.Npad, (rb0 + j) * 32 + 8 * i + 4 * (lane >> 5), lane & 31), o);
   }
   TRACE_STAMP(tr, 3);
   publish_wait();
   __syncthreads();
   if (threadIdx.x == 0) {
     int old = __hip_atomic_fetch_add(g.counters + grp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (old == g.S - 1);
+    s_last = (old == (EXPERTS ? g.S * __popcll(used) : g.S) - 1);
     if (s_last) __hip_atomic_store(g.counters + grp, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
@@ -1283,7 +1321,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   if (g.epi != EPI_RESID) block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);
   switch (g.epi) {
     case EPI_QKV: epilogue_qkv<NXP>(g, n0, n1, rstd_s, el); break;
-    case EPI_RESID: epilogue_resid<NXP>(g, grp, n0, n1, sh_small); break;
+    case EPI_RESID: epilogue_resid<NXP, EXPERTS>(g, grp, n0, n1, sh_small, used); break;
     case EPI_SWIGLU: epilogue_swiglu<NXP>(g, n0, n1, rstd_s); break;
     default: epilogue_logits(g, n0, n1, rstd_s, el); break;
   }
