@@ -750,12 +750,12 @@ __device__ __forceinline__ FkWeights<NWP> fk_weights(const bf16_t* W, size_t wps
 }
 
 template <int NWP, int NXP, int NR, int DEPTH>
-__device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS, int M, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
+__device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
   constexpr int PMAX = NWP > NXP ? NWP : NXP;
   if (ke <= kb) return;
   u32x4 ta[DEPTH][NR][NWP], tb[DEPTH][NXP];
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, NXP * KS * 1024, 0x00020000);
-  const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : OUT_OF_RANGE;  // dead rows
+  const uint32_t xlane = row ? (uint32_t)lane * 16u : OUT_OF_RANGE;   // row: this lane's activation row is wanted
   // Weights non-temporal: a weight byte is used once per pass and a pass's weights exceed every cache, so keeping them out leaves the L2s
   // to the activations (7B, LLaMA shapes, us before / after: gate/up 36.5 / 34.5, LM head 49.0 / 45.0, QKV 25.4 / 23.9; a bare
   // read of 2 GB runs at 6.9 TB/s with the hint and 6.25 without).  The 4-bit and fp32 streams keep plain loads: their head fits
@@ -812,10 +812,10 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
     if (k + dd < ke) mul(dd);
 }
 template <int NWP, int NXP, int NR>
-__device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, int M, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
+__device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
   constexpr int DEPTH = NWP == 1 ? (NR == 1 ? 8 : NR == 2 ? 6 : NR == 3 ? 5 : 4) : NR == 1 ? 4 : 2;   // ~24 KiB in flight per wave; deeper measured the same
-  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, M, kb, ke, fw, acc, lane);
-  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, M, kb, ke, fw, acc, lane);
+  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, row, kb, ke, fw, acc, lane);
+  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, row, kb, ke, fw, acc, lane);
 }
 
 // ---- the same stream over 4-bit weights (see k_pack_weight_q4 for the layout) -------------------------------------------
@@ -965,6 +965,8 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   if (g.skip_flag && g.skip_flag[EXPERTS ? blockIdx.y : 0] == 0) return;   // MoE: no row selected this expert (uniform over its work-groups)
   if constexpr (EXPERTS) { g.W += blockIdx.y * g.w_stride; g.xf_out += blockIdx.y * g.out_stride; }
   const int lane = threadIdx.x & 63, w = wave_id();
+  bool row = (lane & 31) < g.M;                                 // dead rows (and, here, rows that did not select the expert) are not fetched
+  if constexpr (EXPERTS) row = row && g.row_w[(size_t)blockIdx.y * g.row_w_stride + (lane & 31)] != 0.f;
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
   const unsigned G = gridDim.x;
@@ -993,7 +995,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
     fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, rb0, nr, g.KS), sq, g.NG, acc, lane);
     if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
-  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane, row_lo, row_hi), acc, lane);
+  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, row, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane, row_lo, row_hi), acc, lane);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
   // residual epilogue: what the first item of a thread adds and multiplies, requested before the sums
   f32x4 rh = {0.f, 0.f, 0.f, 0.f}, rbias = rh, rgain = rh;
@@ -1268,6 +1270,8 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
     g.W += blockIdx.y * g.w_stride; g.XF += blockIdx.y * g.x_stride;
   }
   const int lane = threadIdx.x & 63, w = wave_id();
+  bool row = (lane & 31) < g.M;                                 // dead rows (and, here, rows that did not select the expert) are not fetched
+  if constexpr (EXPERTS) row = row && g.row_w[(size_t)blockIdx.y * g.row_w_stride + (lane & 31)] != 0.f;
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
   const unsigned uS = g.S, ugroups = g.groups, uNRB = g.NRB, uKS = g.KS;
@@ -1291,7 +1295,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
     fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, rb0, nr, g.KS), sq, g.NG, acc, lane);
     if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
   } else
-  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, g.M, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane), acc, lane);
+  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, row, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane), acc, lane);
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
