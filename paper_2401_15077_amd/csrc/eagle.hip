@@ -219,7 +219,6 @@ static void take_packed(Arena& a, PackedW& w, int N, int K, int NWP, bool q4 = f
   } else w.w = a.take<bf16_t>(w.plane_stride * NWP);
 }
 
-// Lays the context's buffers out in the workspace (or just measures when c->ws == nullptr).
 // Streamed split-K plan of a matrix on the fast path; S = 0 where the fetch model prices the LDS-staged kernel (plan2) lower.
 static PlanXK xk_plan(const eagle_ctx* c, const PackedW& w) {
   const Plan2 p = plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4);
@@ -231,14 +230,15 @@ static PlanXK xk_plan(const eagle_ctx* c, const PackedW& w) {
 }
 // Mixture of experts on the fast path: all experts' gate/up in one launch and all their downs in another, where those are the whole-K and
 // the streamed split-K kernel (wide matrices).  Two launches an expert are sixteen a layer with eight experts, each with its own first
-// tiles, drain and (down) exchange, and many of them for nothing in the head's
-// passes of a few rows.  In two, a row is fetched only for the experts it selected.  Mixtral widths, us a pass of one layer (verify and head
-// passes together): gate/up 264 in eight launches, 231 in one, 226 with the rows; down 161 / 133 / 124.
+// tiles, drain and (down) exchange, and many of them for nothing in the head's passes of a few rows.  In two, a row is fetched only for
+// the experts it selected.  Mixtral widths, us a pass of one layer (verify and head passes together): gate/up 264 in eight launches, 231
+// in one, 226 with the rows; down 161 / 133 / 124.
 static bool moe_in_two(const eagle_ctx* c, const PackedW& gu, const PackedW& dn) {
   return c->cfg.n_experts > 1 && c->big_gemm && gu.NRB >= c->n_cu && !plan_is_whole_k(gu.NRB, gu.KS, c->NWP + c->NXP, c->n_cu) &&
          !plan_is_whole_k(dn.NRB, dn.KS, c->NWP + c->NXP, c->n_cu) && xk_plan(c, dn).S > 0;
 }
 
+// Lays the context's buffers out in the workspace (or just measures when c->ws == nullptr).
 static size_t layout(eagle_ctx* c) {
   const eagle_config& g = c->cfg;
   Arena a(c->ws);
