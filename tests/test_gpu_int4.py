@@ -75,3 +75,38 @@ def test_int4_rejects_what_it_cannot_run():
     assert e.value.code == -1
     with pytest.raises(pkg.EagleError):
         pkg.Eagle(synth.SHAPES["mini-gqa"], *synth.TREES["B63"], max_seq=256, weight_bits=4)      # 63 rows per pass
+
+
+@pytest.mark.parametrize("shape_name, n_layers", [("mini-gqa", 2), ("llama2-7b", 1)])
+def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers):
+    """Five sequences, 30 rows in the verify pass; the pending token of the fourth (rows 18..23) has NaN for an embedding.  The others, rows
+    2..7 (16 rows beside them, sums of x in the same matrix instruction) among them, keep their bits.  The small model takes the kernels
+    that hold the activations in LDS for O and down, the large one for the LM head; the rest stream them."""
+    s = synth.SHAPES[shape_name].twin(n_layers)
+    par, rk = synth.TREES["chain5"]
+    W = dict(synth.iter_weights(s, 57, synth.device_fmt(s)))
+    eng = pkg.Eagle(s, par, rk, max_batch=5, max_seq=96, weight_bits=4)
+    others = [0, 1, 2, 4]
+
+    def verified(prompts):
+        eng.reset()
+        first = [eng.prefill(b, p) for b, p in enumerate(prompts)]
+        trees = eng.draft_tree()
+        eng.verify()
+        return first, trees, [eng.get_buffer(pkg.BUF_LOGITS, b) for b in range(5)]
+
+    eng.load_weights(W)
+    for seed in range(57, 77):                                  # until only the fourth sequence uses its pending token
+        prompts = [synth.prompt(seed, 24 + 3 * b, s.vocab, stream=b) for b in range(5)]
+        first, trees, clean = verified(prompts)
+        if all(first[3] not in p for p in prompts) and all(first[3] not in trees[b] for b in others):
+            break
+    else:
+        pytest.fail("no prompts of that kind")
+    W["embed"][first[3]] = 0x7FC0
+    eng.load_named("embed", W["embed"])
+    again, trees2, logits = verified(prompts)
+    assert again == first and np.isnan(logits[3]).all() and np.isfinite(clean[3]).all()
+    for b in others:
+        assert np.array_equal(trees[b], trees2[b]) and np.isfinite(clean[b]).all() and np.array_equal(clean[b], logits[b]), b
+    eng.close()
