@@ -692,15 +692,16 @@ static hipError_t launch_gemm_mt(eagle_ctx* c, const PackedW& w, const bf16_t* X
 }
 
 // The work-group tile of the plan, with or without the SwiGLU epilogue.
+template <int RBW, int MW, bool SWIGLU, bool PLAIN>
+static hipError_t launch_pf(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, const GemmPlan& p, bf16_t* swiglu_out, int M) {
+  return launch_k(c, c->cur_class, (double)w.N * w.K * c->elt, SWIGLU ? "k_gemm_pf<swiglu>" : "k_gemm_pf", k_gemm_pf<RBW, MW, SWIGLU, false, PLAIN>, dim3(pf_grid(w.NRB, MT, p)),
+                  dim3(128 * MW), (size_t)0, (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M, (const MoePlan*)nullptr, (size_t)0, 0);
+}
 template <int RBW, int MW>
 static hipError_t launch_pf(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, const GemmPlan& p, bf16_t* swiglu_out, int M) {
-  const int MQ = (MT + 2 * MW - 1) / (2 * MW), G = ((w.NRB + 2 * RBW - 1) / (2 * RBW)) * p.S;
-  const dim3 grid((G + 7) / 8 * 8 * MQ), block(128 * MW);
-  const double bytes = (double)w.N * w.K * c->elt;
-  if (swiglu_out) return launch_k(c, c->cur_class, bytes, "k_gemm_pf<swiglu>", k_gemm_pf<RBW, MW, true>, grid, block, (size_t)0,
-                                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M, (const MoePlan*)nullptr, (size_t)0, 0);
-  return launch_k(c, c->cur_class, bytes, "k_gemm_pf", k_gemm_pf<RBW, MW, false>, grid, block, (size_t)0,
-                  (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, (bf16_t*)nullptr, M, (const MoePlan*)nullptr, (size_t)0, 0);
+  if constexpr (MW <= 2)
+    if (plan_pf_plain_loads(w.NRB, MT, M, c->n_cu, p)) return swiglu_out ? launch_pf<RBW, MW, true, true>(c, w, XF, MT, p, swiglu_out, M) : launch_pf<RBW, MW, false, true>(c, w, XF, MT, p, nullptr, M);
+  return swiglu_out ? launch_pf<RBW, MW, true, false>(c, w, XF, MT, p, swiglu_out, M) : launch_pf<RBW, MW, false, false>(c, w, XF, MT, p, nullptr, M);
 }
 
 template <int RBW, int MW, bool SWIGLU>

@@ -511,7 +511,7 @@ __device__ __forceinline__ void buffer_to_lds16(__amdgpu_buffer_rsrc_t rs, void*
 // the previous one's; columns beyond the last expert's end leave at once.
 constexpr int MOE_MAX_COLS = 256;
 struct MoePlan { int n_cols, pad[3]; int expert[MOE_MAX_COLS], tile0[MOE_MAX_COLS], rows[MOE_MAX_COLS]; };   // per column: expert, first tile, rows
-template <int RBW, int MW, bool SWIGLU = false, bool GROUPED = false>
+template <int RBW, int MW, bool SWIGLU = false, bool GROUPED = false, bool PLAIN = false>
 __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ XF,
                                                          float* __restrict__ PT, int NRB, int KS, int ks_per_split, int S, int Npad,
                                                          int MT /*32-row tiles of the pass*/, bf16_t* act, int M,
@@ -545,26 +545,30 @@ __global__ __launch_bounds__(128 * MW, 2) void k_gemm_pf(const bf16_t* __restric
   const bool busy = mt0 < tile_end && rb0 < NRB;
   // The tiles this wave loads, the same number in every wave (the last tile is loaded more than once where they do not divide).  Buffer
   // loads: a tile's base in a resource, the k-step in the scalar offset, no address arithmetic in the vector unit, and lanes of rows or
-  // blocks beyond the end out of range, which move nothing and leave zeros (zeros also cost the matrix pipes less power).  us a launch,
-  // before / after: grouped experts of a 1000-row prompt at Mixtral widths 1053 / 914 and 561 / 478; 183 to 300 rows at 7B widths 148 /
-  // 131, 83 / 71, 82 / 63; 104 rows, O and down 24.0 / 23.5; full tiles (1024 rows at 13B widths) 193 / 190 and 485 / 476.
+  // blocks beyond the end out of range, which move nothing and leave zeros (zeros also cost the matrix pipes less power).  PLAIN:
+  // loads of an address a lane, tiles beyond the end as the last one there is.  (Which launches take which, and what both measured:
+  // plan_pf_plain_loads.  Grouped experts of a 1000-row prompt at Mixtral widths, us, buffer / plain loads on each of two cards: gate/up 931 / 970 and 865 /
+  // 1013, down 474 / 460 and 444 / 491; of a 104-row one 381 / 386 and 381 / 389, 255 / 272 and 257 / 283.)
   BufferRsrc src[LPW];
+  const bf16_t* ptr[LPW];
   uint32_t vo[LPW];
   int dst[LPW];
 #pragma unroll
   for (int u = 0; u < LPW; ++u) {
     const int i = min(w + u * NW, NTILE - 1), t = tile0 + (i - WT) % RT;
-    const bf16_t* p = i < WT ? Wp + (size_t)min(nt * WT + i, NRB - 1) * KS * 512 : XF + (size_t)((i - WT) / RT * MT + min(t, tile_end - 1)) * KS * 512;
-    src[u].rs = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, KS * 1024, 0x00020000);
+    ptr[u] = i < WT ? Wp + (size_t)min(nt * WT + i, NRB - 1) * KS * 512 : XF + (size_t)((i - WT) / RT * MT + min(t, tile_end - 1)) * KS * 512;
+    src[u].rs = __builtin_amdgcn_make_buffer_rsrc((void*)ptr[u], 0, KS * 1024, 0x00020000);
     vo[u] = (i < WT ? nt * WT + i < NRB : t * 32 + (lane & 31) < row_end) ? lane * 16u : 0x80000000u;
     dst[u] = i * 64;
   }
   // (k-steps beyond the end are clamped, so that the number of loads in flight is the same on every path)
   auto dma = [&](u32x4* slot, int k) {
-    const uint32_t ko = (uint32_t)min(k, klast) * 1024u;
+    const uint32_t kk = (uint32_t)min(k, klast);
 #pragma unroll
-    for (int u = 0; u < LPW; ++u)
-      buffer_to_lds16(src[u].rs, slot + dst[u], vo[u], ko);
+    for (int u = 0; u < LPW; ++u) {
+      if constexpr (PLAIN) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ptr[u] + (size_t)kk * 512 + lane * 8), (__attribute__((address_space(3))) void*)(slot + dst[u]), 16, 0, 0);
+      else buffer_to_lds16(src[u].rs, slot + dst[u], vo[u], kk * 1024u);
+    }
   };
   f32x16 acc[RBW][2];
 #pragma unroll

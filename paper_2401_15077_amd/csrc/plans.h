@@ -89,6 +89,22 @@ static inline GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epi
   return best;
 }
 
+// Work-groups of the large-M GEMM: weight-row tiles x K slices, rounded up to whole rounds over the 8 XCDs, x columns of row tiles.
+static inline int pf_grid(int NRB, int MT, const GemmPlan& p) { return ((NRB + 2 * p.rbw - 1) / (2 * p.rbw) * p.S + 7) / 8 * 8 * ((MT + 2 * p.mw - 1) / (2 * p.mw)); }
+// Which of its launches bring their tiles by plain loads, an address a lane, instead of buffer loads: those of two- and four-wave
+// work-groups in a single round (a work-group a CU, hence a wave a SIMD or less).  us a launch, buffer / plain loads, on each of two
+// cards: 192 rows at 7B widths, gate/up 75.9 / 70.8 and 79.0 / 76.5, QKV 42.4 / 40.5 and 43.7 / 42.6, down 37.0 / 35.5 and 38.7 / 38.4;
+// 512 rows, down 73.5 / 71.9 and 79.4 / 79.3; 700 rows, O 48.5 / 45.9 and 55.2 / 49.0; 512 rows at 13B widths, down 118.7 / 116.5 and
+// 127.2 / 125.6.  (Fewer scalar instructions a k-step do not change it.)  Everywhere else buffer loads are the faster ones: two
+// work-groups a CU (700 rows at 7B widths, QKV in 768 work-groups 115.8 / 123.4 and 123.6 / 130.9; 1024 rows, gate/up in 704 273 / 306
+// and 293 / 325), eight waves (512 rows at 7B widths, gate/up 140 / 148 and 154 / 161; 2011 rows at 70B widths 2589 / 2882 and 2750 /
+// 3016), and a single column of four tiles with 16 rows or more beyond the end, which buffer loads leave out and the waves would
+// multiply (72 rows at 7B widths, down 25.4 / 26.6 and 25.9 / 27.5; 104 rows 30.0 / 31.1 and 30.2 / 31.2; whole prompts of 80 and 96
+// rows 3.7 and 2.5 % slower with plain loads, 112 rows 1.3, 120 even, 128 rows 0.2 to 1.5 % faster).
+static inline bool plan_pf_plain_loads(int NRB, int MT, int M, int n_cu, const GemmPlan& p) {
+  return p.mw <= 2 && pf_grid(NRB, MT, p) <= n_cu && !(p.mw == 2 && M <= 112);
+}
+
 // The same model for the grouped GEMMs of a mixture of experts: M rows x topk experts each, padded per expert to columns of
 // 2 * mw tiles.  Routing is uneven, so half a column more per expert and half a round more at the end are counted.  Both GEMMs of
 // the MLP share the column width; gate/up keeps one K slice (SwiGLU in its epilogue).

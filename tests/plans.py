@@ -20,6 +20,7 @@ void shim_moe(const int* a, int* o) {
   put(p.gu, o); put(p.dn, o + 4); o[8] = p.cols;
 }
 int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
+int shim_plain_loads(int NRB, int MT, int M, int n_cu, int S, int rbw, int mw) { GemmPlan p{}; p.S = S; p.rbw = rbw; p.mw = mw; return plan_pf_plain_loads(NRB, MT, M, n_cu, p); }
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
 int shim_q4_w_span(int nr, int KS) { return q4_w_span(nr, KS); }
@@ -44,6 +45,10 @@ class Plans:
         o = (ctypes.c_int * 4)()
         self.lib.shim_pf(NRB, KS, MT, n_cu, fused, q4, fixed, o)
         return Plan(*o)
+
+    def plain_loads(self, NRB, rows, p, n_cu=256):
+        """Whether a launch of the large-M GEMM with plan `p` brings its tiles by plain loads (else by buffer loads)"""
+        return bool(self.lib.shim_plain_loads(NRB, (rows + 31) // 32, rows, n_cu, p.S, p.rbw, p.mw))
 
     def moe(self, d, F, M, topk, E, n_cu=256):
         """-> (gate/up plan, down plan, columns) for M rows of a mixture of E experts with widths d and F"""

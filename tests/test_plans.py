@@ -7,6 +7,7 @@ import pytest
 import synth
 from plans import Plans
 from test_gpu_large_m import DENSE, EXPERTS, LOSS_ROWS
+from test_gpu_tile_loads import CASES as TILE_LOADS, shape_of
 
 SHAPES_16 = {(4, 1), (3, 1), (4, 2), (3, 2), (4, 4), (3, 4), (2, 4)}     # what gemm() launches
 SHAPES_4 = {(2, 2)}
@@ -97,6 +98,32 @@ def test_oracle_cases_reach_every_tile(plans):
     # the small models of that file: tiles of two and four row tiles only
     small = [plans.prompt(synth.SHAPES["mini-gqa"], rows) for rows in range(33, 2049, 32)]
     assert {(p.rbw, p.mw) for l in small for p in l.values()} == {(3, 1), (3, 2)}
+
+
+def _row_blocks(s):
+    a = s.n_heads * s.head_dim
+    return {"qkv": (a + 2 * s.n_kv_heads * s.head_dim) // 32, "o": s.d_model // 32, "fc": s.d_model // 32, "gate_up": 2 * s.d_ffn // 32, "down": s.d_model // 32}
+
+
+def test_launches_that_bring_their_tiles_by_plain_loads(plans):
+    """Two- and four-wave work-groups in a single round of them, but for one column of four tiles with 16 rows or more beyond the
+    end; the cases of test_gpu_tile_loads.py take both ways with every such tile."""
+    def ways(s, rows):
+        blocks = _row_blocks(s)
+        return {m: (p, plans.plain_loads(blocks[m], rows, p)) for m, p in plans.prompt(s, rows).items()}
+
+    for name in ("llama2-7b", "llama2-13b"):
+        for rows in (40, 64, 113, 128, 161, 192, 256):
+            assert all(plain for p, plain in ways(synth.SHAPES[name], rows).values() if p.mw <= 2), (name, rows)
+        for rows in (65, 72, 96, 104, 112):
+            assert not any(plain for _, plain in ways(synth.SHAPES[name], rows).values()), (name, rows)
+    for rows in (700, 1024):
+        w = ways(synth.SHAPES["llama2-7b"], rows)
+        assert w["o"][1] and not w["gate_up"][1]               # one round of O's work-groups, three of gate/up's
+    assert not any(plain for p, plain in ways(synth.SHAPES["llama2-70b"], 2011).values() if p.mw == 4)
+    seen = {(p.rbw, p.mw, m == "gate_up" and p.S == 1, plain) for d, ffn, lens in TILE_LOADS for rows in lens for m, (p, plain) in ways(shape_of(d, ffn), rows).items()}
+    assert seen >= {(3, 1, False, True), (3, 1, True, True), (4, 1, False, True), (3, 2, False, True), (3, 2, True, True), (4, 2, False, True), (4, 2, True, True),
+                    (3, 2, False, False), (3, 2, True, False), (4, 2, False, False)}, seen
 
 
 @pytest.mark.parametrize("slices", [1, 3, 8])
