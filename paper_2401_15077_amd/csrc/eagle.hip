@@ -927,7 +927,7 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
     return EAGLE_OK;
   }
   c->cur_class = KC_GATEUP;
-  if (plan_is_wk(w.gu.NRB, MT, c->n_cu, c->big_gemm, c->fixed_sums, c->q4)) {
+  if (plan_is_wk(w.gu.NRB, w.gu.KS, MT, c->n_cu, c->big_gemm, c->fixed_sums, c->q4)) {
     if ((rc = gemm_wk(c, w.gu, c->xf_d, MT, M, c->xf_ffn))) return rc;
     S = 0;
   } else if ((rc = gemm(c, w.gu, c->xf_d, MT, M, &S, c->xf_ffn))) return rc;

@@ -36,11 +36,23 @@ static inline bool plan_is_large_m(int MT, bool big_gemm, bool fixed_sums, bool 
 
 // Which gate/up products of 33 to 128 rows run over all of K in a work-group (k_gemm_wk; plan_pf otherwise): dense bf16 models whose
 // sums are not fixed, with three row blocks on the busiest CU, or four and at most 64 rows.  (With fewer the activations that every
-// work-group fetches outweigh what the K slices cost; with four and more rows the CUs that have three idle for a quarter of the time.
-// Requests with four / three / two sequences and the 26-node tree, ms, K slices / whole K: 7B widths, 8 layers (2.7 row blocks a CU)
-// 36.3 / 35.1, 33.4 / 31.9, 29.8 / 28.3; 13B widths, 6 layers (3.4) four 40.1 / 41.7, two 33.1 / 31.9.)
-static inline bool plan_is_wk(int NRB, int MT, int n_cu, bool big_gemm, bool fixed_sums, bool q4) {
-  return big_gemm && !fixed_sums && !q4 && MT >= 2 && MT <= 4 && NRB > 2 * n_cu && NRB <= (MT == 2 ? 4 : 3) * n_cu;
+// work-group fetches outweigh what the K slices cost; with four and more rows the CUs that have three idle for a quarter of the time.)
+// The same two things bound it below three: the work-groups with two blocks idle, and with four tiles of rows what each fetches grows
+// with K, while the K slices' partial sums do not.  Hence the least number of row blocks a CU for four tiles, and for three with a K
+// beyond 10240.  Whole prompts at 20 to 61 sizes of each K, time with all of K over time with slices, rows 40 to 64 / 72 to 96 / 104 to 128:
+//   K 1024 to 3072, 2.02 to 3 blocks   0.89 to 0.96 / 0.90 to 0.97 / 0.93 to 1.00
+//   K 4096          2.02               0.98 to 0.99 / 0.99 to 1.00 / 1.01 to 1.02,  2.12  0.97 / 0.98 to 0.99 / 0.99 to 1.01,  2.25 to 2.62  0.94 to 0.96 / 0.96 to 0.97 / 0.97 to 1.00
+//   K 5120, 6144    2.02 to 2.62       0.95 to 0.98 / 0.96 to 0.99 / 0.98 to 1.02
+//   K 7168 to 10240 2.02 to 2.62       0.95 to 0.99 / 0.97 to 1.01 / 0.99 to 1.03
+//   K 12288, 16384  2.02 to 2.62       0.98 to 1.01 / 0.99 to 1.02 / 1.01 to 1.04
+//   K 4096 to 10240 2.75 to 3          0.92 to 0.95 / 0.93 to 0.97 / 0.96 to 0.99
+//   K 12288         2.75 to 3          0.95 to 0.97 / 0.97 to 0.98 / 0.99 to 1.00
+//   K 16384         2.75 to 3          0.97 to 0.98 / 0.98 to 0.99 / 1.00 to 1.01
+//   K 1024 to 16384 3.02 to 4          0.86 to 1.00
+static inline bool plan_is_wk(int NRB, int KS, int MT, int n_cu, bool big_gemm, bool fixed_sums, bool q4) {
+  if (!big_gemm || fixed_sums || q4 || MT < 2 || MT > 4 || NRB <= 2 * n_cu || NRB > (MT == 2 ? 4 : 3) * n_cu) return false;
+  const int least = MT == 4 ? (KS <= 192 ? 32 : KS <= 256 ? 34 : KS <= 768 ? 43 : 64) : MT == 3 && KS > 640 ? 43 : 32;   // sixteenths of a row block a CU
+  return 16 * NRB >= least * n_cu;
 }
 
 // Which prompt passes take the attention kernel of 128 rows a work-group (k2_attn_prompt) instead of the one of 32 (k2_attn): those

@@ -21,6 +21,7 @@ void shim_moe(const int* a, int* o) {
 }
 int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
 int shim_plain_loads(int NRB, int MT, int M, int n_cu, int S, int rbw, int mw) { GemmPlan p{}; p.S = S; p.rbw = rbw; p.mw = mw; return plan_pf_plain_loads(NRB, MT, M, n_cu, p); }
+int shim_wk(int NRB, int KS, int MT, int n_cu, int big, int fixed, int q4) { return plan_is_wk(NRB, KS, MT, n_cu, big != 0, fixed != 0, q4 != 0); }
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
 int shim_q4_w_span(int nr, int KS) { return q4_w_span(nr, KS); }
@@ -60,6 +61,10 @@ class Plans:
     def whole_k(self, NRB, KS, planes, n_cu=256):
         return bool(self.lib.shim_whole_k(NRB, KS, planes, n_cu))
 
+    def whole_k_rows(self, NRB, KS, rows, n_cu=256, big=True, fixed=False, q4=False):
+        """Whether a gate/up product of `rows` rows runs over all of K in a work-group (k_gemm_wk)"""
+        return bool(self.lib.shim_wk(NRB, KS, (rows + 31) // 32, n_cu, big, fixed, q4))
+
     def prompt_attn(self, heads, rows, max_seq, n_cu=256):
         """-> for every pass of a prompt of a bf16 model with an fp32 cache (eagle_prefill: whole windows of 512 rows, at most 2048, passes of
         about equal length): its first row, its rows and whether it takes the attention kernel of 128 rows a work-group"""
@@ -75,7 +80,8 @@ class Plans:
         return self.lib.shim_moe_tiles(M, topk, E)
 
     def prompt(self, s, rows, kv="fp32", bits=16):
-        """matrix -> plan of one prompt pass of `rows` rows of a bf16 model (matrices that do not take the large-M GEMM are left out)"""
+        """matrix -> plan of one prompt pass of `rows` rows of a bf16 model (matrices that do not take the large-M GEMM are left out, gate/up
+        that runs over all of K in a work-group among them)"""
         MT, fixed = (rows + 31) // 32, kv == "bf16" and s.n_experts == 0
         d, a, q4, out = s.d_model, s.n_heads * s.head_dim, bits == 4, {}
         kw = dict(q4=q4, fixed=fixed)
@@ -83,7 +89,8 @@ class Plans:
             out["qkv"] = self.pf((a + 2 * s.n_kv_heads * s.head_dim) // 32, d // 16, MT, **kw)
             out["o"], out["fc"] = self.pf(d // 32, a // 16, MT, **kw), self.pf(d // 32, 2 * d // 16, MT, **kw)
             if not s.n_experts:
-                out["gate_up"] = self.pf(2 * s.d_ffn // 32, d // 16, MT, fused=True, **kw)
+                if not self.whole_k_rows(2 * s.d_ffn // 32, d // 16, rows, **kw):
+                    out["gate_up"] = self.pf(2 * s.d_ffn // 32, d // 16, MT, fused=True, **kw)
                 out["down"] = self.pf(d // 32, s.d_ffn // 16, MT, **kw)
         if s.n_experts:                         # experts are grouped whatever the rows
             out["gate_up"], out["down"], _ = self.moe(d, s.d_ffn, 32 * MT, s.experts_per_tok, s.n_experts)

@@ -126,6 +126,38 @@ def test_launches_that_bring_their_tiles_by_plain_loads(plans):
                     (3, 2, False, False), (3, 2, True, False), (4, 2, False, False)}, seen
 
 
+WK_LAUNCHED = {(3, 2), (3, 3), (3, 4), (4, 2)}                           # (most row blocks of a work-group, row tiles) that gemm_wk() launches
+
+
+@pytest.mark.parametrize("n_cu", [256, 64])
+def test_whole_k_gate_up_gives_every_work_group_what_it_is_built_for(plans, n_cu):
+    """Accepted sizes leave a work-group NRMAX - 1 or NRMAX row blocks, with a kernel for that NRMAX and the row tiles; everything else
+    that the large-M GEMM serves is refused."""
+    seen = set()
+    for NRB in range(n_cu, 5 * n_cu + 2):
+        for KS in (16, 64, 192, 196, 256, 320, 512, 640, 768, 1024):
+            for rows in (1, 32, 33, 64, 65, 96, 97, 128, 129, 512):
+                MT = (rows + 31) // 32
+                if not plans.whole_k_rows(NRB, KS, rows, n_cu):
+                    continue
+                shares = {(w + 1) * NRB // n_cu - w * NRB // n_cu for w in range(n_cu)}
+                most = -(-NRB // n_cu)
+                assert max(shares) == most and min(shares) >= most - 1 and (most, MT) in WK_LAUNCHED, (NRB, KS, rows)
+                seen.add((most, MT))
+                assert not any(plans.whole_k_rows(NRB, KS, rows, n_cu, **kw) for kw in (dict(big=False), dict(fixed=True), dict(q4=True)))
+    assert seen == WK_LAUNCHED
+
+
+def test_whole_k_gate_up_only_where_it_is_the_faster_one(plans):
+    """Four tiles of rows with a long K need nearly three row blocks on every CU, three tiles with a K beyond 10240 too."""
+    for d, blocks, slower in ((4096, 516, (104, 128)), (4096, 536, (104, 128)), (7168, 672, (120, 128)), (8192, 516, (104, 128)), (8192, 640, (104, 128)),
+                              (12288, 576, (80, 96, 104, 128)), (16384, 768, (128,))):
+        assert not any(plans.whole_k_rows(blocks, d // 16, rows) for rows in slower), (d, blocks)
+    for d, blocks, faster in ((1024, 516, (40, 64, 72, 96, 104, 128)), (4096, 516, (40, 64, 72)), (4096, 576, (104, 128)), (4096, 688, (40, 72, 104, 128)),
+                              (8192, 516, (40, 64)), (8192, 704, (40, 72, 104, 128)), (5120, 864, (40, 64)), (16384, 1024, (40, 64))):
+        assert all(plans.whole_k_rows(blocks, d // 16, rows) for rows in faster), (d, blocks)
+
+
 @pytest.mark.parametrize("slices", [1, 3, 8])
 def test_4bit_streams_keep_their_scalar_offsets_inside_the_buffers(plans, slices):
     """What the 4-bit stream with three row blocks (fk_stream_q4) requests while a wave works on group g of its run [gb, ge): the tiles
