@@ -662,7 +662,9 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   u32x4 pre[DEPTH * RW * NWP];
   if constexpr (!Q4) k2_prologue_dispatch<NWP, NXP, RW, RW, DEPTH>(nr, kb, ke, wp, g.wps, pre);
 
-  // stage this work-group's K slice of X: per plane a contiguous run of kt tiles (8 loads in flight per thread)
+  // stage this work-group's K slice of X: per plane a contiguous run of kt tiles (8 loads in flight per thread).  4-bit weights: rows beyond
+  // the pass are staged as zeros, since what an earlier pass left there, a NaN say, would send the waves over their groups again (k2_stream_q4).
+  const bool live = !Q4 || (int)(threadIdx.x & 31) < g.M;     // every element that a thread moves is of one row
   for (int p = 0; p < NXP; ++p) {
     const u32x4* src = (const u32x4*)(g.XF + ((size_t)p * g.KS + ks0) * 512);
     u32x4* dst = xs + (size_t)p * kt * 64;
@@ -670,7 +672,11 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
     for (int i0 = 0; i0 < n; i0 += V2_THREADS * 8) {
       u32x4 v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = src[min(i0 + u * V2_THREADS + (int)threadIdx.x, n - 1)];
+      for (int u = 0; u < 8; ++u) v[u] = u32x4{0u, 0u, 0u, 0u};
+      if (live) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[min(i0 + u * V2_THREADS + (int)threadIdx.x, n - 1)];
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int i = i0 + u * V2_THREADS + (int)threadIdx.x;
