@@ -317,27 +317,12 @@ static size_t layout(eagle_ctx* c) {
   const bool grouped = c->big_gemm && g.n_experts > 0;
   const int slots = grouped ? 32 * moe_tiles(Mm, g.experts_per_tok, g.n_experts) : 0;
   c->xf_ffn = a.take<bf16_t>((size_t)c->NXP * std::max(Mm, slots) * F);
-  // (k_gemm_pf_q4: the last column of row tiles may read up to 3 tiles beyond the end)
-  c->group_sums = a.take<float>(c->q4 ? (size_t)std::max(std::max(F, H * dh), 2 * d) / EAGLE_Q4_GROUP * Mm + 96 : 1);
+  c->group_sums = a.take<float>(c->q4 ? (size_t)std::max(std::max(F, H * dh), 2 * d) / EAGLE_Q4_GROUP * Mm : 1);
   c->moe_plan = a.take<MoePlan>(1);
   c->moe_slot = a.take<int>(grouped ? (size_t)g.n_experts * Mm : 1);
   c->moe_row = a.take<int>(std::max(1, slots));
   c->xf_moe = a.take<bf16_t>(std::max((size_t)8, (size_t)c->NXP * slots * d));
   // fast path buffers
-  c->h2 = a.take<float>((size_t)32 * d);
-  c->xf2_d = a.take<bf16_t>((size_t)c->NXP * 32 * d);
-  c->xf2_dB = a.take<bf16_t>(g.n_experts > 0 ? (size_t)c->NXP * 32 * d : 8);
-  c->moe_w = a.take<float>((size_t)std::max(1, g.n_experts) * c->Mmax);
-  c->expert_used = a.take<int>(std::max(1, g.n_experts));
-  c->experts_touched = a.take<int>(1);
-  c->xn = a.take<float>(g.n_experts > 0 ? (size_t)Mm * d : 8);
-  c->xf2_2d = a.take<bf16_t>((size_t)c->NXP * 32 * 2 * d);
-  c->xf2_att = a.take<bf16_t>((size_t)c->NXP * 32 * H * dh);
-  c->xf2_ffn = a.take<bf16_t>((size_t)c->NXP * 32 * F * (grouped ? std::max(1, g.n_experts) : 1));
-  c->facts = a.take<RowFact>(Mm);
-  c->ssq1 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32); c->ssq2 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32);
-  c->trace = a.take<unsigned long long>(1024 * 8);
-  c->cnt_gemm = a.take<int>(1024); c->cnt_attn = a.take<int>((size_t)128 * H);
   size_t worst2 = 0;
   auto consider2 = [&](const PackedW& w) {
     Plan2 p = plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4);
@@ -349,8 +334,23 @@ static size_t layout(eagle_ctx* c) {
     if (w.moe) { consider2(w.e_gu[0]); consider2(w.e_dn[0]); } else { consider2(w.gu); consider2(w.dn); }
   }
   c->pt2_floats = worst2;
-  // (all experts of a layer in one launch: the slices of each)
-  for (auto& w : c->layers)
+  bool two = false;                                             // all experts of a layer in one launch: an input of down each
+  for (auto& w : c->layers) two = two || (w.moe && moe_in_two(c, w.e_gu[0], w.e_dn[0]));
+  c->h2 = a.take<float>((size_t)32 * d);
+  c->xf2_d = a.take<bf16_t>((size_t)c->NXP * 32 * d);
+  c->xf2_dB = a.take<bf16_t>(g.n_experts > 0 ? (size_t)c->NXP * 32 * d : 8);
+  c->moe_w = a.take<float>((size_t)std::max(1, g.n_experts) * c->Mmax);
+  c->expert_used = a.take<int>(std::max(1, g.n_experts));
+  c->experts_touched = a.take<int>(1);
+  c->xn = a.take<float>(g.n_experts > 0 ? (size_t)Mm * d : 8);
+  c->xf2_2d = a.take<bf16_t>((size_t)c->NXP * 32 * 2 * d);
+  c->xf2_att = a.take<bf16_t>((size_t)c->NXP * 32 * H * dh);
+  c->xf2_ffn = a.take<bf16_t>((size_t)c->NXP * 32 * F * (two ? g.n_experts : 1));
+  c->facts = a.take<RowFact>(Mm);
+  c->ssq1 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32); c->ssq2 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32);
+  c->trace = a.take<unsigned long long>(1024 * 8);
+  c->cnt_gemm = a.take<int>(1024); c->cnt_attn = a.take<int>((size_t)128 * H);
+  for (auto& w : c->layers)                                     // (and the slices of each)
     if (w.moe && moe_in_two(c, w.e_gu[0], w.e_dn[0])) { worst2 = std::max(worst2, (size_t)g.n_experts * xk_plan(c, w.e_dn[0]).S * w.e_dn[0].Npad * 32); break; }
   c->pt2_all = worst2;
   c->PT2 = a.take<float>(worst2);

@@ -2,6 +2,7 @@
 import ctypes
 import os
 import re
+from dataclasses import replace
 
 import numpy as np
 import pytest
@@ -51,6 +52,18 @@ def test_workspace_size_and_config_validation(lib):
     big = pkg.make_config(synth.SHAPES["llama2-7b"], *synth.TREES["T26"], max_seq=1024)
     n7 = lib.eagle_workspace_bytes(ctypes.byref(big))
     assert 13.4e9 < n7 < 17e9
+
+
+def test_workspace_holds_one_input_of_down_where_experts_run_one_by_one(lib):
+    """Eight experts more of a narrow mixture (a launch an expert on the fast path): their weights, and for the general path up to a tile of
+    rows more each, gathered and behind SwiGLU (and K slices of it, a quarter of that); not a 32-row input of down each on the fast path as
+    well."""
+    def need(E):
+        s = replace(synth.SHAPES["mini-moe"], name="narrow", n_layers=1, d_model=64, d_ffn=4032, n_heads=2, n_kv_heads=2, n_experts=E, experts_per_tok=1, draft_moe=False)
+        cfg = pkg.make_config(s, *synth.TREES["T8"], max_seq=64)
+        return lib.eagle_workspace_bytes(ctypes.byref(cfg))
+    weights, tiles = 8 * 3 * 64 * 4032 * 2, 8 * 2 * 32 * (64 + 4032) * 2
+    assert tiles < need(16) - need(8) - weights < 1.5 * tiles
 
 
 def test_null_arguments_are_errors_not_crashes(lib):
