@@ -219,23 +219,11 @@ static void take_packed(Arena& a, PackedW& w, int N, int K, int NWP, bool q4 = f
   } else w.w = a.take<bf16_t>(w.plane_stride * NWP);
 }
 
-// Streamed split-K plan of a matrix on the fast path; S = 0 where the fetch model prices the LDS-staged kernel (plan2) lower.
-static PlanXK xk_plan(const eagle_ctx* c, const PackedW& w) {
-  const Plan2 p = plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4);
-  PlanXK px = plan_xk(w.NRB, w.KS, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
-  const int R = (w.NRB + p.groups - 1) / p.groups, kt_s = (w.KS + p.S - 1) / p.S;
-  const long staged = (long)R * kt_s + (long)c->NXP * kt_s + 2L * p.S * R * 4 + 40;
-  if (px.S > 0 && px.cost >= staged) px.S = 0;
-  return px;
-}
-// Mixture of experts on the fast path: all experts' gate/up in one launch and all their downs in another, where those are the whole-K and
-// the streamed split-K kernel (wide matrices).  Two launches an expert are sixteen a layer with eight experts, each with its own first
-// tiles, drain and (down) exchange, and many of them for nothing in the head's passes of a few rows.  In two, a row is fetched only for
-// the experts it selected.  Mixtral widths, us a pass of one layer (verify and head passes together): gate/up 264 in eight launches, 231
-// in one, 226 with the rows; down 161 / 133 / 124.
+// Streamed split-K plan of a matrix on the fast path (S = 0: the LDS-staged kernel).
+static PlanXK xk_plan(const eagle_ctx* c, const PackedW& w) { return plan_streamed(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, c->pt2_floats, w.q4); }
+// Mixture of experts on the fast path: all experts' gate/up in one launch and all their downs in another.
 static bool moe_in_two(const eagle_ctx* c, const PackedW& gu, const PackedW& dn) {
-  return c->cfg.n_experts > 1 && c->big_gemm && gu.NRB >= c->n_cu && !plan_is_whole_k(gu.NRB, gu.KS, c->NWP + c->NXP, c->n_cu) &&
-         !plan_is_whole_k(dn.NRB, dn.KS, c->NWP + c->NXP, c->n_cu) && xk_plan(c, dn).S > 0;
+  return c->cfg.n_experts > 1 && c->big_gemm && plan_experts_in_two(gu.NRB, gu.KS, dn.NRB, dn.KS, c->NXP, c->NWP, c->n_cu, c->pt2_floats);
 }
 
 // Lays the context's buffers out in the workspace (or just measures when c->ws == nullptr).
@@ -325,8 +313,7 @@ static size_t layout(eagle_ctx* c) {
   // fast path buffers
   size_t worst2 = 0;
   auto consider2 = [&](const PackedW& w) {
-    Plan2 p = plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4);
-    worst2 = std::max(worst2, (size_t)p.S * w.Npad * 32);
+    worst2 = std::max(worst2, plan2(w.NRB, w.KS, c->NXP, c->NWP, c->n_cu, w.q4).S * (size_t)w.Npad * 32);
   };
   consider2(c->lm_head); consider2(c->fc);
   for (auto& w : c->layers) {

@@ -216,3 +216,24 @@ static inline Plan2 plan2(int NRB, int KS, int NXP, int NWP, int n_cu, bool q4 =
   p.lds = std::max(xs, red);
   return p;
 }
+
+// Split-K plan of a matrix with streamed activations; S = 0 where the fetch model prices the LDS-staged kernel (plan2) lower.
+static inline PlanXK plan_streamed(int NRB, int KS, int NXP, int NWP, int n_cu, size_t pt_floats, bool q4 = false) {
+  const Plan2 p = plan2(NRB, KS, NXP, NWP, n_cu, q4);
+  PlanXK px = plan_xk(NRB, KS, NXP, n_cu, (size_t)NRB * 32 * 32, pt_floats);
+  const int R = (NRB + p.groups - 1) / p.groups, kt_s = (KS + p.S - 1) / p.S;
+  const long staged = (long)R * kt_s + (long)NXP * kt_s + 2L * p.S * R * 4 + 40;
+  if (px.S > 0 && px.cost >= staged) px.S = 0;
+  return px;
+}
+
+// Passes of up to 32 rows of a mixture: all experts' gate/up in one launch and all their downs in another, where those are the whole-K and
+// the streamed split-K kernel (wide matrices).  Two launches an expert are sixteen a layer with eight experts, each with its own first
+// tiles, drain and (down) exchange, and many of them for nothing in the head's passes of a few rows.  In two, a row is fetched only for
+// the experts it selected.  Two layers and the head, 26-node tree, us a step, launches an expert / two: Mixtral widths, 8 experts, 2 choices 3376 / 3098,
+// 2 and 1 1498 / 1459, 16 and 4 6341 / 5714; d 6144, ffn 16384, 8 and 2 5176 / 4885; d 2176, ffn 4160, 8 and 2 1574 / 1311, 64 and 1
+// 4138 / 2077.  (Slices of down are planned for one expert.)
+static inline bool plan_experts_in_two(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int NXP, int NWP, int n_cu, size_t pt_floats) {
+  return gu_NRB >= n_cu && !plan_is_whole_k(gu_NRB, gu_KS, NWP + NXP, n_cu) && !plan_is_whole_k(dn_NRB, dn_KS, NWP + NXP, n_cu) &&
+         plan_streamed(dn_NRB, dn_KS, NXP, NWP, n_cu, pt_floats).S > 0;
+}

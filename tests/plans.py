@@ -22,6 +22,15 @@ void shim_moe(const int* a, int* o) {
 int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
 int shim_plain_loads(int NRB, int MT, int M, int n_cu, int S, int rbw, int mw) { GemmPlan p{}; p.S = S; p.rbw = rbw; p.mw = mw; return plan_pf_plain_loads(NRB, MT, M, n_cu, p); }
 int shim_wk(int NRB, int KS, int MT, int n_cu, int big, int fixed, int q4) { return plan_is_wk(NRB, KS, MT, n_cu, big != 0, fixed != 0, q4 != 0); }
+// matrices: row blocks and k-steps of n of them, gate/up and down of an expert first; bf16 weights (one plane), two planes of activations
+int shim_experts_in_two(const int* m, int n, int n_cu, int* o) {
+  size_t pt = 0;
+  for (int i = 0; i < n; ++i) pt = std::max(pt, plan2(m[2 * i], m[2 * i + 1], 2, 1, n_cu).S * (size_t)m[2 * i] * 32 * 32);
+  const PlanXK dn = plan_streamed(m[2], m[3], 2, 1, n_cu, pt);
+  const int grid = std::max(n_cu, (m[0] + 3) / 4);
+  o[0] = (m[0] + grid - 1) / grid; o[1] = dn.S; o[2] = dn.nrmax;
+  return plan_experts_in_two(m[0], m[1], m[2], m[3], 2, 1, n_cu, pt);
+}
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
 int shim_q4_w_span(int nr, int KS) { return q4_w_span(nr, KS); }
@@ -64,6 +73,16 @@ class Plans:
     def whole_k_rows(self, NRB, KS, rows, n_cu=256, big=True, fixed=False, q4=False):
         """Whether a gate/up product of `rows` rows runs over all of K in a work-group (k_gemm_wk)"""
         return bool(self.lib.shim_wk(NRB, KS, (rows + 31) // 32, n_cu, big, fixed, q4))
+
+    def experts_in_two(self, s, n_cu=256):
+        """Passes of up to 32 rows: (most gate/up row blocks of a work-group, K slices and most row blocks of down) where all experts share
+        two launches a layer, else None"""
+        a, d = s.n_heads * s.head_dim, s.d_model
+        m = [(2 * s.d_ffn // 32, d // 16), (d // 32, s.d_ffn // 16), ((s.vocab + 31) // 32, d // 16), (d // 32, 2 * d // 16),
+             ((a + 2 * s.n_kv_heads * s.head_dim) // 32, d // 16), (d // 32, a // 16)]
+        o = (ctypes.c_int * 3)()
+        two = self.lib.shim_experts_in_two((ctypes.c_int * 12)(*[x for r in m for x in r]), len(m), n_cu, o)
+        return tuple(o) if two and s.n_experts > 1 else None
 
     def prompt_attn(self, heads, rows, max_seq, n_cu=256):
         """-> for every pass of a prompt of a bf16 model with an fp32 cache (eagle_prefill: whole windows of 512 rows, at most 2048, passes of

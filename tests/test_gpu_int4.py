@@ -77,11 +77,12 @@ def test_int4_rejects_what_it_cannot_run():
         pkg.Eagle(synth.SHAPES["mini-gqa"], *synth.TREES["B63"], max_seq=256, weight_bits=4)      # 63 rows per pass
 
 
+@pytest.mark.parametrize("bits", [0x7FC0, 0x7F80, 0xFF80], ids=["nan", "inf", "minus-inf"])
 @pytest.mark.parametrize("shape_name, n_layers", [("mini-gqa", 2), ("llama2-7b", 1)])
-def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers):
-    """Five sequences, 30 rows in the verify pass; the pending token of the fourth (rows 18..23) has NaN for an embedding.  The others, rows
-    2..7 (16 rows beside them, sums of x in the same matrix instruction) among them, keep their bits.  The small model takes the kernels
-    that hold the activations in LDS for O and down, the large one for the LM head; the rest stream them."""
+def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers, bits):
+    """Five sequences, 30 rows in the verify pass; the pending token of the fourth (rows 18..23) has NaN or infinities for an embedding.  The
+    others, rows 2..7 (16 rows beside them, sums of x in the same matrix instruction) among them, keep their bits.  The small model takes
+    the kernels that hold the activations in LDS for O and down, the large one for the LM head; the rest stream them."""
     s = synth.SHAPES[shape_name].twin(n_layers)
     par, rk = synth.TREES["chain5"]
     W = dict(synth.iter_weights(s, 57, synth.device_fmt(s)))
@@ -103,7 +104,7 @@ def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers):
             break
     else:
         pytest.fail("no prompts of that kind")
-    W["embed"][first[3]] = 0x7FC0
+    W["embed"][first[3]] = bits
     eng.load_named("embed", W["embed"])
     again, trees2, logits = verified(prompts)
     assert again == first and np.isnan(logits[3]).all() and np.isfinite(clean[3]).all()

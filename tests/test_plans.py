@@ -1,13 +1,16 @@
 """The work splits of the matrix products (csrc/plans.h): every split covers K in whole units, every tile shape is one that the
 library launches, grouped experts stay within the columns and tiles that the workspace holds."""
 import random
+from dataclasses import replace
 
 import pytest
 
 import synth
 from plans import Plans
+from test_gpu_experts_in_two import CASES as IN_TWO, shape_of as mixture_of
 from test_gpu_large_m import DENSE, EXPERTS, LOSS_ROWS
 from test_gpu_tile_loads import CASES as TILE_LOADS, shape_of
+from test_gpu_whole_k_rows import CASES as WHOLE_K
 
 SHAPES_16 = {(4, 1), (3, 1), (4, 2), (3, 2), (4, 4), (3, 4), (2, 4)}     # what gemm() launches
 SHAPES_4 = {(2, 2)}
@@ -156,6 +159,29 @@ def test_whole_k_gate_up_only_where_it_is_the_faster_one(plans):
     for d, blocks, faster in ((1024, 516, (40, 64, 72, 96, 104, 128)), (4096, 516, (40, 64, 72)), (4096, 576, (104, 128)), (4096, 688, (40, 72, 104, 128)),
                               (8192, 516, (40, 64)), (8192, 704, (40, 72, 104, 128)), (5120, 864, (40, 64)), (16384, 1024, (40, 64))):
         assert all(plans.whole_k_rows(blocks, d // 16, rows) for rows in faster), (d, blocks)
+
+
+def test_whole_k_gate_up_cases_take_it(plans):
+    """Every row count of test_gpu_whole_k_rows.py; work-groups of two and three and of three and four blocks, every number of row tiles."""
+    seen = set()
+    for d, ffn, lens in WHOLE_K.values():
+        for rows in lens:
+            assert plans.whole_k_rows(ffn // 16, d // 16, rows), (d, ffn, rows)
+            seen.add((-(-(ffn // 16) // 256), (rows + 31) // 32))
+    assert seen == WK_LAUNCHED
+
+
+def test_expert_cases_share_two_launches(plans):
+    """All cases of test_gpu_experts_in_two.py, and between them every kernel that such a launch may take; not narrow experts (fewer gate/up row
+    blocks than CUs, or as many with a short K) nor a single one."""
+    two = {name: plans.experts_in_two(mixture_of(name)) for name in IN_TWO}
+    assert all(two.values()), two
+    assert {max(2, gu) for gu, _, _ in two.values()} == {2, 3, 4} == {max(2, dn) for _, _, dn in two.values()}
+    assert min(S for _, S, _ in two.values()) <= 4 < max(S for _, S, _ in two.values())
+    assert plans.experts_in_two(synth.SHAPES["mixtral-8x7b"]) == (4, 4, 2)
+    wide = mixture_of("e3-top1")
+    for other in (replace(wide, d_ffn=4032), replace(wide, d_ffn=4096, d_model=2048, n_heads=32, n_kv_heads=32), replace(wide, n_experts=1), synth.SHAPES["mini-moe"]):
+        assert plans.experts_in_two(other) is None, other
 
 
 @pytest.mark.parametrize("slices", [1, 3, 8])
