@@ -420,10 +420,10 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ Wp, siz
 // (Rings of 6 and 8 k-steps measured the same or slower, a K order rotated per work-group the same.)
 // Which tile: the host (plan_pf) takes the shape whose work-groups fill the CUs of every XCD in the fewest, fullest rounds.
 // Bound: the matrix pipes at the clock the card holds under them; the library's own 8192-cubed bf16 product reaches 1.2 PFLOP/s on
-// this card.  Issued work of both planes: 512 rows at 7B widths 1.0 PFLOP/s (QKV 101, O and down 64 on average, gate/up 182 us; the
-// kernel before, tiles of 8 x 4 with the activations through registers, 125, 67 and 217), 1024 rows at 13B widths 1.18 (gate/up 493
-// us), 2011 rows at 70B widths 1.28 (gate/up 2957 us).  With N(0, 0.02) weights the clock is higher: 91, 58 and 159 us at 7B.  Pipes
-// busy: 61 to 67 % at 512 rows, 71 to 73 % from 1024 on.
+// this card.  Issued work of both planes: 512 rows at 7B widths 1.0 to 1.07 PFLOP/s (QKV 102, O and down 64 on average, gate/up 173 us; the
+// kernel before, tiles of 8 x 4 with the activations through registers, 125, 67 and 217), 1024 rows at 13B widths 1.20 (gate/up 481
+// us), 2011 rows at 70B widths 1.33 (gate/up 2837 us).  With N(0, 0.02) weights the clock is higher: 95, 59 and 159 us at 7B.  Pipes
+// busy: 63 to 74 % at 512 rows, 77 to 78 % from 1024 on.
 // Work-groups that share a weight tile (the activation-row tiles of one weight-row tile) get ids 8 apart, i.e. the same
 // XCD under round-robin dispatch, next to each other in dispatch order: the tile comes from HBM once and from that
 // XCD's L2 afterwards.
