@@ -681,7 +681,7 @@ static hipError_t launch_gemm_mt(eagle_ctx* c, const PackedW& w, const bf16_t* X
 // The work-group tile of the plan, with or without the SwiGLU epilogue.
 template <int RBW, int MW, bool SWIGLU, bool PLAIN>
 static hipError_t launch_pf(eagle_ctx* c, const PackedW& w, const bf16_t* XF, int MT, const GemmPlan& p, bf16_t* swiglu_out, int M) {
-  return launch_k(c, c->cur_class, (double)w.N * w.K * c->elt, SWIGLU ? "k_gemm_pf<swiglu>" : "k_gemm_pf", k_gemm_pf<RBW, MW, SWIGLU, false, PLAIN>, dim3(pf_grid(w.NRB, MT, p)),
+  return launch_k(c, c->cur_class, (double)w.N * w.K * c->elt, SWIGLU ? "k_gemm_pf<swiglu>" : "k_gemm_pf", k_gemm_pf<RBW, MW, SWIGLU, false, PLAIN>, dim3(pf_grid(w.NRB, pf_cols(MT, p), p)),
                   dim3(128 * MW), (size_t)0, (const bf16_t*)w.w, XF, c->PT, w.NRB, w.KS, p.ks_per_split, p.S, w.Npad, MT, swiglu_out, M, (const MoePlan*)nullptr, (size_t)0, 0);
 }
 template <int RBW, int MW>
@@ -691,12 +691,13 @@ static hipError_t launch_pf(eagle_ctx* c, const PackedW& w, const bf16_t* XF, in
   return swiglu_out ? launch_pf<RBW, MW, true, false>(c, w, XF, MT, p, swiglu_out, M) : launch_pf<RBW, MW, false, false>(c, w, XF, MT, p, nullptr, M);
 }
 
-template <int RBW, int MW, bool SWIGLU>
+template <int RBW, int MW, bool SWIGLU, bool PLAIN = false>
 static hipError_t launch_pf_moe(eagle_ctx* c, const std::vector<PackedW>& w, const bf16_t* XF, int MT, const GemmPlan& p, int cols, bf16_t* act) {
-  const int G = ((w[0].NRB + 2 * RBW - 1) / (2 * RBW)) * p.S;
+  if constexpr (MW <= 2 && !PLAIN)
+    if (plan_pf_one_round(w[0].NRB, cols, c->n_cu, p)) return launch_pf_moe<RBW, MW, SWIGLU, true>(c, w, XF, MT, p, cols, act);
   const size_t stride = w.size() > 1 ? (size_t)(w[1].w - w[0].w) : 0;
-  return launch_k(c, c->cur_class, (double)w[0].N * w[0].K * c->elt * w.size(), "k_gemm_pf<experts>", k_gemm_pf<RBW, MW, SWIGLU, true>,
-                  dim3((G + 7) / 8 * 8 * cols), dim3(128 * MW), (size_t)0, (const bf16_t*)w[0].w, XF, c->PT, w[0].NRB, w[0].KS, p.ks_per_split, p.S,
+  return launch_k(c, c->cur_class, (double)w[0].N * w[0].K * c->elt * w.size(), "k_gemm_pf<experts>", k_gemm_pf<RBW, MW, SWIGLU, true, PLAIN>,
+                  dim3(pf_grid(w[0].NRB, cols, p)), dim3(128 * MW), (size_t)0, (const bf16_t*)w[0].w, XF, c->PT, w[0].NRB, w[0].KS, p.ks_per_split, p.S,
                   w[0].Npad, MT, act, 0, (const MoePlan*)c->moe_plan, stride, cols);
 }
 template <bool SWIGLU>
@@ -892,8 +893,9 @@ static int layer_forward(eagle_ctx* c, const Pass& pass, int M, int MT, int li, 
       LAUNCH_CHECK();
       k_moe_gather<<<dim3(tiles, (g.d_model / 16 + 15) / 16), 256, 0, c->stream>>>(c->moe_plan, c->moe_row, c->xf_d, MT, c->xf_moe, tiles, g.d_model / 16, c->NXP);
       LAUNCH_CHECK();
-      hipError_t e = (c->cur_class = KC_GATEUP, launch_pf_moe<true>(c, w.e_gu, c->xf_moe, tiles, p.gu, p.cols, c->xf_ffn));
-      if (e == hipSuccess) e = (c->cur_class = KC_DOWN, launch_pf_moe<false>(c, w.e_dn, c->xf_ffn, tiles, p.dn, p.cols, nullptr));
+      const int cols = std::min(p.cols, M * k);                 // every column has a row
+      hipError_t e = (c->cur_class = KC_GATEUP, launch_pf_moe<true>(c, w.e_gu, c->xf_moe, tiles, p.gu, cols, c->xf_ffn));
+      if (e == hipSuccess) e = (c->cur_class = KC_DOWN, launch_pf_moe<false>(c, w.e_dn, c->xf_ffn, tiles, p.dn, cols, nullptr));
       if (e != hipSuccess) return fail(EAGLE_EHIP, "expert gemm launch failed: %s", hipGetErrorString(e));
       k_resnorm<true><<<M, RESNORM_THREADS, 0, c->stream>>>(c->h, c->PT, p.dn.S, w.e_dn[0].Npad, tiles * 32, nullptr, c->h, next_gain, g.rms_eps, c->xf_d, MT, c->NXP, xout,
                                           g.d_model, nullptr, c->moe_w, c->moe_slot, c->Mmax, E);

@@ -102,7 +102,8 @@ static inline GemmPlan plan_pf(int NRB, int KS, int MT, int n_cu, bool fused_epi
 }
 
 // Work-groups of the large-M GEMM: weight-row tiles x K slices, rounded up to whole rounds over the 8 XCDs, x columns of row tiles.
-static inline int pf_grid(int NRB, int MT, const GemmPlan& p) { return ((NRB + 2 * p.rbw - 1) / (2 * p.rbw) * p.S + 7) / 8 * 8 * ((MT + 2 * p.mw - 1) / (2 * p.mw)); }
+static inline int pf_cols(int MT, const GemmPlan& p) { return (MT + 2 * p.mw - 1) / (2 * p.mw); }
+static inline int pf_grid(int NRB, int cols, const GemmPlan& p) { return ((NRB + 2 * p.rbw - 1) / (2 * p.rbw) * p.S + 7) / 8 * 8 * cols; }
 // Which of its launches bring their tiles by plain loads, an address a lane, instead of buffer loads: those of two- and four-wave
 // work-groups in a single round (a work-group a CU, hence a wave a SIMD or less).  us a launch, buffer / plain loads, on each of two
 // cards: 192 rows at 7B widths, gate/up 75.9 / 70.8 and 79.0 / 76.5, QKV 42.4 / 40.5 and 43.7 / 42.6, down 37.0 / 35.5 and 38.7 / 38.4;
@@ -113,8 +114,12 @@ static inline int pf_grid(int NRB, int MT, const GemmPlan& p) { return ((NRB + 2
 // 3016), and a single column of four tiles with 16 rows or more beyond the end, which buffer loads leave out and the waves would
 // multiply (72 rows at 7B widths, down 25.4 / 26.6 and 25.9 / 27.5; 104 rows 30.0 / 31.1 and 30.2 / 31.2; whole prompts of 80 and 96
 // rows 3.7 and 2.5 % slower with plain loads, 112 rows 1.3, 120 even, 128 rows 0.2 to 1.5 % faster).
+// Grouped experts (`cols` columns, each with rows of its own) take the same line without the last exception: 5 rows at d 1024, ffn 2048, two
+// experts, 48 and 96 work-groups, 22.4 / 20.7 and 7.3 / 6.8; 200 rows at Mixtral widths with two experts, down in 240 76.5 / 73.9, gate/up in 336
+// 184 / 197; 64 rows at d 1024, ffn 2816, eight experts, 288 each, 35.3 / 39.5 and 20.7 / 22.5.
+static inline bool plan_pf_one_round(int NRB, int cols, int n_cu, const GemmPlan& p) { return p.mw <= 2 && pf_grid(NRB, cols, p) <= n_cu; }
 static inline bool plan_pf_plain_loads(int NRB, int MT, int M, int n_cu, const GemmPlan& p) {
-  return p.mw <= 2 && pf_grid(NRB, MT, p) <= n_cu && !(p.mw == 2 && M <= 112);
+  return plan_pf_one_round(NRB, pf_cols(MT, p), n_cu, p) && !(p.mw == 2 && M <= 112);
 }
 
 // The same model for the grouped GEMMs of a mixture of experts: M rows x topk experts each, padded per expert to columns of

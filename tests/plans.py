@@ -21,6 +21,7 @@ void shim_moe(const int* a, int* o) {
 }
 int shim_whole_k(int NRB, int KS, int planes, int n_cu) { return plan_is_whole_k(NRB, KS, planes, n_cu); }
 int shim_plain_loads(int NRB, int MT, int M, int n_cu, int S, int rbw, int mw) { GemmPlan p{}; p.S = S; p.rbw = rbw; p.mw = mw; return plan_pf_plain_loads(NRB, MT, M, n_cu, p); }
+int shim_one_round(int NRB, int cols, int n_cu, int S, int rbw, int mw) { GemmPlan p{}; p.S = S; p.rbw = rbw; p.mw = mw; return plan_pf_one_round(NRB, cols, n_cu, p); }
 int shim_wk(int NRB, int KS, int MT, int n_cu, int big, int fixed, int q4) { return plan_is_wk(NRB, KS, MT, n_cu, big != 0, fixed != 0, q4 != 0); }
 // matrices: row blocks and k-steps of n of them, gate/up and down of an expert first; bf16 weights (one plane), two planes of activations
 int shim_experts_in_two(const int* m, int n, int n_cu, int* o) {
@@ -59,6 +60,12 @@ class Plans:
     def plain_loads(self, NRB, rows, p, n_cu=256):
         """Whether a launch of the large-M GEMM with plan `p` brings its tiles by plain loads (else by buffer loads)"""
         return bool(self.lib.shim_plain_loads(NRB, (rows + 31) // 32, rows, n_cu, p.S, p.rbw, p.mw))
+
+    def experts_plain_loads(self, s, rows, n_cu=256):
+        """The same of the grouped gate/up and down launches of a mixture: (gate/up, down)"""
+        gu, dn, cols = self.moe(s.d_model, s.d_ffn, (rows + 31) // 32 * 32, s.experts_per_tok, s.n_experts, n_cu)
+        cols = min(cols, rows * s.experts_per_tok)
+        return tuple(bool(self.lib.shim_one_round(NRB, cols, n_cu, p.S, p.rbw, p.mw)) for NRB, p in ((2 * s.d_ffn // 32, gu), (s.d_model // 32, dn)))
 
     def moe(self, d, F, M, topk, E, n_cu=256):
         """-> (gate/up plan, down plan, columns) for M rows of a mixture of E experts with widths d and F"""

@@ -129,6 +129,15 @@ def test_launches_that_bring_their_tiles_by_plain_loads(plans):
                     (3, 2, False, False), (3, 2, True, False), (4, 2, False, False)}, seen
 
 
+def test_expert_launches_that_bring_their_tiles_by_plain_loads(plans):
+    """A single round of work-groups, columns beyond rows x choices not counted; the oracle cases take both ways."""
+    narrow, mixtral = EXPERTS["d256-e64-top4"][0], synth.SHAPES["mixtral-8x7b"]
+    assert plans.experts_plain_loads(narrow, 3) == (True, True) and plans.experts_plain_loads(narrow, 150) == (False, False)
+    assert plans.experts_plain_loads(mixtral, 1) == (True, True) and plans.experts_plain_loads(mixtral, 300) == (False, False)
+    seen = {plain for s, lens, _ in EXPERTS.values() for rows in lens for plain in plans.experts_plain_loads(s, rows)}
+    assert seen == {True, False}
+
+
 WK_LAUNCHED = {(3, 2), (3, 3), (3, 4), (4, 2)}                           # (most row blocks of a work-group, row tiles) that gemm_wk() launches
 
 
