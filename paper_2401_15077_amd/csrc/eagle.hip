@@ -336,7 +336,7 @@ static size_t layout(eagle_ctx* c) {
   c->facts = a.take<RowFact>(Mm);
   c->ssq1 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32); c->ssq2 = a.take<float>(PLAN_MAX_NORM_GROUPS * 32);
   c->trace = a.take<unsigned long long>(1024 * 8);
-  c->cnt_gemm = a.take<int>(1024); c->cnt_attn = a.take<int>((size_t)128 * H);
+  c->cnt_gemm = a.take<int>(1024 * COUNTER_STRIDE); c->cnt_attn = a.take<int>((size_t)128 * H * COUNTER_STRIDE);
   for (auto& w : c->layers)                                     // (and the slices of each)
     if (w.moe && moe_in_two(c, w.e_gu[0], w.e_dn[0])) { worst2 = std::max(worst2, (size_t)g.n_experts * xk_plan(c, w.e_dn[0]).S * w.e_dn[0].Npad * 32); break; }
   c->pt2_all = worst2;
@@ -776,15 +776,7 @@ static int collect_gemm_events(eagle_ctx* c) {
   return EAGLE_OK;
 }
 
-// KV splits of the attention kernel for `tokens` keys and `units` (head, sequence, row block) triples: one 32-token
-// block per wave (128 tokens per work-group) while that keeps the grid within one work-group per CU -- the kernel's
-// registers allow no more, and a second round of work-groups costs more than a wave walking a few blocks in turn.  Up to 192
-// tokens stay in one work-group: a second block in two of its waves costs less than the exchange between two work-groups (a
-// tiny model's launch 8.9 -> 5.1 us; 7B with 139 tokens: a request of 8 layers 22.6 -> 22.3 ms).
-static int attn_splits(const eagle_ctx* c, int tokens, int units) {
-  const int by_tokens = !c->fixed_sums && tokens <= 192 ? 1 : (tokens + 127) / 128, by_cus = std::max(1, c->n_cu / std::max(1, units));
-  return std::max(1, std::min(16, std::min(by_tokens, by_cus)));
-}
+static int attn_splits(const eagle_ctx* c, int tokens, int units) { return plan_attn_splits(c->fixed_sums, tokens, units, c->n_cu); }
 
 // Algorithmic HBM bytes of one attention launch: keys and values of every sequence's cached context plus the pass's
 // own rows, once (host mirror of the cached lengths; prefill chunks: the chunk's causal prefix).
@@ -815,6 +807,10 @@ static AttnArgs attn_args(eagle_ctx* c, const Pass& pass, const KVCache& kv, int
   a.facts = c->facts; a.kv = kv; a.Q = c->Q; a.part_o = c->part_o; a.part_ml = c->part_ml;
   a.H = c->cfg.n_heads; a.n_splits = n_splits; a.n_new = n_new; a.scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
   a.counters = c->cnt_attn; a.xf_out = xf_out; a.nplanes = c->NXP; a.MT = MT; a.rblocks = rblocks; a.trace = trace;
+  const bool known = pass.ctx_known && (pass.kind == PASS_VERIFY || pass.kind == PASS_VANILLA || pass.kind == PASS_DRAFT_LEVEL);
+  const int before = pass.kind == PASS_DRAFT_LEVEL ? 1 : 0;     // (row_info)
+  a.slot0 = known ? pass.seq0 : -1;
+  a.ctx[0] = pass.ctx0 - before; a.ctx[1] = pass.ctx1 - before; a.ctx[2] = pass.ctx2 - before; a.ctx[3] = pass.ctx3 - before;
   return a;
 }
 

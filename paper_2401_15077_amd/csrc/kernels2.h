@@ -22,6 +22,10 @@
 __device__ inline void coh_store(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float coh_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// Ints between two arrival counters: a 256-byte piece of memory each.  (Side by side, the arrivals of a launch were 256 atomic additions to two
+// cache lines: O 11.7 -> 11.4 us, the head's O 10.6 -> 10.2, fc 17.4 -> 17.2 at 7B widths.)
+constexpr int COUNTER_STRIDE = 64;
+
 // 16-byte agent-scope accesses: buffer instructions carry the scope bit (aux 16 = sc1); byte offsets below 2 GiB.
 __device__ inline __amdgpu_buffer_rsrc_t coh_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7FFFFFFF, 0x00020000);
@@ -744,9 +748,9 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   publish_wait();                                               // every coherent store above has been acknowledged
   __syncthreads();
   if (threadIdx.x == 0) {
-    int old = __hip_atomic_fetch_add(g.counters + grp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int old = __hip_atomic_fetch_add(g.counters + grp * COUNTER_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = (old == g.S - 1);
-    if (s_last) __hip_atomic_store(g.counters + grp, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+    if (s_last) __hip_atomic_store(g.counters + grp * COUNTER_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
   }
   __syncthreads();
   TRACE_STAMP(tr, 3);
@@ -1362,9 +1366,9 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
   publish_wait();
   __syncthreads();
   if (threadIdx.x == 0) {
-    int old = __hip_atomic_fetch_add(g.counters + grp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int old = __hip_atomic_fetch_add(g.counters + grp * COUNTER_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = (old == (EXPERTS ? g.S * __popcll(used) : g.S) - 1);
-    if (s_last) __hip_atomic_store(g.counters + grp, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (s_last) __hip_atomic_store(g.counters + grp * COUNTER_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
   if (!s_last) return;
@@ -1467,34 +1471,50 @@ __device__ inline void load8(const bf16_t* p, float* x) {
   x[6] = __builtin_bit_cast(float, r.w << 16); x[7] = __builtin_bit_cast(float, r.w & 0xFFFF0000u);
 }
 
-// Folds NS splits (e, e+1, ...) of one (row, head) into the running (max, denominator, outputs) of IT items (rows) at once:
-// every load of the chunk is in flight before the first use.
-template <int DH, int IT, int NS>
-__device__ __forceinline__ void attn_merge_chunk(const float* part_o, const float* part_ml, const size_t* e0, int d0, float* mx, float* den, f32x4* x) {
-  float msv[IT][NS], lsv[IT][NS];
+// Folds NS splits of one (row, head) into the running (max, denominator, outputs) of IT items (rows, `row_o` / `row_ml` bytes apart in the two
+// buffers) at once: every load of the chunk is in flight before the first use.  oo[i], om[i]: a lane's byte offsets of the first split's outputs
+// and (max, sum) pairs.  FIRST: nothing to rescale.
+// What a merge takes is instructions on one chain, not bytes (a wave alone on its SIMD issues one in four to eight cycles): so the addresses are
+// 32-bit offsets with the split in the instruction, two pairs come with one load, and a thread merges all its rows at once.  From the last
+// arrival to the end of a launch at 7B (26 rows, five splits), by time stamps: 3.6 us with 64-bit addresses, a load per number and two rows at a
+// time, 2.5 us now; the loads' own round trip is 0.5.
+template <int DH, int IT, int NS, bool FIRST>
+__device__ __forceinline__ void attn_merge_chunk(__amdgpu_buffer_rsrc_t po, __amdgpu_buffer_rsrc_t pm, const uint32_t* oo, const uint32_t* om, uint32_t row_o, uint32_t row_ml,
+                                                 float* mx, float* den, f32x4* x) {
+  u32x4 ml[IT][(NS + 1) / 2];
   f32x4 ov[IT][NS];
 #pragma unroll
-  for (int i = 0; i < IT; ++i)
+  for (int i = 0; i < IT; ++i) {
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      const size_t e = e0[i] + u;
-      msv[i][u] = coh_load(part_ml + e * 2);
-      lsv[i][u] = coh_load(part_ml + e * 2 + 1);
-      ov[i][u] = coh_load16(part_o, (uint32_t)((e * DH + d0) * 4));
+    for (int u = 0; u + 1 < NS; u += 2) ml[i][u / 2] = __builtin_amdgcn_raw_buffer_load_b128(pm, om[i] + u * 8, i * row_ml, 16);
+    if (NS & 1) {
+      const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(pm, om[i] + (NS - 1) * 8, i * row_ml, 16));
+      ml[i][NS / 2].x = v.x; ml[i][NS / 2].y = v.y;
     }
 #pragma unroll
+    for (int u = 0; u < NS; ++u) ov[i][u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(po, oo[i] + u * (DH * 4), i * row_o, 16));
+  }
+#pragma unroll
   for (int i = 0; i < IT; ++i) {
+    float msv[NS], lsv[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      msv[u] = __builtin_bit_cast(float, u & 1 ? ml[i][u / 2].z : ml[i][u / 2].x);
+      lsv[u] = __builtin_bit_cast(float, u & 1 ? ml[i][u / 2].w : ml[i][u / 2].y);
+    }
     float cmx = mx[i];
 #pragma unroll
-    for (int u = 0; u < NS; ++u) cmx = fmaxf(cmx, msv[i][u]);
-    const float resc = (mx[i] == -INFINITY) ? 0.f : __expf(mx[i] - cmx);   // nothing to rescale on the first chunk
-    den[i] *= resc;
-    x[i] *= resc;
+    for (int u = 0; u < NS; ++u) cmx = fmaxf(cmx, msv[u]);
+    if constexpr (!FIRST) {
+      const float resc = (mx[i] == -INFINITY) ? 0.f : __expf(mx[i] - cmx);
+      den[i] *= resc;
+      x[i] *= resc;
+    }
     mx[i] = cmx;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const float wv = (msv[i][u] != -INFINITY) ? __expf(msv[i][u] - cmx) : 0.f;
-      den[i] += wv * lsv[i][u];
+      const float wv = (msv[u] != -INFINITY) ? __expf(msv[u] - cmx) : 0.f;
+      den[i] += wv * lsv[u];
       x[i] += wv * ov[i][u];
     }
   }
@@ -1504,8 +1524,76 @@ struct AttnArgs {
   int rows_per_seq, causal;                // rows of a sequence in the pass; pending rows and prompts see their own rows causally
   const RowFact* facts; KVCache kv; const float* Q; float* part_o; float* part_ml;
   int H, n_splits, n_new; float scale; int* counters; bf16_t* xf_out; int nplanes, MT, rblocks;   // MT = 32-row tiles of the XF output
+  // positions in front of the new ones in the first four sequences as the host knows them, and the first sequence's slot (-1: the row facts hold both)
+  int slot0, ctx[4];
   unsigned long long* trace;               // profiling builds only
 };
+
+// Four consecutive columns of attention output, as input of the output projection: byte offsets of row m, columns k.. of plane 0.
+__device__ __forceinline__ uint32_t xf_bytes(int m, int k, int KS) { return ((uint32_t)(m >> 5) * (uint32_t)KS + (k >> 4)) * 1024u + (m & 31) * 16u + ((k & 15) >> 3) * 512u + (k & 7) * 2u; }
+__device__ __forceinline__ void attn_store(const AttnArgs& A, __amdgpu_buffer_rsrc_t xf, int m, int k, f32x4 v) {
+  const int KS = A.H * A.kv.head_dim / 16;
+  const uint32_t at = xf_bytes(m, k, KS), plane = (uint32_t)A.MT * (uint32_t)KS * 1024u;
+  float r[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    if (q < A.nplanes) {
+      u32x2 u; u.x = split_pair(r[0], r[1]); u.y = split_pair(r[2], r[3]);
+      __builtin_amdgcn_raw_buffer_store_b64(u, xf, at, q * plane, 0);
+    }
+}
+
+// The rows q0, q0 + RT, ... (IT of them) of one (sequence, head), columns d0..d0+3: all splits together.  at: byte offset of (row q0, split 0)'s outputs.
+template <int DH, int IT>
+__device__ __forceinline__ void attn_merge(const AttnArgs& A, __amdgpu_buffer_rsrc_t xf, int r0, int R, int hd, int q0, int d0, uint32_t at) {
+  constexpr int RT = 256 / (DH / 4);
+  const int n_splits = A.n_splits;
+  const __amdgpu_buffer_rsrc_t po = coh_rsrc(A.part_o), pm = coh_rsrc(A.part_ml);
+  const uint32_t row_o = (uint32_t)(RT * A.H * n_splits) * (DH * 4), row_ml = (uint32_t)(RT * A.H * n_splits) * 8u;
+  const uint32_t ml_at = ((uint32_t)(r0 + q0) * A.H + hd) * n_splits * 8u;
+  uint32_t oo[IT], om[IT];
+  float mx[IT], den[IT];
+  f32x4 x[IT];
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const bool row = q0 + RT * i < R;
+    oo[i] = row ? at : OUT_OF_RANGE; om[i] = row ? ml_at : OUT_OF_RANGE;
+    mx[i] = -INFINITY; den[i] = 0.f;
+    x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#define CHUNK(NS, FIRST) attn_merge_chunk<DH, IT, NS, FIRST>(po, pm, oo, om, row_o, row_ml, mx, den, x)
+  switch (min(n_splits, 8)) {                                  // uniform: exactly the loads that are needed
+    case 2: CHUNK(2, true); break;
+    case 3: CHUNK(3, true); break;
+    case 4: CHUNK(4, true); break;
+    case 5: CHUNK(5, true); break;
+    case 6: CHUNK(6, true); break;
+    case 7: CHUNK(7, true); break;
+    default: CHUNK(8, true); break;
+  }
+  if (n_splits > 8) {                                           // (at most 16)
+#pragma unroll
+    for (int i = 0; i < IT; ++i) { oo[i] += 8 * (DH * 4); om[i] += 8 * 8; }
+    switch (n_splits - 8) {
+      case 1: CHUNK(1, false); break;
+      case 2: CHUNK(2, false); break;
+      case 3: CHUNK(3, false); break;
+      case 4: CHUNK(4, false); break;
+      case 5: CHUNK(5, false); break;
+      case 6: CHUNK(6, false); break;
+      case 7: CHUNK(7, false); break;
+      default: CHUNK(8, false); break;
+    }
+  }
+#undef CHUNK
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const int q2 = q0 + RT * i;
+    if (q2 >= R) continue;
+    const float inv = den[i] > 0.f ? 1.0f / den[i] : 0.f;
+    attn_store(A, xf, r0 + q2, hd * DH + d0, x[i] * inv);
+  }
+}
 
 // Work-group = (KV split, query head, (sequence of the pass, 32-row block of that sequence's rows)).
 template <typename CT, int DH>
@@ -1518,11 +1606,9 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   float* ml_s = o_s + 4 * 32 * OS;          // [4 waves][2][32]
   __shared__ int s_last;
   const int split = blockIdx.x, hd = blockIdx.y, z = blockIdx.z;
-  const int H = A.H, n_splits = A.n_splits, n_new = A.n_new, MT = A.MT, nplanes = A.nplanes;
+  const int H = A.H, n_splits = A.n_splits, n_new = A.n_new;
   const KVCache& kv = A.kv;
   const float* Q = A.Q;
-  float *part_o = A.part_o, *part_ml = A.part_ml;
-  bf16_t* xf_out = A.xf_out;
   const int seq_l = z / A.rblocks, rblk = z % A.rblocks;
   // optional time stamps: 0 entered, 1 keys/values consumed, 2 waves merged + partials written, 3 arrived, 4 splits merged
   unsigned long long* tr = TRACE_PTR((A.trace && threadIdx.x == 0 && seq_l == 0) ? A.trace + ((size_t)hd * n_splits + split) * 8 : nullptr);
@@ -1541,7 +1627,9 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   // (the rows' facts were written by the pass's first kernel)
   const bool causal = A.causal;
   const RowFact fq = A.facts[r0 + min(q, R - 1)];                 // this lane's query row
-  const int seq = __builtin_amdgcn_readfirstlane(fq.seq), base = __builtin_amdgcn_readfirstlane(fq.base);
+  int seq, base;
+  if (A.slot0 >= 0) { seq = A.slot0 + seq_l; base = seq_l == 0 ? A.ctx[0] : seq_l == 1 ? A.ctx[1] : seq_l == 2 ? A.ctx[2] : A.ctx[3]; }
+  else { seq = __builtin_amdgcn_readfirstlane(fq.seq); base = __builtin_amdgcn_readfirstlane(fq.base); }
   const int rel = fq.rel;
   const unsigned long long mask = (unsigned long long)fq.mask_hi << 32 | fq.mask_lo;
   // causal passes (prompt chunks, pending rows): the rows of this 32-row block see no new token beyond its own last row,
@@ -1558,10 +1646,13 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   // A block's address is the same for the whole wave and stays in scalar registers; a lane adds a 32-bit offset.  (With an address
   // per lane the 64 value loads of a block took their offsets from vector registers; that, a branch per score for the mask and
   // the queries requested behind the facts: 15.2 us a launch at 7B, 550 keys, 26 rows, 13.9 without.)
+  // Where the host knows the cached lengths, the first block's address needs one look-up and its keys are requested before the queries are
+  // converted.  (That, the merge of the waves with all its reads out at once, and the merge of the splits above: 13.6 -> 11.4 us.  With the first
+  // values requested there too, the queries wait behind them: 12.3.)
   float kx[KSN][8];
   size_t blk = 0;
   auto block_of = [&](int tok) -> size_t {
-    const int phys = __builtin_amdgcn_readfirstlane(kv.page_table[seq * kv.pages_per_seq + (tok >> kv.page_shift)]);
+    const int phys = ((const __attribute__((address_space(4))) int*)kv.page_table)[seq * kv.pages_per_seq + (tok >> kv.page_shift)];
     return (((size_t)phys * kv.n_kv_heads + kvh) << kv.page_shift | (size_t)(tok & ((1 << kv.page_shift) - 1))) * DH;
   };
   const uint32_t k_lane = (uint32_t)((lane & 31) * DH + 8 * hh), v_lane = (uint32_t)(4 * hh * DH + (lane & 31));
@@ -1584,6 +1675,11 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
           vx[j][b][t] = cache_load(vp + tl * DH + 32 * b + v_lane);
         }
   };
+  {
+    const int tok0 = t_begin + 32 * w;
+    blk = block_of(tok0 < t_end ? tok0 : 0);                   // (a wave without a block requests one too: behind a branch its wait for the queries would be a wait for all)
+    load_keys(blk);
+  }
   // The scaled queries as bf16 hi + lo B-operand fragments live in LDS, built once by the four waves together (wave w
   // converts k-steps w, w+4, ...); they share the memory of o_s, which is not written before every wave has left the
   // key loop.  (One load and one conversion of the queries per work-group instead of one per wave.)
@@ -1600,10 +1696,6 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
     q_s[(1 * KSN + ks) * 64 + lane] = l8;
   }
   __syncthreads();
-  {
-    const int tok0 = t_begin + 32 * w;
-    if (tok0 < t_end) { blk = block_of(tok0); load_keys(blk); }
-  }
   float m_run = -INFINITY, l_run = 0.f;
   f32x16 oacc[DB];
 #pragma unroll
@@ -1691,31 +1783,40 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   // other splits' below, in contiguous runs.  (With a row per lane each 16-byte access of a wave touched 64 cache lines.)
   constexpr int LD = DH / 4, RT = 256 / LD, NI = 32 / RT;       // lanes per row, rows at a time, items per thread
   const int d0 = (tid % LD) * 4, q0 = tid / LD;
-  const int KSX = H * DH / 16;
+  const uint32_t at = ((uint32_t)(r0 + q0) * H + hd) * n_splits * (DH * 4) + d0 * 4;   // outputs of (row q0, split 0)
+  const __amdgpu_buffer_rsrc_t xf = __builtin_amdgcn_make_buffer_rsrc((void*)A.xf_out, 0, 0x7FFFFFFF, 0x00020000);
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int q2 = q0 + RT * i;
-    if (q2 >= R) continue;
+    float mw[4], lw[4];
+    f32x4 ow[4];
+#pragma unroll
+    for (int ww = 0; ww < 4; ++ww) {
+      mw[ww] = ml_s[(ww * 2) * 32 + q2]; lw[ww] = ml_s[(ww * 2 + 1) * 32 + q2];
+      ow[ww] = *(const f32x4*)(o_s + ((size_t)ww * 32 + q2) * OS + d0);
+    }
     float mm = -INFINITY;
 #pragma unroll
-    for (int ww = 0; ww < 4; ++ww) mm = fmaxf(mm, ml_s[(ww * 2) * 32 + q2]);
+    for (int ww = 0; ww < 4; ++ww) mm = fmaxf(mm, mw[ww]);
     float L = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ww = 0; ww < 4; ++ww) {
-      const float mw = ml_s[(ww * 2) * 32 + q2];
-      const float wgt = (mw == -INFINITY) ? 0.f : __expf(mw - mm);
-      L += wgt * ml_s[(ww * 2 + 1) * 32 + q2];
-      o += wgt * *(const f32x4*)(o_s + ((size_t)ww * 32 + q2) * OS + d0);
+      const float wgt = (mw[ww] == -INFINITY) ? 0.f : __expf(mw[ww] - mm);
+      L += wgt * lw[ww];
+      o += wgt * ow[ww];
     }
+    if (q2 >= R) continue;
     if (n_splits == 1) {
       const float inv = L > 0.f ? 1.0f / L : 0.f;
       o *= inv;
-      xf_store4(xf_out, r0 + q2, hd * DH + d0, MT, KSX, nplanes, o);
+      attn_store(A, xf, r0 + q2, hd * DH + d0, o);
     } else {
-      const size_t e = ((size_t)(r0 + q2) * H + hd) * n_splits + split;
-      coh_store16(part_o, (uint32_t)((e * DH + d0) * 4), o);
-      if (d0 == 0) { coh_store(part_ml + e * 2, mm); coh_store(part_ml + e * 2 + 1, L); }
+      coh_store16(A.part_o, at + (uint32_t)(RT * i * H * n_splits + split) * (DH * 4), o);
+      if (d0 == 0) {
+        const u32x2 u = {__builtin_bit_cast(uint32_t, mm), __builtin_bit_cast(uint32_t, L)};
+        __builtin_amdgcn_raw_buffer_store_b64(u, coh_rsrc(A.part_ml), (uint32_t)(((r0 + q2) * H + hd) * n_splits + split) * 8u, 0, 16);
+      }
     }
   }
   TRACE_STAMP(tr, 2);
@@ -1723,7 +1824,7 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   publish_wait();
   __syncthreads();
   if (tid == 0) {
-    int* cnt = A.counters + z * H + hd;
+    int* cnt = A.counters + (z * H + hd) * COUNTER_STRIDE;
     int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = (old == n_splits - 1);
     if (s_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1732,45 +1833,11 @@ __global__ __launch_bounds__(256) void k2_attn(AttnArgs A) {
   TRACE_STAMP(tr, 3);
   if (!s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  // merge the splits of (sequence, head), two rows of a thread at a time.  Every load of up to 8 splits -- (max, sum) pairs and
-  // partial outputs -- is in flight at once, so the merge costs one memory round trip per pair of rows; more splits continue
-  // with a running rescale, in split order.
-  constexpr int IT = 2;
-#pragma unroll
-  for (int i0 = 0; i0 < NI; i0 += IT) {
-    if (q0 + RT * i0 >= R) break;
-    size_t rowhead[IT];
-    float mx[IT], den[IT];
-    f32x4 x[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      rowhead[i] = ((size_t)(r0 + min(q0 + RT * (i0 + i), R - 1)) * H + hd) * n_splits;
-      mx[i] = -INFINITY; den[i] = 0.f;
-      x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    for (int sp0 = 0; sp0 < n_splits; sp0 += 8) {
-      size_t e[IT];
-#pragma unroll
-      for (int i = 0; i < IT; ++i) e[i] = rowhead[i] + sp0;
-      switch (min(n_splits - sp0, 8)) {                        // uniform: exactly the loads that are needed
-        case 1: attn_merge_chunk<DH, IT, 1>(part_o, part_ml, e, d0, mx, den, x); break;
-        case 2: attn_merge_chunk<DH, IT, 2>(part_o, part_ml, e, d0, mx, den, x); break;
-        case 3: attn_merge_chunk<DH, IT, 3>(part_o, part_ml, e, d0, mx, den, x); break;
-        case 4: attn_merge_chunk<DH, IT, 4>(part_o, part_ml, e, d0, mx, den, x); break;
-        case 5: attn_merge_chunk<DH, IT, 5>(part_o, part_ml, e, d0, mx, den, x); break;
-        case 6: attn_merge_chunk<DH, IT, 6>(part_o, part_ml, e, d0, mx, den, x); break;
-        case 7: attn_merge_chunk<DH, IT, 7>(part_o, part_ml, e, d0, mx, den, x); break;
-        default: attn_merge_chunk<DH, IT, 8>(part_o, part_ml, e, d0, mx, den, x); break;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      const int q2 = q0 + RT * (i0 + i);
-      if (q2 >= R) continue;
-      const float inv = den[i] > 0.f ? 1.0f / den[i] : 0.f;
-      xf_store4(xf_out, r0 + q2, hd * DH + d0, MT, KSX, nplanes, x[i] * inv);
-    }
-  }
+  // merge the splits of (sequence, head).  Every load of up to 8 splits of a thread's rows -- (max, sum) pairs and partial outputs -- is in
+  // flight at once, so the merge costs one memory round trip; more splits continue with a running rescale, in split order.
+  if (R <= RT) attn_merge<DH, 1>(A, xf, r0, R, hd, q0, d0, at);
+  else if (R <= 2 * RT) attn_merge<DH, 2>(A, xf, r0, R, hd, q0, d0, at);
+  else attn_merge<DH, NI>(A, xf, r0, R, hd, q0, d0, at);
   TRACE_STAMP(tr, 4);
 }
 

@@ -62,6 +62,16 @@ static inline bool plan_is_wk(int NRB, int KS, int MT, int n_cu, bool big_gemm, 
 // rows 40 / 27, 2011 rows 690 / 290.
 static inline bool plan_is_prompt_attn(int rows, int heads, int n_cu) { return rows >= 256 && heads * ((rows + 31) / 32) >= 2 * n_cu; }
 
+// KV splits of the attention kernel for `tokens` keys and `units` (head, sequence, row block) triples: one 32-token
+// block per wave (128 tokens per work-group) while that keeps the grid within one work-group per CU -- the kernel's
+// registers allow no more, and a second round of work-groups costs more than a wave walking a few blocks in turn.  Up to 192
+// tokens stay in one work-group: a second block in two of its waves costs less than the exchange between two work-groups (a
+// tiny model's launch 8.9 -> 5.1 us; 7B with 139 tokens: a request of 8 layers 22.6 -> 22.3 ms).
+static inline int plan_attn_splits(bool fixed_sums, int tokens, int units, int n_cu) {
+  const int by_tokens = !fixed_sums && tokens <= 192 ? 1 : (tokens + 127) / 128, by_cus = std::max(1, n_cu / std::max(1, units));
+  return std::max(1, std::min(16, std::min(by_tokens, by_cus)));
+}
+
 // Tile shape and work split of the large-M GEMM (k_gemm_pf): the (row blocks per wave, wave columns, K slices) that is cheapest
 // in a model of two terms, in us.  What the busiest CU multiplies: rounds x (32 x 32 tiles of a work-group) x k-steps of a slice
 // x the shape's measured time per tile and k-step.  Groups of work-groups that share a weight tile go round the 8 XCDs, so a

@@ -32,6 +32,7 @@ int shim_experts_in_two(const int* m, int n, int n_cu, int* o) {
   o[0] = (m[0] + grid - 1) / grid; o[1] = dn.S; o[2] = dn.nrmax;
   return plan_experts_in_two(m[0], m[1], m[2], m[3], 2, 1, n_cu, pt);
 }
+int shim_attn_splits(int fixed, int tokens, int units, int n_cu) { return plan_attn_splits(fixed != 0, tokens, units, n_cu); }
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
 int shim_q4_w_span(int nr, int KS) { return q4_w_span(nr, KS); }
@@ -73,6 +74,10 @@ class Plans:
         o = (ctypes.c_int * 9)()
         self.lib.shim_moe(a, o)
         return Plan(*o[:4]), Plan(*o[4:8]), o[8]
+
+    def attn_splits(self, fixed, tokens, units, n_cu=256):
+        """Work-groups that share the keys of `units` (head, sequence, row block) triples"""
+        return self.lib.shim_attn_splits(fixed, tokens, units, n_cu)
 
     def whole_k(self, NRB, KS, planes, n_cu=256):
         return bool(self.lib.shim_whole_k(NRB, KS, planes, n_cu))
