@@ -86,7 +86,6 @@ struct eagle_ctx {
   // 4-bit weights: epilogue classes (1 << epi) that take the streamed split-K kernel.  Measured at d = 4096, 26 rows (us, streamed
   // split-K / LDS-staged split-K, whose 128 KB slice limit forces 11 slices at K = 11008 / whole-K): O 10.5 / 12.0 / 14.6, down
   // 16.4 / 24.5 / 29.0, FC (4 rows) 12.9 / 17.3 / 18.5; QKV 20.6 streamed, 18.5 whole-K: the residual epilogue only.
-  int q4_xk_mask = 1 << EPI_RESID;
   int NWP, NXP, elt, kv_elt;         // weight planes, activation planes, bytes per weight / per KV element
   TreeDev tree_h; TreeDev* tree_d;
   int M, D, Mmax, max_level_rows;
@@ -527,7 +526,6 @@ extern "C" int eagle_init(const eagle_config* cfg, void* workspace_dev, size_t w
   memset(&c->prof, 0, sizeof(c->prof));
 #ifdef EAGLE_TRACE
   if (const char* t = getenv("EAGLE_Q4_STAGED")) c->q4_staged = atoi(t) != 0;
-  if (const char* t = getenv("EAGLE_Q4_XK")) c->q4_xk_mask = atoi(t);
   if (const char* t = getenv("EAGLE_GEMM_TRACE")) c->trace_sel = atoi(t);
   if (const char* t = getenv("EAGLE_ATTN_TRACE")) c->attn_trace_sel = atoi(t);
   if (getenv("EAGLE_EXPAND_TRACE")) c->expand_trace = 1;
@@ -1000,54 +998,55 @@ static hipError_t launch_k2(eagle_ctx* c, double bytes, const Gemm2& g, size_t l
   return launch_k(c, c->cur_class, bytes, Q4 ? "k2_gemm<4-bit weights>" : "k2_gemm", k2_gemm<NWP, NXP, RW, DEPTH, Q4>, dim3(g.groups * g.S), dim3(V2_THREADS), lds, g);
 }
 
-template <int NRMAX, bool HALF = false, int NWP = 1, int NXP = 2, bool EXPERTS = false>
-static hipError_t launch_fk(eagle_ctx* c, double bytes, const Gemm2& g, int grid, int experts = 1) {
+template <int EPI, int NRMAX, bool HALF, int NWP, int NXP, bool Q4, bool EXPERTS>
+static hipError_t launch_fk_epi(eagle_ctx* c, double bytes, Gemm2& g, int grid, int experts) {
   static bool attr_set = false;
   const size_t lds = (size_t)8 * NRMAX * 4096;
   if (lds > 144 * 1024) return hipErrorInvalidValue;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<NWP, NXP, NRMAX, HALF, false, EXPERTS>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<EPI, NWP, NXP, NRMAX, HALF, Q4, EXPERTS>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  return launch_k(c, c->cur_class, bytes, HALF ? "k2_gemm_fk<half blocks>" : "k2_gemm_fk", k2_gemm_fk<NWP, NXP, NRMAX, HALF, false, EXPERTS>, dim3(grid, experts), dim3(V2_THREADS), lds, g);
+  const Share sh = share_of(HALF ? 2 * g.NRB : g.NRB, grid);
+  g.groups = grid; g.share_a = sh.a; g.share_b = sh.b;
+  return launch_k(c, c->cur_class, bytes, Q4 ? "k2_gemm_fk<4-bit weights>" : HALF ? "k2_gemm_fk<half blocks>" : "k2_gemm_fk", k2_gemm_fk<EPI, NWP, NXP, NRMAX, HALF, Q4, EXPERTS>,
+                  dim3(grid, experts), dim3(V2_THREADS), lds, g);
 }
-
-template <int NRMAX>
-static hipError_t launch_fk_q4(eagle_ctx* c, double bytes, const Gemm2& g, int grid) {
-  static bool attr_set = false;
-  const size_t lds = (size_t)8 * NRMAX * 4096;
-  if (lds > 144 * 1024) return hipErrorInvalidValue;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_fk<1, 2, NRMAX, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
+template <int NRMAX, bool HALF = false, int NWP = 1, int NXP = 2, bool EXPERTS = false, bool Q4 = false>
+static hipError_t launch_fk(eagle_ctx* c, double bytes, Gemm2& g, int grid, int experts = 1) {
+  if constexpr (HALF) return launch_fk_epi<EPI_QKV, NRMAX, HALF, NWP, NXP, Q4, EXPERTS>(c, bytes, g, grid, experts);
+  else if constexpr (EXPERTS) return launch_fk_epi<EPI_SWIGLU, NRMAX, HALF, NWP, NXP, Q4, EXPERTS>(c, bytes, g, grid, experts);
+  else {
+    if constexpr (NRMAX <= 2)
+      if (g.epi == EPI_RESID) return launch_fk_epi<EPI_RESID, NRMAX, HALF, NWP, NXP, Q4, EXPERTS>(c, bytes, g, grid, experts);
+    switch (g.epi) {
+      case EPI_QKV: return launch_fk_epi<EPI_QKV, NRMAX, HALF, NWP, NXP, Q4, EXPERTS>(c, bytes, g, grid, experts);
+      case EPI_SWIGLU: return launch_fk_epi<EPI_SWIGLU, NRMAX, HALF, NWP, NXP, Q4, EXPERTS>(c, bytes, g, grid, experts);
+      case EPI_LOGITS: return launch_fk_epi<EPI_LOGITS, NRMAX, HALF, NWP, NXP, Q4, EXPERTS>(c, bytes, g, grid, experts);
+      default: return hipErrorInvalidValue;
+    }
   }
-  return launch_k(c, c->cur_class, bytes, "k2_gemm_fk<4-bit weights>", k2_gemm_fk<1, 2, NRMAX, false, true>, dim3(grid), dim3(V2_THREADS), lds, g);
 }
 
-template <int NRMAX, bool EXPERTS = false>
-static hipError_t launch_xk(eagle_ctx* c, double bytes, const Gemm2& g, int experts = 1) {
-  static bool attr_set = false;
-  const size_t lds = (size_t)8 * NRMAX * 4096;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_xk<1, 2, NRMAX, false, EXPERTS>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  return launch_k(c, c->cur_class, bytes, "k2_gemm_xk", k2_gemm_xk<1, 2, NRMAX, false, EXPERTS>, dim3(g.groups * g.S, experts), dim3(V2_THREADS), lds, g);
-}
-
-template <int NRMAX>
-static hipError_t launch_xk_q4(eagle_ctx* c, double bytes, const Gemm2& g) {
+template <bool RESID, int NRMAX, bool Q4, bool EXPERTS>
+static hipError_t launch_xk_epi(eagle_ctx* c, double bytes, Gemm2& g, int experts) {
   static bool attr_set = false;
   const size_t lds = (size_t)8 * NRMAX * 4096;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_xk<1, 2, NRMAX, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k2_gemm_xk<RESID, 2, NRMAX, Q4, EXPERTS>, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  return launch_k(c, c->cur_class, bytes, "k2_gemm_xk<4-bit weights>", k2_gemm_xk<1, 2, NRMAX, true>, dim3(g.groups * g.S), dim3(V2_THREADS), lds, g);
+  g.share_a = magic_of(g.groups); g.S_magic = magic_of(g.S);
+  if (!magic_holds((uint64_t)g.groups * g.NRB, g.groups) || !magic_holds((uint64_t)g.S * (Q4 ? g.NG : g.KS), g.S)) return hipErrorInvalidValue;   // (at most 256 groups of 4 row blocks, 16 slices)
+  return launch_k(c, c->cur_class, bytes, Q4 ? "k2_gemm_xk<4-bit weights>" : "k2_gemm_xk", k2_gemm_xk<RESID, 2, NRMAX, Q4, EXPERTS>, dim3(g.S, g.groups, experts), dim3(V2_THREADS), lds, g);
+}
+template <int NRMAX, bool EXPERTS = false, bool Q4 = false>
+static hipError_t launch_xk(eagle_ctx* c, double bytes, Gemm2& g, int experts = 1) {
+  if constexpr (!EXPERTS && !Q4)
+    if (g.epi != EPI_RESID) return launch_xk_epi<false, NRMAX, Q4, EXPERTS>(c, bytes, g, experts);
+  return launch_xk_epi<true, NRMAX, Q4, EXPERTS>(c, bytes, g, experts);
 }
 
 // Work split of the streamed split-K kernel for 4-bit weights: slices of whole groups, at least one group per wave, at
@@ -1080,14 +1079,14 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   if (groups_out) *groups_out = p.groups;
   const double bytes = w.bytes(c->elt) * experts;
   hipError_t e;
-  if (w.q4 && ((c->q4_xk_mask >> g.epi) & 1)) {
+  if (w.q4 && g.epi == EPI_RESID) {
     const PlanXK px = plan_xk_q4(w.NRB, w.NG, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
     if (px.S > 0) {
       g.S = px.S; g.groups = px.groups; g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
       g.trace = nullptr;
       if (groups_out) *groups_out = px.groups;
       if (g.ssq_out && px.groups > PLAN_MAX_NORM_GROUPS) return fail(EAGLE_EINVAL, "internal: more than 256 row groups feed a norm");
-      e = px.nrmax <= 1 ? launch_xk_q4<1>(c, bytes, g) : px.nrmax == 2 ? launch_xk_q4<2>(c, bytes, g) : launch_xk_q4<3>(c, bytes, g);
+      e = px.nrmax <= 1 ? launch_xk<1, false, true>(c, bytes, g) : px.nrmax == 2 ? launch_xk<2, false, true>(c, bytes, g) : launch_xk<3, false, true>(c, bytes, g);
       if (e != hipSuccess) return fail(EAGLE_EHIP, "4-bit gemm launch failed: %s", hipGetErrorString(e));
       return EAGLE_OK;
     }
@@ -1116,7 +1115,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;
     if (groups_out) *groups_out = grid;
-    e = nrmax <= 1 ? launch_fk_q4<1>(c, bytes, g, grid) : nrmax == 2 ? launch_fk_q4<2>(c, bytes, g, grid) : launch_fk_q4<3>(c, bytes, g, grid);
+    e = nrmax <= 1 ? launch_fk<1, false, 1, 2, false, true>(c, bytes, g, grid) : nrmax == 2 ? launch_fk<2, false, 1, 2, false, true>(c, bytes, g, grid) : launch_fk<3, false, 1, 2, false, true>(c, bytes, g, grid);
     if (e != hipSuccess) return fail(EAGLE_EHIP, "4-bit gemm launch failed: %s", hipGetErrorString(e));
     return EAGLE_OK;
   }

@@ -79,35 +79,47 @@ __device__ inline float block_row_rstd(const float* ssq, int groups, float inv_d
   __syncthreads();
   return tmp[16];
 }
-// The same value for all 32 rows at once, computed by a 512-thread block: thread (m, class c) requests its class's groups (at
-// most 16) and its row's facts BEFORE the weight stream without using them, so that they arrive in front of the first weight
-// tile and no load of the stream waits for them; the classes are combined through LDS when the epilogue needs the result
-// (block_rstd_finish).  ssq always points at 256 * 32 floats.  (Read and summed in front of the stream, with the row's facts
+// The same value for all 32 rows at once, computed by a 512-thread block: thread (m, class c) requests the first four of its class's
+// groups and its row's facts beside the weight stream's first requests without using them, so that no load of the stream waits for
+// them; the classes are combined through LDS when the epilogue needs the result.  ssq always points at 256 * 32 floats.  (Read and summed in front of the stream, with the row's facts
 // found by walking tree and page table, these were 4 to 5 dependent memory round trips before the first weight load; without
 // them: QKV 26.9 -> 25.4, gate/up 38.1 -> 36.5, down 26.2 -> 25.4 us at 7B widths, 4-bit gate/up 30.0 -> 22.3 us.)
-struct EarlyLoads { float ssq[16]; int pos, kv_row, out_row; };
-__device__ __forceinline__ void early_issue(const RowScale& rs, const RowFact* facts, EarlyLoads& e) {
-  const float* p = rs.ssq + (threadIdx.x >> 5) * 32 + (threadIdx.x & 31);
+struct EarlyLoads { float ssq[4]; int pos, kv_row, out_row; };
+__device__ __forceinline__ void early_issue(const float* ssq, const RowFact* facts, EarlyLoads& e) {
+  const float* p = ssq + threadIdx.x;
   const RowFact* f = facts + (threadIdx.x & 31);
   e.pos = f->pos; e.kv_row = f->kv_row; e.out_row = f->out_row;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) e.ssq[i] = 0.f;
-  if (rs.groups > 0) {                                         // (uniform branches: unneeded groups are not fetched)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) e.ssq[i] = p[(size_t)i * 512];
-  }
-  if (rs.groups > 64) {
-#pragma unroll
-    for (int i = 4; i < 16; ++i) e.ssq[i] = p[(size_t)i * 512];
-  }
+  for (int i = 0; i < 4; ++i) e.ssq[i] = p[(size_t)i * 512];   // (no branch: behind one, the wait for the first weight tile would be a wait for all requests)
 }
 __device__ inline float early_ssq(const RowScale& rs, EarlyLoads& e) {
   float a = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(e.ssq[i]));   // the sum stays here: hoisted, it would wait in front of the stream
+  for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(e.ssq[i]));    // the sum stays here: hoisted, it would wait in front of the stream
 #pragma unroll
-  for (int i = 0; i < 16; ++i) a += (int)(threadIdx.x >> 5) + 16 * i < rs.groups ? e.ssq[i] : 0.f;
+  for (int i = 0; i < 4; ++i) a += (int)(threadIdx.x >> 5) + 16 * i < rs.groups ? e.ssq[i] : 0.f;
+  if (rs.groups > 64) {
+    const float* p = rs.ssq + threadIdx.x;
+    float v[12];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) v[i] = p[(size_t)(i + 4) * 512];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) a += (int)(threadIdx.x >> 5) + 16 * (i + 4) < rs.groups ? v[i] : 0.f;
+  }
   return a;
+}
+// 1/rms of row m from the classes that block_rstd_park left in tmp[16][32], a barrier before.
+__device__ __forceinline__ void block_rstd_park(const RowScale& rs, float part, float* tmp) {
+  if (rs.groups > 0) tmp[threadIdx.x] = part;
+}
+__device__ __forceinline__ float block_rstd(const RowScale& rs, const float* tmp, int m) {
+  if (rs.groups == 0) return 1.0f;
+  float v[16], tot = 0.f;
+#pragma unroll
+  for (int cc = 0; cc < 16; ++cc) v[cc] = tmp[cc * 32 + m];
+#pragma unroll
+  for (int cc = 0; cc < 16; ++cc) tot += v[cc];
+  return 1.0f / sqrtf(tot * rs.inv_d + rs.eps);
 }
 __device__ inline void block_rstd_finish(const RowScale& rs, float part, float* out, float* tmp) {
   if (rs.groups == 0) {
@@ -138,13 +150,18 @@ __device__ __forceinline__ void publish_wait() {
 }
 
 struct Gemm2 {
-  const bf16_t* W; size_t wps; int NRB, KS, Npad, N;
-  const bf16_t* XF;                       // NXP planes of KS tiles (one 32-row tile per k-step)
-  int S, groups, lanes, kparts;
-  float* PT; int* counters;
-  int M, epi;
-  RowScale in_scale;
+  // what the start of a weight stream needs, side by side: one fetch of arguments before the first request
+  const bf16_t* W; const bf16_t* XF;      // XF: NXP planes of KS tiles (one 32-row tile per k-step)
+  int NRB, KS, M, groups;                 // groups: row groups = work-groups of a K slice
+  uint32_t share_a, share_b, S_magic;     // the row groups' shares of the row blocks (share_begin; k2_gemm_xk: div_magic of groups) and div_magic of S
+  int S, NG;                              // 4-bit weights: NG groups along K
+  const int* skip_flag;                   // MoE: an expert's work is a no-op when its flag is 0 (no row uses it); [experts] with EXPERTS
   const RowFact* facts;                   // [32] rows of the pass
+  RowScale in_scale;
+  size_t wps; int Npad, N;
+  int lanes, kparts;
+  float* PT; int* counters;
+  int epi;
   // EPI_QKV
   KVCache kv; int kv_f32; float* Q; const float* rope_cos; const float* rope_sin; int H;
   // EPI_RESID / EPI_SWIGLU
@@ -152,10 +169,9 @@ struct Gemm2 {
   // EPI_LOGITS
   float* logits; int V;
   Q4Format q4;                            // 4-bit weights: how a code becomes a bf16 value
-  const bf16_t* SC; int NG;               // 4-bit weights: scales [NRB][NG][2][16] and groups along K (W then holds codes)
+  const bf16_t* SC;                       // 4-bit weights: scales [NRB][NG][2][16] (W then holds codes)
   const float* row_w;                     // MoE: per-row routing weight applied to this GEMM's result (nullptr = 1)
-  const int* skip_flag;                   // MoE: an expert's work is a no-op when its flag is 0 (no row uses it); [gridDim.y] with EXPERTS
-  // EXPERTS (all experts of a layer in one launch, gridDim.y of them): elements between their matrices, inputs and outputs, and between their routing weights
+  // EXPERTS (all experts of a layer in one launch): elements between their matrices, inputs and outputs, and between their routing weights
   size_t w_stride, x_stride, out_stride; int row_w_stride;
   unsigned long long* trace;              // profiling builds (-DEAGLE_TRACE) only: [work-group][8] time stamps of this launch
 };
@@ -226,7 +242,15 @@ __device__ inline void pt_sum16(const float* __restrict__ PT, int S, int Npad, i
 // Kernel arguments that the start of a weight stream needs, fetched together: the arguments come from memory, and a wait
 // between two groups of them costs another round trip in front of the first weight tile.
 __device__ __forceinline__ void pin_args(const Gemm2& g) {
-  asm volatile("" ::"s"(g.W), "s"(g.XF), "s"(g.NRB), "s"(g.KS), "s"(g.M), "s"(g.facts), "s"(g.in_scale.ssq), "s"(g.in_scale.groups), "s"(g.skip_flag));
+  asm volatile("" ::"s"(g.W), "s"(g.XF), "s"(g.NRB), "s"(g.KS), "s"(g.M), "s"(g.groups), "s"(g.share_a), "s"(g.share_b), "s"(g.S_magic), "s"(g.S), "s"(g.NG), "s"(g.skip_flag), "s"(g.facts), "s"(g.in_scale.ssq));
+}
+
+// The arguments again, for the epilogue: fetched where this stands (behind a stream's first requests) and not before it.  Left to the compiler,
+// theirs is a second fetch, and a wait for it, in front of the first request.
+__device__ __forceinline__ Gemm2 late_args() {
+  const __attribute__((address_space(4))) Gemm2* p = (const __attribute__((address_space(4))) Gemm2*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p)::"memory");
+  return *(const Gemm2*)p;
 }
 
 // Four consecutive values of row m, columns k.. (k a multiple of 4), as GEMM input (8 bytes per plane).
@@ -238,6 +262,35 @@ __device__ inline void xf_store4(bf16_t* XF, int m, int k, int MT, int KS, int n
       uint2 v; v.x = split_pair(r[0], r[1]); v.y = split_pair(r[2], r[3]);
       *(uint2*)(XF + xf_index(m, k, q, MT, KS)) = v;
     }
+}
+
+// Rows n..n+3 (a multiple of 4) of the fused QKV matrix for token m: two rotate-half pairs of a query or key head, or four dimensions of a
+// value head, where they belong.
+__device__ __forceinline__ void qkv_store(const Gemm2& g, int n, int m, int dh_shift, f32x4 sum, float rs, float2 cs, float2 sn, int kv_row, int H, int KVH) {
+  const int dh = 1 << dh_shift, hd = n >> dh_shift, pr = n & (dh - 1);
+  const f32x4 v = {sum.x * rs, sum.y * rs, sum.z * rs, sum.w * rs};
+  const int i = pr >> 1, half = dh >> 1;
+  float2 lo, hi;                                                // dimensions i, i + 1 and half + i, half + i + 1
+  { const float a = v.x, b = v.y; lo.x = a * cs.x - b * sn.x; hi.x = b * cs.x + a * sn.x; }
+  { const float a = v.z, b = v.w; lo.y = a * cs.y - b * sn.y; hi.y = b * cs.y + a * sn.y; }
+  if (hd < H) {
+    float* q = g.Q + ((size_t)m * H + hd) * dh;
+    *(float2*)(q + i) = lo; *(float2*)(q + half + i) = hi;
+  } else if (kv_row >= 0) {
+    const bool key = hd < H + KVH;
+    const int kvh = hd - H - (key ? 0 : KVH);
+    const size_t off = ((size_t)kv_row + ((size_t)kvh << g.kv.page_shift)) * dh;
+    if (g.kv_f32) {
+      float* p = (float*)(key ? g.kv.k : g.kv.v) + off;
+      if (key) { *(float2*)(p + i) = lo; *(float2*)(p + half + i) = hi; }
+      else *(f32x4*)(p + pr) = v;
+    } else {
+      bf16_t* p = (bf16_t*)(key ? g.kv.k : g.kv.v) + off;
+      auto pack = [](float a, float b) { return (uint32_t)f32_to_bf16(a) | (uint32_t)f32_to_bf16(b) << 16; };
+      if (key) { *(uint32_t*)(p + i) = pack(lo.x, lo.y); *(uint32_t*)(p + half + i) = pack(hi.x, hi.y); }
+      else { uint2 u; u.x = pack(v.x, v.y); u.y = pack(v.z, v.w); *(uint2*)(p + pr) = u; }
+    }
+  }
 }
 
 template <int NXP>
@@ -293,23 +346,32 @@ __device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float*
 // chunk by chunk in row order, chunks c, c + 16, ... in one chain: the lower lanes begin a chunk's part, the upper ones go on.
 // EXPERTS: the partials of every expert in `used` (g.S slices each), added per row in expert order with the routing weights, as one
 // launch per expert behind the other would.
-template <int NXP, bool EXPERTS = false>
-__device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, float* sh /*>= 16*32 floats*/, unsigned long long used = 1) {
+struct ResidItem { f32x4 h, bias, gain; };
+__device__ __forceinline__ ResidItem resid_item(const Gemm2& g, int n8, bool on) {
+  const int m = threadIdx.x & 31, n = n8 + 4 * ((threadIdx.x >> 5) & 1);
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  ResidItem r;
+  r.h = on && g.h_in && m < g.M ? *(const f32x4*)(g.h_in + (size_t)m * g.d + n) : zero;
+  r.bias = on && g.bias ? *(const f32x4*)(g.bias + n) : zero;
+  r.gain = on && g.gain_next ? *(const f32x4*)(g.gain_next + n) : zero;
+  return r;
+}
+// The items of the first ITEMS chunks of a wave (c = w, w + 8, ...) come with the call; ITEMS = 0: none, and any number of chunks.
+template <int NXP, bool EXPERTS = false, int ITEMS = 0>
+__device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, float* sh /*>= 16*32 floats*/, const ResidItem* ri = nullptr, unsigned long long used = 1) {
   const int lane = threadIdx.x & 63, m = lane & 31, hh = lane >> 5, w = threadIdx.x >> 6;
   const bool live = m < g.M;
   const int nchunks = (n1 - n0) >> 3;                        // n0 and n1 are multiples of 32 (d_model is one of 64)
   const float rw = !EXPERTS && g.row_w ? g.row_w[m] : 1.0f;
   float ss[2] = {0.f, 0.f};                                  // chains w and w + 8
-  int turn = 0;
-  for (int c = w; c < nchunks; c += V2_THREADS / 64, turn ^= 1) {
+  const uint32_t slice = (uint32_t)g.Npad * 128u;            // bytes of a slice's partials
+  auto chunk = [&](int c, int turn, const ResidItem& r) {
     const int n = n0 + 8 * c + 4 * hh;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    const f32x4 hv = g.h_in && live ? *(const f32x4*)(g.h_in + (size_t)m * g.d + n) : zero;
-    const f32x4 bv = g.bias ? *(const f32x4*)(g.bias + n) : zero;
-    const f32x4 gv = g.gain_next ? *(const f32x4*)(g.gain_next + n) : zero;
+    const uint32_t at = pt_quad_bytes(0, g.Npad, n, m);
     f32x4 v = zero;
     if constexpr (EXPERTS) {
-      v = hv;
+      v = r.h;
       for (unsigned long long left = used; left; ) {           // four experts' first four slices in flight at once
         int ex[4], cnt = 0;
         f32x4 p[4][4];
@@ -335,18 +397,19 @@ __device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, f
         }
       }
     } else {
+      const __amdgpu_buffer_rsrc_t pt = coh_rsrc(g.PT);
       for (int s0 = 0; s0 < g.S; s0 += 8) {                  // added in split order
         f32x4 p[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (u < 4 || g.S > 4) p[u] = coh_load16(g.PT, pt_quad_bytes(min(s0 + u, g.S - 1), g.Npad, n, m));
+          if (u < 4 || g.S > 4) p[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pt, at, (uint32_t)min(s0 + u, g.S - 1) * slice, 16));
 #pragma unroll
         for (int u = 0; u < 8; ++u)
           if (s0 + u < g.S) v += p[u];
       }
       if (g.row_w) v *= rw;
-      if (g.bias) v += bv;
-      if (g.h_in && live) v += hv;
+      if (g.bias) v += r.bias;
+      if (g.h_in && live) v += r.h;
     }
     if (live) *(f32x4*)(g.h_out + (size_t)m * g.d + n) = v;
     float a = turn ? ss[1] : ss[0];
@@ -359,15 +422,27 @@ __device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, f
     a = __shfl(a, m + 32, 64);
     if (turn) ss[1] = a; else ss[0] = a;
     f32x4 x = v;
-    if (g.gain_next) x = v * gv;
+    if (g.gain_next) x = v * r.gain;
     if (live) xf_store4(g.xf_out, m, n, 1, g.xf_KS, NXP, x);
+  };
+  if constexpr (ITEMS > 0) {
+#pragma unroll
+    for (int t = 0; t < ITEMS; ++t)
+      if (w + 8 * t < nchunks) chunk(w + 8 * t, t & 1, ri[t]);
+  } else {
+    int turn = 0;
+    for (int c = w; c < nchunks; c += V2_THREADS / 64, turn ^= 1) chunk(c, turn, resid_item(g, n0 + 8 * c, true));
   }
+  if (!g.ssq_out) return;                                    // (uniform)
   __syncthreads();
   if (hh == 0) { sh[w * 32 + m] = ss[0]; sh[(w + 8) * 32 + m] = ss[1]; }
   __syncthreads();
-  if (threadIdx.x < 32 && g.ssq_out) {
-    float a = 0.f;
-    for (int i = 0; i < V2_THREADS / 32; ++i) a += sh[i * 32 + threadIdx.x];
+  if (threadIdx.x < 32) {
+    float v[V2_THREADS / 32], a = 0.f;
+#pragma unroll
+    for (int i = 0; i < V2_THREADS / 32; ++i) v[i] = sh[i * 32 + threadIdx.x];
+#pragma unroll
+    for (int i = 0; i < V2_THREADS / 32; ++i) a += v[i];
     g.ssq_out[grp * 32 + threadIdx.x] = a;
   }
 }
@@ -635,7 +710,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm(Gemm2 g) {
   __shared__ int s_last;
   pin_args(g);
   EarlyLoads el;                                                // used by the epilogue, much later
-  early_issue(g.in_scale, g.facts, el);
+  early_issue(g.in_scale.ssq, g.facts, el);
   if (g.skip_flag && *g.skip_flag == 0) return;               // uniform over the whole grid
   u32x4* xs = (u32x4*)smem;
   const int lane = threadIdx.x & 63, w = wave_id();
@@ -796,10 +871,21 @@ __device__ __forceinline__ FkWeights<NWP> fk_weights(const bf16_t* W, size_t wps
   return f;
 }
 
-template <int NWP, int NXP, int NR, int DEPTH>
-__device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
+// Zero sums, made here and not in front of the first requests.
+template <int NR>
+__device__ __forceinline__ void fk_zero(f32x16* acc) {
+  float zero = 0.f;
+  asm volatile("" : "+v"(zero));
+#pragma unroll
+  for (int j = 0; j < NR; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = zero;
+}
+// behind(): what else the kernel requests, behind the stream's first requests.
+template <int NWP, int NXP, int NR, int DEPTH, class F>
+__device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane, F&& behind) {
   constexpr int PMAX = NWP > NXP ? NWP : NXP;
-  if (ke <= kb) return;
+  const int klast = max(ke - 1, kb);                            // (a wave without a k-step requests one that it does not use)
   u32x4 ta[DEPTH][NR][NWP], tb[DEPTH][NXP];
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, NXP * KS * 1024, 0x00020000);
   const uint32_t xlane = row ? (uint32_t)lane * 16u : OUT_OF_RANGE;   // row: this lane's activation row is wanted
@@ -828,7 +914,10 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
             acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ta[dd][j][p]), __builtin_bit_cast(bf16x8, tb[dd][q]), acc[j], 0, 0, 0);
   };
 #pragma unroll
-  for (int dd = 0; dd < DEPTH; ++dd) load(dd, min(kb + dd, ke - 1));
+  for (int dd = 0; dd < DEPTH; ++dd) load(dd, min(kb + dd, klast));
+  __builtin_amdgcn_sched_barrier(0);
+  behind();
+  fk_zero<NR>(acc);
   int k = kb;
   // A round that has all of the next one to request; then the rounds that do not.  (With the k-steps behind the end clamped to the
   // last one, a wave's 32 came as 35 or 36 at K = 4096 and O's 8 as 12, on the L2 -> CU path that binds these kernels; requested out
@@ -858,11 +947,12 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
   for (int dd = 0; dd < DEPTH; ++dd)
     if (k + dd < ke) mul(dd);
 }
-template <int NWP, int NXP, int NR>
-__device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane) {
+template <int NWP, int NXP, int NR, class F>
+__device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane, F&& behind) {
   constexpr int DEPTH = NWP == 1 ? (NR == 1 ? 8 : NR == 2 ? 6 : NR == 3 ? 5 : 4) : NR == 1 ? 4 : 2;   // ~24 KiB in flight per wave; deeper measured the same
-  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, row, kb, ke, fw, acc, lane);
-  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, row, kb, ke, fw, acc, lane);
+  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, row, kb, ke, fw, acc, lane, behind);
+  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, row, kb, ke, fw, acc, lane, behind);
+  else behind();                                               // (no row block: nothing to multiply)
 }
 
 // ---- the same stream over 4-bit weights (see k_pack_weight_q4 for the layout) -------------------------------------------
@@ -872,11 +962,16 @@ __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int
 // the same k-steps, and the group is folded into the result as  acc += s_row * (partial - 24 * sum_x)  in fp32.
 // Activation fragments are streamed from L2 as in fk_stream, one group (8 k-steps) ahead; the next group's codes are
 // requested as soon as a super-tile's registers are free.
-template <int NXP, int NR, bool APART>
+template <int NXP, int NR, bool APART, class F>
 __device__ __forceinline__ bool fk_stream_q4(const Q4Format fmt, const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs /*codes from block 0 on*/,
                                              const u32x4* const* sq /*scales of (block j, group 0), this lane's half*/, int NG,
-                                             f32x16* acc, int lane) {
-  if (ge <= gb) return false;
+                                             f32x16* acc, int lane, F&& behind) {
+  if (ge <= gb) {
+    behind();
+#pragma unroll
+    for (int j = 0; j < NR; ++j) acc[j] = f32x16{};
+    return false;
+  }
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)XF, 0, q4_x_span(NXP, KS) * 1024, 0x00020000);
   const uint32_t xlane = (lane & 31) < M ? (uint32_t)lane * 16u : OUT_OF_RANGE;   // dead rows: zeros
 #define Q4_XLOAD(q, kk, past) __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, xlane | (past), (uint32_t)(((q) * KS + (kk)) * 1024), 0))
@@ -891,6 +986,9 @@ __device__ __forceinline__ bool fk_stream_q4(const Q4Format fmt, const bf16_t* _
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int q = 0; q < NXP; ++q) tb[i][q] = Q4_XLOAD(q, 8 * gb + i, 0u);
+  __builtin_amdgcn_sched_barrier(0);
+  behind();
+  fk_zero<NR>(acc);
   // The last group, a copy of the loop's body, requests nothing: clamped to itself it fetched its activations and codes twice, one
   // group in four at K = 4096 and the only one in O's slices.  (Three row blocks, for which a second body spills, request out of range.)
   constexpr bool COPY = NR < 3;
@@ -969,15 +1067,14 @@ __device__ __forceinline__ bool fk_stream_q4(const Q4Format fmt, const bf16_t* _
 #undef Q4_WLOAD
   return acc[0][0] != acc[0][0];                               // (a sum of NaN in any group stays in every result of its row)
 }
-template <int NXP, int NR>
+template <int NXP, int NR, class F>
 __device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt, const bf16_t* XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs,
-                                                      const u32x4* const* sq, int NG, f32x16* acc, int lane) {
+                                                      const u32x4* const* sq, int NG, f32x16* acc, int lane, F&& behind) {
   if (nr == NR) {
-    if (!__any(fk_stream_q4<NXP, NR, false>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane))) return;
-#pragma unroll
-    for (int j = 0; j < NR; ++j) acc[j] = f32x16{};
-    fk_stream_q4<NXP, NR, true>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane);
-  } else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane);
+    if (!__any(fk_stream_q4<NXP, NR, false>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, behind))) return;
+    fk_stream_q4<NXP, NR, true>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, [] {});
+  } else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, behind);
+  else behind();
 }
 // The codes of nr row blocks from rb0 on.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t q4_codes(const bf16_t* W, int rb0, int nr, int KS) {
@@ -1004,75 +1101,81 @@ __device__ __forceinline__ f32x4 fk_sum4(const float* red, int nrmax, int j, int
 // each).  A work-group then owns a run of halves; of a block it shares with a neighbour it loads and finishes only its own
 // 16 rows (the other lanes of the tile load nothing and multiply zeros).  Rotate-half pairs are adjacent rows, so a half
 // holds whole pairs.  Epilogue: QKV.
-template <int NWP, int NXP, int NRMAX, bool HALF = false, bool Q4 = false, bool EXPERTS = false>
+// What a decoding step spends beside its streams is instructions on one chain, from a work-group's entry to its first request and from its
+// last tile to its last store (a wave issues one in four to eight cycles): so the arguments come in one fetch, the shares without a
+// division, everything else behind the first requests, what the epilogue reads on its way before the sums, and the epilogue is a template
+// argument.  7B, us a launch before / after, here and in k2_gemm_xk: 26 rows, QKV 23.0 / 21.8, gate/up 32.9 / 32.5, O 11.4 / 10.7, down 23.0 /
+// 22.3; the head's passes of a few rows, QKV 18.6 / 17.9, gate/up 32.0 / 31.1, O 10.2 / 9.3, down 19.9 / 19.3, fc 17.3 / 16.2.
+template <int EPI, int NWP, int NXP, int NRMAX, bool HALF = false, bool Q4 = false, bool EXPERTS = false>
 __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
   static_assert(!Q4 || (!HALF && NWP == 1), "4-bit weights: whole row blocks, one plane");
+  static_assert((!HALF || EPI == EPI_QKV) && (!EXPERTS || EPI == EPI_SWIGLU) && (EPI != EPI_RESID || NRMAX <= 2), "forms that exist");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ float sh_small[16 * 33];
-  __shared__ float rstd_s[32];
+  __shared__ float sh_small[16 * 32];
   float* red = (float*)smem;                                    // [8][NRMAX][16][64]
   pin_args(g);
-  EarlyLoads el;                                                // used by the epilogue, much later
-  constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
-  if constexpr (!LATE) early_issue(g.in_scale, g.facts, el);
   if (g.skip_flag && g.skip_flag[EXPERTS ? blockIdx.y : 0] == 0) return;   // MoE: no row selected this expert (uniform over its work-groups)
-  if constexpr (EXPERTS) { g.W += blockIdx.y * g.w_stride; g.xf_out += blockIdx.y * g.out_stride; }
+  const bf16_t* W = g.W;
+  if constexpr (EXPERTS) W += blockIdx.y * g.w_stride;
   const int lane = threadIdx.x & 63, w = wave_id();
   bool row = (lane & 31) < g.M;                                 // dead rows (and, here, rows that did not select the expert) are not fetched
   if constexpr (EXPERTS) row = row && g.row_w[(size_t)blockIdx.y * g.row_w_stride + (lane & 31)] != 0.f;
   unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
   TRACE_STAMP(tr, 0);
-  const unsigned G = gridDim.x;
-  int rb0, rb1, row_lo = 0, row_hi = 32;                        // rows [row_lo, 32) of the first block, [0, row_hi) of the last
-  if constexpr (HALF) {
-    const unsigned U = 2u * (unsigned)g.NRB;
-    const unsigned u0 = (unsigned)blockIdx.x * U / G, u1 = (unsigned)(blockIdx.x + 1) * U / G;
-    rb0 = (int)(u0 >> 1); rb1 = (int)((u1 + 1) >> 1);
-    row_lo = (u0 & 1) ? 16 : 0; row_hi = (u1 & 1) ? 16 : 32;
-  } else {
-    rb0 = (unsigned)blockIdx.x * (unsigned)g.NRB / G; rb1 = (unsigned)(blockIdx.x + 1) * (unsigned)g.NRB / G;
-  }
+  const uint32_t U = HALF ? 2u * (uint32_t)g.NRB : (uint32_t)g.NRB;
+  const uint32_t u0 = share_begin(blockIdx.x, U, g.share_a, g.share_b), u1 = share_begin(blockIdx.x + 1, U, g.share_a, g.share_b);
+  const int rb0 = HALF ? u0 >> 1 : u0, rb1 = HALF ? (u1 + 1) >> 1 : u1;
+  const int row_lo = HALF && (u0 & 1) ? 16 : 0, row_hi = HALF && (u1 & 1) ? 16 : 32;   // rows [row_lo, 32) of the first block, [0, row_hi) of the last
   const int nr = rb1 - rb0;                                     // <= NRMAX (host)
-  const int kb = (unsigned)w * (unsigned)g.KS / 8u, ke = (unsigned)(w + 1) * (unsigned)g.KS / 8u;
+  EarlyLoads el;                                                // used by the epilogue, much later
+  constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
+  Gemm2 e;                                                      // the arguments as the epilogue reads them
+  auto early = [&] {
+    e = late_args();
+    if constexpr (!LATE) early_issue(g.in_scale.ssq, g.facts, el);
+  };
   f32x16 acc[NRMAX];
-#pragma unroll
-  for (int j = 0; j < NRMAX; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
   if constexpr (Q4) {
     // K is split over the waves by groups of 128; pointers to the codes / scales of each row block
     const int gb = (unsigned)w * (unsigned)g.NG / 8u, ge = (unsigned)(w + 1) * (unsigned)g.NG / 8u;
     const u32x4* sq[NRMAX];
 #pragma unroll
     for (int j = 0; j < NRMAX; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(rb0 + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, rb0, nr, g.KS), sq, g.NG, acc, lane);
-    if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
-  } else
-  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, row, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane, row_lo, row_hi), acc, lane);
-  TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
-  // residual epilogue: what the first item of a thread adds and multiplies, requested before the sums
-  f32x4 rh = {0.f, 0.f, 0.f, 0.f}, rbias = rh, rgain = rh;
-  auto load_resid = [&](int n) {
-    const int mm = threadIdx.x & 31;
-    if (g.h_in && mm < g.M) rh = *(const f32x4*)(g.h_in + (size_t)mm * g.d + n);
-    if (g.bias) rbias = *(const f32x4*)(g.bias + n);
-    if (g.gain_next) rgain = *(const f32x4*)(g.gain_next + n);
-  };
-  constexpr bool RESID = !HALF && NRMAX <= 2;                   // (host: at most two row blocks where this epilogue is used)
-  if (RESID && g.epi == EPI_RESID) {
-    const int n = (rb0 + (threadIdx.x >> 8)) * 32 + 4 * ((threadIdx.x >> 5) & 7);
-    if ((int)threadIdx.x >> 8 < nr && n < g.N) load_resid(n);
+    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(W, rb0, nr, g.KS), sq, g.NG, acc, lane, early);
+    if constexpr (LATE) early_issue(e.in_scale.ssq, e.facts, el);
+  } else {
+    const int kb = (unsigned)w * (unsigned)g.KS / 8u, ke = (unsigned)(w + 1) * (unsigned)g.KS / 8u;
+    fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, row, kb, ke, fk_weights<NWP>(W, g.wps, rb0, nr, g.KS, lane, row_lo, row_hi), acc, lane, early);
   }
+  TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
+  if constexpr (EXPERTS) e.xf_out += blockIdx.y * e.out_stride;
+  const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;     // 16 slots of 32 tokens
+  const bool live = m < e.M;
+  // what the first item of a thread needs from memory is requested before the sums
+  f32x4 rh = {0.f, 0.f, 0.f, 0.f}, rbias = rh, rgain = rh;     // residual epilogue: what an item adds and multiplies
+  auto load_resid = [&](int n) {
+    if (e.h_in && live) rh = *(const f32x4*)(e.h_in + (size_t)m * e.d + n);
+    if (e.bias) rbias = *(const f32x4*)(e.bias + n);
+    if (e.gain_next) rgain = *(const f32x4*)(e.gain_next + n);
+  };
+  const int dh_shift = 31 - __builtin_clz(e.kv.head_dim), half = e.kv.head_dim >> 1;   // QKV (32, 64 or 128 dimensions)
+  float2 rcs = {0.f, 0.f}, rsn = {0.f, 0.f};                    // ... the angles of an item's two pairs
+  auto load_angles = [&](int n) {
+    if (!live) return;                                          // (no position of its own)
+    const size_t at = (size_t)el.pos * half + ((n & (2 * half - 1)) >> 1);
+    rcs = *(const float2*)(e.rope_cos + at); rsn = *(const float2*)(e.rope_sin + at);
+  };
+  const int first = (rb0 + (slot >> 3)) * 32 + 4 * (slot & 7);
+  if (EPI == EPI_RESID && (slot >> 3) < nr && first < e.N) load_resid(first);
+  if (EPI == EPI_QKV && (slot >> 3) < nr && first < e.N) load_angles(first);
   // park every wave's sums in LDS
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
     if (j < nr) fk_park(red, NRMAX, w, j, lane, acc[j]);
-  block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);   // (contains the barriers that publish `red`)
+  if constexpr (EPI != EPI_RESID) block_rstd_park(e.in_scale, early_ssq(e.in_scale, el), sh_small);
   __syncthreads();
-  const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;     // 16 slots of 32 tokens
-  const bool live = m < g.M;
-  const float rs = live ? rstd_s[m] : 0.f;
-  if (g.epi == EPI_SWIGLU) {
+  const float rs = EPI != EPI_RESID && live ? block_rstd(e.in_scale, sh_small, m) : 0.f;
+  if constexpr (EPI == EPI_SWIGLU) {
     // item = (row block j, quarter qt): outputs f = rb*16 + 4*qt .. +3 from gate rows 4*qt.. and up rows 16 + 4*qt..
     for (int it = slot; it < nr * 4; it += 16) {
       const int j = it >> 2, qt = it & 3;
@@ -1083,79 +1186,62 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
         const float gg = gq[t] * rs, uu = uq[t] * rs;
         x[t] = gg / (1.0f + __expf(-gg)) * uu;
       }
-      if (live) xf_store4(g.xf_out, m, (rb0 + j) * 16 + 4 * qt, 1, g.xf_KS, NXP, x);
+      if (live) xf_store4(e.xf_out, m, (rb0 + j) * 16 + 4 * qt, 1, e.xf_KS, NXP, x);
     }
-  } else if (g.epi == EPI_QKV) {
-    const int dh = g.kv.head_dim, half = dh >> 1, KVH = g.kv.n_kv_heads, H = g.H;
+  } else if constexpr (EPI == EPI_QKV) {
+    const int KVH = e.kv.n_kv_heads, H = e.H;
     // item = (row block j, quad qd of 8): rows 4qd.. of the block, two rotate-half pairs
     for (int it = slot; it < nr * 8; it += 16) {
       const int j = it >> 3, qd = it & 7;
       if (HALF && (4 * qd < (j == 0 ? row_lo : 0) || 4 * qd >= (j == nr - 1 ? row_hi : 32))) continue;   // the neighbour's rows
+      const int n = (rb0 + j) * 32 + 4 * qd;
+      if (n >= e.N) continue;                                   // (N is a multiple of 32)
+      if (it != slot) load_angles(n);
       const f32x4 sum = fk_sum4(red, NRMAX, j, qd, m);
-#pragma unroll
-     for (int p = 0; p < 2; ++p) {
-      const int n = (rb0 + j) * 32 + 4 * qd + 2 * p;
-      if (n >= g.N || !live) continue;
-      float a = sum[2 * p] * rs, b = sum[2 * p + 1] * rs;
-      const int hd = n / dh, pr = n % dh;
-      int d1, d2;
-      if (hd < H + KVH) {        // q or k head: the two rows are a rotate-half pair
-        const int i = pr >> 1;
-        const float cs = g.rope_cos[(size_t)el.pos * half + i], sn = g.rope_sin[(size_t)el.pos * half + i];
-        const float a2 = a * cs - b * sn, b2 = b * cs + a * sn;
-        a = a2; b = b2; d1 = i; d2 = i + half;
-      } else { d1 = pr; d2 = pr + 1; }
-      if (hd < H) {
-        float* q = g.Q + ((size_t)m * H + hd) * dh;
-        q[d1] = a; q[d2] = b;
-      } else if (el.kv_row >= 0) {
-        const int kvh = (hd - H) % KVH;
-        const size_t off = ((size_t)el.kv_row + ((size_t)kvh << g.kv.page_shift)) * dh;
-        void* base = hd < H + KVH ? g.kv.k : g.kv.v;
-        if (g.kv_f32) { ((float*)base)[off + d1] = a; ((float*)base)[off + d2] = b; }
-        else { ((bf16_t*)base)[off + d1] = f32_to_bf16(a); ((bf16_t*)base)[off + d2] = f32_to_bf16(b); }
-      }
-     }
+      if (!live) continue;
+      qkv_store(e, n, m, dh_shift, sum, rs, rcs, rsn, el.kv_row, H, KVH);
     }
-  } else if (RESID && g.epi == EPI_RESID) {
+  } else if constexpr (EPI == EPI_RESID) {
     // h_out = h_in + (routing weight *) W x + bias; per-token partial sums of squares for the consumer's RMSNorm; x * gain of the
     // next norm as GEMM input.  item = (row block j, quad of 4 rows), the residual, bias and gain of the first on their way already
-    const float rw = g.row_w ? g.row_w[m] : 1.0f;
+    const float rw = e.row_w ? e.row_w[m] : 1.0f;
     float ss = 0.f;
     for (int it = slot; it < nr * 8; it += 16) {
       const int j = it >> 3, qd = it & 7;
       const int n = (rb0 + j) * 32 + 4 * qd;
-      if (n >= g.N) continue;                                   // (N is a multiple of 64)
+      if (n >= e.N) continue;                                   // (N is a multiple of 64)
       if (it != slot) load_resid(n);
       f32x4 v = fk_sum4(red, NRMAX, j, qd, m);
-      if (g.row_w) v *= rw;
-      if (g.bias) v += rbias;
-      if (g.h_in && live) v += rh;
-      if (live) *(f32x4*)(g.h_out + (size_t)m * g.d + n) = v;
+      if (e.row_w) v *= rw;
+      if (e.bias) v += rbias;
+      if (e.h_in && live) v += rh;
+      if (live) *(f32x4*)(e.h_out + (size_t)m * e.d + n) = v;
 #pragma unroll
       for (int t = 0; t < 4; ++t) ss = fmaf(v[t], v[t], ss);
-      if (live) xf_store4(g.xf_out, m, n, 1, g.xf_KS, NXP, g.gain_next ? v * rgain : v);
+      if (live) xf_store4(e.xf_out, m, n, 1, e.xf_KS, NXP, e.gain_next ? v * rgain : v);
     }
-    sh_small[slot * 32 + m] = ss;
-    __syncthreads();
-    if (threadIdx.x < 32 && g.ssq_out) {
-      float a = 0.f;
-      for (int i = 0; i < 16; ++i) a += sh_small[i * 32 + threadIdx.x];
-      g.ssq_out[blockIdx.x * 32 + threadIdx.x] = a;
+    if (e.ssq_out) {                                            // (uniform)
+      sh_small[slot * 32 + m] = ss;
+      __syncthreads();
+      if (threadIdx.x < 32) {
+        float a = 0.f;
+        for (int i = 0; i < 16; ++i) a += sh_small[i * 32 + threadIdx.x];
+        e.ssq_out[blockIdx.x * 32 + threadIdx.x] = a;
+      }
     }
   } else {                                                      // EPI_LOGITS
-    const int nend = min(g.N, g.V);
-    const bool vec = (g.V & 3) == 0;
-    const long dst = live && el.out_row >= 0 ? (long)el.out_row * g.V : -1;
+    const int nend = min(e.N, e.V);
+    const bool vec = (e.V & 3) == 0;
+    const long dst = live && el.out_row >= 0 ? (long)el.out_row * e.V : -1;
     for (int it = slot; it < nr * 8; it += 16) {                // item = (row block j, quad of 4 rows)
       const int j = it >> 3, qd = it & 7;
       const int n = (rb0 + j) * 32 + 4 * qd;
       if (dst < 0 || n >= nend) continue;
       const f32x4 v = fk_sum4(red, NRMAX, j, qd, m) * rs;
-      if (vec && n + 4 <= nend) *(f32x4*)(g.logits + dst + n) = v;
+      if (vec && n + 4 <= nend) *(f32x4*)(e.logits + dst + n) = v;
       else {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) if (n + t < nend) g.logits[dst + n + t] = v[t];
+        for (int t = 0; t < 4; ++t) if (n + t < nend) e.logits[dst + n + t] = v[t];
       }
     }
   }
@@ -1304,83 +1390,97 @@ __global__ __launch_bounds__(256, 1) void k_gemm_wk(GemmWK g) {
 // S x (row blocks) x 4 KiB per row group, and nothing waits for an LDS fill before the weight stream starts.
 // Partials, arrival counter and epilogues are those of k2_gemm.
 // Q4: 4-bit codes (k_pack_weight_q4); the slices are then whole groups of 128 columns (host: at least 8 groups a slice).
-template <int NWP, int NXP, int NRMAX, bool Q4 = false, bool EXPERTS = false>
+// Grid: K slices, row groups, experts.  RESID: the residual epilogue, else whichever g.epi names.
+template <bool RESID, int NXP, int NRMAX, bool Q4 = false, bool EXPERTS = false>
 __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
-  static_assert(!Q4 || NWP == 1, "4-bit weights: one plane");
+  static_assert(!EXPERTS || (RESID && !Q4), "forms that exist");
+  constexpr int ITEMS = (NRMAX + 1) / 2;                        // (row block, register quad) items of a wave
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float sh_small[16 * 33];
   __shared__ float rstd_s[32];
   __shared__ int s_last;
   float* red = (float*)smem;                                    // [8][NRMAX][16][64]
   pin_args(g);
-  EarlyLoads el;                                                // used by the epilogue, much later
-  constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
-  if constexpr (!LATE) early_issue(g.in_scale, g.facts, el);
-  if (g.skip_flag && g.skip_flag[EXPERTS ? blockIdx.y : 0] == 0) return;   // uniform over the expert's work-groups
+  if (g.skip_flag && g.skip_flag[EXPERTS ? blockIdx.z : 0] == 0) return;   // uniform over the expert's work-groups
+  const bf16_t *W = g.W, *XF = g.XF;
   unsigned long long used = 1;                                  // the experts of this launch that some row selected
   if constexpr (EXPERTS) {
-    used = __ballot((threadIdx.x & 63) < gridDim.y && g.skip_flag[min(threadIdx.x & 63, gridDim.y - 1)] != 0);
-    g.W += blockIdx.y * g.w_stride; g.XF += blockIdx.y * g.x_stride;
+    used = __ballot((threadIdx.x & 63) < gridDim.z && g.skip_flag[min(threadIdx.x & 63, gridDim.z - 1)] != 0);
+    W += blockIdx.z * g.w_stride; XF += blockIdx.z * g.x_stride;
   }
   const int lane = threadIdx.x & 63, w = wave_id();
   bool row = (lane & 31) < g.M;                                 // dead rows (and, here, rows that did not select the expert) are not fetched
-  if constexpr (EXPERTS) row = row && g.row_w[(size_t)blockIdx.y * g.row_w_stride + (lane & 31)] != 0.f;
-  unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)blockIdx.x * 8 : nullptr);
+  if constexpr (EXPERTS) row = row && g.row_w[(size_t)blockIdx.z * g.row_w_stride + (lane & 31)] != 0.f;
+  unsigned long long* tr = TRACE_PTR((g.trace && threadIdx.x == 0) ? g.trace + (size_t)(blockIdx.x + g.S * blockIdx.y) * 8 : nullptr);
   TRACE_STAMP(tr, 0);
-  const unsigned uS = g.S, ugroups = g.groups, uNRB = g.NRB, uKS = g.KS;
-  const int s = blockIdx.x % uS, grp = blockIdx.x / uS;
-  const int rb0 = (unsigned)grp * uNRB / ugroups, rb1 = (unsigned)(grp + 1) * uNRB / ugroups;
+  const uint32_t uS = g.S, uNRB = g.NRB, uKS = g.KS, s = blockIdx.x, grp = blockIdx.y;
+  const int rb0 = div_magic(grp * uNRB, g.share_a), rb1 = div_magic(grp * uNRB + uNRB, g.share_a);
   const int nr = rb1 - rb0;                                     // <= NRMAX (host)
-  const int ks0 = (unsigned)s * uKS / uS, ks1 = (unsigned)(s + 1) * uKS / uS, kt = ks1 - ks0;
-  const int kb = ks0 + (unsigned)w * (unsigned)kt / 8u, ke = ks0 + (unsigned)(w + 1) * (unsigned)kt / 8u;
+  EarlyLoads el;                                                // used by the epilogue, much later
+  constexpr bool LATE = Q4 && NRMAX == 3;                       // no registers to hold them through the 4-bit stream (12 to 15 spilled)
+  Gemm2 e;                                                      // the arguments as the epilogue reads them
+  auto early = [&] {
+    e = late_args();
+    if constexpr (!LATE && !RESID) early_issue(g.in_scale.ssq, g.facts, el);
+  };
   f32x16 acc[NRMAX];
-#pragma unroll
-  for (int j = 0; j < NRMAX; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
   if constexpr (Q4) {
-    const unsigned uNG = g.NG;
-    const int G0 = (unsigned)s * uNG / uS, G1 = (unsigned)(s + 1) * uNG / uS, gt = G1 - G0;
+    const uint32_t uNG = g.NG;
+    const int G0 = div_magic(s * uNG, g.S_magic), G1 = div_magic(s * uNG + uNG, g.S_magic), gt = G1 - G0;
     const int gb = G0 + (unsigned)w * (unsigned)gt / 8u, ge = G0 + (unsigned)(w + 1) * (unsigned)gt / 8u;
     const u32x4* sq[NRMAX];
 #pragma unroll
     for (int j = 0; j < NRMAX; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(rb0 + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, rb0, nr, g.KS), sq, g.NG, acc, lane);
-    if constexpr (LATE) early_issue(g.in_scale, g.facts, el);
-  } else
-  fk_stream_dispatch<NWP, NXP, NRMAX>(nr, g.XF, g.KS, row, kb, ke, fk_weights<NWP>(g.W, g.wps, rb0, nr, g.KS, lane), acc, lane);
+    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, XF, g.KS, g.M, gb, ge, q4_codes(W, rb0, nr, g.KS), sq, g.NG, acc, lane, early);
+    if constexpr (LATE && !RESID) early_issue(e.in_scale.ssq, e.facts, el);
+  } else {
+    const int ks0 = div_magic(s * uKS, g.S_magic), ks1 = div_magic(s * uKS + uKS, g.S_magic), kt = ks1 - ks0;
+    const int kb = ks0 + (unsigned)w * (unsigned)kt / 8u, ke = ks0 + (unsigned)(w + 1) * (unsigned)kt / 8u;
+    fk_stream_dispatch<1, NXP, NRMAX>(nr, XF, g.KS, row, kb, ke, fk_weights<1>(W, g.wps, rb0, nr, g.KS, lane), acc, lane, early);
+  }
   TRACE_STAMP_AFTER(tr, 2, acc[0][0]);
+  // what the residual epilogue adds and multiplies, if this turns out to be the work-group that runs it: on its way during the sums
+  ResidItem ri[ITEMS];
+  if constexpr (RESID) {
+#pragma unroll
+    for (int t = 0; t < ITEMS; ++t) ri[t] = resid_item(e, rb0 * 32 + 8 * (w + 8 * t), w + 8 * t < nr * 4);
+  }
 #pragma unroll
   for (int j = 0; j < NRMAX; ++j)
     if (j < nr) fk_park(red, NRMAX, w, j, lane, acc[j]);
   __syncthreads();
   // the waves share the sum and the publication: item = (row block j, register quad i) -> rows 8i + 4(lane/32) + 0..3
-  for (int it = w; it < nr * 4; it += 8) {
-    const int j = it >> 2, i = it & 3;
+#pragma unroll
+  for (int t = 0; t < ITEMS; ++t) {
+    const int it = w + 8 * t, j = it >> 2, i = it & 3;
+    if (it >= nr * 4) break;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ww = 0; ww < 8; ++ww) o += *(const f32x4*)(red + ((((size_t)ww * NRMAX + j) * 4 + i) * 64 + lane) * 4);
-    coh_store16(g.PT, pt_quad_bytes(EXPERTS ? (int)(blockIdx.y * uS) + s : s, g.Npad, (rb0 + j) * 32 + 8 * i + 4 * (lane >> 5), lane & 31), o);
+    coh_store16(e.PT, pt_quad_bytes(EXPERTS ? (int)(blockIdx.z * uS + s) : s, e.Npad, (rb0 + j) * 32 + 8 * i + 4 * (lane >> 5), lane & 31), o);
   }
   TRACE_STAMP(tr, 3);
   publish_wait();
   __syncthreads();
   if (threadIdx.x == 0) {
-    int old = __hip_atomic_fetch_add(g.counters + grp * COUNTER_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (old == (EXPERTS ? g.S * __popcll(used) : g.S) - 1);
-    if (s_last) __hip_atomic_store(g.counters + grp * COUNTER_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int* cnt = e.counters + grp * COUNTER_STRIDE;
+    int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = (old == (EXPERTS ? e.S * __popcll(used) : e.S) - 1);
+    if (s_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
   if (!s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  const int n0 = rb0 * 32, n1 = min(rb1 * 32, g.N);
+  const int n0 = rb0 * 32, n1 = min(rb1 * 32, e.N);
   if (n1 <= n0) return;
-  if (g.epi != EPI_RESID) block_rstd_finish(g.in_scale, early_ssq(g.in_scale, el), rstd_s, sh_small);
-  switch (g.epi) {
-    case EPI_QKV: epilogue_qkv<NXP>(g, n0, n1, rstd_s, el); break;
-    case EPI_RESID: epilogue_resid<NXP, EXPERTS>(g, grp, n0, n1, sh_small, used); break;
-    case EPI_SWIGLU: epilogue_swiglu<NXP>(g, n0, n1, rstd_s); break;
-    default: epilogue_logits(g, n0, n1, rstd_s, el); break;
+  if constexpr (RESID) epilogue_resid<NXP, EXPERTS, ITEMS>(e, grp, n0, n1, sh_small, ri, used);
+  else {
+    block_rstd_finish(e.in_scale, early_ssq(e.in_scale, el), rstd_s, sh_small);
+    switch (e.epi) {
+      case EPI_QKV: epilogue_qkv<NXP>(e, n0, n1, rstd_s, el); break;
+      case EPI_SWIGLU: epilogue_swiglu<NXP>(e, n0, n1, rstd_s); break;
+      default: epilogue_logits(e, n0, n1, rstd_s, el); break;
+    }
   }
   TRACE_STAMP(tr, 4);
 }

@@ -32,6 +32,13 @@ int shim_experts_in_two(const int* m, int n, int n_cu, int* o) {
   o[0] = (m[0] + grid - 1) / grid; o[1] = dn.S; o[2] = dn.nrmax;
   return plan_experts_in_two(m[0], m[1], m[2], m[3], 2, 1, n_cu, pt);
 }
+uint32_t shim_div(uint32_t x, uint32_t n) { return div_magic(x, magic_of(n)); }
+int shim_div_holds(uint64_t x, uint32_t n) { return magic_holds(x, n); }
+int shim_shares(uint32_t units, uint32_t n, uint32_t* o) {
+  const Share s = share_of(units, n);
+  for (uint32_t i = 0; i <= n; ++i) o[i] = share_begin(i, units, s.a, s.b);
+  return s.b == SHARE_IN_TURN;
+}
 int shim_attn_splits(int fixed, int tokens, int units, int n_cu) { return plan_attn_splits(fixed != 0, tokens, units, n_cu); }
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
@@ -49,6 +56,9 @@ class Plans:
         inc = os.path.join(os.path.dirname(pkg.__file__), "csrc")
         subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", inc, src, "-o", lib])
         self.lib = ctypes.CDLL(lib)
+        self.lib.shim_div.argtypes = [ctypes.c_uint32, ctypes.c_uint32]
+        self.lib.shim_div.restype = ctypes.c_uint32
+        self.lib.shim_div_holds.argtypes = [ctypes.c_uint64, ctypes.c_uint32]
 
     def large_m(self, MT, big=True, fixed=False, q4=False):
         return bool(self.lib.shim_large_m(MT, big, fixed, q4))
@@ -74,6 +84,12 @@ class Plans:
         o = (ctypes.c_int * 9)()
         self.lib.shim_moe(a, o)
         return Plan(*o[:4]), Plan(*o[4:8]), o[8]
+
+    def shares(self, units, n):
+        """Where the n shares of `units` units begin (and the last one ends), and whether longer and shorter ones take turns"""
+        o = (ctypes.c_uint32 * (n + 1))()
+        in_turn = bool(self.lib.shim_shares(units, n, o))
+        return list(o), in_turn
 
     def attn_splits(self, fixed, tokens, units, n_cu=256):
         """Work-groups that share the keys of `units` (head, sequence, row block) triples"""

@@ -219,3 +219,27 @@ def test_4bit_streams_keep_their_scalar_offsets_inside_the_buffers(plans, slices
 def test_whole_k_matrices_leave_no_more_partial_sums_of_squares_than_their_buffers_hold(plans, n_cu):
     for NRB in (1, 63, 64, 65, 255, 256, 257, 304, 305):
         assert plans.whole_k(NRB, 64, 3, n_cu) == (NRB <= min(n_cu, 256)), NRB
+
+
+def test_divisions_by_a_multiplication_are_exact(plans):
+    """Row groups (up to 256 of four row blocks) and K slices (up to 16 of any K) of k2_gemm_xk: every quotient it forms."""
+    for n in list(range(1, 257)):
+        for x in {0, 1, n - 1, n, n + 1, 4 * n * n - 1, 4 * n * n, *range(0, 4 * n * n, max(1, n * n // 50))}:
+            assert plans.lib.shim_div_holds(x, n) and plans.lib.shim_div(x, n) == x // n, (x, n)
+    for n in range(1, 17):
+        for ks in (16, 250, 344, 688, 896, 1792, 5000, 8191):
+            for s in range(n + 1):
+                assert plans.lib.shim_div(s * ks, n) == s * ks // n, (s, ks, n)
+    assert not plans.lib.shim_div_holds(1 << 31, 1) and plans.lib.shim_div((1 << 31) - 1, 1) == (1 << 31) - 1
+
+
+@pytest.mark.parametrize("units,n,in_turn", [(688, 256, True), (768, 256, True), (1000, 256, True), (1792, 448, True), (8, 8, True), (32, 32, True), (1, 1, True), (257, 256, True),
+                                             (4000, 1000, False), (8016, 2004, False), (3001, 751, True), (5, 256, True)])
+def test_shares_cover_all_units_and_differ_by_one(plans, units, n, in_turn):
+    begin, got = plans.shares(units, n)
+    assert got == in_turn
+    assert begin[0] == 0 and begin[-1] == units
+    sizes = [b - a for a, b in zip(begin, begin[1:])]
+    assert min(sizes) >= units // n and max(sizes) <= -(-units // n)
+    if in_turn:
+        assert begin == [i * units // n for i in range(n + 1)]
