@@ -116,7 +116,8 @@ struct eagle_ctx {
   SeqState st; HintDev hint;
   int *hint_future, *hint_n; float *hint_alpha, *hint_bias; unsigned long long* hint_seed;
   float *pend_f, *node_f, *F, *chunk_f, *featbuf;
-  float *draft_logits, *L, *vanilla_logits, *pbuf, *qbuf, *gumbel;
+  float *draft_logits, *L, *vanilla_logits, *pbuf, *qbuf;
+  unsigned long long* part_keys; int* cnt_expand;               // child selection: the best keys of a row's parts, arrivals
   int *tree_tok, *on_path, *path, *tok_out, *len_out, *row_amax;
   void* res_host = nullptr;          // pinned host copy of [path | tok_out | len_out]
   ~eagle_ctx() { if (res_host) (void)hipHostFree(res_host); }
@@ -133,7 +134,7 @@ struct eagle_ctx {
   RowFact* facts;                      // [Mmax] rows of the pass in flight (written by its first kernel)
   float *moe_w, *xn; int* expert_used; int* experts_touched;   // (profiling) experts used, summed over the layers of a verify    // routing weights [E][largest pass], used flags [E], fp32 normalised rows (general path)
   int ssq1_groups = 0, ssq2_groups = 0;
-  unsigned long long* trace = nullptr; int trace_sel = -1, gemm_no = 0, attn_trace_sel = -1, attn_no = 0, expand_trace = 0;   // profiling builds only
+  unsigned long long* trace = nullptr; int trace_sel = -1, gemm_no = 0, attn_trace_sel = -1, attn_no = 0;   // profiling builds only
   int n_cu = 256;                      // compute units of the device (queried by eagle_init; 256 assumed when no device is visible)
   int device = 0;
   void* static_scratch = nullptr;      // this device's address of the library's static scratch array
@@ -291,7 +292,8 @@ static size_t layout(eagle_ctx* c) {
   c->vanilla_logits = a.take<float>((size_t)B * V);
   c->pbuf = a.take<float>((size_t)B * V);
   c->qbuf = a.take<float>((size_t)B * V);
-  c->gumbel = a.take<float>(g.temperature > 0.f ? (size_t)B * std::max(1, c->max_level_rows) * V : 1);
+  c->part_keys = a.take<unsigned long long>((size_t)B * std::max(1, c->max_level_rows) * EXPAND_PARTS_MAX * EAGLE_MAX_CHILD);
+  c->cnt_expand = a.take<int>((size_t)B * std::max(1, c->max_level_rows) * COUNTER_STRIDE);
   c->tree_tok = a.take<int>((size_t)B * M); c->on_path = a.take<int>((size_t)B * M); c->row_amax = a.take<int>((size_t)B * M);
   c->path = a.take<int>((size_t)B * D1); c->tok_out = a.take<int>((size_t)B * D1); c->len_out = a.take<int>(B);   // kept adjacent: fetched in one copy
   // activations
@@ -528,7 +530,6 @@ extern "C" int eagle_init(const eagle_config* cfg, void* workspace_dev, size_t w
   if (const char* t = getenv("EAGLE_Q4_STAGED")) c->q4_staged = atoi(t) != 0;
   if (const char* t = getenv("EAGLE_GEMM_TRACE")) c->trace_sel = atoi(t);
   if (const char* t = getenv("EAGLE_ATTN_TRACE")) c->attn_trace_sel = atoi(t);
-  if (getenv("EAGLE_EXPAND_TRACE")) c->expand_trace = 1;
 #endif
   *out = c;
   return EAGLE_OK;
@@ -968,13 +969,21 @@ static int target_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, 
   return EAGLE_OK;
 }
 
+static LevelParents level_parents(const eagle_ctx* c, const Pass& p) {
+  LevelParents l;
+  memset(&l, 0, sizeof(l));
+  l.M = c->M; l.D1 = c->D + 1;
+  if (p.kind == PASS_DRAFT_LEVEL)
+    for (int i = 0; i < p.rows_per_seq; ++i) { const int v = c->tree_h.level_rows[p.level][i]; l.node[i] = (uint8_t)v; l.parent[i] = (uint8_t)c->tree_h.parent[v]; }
+  return l;
+}
 // Autoregression Head over the rows of `pass`: concat(feature, token embedding) -> FC -> decoder layer (-> LM head).
 static int head_forward(eagle_ctx* c, const Pass& pass, int t_max, int n_new, bool want_logits) {
   const eagle_config& g = c->cfg;
   const int M = pass.rows_per_seq * pass.n_seq, MT = (M + 31) / 32;
   int rc, S;
-  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts);
-  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts);
+  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts, level_parents(c, pass));
+  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf_2d, g.d_model, g.vocab, MT, c->NXP, kv_for(c, g.n_layers), c->facts, level_parents(c, pass));
   LAUNCH_CHECK();
   if ((rc = (c->cur_class = KC_FC, gemm(c, c->fc, c->xf_2d, MT, M, &S)))) return rc;
   const float* bias = c->loaded_layer[EAGLE_W_FC_BIAS][0] ? c->fc_bias : nullptr;
@@ -1282,8 +1291,8 @@ static int head_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_new,
   const eagle_config& cf = c->cfg;
   const int M = pass.rows_per_seq * pass.n_seq, d = cf.d_model;
   int rc;
-  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts);
-  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts);
+  if (c->f32) k_fc_input<float><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const float*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts, level_parents(c, pass));
+  else k_fc_input<bf16_t><<<dim3(M, 4), 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, c->pend_f, c->node_f, c->chunk_f, (const bf16_t*)c->embed, c->xf2_2d, d, cf.vocab, 1, c->NXP, kv_for(c, cf.n_layers), c->facts, level_parents(c, pass));
   LAUNCH_CHECK();
   Gemm2 g = gemm2_base(c, M);
   g.epi = EPI_RESID; g.h_in = nullptr; g.h_out = c->h2; g.bias = c->loaded_layer[EAGLE_W_FC_BIAS][0] ? c->fc_bias : nullptr;
@@ -1468,6 +1477,17 @@ static LevelNodes level_nodes(const eagle_ctx* c, int level) {
   return l;
 }
 
+// The children of a level's nr parent nodes (level -1: the root) of every sequence, from their rows of draft_logits.
+static int expand(eagle_ctx* c, int level, int nr, const float* feat_src, int src_rows) {
+  const eagle_config& g = c->cfg;
+  const int parts = plan_expand_parts(g.vocab);
+  if (nr > std::max(1, c->max_level_rows)) return fail(EAGLE_EINVAL, "internal: %d parent nodes in a level", nr);
+  k_expand<<<dim3(parts, nr, c->n_active), EXPAND_THREADS, 0, c->stream>>>(level, level_nodes(c, level), c->tree_d, c->M, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint,
+                                                                          g.vocab, parts, (g.vocab + parts - 1) / parts, nr, g.temperature, g.seed, c->part_keys, c->cnt_expand, feat_src, c->node_f, g.d_model, src_rows);
+  LAUNCH_CHECK();
+  return EAGLE_OK;
+}
+
 static int do_draft(eagle_ctx* c) {
   int rc = step_ready(c);
   if (rc) return rc;
@@ -1479,11 +1499,7 @@ static int do_draft(eagle_ctx* c) {
   pass_ctx(c, p1);
   const bool fast1 = D1 * B <= 32;
   if ((rc = (fast1 ? head_forward2(c, p1, ctx, D1, false) : head_forward(c, p1, ctx + D1, D1, true)))) return rc;
-  dim3 g0(1, B);
-  const float* src1 = fast1 ? c->h2 : nullptr;   // fast path: k_expand stores the root's head feature itself
-  if (g.vocab > 32768) k_expand<true><<<g0, 1024, 0, c->stream>>>(-1, level_nodes(c, -1), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, src1, c->node_f, g.d_model, D1);
-  else k_expand<false><<<g0, 1024, 0, c->stream>>>(-1, level_nodes(c, -1), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, c->expand_trace ? c->trace : nullptr, src1, c->node_f, g.d_model, D1);
-  LAUNCH_CHECK();
+  if ((rc = expand(c, -1, 1, fast1 ? c->h2 : nullptr, D1))) return rc;   // fast path: k_expand stores the root's head feature itself
   for (int lev = 1; lev < c->D; ++lev) {
     int nr = c->tree_h.n_level_rows[lev];
     if (nr == 0) break;
@@ -1491,11 +1507,7 @@ static int do_draft(eagle_ctx* c) {
     pass_ctx(c, pl);
     const bool fastl = nr * B <= 32;
     if ((rc = (fastl ? head_forward2(c, pl, ctx, c->M, false) : head_forward(c, pl, ctx + c->M, c->M, true)))) return rc;
-    dim3 gl(nr, B);
-    const float* srcl = fastl ? c->h2 : nullptr;
-    if (g.vocab > 32768) k_expand<true><<<gl, 1024, 0, c->stream>>>(lev, level_nodes(c, lev), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, srcl, c->node_f, g.d_model, nr);
-    else k_expand<false><<<gl, 1024, 0, c->stream>>>(lev, level_nodes(c, lev), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, srcl, c->node_f, g.d_model, nr);
-    LAUNCH_CHECK();
+    if ((rc = expand(c, lev, nr, fastl ? c->h2 : nullptr, nr))) return rc;
   }
   c->phase = 1;
   return EAGLE_OK;
@@ -1752,14 +1764,9 @@ extern "C" int eagle_expand_level(eagle_ctx* c, int32_t level) {
   if (!c) return fail(EAGLE_EINVAL, "null context");
   if (c->n_active < 1) return fail(EAGLE_ESTATE, "no active sequence");
   if (level != -1 && (level < 1 || level >= c->D)) return fail(EAGLE_EINVAL, "level must be -1 (the root) or 1..depth-1");
-  const eagle_config& g = c->cfg;
   const int nr = level < 0 ? 1 : c->tree_h.n_level_rows[level];
   if (nr == 0) return EAGLE_OK;
-  dim3 grid(nr, c->n_active);
-  if (g.vocab > 32768) k_expand<true><<<grid, 1024, 0, c->stream>>>(level, level_nodes(c, level), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, nullptr, c->node_f, g.d_model, nr);
-  else k_expand<false><<<grid, 1024, 0, c->stream>>>(level, level_nodes(c, level), c->tree_d, c->st, c->draft_logits, c->tree_tok, c->on_path, c->hint, g.vocab, g.temperature, g.seed, nullptr, nullptr, c->node_f, g.d_model, nr);
-  LAUNCH_CHECK();
-  return EAGLE_OK;
+  return expand(c, level, nr, nullptr, nr);
 }
 
 extern "C" int eagle_force_accept(eagle_ctx* c, const int32_t* path, const int32_t* len, const int32_t* bonus) {

@@ -2,6 +2,7 @@
 // tree-masked verification (Sec. 3.3) and acceptance (Sec. 2, App. A.2 Alg. 1) + commit.
 #pragma once
 #include "common.h"
+#include "plans.h"
 
 // ============================================================================ device-side model state
 struct TreeDev {
@@ -35,7 +36,8 @@ struct RowInfo {
   unsigned long long mask;
 };
 
-__device__ inline RowInfo row_info(const Pass& p, const TreeDev* t, const SeqState& st, int r) {
+// level_node: the row's node in a level pass, where the caller knows it.
+__device__ inline RowInfo row_info(const Pass& p, const TreeDev* t, const SeqState& st, int r, int level_node = -1) {
   RowInfo o;
   int i = r % p.rows_per_seq;
   o.seq = p.seq0 + r / p.rows_per_seq;
@@ -58,7 +60,7 @@ __device__ inline RowInfo row_info(const Pass& p, const TreeDev* t, const SeqSta
       break;
     }
     case PASS_DRAFT_LEVEL: {
-      int v = t->level_rows[p.level][i];
+      const int v = level_node >= 0 ? level_node : t->level_rows[p.level][i];
       o.node = v; o.base = ctx - 1; o.rel = v; o.pos = ctx - 1 + t->depth[v]; o.slot = ctx - 1 + v; o.mask = t->anc[v];
       break;
     }
@@ -114,6 +116,24 @@ __device__ inline float cache_load(const bf16_t* p) { return bf16_to_f32(*p); }
 __device__ inline void cache_store(float* p, float v) { *p = v; }
 __device__ inline void cache_store(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 
+// Ints between two arrival counters: a 256-byte piece of memory each.  (Side by side, the arrivals of a launch were 256 atomic additions to two
+// cache lines: O 11.7 -> 11.4 us, the head's O 10.6 -> 10.2, fc 17.4 -> 17.2 at 7B widths.)
+constexpr int COUNTER_STRIDE = 64;
+
+// Before a work-group announces its coherent stores through an arrival counter, every wave waits until its own
+// vector-memory stores have been acknowledged.  A work-group-scope release fence alone does not do that on this
+// target (waves of one work-group share a CU, so the compiler emits no vector-memory wait for it), and the stores
+// go to other L2 channels than the counter: without the wait the counter can be seen before the data.
+// s_waitcnt 0x0F70 = vmcnt(0), expcnt and lgkmcnt left alone.
+__device__ __forceinline__ void publish_wait() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+}
+
+// A value that nothing writes while the kernel runs, at an address that is the same for the whole wave: fetched into a scalar register.
+template <typename T>
+__device__ __forceinline__ T read_only(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
+
 // ============================================================================ block reductions
 __device__ inline float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -165,12 +185,33 @@ __device__ inline unsigned long long key_max_dpp(unsigned long long k) {   // la
 __device__ inline unsigned long long key_of_lane(unsigned long long k, int lane) {
   return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, lane);
 }
+// Largest key of the wave.
+__device__ inline unsigned long long wave_max_key(unsigned long long k) {
+  k = key_max_dpp<0x111, 0xf>(k); k = key_max_dpp<0x112, 0xf>(k); k = key_max_dpp<0x114, 0xf>(k); k = key_max_dpp<0x118, 0xf>(k);   // row_shr 1, 2, 4, 8
+  k = key_max_dpp<0x142, 0xa>(k); k = key_max_dpp<0x143, 0xc>(k);                                                                  // row_bcast 15, 31
+  return key_of_lane(k, 63);
+}
+// The n largest of a wave's keys, N of them a lane, no two alike but for 0 (none): lane r returns the r-th.
+template <int N>
+__device__ inline unsigned long long wave_top_keys(const unsigned long long* keys, int n) {
+  unsigned long long mine = 0, res = 0;
+#pragma unroll
+  for (int u = 0; u < N; ++u) mine = keys[u] > mine ? keys[u] : mine;
+  for (int r = 0; r < n; ++r) {
+    const unsigned long long top = wave_max_key(mine);
+    if ((int)(threadIdx.x & 63) == r) res = top;
+    if (mine == top && r + 1 < n) {                              // its owner: the next of its own
+      mine = 0;
+#pragma unroll
+      for (int u = 0; u < N; ++u) mine = keys[u] < top && keys[u] > mine ? keys[u] : mine;
+    }
+  }
+  return res;
+}
 // Largest key of the block (at most 16 waves); sh: 16 entries.  Lane moves inside the vector unit (row shifts, row broadcasts) instead of
 // exchanges through the LDS unit (child selection at 1024 entries, two to four rounds: 12.3 -> 8.6 us a launch).
 __device__ inline unsigned long long block_max_key(unsigned long long k, unsigned long long* sh) {
-  k = key_max_dpp<0x111, 0xf>(k); k = key_max_dpp<0x112, 0xf>(k); k = key_max_dpp<0x114, 0xf>(k); k = key_max_dpp<0x118, 0xf>(k);   // row_shr 1, 2, 4, 8
-  k = key_max_dpp<0x142, 0xa>(k); k = key_max_dpp<0x143, 0xc>(k);                                                                  // row_bcast 15, 31
-  k = key_of_lane(k, 63);
+  k = wave_max_key(k);
   const int nw = (blockDim.x + 63) >> 6, l = threadIdx.x & 15;
   __syncthreads();                                               // (sh may still be read from the call before)
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = k;
@@ -838,6 +879,16 @@ __global__ __launch_bounds__(256) void k_embed(Pass pass, const TreeDev* tree, S
   }
 }
 
+// Eight consecutive numbers of a row.
+__device__ __forceinline__ void embed8(const float* p, float* x) {
+  const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
+  x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+}
+__device__ __forceinline__ void embed8(const bf16_t* p, float* x) {
+  const u32x4 r = *(const u32x4*)p;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) { x[2 * t] = __builtin_bit_cast(float, r[t] << 16); x[2 * t + 1] = __builtin_bit_cast(float, r[t] & 0xFFFF0000u); }
+}
 __device__ inline void xf_store8(bf16_t* XF, int m, int k8, int MT, int KS, int nplanes, const float* x) {
   // plane q holds bf16(x - planes 0..q-1), as split_bf16 defines it; written plane by plane so that nothing is indexed
   // by a run-time value (an array indexed by the plane number would live on the stack)
@@ -869,24 +920,27 @@ __device__ inline int xcd_row() {
 //   pending pass : feature = target feature kept at the last commit, token = committed token at pos+1
 //   level pass   : feature = the head's output at the node's parent, token = the node's drafted token
 //   draft prefill: feature = target feature of the prompt position, token = the next prompt token
+struct LevelParents { int M, D1; uint8_t node[EAGLE_MAX_NODES], parent[EAGLE_MAX_NODES]; };   // nodes of the tree, its depth + 1, a level's nodes and their parents by row
 template <typename EmbT>
 __global__ __launch_bounds__(256) void k_fc_input(Pass pass, const TreeDev* tree, SeqState st, const int* tree_tok,
                                                   const float* pend_f /*[seq][D+1][d]*/, const float* node_f /*[seq][M][d]*/,
                                                   const float* chunk_f /*[chunk][d]*/, const EmbT* __restrict__ embed,
-                                                  bf16_t* XF, int d, int vocab, int MT, int nplanes, KVCache kv, RowFact* facts) {
+                                                  bf16_t* XF, int d, int vocab, int MT, int nplanes, KVCache kv, RowFact* facts, LevelParents lp) {
   const int r = xcd_row();
-  RowInfo ri = row_info(pass, tree, st, r);
+  const bool level = pass.kind == PASS_DRAFT_LEVEL;
+  const int i = level ? r % pass.rows_per_seq : 0;
+  RowInfo ri = row_info(pass, tree, st, r, level ? lp.node[i] : -1);
   if (blockIdx.y == 0 && threadIdx.x == 0) facts[r] = row_fact(pass, tree, ri, kv);
   const int KS = 2 * d / 16;
   const float* f = nullptr;
   int tok = 0;
   if (ri.valid) {
     if (pass.kind == PASS_DRAFT_PENDING) {
-      f = pend_f + ((size_t)ri.seq * (tree->D + 1) + ri.rel) * d;
+      f = pend_f + ((size_t)ri.seq * lp.D1 + ri.rel) * d;
       tok = st.tokens[(size_t)ri.seq * st.tok_stride + ri.pos + 1];
     } else if (pass.kind == PASS_DRAFT_LEVEL) {
-      f = node_f + ((size_t)ri.seq * tree->M + tree->parent[ri.node]) * d;
-      tok = tree_tok[ri.seq * tree->M + ri.node];
+      f = node_f + ((size_t)ri.seq * lp.M + lp.parent[i]) * d;
+      tok = tree_tok[ri.seq * lp.M + ri.node];
     } else {
       f = chunk_f + (size_t)ri.rel * d;
       tok = st.tokens[(size_t)ri.seq * st.tok_stride + ri.pos + 1];
@@ -895,16 +949,10 @@ __global__ __launch_bounds__(256) void k_fc_input(Pass pass, const TreeDev* tree
   tok = min(max(tok, 0), vocab - 1);
   // blockIdx.y splits the 2d columns so that a pass of a few rows still spreads over many CUs
   for (int k8 = (blockIdx.y * blockDim.x + threadIdx.x) * 8; k8 < 2 * d; k8 += gridDim.y * blockDim.x * 8) {
-    float x[8];
-    for (int t = 0; t < 8; ++t) {
-      int k = k8 + t;
-      float v = 0.f;
-      if (ri.valid) {
-        if (k < d) v = f[k];
-        else if constexpr (sizeof(EmbT) == 4) v = ((const float*)embed)[(size_t)tok * d + (k - d)];
-        else v = bf16_to_f32(((const bf16_t*)embed)[(size_t)tok * d + (k - d)]);
-      }
-      x[t] = v;
+    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (ri.valid) {
+      if (k8 < d) embed8(f + k8, x);
+      else embed8(embed + (size_t)tok * d + (k8 - d), x);
     }
     xf_store8(XF, r, k8, MT, KS, nplanes, x);
   }
@@ -1407,172 +1455,113 @@ struct HintDev {
 // Children of one tree node = the top-k entries of its (knob-adjusted, Gumbel-perturbed when non-greedy) head
 // logits, rank r = (r+1)-th largest, equal scores -> lower token id (App. A.1).  Block = (parent row, seq).
 struct LevelNodes { uint8_t node[EAGLE_MAX_NODES]; };            // a level's parent nodes, by row of its pass (kernel argument: no load in front)
-template <bool BIGV>   // BIGV: more than 32768 vocabulary entries (the scores of a row do not fit the block's registers)
-__global__ __launch_bounds__(1024) void k_expand(int level /*-1 = root*/, LevelNodes nodes, const TreeDev* tree, SeqState st,
-                                                 float* draft_logits /*[seq][M][V]*/, int* tree_tok, int* on_path, HintDev hint,
-                                                 int V, float temperature, unsigned long long rng_seed, unsigned long long* trace,
-                                                 const float* __restrict__ feat_src /*[pass rows][d] or null*/, float* node_f /*[seq][M][d]*/,
-                                                 int d, int src_rows_per_seq) {
-  __shared__ unsigned long long shk[16];
-  const int seq = blockIdx.y;
-  unsigned long long* tr = TRACE_PTR((trace && threadIdx.x == 0 && blockIdx.x == 0 && seq == 0) ? trace : nullptr);
-  TRACE_STAMP(tr, 0);
-  const int v = nodes.node[blockIdx.x];
-  const int M = tree->M;
+// A row's vocabulary is shared by `parts` work-groups of four waves (plan_expand_parts), eight tokens a thread at a time: each wave keeps its best
+// children without a barrier, one wave the work-group's, and the row's last work-group to arrive the row's (the exchange of k2_gemm: store,
+// acknowledge, count, read back).  Bound: a work-group's chain of latencies.  One work-group of sixteen waves for a row took two barriers a child
+// and all of a row's noise: us a launch, one row with four children of 32000 tokens 22.7 / now 7.7; four rows 16.2 / 6.2; one row with
+// noise 22.6 / 6.4; 1024 tokens (one part) 8.6 / 3.7.  (With the next level's FC input made here as well -- the features beside the choice, the embeddings by the
+// last work-group -- a launch grew by the 4 to 8 us that k_fc_input takes.)
+constexpr int EXPAND_THREADS = 256, EXPAND_KEYS = 8;             // tokens a thread takes at a time
+__global__ __launch_bounds__(EXPAND_THREADS) void k_expand(int level /*-1 = root*/, LevelNodes nodes, const TreeDev* tree, int M, SeqState st,
+                                                           float* draft_logits /*[seq][M][V]*/, int* tree_tok, int* on_path, HintDev hint,
+                                                           int V, int parts, int per /*tokens of a part*/, int rows, float temperature, unsigned long long rng_seed,
+                                                           unsigned long long* part_keys /*[seq][row][parts][8]*/, int* arrivals /*[seq][row]*/,
+                                                           const float* __restrict__ feat_src /*[pass rows][d] or null*/, float* node_f /*[seq][M][d]*/,
+                                                           int d, int src_rows_per_seq) {
+  __shared__ unsigned long long list[4 * EAGLE_MAX_CHILD];
+  const int part = blockIdx.x, row = blockIdx.y, seq = blockIdx.z;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int v = nodes.node[row];
   float* lg = draft_logits + ((size_t)seq * M + v) * V;
-  // Loads are grouped by what they depend on, so that the kernel pays two memory round trips, not one per fact:
-  // (1) everything addressed by (seq, v) alone, including the first 32 logits of every thread ...
-  constexpr int XPT = 32;                                      // logits per thread and chunk (1024 threads: 32768)
-  float x[XPT];
+  const int begin = part * per, end = min(V, begin + per);
+  // the first tokens' logits are on their way before any fact about the row is known
+  float x[EXPAND_KEYS];
+  auto request = [&](int at) {
 #pragma unroll
-  for (int u = 0; u < XPT; ++u) {
-    x[u] = -INFINITY;
-    if (u * 1024 < V) x[u] = lg[min(u * 1024 + (int)threadIdx.x, V - 1)];
-  }
-  const int n = st.n_tok[seq];
-  // The node's own head feature (the row of the pass that produced these logits) goes to node_f when the caller asks for it: one
-  // block per row of the pass exists anyway, which saves a separate copy kernel per pass.  Row of the pass: a level pass lists the
-  // level's parent nodes in order; in a pending pass the root is the sequence's last pending row.
-  const int feat_row = feat_src ? seq * src_rows_per_seq + (level < 0 ? max(st.n_pend[seq] - 1, 0) : (int)blockIdx.x) : 0;
-  const int hn = hint.n[seq];
-  const unsigned long long hseed = hint.seed[seq];
-  const float halpha = hint.alpha[seq], hbias = hint.bias[seq];
-  const int depth_v = tree->depth[v], nk = tree->nchild[v];
-  const int on_v = v == 0 ? 0 : on_path[seq * M + v];
-  const unsigned long long step_no = (unsigned long long)st.step_no[seq];
-  // (2) ... then what needs the sequence length: the feature row, stored at the end, the root token, the target's future tokens at two positions
-  f32x4 feat[2];                                               // columns 4 * tid .. of 8192; wider rows: below
-  const float* feat_in = feat_src ? feat_src + (size_t)feat_row * d : nullptr;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    feat[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int k = 4096 * i + 4 * (int)threadIdx.x;
-    if (feat_src && k < d) feat[i] = *(const f32x4*)(feat_in + k);
-  }
-  const int stride = hint.stride;
-  const int pos_child = n + depth_v;
-  const int root_tok = st.tokens[(size_t)seq * st.tok_stride + max(n - 1, 0)];
-  const int fut_root = hint.future[(size_t)seq * stride + min(max(n - 1, 0), stride - 1)];
-  const int fut_child = hint.future[(size_t)seq * stride + min(pos_child, stride - 1)];
-  int on = on_v;
-  if (v == 0) {
-    on = (hn > n - 1) && fut_root == root_tok;
-    if (threadIdx.x == 0) { tree_tok[seq * M] = root_tok; on_path[seq * M] = on; }
-  }
+    for (int u = 0; u < EXPAND_KEYS; ++u) x[u] = lg[min(at + u * EXPAND_THREADS + (int)threadIdx.x, V - 1)];
+  };
+  request(begin);
+  const int n = read_only(st.n_tok + seq), hn = read_only(hint.n + seq), nk = read_only(tree->nchild + v);
+  const int child = tree->child[v][min(lane, EAGLE_MAX_CHILD - 1)];
   // acceptance knob of the synthetic workload
-  const int hinted = (on && pos_child < hn) ? fut_child : -1;
+  int hinted = -1, on = 0;
   float adj = 0.f;
-  if (hinted >= 0) {
-    uint32_t k24 = rng_u24(rng_prefix(hseed, PURPOSE_HINT, 0), (uint32_t)seq, 0, (uint32_t)pos_child);
-    adj = ((float)k24 * 5.9604644775390625e-8f < halpha) ? hbias : -hbias;
+  if (hn > 0) {
+    const int pos_child = n + read_only(tree->depth + v), last = max(n - 1, 0);
+    const int* future = hint.future + (size_t)seq * hint.stride;
+    on = v ? on_path[seq * M + v] : hn > n - 1 && read_only(future + min(last, hint.stride - 1)) == read_only(st.tokens + (size_t)seq * st.tok_stride + last);
+    if (on && pos_child < hn) {
+      hinted = read_only(future + min(pos_child, hint.stride - 1));
+      const uint32_t k24 = rng_u24(rng_prefix(read_only(hint.seed + seq), PURPOSE_HINT, 0), (uint32_t)seq, 0, (uint32_t)pos_child);
+      adj = ((float)k24 * 5.9604644775390625e-8f < read_only(hint.alpha + seq)) ? read_only(hint.bias + seq) : -read_only(hint.bias + seq);
+    }
   }
   const bool gumbel = temperature > 0.f;
   unsigned long long pre = 0ull;
-  if (gumbel) pre = rng_prefix(rng_seed, PURPOSE_GUMBEL, step_no);
-  int childs[EAGLE_MAX_CHILD];
+  if (gumbel) pre = rng_prefix(rng_seed, PURPOSE_GUMBEL, (unsigned long long)read_only(st.step_no + seq));
+  // The node's own head feature (the row of the pass that produced these logits) goes to node_f when the caller asks for it, which saves a
+  // separate copy kernel per pass.  Row of the pass: a level pass lists the level's parent nodes in order; in a pending pass the root is the
+  // sequence's last pending row.
+  if (feat_src) {
+    const float* src = feat_src + (size_t)(seq * src_rows_per_seq + (level < 0 ? max(read_only(st.n_pend + seq) - 1, 0) : row)) * d;
+    float* dst = node_f + ((size_t)seq * M + v) * d;
+    for (int k = 4 * (part * EXPAND_THREADS + (int)threadIdx.x); k < d; k += 4 * parts * EXPAND_THREADS) *(f32x4*)(dst + k) = *(const f32x4*)(src + k);
+  }
+  unsigned long long best = 0;                                 // wave 0: lane r has the work-group's r-th best so far
+  for (int at = begin; at < end; at += EXPAND_KEYS * EXPAND_THREADS) {
+    if (at > begin) request(at);
+    unsigned long long keys[EXPAND_KEYS];
 #pragma unroll
-  for (int q = 0; q < EAGLE_MAX_CHILD; ++q) childs[q] = tree->child[v][q];
-  int picked[EAGLE_MAX_CHILD];                                 // thread 0 writes the results once, after the rounds
-#pragma unroll
-  for (int q = 0; q < EAGLE_MAX_CHILD; ++q) picked[q] = 0;
-  TRACE_STAMP_AFTER(tr, 1, x[0]);
-  if constexpr (!BIGV) {
-    // Scores stay in registers.  Every thread offers its best entry; the block picks the overall best (ties to the
-    // lower token id); only the thread that owned it removes it and looks for its next best.
-#pragma unroll
-    for (int u = 0; u < XPT; ++u) {
-      if (u * 1024 >= V) continue;                             // (uniform: a small vocabulary uses the first few)
-      const int j = u * 1024 + (int)threadIdx.x;
+    for (int u = 0; u < EXPAND_KEYS; ++u) {
+      const int j = at + u * EXPAND_THREADS + (int)threadIdx.x;
       float sc = x[u];
-      if (j == hinted) { sc += adj; lg[j] = sc; }            // later phases read the adjusted logits
+      if (j == hinted && j < end) { sc += adj; lg[j] = sc; }     // later phases read the adjusted logits
       if (gumbel) {
-        float un = ((float)rng_u24(pre, (uint32_t)seq, (uint32_t)v, (uint32_t)min(j, V - 1)) + 0.5f) * 5.9604644775390625e-8f;
+        const float un = ((float)rng_u24(pre, (uint32_t)seq, (uint32_t)v, (uint32_t)min(j, V - 1)) + 0.5f) * 5.9604644775390625e-8f;
         sc = sc / temperature - logf(-logf(un));
       }
-      x[u] = j < V && sc == sc ? sc : -INFINITY;             // (a NaN is no better than -inf, see arg_key)
+      keys[u] = j < end ? arg_key(sc, j) : 0ull;               // (a NaN is no better than -inf, but it has a token)
     }
-    // a thread's best entry that is not taken yet: bit u of `taken`
-    uint32_t taken = 0;
-    auto best = [&]() {
-      float lv = -INFINITY; int lu = -1;
-#pragma unroll
-      for (int u = 0; u < XPT; ++u) {
-        if (u * 1024 >= V) continue;
-        const bool win = !(taken >> u & 1) && (x[u] > lv || lu < 0);
-        lv = win ? x[u] : lv; lu = win ? u : lu;
-      }
-      const int j = lu * 1024 + (int)threadIdx.x;
-      return lu >= 0 && j < V ? arg_key(lv, j) : 0ull;
-    };
-    unsigned long long mine = best();
-    TRACE_STAMP_AFTER(tr, 2, x[0]);
-    for (int r = 0; r < nk; ++r) {
-      const unsigned long long top = block_max_key(mine, shk);
-      const int bi = arg_index(top);
-      if (top == mine) { taken |= 1u << (bi >> 10); mine = best(); }   // mine: take it out, find my next best
-#pragma unroll
-      for (int q = 0; q < EAGLE_MAX_CHILD; ++q) if (q == r) picked[q] = bi;
-    }
-  } else {
-    // Larger vocabularies: one pass with a per-thread sorted top-nk list, then rounds over the lists' heads.
-    float tv[EAGLE_MAX_CHILD];
-    int ti[EAGLE_MAX_CHILD];
-#pragma unroll
-    for (int q = 0; q < EAGLE_MAX_CHILD; ++q) { tv[q] = -INFINITY; ti[q] = 0x7fffffff; }
-    for (int j0 = 0; j0 < V; j0 += XPT * 1024) {
-      if (j0 > 0) {
-#pragma unroll
-        for (int u = 0; u < XPT; ++u) x[u] = lg[min(j0 + u * 1024 + (int)threadIdx.x, V - 1)];
-      }
-#pragma unroll
-      for (int u = 0; u < XPT; ++u) {
-        const int j = j0 + u * 1024 + (int)threadIdx.x;
-        if (j >= V) continue;
-        float sc = x[u];
-        if (j == hinted) { sc += adj; lg[j] = sc; }
-        if (gumbel) {
-          float un = ((float)rng_u24(pre, (uint32_t)seq, (uint32_t)v, (uint32_t)j) + 0.5f) * 5.9604644775390625e-8f;
-          sc = sc / temperature - logf(-logf(un));
-        }
-        float cv = sc == sc ? sc : -INFINITY; int ci = j;      // (a NaN is no better than -inf, but it has a token)
-#pragma unroll
-        for (int q = 0; q < EAGLE_MAX_CHILD; ++q) {
-          const bool win = cv > tv[q] || (cv == tv[q] && ci < ti[q]);
-          const float ov = tv[q]; const int oi = ti[q];
-          if (win) { tv[q] = cv; ti[q] = ci; cv = ov; ci = oi; }
-        }
-      }
-    }
-    for (int r = 0; r < nk; ++r) {
-      const int bi = arg_index(block_max_key(arg_key(tv[0], ti[0]), shk));
-      if (bi == ti[0]) {
-#pragma unroll
-        for (int q = 0; q + 1 < EAGLE_MAX_CHILD; ++q) { tv[q] = tv[q + 1]; ti[q] = ti[q + 1]; }
-        tv[EAGLE_MAX_CHILD - 1] = -INFINITY; ti[EAGLE_MAX_CHILD - 1] = 0x7fffffff;
-      }
-#pragma unroll
-      for (int q = 0; q < EAGLE_MAX_CHILD; ++q) if (q == r) picked[q] = bi;
+    const unsigned long long wave_best = wave_top_keys<EXPAND_KEYS>(keys, nk);
+    if (at > begin) __syncthreads();                           // (wave 0 has read the last ones)
+    if (lane < EAGLE_MAX_CHILD) list[w * EAGLE_MAX_CHILD + lane] = wave_best;
+    __syncthreads();
+    if (w == 0) {
+      const unsigned long long both[2] = {lane < 4 * EAGLE_MAX_CHILD ? list[min(lane, 4 * EAGLE_MAX_CHILD - 1)] : 0ull, best};
+      best = wave_top_keys<2>(both, nk);
     }
   }
-  if (threadIdx.x == 0) {
+  if (w) return;
+  if (parts > 1) {
+    const int slot = seq * rows + row;
+    unsigned long long* keys = part_keys + (size_t)slot * parts * EAGLE_MAX_CHILD;
+    int* cnt = arrivals + slot * COUNTER_STRIDE;
+    if (lane < EAGLE_MAX_CHILD) __hip_atomic_store(keys + part * EAGLE_MAX_CHILD + lane, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    publish_wait();
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(old) != parts - 1) return;
+    if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    unsigned long long all[EXPAND_PARTS_MAX * EAGLE_MAX_CHILD / 64];
 #pragma unroll
-    for (int q = 0; q < EAGLE_MAX_CHILD; ++q)
-      if (q < nk) {
-        // (fewer tokens in the vocabulary than children: nothing is left to pick, and acceptance indexes its vectors with the token)
-        tree_tok[seq * M + childs[q]] = min(max(picked[q], 0), V - 1);
-        on_path[seq * M + childs[q]] = (hinted >= 0 && picked[q] == hinted);
-      }
-  }
-  if (feat_src) {
-    float* dst = node_f + ((size_t)seq * M + v) * d;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int k = 4096 * i + 4 * (int)threadIdx.x;
-      if (k < d) *(f32x4*)(dst + k) = feat[i];
+    for (int u = 0; u < EXPAND_PARTS_MAX * EAGLE_MAX_CHILD / 64; ++u) {
+      const int i = u * 64 + lane;
+      all[u] = __hip_atomic_load(keys + min(i, parts * EAGLE_MAX_CHILD - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (i >= parts * EAGLE_MAX_CHILD) all[u] = 0ull;
     }
-    for (int k = 8192 + (int)threadIdx.x; k < d; k += 1024) dst[k] = feat_in[k];
+    best = wave_top_keys<EXPAND_PARTS_MAX * EAGLE_MAX_CHILD / 64>(all, nk);
   }
-  TRACE_STAMP(tr, 3);
+  if (lane < nk) {
+    // (fewer tokens in the vocabulary than children: nothing is left to pick, and acceptance indexes its vectors with the token)
+    const int pick = best ? arg_index(best) : -1;
+    tree_tok[seq * M + child] = min(max(pick, 0), V - 1);
+    on_path[seq * M + child] = hinted >= 0 && pick == hinted;
+  }
+  if (v == 0 && lane == 0) {
+    tree_tok[seq * M] = read_only(st.tokens + (size_t)seq * st.tok_stride + max(n - 1, 0));
+    on_path[seq * M] = on;
+  }
 }
 
 // softmax(x / T) over V entries into p (block-wide), returns nothing; sh >= 16 floats

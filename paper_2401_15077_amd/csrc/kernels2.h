@@ -22,10 +22,6 @@
 __device__ inline void coh_store(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline float coh_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Ints between two arrival counters: a 256-byte piece of memory each.  (Side by side, the arrivals of a launch were 256 atomic additions to two
-// cache lines: O 11.7 -> 11.4 us, the head's O 10.6 -> 10.2, fc 17.4 -> 17.2 at 7B widths.)
-constexpr int COUNTER_STRIDE = 64;
-
 // 16-byte agent-scope accesses: buffer instructions carry the scope bit (aux 16 = sc1); byte offsets below 2 GiB.
 __device__ inline __amdgpu_buffer_rsrc_t coh_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7FFFFFFF, 0x00020000);
@@ -138,16 +134,6 @@ __device__ inline void block_rstd_finish(const RowScale& rs, float part, float* 
 }
 
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
-
-// Before a work-group announces its coherent stores through an arrival counter, every wave waits until its own
-// vector-memory stores have been acknowledged.  A work-group-scope release fence alone does not do that on this
-// target (waves of one work-group share a CU, so the compiler emits no vector-memory wait for it), and the stores
-// go to other L2 channels than the counter: without the wait the counter can be seen before the data.
-// s_waitcnt 0x0F70 = vmcnt(0), expcnt and lgkmcnt left alone.
-__device__ __forceinline__ void publish_wait() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-}
 
 struct Gemm2 {
   // what the start of a weight stream needs, side by side: one fetch of arguments before the first request

@@ -30,6 +30,10 @@ static inline Share share_of(uint32_t units, uint32_t n) {
 }
 constexpr uint32_t share_begin(uint32_t i, uint32_t units, uint32_t a, uint32_t b) { return b == SHARE_IN_TURN ? div_magic(i * units, a) : i * a + (i < b ? i : b); }
 
+// Work-groups that share a row's vocabulary in the choice of its children: about 2048 tokens each, at most EXPAND_PARTS_MAX.
+constexpr int EXPAND_PARTS_MAX = 16;
+static inline int plan_expand_parts(int vocab) { return std::max(1, std::min(EXPAND_PARTS_MAX, (vocab + 2047) / 2048)); }
+
 struct GemmPlan { int S, ks_per_split, chunk, rbw, mw; };   // rbw, mw: tile shape of the large-M GEMM (0: k_gemm)
 
 static inline GemmPlan plan_gemm(int NRB, int KS, int NXP, int MT) {
