@@ -118,7 +118,7 @@ struct eagle_ctx {
   float *pend_f, *node_f, *F, *chunk_f, *featbuf;
   float *draft_logits, *L, *vanilla_logits, *pbuf, *qbuf;
   unsigned long long* part_keys; int* cnt_expand;               // child selection: the best keys of a row's parts, arrivals
-  int *tree_tok, *on_path, *path, *tok_out, *len_out, *row_amax;
+  int *tree_tok, *on_path, *path, *tok_out, *len_out; int2* outcome;
   void* res_host = nullptr;          // pinned host copy of [path | tok_out | len_out]
   ~eagle_ctx() { if (res_host) (void)hipHostFree(res_host); }
   // activations
@@ -294,7 +294,7 @@ static size_t layout(eagle_ctx* c) {
   c->qbuf = a.take<float>((size_t)B * V);
   c->part_keys = a.take<unsigned long long>((size_t)B * std::max(1, c->max_level_rows) * EXPAND_PARTS_MAX * EAGLE_MAX_CHILD);
   c->cnt_expand = a.take<int>((size_t)B * std::max(1, c->max_level_rows) * COUNTER_STRIDE);
-  c->tree_tok = a.take<int>((size_t)B * M); c->on_path = a.take<int>((size_t)B * M); c->row_amax = a.take<int>((size_t)B * M);
+  c->tree_tok = a.take<int>((size_t)B * M); c->on_path = a.take<int>((size_t)B * M); c->outcome = a.take<int2>((size_t)B * M);
   c->path = a.take<int>((size_t)B * D1); c->tok_out = a.take<int>((size_t)B * D1); c->len_out = a.take<int>(B);   // kept adjacent: fetched in one copy
   // activations
   const int Mm = c->Mmax, MTm = Mm / 32;
@@ -519,7 +519,7 @@ extern "C" int eagle_init(const eagle_config* cfg, void* workspace_dev, size_t w
         hipStreamSynchronize(c->stream) != hipSuccess) { delete c; return fail(EAGLE_EHIP, "page table upload failed"); }
   }
   if (g.temperature > 0.f && g.vocab <= 32768 &&
-      (hipFuncSetAttribute((const void*)k_accept<ACCEPT_SAMPLED>, hipFuncAttributeMaxDynamicSharedMemorySize, CDF_LDS) != hipSuccess ||
+      (hipFuncSetAttribute((const void*)k_outcome<ACCEPT_SAMPLED>, hipFuncAttributeMaxDynamicSharedMemorySize, CDF_LDS) != hipSuccess ||
        hipFuncSetAttribute((const void*)k_choose<false>, hipFuncAttributeMaxDynamicSharedMemorySize, CDF_LDS) != hipSuccess)) { delete c; return fail(EAGLE_EHIP, "shared memory of the sampling kernels"); }
   c->hint.future = c->hint_future; c->hint.stride = c->st.tok_stride; c->hint.n = c->hint_n;
   c->hint.alpha = c->hint_alpha; c->hint.bias = c->hint_bias; c->hint.seed = c->hint_seed;
@@ -1275,8 +1275,8 @@ static int target_forward2(eagle_ctx* c, const Pass& pass, int ctx_max, int n_ne
   const int M = pass.rows_per_seq * pass.n_seq, d = cf.d_model;
   int rc;
   const int eg = std::max(1, std::min(64, d / 64));
-  if (c->f32) k2_embed<float, 3><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const float*)c->embed, cf.vocab, M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2, kv_for(c, 0), c->facts);
-  else k2_embed<bf16_t, 2><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const bf16_t*)c->embed, cf.vocab, M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2, kv_for(c, 0), c->facts);
+  if (c->f32) k2_embed<float, 3><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const float*)c->embed, cf.vocab, M, c->M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2, kv_for(c, 0), c->facts);
+  else k2_embed<bf16_t, 2><<<eg, 256, 0, c->stream>>>(pass, c->tree_d, c->st, c->tree_tok, (const bf16_t*)c->embed, cf.vocab, M, c->M, d, c->h2, c->layers[0].attn_norm, c->xf2_d, c->ssq2, kv_for(c, 0), c->facts);
   LAUNCH_CHECK();
   c->ssq2_groups = eg;
   for (int l = 0; l < cf.n_layers; ++l)
@@ -1532,36 +1532,41 @@ static int do_verify(eagle_ctx* c) {
   return EAGLE_OK;
 }
 
-static int do_compact(eagle_ctx* c);
-
-// Acceptance + commit.  pbuf / qbuf (fp32 [n_active][vocab] each, non-greedy only) and row_amax (int [n_active][M], greedy
-// only) are the kernels' scratch: the caller's workspace, or the library's static device array.
-static int do_accept(eagle_ctx* c, float* pbuf, float* qbuf, int* row_amax) {
-  if (c->phase != 2) return fail(EAGLE_ESTATE, "eagle_accept needs verified logits (call eagle_verify first)");
+// Path, tokens and lengths, KV rows, pending features and the sequences' state: from the nodes' outcomes, or (null) along a path that is there.
+static int do_commit(eagle_ctx* c, const int2* outcome) {
   const eagle_config& g = c->cfg;
-  const int B = c->n_active;
-  if (g.temperature <= 0.f) { k_row_argmax<<<B * c->M, 1024, 0, c->stream>>>(c->L, g.vocab, row_amax); LAUNCH_CHECK(); }
-#define ACCEPT(KIND, LDS) k_accept<KIND><<<B, 1024, LDS, c->stream>>>(c->tree_d, c->st, c->L, c->draft_logits, c->tree_tok, g.vocab, g.temperature, g.seed, pbuf, qbuf, c->path, c->tok_out, c->len_out, row_amax)
-  if (g.temperature <= 0.f) ACCEPT(ACCEPT_GREEDY, 0);
-  else if (g.vocab > 32768) ACCEPT(ACCEPT_SAMPLED_BIGV, 0);
-  else ACCEPT(ACCEPT_SAMPLED, CDF_LDS);
-#undef ACCEPT
-  LAUNCH_CHECK();
-  return do_compact(c);
-}
-static int do_accept(eagle_ctx* c) { return do_accept(c, c->pbuf, c->qbuf, c->row_amax); }
-
-static int do_compact(eagle_ctx* c) {
-  const eagle_config& g = c->cfg;
-  const int B = c->n_active;
-  dim3 grid(4, g.n_layers + 1, B);
-  KVCache kv = kv_for(c, 0);
-  if (c->kv_f32) k_compact<float><<<grid, 256, 0, c->stream>>>(c->tree_d, c->st, c->path, c->len_out, c->kc, c->vc, c->layer_stride, g.n_layers, kv, c->F, c->pend_f, g.d_model);
-  else k_compact<bf16_t><<<grid, 256, 0, c->stream>>>(c->tree_d, c->st, c->path, c->len_out, c->kc, c->vc, c->layer_stride, g.n_layers, kv, c->F, c->pend_f, g.d_model);
+  const dim3 grid(1, g.n_layers + 1, c->n_active);
+  const KVCache kv = kv_for(c, 0);
+  Pass p{PASS_VERIFY, c->M, c->n_active, 0, 0, 0, 0};
+  pass_ctx(c, p);                                              // (the lengths before this step: fetch_results adds to them)
+#define COMMIT(CT, WALK) k_commit<CT, WALK><<<grid, 1024, 0, c->stream>>>(c->M, c->D + 1, p, c->st, outcome, c->tree_tok, c->path, c->len_out, c->tok_out, c->kc, c->vc, c->layer_stride, g.n_layers, kv, c->F, c->pend_f, g.d_model)
+  if (c->kv_f32) { if (outcome) COMMIT(float, true); else COMMIT(float, false); }
+  else { if (outcome) COMMIT(bf16_t, true); else COMMIT(bf16_t, false); }
+#undef COMMIT
   LAUNCH_CHECK();
   c->phase = 0;
   return EAGLE_OK;
 }
+
+// Acceptance + commit.  pbuf / qbuf (fp32 [n_active][vocab] each, walks over large vocabularies only) and outcome ([n_active][M]) are the
+// kernels' scratch: the caller's workspace, or the library's static device array.
+static int do_accept(eagle_ctx* c, float* pbuf, float* qbuf, int2* outcome) {
+  if (c->phase != 2) return fail(EAGLE_ESTATE, "eagle_accept needs verified logits (call eagle_verify first)");
+  const eagle_config& g = c->cfg;
+  const int B = c->n_active;
+  const dim3 nodes(c->M, B);
+  if (g.temperature <= 0.f)
+    k_outcome<ACCEPT_GREEDY><<<nodes, 1024, 0, c->stream>>>(c->tree_d, c->M, c->st, c->L, c->draft_logits, c->tree_tok, g.vocab, g.temperature, g.seed, outcome);
+  else if (g.vocab <= 32768)
+    k_outcome<ACCEPT_SAMPLED><<<nodes, 1024, CDF_LDS, c->stream>>>(c->tree_d, c->M, c->st, c->L, c->draft_logits, c->tree_tok, g.vocab, g.temperature, g.seed, outcome);
+  else {
+    k_accept<<<B, 1024, 0, c->stream>>>(c->tree_d, c->st, c->L, c->draft_logits, c->tree_tok, g.vocab, g.temperature, g.seed, pbuf, qbuf, c->path, c->tok_out, c->len_out);
+    outcome = nullptr;
+  }
+  LAUNCH_CHECK();
+  return do_commit(c, outcome);
+}
+static int do_accept(eagle_ctx* c) { return do_accept(c, c->pbuf, c->qbuf, c->outcome); }
 
 static int fetch_results(eagle_ctx* c, int32_t* out_tokens, int32_t* out_len, int32_t* path) {
   const int B = c->n_active, D1 = c->D + 1;
@@ -1607,11 +1612,11 @@ extern "C" int eagle_accept_static(eagle_ctx* c, int32_t* out_tokens, int32_t* o
   const eagle_config& g = c->cfg;
   const size_t B = (size_t)c->n_active;
   const size_t vec = (B * g.vocab * 4 + 255) & ~(size_t)255;                  // one fp32 [n_active][vocab] array
-  const size_t need = g.temperature > 0.f ? 2 * vec : B * c->M * 4;
+  const size_t need = std::max(B * c->M * sizeof(int2), g.temperature > 0.f ? 2 * vec : 0);
   if (need > EAGLE_STATIC_SCRATCH_BYTES)
     return fail(EAGLE_EINVAL, "eagle_accept_static: %zu active slots x vocab %d need %zu bytes of scratch, the static array holds %u", B, g.vocab, need, EAGLE_STATIC_SCRATCH_BYTES);
   char* sp = (char*)c->static_scratch;
-  int rc = do_accept(c, (float*)sp, (float*)(sp + vec), (int*)sp);
+  int rc = do_accept(c, (float*)sp, (float*)(sp + vec), (int2*)sp);
   if (rc) return rc;
   return fetch_results(c, out_tokens, out_len, path);
 }
@@ -1784,11 +1789,11 @@ extern "C" int eagle_force_accept(eagle_ctx* c, const int32_t* path, const int32
   }
   HIPCHK(hipMemcpyAsync(c->path, path, (size_t)B * D1 * 4, hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipMemcpyAsync(c->len_out, len, (size_t)B * 4, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpyAsync(c->row_amax, bonus, (size_t)B * 4, hipMemcpyHostToDevice, c->stream));   // (idle scratch: B ints)
+  HIPCHK(hipMemcpyAsync(c->outcome, bonus, (size_t)B * 4, hipMemcpyHostToDevice, c->stream));   // (idle scratch: B ints)
   HIPCHK(hipStreamSynchronize(c->stream));
-  k_force_commit<<<(B + 63) / 64, 64, 0, c->stream>>>(c->tree_d, c->st, c->path, c->len_out, c->row_amax, c->tree_tok, c->tok_out, B);
+  k_force_commit<<<(B + 63) / 64, 64, 0, c->stream>>>(c->tree_d, c->st, c->path, c->len_out, (const int*)c->outcome, c->tree_tok, c->tok_out, B);
   LAUNCH_CHECK();
-  int rc = do_compact(c);
+  int rc = do_commit(c, nullptr);
   if (rc) return rc;
   return fetch_results(c, nullptr, nullptr, nullptr);
 }

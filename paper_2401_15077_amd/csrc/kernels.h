@@ -19,7 +19,7 @@ struct SeqState {          // all device pointers, one entry per sequence slot
   int* n_pend;             // target features waiting for the head's first pass (1..D+1)
   int* n_tok;              // committed tokens (= ctx_len + 1 between steps)
   int* step_no;            // draw counter for the generator
-  int* commit_base;        // ctx_len before the last commit (read by the compaction kernel)
+  int* commit_base;        // ctx_len before the last commit (read by the commit kernel)
   int* tokens;             // [max_batch][tok_stride]
   int tok_stride;
 };
@@ -1757,31 +1757,102 @@ __global__ __launch_bounds__(1024) void k_choose(SeqState st, int seq0, const fl
   }
 }
 
-// Acceptance (Sec. 2; App. A.2, Alg. 1 applied recursively at every node).  Block = one sequence.
+// Acceptance (Sec. 2; App. A.2, Alg. 1 applied recursively at every node).
 //   greedy : follow the child whose token equals argmax of the target logits at the current node
 //   T > 0  : children in rank order, accept child i when r * q_i(t_i) < p(t_i); on rejection
 //            p <- norm(max(0, p - q_i)) and q_{i+1} = q_i without t_i, renormalised (children were drawn
 //            without replacement); when nothing is accepted draw the bonus token from what is left of p.
-// arg-max token of every row of logits (lowest id among equals), one block per row: the greedy walk below visits up
-// to depth + 1 nodes one after the other, and scanning their rows there would run on a single CU
-__global__ __launch_bounds__(1024) void k_row_argmax(const float* __restrict__ L, int V, int* __restrict__ amax) {
-  __shared__ unsigned long long shk[16];
-  const int bi = row_argmax(L + (size_t)blockIdx.x * V, V, shk);
-  if (threadIdx.x == 0) amax[blockIdx.x] = bi;
+// What happens at a node depends on the node alone (its rows, its children, random numbers named after the nodes), not on how the walk came
+// there.  So every node's outcome -- the child that is accepted or -1, and the token that follows the path if it ends there -- is found at once,
+// a work-group a node, and the walk is a few look-ups (k_commit).
+enum { ACCEPT_GREEDY, ACCEPT_SAMPLED };
+struct AcceptShared { float v[16]; double f[1025 + 16]; int res, next; float pt, qt; };
+// T > 0 at one node, target and proposal in registers (see reg_softmax); the child that is accepted, else -1 and the bonus token.
+__device__ inline int sample_node(const TreeDev* tree, const float* L, const float* draft_logits, const int* tree_tok, int V, float temperature, unsigned long long rng_seed,
+                                  int step, int seq, int M, int cur, float* ps, AcceptShared& sh, int* bonus) {
+  const float* lg = L + ((size_t)seq * M + cur) * V;
+  const int nk = tree->nchild[cur];
+  const int tid = threadIdx.x;
+  const float invT = 1.0f / temperature;
+  float p[VPT], q[VPT];
+  reg_softmax(lg, p, V, invT, sh.v);
+  if (nk > 0) reg_softmax(draft_logits + ((size_t)seq * M + cur) * V, q, V, invT, sh.v);
+  if (tid == 0) sh.next = -1;
+  for (int r = 0; r < nk; ++r) {
+    const int c = tree->child[cur][r];
+    const int t = __builtin_amdgcn_readfirstlane(tree_tok[seq * M + c]);
+    const float rr = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_ACCEPT, (unsigned long long)step), (uint32_t)seq, (uint32_t)c, 0) * 5.9604644775390625e-8f;
+    float sm = 0.f, qs = 0.f;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+      if (u * 1024 >= V) continue;
+      if (tid == t - u * 1024) { sh.pt = p[u]; sh.qt = q[u]; }
+      sm += fmaxf(p[u] - q[u], 0.f);
+    }
+    __syncthreads();
+    if (rr * sh.qt < sh.pt) { if (tid == 0) sh.next = c; break; }
+    // residual target, proposal without t
+    sm = block_sum(sm, sh.v);
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+      if (u * 1024 >= V) continue;
+      if (sm > 1e-20f) p[u] = fmaxf(p[u] - q[u], 0.f) / sm;
+      if (tid == t - u * 1024) q[u] = 0.f;
+      qs += q[u];
+      if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    qs = block_sum(qs, sh.v);
+    if (qs > 0.f)
+#pragma unroll
+      for (int u = 0; u < VPT; ++u) {
+        q[u] /= qs;
+        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+    __syncthreads();                                            // (sh.pt, sh.qt and sh.v are written again)
+  }
+  __syncthreads();
+  const int next = sh.next;
+  if (next < 0) {
+    const float u = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_FINAL, (unsigned long long)step), (uint32_t)seq, (uint32_t)cur, 0) * 5.9604644775390625e-8f;
+    *bonus = reg_inverse_cdf(p, V, u, ps, sh.f, &sh.res);
+  }
+  return next;
 }
 
-enum { ACCEPT_GREEDY, ACCEPT_SAMPLED, ACCEPT_SAMPLED_BIGV };   // BIGV: more than 32768 vocabulary entries
+// The outcome of every node (block = node, sequence; at most 128 of them), and where the commit begins.  Sampled, us a launch at 32000 entries: a chain
+// of six nodes 60 along the walk / 35, 26 nodes 117 / 38.
 template <int KIND>
+__global__ __launch_bounds__(1024) void k_outcome(const TreeDev* tree, int M, SeqState st, const float* L /*[seq][M][V]*/, const float* draft_logits, const int* tree_tok, int V,
+                                                  float temperature, unsigned long long rng_seed, int2* outcome /*[seq][M]: next node or -1, token*/) {
+  const int node = blockIdx.x, seq = blockIdx.y;
+  if (node == 0 && threadIdx.x == 0) st.commit_base[seq] = st.ctx_len[seq];
+  int2 o;
+  if constexpr (KIND == ACCEPT_GREEDY) {
+    __shared__ unsigned long long shk[16];
+    const int lane = threadIdx.x & 63, nk = read_only(tree->nchild + node);
+    const int child = tree->child[node][min(lane, EAGLE_MAX_CHILD - 1)];
+    const int tok = lane < nk ? tree_tok[seq * M + child] : -1;
+    o.y = row_argmax(L + ((size_t)seq * M + node) * V, V, shk);   // (every thread has it)
+    const unsigned long long hit = __ballot(tok == o.y);
+    o.x = hit ? __builtin_amdgcn_readlane(child, __ffsll((long long)hit) - 1) : -1;
+  } else {
+    __shared__ AcceptShared sh;
+    extern __shared__ __attribute__((aligned(16))) float ps[];
+    o.y = 0;
+    o.x = sample_node(tree, L, draft_logits, tree_tok, V, temperature, rng_seed, st.step_no[seq], seq, M, node, ps, sh, &o.y);
+  }
+  if (threadIdx.x == 0) outcome[seq * M + node] = o;
+}
+
+// T > 0, vocabularies beyond 32768 entries: the walk of one sequence by one block, node after node, over two vectors in memory.
 __global__ __launch_bounds__(1024) void k_accept(const TreeDev* tree, SeqState st, const float* L /*[seq][M][V]*/,
                                                  const float* draft_logits, const int* tree_tok, int V, float temperature,
                                                  unsigned long long rng_seed, float* pbuf, float* qbuf,
-                                                 int* path_out /*[seq][D+1]*/, int* tok_out, int* len_out,
-                                                 const int* __restrict__ amax /*[seq][M], greedy only*/) {
-  __shared__ float shv[16];
-  __shared__ double sh_f[1025 + 16];
-  __shared__ int res, s_next;
-  __shared__ float s_pt, s_qt;
-  extern __shared__ __attribute__((aligned(16))) float ps[];
+                                                 int* path_out /*[seq][D+1]*/, int* tok_out, int* len_out) {
+  __shared__ AcceptShared sh;
+  float* shv = sh.v;
+  double* sh_f = sh.f;
+  int &res = sh.res, &s_next = sh.next;
   const int seq = blockIdx.x, M = tree->M, D1 = tree->D + 1;
   int cur = 0, len = 1, bonus = 0;
   if (threadIdx.x == 0) path_out[seq * D1] = 0;
@@ -1789,100 +1860,41 @@ __global__ __launch_bounds__(1024) void k_accept(const TreeDev* tree, SeqState s
   while (true) {
     const float* lg = L + ((size_t)seq * M + cur) * V;
     const int nk = tree->nchild[cur];
-    if constexpr (KIND == ACCEPT_GREEDY) {
-      const int bi = amax[seq * M + cur];
-      if (threadIdx.x == 0) {
-        s_next = -1;
-        for (int r = 0; r < nk; ++r) {
-          int c = tree->child[cur][r];
-          if (tree_tok[seq * M + c] == bi) { s_next = c; break; }
-        }
-      }
+    float* p = pbuf + (size_t)seq * V;
+    float* q = qbuf + (size_t)seq * V;
+    const float invT = 1.0f / temperature;
+    block_softmax(lg, p, V, invT, shv);
+    if (nk > 0) block_softmax(draft_logits + ((size_t)seq * M + cur) * V, q, V, invT, shv);
+    if (threadIdx.x == 0) s_next = -1;
+    __syncthreads();
+    for (int r = 0; r < nk; ++r) {
+      const int c = tree->child[cur][r];
+      const int t = tree_tok[seq * M + c];
+      float rr = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_ACCEPT, (unsigned long long)step), (uint32_t)seq, (uint32_t)c, 0) * 5.9604644775390625e-8f;
+      bool ok = rr * q[t] < p[t];
       __syncthreads();
-      if (s_next < 0) { bonus = bi; break; }
-    } else if constexpr (KIND == ACCEPT_SAMPLED) {
-      // target and proposal of the node in registers (see reg_softmax); the same sums as below
-      const int tid = threadIdx.x;
-      const float invT = 1.0f / temperature;
-      float p[VPT], q[VPT];
-      reg_softmax(lg, p, V, invT, shv);
-      if (nk > 0) reg_softmax(draft_logits + ((size_t)seq * M + cur) * V, q, V, invT, shv);
-      if (tid == 0) s_next = -1;
-      for (int r = 0; r < nk; ++r) {
-        const int c = tree->child[cur][r];
-        const int t = __builtin_amdgcn_readfirstlane(tree_tok[seq * M + c]);
-        const float rr = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_ACCEPT, (unsigned long long)step), (uint32_t)seq, (uint32_t)c, 0) * 5.9604644775390625e-8f;
-        float sm = 0.f, qs = 0.f;
-#pragma unroll
-        for (int u = 0; u < VPT; ++u) {
-          if (u * 1024 >= V) continue;
-          if (tid == t - u * 1024) { s_pt = p[u]; s_qt = q[u]; }
-          sm += fmaxf(p[u] - q[u], 0.f);
-        }
-        __syncthreads();
-        if (rr * s_qt < s_pt) { if (tid == 0) s_next = c; break; }
-        // residual target, proposal without t
-        sm = block_sum(sm, shv);
-#pragma unroll
-        for (int u = 0; u < VPT; ++u) {
-          if (u * 1024 >= V) continue;
-          if (sm > 1e-20f) p[u] = fmaxf(p[u] - q[u], 0.f) / sm;
-          if (tid == t - u * 1024) q[u] = 0.f;
-          qs += q[u];
-          if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-        qs = block_sum(qs, shv);
-        if (qs > 0.f)
-#pragma unroll
-          for (int u = 0; u < VPT; ++u) {
-            q[u] /= qs;
-            if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-          }
-        __syncthreads();                                        // (s_pt, s_qt and shv are written again)
-      }
+      if (ok) { if (threadIdx.x == 0) s_next = c; break; }
+      // residual target, proposal without t
+      float sm = 0.f;
+      for (int j = threadIdx.x; j < V; j += blockDim.x) { float d = fmaxf(p[j] - q[j], 0.f); sm += d; }
+      sm = block_sum(sm, shv);
+      if (sm > 1e-20f)
+        for (int j = threadIdx.x; j < V; j += blockDim.x) p[j] = fmaxf(p[j] - q[j], 0.f) / sm;
       __syncthreads();
-      if (s_next < 0) {
-        const float u = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_FINAL, (unsigned long long)step), (uint32_t)seq, (uint32_t)cur, 0) * 5.9604644775390625e-8f;
-        bonus = reg_inverse_cdf(p, V, u, ps, sh_f, &res);
-        break;
-      }
-    } else {
-      float* p = pbuf + (size_t)seq * V;
-      float* q = qbuf + (size_t)seq * V;
-      const float invT = 1.0f / temperature;
-      block_softmax(lg, p, V, invT, shv);
-      if (nk > 0) block_softmax(draft_logits + ((size_t)seq * M + cur) * V, q, V, invT, shv);
-      if (threadIdx.x == 0) s_next = -1;
+      if (threadIdx.x == 0) q[t] = 0.f;
       __syncthreads();
-      for (int r = 0; r < nk; ++r) {
-        const int c = tree->child[cur][r];
-        const int t = tree_tok[seq * M + c];
-        float rr = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_ACCEPT, (unsigned long long)step), (uint32_t)seq, (uint32_t)c, 0) * 5.9604644775390625e-8f;
-        bool ok = rr * q[t] < p[t];
-        __syncthreads();
-        if (ok) { if (threadIdx.x == 0) s_next = c; break; }
-        // residual target, proposal without t
-        float sm = 0.f;
-        for (int j = threadIdx.x; j < V; j += blockDim.x) { float d = fmaxf(p[j] - q[j], 0.f); sm += d; }
-        sm = block_sum(sm, shv);
-        if (sm > 1e-20f)
-          for (int j = threadIdx.x; j < V; j += blockDim.x) p[j] = fmaxf(p[j] - q[j], 0.f) / sm;
-        __syncthreads();
-        if (threadIdx.x == 0) q[t] = 0.f;
-        __syncthreads();
-        float qs = 0.f;
-        for (int j = threadIdx.x; j < V; j += blockDim.x) qs += q[j];
-        qs = block_sum(qs, shv);
-        if (qs > 0.f)
-          for (int j = threadIdx.x; j < V; j += blockDim.x) q[j] = q[j] / qs;
-        __syncthreads();
-      }
+      float qs = 0.f;
+      for (int j = threadIdx.x; j < V; j += blockDim.x) qs += q[j];
+      qs = block_sum(qs, shv);
+      if (qs > 0.f)
+        for (int j = threadIdx.x; j < V; j += blockDim.x) q[j] = q[j] / qs;
       __syncthreads();
-      if (s_next < 0) {
-        float u = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_FINAL, (unsigned long long)step), (uint32_t)seq, (uint32_t)cur, 0) * 5.9604644775390625e-8f;
-        bonus = block_inverse_cdf(p, V, u, sh_f, &res);
-        break;
-      }
+    }
+    __syncthreads();
+    if (s_next < 0) {
+      float u = (float)rng_u24(rng_prefix(rng_seed, PURPOSE_FINAL, (unsigned long long)step), (uint32_t)seq, (uint32_t)cur, 0) * 5.9604644775390625e-8f;
+      bonus = block_inverse_cdf(p, V, u, sh_f, &res);
+      break;
     }
     cur = s_next;
     if (threadIdx.x == 0) path_out[seq * D1 + len] = cur;
@@ -1907,44 +1919,93 @@ __global__ __launch_bounds__(1024) void k_accept(const TreeDev* tree, SeqState s
 // Commit (Sec. 3.3: accepted tokens and their features are kept): for every layer, KV rows of the accepted
 // nodes move from slot base+path[i] to base+i, and the accepted nodes' target features become the pending
 // features of the next drafting phase.  ONE launch: blockIdx.y = layer (last y = the feature rows).
-// A thread owns one 16-byte column of a row and moves i = 1..len-1 in increasing order; since path[i] >= i and
+// A thread owns one 16-byte column of a row and moves i = 1..len-1 in increasing order, four at a time; since path[i] >= i and
 // path is increasing, a destination is never a source that is still to be read.
-template <typename CT>
-__global__ __launch_bounds__(256) void k_compact(const TreeDev* tree, SeqState st, const int* path, const int* len_p,
-                                                 void* kcache, void* vcache, size_t layer_stride_elems, int n_layers,
-                                                 KVCache kv, const float* F /*[seq][M][d]*/, float* pend_f, int d) {
-  const int seq = blockIdx.z, layer = blockIdx.y;
-  const int D1 = tree->D + 1, M = tree->M;
-  const int len = len_p[seq];
-  const int* pth = path + seq * D1;
+// WALK: the path is not there yet; every block finds it from the nodes' outcomes, and the block of the features writes it and the sequence's new
+// state, which no other block reads (they begin at commit_base).  us a step, 26 nodes, 7B: arg-max 6.7, walk 7.3 and
+// this 10.4 / now outcomes 7.7 and this 10.6.  (132 blocks of 256 threads instead of a block a layer: 14.3; each first reads the same few lines, and the XCDs
+// get those one after the other.)
+template <typename CT, bool WALK>
+__global__ __launch_bounds__(1024) void k_commit(int M, int D1, Pass pass /*cached lengths, where the host knows them*/, SeqState st, const int2* __restrict__ outcome, const int* __restrict__ tree_tok, int* path, int* len_p, int* tok_out,
+                                                void* kcache, void* vcache, size_t layer_stride_elems, int n_layers, KVCache kv,
+                                                const float* __restrict__ F /*[seq][M][d]*/, float* __restrict__ pend_f, int d) {
+  __shared__ int2 s_out[EAGLE_MAX_NODES];
+  __shared__ int s_path[EAGLE_MAX_DEPTH + 1], s_len, s_bonus;
+  const int seq = blockIdx.z, layer = blockIdx.y, tid = threadIdx.x;
+  int base;
+  if (pass.ctx_known) base = seq == 0 ? pass.ctx0 : seq == 1 ? pass.ctx1 : seq == 2 ? pass.ctx2 : pass.ctx3;
+  else base = __builtin_amdgcn_readfirstlane(st.commit_base[seq]);
+  if (WALK) {
+    if (tid < M) s_out[tid] = outcome[seq * M + tid];
+  } else if (tid < D1) s_path[tid] = path[seq * D1 + tid];
+  // pages of the new rows (at most 64 of them, in pages of at least 32 tokens)
+  const int p0 = base >> kv.page_shift;
+  int page[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) page[i] = kv.page_table[seq * kv.pages_per_seq + min(p0 + i, kv.pages_per_seq - 1)];
+  if (!WALK && tid == 0) s_len = len_p[seq];
+  __syncthreads();
+  if (WALK) {
+    if (tid == 0) {
+      int cur = 0, len = 1;
+      s_path[0] = 0;
+      for (int2 o = s_out[0]; o.x >= 0 && len < D1; o = s_out[cur]) { cur = o.x; s_path[len++] = cur; }
+      s_len = len; s_bonus = s_out[cur].y;
+    }
+    __syncthreads();
+  }
+  const int len = s_len;
   if (layer == n_layers) {
-    for (int i = 0; i < len; ++i) {
-      const float* src = F + ((size_t)seq * M + pth[i]) * d;
-      float* dst = pend_f + ((size_t)seq * D1 + i) * d;
-      for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < d; k += gridDim.x * blockDim.x) dst[k] = src[k];
+    const int step = 4 * (int)(gridDim.x * blockDim.x);
+    for (int i0 = 0; i0 < len; i0 += 4)
+      for (int k = 4 * (int)(blockIdx.x * blockDim.x + tid); k < d; k += step) {
+        f32x4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *(const f32x4*)(F + ((size_t)seq * M + s_path[min(i0 + i, len - 1)]) * d + k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (i0 + i < len) *(f32x4*)(pend_f + ((size_t)seq * D1 + i0 + i) * d + k) = v[i];
+      }
+    if (WALK && blockIdx.x == 0 && tid < len) {                // (len <= 16: lanes of the first wave)
+      const int n = st.n_tok[seq], steps = st.step_no[seq];
+      const int t = tid + 1 < len ? tree_tok[seq * M + s_path[tid + 1]] : s_bonus;
+      path[seq * D1 + tid] = s_path[tid];
+      tok_out[seq * D1 + tid] = t;
+      st.tokens[(size_t)seq * st.tok_stride + n + tid] = t;
+      if (tid == 0) {
+        len_p[seq] = len;
+        st.n_tok[seq] = n + len; st.ctx_len[seq] = base + len; st.n_pend[seq] = len; st.step_no[seq] = steps + 1;
+      }
     }
     return;
   }
-  const int base = st.commit_base[seq];
+  int first = 1;                                               // rows up to the first that moves stay (behind it all move)
+  while (first < len && s_path[first] == first) ++first;
   constexpr int EPC = 16 / sizeof(CT);                        // elements per 16-byte column
-  const int cols = kv.n_kv_heads * kv.head_dim / EPC;
-  kv.k = (CT*)kcache + (size_t)layer * layer_stride_elems;
-  kv.v = (CT*)vcache + (size_t)layer * layer_stride_elems;
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < 2 * cols; c += gridDim.x * blockDim.x) {
-    const int which = c / cols, cc = c % cols;
-    const int kvh = cc * EPC / kv.head_dim, off = cc * EPC % kv.head_dim;
-    CT* cache = (CT*)(which ? kv.v : kv.k);
-    for (int i = 1; i < len; ++i) {
-      if (pth[i] == i) continue;
-      u32x4 val = *(const u32x4*)(cache + kv_offset(kv, seq, base + pth[i], kvh) + off);
-      *(u32x4*)(cache + kv_offset(kv, seq, base + i, kvh) + off) = val;
+  const int cols = kv.n_kv_heads * kv.head_dim / EPC, dh_shift = 31 - __builtin_clz(kv.head_dim);
+  const uint32_t mask = (1u << kv.page_shift) - 1;
+  for (int c = blockIdx.x * blockDim.x + tid; c < 2 * cols; c += gridDim.x * blockDim.x) {
+    const int cc = c >= cols ? c - cols : c;
+    const int kvh = cc * EPC >> dh_shift, off = cc * EPC & (kv.head_dim - 1);
+    CT* cache = (CT*)(c >= cols ? vcache : kcache) + (size_t)layer * layer_stride_elems + off;
+    auto row_at = [&](int i) {
+      const int pos = base + i, k = (pos >> kv.page_shift) - p0;
+      const int phys = k == 0 ? page[0] : k == 1 ? page[1] : page[2];
+      return (u32x4*)(cache + ((((size_t)phys * kv.n_kv_heads + kvh) << kv.page_shift) + (pos & mask) << dh_shift));
+    };
+    for (int i0 = first; i0 < len; i0 += 4) {
+      u32x4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = *row_at(s_path[min(i0 + i, len - 1)]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i0 + i < len) *row_at(i0 + i) = v[i];
     }
   }
 }
 
-// Commit of paths handed in by the caller instead of found by k_accept (lock-step tests drive the engine along the
-// oracle's choices with it): the bookkeeping at the end of k_accept, for every sequence.  bonus[seq] = the token that
-// follows the accepted drafts.  k_compact runs afterwards as in a normal step.
+// Commit of paths handed in by the caller instead of found by acceptance (lock-step tests drive the engine along the
+// oracle's choices with it): the bookkeeping at the end of a step, for every sequence.  bonus[seq] = the token that
+// follows the accepted drafts.  k_commit runs afterwards along the given path.
 __global__ void k_force_commit(const TreeDev* tree, SeqState st, const int* path /*[seq][D+1]*/, const int* len_p,
                                const int* bonus, const int* tree_tok, int* tok_out, int n_seq) {
   const int seq = blockIdx.x * blockDim.x + threadIdx.x;

@@ -1475,8 +1475,8 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_xk(Gemm2 g) {
 // partial sums of squares, one column slab per block (the same outputs a residual epilogue produces).
 template <typename EmbT, int NXP>
 __global__ __launch_bounds__(256) void k2_embed(Pass pass, const TreeDev* tree, SeqState st, const int* tree_tok,
-                                                const EmbT* __restrict__ embed, int vocab, int M, int d, float* h,
-                                                const float* gain, bf16_t* xf_out, float* ssq_out, KVCache kv, RowFact* facts) {
+                                                const EmbT* __restrict__ embed, int vocab, int M, int nodes /*of the tree*/, int d, float* h,
+                                                const float* __restrict__ gain, bf16_t* xf_out, float* ssq_out, KVCache kv, RowFact* facts) {
   __shared__ float sh[8 * 32];
   const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;          // 8 slots
   const int grp = blockIdx.x, groups = gridDim.x;
@@ -1485,23 +1485,24 @@ __global__ __launch_bounds__(256) void k2_embed(Pass pass, const TreeDev* tree, 
   int tok = 0;
   if (live) {
     RowInfo ri = row_info(pass, tree, st, m);
-    if (pass.kind == PASS_VERIFY) tok = tree_tok[ri.seq * tree->M + ri.node];
+    if (pass.kind == PASS_VERIFY) tok = tree_tok[ri.seq * nodes + ri.node];
     else tok = st.tokens[(size_t)ri.seq * st.tok_stride + ri.pos];
     tok = min(max(tok, 0), vocab - 1);
     if (blockIdx.x == 0 && slot == 0) facts[m] = row_fact(pass, tree, ri, kv);
   }
   float ss = 0.f;
   for (int c = c0 + slot; c < c1; c += 8) {
-    float x[8];
+    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, gn[8];
+    embed8(gain + 8 * c, gn);
+    if (live) {
+      embed8(embed + (size_t)tok * d + 8 * c, x);
+      *(f32x4*)(h + (size_t)m * d + 8 * c) = f32x4{x[0], x[1], x[2], x[3]};
+      *(f32x4*)(h + (size_t)m * d + 8 * c + 4) = f32x4{x[4], x[5], x[6], x[7]};
+    }
+#pragma unroll
     for (int t = 0; t < 8; ++t) {
-      float v = 0.f;
-      if (live) {
-        if constexpr (sizeof(EmbT) == 4) v = ((const float*)embed)[(size_t)tok * d + 8 * c + t];
-        else v = bf16_to_f32(((const bf16_t*)embed)[(size_t)tok * d + 8 * c + t]);
-        h[(size_t)m * d + 8 * c + t] = v;
-      }
-      ss += v * v;
-      x[t] = v * gain[8 * c + t];
+      ss += x[t] * x[t];
+      x[t] *= gn[t];
     }
     if (live) xf_store8(xf_out, m, 8 * c, 1, d / 16, NXP, x);
   }
@@ -1520,10 +1521,22 @@ __global__ __launch_bounds__(256) void k2_features(Pass pass, const TreeDev* tre
                                                    int d, float* __restrict__ node_dst, float* __restrict__ pend_dst, float* __restrict__ chunk_dst) {
   __shared__ float tmp[17];
   const int m = blockIdx.x;
+  constexpr int AHEAD = 4;                                      // chunks requested before the row's scale is known
+  f32x4 hv[AHEAD], gv[AHEAD];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) {
+    const int k = min(4 * (int)threadIdx.x + 1024 * i, d - 4);
+    hv[i] = *(const f32x4*)(h + (size_t)m * d + k); gv[i] = *(const f32x4*)(gain + k);
+  }
   float* dst = feature_row(pass, tree, st, m, node_dst, pend_dst, chunk_dst, d);
   const float r = block_row_rstd(rs.ssq, rs.groups, rs.inv_d, rs.eps, m, tmp);
   if (!dst) return;
-  for (int k = 4 * threadIdx.x; k < d; k += 1024) *(f32x4*)(dst + k) = *(const f32x4*)(h + (size_t)m * d + k) * r * *(const f32x4*)(gain + k);
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) {
+    const int k = 4 * (int)threadIdx.x + 1024 * i;
+    if (k < d) *(f32x4*)(dst + k) = hv[i] * r * gv[i];
+  }
+  for (int k = 4 * (int)threadIdx.x + 1024 * AHEAD; k < d; k += 1024) *(f32x4*)(dst + k) = *(const f32x4*)(h + (size_t)m * d + k) * r * *(const f32x4*)(gain + k);
 }
 
 // ============================================================================ tree-masked paged attention, <= 32 rows per sequence
