@@ -909,8 +909,8 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
   // last one, a wave's 32 came as 35 or 36 at K = 4096 and O's 8 as 12, on the L2 -> CU path that binds these kernels; requested out
   // of range they move nothing and still cost more than a branch.  26 rows at 7B, us clamped / out of range / branch: QKV 25.3 /
   // 25.9 / 24.7, gate/up 35.4 / 36.0 / 34.7, O 13.6 / 13.3 / 12.5, down 24.0 / 23.5 / 23.5.  Four row blocks, whose depth divides
-  // the usual K: LM head 44.8 / 45.9 / 45.5, so they keep one loop.  A wave with fewer k-steps than DEPTH -- K below 1024 in bf16 and
-  // 512 in fp32 -- still fills its ring with the last one above.)
+  // the usual K: LM head 44.8 / 45.9 / 45.5, so they keep one loop.  A wave with fewer k-steps than DEPTH still fills its
+  // ring with the last one above, but for one row block and at most half of the ring: fk_stream_dispatch.)
   constexpr bool EXACT = NR < 4;
   for (; k + (EXACT ? 2 * DEPTH - 1 : DEPTH) < ke; k += DEPTH) {
 #pragma unroll
@@ -936,8 +936,13 @@ __device__ __forceinline__ void fk_stream(const bf16_t* __restrict__ XF, int KS,
 template <int NWP, int NXP, int NR, class F>
 __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int KS, bool row, int kb, int ke, const FkWeights<NWP>& fw, f32x16* acc, int lane, F&& behind) {
   constexpr int DEPTH = NWP == 1 ? (NR == 1 ? 8 : NR == 2 ? 6 : NR == 3 ? 5 : 4) : NR == 1 ? 4 : 2;   // ~24 KiB in flight per wave; deeper measured the same
-  if (nr == NR) fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, row, kb, ke, fw, acc, lane, behind);
-  else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, row, kb, ke, fw, acc, lane, behind);
+  if (nr == NR) {
+    // (small matrices: a ring of no more k-steps than the wave has.  Clamped to the last one, a launch at d 256 in fp32 fetched every tile twice: tiny request
+    // 5.82 -> 5.37 ms)
+    if constexpr (NR == 1)
+      if (ke - kb <= DEPTH / 2) return fk_stream<NWP, NXP, NR, DEPTH / 2>(XF, KS, row, kb, ke, fw, acc, lane, behind);
+    fk_stream<NWP, NXP, NR, DEPTH>(XF, KS, row, kb, ke, fw, acc, lane, behind);
+  } else if constexpr (NR > 1) fk_stream_dispatch<NWP, NXP, NR - 1>(nr, XF, KS, row, kb, ke, fw, acc, lane, behind);
   else behind();                                               // (no row block: nothing to multiply)
 }
 
