@@ -1100,11 +1100,28 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
       return EAGLE_OK;
     }
   }
-  if (w.q4 && c->q4_staged && (g.epi == EPI_RESID || (w.NRB + 2) / 3 > c->n_cu)) {   // (or too many row blocks for one round of whole-K work-groups: the LM head)
-    // 4-bit weights, the LM head (and narrow matrices the streamed split-K plan cannot take): split-K with the activation
+  if (w.q4 && g.epi == EPI_LOGITS && w.NRB > 3 * c->n_cu && w.NRB <= LQ4_BLOCKS * c->n_cu) {
+    // the LM head: one round of whole-K work-groups of four row blocks.  (Fewer blocks fit three a work-group, below; more, vocabularies beyond
+    // 32768, would be a second round.)  us a launch at the ends of the range, staged split-K / this, 26 rows, K 4096: 24608 tokens 25 / 20, 32768 29 / 21
+    constexpr size_t lds = (size_t)4 * LQ4_BLOCKS * 4096;
+    g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
+    g.trace = nullptr;
+    const Share sh = share_of(w.NRB, c->n_cu);
+    g.groups = c->n_cu; g.share_a = sh.a; g.share_b = sh.b;
+    static bool attr_set = false;
+    if (!attr_set) {
+      HIPCHK(hipFuncSetAttribute((const void*)k2_logits_q4, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+      attr_set = true;
+    }
+    e = launch_k(c, c->cur_class, bytes, "k2_logits_q4", k2_logits_q4, dim3(c->n_cu), dim3(V2_THREADS), lds, g);
+    if (e != hipSuccess) return fail(EAGLE_EHIP, "4-bit gemm launch failed: %s", hipGetErrorString(e));
+    return EAGLE_OK;
+  }
+  if (w.q4 && c->q4_staged && (g.epi == EPI_RESID || (w.NRB + 2) / 3 > c->n_cu)) {   // (or too many row blocks for one round of whole-K work-groups: larger LM heads)
+    // 4-bit weights, LM heads of more than 32768 tokens (and narrow matrices the streamed split-K plan cannot take): split-K with the activation
     // slice staged in LDS.  With a quarter of the weight bytes the activation fragments are most of what a CU fetches;
     // staged, a work-group fetches its K slice of them once.  (Measured at d = 4096: O 12.0 us against 14.6 whole-K, down
-    // 24.5 against 29.0, LM head 37.7 against 39.7; the wide matrices are faster whole-K: QKV 20.2 against 27.3, measured
+    // 24.5 against 29.0; the wide matrices are faster whole-K: QKV 20.2 against 27.3, measured
     // before, since their epilogues would run on 64 CUs only.)
     g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;

@@ -1073,7 +1073,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t q4_codes(const bf16_t* W, int 
 }
 
 // The waves' accumulators parked in LDS as red[w][j][i][lane], 16 bytes each = registers 4i..4i+3 (MFMA layout: rows 8i + 4*(lane/32)
-// + 0..3 of row block j, token lane%32).  Sum over the 8 waves, in order, of the four rows 4*qd.. of block j, token m.
+// + 0..3 of row block j, token lane%32).  Sum over the waves, in order, of the four rows 4*qd.. of block j, token m.
 __device__ __forceinline__ void fk_park(float* red, int nrmax, int w, int j, int lane, const f32x16& acc) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -1081,10 +1081,11 @@ __device__ __forceinline__ void fk_park(float* red, int nrmax, int w, int j, int
     *(f32x4*)(red + ((((size_t)w * nrmax + j) * 4 + i) * 64 + lane) * 4) = v;
   }
 }
+template <int NW = 8>
 __device__ __forceinline__ f32x4 fk_sum4(const float* red, int nrmax, int j, int qd, int m) {
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int w = 0; w < 8; ++w) a += *(const f32x4*)(red + ((((size_t)w * nrmax + j) * 4 + (qd >> 1)) * 64 + m + 32 * (qd & 1)) * 4);
+  for (int w = 0; w < NW; ++w) a += *(const f32x4*)(red + ((((size_t)w * nrmax + j) * 4 + (qd >> 1)) * 64 + m + 32 * (qd & 1)) * 4);
   return a;
 }
 // HALF: the unit of the work split is half a row block (16 weight rows) instead of a whole one, for matrices whose
@@ -1237,6 +1238,60 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
     }
   }
   TRACE_STAMP(tr, 4);
+}
+
+// ---- whole-K LM head over 4-bit weights -----------------------------------------------------------------------------------------
+// Up to four row blocks a work-group, their sums scaled into logits in place: more than three blocks do not fit k2_gemm_fk's waves, so the
+// LM head ran split over K with the activations in LDS (k2_gemm), and every K slice wrote and read back its sums of the whole vocabulary.
+// Here wave w takes blocks 2 (w % 2) and on over K part w / 2, two waves a SIMD; the two waves of a part ask for the same activations one
+// after the other.  us a launch, k2_gemm / here, 32000 tokens, 26 rows and 1 to 4: 4096 columns 28 / 20.4 and 33 / 25.4 (a request's mean, in its
+// trace, 30.8 / 22.8), 5120 35 / 27 and 40 / 33, 8192 66 / 44 and 76 / 53, 256 8.6 / 5.4; 24608 tokens of 4096 25 / 20.  Four waves of
+// four blocks each (360 registers): 23.7 for 22.8.  Bound: instructions (expanding codes and folding groups beside the MFMAs) and 32 KB of codes
+// in flight a CU; the codes' 65 MB take 11 us at 6 TB/s.
+constexpr int LQ4_BLOCKS = 4;
+__global__ __launch_bounds__(V2_THREADS) void k2_logits_q4(Gemm2 g) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ float sh_small[16 * 32];
+  float* red = (float*)smem;                                    // [4 K parts][LQ4_BLOCKS][16][64]
+  pin_args(g);
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const uint32_t NRB = g.NRB;
+  const int rb0 = share_begin(blockIdx.x, NRB, g.share_a, g.share_b), rb1 = share_begin(blockIdx.x + 1, NRB, g.share_a, g.share_b), nr = rb1 - rb0;   // <= LQ4_BLOCKS (host)
+  const int pair = w & 1, part = w >> 1, mine = min(max(nr - 2 * pair, 0), 2), first = min(rb0 + 2 * pair, g.NRB - 1);
+  EarlyLoads el;
+  Gemm2 e;                                                      // the arguments as the epilogue reads them
+  auto early = [&] {
+    e = late_args();
+    early_issue(g.in_scale.ssq, g.facts, el);
+  };
+  f32x16 acc[2];
+  const int gb = (unsigned)part * (unsigned)g.NG / 4u, ge = (unsigned)(part + 1) * (unsigned)g.NG / 4u;
+  const u32x4* sq[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(first + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
+  fk_stream_q4_dispatch<2, 2>(mine, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(g.W, first, mine, g.KS), sq, g.NG, acc, lane, early);
+  const int m = threadIdx.x & 31, slot = threadIdx.x >> 5;      // 16 slots of 32 tokens
+  const bool live = m < e.M;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    if (j < mine) fk_park(red, LQ4_BLOCKS, part, 2 * pair + j, lane, acc[j]);
+  block_rstd_park(e.in_scale, early_ssq(e.in_scale, el), sh_small);
+  __syncthreads();
+  const float rs = live ? block_rstd(e.in_scale, sh_small, m) : 0.f;
+  const int nend = min(e.N, e.V);
+  const bool vec = (e.V & 3) == 0;
+  const long dst = live && el.out_row >= 0 ? (long)el.out_row * e.V : -1;
+  for (int it = slot; it < nr * 8; it += 16) {                  // item = (row block j, quad of 4 rows)
+    const int j = it >> 3, qd = it & 7;
+    const int n = (rb0 + j) * 32 + 4 * qd;
+    if (dst < 0 || n >= nend) continue;
+    const f32x4 v = fk_sum4<4>(red, LQ4_BLOCKS, j, qd, m) * rs;
+    if (vec && n + 4 <= nend) *(f32x4*)(e.logits + dst + n) = v;
+    else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) if (n + t < nend) e.logits[dst + n + t] = v[t];
+    }
+  }
 }
 
 // ---- whole-K gate/up of passes of 33 to 128 rows --------------------------------------------------------------------------------

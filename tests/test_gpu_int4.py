@@ -82,7 +82,7 @@ def test_int4_rejects_what_it_cannot_run():
 def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers, bits):
     """Five sequences, 30 rows in the verify pass; the pending token of the fourth (rows 18..23) has NaN or infinities for an embedding.  The
     others, rows 2..7 (16 rows beside them, sums of x in the same matrix instruction) among them, keep their bits.  The small model takes
-    the kernels that hold the activations in LDS for O and down, the large one for the LM head; the rest stream them."""
+    the kernels that hold the activations in LDS for O and down; the rest stream them."""
     s = synth.SHAPES[shape_name].twin(n_layers)
     par, rk = synth.TREES["chain5"]
     W = dict(synth.iter_weights(s, 57, synth.device_fmt(s)))
@@ -114,9 +114,9 @@ def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers, bits):
 
 
 def test_int4_rows_of_an_earlier_pass_cost_a_later_one_nothing():
-    """The 4-bit LM head holds the activations in LDS and goes over its groups again where a row is NaN.  A pass of 30 rows with NaN in rows
+    """The 4-bit LM head goes over its groups again where a row is NaN.  A pass of 30 rows with NaN in rows
     18..23 leaves them in the buffer; the six-row passes behind it (one sequence, clean) take the time that they took before.  Their
-    launches repeat within a few per cent; a second run over the groups doubles them (31 us, 64 while such rows were still staged)."""
+    launches repeat within a few per cent; a second run over the groups doubles them (31 us, 64 while the LM head held the activations in LDS and such rows were still staged)."""
     s = synth.SHAPES["llama2-7b"].twin(1)
     par, rk = synth.TREES["chain5"]
     W = dict(synth.iter_weights(s, 57, synth.device_fmt(s)))
