@@ -117,8 +117,8 @@ int eagle_accept(eagle_ctx *ctx, int32_t *out_tokens, int32_t *out_len, int32_t 
 
 /* eagle_accept for callers that cannot allocate or hand over scratch memory (code that must not call hipMalloc: tight
  * serving loops, harnesses that forbid it): the same kernels, but their scratch -- the two fp32 [n_active, vocab]
- * probability vectors of Alg. 1 (vocabularies of at most 32768 entries keep them in registers), or the per-node arg-max
- * array of the greedy walk -- lives in a 4 MiB array that is part of the library's device code instead of in the context's
+ * probability vectors of Alg. 1 (vocabularies of at most 32768 entries keep them in registers), and the nodes'
+ * outcomes -- lives in a 4 MiB array that is part of the library's device code instead of in the context's
  * workspace.  Inputs (the verified logits, the tree) and outputs are those of eagle_accept.  Limit, whatever the
  * vocabulary: non-greedy, n_active * vocab <= 524288 (16 slots at vocab 32000); greedy always fits.  EAGLE_EINVAL beyond
  * that, before anything is launched.  The call allocates nothing.  Every context on one GPU shares that GPU's array (it
