@@ -291,6 +291,13 @@ __global__ __launch_bounds__(256) void k_pack_weight(const SrcT* __restrict__ sr
 struct Q4Format { uint32_t keep, bias; float offset; };        // bits of the codes, what they are or-ed into, what that adds to a code's value
 constexpr int Q4_ROT_LARGE_M = 3;                               // the packing that k_gemm_pf_q4 and k_group_sums are built for
 __host__ __device__ constexpr Q4Format q4_format(int rot) { return rot ? Q4Format{0x00780078u, 0x41804180u, 24.0f} : Q4Format{0x000F000Fu, 0x43004300u, 136.0f}; }
+// An instruction reads one scalar register or constant at most: with `bias` in a vector register the mask and the bias are one instruction
+// (v_and_or_b32), with both constants scalar two; seven instead of eleven instructions for the eight codes.  7B in 4 bits, us a launch before / after: QKV 15.75 / 15.55, gate/up
+// 19.9 / 19.5, down 13.9 / 13.7, LM head of a draft level 21.3 / 20.5, prompt of 512 tokens 18.3 / 17.9 ms; the same bits.
+__device__ __forceinline__ Q4Format q4_pin(Q4Format f) {
+  asm volatile("" : "+s"(f.keep), "+v"(f.bias));
+  return f;
+}
 __device__ __forceinline__ u32x4 q4_expand(uint32_t wd, const Q4Format& f) {
   u32x4 v;
   v.x = (wd & f.keep) | f.bias;
@@ -738,6 +745,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][t][r] = 0.f;
   u32x4 fb[2][NXP * 2], cd[2][RBW];
+  const Q4Format fmt = q4_pin(q4_format(Q4_ROT_LARGE_M));
   auto frags = [&](const u32x4* slot, int b) {
 #pragma unroll
     for (int q = 0; q < NXP; ++q)
@@ -754,7 +762,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_pf_q4(const u32x4* __restrict__
 #pragma unroll
     for (int j = 0; j < RBW; ++j) {
       const uint32_t wd = cd[(i >> 2) & 1][j][i & 3];
-      av[j] = q4_expand(wd, q4_format(Q4_ROT_LARGE_M));
+      av[j] = q4_expand(wd, fmt);
     }
 #pragma unroll
     for (int q = 0; q < NXP; ++q)

@@ -604,9 +604,10 @@ __device__ __forceinline__ float q4_row_sums(const u32x4& ones, int lane, F&& fe
 // slice starts at group g0 of the matrix).  With a quarter of the weight bytes the activation fragments are what a CU
 // fetches most of, so here they are fetched ONCE per work-group (into LDS) and every wave reads them from there.
 template <int NXP, int NR, bool APART>
-__device__ __forceinline__ bool k2_stream_q4(const Q4Format fmt, const u32x4* __restrict__ xs, int kt, int g0, int gb, int ge, const u32x4* const* wq,
+__device__ __forceinline__ bool k2_stream_q4(const Q4Format format, const u32x4* __restrict__ xs, int kt, int g0, int gb, int ge, const u32x4* const* wq,
                                              const u32x4* const* sq, f32x16* acc, int lane) {
   if (ge <= gb) return false;
+  const Q4Format fmt = q4_pin(format);
   const int glast = ge - 1;
   u32x4 a4[2][NR];
   const u32x4 ones = q4_ones(lane);
@@ -953,8 +954,9 @@ __device__ __forceinline__ void fk_stream_dispatch(int nr, const bf16_t* XF, int
 // the same k-steps, and the group is folded into the result as  acc += s_row * (partial - 24 * sum_x)  in fp32.
 // Activation fragments are streamed from L2 as in fk_stream, one group (8 k-steps) ahead; the next group's codes are
 // requested as soon as a super-tile's registers are free.
-template <int NXP, int NR, bool APART, class F>
-__device__ __forceinline__ bool fk_stream_q4(const Q4Format fmt, const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs /*codes from block 0 on*/,
+// PIN: q4_pin.  (Not for QKV with three row blocks, which has no register left for it: four spilled.)
+template <int NXP, int NR, bool APART, bool PIN, class F>
+__device__ __forceinline__ bool fk_stream_q4(const Q4Format format, const bf16_t* __restrict__ XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs /*codes from block 0 on*/,
                                              const u32x4* const* sq /*scales of (block j, group 0), this lane's half*/, int NG,
                                              f32x16* acc, int lane, F&& behind) {
   if (ge <= gb) {
@@ -979,6 +981,7 @@ __device__ __forceinline__ bool fk_stream_q4(const Q4Format fmt, const bf16_t* _
     for (int q = 0; q < NXP; ++q) tb[i][q] = Q4_XLOAD(q, 8 * gb + i, 0u);
   __builtin_amdgcn_sched_barrier(0);
   behind();
+  const Q4Format fmt = PIN ? q4_pin(format) : format;
   fk_zero<NR>(acc);
   // The last group, a copy of the loop's body, requests nothing: clamped to itself it fetched its activations and codes twice, one
   // group in four at K = 4096 and the only one in O's slices.  (Three row blocks, for which a second body spills, request out of range.)
@@ -1058,13 +1061,13 @@ __device__ __forceinline__ bool fk_stream_q4(const Q4Format fmt, const bf16_t* _
 #undef Q4_WLOAD
   return acc[0][0] != acc[0][0];                               // (a sum of NaN in any group stays in every result of its row)
 }
-template <int NXP, int NR, class F>
+template <int NXP, int NR, bool PIN = true, class F>
 __device__ __forceinline__ void fk_stream_q4_dispatch(int nr, const Q4Format fmt, const bf16_t* XF, int KS, int M, int gb, int ge, __amdgpu_buffer_rsrc_t wrs,
                                                       const u32x4* const* sq, int NG, f32x16* acc, int lane, F&& behind) {
   if (nr == NR) {
-    if (!__any(fk_stream_q4<NXP, NR, false>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, behind))) return;
-    fk_stream_q4<NXP, NR, true>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, [] {});
-  } else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1>(nr, fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, behind);
+    if (!__any(fk_stream_q4<NXP, NR, false, PIN>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, behind))) return;
+    fk_stream_q4<NXP, NR, true, PIN>(fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, [] {});
+  } else if constexpr (NR > 1) fk_stream_q4_dispatch<NXP, NR - 1, PIN>(nr, fmt, XF, KS, M, gb, ge, wrs, sq, NG, acc, lane, behind);
   else behind();
 }
 // The codes of nr row blocks from rb0 on.
@@ -1133,7 +1136,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
     const u32x4* sq[NRMAX];
 #pragma unroll
     for (int j = 0; j < NRMAX; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(rb0 + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
-    fk_stream_q4_dispatch<NXP, NRMAX>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(W, rb0, nr, g.KS), sq, g.NG, acc, lane, early);
+    fk_stream_q4_dispatch<NXP, NRMAX, !(NRMAX == 3 && EPI == EPI_QKV)>(nr, g.q4, g.XF, g.KS, g.M, gb, ge, q4_codes(W, rb0, nr, g.KS), sq, g.NG, acc, lane, early);
     if constexpr (LATE) early_issue(e.in_scale.ssq, e.facts, el);
   } else {
     const int kb = (unsigned)w * (unsigned)g.KS / 8u, ke = (unsigned)(w + 1) * (unsigned)g.KS / 8u;
