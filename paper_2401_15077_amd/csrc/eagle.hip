@@ -99,7 +99,7 @@ struct eagle_ctx {
   // which turns a difference of 1e-7 between two orders of an fp32 sum into one of 2^-9 in about one entry of a thousand (1e-4
   // relative on the logits of a 32-layer model): neither order is the more accurate one, but results would move visibly from
   // release to release.  Kept: K slices by plan_slices, prompt passes of 512 rows (32 with 4-bit weights, whose codes then expand
-  // around 128 in every pass), the norm's sums of k_resnorm_fixed, k_gemm up to 64 rows.  (How many rows a pass has decides the
+  // around 128 in every pass), the norm's sums of k_resnorm_fixed, k_gemm up to 64 rows, the K slices of 4-bit LM heads.  (How many rows a pass has decides the
   // order here as everywhere on the general path.)  Mixtures of experts are not held to it: grouping the rows by expert has
   // reordered their sums already, and a router near-tie moves their logits as much as the rounding of the cache does.
   bool fixed_sums = false;
@@ -1100,10 +1100,8 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
       return EAGLE_OK;
     }
   }
-  if (w.q4 && g.epi == EPI_LOGITS && w.NRB > 3 * c->n_cu && w.NRB <= LQ4_BLOCKS * c->n_cu) {
-    // the LM head: one round of whole-K work-groups of four row blocks.  (Fewer blocks fit three a work-group, below; more, vocabularies beyond
-    // 32768, would be a second round.)  us a launch at the ends of the range, staged split-K / this, 26 rows, K 4096: 24608 tokens 25 / 20, 32768 29 / 21
-    constexpr size_t lds = (size_t)4 * LQ4_BLOCKS * 4096;
+  if (w.q4 && g.epi == EPI_LOGITS && plan_is_logits_q4(w.NRB, c->n_cu, p, c->fixed_sums)) {   // the LM head: one round of whole-K work-groups of four row blocks
+    constexpr size_t lds = (size_t)LQ4_PARTS * LQ4_BLOCKS * 4096;
     g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;
     const Share sh = share_of(w.NRB, c->n_cu);
@@ -1118,7 +1116,7 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
     return EAGLE_OK;
   }
   if (w.q4 && c->q4_staged && (g.epi == EPI_RESID || (w.NRB + 2) / 3 > c->n_cu)) {   // (or too many row blocks for one round of whole-K work-groups: larger LM heads)
-    // 4-bit weights, LM heads of more than 32768 tokens (and narrow matrices the streamed split-K plan cannot take): split-K with the activation
+    // 4-bit weights, LM heads that k2_logits_q4 does not take (and narrow matrices the streamed split-K plan cannot take): split-K with the activation
     // slice staged in LDS.  With a quarter of the weight bytes the activation fragments are most of what a CU fetches;
     // staged, a work-group fetches its K slice of them once.  (Measured at d = 4096: O 12.0 us against 14.6 whole-K, down
     // 24.5 against 29.0; the wide matrices are faster whole-K: QKV 20.2 against 27.3, measured

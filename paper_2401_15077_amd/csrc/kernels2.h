@@ -1251,11 +1251,10 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
 // trace, 30.8 / 22.8), 5120 35 / 27 and 40 / 33, 8192 66 / 44 and 76 / 53, 256 8.6 / 5.4; 24608 tokens of 4096 25 / 20.  Four waves of
 // four blocks each (360 registers): 23.7 for 22.8.  Bound: instructions (expanding codes and folding groups beside the MFMAs) and 32 KB of codes
 // in flight a CU; the codes' 65 MB take 11 us at 6 TB/s.
-constexpr int LQ4_BLOCKS = 4;
 __global__ __launch_bounds__(V2_THREADS) void k2_logits_q4(Gemm2 g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ float sh_small[16 * 32];
-  float* red = (float*)smem;                                    // [4 K parts][LQ4_BLOCKS][16][64]
+  float* red = (float*)smem;                                    // [LQ4_PARTS][LQ4_BLOCKS][16][64]
   pin_args(g);
   const int lane = threadIdx.x & 63, w = wave_id();
   const uint32_t NRB = g.NRB;
@@ -1268,7 +1267,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_logits_q4(Gemm2 g) {
     early_issue(g.in_scale.ssq, g.facts, el);
   };
   f32x16 acc[2];
-  const int gb = (unsigned)part * (unsigned)g.NG / 4u, ge = (unsigned)(part + 1) * (unsigned)g.NG / 4u;
+  const int gb = (unsigned)part * (unsigned)g.NG / LQ4_PARTS, ge = (unsigned)(part + 1) * (unsigned)g.NG / LQ4_PARTS;
   const u32x4* sq[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) sq[j] = (const u32x4*)g.SC + (size_t)min(first + j, g.NRB - 1) * (size_t)g.NG * 4 + 2 * (lane >> 5);
@@ -1288,7 +1287,7 @@ __global__ __launch_bounds__(V2_THREADS) void k2_logits_q4(Gemm2 g) {
     const int j = it >> 3, qd = it & 7;
     const int n = (rb0 + j) * 32 + 4 * qd;
     if (dst < 0 || n >= nend) continue;
-    const f32x4 v = fk_sum4<4>(red, LQ4_BLOCKS, j, qd, m) * rs;
+    const f32x4 v = fk_sum4<LQ4_PARTS>(red, LQ4_BLOCKS, j, qd, m) * rs;
     if (vec && n + 4 <= nend) *(f32x4*)(e.logits + dst + n) = v;
     else {
 #pragma unroll

@@ -251,6 +251,15 @@ static inline Plan2 plan2(int NRB, int KS, int NXP, int NWP, int n_cu, bool q4 =
   return p;
 }
 
+// LM heads of 4-bit models that run over all of K in work-groups of four row blocks, K in four parts (k2_logits_q4): one round of them.  (Fewer blocks fit
+// three a work-group of k2_gemm_fk; more, vocabularies beyond 32768, would be a second round.)  us a launch at the ends of the range, split-K in
+// LDS / this, 26 rows, K 4096: 24608 tokens 25 / 20, 32768 29 / 21.  Where sums keep their order (fixed_sums) only if `staged`, the split-K plan, cuts K into the
+// same four parts and adds them in the same order: K of 3200 to 4096.  (The others, a launch: K 5120 35 / 27, 8192 66 / 44.)
+constexpr int LQ4_BLOCKS = 4, LQ4_PARTS = 4;
+static inline bool plan_is_logits_q4(int NRB, int n_cu, const Plan2& staged, bool fixed_sums) {
+  return NRB > 3 * n_cu && NRB <= LQ4_BLOCKS * n_cu && (!fixed_sums || (staged.S == LQ4_PARTS && staged.kparts == 1));
+}
+
 // Split-K plan of a matrix with streamed activations; S = 0 where the fetch model prices the LDS-staged kernel (plan2) lower.
 static inline PlanXK plan_streamed(int NRB, int KS, int NXP, int NWP, int n_cu, size_t pt_floats, bool q4 = false) {
   const Plan2 p = plan2(NRB, KS, NXP, NWP, n_cu, q4);

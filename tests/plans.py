@@ -39,6 +39,11 @@ int shim_shares(uint32_t units, uint32_t n, uint32_t* o) {
   for (uint32_t i = 0; i <= n; ++i) o[i] = share_begin(i, units, s.a, s.b);
   return s.b == SHARE_IN_TURN;
 }
+void shim_staged(int NRB, int KS, int planes, int n_cu, int q4, int* o) {
+  const Plan2 p = plan2(NRB, KS, planes, 1, n_cu, q4 != 0);
+  o[0] = p.S; o[1] = p.kparts;
+}
+int shim_logits_q4(int NRB, int KS, int n_cu, int fixed) { return plan_is_logits_q4(NRB, n_cu, plan2(NRB, KS, 2, 1, n_cu, true), fixed != 0); }
 int shim_attn_splits(int fixed, int tokens, int units, int n_cu) { return plan_attn_splits(fixed != 0, tokens, units, n_cu); }
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
@@ -94,6 +99,16 @@ class Plans:
     def attn_splits(self, fixed, tokens, units, n_cu=256):
         """Work-groups that share the keys of `units` (head, sequence, row block) triples"""
         return self.lib.shim_attn_splits(fixed, tokens, units, n_cu)
+
+    def staged_q4(self, NRB, KS, n_cu=256):
+        """(K slices, parts of K in a work-group) of the split-K kernel that holds the activations in LDS, 4-bit weights"""
+        o = (ctypes.c_int * 2)()
+        self.lib.shim_staged(NRB, KS, 2, n_cu, 1, o)
+        return tuple(o)
+
+    def logits_q4(self, NRB, KS, fixed=False, n_cu=256):
+        """Whether a 4-bit LM head of NRB row blocks runs over all of K in a work-group of four (k2_logits_q4)"""
+        return bool(self.lib.shim_logits_q4(NRB, KS, n_cu, fixed))
 
     def whole_k(self, NRB, KS, planes, n_cu=256):
         return bool(self.lib.shim_whole_k(NRB, KS, planes, n_cu))

@@ -9,6 +9,7 @@ import pytest
 import paper_2401_15077_amd as pkg
 import synth
 from oracle.int4_weights import dequantize, quantize
+from plans import Plans
 
 pytestmark = pytest.mark.gpu
 
@@ -38,3 +39,30 @@ def test_logits_of_every_row(vocab, d):
         err = np.abs(got - x @ Wq.T)
         assert (err <= bound).all() and err.max() < 2e-3 * np.abs(got).max(), (b, err.max(), (err / bound).max())
     eng.close()
+
+
+@pytest.mark.parametrize("d,slices", [(4096, 4), (4224, 5)])
+def test_bf16_cache_keeps_the_order_of_sums(d, slices, tmp_path):
+    """With a bf16 cache the order of sums depends on no choice of kernel: 32000 tokens and 32800 of which the first 32000 are the same (one row
+    block more than k2_logits_q4 takes: the split-K kernel, with the K slices that it always had) give the same bits for those."""
+    plans = Plans(str(tmp_path))
+    assert plans.staged_q4(1000, d // 16) == plans.staged_q4(1025, d // 16) == (slices, 1) and not plans.logits_q4(1025, d // 16)
+    s = replace(synth.SHAPES["mini-gqa"], name=f"q4-bf16-d{d}", n_layers=1, d_model=d, n_heads=4, n_kv_heads=2, d_ffn=128, vocab=32800)
+    par, rk = synth.TREES["T26"]
+    print(s.name, flush=True)
+    W = synth.make_weights(s, 73, synth.device_fmt(s))
+    W["lm_head"][32000:] = 0                                     # (logits of zero: never chosen)
+    got = []
+    for vocab in (32800, 32000):
+        eng = pkg.Eagle(replace(s, vocab=vocab), par, rk, max_seq=96, weight_bits=4, kv_dtype="bf16")
+        eng.load_weights({k: np.ascontiguousarray(w[:vocab]) if k in ("embed", "lm_head") else w for k, w in W.items()})
+        first = eng.prefill(0, synth.prompt(73, 29, 32000))
+        out = [eng.get_buffer(pkg.BUF_VANILLA_LOGITS)[:32000]]
+        tree = eng.draft_tree()[0]
+        eng.verify()
+        out += [eng.get_buffer(pkg.BUF_DRAFT_LOGITS)[0, :32000], eng.get_buffer(pkg.BUF_LOGITS)[:, :32000]]
+        got.append((first, list(tree), out))
+        eng.close()
+    assert got[0][:2] == got[1][:2]
+    for a, b in zip(got[0][2], got[1][2]):
+        assert np.array_equal(a, b), np.abs(a - b).max()

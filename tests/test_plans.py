@@ -243,3 +243,14 @@ def test_shares_cover_all_units_and_differ_by_one(plans, units, n, in_turn):
     assert min(sizes) >= units // n and max(sizes) <= -(-units // n)
     if in_turn:
         assert begin == [i * units // n for i in range(n + 1)]
+
+
+def test_4bit_lm_heads_over_all_of_k(plans):
+    """Four row blocks a CU and no more; where sums keep their order, only with the split-K kernel's own parts of K (four slices)."""
+    for KS in (8, 128, 256, 264, 320, 512):
+        assert [NRB for NRB in range(700, 1100) if plans.logits_q4(NRB, KS)] == list(range(769, 1025)), KS
+    for KS in range(8, 1025, 8):
+        for NRB in (769, 1000, 1024):
+            assert plans.logits_q4(NRB, KS, fixed=True) == (plans.staged_q4(NRB, KS) == (4, 1)), (NRB, KS)
+    assert plans.logits_q4(1000, 256, fixed=True)                # d 4096
+    assert not any(plans.logits_q4(1000, KS, fixed=True) for KS in (128, 264, 320, 512))   # 2048, 4224, 5120, 8192
