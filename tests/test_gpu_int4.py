@@ -2,6 +2,8 @@
 the bf16 weights it is given as it loads them; the oracle is the plain oracle run on the independently quantised and
 de-quantised weights (oracle/int4_weights.py).  Same lock-step protocol and the same tolerance as the bf16 path: the
 codes and scales are exact on both sides, so the only difference left is the order of fp32 additions."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -78,12 +80,12 @@ def test_int4_rejects_what_it_cannot_run():
 
 
 @pytest.mark.parametrize("bits", [0x7FC0, 0x7F80, 0xFF80], ids=["nan", "inf", "minus-inf"])
-@pytest.mark.parametrize("shape_name, n_layers", [("mini-gqa", 2), ("llama2-7b", 1)])
-def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers, bits):
+@pytest.mark.parametrize("shape_name, n_layers, vocab", [("mini-gqa", 2, 512), ("llama2-7b", 1, 32000), ("llama2-7b", 1, 33000)])
+def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers, vocab, bits):
     """Five sequences, 30 rows in the verify pass; the pending token of the fourth (rows 18..23) has NaN or infinities for an embedding.  The
-    others, rows 2..7 (16 rows beside them, sums of x in the same matrix instruction) among them, keep their bits.  The small model takes
-    the kernels that hold the activations in LDS for O and down; the rest stream them."""
-    s = synth.SHAPES[shape_name].twin(n_layers)
+    others, rows 2..7 (16 rows beside them, sums of x in the same matrix instruction) among them, keep their bits.  The kernel that holds the
+    activations in LDS serves O and down of the small model and the LM head of 33000 tokens; the rest stream them."""
+    s = replace(synth.SHAPES[shape_name].twin(n_layers), vocab=vocab)
     par, rk = synth.TREES["chain5"]
     W = dict(synth.iter_weights(s, 57, synth.device_fmt(s)))
     eng = pkg.Eagle(s, par, rk, max_batch=5, max_seq=96, weight_bits=4)
@@ -113,11 +115,13 @@ def test_int4_rows_with_nan_touch_no_other_row(shape_name, n_layers, bits):
     eng.close()
 
 
-def test_int4_rows_of_an_earlier_pass_cost_a_later_one_nothing():
-    """The 4-bit LM head goes over its groups again where a row is NaN.  A pass of 30 rows with NaN in rows
-    18..23 leaves them in the buffer; the six-row passes behind it (one sequence, clean) take the time that they took before.  Their
-    launches repeat within a few per cent; a second run over the groups doubles them (31 us, 64 while the LM head held the activations in LDS and such rows were still staged)."""
-    s = synth.SHAPES["llama2-7b"].twin(1)
+@pytest.mark.parametrize("vocab, kernel", [(32000, "k2_logits_q4"), (33000, "k2_gemm<4-bit weights>")])
+def test_int4_rows_of_an_earlier_pass_cost_a_later_one_nothing(vocab, kernel):
+    """The 4-bit LM head goes over its groups again where a row is NaN.  A pass of 30 rows with NaN in rows 18..23 leaves them in the buffer;
+    the six-row passes behind it (one sequence, clean) take the time that they took before.  The kernel of 32000 tokens does not fetch rows
+    beyond the pass; the one of 33000, which holds the activations in LDS, stages zeros for them.  Launches repeat within a few per cent; a
+    second run over the groups doubles them (the latter, 32000 tokens, 31 us, 64 while such rows were staged as they were)."""
+    s = replace(synth.SHAPES["llama2-7b"].twin(1), vocab=vocab)
     par, rk = synth.TREES["chain5"]
     W = dict(synth.iter_weights(s, 57, synth.device_fmt(s)))
     eng = pkg.Eagle(s, par, rk, max_batch=5, max_seq=160, weight_bits=4)
@@ -131,6 +135,7 @@ def test_int4_rows_of_an_earlier_pass_cost_a_later_one_nothing():
         for _ in range(8):
             eng.step()
         row = [k for k in eng.get_kernel_stats(1) if k["name"] == "lm_head"][0]
+        assert row["kernel"] == kernel
         eng.set_profiling(0)
         return 1e3 * row["ms"] / row["launches"]
 
