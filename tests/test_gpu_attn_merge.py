@@ -18,7 +18,9 @@ BOUND, STEP = {"fp32": 4 * 2.0 ** -13, "bf16": 1e-3}, 2e-2
 # heads, key heads, head dimension, tree, prompt, cache, splits of a verify pass
 CASES = [(4, 2, 128, "T26", 150, "fp32", 2), (4, 4, 128, "T26", 520, "fp32", 5), (4, 2, 128, "T10", 840, "fp32", 8), (4, 2, 128, "T15", 970, "fp32", 9),
          (4, 1, 128, "root", 400, "fp32", 4), (4, 2, 64, "T26", 1500, "fp32", 13), (4, 4, 64, "T10", 300, "fp32", 3), (8, 2, 32, "T26", 1960, "fp32", 16),
-         (8, 2, 32, "chain5", 700, "bf16", 6), (4, 2, 128, "T26", 2300, "bf16", 16), (4, 2, 64, "T8", 860, "bf16", 8)]
+         (8, 2, 32, "chain5", 700, "bf16", 6), (4, 2, 128, "T26", 2300, "bf16", 16), (4, 2, 64, "T8", 860, "bf16", 8),
+         (4, 2, 128, "T26", 100, "fp32", 1), (4, 2, 128, "T26", 790, "fp32", 7), (4, 4, 64, "T26", 1200, "fp32", 10), (4, 2, 128, "T15", 1330, "fp32", 11),
+         (8, 2, 32, "T26", 1450, "bf16", 12), (4, 2, 64, "T10", 1710, "fp32", 14), (4, 1, 128, "T26", 1840, "fp32", 15)]
 
 
 def _shape(heads, kv_heads, dh):
@@ -29,7 +31,7 @@ def test_cases_have_the_splits_that_they_name(tmp_path):
     plans = Plans(str(tmp_path))
     for heads, _, _, tree, prompt, kv, splits in CASES:
         assert plans.attn_splits(kv == "bf16", prompt + 64, heads) == splits, (tree, prompt)
-    assert {c[-1] for c in CASES} >= {2, 3, 4, 5, 6, 8, 9, 13, 16}
+    assert {c[-1] for c in CASES} == set(range(1, 17))
 
 
 @pytest.mark.gpu
