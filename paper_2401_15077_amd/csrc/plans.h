@@ -22,7 +22,8 @@ static inline uint32_t magic_of(uint32_t n) { return (uint32_t)((1ull << 31) / n
 static inline bool magic_holds(uint64_t x_max, uint32_t n) { return n > 0 && x_max * n < (1ull << 31); }
 constexpr uint32_t div_magic(uint32_t x, uint32_t magic) { return (uint32_t)((uint64_t)(2 * x) * magic >> 32); }
 // Where share i of `units` in n shares begins: floor(i * units / n), longer and shorter shares in turn (7B, us with the longer ones in front: LM
-// head 46.0, gate/up 32.8; in turn 45.1 and 32.5); beyond the magic's range (vocabularies of 90000 and more) the longer ones in front.
+// head 46.0, gate/up 32.8; in turn 45.1 and 32.5); beyond the magic's range the longer ones in front: LM heads of more than 3248 row blocks, 103936
+// tokens, on a quarter as many work-groups.
 constexpr uint32_t SHARE_IN_TURN = 0xFFFFFFFFu;
 struct Share { uint32_t a, b; };
 static inline Share share_of(uint32_t units, uint32_t n) {

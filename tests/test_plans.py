@@ -234,7 +234,7 @@ def test_divisions_by_a_multiplication_are_exact(plans):
 
 
 @pytest.mark.parametrize("units,n,in_turn", [(688, 256, True), (768, 256, True), (1000, 256, True), (1792, 448, True), (8, 8, True), (32, 32, True), (1, 1, True), (257, 256, True),
-                                             (4000, 1000, False), (8016, 2004, False), (3001, 751, True), (5, 256, True)])
+                                             (4000, 1000, False), (8016, 2004, False), (3001, 751, True), (3248, 812, True), (3249, 813, False), (5, 256, True)])
 def test_shares_cover_all_units_and_differ_by_one(plans, units, n, in_turn):
     begin, got = plans.shares(units, n)
     assert got == in_turn
