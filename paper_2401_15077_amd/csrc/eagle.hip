@@ -83,9 +83,6 @@ struct eagle_ctx {
   char* ws; size_t ws_bytes, zero_end;
   bool f32, kv_f32, q4 = false;      // q4: weight matrices stored in 4 bits
   bool q4_staged = true;
-  // 4-bit weights: epilogue classes (1 << epi) that take the streamed split-K kernel.  Measured at d = 4096, 26 rows (us, streamed
-  // split-K / LDS-staged split-K, whose 128 KB slice limit forces 11 slices at K = 11008 / whole-K): O 10.5 / 12.0 / 14.6, down
-  // 16.4 / 24.5 / 29.0, FC (4 rows) 12.9 / 17.3 / 18.5; QKV 20.6 streamed, 18.5 whole-K: the residual epilogue only.
   int NWP, NXP, elt, kv_elt;         // weight planes, activation planes, bytes per weight / per KV element
   TreeDev tree_h; TreeDev* tree_d;
   int M, D, Mmax, max_level_rows;
@@ -1089,6 +1086,8 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   const double bytes = w.bytes(c->elt) * experts;
   hipError_t e;
   if (w.q4 && g.epi == EPI_RESID) {
+    // the streamed split-K kernel.  d = 4096, 26 rows, us: streamed split-K / split-K in LDS, whose 128 KB slice limit forces 11 slices at
+    // K = 11008 / whole-K: O 10.5 / 12.0 / 14.6, down 16.4 / 24.5 / 29.0, FC (4 rows) 12.9 / 17.3 / 18.5; but QKV 20.6 streamed, 18.5 whole-K.
     const PlanXK px = plan_xk_q4(w.NRB, w.NG, c->NXP, c->n_cu, (size_t)w.Npad * 32, c->pt2_floats);
     if (px.S > 0) {
       g.S = px.S; g.groups = px.groups; g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
@@ -1118,9 +1117,8 @@ static int gemm2(eagle_ctx* c, const PackedW& w, const bf16_t* XF, Gemm2& g, int
   if (w.q4 && c->q4_staged && (g.epi == EPI_RESID || (w.NRB + 2) / 3 > c->n_cu)) {   // (or too many row blocks for one round of whole-K work-groups: larger LM heads)
     // 4-bit weights, LM heads that k2_logits_q4 does not take (and narrow matrices the streamed split-K plan cannot take): split-K with the activation
     // slice staged in LDS.  With a quarter of the weight bytes the activation fragments are most of what a CU fetches;
-    // staged, a work-group fetches its K slice of them once.  (Measured at d = 4096: O 12.0 us against 14.6 whole-K, down
-    // 24.5 against 29.0; the wide matrices are faster whole-K: QKV 20.2 against 27.3, measured
-    // before, since their epilogues would run on 64 CUs only.)
+    // staged, a work-group fetches its K slice of them once.  (The wide matrices are faster whole-K, us at d = 4096: QKV 20.2
+    // against 27.3, since their epilogues would run on 64 CUs only.)
     g.SC = w.sc; g.NG = w.NG; g.q4 = q4_format(c->q4_rot);
     g.trace = nullptr;
     switch (p.RW) {

@@ -1998,7 +1998,7 @@ __global__ __launch_bounds__(1024) void k_commit(int M, int D1, Pass pass /*cach
     auto row_at = [&](int i) {
       const int pos = base + i, k = (pos >> kv.page_shift) - p0;
       const int phys = k == 0 ? page[0] : k == 1 ? page[1] : page[2];
-      return (u32x4*)(cache + ((((size_t)phys * kv.n_kv_heads + kvh) << kv.page_shift) + (pos & mask) << dh_shift));
+      return (u32x4*)(cache + (((((size_t)phys * kv.n_kv_heads + kvh) << kv.page_shift) + (pos & mask)) << dh_shift));
     };
     for (int i0 = first; i0 < len; i0 += 4) {
       u32x4 v[4];

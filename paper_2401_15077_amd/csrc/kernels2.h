@@ -16,13 +16,10 @@
 #define V2_THREADS 512
 
 // Data that one work-group writes and another reads INSIDE one kernel (split-K partials, attention partials) goes
-// through agent-scope relaxed atomics: such stores are written through to the device-coherent level and such
+// through agent-scope accesses: such stores are written through to the device-coherent level and such
 // loads never hit a stale line of another XCD's L2, so no cache write-back / invalidate is needed around the
 // arrival counter -- a work-group-scope fence (a wait for the stores to be acknowledged) is enough.
-__device__ inline void coh_store(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float coh_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// 16-byte agent-scope accesses: buffer instructions carry the scope bit (aux 16 = sc1); byte offsets below 2 GiB.
+// Buffer instructions carry the scope bit (aux 16 = sc1); byte offsets below 2 GiB.
 __device__ inline __amdgpu_buffer_rsrc_t coh_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7FFFFFFF, 0x00020000);
 }
@@ -104,7 +101,7 @@ __device__ inline float early_ssq(const RowScale& rs, EarlyLoads& e) {
   }
   return a;
 }
-// 1/rms of row m from the classes that block_rstd_park left in tmp[16][32], a barrier before.
+// The classes' sums left in tmp[16][32] and, a barrier later, 1/rms of row m from them.
 __device__ __forceinline__ void block_rstd_park(const RowScale& rs, float part, float* tmp) {
   if (rs.groups > 0) tmp[threadIdx.x] = part;
 }
@@ -326,12 +323,7 @@ __device__ inline void epilogue_qkv(const Gemm2& g, int n0, int n1, const float*
   }
 }
 
-// A wave owns chunks of 8 output rows (n), a lane four of them: lanes 0..31 the first four of tokens 0..31, lanes 32..63 the other
-// four; residual, bias, gain and the partials come as 16-byte loads, all in flight together.  (A lane per chunk and token, row by
-// row, used half of the threads and touched 64 lines with each of its 16 four-byte accesses.)  A token's squares are added
-// chunk by chunk in row order, chunks c, c + 16, ... in one chain: the lower lanes begin a chunk's part, the upper ones go on.
-// EXPERTS: the partials of every expert in `used` (g.S slices each), added per row in expert order with the routing weights, as one
-// launch per expert behind the other would.
+// What a lane of the residual epilogue adds and multiplies in the chunk of 8 output rows from n8 on.
 struct ResidItem { f32x4 h, bias, gain; };
 __device__ __forceinline__ ResidItem resid_item(const Gemm2& g, int n8, bool on) {
   const int m = threadIdx.x & 31, n = n8 + 4 * ((threadIdx.x >> 5) & 1);
@@ -342,6 +334,12 @@ __device__ __forceinline__ ResidItem resid_item(const Gemm2& g, int n8, bool on)
   r.gain = on && g.gain_next ? *(const f32x4*)(g.gain_next + n) : zero;
   return r;
 }
+// A wave owns chunks of 8 output rows (n), a lane four of them: lanes 0..31 the first four of tokens 0..31, lanes 32..63 the other
+// four; residual, bias, gain and the partials come as 16-byte loads, all in flight together.  (A lane per chunk and token, row by
+// row, used half of the threads and touched 64 lines with each of its 16 four-byte accesses.)  A token's squares are added
+// chunk by chunk in row order, chunks c, c + 16, ... in one chain: the lower lanes begin a chunk's part, the upper ones go on.
+// EXPERTS: the partials of every expert in `used` (g.S slices each), added per row in expert order with the routing weights, as one
+// launch per expert behind the other would.
 // The items of the first ITEMS chunks of a wave (c = w, w + 8, ...) come with the call; ITEMS = 0: none, and any number of chunks.
 template <int NXP, bool EXPERTS = false, int ITEMS = 0>
 __device__ inline void epilogue_resid(const Gemm2& g, int grp, int n0, int n1, float* sh /*>= 16*32 floats*/, const ResidItem* ri = nullptr, unsigned long long used = 1) {
