@@ -1367,9 +1367,11 @@ extern "C" int eagle_prefill(eagle_ctx* c, int32_t seq, const int32_t* prompt, i
     const bool last = start + cn == n;
     c->last_off = (cn - 1) / c->pf_window * c->pf_window; c->last_rows = cn - c->last_off;
     Pass pt{PASS_PREFILL_T, cn, 1, seq, 0, start, cn};
-    // Short passes take the fused kernels (not mixtures, and not where sums keep the order of the general path).  A prompt of 2 / 22 / 32 tokens,
+    // Short passes take the fused kernels (not where sums keep the order of the general path, and not mixtures, below).  A prompt of 2 / 22 / 32 tokens,
     // us, general / fused: 7B widths, 16 layers 2243 / 1636, 2301 / 1758, 2339 / 1838; 13B, 8 layers 1675 / 1337, 1711 / 1429, 1746 / 1494; 70B, 4
     // layers 2092 / 1723, 2108 / 1839, 2117 / 1914; tiny fp32 191 / 145, 205 / 142, 207 / 148.  (Two such passes for 33 rows would be 1.6 times the general one.)
+    // Mixtures gain or lose with their widths and stay on the general path, which groups the rows by expert: Mixtral widths, 6 layers, 2742 / 1785, 4273 / 3797,
+    // 4285 / 4033; eight experts at d 2176, ffn 4160, 4 layers, 771 / 618, 975 / 1052, 980 / 1130; four at d 256 224 / 215, 232 / 229, 232 / 230.
     const bool fast = cn <= 32 && (c->q4 || (!c->fixed_sums && g.n_experts == 0));
     if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, last)
                    : target_forward(c, pt, start + cn, cn, last, c->vanilla_logits, 1, 1))) return rc;
@@ -1628,6 +1630,7 @@ extern "C" int eagle_accept_static(eagle_ctx* c, int32_t* out_tokens, int32_t* o
   const eagle_config& g = c->cfg;
   const size_t B = (size_t)c->n_active;
   const size_t vec = (B * g.vocab * 4 + 255) & ~(size_t)255;                  // one fp32 [n_active][vocab] array
+  // (one limit for every vocabulary, though those up to 32768 no longer use the vectors: what a call accepts does not hang on the kernel that serves it)
   const size_t need = std::max(B * c->M * sizeof(int2), g.temperature > 0.f ? 2 * vec : 0);
   if (need > EAGLE_STATIC_SCRATCH_BYTES)
     return fail(EAGLE_EINVAL, "eagle_accept_static: %zu active slots x vocab %d need %zu bytes of scratch, the static array holds %u", B, g.vocab, need, EAGLE_STATIC_SCRATCH_BYTES);

@@ -1245,9 +1245,9 @@ __global__ __launch_bounds__(V2_THREADS) void k2_gemm_fk(Gemm2 g) {
 // Up to four row blocks a work-group, their sums scaled into logits in place: more than three blocks do not fit k2_gemm_fk's waves, so the
 // LM head ran split over K with the activations in LDS (k2_gemm), and every K slice wrote and read back its sums of the whole vocabulary.
 // Here wave w takes blocks 2 (w % 2) and on over K part w / 2, two waves a SIMD; the two waves of a part ask for the same activations one
-// after the other.  us a launch, k2_gemm / here, 32000 tokens, 26 rows and 1 to 4: 4096 columns 28 / 20.4 and 33 / 25.4 (a request's mean, in its
-// trace, 30.8 / 22.8), 5120 35 / 27 and 40 / 33, 8192 66 / 44 and 76 / 53, 256 8.6 / 5.4; 24608 tokens of 4096 25 / 20.  Four waves of
-// four blocks each (360 registers): 23.7 for 22.8.  Bound: instructions (expanding codes and folding groups beside the MFMAs) and 32 KB of codes
+// after the other.  us a launch, k2_gemm / here, 32000 tokens, 26 rows and 1 to 4: 4096 columns 32 / 24.1 and 26.6 / 18.2, 5120 38 / 28.8 and 32 /
+// 21.4, 8192 80 / 50 and 64 / 43, 2048 20 / 15.4 and 16.8 / 12, 256 10.8 / 7.8 and 8.0 / 5.3.  Four waves of four blocks each (360 registers), a request's
+// mean: 23.7 for 22.8.  Bound: instructions (expanding codes and folding groups beside the MFMAs) and 32 KB of codes
 // in flight a CU; the codes' 65 MB take 11 us at 6 TB/s.
 __global__ __launch_bounds__(V2_THREADS) void k2_logits_q4(Gemm2 g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];

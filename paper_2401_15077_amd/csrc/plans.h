@@ -31,7 +31,10 @@ static inline Share share_of(uint32_t units, uint32_t n) {
 }
 constexpr uint32_t share_begin(uint32_t i, uint32_t units, uint32_t a, uint32_t b) { return b == SHARE_IN_TURN ? div_magic(i * units, a) : i * a + (i < b ? i : b); }
 
-// Work-groups that share a row's vocabulary in the choice of its children: about 2048 tokens each, at most EXPAND_PARTS_MAX.
+// Work-groups that share a row's vocabulary in the choice of its children: 2048 tokens each, what a work-group takes in one round, at most
+// EXPAND_PARTS_MAX of them.  Smaller parts cost the exchange (2 us) where one part would do, larger ones a round each.  us a launch (root with four
+// children, greedy / with noise), parts of 1024, 2048, 4096: 2048 tokens 6.4 / 7.5, 4.3 / 6.2, 4.3 / 6.5; 4096 6.3 / 7.9, 6.2 / 7.3, 6.7 / 9.2; 8192 6.4 / 8.2, 6.4 / 7.6, 8.4 / 11.1;
+// 32000 (16 parts, 16, 8) 6.4 / 8.1, 6.4 / 7.9, 8.9 / 11.6; beyond 32768 more rounds of 16 parts: 65536 9.3 / 12.0, 128256 14.5 / 19.3.
 constexpr int EXPAND_PARTS_MAX = 16;
 static inline int plan_expand_parts(int vocab) { return std::max(1, std::min(EXPAND_PARTS_MAX, (vocab + 2047) / 2048)); }
 
@@ -253,9 +256,11 @@ static inline Plan2 plan2(int NRB, int KS, int NXP, int NWP, int n_cu, bool q4 =
 }
 
 // LM heads of 4-bit models that run over all of K in work-groups of four row blocks, K in four parts (k2_logits_q4): one round of them.  (Fewer blocks fit
-// three a work-group of k2_gemm_fk; more, vocabularies beyond 32768, would be a second round.)  us a launch at the ends of the range, split-K in
-// LDS / this, 26 rows, K 4096: 24608 tokens 25 / 20, 32768 29 / 21.  Where sums keep their order (fixed_sums) only if `staged`, the split-K plan, cuts K into the
-// same four parts and adds them in the same order: K of 3200 to 4096.  (The others, a launch: K 5120 35 / 27, 8192 66 / 44.)
+// three a work-group of k2_gemm_fk.  More are a second round, which is dearer at first: 26 rows, K 4096, us a launch, split-K in LDS / this in several
+// rounds: 32769 tokens 35 / 39, 40000 37 / 40, 49152 43 / 41, 65536 72 / 46, 128256 123 / 102; K 8192 87 / 86, 128 / 99 at 65536, 264 / 190 at 128256;
+// K 1024 17 / 17, 20 / 19, 30 / 32.  The largest vocabularies stay as they are, with that to gain.)  us a launch at the ends of the range, split-K in LDS / this,
+// K 4096: 26 rows, 24608 tokens 29 / 23, 32768 32.5 / 24.5; 1 to 4 rows 24 / 17.5 and 27 / 19.  Where sums keep their order (fixed_sums) only if `staged`, the split-K plan, cuts K into the
+// same four parts and adds them in the same order: K of 3200 to 4096.  (The others, 26 rows: K 2048 20 / 15.5, 5120 38 / 29, 8192 80 / 50.)
 constexpr int LQ4_BLOCKS = 4, LQ4_PARTS = 4;
 static inline bool plan_is_logits_q4(int NRB, int n_cu, const Plan2& staged, bool fixed_sums) {
   return NRB > 3 * n_cu && NRB <= LQ4_BLOCKS * n_cu && (!fixed_sums || (staged.S == LQ4_PARTS && staged.kparts == 1));

@@ -142,8 +142,8 @@ def test_literal_head_recipe_lockstep(shape_name, n_layers, key):
 # ----------------------------------------------------------------------------- vocabularies beyond 32768 entries
 @pytest.mark.parametrize("temperature", [0.0, 1.0])
 def test_vocab_beyond_32768_lockstep(temperature):
-    """40000-entry vocabulary on the tiny widths: the child-selection kernel's large-vocabulary branch (per-thread
-    sorted top-k lists), greedy and Gumbel top-k."""
+    """40000-entry vocabulary on the tiny widths: child selection in several rounds of a row's parts and acceptance over vectors in
+    memory, greedy and Gumbel top-k."""
     s = synth.SHAPES["tiny-v40k"]
     par, rk = synth.TREES["T15"]
     eng = pkg.Eagle(s, par, rk, max_seq=160, temperature=temperature, seed=31)

@@ -1,5 +1,5 @@
-"""Child selection and acceptance at the edges of their vocabulary ranges (a thread of the kernels owns every 1024th entry, at most 32 of
-them in registers): the fp32 oracle's own logits, and integer logits full of ties."""
+"""Child selection and acceptance at the edges of their vocabulary ranges (child selection: parts of 2048 entries, several rounds of sixteen beyond
+32768; acceptance: a thread owns every 1024th entry, at most 32 of them in registers): the fp32 oracle's own logits, and integer logits full of ties."""
 from dataclasses import replace
 
 import numpy as np
