@@ -1367,12 +1367,7 @@ extern "C" int eagle_prefill(eagle_ctx* c, int32_t seq, const int32_t* prompt, i
     const bool last = start + cn == n;
     c->last_off = (cn - 1) / c->pf_window * c->pf_window; c->last_rows = cn - c->last_off;
     Pass pt{PASS_PREFILL_T, cn, 1, seq, 0, start, cn};
-    // Short passes take the fused kernels (not where sums keep the order of the general path, and not mixtures, below).  A prompt of 2 / 22 / 32 tokens,
-    // us, general / fused: 7B widths, 16 layers 2243 / 1636, 2301 / 1758, 2339 / 1838; 13B, 8 layers 1675 / 1337, 1711 / 1429, 1746 / 1494; 70B, 4
-    // layers 2092 / 1723, 2108 / 1839, 2117 / 1914; tiny fp32 191 / 145, 205 / 142, 207 / 148.  (Two such passes for 33 rows would be 1.6 times the general one.)
-    // Mixtures gain or lose with their widths and stay on the general path, which groups the rows by expert: Mixtral widths, 6 layers, 2742 / 1785, 4273 / 3797,
-    // 4285 / 4033; eight experts at d 2176, ffn 4160, 4 layers, 771 / 618, 975 / 1052, 980 / 1130; four at d 256 224 / 215, 232 / 229, 232 / 230.
-    const bool fast = cn <= 32 && (c->q4 || (!c->fixed_sums && g.n_experts == 0));
+    const bool fast = plan_is_short_prompt(cn, g.d_model, c->NWP + c->NXP, c->f32, c->q4, c->fixed_sums, g.n_experts);
     if ((rc = fast ? target_forward2(c, pt, start + cn, cn, c->vanilla_logits, last)
                    : target_forward(c, pt, start + cn, cn, last, c->vanilla_logits, 1, 1))) return rc;
     if (last) {

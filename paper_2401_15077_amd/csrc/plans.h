@@ -201,7 +201,21 @@ static inline PlanMoe plan_moe(int gu_NRB, int gu_KS, int dn_NRB, int dn_KS, int
 // (store, acknowledge, count, read back: 5 us).  Whole requests, ms, sliced / whole: fp32, d 256 (96 KiB) 8.8 / 7.6; bf16, d 1024 (192)
 // 9.7 / 8.9; d 2048 (384) 12.5 / 12.0; matrices of 528 KiB 8.8 / 9.3.  A matrix that feeds a norm leaves partial sums of squares per
 // work-group, of which there may be PLAN_MAX_NORM_GROUPS, however many CUs the device has.
-static inline bool plan_is_whole_k(int NRB, int KS, int planes, int n_cu) { return NRB <= std::min(n_cu, PLAN_MAX_NORM_GROUPS) && (long)KS * planes <= 400; }
+static inline bool plan_is_short_k(int KS, int planes) { return (long)KS * planes <= 400; }
+static inline bool plan_is_whole_k(int NRB, int KS, int planes, int n_cu) { return NRB <= std::min(n_cu, PLAN_MAX_NORM_GROUPS) && plan_is_short_k(KS, planes); }
+
+// Which prompt passes of at most 32 rows take the fused kernels of the decoding steps: those of dense models, in fp32 only where d_model is a short K, and
+// not where sums keep the order of the general path (fixed_sums); with 4-bit weights all.  (Two such passes for 33 rows would be 1.6 times the general one.)
+// A prompt of 2 / 22 / 32 tokens, us, general / fused: 7B widths, 16 layers 2243 / 1636, 2301 / 1758, 2339 / 1838; 13B, 8 layers 1675 / 1337, 1711 / 1429, 1746 /
+// 1494; 70B, 4 layers 2092 / 1723, 2108 / 1839, 2117 / 1914; tiny fp32 191 / 145, 205 / 142, 207 / 148.
+// fp32, four layers, general over fused for 1 to 32 rows: d 64 to 768 1.17 to 1.47, 1024 1.11 to 1.19 (attention of 4 d 1.02 to 1.06, ffn of 16 d 1.04 to 1.07, of 32 d 0.97 to 1.00).  Beyond, where
+// the fused products are k2_gemm's with three planes of weights, neither is ahead: d 1088 to 1280 1.02 to 1.09, 1408 0.97, 1536 to 1792 1.02 to 1.06, 1984 and 2048
+// 0.92, 2304 and 2560 1.04, 3072 0.99, 3584 and 4096 0.95, 5120 0.85, and with longer ffn 0.92 to 0.98 from d 1280 on.
+// Mixtures gain or lose with their widths and stay on the general path, which groups the rows by expert: 2 / 22 / 32 tokens, Mixtral widths, 6 layers, 2742 / 1785,
+// 4273 / 3797, 4285 / 4033; eight experts at d 2176, ffn 4160, 4 layers, 771 / 618, 975 / 1052, 980 / 1130; four at d 256 224 / 215, 232 / 229, 232 / 230.
+static inline bool plan_is_short_prompt(int rows, int d, int planes, bool f32, bool q4, bool fixed_sums, int experts) {
+  return rows <= 32 && (q4 || (!fixed_sums && experts == 0 && (!f32 || plan_is_short_k(d / 16, planes))));
+}
 
 // Work split of the split-K kernel with streamed activations: S slices x groups of at most 4 row blocks, chosen by a
 // fetch model in KiB per work-group (weights + the live part of the X slice + twice the partials the last work-group

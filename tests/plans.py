@@ -44,6 +44,9 @@ void shim_staged(int NRB, int KS, int planes, int n_cu, int q4, int* o) {
   o[0] = p.S; o[1] = p.kparts;
 }
 int shim_logits_q4(int NRB, int KS, int n_cu, int fixed) { return plan_is_logits_q4(NRB, n_cu, plan2(NRB, KS, 2, 1, n_cu, true), fixed != 0); }
+int shim_short_prompt(int rows, int d, int f32, int q4, int fixed, int experts) {
+  return plan_is_short_prompt(rows, d, f32 ? 6 : 3, f32 != 0, q4 != 0, fixed != 0, experts);
+}
 int shim_attn_splits(int fixed, int tokens, int units, int n_cu) { return plan_attn_splits(fixed != 0, tokens, units, n_cu); }
 int shim_prompt_attn(int rows, int heads, int n_cu) { return plan_is_prompt_attn(rows, heads, n_cu); }
 int shim_q4_x_span(int planes, int KS) { return q4_x_span(planes, KS); }
@@ -99,6 +102,10 @@ class Plans:
     def attn_splits(self, fixed, tokens, units, n_cu=256):
         """Work-groups that share the keys of `units` (head, sequence, row block) triples"""
         return self.lib.shim_attn_splits(fixed, tokens, units, n_cu)
+
+    def short_prompt(self, s, rows, kv="fp32", bits=16):
+        """Whether a prompt pass of `rows` rows takes the fused kernels of the decoding steps"""
+        return bool(self.lib.shim_short_prompt(rows, s.d_model, s.dtype == "fp32", bits == 4, kv == "bf16" and s.n_experts == 0, s.n_experts))
 
     def staged_q4(self, NRB, KS, n_cu=256):
         """(K slices, parts of K in a work-group) of the split-K kernel that holds the activations in LDS, 4-bit weights"""

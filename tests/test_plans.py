@@ -254,3 +254,15 @@ def test_4bit_lm_heads_over_all_of_k(plans):
             assert plans.logits_q4(NRB, KS, fixed=True) == (plans.staged_q4(NRB, KS) == (4, 1)), (NRB, KS)
     assert plans.logits_q4(1000, 256, fixed=True)                # d 4096
     assert not any(plans.logits_q4(1000, KS, fixed=True) for KS in (128, 264, 320, 512))   # 2048, 4224, 5120, 8192
+
+
+def test_prompts_of_at_most_32_rows_take_the_fused_kernels_where_those_are_ahead(plans):
+    for rows in (1, 2, 31, 32):
+        for d in (64, 1024, 1088, 2048, 2560, 4096, 8192):
+            fp32, bf16 = (replace(synth.SHAPES[base], d_model=d) for base in ("tiny", "llama2-7b"))
+            assert plans.short_prompt(fp32, rows) == (d <= 1024)
+            assert plans.short_prompt(bf16, rows) and plans.short_prompt(bf16, rows, bits=4) and plans.short_prompt(bf16, rows, kv="bf16", bits=4)
+            assert not plans.short_prompt(bf16, rows, kv="bf16") and not plans.short_prompt(fp32, rows, kv="bf16")
+        assert not plans.short_prompt(synth.SHAPES["mixtral-8x7b"], rows) and not plans.short_prompt(synth.SHAPES["mini-moe"], rows)
+    for s in synth.SHAPES.values():
+        assert not plans.short_prompt(s, 33) and not plans.short_prompt(s, 33, bits=4)
