@@ -1664,15 +1664,19 @@ __device__ __forceinline__ void attn_merge_chunk(__amdgpu_buffer_rsrc_t po, __am
     float cmx = mx[i];
 #pragma unroll
     for (int u = 0; u < NS; ++u) cmx = fmaxf(cmx, msv[u]);
-    if constexpr (!FIRST) {
-      const float resc = (mx[i] == -INFINITY) ? 0.f : __expf(mx[i] - cmx);
-      den[i] *= resc;
-      x[i] *= resc;
-    }
+    const float resc = FIRST || mx[i] == -INFINITY ? 0.f : __expf(mx[i] - cmx);
     mx[i] = cmx;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
       const float wv = (msv[u] != -INFINITY) ? __expf(msv[u] - cmx) : 0.f;
+      if (!FIRST && u == 0) {
+        // A fused multiply-add rounds one of its two products by itself; which one is written out.  (Left to the compiler it changed with the code around
+        // it, and with a bf16 cache logits moved by up to 1e-5.)
+        const f32x4 r4 = {resc, resc, resc, resc}, w4 = {wv, wv, wv, wv};
+        den[i] = NS == 1 ? __builtin_fmaf(wv, lsv[u], den[i] * resc) : __builtin_fmaf(den[i], resc, wv * lsv[u]);
+        x[i] = NS == 1 ? __builtin_elementwise_fma(w4, ov[i][u], x[i] * r4) : __builtin_elementwise_fma(x[i], r4, ov[i][u] * w4);
+        continue;
+      }
       den[i] += wv * lsv[u];
       x[i] += wv * ov[i][u];
     }
