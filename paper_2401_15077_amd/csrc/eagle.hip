@@ -96,8 +96,8 @@ struct eagle_ctx {
   // which turns a difference of 1e-7 between two orders of an fp32 sum into one of 2^-9 in about one entry of a thousand (1e-4
   // relative on the logits of a 32-layer model): neither order is the more accurate one, but results would move visibly from
   // release to release.  Kept: K slices by plan_slices, prompt passes of 512 rows (32 with 4-bit weights, whose codes then expand
-  // around 128 in every pass), the norm's sums of k_resnorm_fixed, k_gemm up to 64 rows, the K slices of 4-bit LM heads.  (How many rows a pass has decides the
-  // order here as everywhere on the general path.)  Mixtures of experts are not held to it: grouping the rows by expert has
+  // around 128 in every pass), the norm's sums of k_resnorm_fixed, k_gemm up to 64 rows, the K slices of 4-bit LM heads,
+  // the key splits of attention over few tokens.  (How many rows a pass has decides the order here as everywhere on the general path.)  Mixtures of experts are not held to it: grouping the rows by expert has
   // reordered their sums already, and a router near-tie moves their logits as much as the rounding of the cache does.
   bool fixed_sums = false;
   int q4_rot = Q4_ROT_LARGE_M;       // 4-bit codes: rotation of the packed words (3: they expand to 16 + code, 0: to 128 + code)
