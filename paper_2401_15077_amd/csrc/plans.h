@@ -208,6 +208,7 @@ static inline bool plan_is_whole_k(int NRB, int KS, int planes, int n_cu) { retu
 // not where sums keep the order of the general path (fixed_sums); with 4-bit weights all.  (Two such passes for 33 rows would be 1.6 times the general one.)
 // A prompt of 2 / 22 / 32 tokens, us, general / fused: 7B widths, 16 layers 2243 / 1636, 2301 / 1758, 2339 / 1838; 13B, 8 layers 1675 / 1337, 1711 / 1429, 1746 /
 // 1494; 70B, 4 layers 2092 / 1723, 2108 / 1839, 2117 / 1914; tiny fp32 191 / 145, 205 / 142, 207 / 148.
+// bf16, two layers, 21 shapes with d 64 to 8192 (ffn of 1.5 d to 11 d, attention of d / 4 to 4 d), general over fused for 1 to 32 rows: 1.10 to 1.38.
 // fp32, four layers, general over fused for 1 to 32 rows: d 64 to 768 1.17 to 1.47, 1024 1.11 to 1.19 (attention of 4 d 1.02 to 1.06, ffn of 16 d 1.04 to 1.07, of 32 d 0.97 to 1.00).  Beyond, where
 // the fused products are k2_gemm's with three planes of weights, neither is ahead: d 1088 to 1280 1.02 to 1.09, 1408 0.97, 1536 to 1792 1.02 to 1.06, 1984 and 2048
 // 0.92, 2304 and 2560 1.04, 3072 0.99, 3584 and 4096 0.95, 5120 0.85, and with longer ffn 0.92 to 0.98 from d 1280 on.
